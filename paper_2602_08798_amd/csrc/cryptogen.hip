@@ -42,6 +42,55 @@ static int static_scratch_address(int device, void **out)
     return CG_OK;
 }
 
+// Side streams of the one-call decode step, one pair per GPU for all contexts.  The runtime maps
+// streams onto four hardware queues: with a pair per context, the pairs of the third and later
+// contexts of a process landed on the queue of the caller's own stream and the step's branches ran
+// one after the other (12 heads, 512 tokens, N = 8192, four contexts alive: 0.725 ms a step, against
+// 0.515 with one pair).  The pair is created by a device's first context and destroyed with its
+// last.  Calls of several contexts and threads may share it: every call waits for its own fork
+// event and is joined by its own join events, so sharing only orders the branches of different
+// calls.  A call on a capturing stream must not share (the capture would take in other callers'
+// work) and uses the context's own pair.
+struct SidePair {
+    hipStream_t stream[2];
+    int users;
+};
+static std::mutex g_side_mu;
+static SidePair g_side[kMaxDevices];
+static void destroy_pair(hipStream_t *p)
+{
+    for (int i = 0; i < 2; i++) {
+        if (p[i]) (void)hipStreamDestroy(p[i]);
+        p[i] = nullptr;
+    }
+}
+static bool create_pair(hipStream_t *p)
+{
+    for (int i = 0; i < 2; i++)
+        if (hipStreamCreateWithFlags(&p[i], hipStreamNonBlocking) != hipSuccess) {
+            p[i] = nullptr;
+            destroy_pair(p);
+            return false;
+        }
+    return true;
+}
+static bool side_acquire(int device, hipStream_t *out)
+{
+    if (device < 0 || device >= kMaxDevices) return false;
+    std::lock_guard<std::mutex> g(g_side_mu);
+    SidePair &sp = g_side[device];
+    if (sp.users == 0 && !create_pair(sp.stream)) return false;
+    sp.users++;
+    for (int i = 0; i < 2; i++) out[i] = sp.stream[i];
+    return true;
+}
+static void side_release(int device)
+{
+    std::lock_guard<std::mutex> g(g_side_mu);
+    SidePair &sp = g_side[device];
+    if (--sp.users == 0) destroy_pair(sp.stream);
+}
+
 // ---------------------------------------------------------------------------
 // host integer helpers (set-up only)
 // ---------------------------------------------------------------------------
@@ -126,9 +175,10 @@ struct cg_ctx {
     int elems, elems_fwd; // elements per thread in the inverse / forward transform kernels (8 or 16)
     // workspace limbs (N * 8 bytes) per unit
     int ws_total;
-    // two side streams (default priority) and fork/join events for entry points that run
-    // independent branches side by side
-    hipStream_t side[2];
+    // side streams (default priority) and fork/join events for entry points that run independent
+    // branches side by side: the device's shared pair, and a pair of the context's own for calls
+    // on a capturing stream
+    hipStream_t side[2], side_own[2];
     hipEvent_t ev_fork, ev_join[2];
     // optional per-launch timing with HIP events (benchmark support)
     bool prof_on;
@@ -377,9 +427,9 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         return CG_EHIP;
     }
     bool ok = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;
+    ok = ok && side_acquire(c->device, c->side) && create_pair(c->side_own);
     for (int i = 0; i < 2 && ok; i++)
-        ok = hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) == hipSuccess &&
-             hipEventCreateWithFlags(&c->ev_join[i], hipEventDisableTiming) == hipSuccess;
+        ok = hipEventCreateWithFlags(&c->ev_join[i], hipEventDisableTiming) == hipSuccess;
     if (!ok) {
         cg_destroy(c);
         return CG_EHIP;
@@ -401,10 +451,10 @@ extern "C" int cg_destroy(cg_ctx *c)
     if (!c) return CG_OK;
     (void)hipDeviceSynchronize();
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
-    for (int i = 0; i < 2; i++) {
+    for (int i = 0; i < 2; i++)
         if (c->ev_join[i]) (void)hipEventDestroy(c->ev_join[i]);
-        if (c->side[i]) (void)hipStreamDestroy(c->side[i]);
-    }
+    destroy_pair(c->side_own);
+    if (c->side[0]) side_release(c->device);
     if (c->dc) (void)hipFree(c->dc);
     if (c->tw) (void)hipFree(c->tw);
     if (c->itw) (void)hipFree(c->itw);
@@ -1298,22 +1348,25 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     // n_cts: then the append goes first on the caller's stream; otherwise it is a third branch.
     const bool append_first = tau / ((uint32_t)c->N / d2) < n_cts;
     if (append_first) CG_TRY(append(s));
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    CG_HIP(hipStreamIsCapturing(s, &cap));
+    hipStream_t *side = cap == hipStreamCaptureStatusNone ? c->side : c->side_own;
     CG_HIP(hipEventRecord(c->ev_fork, s));
-    CG_HIP(hipStreamWaitEvent(c->side[0], c->ev_fork, 0));
-    if (!append_first) CG_HIP(hipStreamWaitEvent(c->side[1], c->ev_fork, 0));
+    CG_HIP(hipStreamWaitEvent(side[0], c->ev_fork, 0));
+    if (!append_first) CG_HIP(hipStreamWaitEvent(side[1], c->ev_fork, 0));
     // Branches are always joined, also after a failed launch, so that the caller's stream never
     // runs ahead of work this call started.
     int rc = scores_impl(c, s, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores,
                          fold_w);
-    const int rc1 = context_impl(c, c->side[0], a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block,
+    const int rc1 = context_impl(c, side[0], a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block,
                                  context, ws_context, block_w, sum_first);
     if (rc == CG_OK) rc = rc1;
     if (!append_first) {
-        const int rc2 = append(c->side[1]);
+        const int rc2 = append(side[1]);
         if (rc == CG_OK) rc = rc2;
     }
     for (int i = 0; i < (append_first ? 1 : 2); i++) {
-        CG_HIP(hipEventRecord(c->ev_join[i], c->side[i]));
+        CG_HIP(hipEventRecord(c->ev_join[i], side[i]));
         CG_HIP(hipStreamWaitEvent(s, c->ev_join[i], 0));
     }
     return rc;
@@ -1558,13 +1611,10 @@ extern "C" int cg_prefill_repack(cg_ctx *c, void *stream, const uint64_t *x, uin
     const double LB = (double)limb_bytes(c);
     Bump w = bump(c, ws);
     uint64_t *y = w.take<uint64_t>((size_t)2 * c->k * batch);
-    double *f = w.take<double>((size_t)2 * c->k * batch);
     // y[u] = x[u] * mask0 (keeps slot 0 of every block)
     const size_t rows = (size_t)batch * 2 * c->k;
-    CG_TRY(launch_fwd(c, s, rows, LdRowsU64{x, nullptr, c->k, c->logn}, StF64{f, c->logn}, KID_FWD_ROWS,
-                      LB * 2.0 * rows));
-    CG_TRY(launch_inv(c, s, rows, LdInvMulPlain{f, static_cast<const double *>(mask0), 1, 1 << 30, 0, 0, c->logn},
-                      StInvU64{y, c->logn}, KID_INV_MULPLAIN, LB * (2.0 * rows + c->k)));
+    CG_TRY(launch_mulplain(c, s, rows, x, static_cast<const double *>(mask0), 0, 0, StInvU64{y, c->logn},
+                           LB * (2.0 * rows + c->k)));
     // pairwise tree inside every group of wdt consecutive units: at level l (shift 2^l)
     // y[j 2^(l+1)] += rotate_right(y[j 2^(l+1) + 2^l], 2^l); rotate right by sh = Galois 3^(N/2 - sh)
     for (int l = 0; l < levels; l++) {
