@@ -147,6 +147,14 @@ def to_host(t: torch.Tensor) -> np.ndarray:
     return t.detach().cpu().contiguous().numpy().view(np.uint64)
 
 
+def _raw_stream(index: int) -> int:
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# the same handle without building a Stream object on every call (a microsecond of the smallest calls)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream)
+
+
 class CgError(RuntimeError):
     pass
 
@@ -161,10 +169,13 @@ def _need(t, numel: int, what: str):
         raise CgSizeError(f"{what}: {t.numel()} elements, at least {numel} needed")
 
 
+_DTYPES = frozenset((torch.int64, torch.float64, torch.uint8))
+
+
 def _ptr(t) -> int:
     if t is None:
         return 0
-    assert t.is_cuda and t.is_contiguous() and t.dtype in (torch.int64, torch.float64, torch.uint8)
+    assert t.is_cuda and t.is_contiguous() and t.dtype in _DTYPES
     return t.data_ptr()
 
 
@@ -175,6 +186,7 @@ class Context:
         self.lib = load_library()
         self.params = params
         self.device = torch.device(device)
+        self._device_index = torch.cuda.current_device() if self.device.index is None else self.device.index
         self.n, self.k, self.nsp = params.n, params.k, params.nsp
         self.dnum = params.k // params.alpha
         self.L = self.k + self.nsp
@@ -189,6 +201,9 @@ class Context:
         s = _Sizes()
         self._check(self.lib.dll.cg_get_sizes(self.h, C.byref(s)))
         self.sizes = s
+        self._unit_bytes = int(s.ws_bytes_per_unit)
+        self._ksk_numel = int(s.ksk_bytes) // 8
+        self._tables = {}
         self._ws = None
         self._ws_step = None
 
@@ -209,13 +224,13 @@ class Context:
 
     @property
     def stream(self) -> int:
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return _raw_stream(self._device_index)
 
     def workspace_bytes(self, batch: int) -> int:
         return int(self.lib.dll.cg_workspace_bytes(self.h, batch))
 
     def workspace(self, batch: int) -> torch.Tensor:
-        need = self.workspace_bytes(batch)
+        need = self._unit_bytes * max(1, batch)
         if self._ws is None or self._ws.numel() < need:
             self._ws = None
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
@@ -229,16 +244,44 @@ class Context:
         return max(0, int(count)) * ncomp * self.k * self.n
 
     def _need_key(self, key, what="key"):
-        _need(key, int(self.sizes.ksk_bytes) // 8, what + " (prepared)")
+        if key.numel() < self._ksk_numel:
+            _need(key, self._ksk_numel, what + " (prepared)")
+
+    def _need_keys(self, keys, what="Galois key"):
+        for i, key in enumerate(keys):
+            if key.numel() < self._ksk_numel:
+                self._need_key(key, f"{what} {i}")
+
+    def _prime_table(self, prime_idx):
+        """The prime assignment as a C array.  Row i modulo prime i mod period, as in stacked ring
+        elements, is recognised by one list comparison (which for small integers compares pointers)
+        and its array built once: turning 16384 entries into a C array one by one took longer than
+        their transforms (0.50 ms against 0.48)."""
+        n = len(prime_idx)
+        if type(prime_idx) is list and n:
+            try:
+                period = prime_idx.index(0, 1, self.L + 1)
+            except ValueError:
+                period = n
+            if period <= self.L:
+                got = self._tables.get((period, n))
+                if got is None:
+                    pattern = (list(range(period)) * (-(-n // period)))[:n]
+                    if len(self._tables) >= 64:
+                        self._tables.clear()
+                    got = self._tables[(period, n)] = (pattern, (C.c_uint32 * n)(*pattern))
+                if prime_idx == got[0]:
+                    return got[1]
+        return (C.c_uint32 * n)(*prime_idx)
 
     # ---- entry points (same names as the C ABI, without the cg_ prefix) ----
     def ntt_forward(self, x, prime_idx, out=None, inverse=False):
         out = torch.empty_like(x) if out is None else out
-        _need(x, len(prime_idx) * self.n, "x")
-        _need(out, len(prime_idx) * self.n, "out")
-        idx = (C.c_uint32 * len(prime_idx))(*prime_idx)
+        n = len(prime_idx)
+        _need(x, n * self.n, "x")
+        _need(out, n * self.n, "out")
         f = self.lib.dll.cg_ntt_inverse if inverse else self.lib.dll.cg_ntt_forward
-        self._check(f(self.h, self.stream, _ptr(x), _ptr(out), idx, len(prime_idx)))
+        self._check(f(self.h, self.stream, _ptr(x), _ptr(out), self._prime_table(prime_idx), n))
         return out
 
     def ntt_inverse(self, x, prime_idx, out=None):
@@ -328,8 +371,7 @@ class Context:
         out = self.empty_ct(batch, n_rot) if out is None else out
         _need(in2, self._cts(batch), "in")
         _need(out, self._cts(batch * n_rot), "out")
-        for i, key in enumerate(gks):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(gks)
         if len(gks) != n_rot:
             raise CgSizeError(f"{n_rot} Galois elements but {len(gks)} keys")
         ws = self.workspace(batch * min(n_rot, 128) + batch)
@@ -344,8 +386,7 @@ class Context:
         out = self.empty_ct(batch) if out is None else out
         _need(in2, self._cts(batch), "in")
         _need(out, self._cts(batch), "out")
-        for i, key in enumerate(gks):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(gks)
         if len(gks) != n_rot:
             raise CgSizeError(f"{n_rot} Galois elements but {len(gks)} keys")
         ws = self.workspace(batch)
@@ -406,8 +447,7 @@ class Context:
         _need(cache, ((heads - 1) * stride + n_cts) * per_ct if heads and n_cts else 0, "cache")
         _need(out, self._cts(n_out), "out")
         self._need_key(rlk, "rlk")
-        for i, key in enumerate(keys):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(keys)
 
     def decode_scores(self, q, kcache, heads, n_cts, d2, rlk, gk_fold, out=None, cache_stride_cts=None):
         out = self.empty_ct(heads, n_cts) if out is None else out
@@ -551,8 +591,7 @@ class Context:
         self._need_key(rlk, "rlk")
         self._need_round_keys(0, d2, fold_round_bits, gk_fold_rounds)
         self._need_round_keys(1, d2, block_round_bits, gk_block_rounds)
-        for i, key in enumerate(list(gk_fold_rounds) + list(gk_block_rounds)):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(list(gk_fold_rounds) + list(gk_block_rounds))
         if cache_ext is not None:
             _need(cache_ext, 2 * heads * cache_stride_cts * (int(self.sizes.ct_ext_bytes) // 8), "cache_ext")
         need = int(self.lib.dll.cg_decode_step_workspace_bytes(self.h, heads, n_cts))
@@ -646,8 +685,7 @@ class Context:
         _need(x, self._cts(1), "x")
         _need(diags, max(0, int(units)) * max(0, int(n_diag)) * self.k * self.n, "diags (prepared)")
         _need(out, self._cts(units), "out")
-        for i, key in enumerate(list(gk_shift) + list(gk_block)):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(list(gk_shift) + list(gk_block))
         ws = self.workspace(units + n_diag)
         shift = self._keys(gk_shift) if len(gk_shift) else None
         self._check(self.lib.dll.cg_cpvm(self.h, self.stream, _ptr(x), _ptr(diags), units, n_diag, d2, shift,
@@ -661,8 +699,7 @@ class Context:
         _need(x, self._cts(1), "x")
         _need(diags, max(0, int(units)) * max(0, int(n_diag)) * self.k * self.n, "diags (prepared)")
         _need(out, self._cts(units), "out")
-        for i, key in enumerate(list(gk_copies) + list(gk_block)):
-            self._need_key(key, f"Galois key {i}")
+        self._need_keys(list(gk_copies) + list(gk_block))
         if len(gk_copies) != max(0, int(n_diag) - 1):
             raise CgSizeError(f"{int(n_diag) - 1} copy keys needed, {len(gk_copies)} given")
         self._need_fold_keys(1, d2, block_round_bits, gk_block)

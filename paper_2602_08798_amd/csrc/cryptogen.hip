@@ -893,13 +893,15 @@ static int public_transform(cg_ctx *c, void *stream, const uint64_t *in, uint64_
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The usual pattern -- row i modulo prime i % period, as in stacked ring elements -- needs no
     // table.  Any other assignment is staged through a context-owned device buffer; that copy
-    // is ordered on the caller's stream before the kernel.
+    // is ordered on the caller's stream before the kernel.  The pattern is 0, 1, ... period - 1 and
+    // then equal to itself shifted by a period: one block comparison, whatever the number of rows.
     uint32_t period = 0;
-    for (uint32_t i = 0; i < n_limbs; i++) if (idx[i] >= period) period = idx[i] + 1;
-    bool periodic = true;
-    for (uint32_t i = 0; i < n_limbs && periodic; i++) periodic = idx[i] == i % period;
+    while (period < n_limbs && period < (uint32_t)c->L && idx[period] == period) period++;
+    const bool periodic =
+        period && memcmp(idx, idx + period, (size_t)(n_limbs - period) * sizeof(uint32_t)) == 0;
     const uint32_t *tab = nullptr;
     if (!periodic) {
+        for (uint32_t i = 0; i < n_limbs; i++) CG_REQUIRE(idx[i] < (uint32_t)c->L);
         // the table is copied from the caller's (pageable) host array when the call is made, not when
         // a captured graph replays: refuse that form on a capturing stream
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
