@@ -193,13 +193,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_INV_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_INV_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ntt_inv<ks_sum>", "moddown<sum>",
-    "ntt_inv<tensor_sum>"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -581,6 +581,31 @@ static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
     }
 #undef CG_INV
 }
+// ct x pt of every row of densely packed ciphertexts with plaintext (unit * pstride + pofs).  A whole
+// row per 1024 threads also at N = 8192: the two transforms of a row follow each other without a trip
+// to memory that a second workgroup on the unit could cover.
+template <class ST>
+static int launch_mulplain(cg_ctx *c, hipStream_t s, size_t nwg, const uint64_t *src, const double *plain, int pstride,
+                           int pofs, ST st, double bytes)
+{
+    ProfScope ps(c, s, KID_MULPLAIN, bytes, (double)nwg);
+#define CG_MP(LG, EL)                                                                                        \
+    do {                                                                                                     \
+        const unsigned threads = (1u << LG) / EL;                                                            \
+        const unsigned grid = ntt_grid<ntt_mulplain_kernel<LG, EL, ST>>(c, nwg, (int)threads);               \
+        if (c->dry) return CG_OK;                                                                            \
+        return launch_kernel(ntt_mulplain_kernel<LG, EL, ST>, dim3(grid), dim3(threads), s, src, plain,      \
+                             pstride, pofs, st, (const double *)c->tw, (const double *)c->itw,               \
+                             (const DevConst *)c->dc, (int)nwg);                                             \
+    } while (0)
+    switch (c->logn) {
+    case 12: CG_MP(12, 8);
+    case 13: CG_MP(13, 8);
+    case 14: CG_MP(14, 16);
+    default: return CG_EINVAL;
+    }
+#undef CG_MP
+}
 static unsigned pw_blocks(const cg_ctx *c, size_t rows) { return (unsigned)((rows * c->N + PW_THREADS - 1) / PW_THREADS); }
 #define CG_TRY(expr) do { int rc_ = (expr); if (rc_ != CG_OK) return rc_; } while (0)
 
@@ -889,7 +914,6 @@ static int public_transform(cg_ctx *c, void *stream, const uint64_t *in, uint64_
                             uint32_t n_limbs, bool inverse)
 {
     CG_REQUIRE(c && idx && ptrs_ok({in, out}) && n_limbs >= 1 && n_limbs <= c->tab_cap);
-    for (uint32_t i = 0; i < n_limbs; i++) CG_REQUIRE(idx[i] < (uint32_t)c->L);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The usual pattern -- row i modulo prime i % period, as in stacked ring elements -- needs no
     // table.  Any other assignment is staged through a context-owned device buffer; that copy
@@ -1052,15 +1076,10 @@ extern "C" int cg_mul_plain(cg_ctx *c, void *stream, const uint64_t *in2, const 
 {
     CG_REQUIRE(c && ptrs_ok({in2, plain, out2, ws}) && batch_ok(batch));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    double *f = static_cast<double *>(ws);
     const size_t rows = (size_t)batch * 2 * c->k;
-    const double LB = (double)limb_bytes(c);
-    CG_TRY(launch_fwd(c, s, rows, LdRowsU64{in2, nullptr, c->k, c->logn}, StF64{f, c->logn}, KID_FWD_ROWS,
-                      LB * 2.0 * rows));
-    return launch_inv(c, s, rows,
-                      LdInvMulPlain{f, static_cast<const double *>(plain), 1, 1 << 30, (int)plain_stride, 0, c->logn},
-                      StInvU64{out2, c->logn}, KID_INV_MULPLAIN,
-                      LB * (2.0 * rows + c->k * (plain_stride ? (double)batch : 1.0)));
+    return launch_mulplain(c, s, rows, in2, static_cast<const double *>(plain), (int)plain_stride, 0,
+                           StInvU64{out2, c->logn},
+                           (double)limb_bytes(c) * (2.0 * rows + c->k * (plain_stride ? (double)batch : 1.0)));
 }
 
 extern "C" int cg_kv_append(cg_ctx *c, void *stream, uint64_t *cache, uint32_t cache_stride_cts, uint32_t n_caches,
@@ -1071,16 +1090,12 @@ extern "C" int cg_kv_append(cg_ctx *c, void *stream, uint64_t *cache, uint32_t c
     const uint32_t B = (uint32_t)c->N / d2, ct_idx = tau / B, blk = tau % B;
     CG_REQUIRE(ct_idx < cache_stride_cts);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    double *f = static_cast<double *>(ws);
     const size_t rows = (size_t)n_caches * 2 * c->k;
     const size_t ct2 = (size_t)2 * c->k * c->N;
-    const double LB = (double)limb_bytes(c);
-    CG_TRY(launch_fwd(c, s, rows, LdRowsU64{rows_dev, nullptr, c->k, c->logn}, StF64{f, c->logn}, KID_FWD_ROWS,
-                      LB * 2.0 * rows));
-    return launch_inv(c, s, rows, LdInvMulPlain{f, static_cast<const double *>(masks), 1, 1 << 30, 0, (int)blk, c->logn},
-                      StInvAppend{cache + (size_t)ct_idx * ct2, (size_t)cache_stride_cts * ct2, blk == 0 ? 1 : 0,
-                                  c->logn},
-                      KID_INV_MULPLAIN, LB * ((blk == 0 ? 2.0 : 3.0) * rows + c->k));
+    return launch_mulplain(c, s, rows, rows_dev, static_cast<const double *>(masks), 0, (int)blk,
+                           StInvAppend{cache + (size_t)ct_idx * ct2, (size_t)cache_stride_cts * ct2,
+                                       blk == 0 ? 1 : 0, c->logn},
+                           (double)limb_bytes(c) * ((blk == 0 ? 2.0 : 3.0) * rows + c->k));
 }
 
 static bool pow2_d(const cg_ctx *c, uint32_t d2) { return d2 >= 2 && (d2 & (d2 - 1)) == 0 && d2 <= (uint32_t)c->N / 4; }
@@ -1728,7 +1743,8 @@ static int warm_launch_table(cg_ctx *c)
         CG_TRY(launch_inv(c, s, rows, LdInvU64{u, nullptr, c->k, c->logn}, StInvU64{u, c->logn}, KID_INV_U64, LB));
         const LdInvMulPlain mp{f, f, 1, 1, 0, 0, c->logn};
         CG_TRY(launch_inv(c, s, rows, mp, StInvU64{u, c->logn}, KID_INV_MULPLAIN, LB));
-        CG_TRY(launch_inv(c, s, rows, mp, StInvAppend{u, 0, 1, c->logn}, KID_INV_MULPLAIN, LB));
+        CG_TRY(launch_mulplain(c, s, rows, u, f, 0, 0, StInvU64{u, c->logn}, LB));
+        CG_TRY(launch_mulplain(c, s, rows, u, f, 0, 0, StInvAppend{u, 0, 1, c->logn}, LB));
         CG_TRY(launch_inv(c, s, rows, LdInvPlainSum{f, f, 1, c->logn}, StInvU64{u, c->logn}, KID_INV_MULPLAIN, LB));
     }
     return CG_OK;

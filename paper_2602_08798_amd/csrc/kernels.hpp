@@ -249,6 +249,9 @@ __device__ __forceinline__ void load_row_now(const LD &ld, int wg, int tid, cons
 // ---------------------------------------------------------------------------
 // forward transform
 // ---------------------------------------------------------------------------
+// storers that keep the row in LDS (told the element's number in chunk_elem order, not a row)
+template <class ST> struct st_in_place { static constexpr bool value = false; };
+
 template <int LOGN, int E, int PASS, bool FROM_REGS, class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
                                          const double *__restrict__ tw, const double *twr, double *twr_next,
@@ -316,7 +319,8 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
 #pragma unroll
         for (int it = 0; it < E; it++) {
             const int idx = chunk_elem<E>(tid, it);
-            st.store(dst_limb, idx, lds[pad(idx)], m);
+            if constexpr (st_in_place<ST>::value) st.store(it, idx, lds[pad(idx)], m);
+            else st.store(dst_limb, idx, lds[pad(idx)], m);
         }
     }
 }
@@ -378,6 +382,9 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
 // ---------------------------------------------------------------------------
 // inverse transform (passes in reverse order; N^-1 folded into the last stage)
 // ---------------------------------------------------------------------------
+// storers that add to what the destination holds (fetch() brings it in)
+template <class ST> struct st_adds { static constexpr bool value = false; };
+
 template <int LOGN, int E, int PASS, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
@@ -407,6 +414,19 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
 #pragma unroll
         for (int c = 0; c < (1 << R); c++) v[g][c] = lds[pb + pad(c << L)];
     }
+    // a storer that adds to what is there has it brought in eight elements at a time, the first eight
+    // before the butterflies where registers allow: read one by one between the stores (which might
+    // alias), every element would wait for its own trip to memory
+    constexpr bool adds = last && st_adds<ST>::value;
+    static_assert(!adds || (1 << R) % 8 == 0, "eight elements of a group at a time");
+    uint64_t old[adds ? 8 : 1];
+    auto fetch_old = [&](int g, int c0) {
+        if constexpr (adds) {
+#pragma unroll
+            for (int c = 0; c < 8; c++) old[c] = st.fetch(wg, base[g] + ((c0 + c) << L), C);
+        }
+    };
+    if (E <= 8) fetch_old(0, 0);
 #pragma unroll
     for (int g = 0; g < G; g++) {
         // every pass starts from |x| <= p/2: the sum path doubles per stage
@@ -444,8 +464,10 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
         for (int c = 0; c < (1 << R); c++) {
             // the last pass pairs elements N/2 apart with consecutive lanes on consecutive
             // addresses: it stores straight to global memory
-            if (last) st.store(wg, base[g] + (c << L), v[g][c], m, C);
-            else lds[pb + pad(c << L)] = v[g][c];
+            if (adds && c % 8 == 0 && (E > 8 || g || c)) fetch_old(g, c);
+            if (!last) lds[pb + pad(c << L)] = v[g][c];
+            else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[g][c], old[c % 8], m, C);
+            else st.store(wg, base[g] + (c << L), v[g][c], m, C);
         }
     }
     if constexpr (!last) {
@@ -1113,15 +1135,100 @@ struct StInvAppend {
     uint64_t *cache;        // first target ciphertext (cache 0)
     size_t cache_stride;    // uint64 between consecutive caches' target ciphertexts
     int fresh, logn;
-    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD m, const DevConst *C) const
+    __device__ __forceinline__ uint64_t *at(int wg, int idx, const DevConst *C) const
     {
         const int rows = 2 * C->k, c = wg / rows, row = wg % rows;
-        uint64_t *p = cache + (size_t)c * cache_stride + ((size_t)row << logn) + idx;
-        double r = canon(v, m);
-        if (!fresh) r = addmod_canon(r, u64_to_f64(*p), m);
-        *p = f64_to_u64(r);
+        return cache + (size_t)c * cache_stride + ((size_t)row << logn) + idx;
+    }
+    __device__ __forceinline__ uint64_t fetch(int wg, int idx, const DevConst *C) const
+    {
+        return fresh ? 0 : *at(wg, idx, C);
+    }
+    __device__ __forceinline__ void store(int wg, int idx, double v, uint64_t old, const ModD m, const DevConst *C) const
+    {
+        *at(wg, idx, C) = f64_to_u64(addmod_canon(canon(v, m), u64_to_f64(old), m));
     }
 };
+template <> struct st_adds<StInvAppend> { static constexpr bool value = true; };
+
+// ---------------------------------------------------------------------------
+// ct x pt in one kernel: forward transform of a row, product with the prepared plaintext row, inverse
+// transform, the row staying in LDS throughout.  A row crosses memory once in each direction (plus
+// the plaintext row, which all ciphertexts of a call share or stream), where the transforms as two
+// launches moved it twice and wrote and read the transformed row.
+// ---------------------------------------------------------------------------
+// storer of the forward half: multiplies in place (a thread's own elements of its wave's chunk)
+template <int E, bool PF>
+struct StTimesPlain {
+    double *lds;
+    const double *row;     // plaintext row
+    const double *pl;      // PF: its values at the thread's elements, brought in ahead
+    __device__ __forceinline__ void store(int it, int idx, double v, const ModD m) const
+    {
+        lds[pad(idx)] = mulmod(v, PF ? pl[it] : row[idx], m);
+    }
+};
+template <int E, bool PF> struct st_in_place<StTimesPlain<E, PF>> { static constexpr bool value = true; };
+template <int LOGN, int E, class ST>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__ plain, int pstride, int pofs, ST st,
+                    const double *__restrict__ tw_all, const double *__restrict__ itw_all,
+                    const DevConst *__restrict__ C, int nwg)
+{
+    __shared__ double lds[lds_doubles<LOGN>()];
+    constexpr int T = (1 << LOGN) / E, NP = Plan<LOGN, E>::NP;
+    // the plaintext row and the next row are brought in ahead where there are registers for it
+    constexpr bool PF = prefetch_rows<LOGN, E>();
+    static_assert(NP == 4 || NP == 5, "pass sequence below");
+    const int tid = threadIdx.x, k = C->k;
+    uint64_t raw[E];
+    int wg = blockIdx.x;
+    auto fetch = [&](int w) {
+#pragma unroll
+        for (int it = 0; it < E; it++) raw[it] = src[((size_t)w << LOGN) + tid + it * T];
+    };
+    if constexpr (PF) fetch(wg);
+    for (;;) {
+        const int pr = wg % k;
+        const ModD m = C->mod[pr];
+        const double *tw = tw_all + ((size_t)pr << LOGN), *itw = itw_all + ((size_t)pr << LOGN);
+        const double *prow = plain + ((size_t)((wg / (2 * k)) * pstride + pofs) * k + pr << LOGN);
+        double twa[TWREGS], twb[TWREGS], in[E], pl[PF ? E : 1];
+        load_tw<LOGN, E, 0, true>(tw, tid, twa);
+        if constexpr (PF) {
+#pragma unroll
+            for (int it = 0; it < E; it++) pl[it] = prow[chunk_elem<E>(tid, it)];
+        } else {
+            fetch(wg);
+        }
+#pragma unroll
+        for (int it = 0; it < E; it++) in[it] = u64_to_f64(raw[it]);
+        const StTimesPlain<E, PF> times{lds, prow, pl};
+        fwd_pass<LOGN, E, 0, true>(lds, in, times, tid, tw, twa, twb, m, 0);
+        fwd_pass<LOGN, E, 1, false>(lds, in, times, tid, tw, twb, twa, m, 0);
+        fwd_pass<LOGN, E, 2, false>(lds, in, times, tid, tw, twa, twb, m, 0);
+        fwd_pass<LOGN, E, 3, false>(lds, in, times, tid, tw, twb, twa, m, 0);
+        if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, times, tid, tw, twa, twb, m, 0);
+        load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
+        wave_sync();
+        if constexpr (NP > 4) {
+            inv_pass<LOGN, E, 4>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
+            inv_pass<LOGN, E, 3>(lds, st, wg, tid, itw, twb, twa, m, pr, C);
+        } else {
+            inv_pass<LOGN, E, 3>(lds, st, wg, tid, itw, twa, twa, m, pr, C);
+        }
+        inv_pass<LOGN, E, 2>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
+        inv_pass<LOGN, E, 1>(lds, st, wg, tid, itw, twb, twa, m, pr, C);
+        const int next = wg + (int)gridDim.x;
+        if constexpr (PF) {
+            if (next < nwg) fetch(next);
+        }
+        inv_pass<LOGN, E, 0>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
+        if (next >= nwg) break;
+        wg = next;
+        lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes
+    }
+}
 
 // ---------------------------------------------------------------------------
 // pointwise kernels
