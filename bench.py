@@ -63,10 +63,12 @@ FP64_LANE_INSTR_PER_ITEM = {
     "ntt_inv<tensor_sum> per unit": 168 * 1024,
     "ntt_inv<u64>": 616 * 1024,
     "ntt_inv<mul_plain>": 688 * 1024,
+    "ntt_fwd_inv<mul_plain>": (472 + 624) * 1024,
     "ntt_inv<ks_inner>": 728 * 1024,
-    # summed inner product of n_rot rotations: 560 per thread outside the rotation loop, 200 per rotation
-    "ntt_inv<ks_sum>": 560 * 1024,
-    "ntt_inv<ks_sum> per rotation": 200 * 1024,
+    # summed inner products of n_rot rotations, per ciphertext: the accumulation is in integers, its final
+    # reduction about 18 FP64 instructions per output value
+    "ks_sum": 18 * 2 * 4 * 8192,
+    "ntt_inv<f64>": 560 * 1024,
     "scale": 373 * 3 * 8192,
     "moddown": 320 * 8192,
     # one thread per pair of coefficients and prime: about 100 outside the rotation loop, 10 per rotation
@@ -469,17 +471,14 @@ def main():
         for _ in range(args.steps):
             serial_fn()
         stats = ws.ctx.profile_end()
-        H, C, L2 = ws.heads, ws.n_cts, 2 * (ws.prm.k + ws.prm.nsp)
-        # rotation-rows and rotation-units of the summed kernels, per step
-        rot_rows = sum(H * C * L2 * r for r in ws.round_sizes(0)) + sum(H * L2 * r for r in ws.round_sizes(1))
+        H, C = ws.heads, ws.n_cts
+        # rotation-units of the summed mod-down, per step
         rot_units = sum(H * C * r for r in ws.round_sizes(0)) + sum(H * r for r in ws.round_sizes(1))
         fp64_step = 0.0
         for s in stats:
             sec = s["total_ms"] * 1e-3
             gbs = s["algo_bytes"] / sec / 1e9
             fp64 = s["work_items"] * FP64_LANE_INSTR_PER_ITEM.get(s["name"], 0)
-            if s["name"] == "ntt_inv<ks_sum>":
-                fp64 += args.steps * rot_rows * FP64_LANE_INSTR_PER_ITEM["ntt_inv<ks_sum> per rotation"]
             if s["name"] == "ntt_inv<tensor_sum>":     # its rows each take in the n_cts units of a head
                 fp64 += s["work_items"] * C * FP64_LANE_INSTR_PER_ITEM["ntt_inv<tensor_sum> per unit"]
             if s["name"] == "moddown<sum>":

@@ -193,13 +193,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_INV_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
-    "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ntt_inv<ks_sum>", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>"};
+    "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -364,6 +364,10 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         const uint64_t ninv = h_inv(N % p, p);
         H.ninv[r] = h_centred(ninv, p);
         H.itw1_ninv[r] = h_centred(h_mul(h_inv(pw[h_bitrev(1, c->logn)], p), ninv, p), p);
+    }
+    for (int r = 0; r < np; r++) {
+        H.two50[r] = h_centred(h_pow(2, 50, c->pr[r]), c->pr[r]);
+        H.two81[r] = h_centred(h_pow(2, 81, c->pr[r]), c->pr[r]);
     }
     int qi[MAXS], bi[MAXS], all[MAXT], sp[MAXS];
     for (int i = 0; i < c->k; i++) qi[i] = i;
@@ -624,6 +628,41 @@ static unsigned pw_blocks(const cg_ctx *c, size_t rows) { return (unsigned)((row
         CG_TRY(rc_pw_);                                                                                \
     } while (0)
 
+// Summed inner products of a series of rotations.  Ciphertexts per thread: as many as leave every
+// compute unit three workgroups (N = 8192, 7 rotations: 12 ciphertexts 14.5 / 13.6 / 14.3 us at one / two /
+// four per thread, 48: 56 / 44 / 40 us) and no more than a quarter of the last group's places empty
+template <int DNUM>
+static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const HoistTab &T, uint32_t n_rot, double *acc,
+                           uint32_t batch)
+{
+    const size_t per = (size_t)c->L * c->N / PW_THREADS;
+    uint32_t u = 8;
+    auto groups = [&]() { return (batch + u - 1) / u; };
+    while (u > 1 && (per * groups() < 3 * (size_t)c->n_cu || 4 * (size_t)groups() * u > 5 * (size_t)batch)) u /= 2;
+    const dim3 block(PW_THREADS), grid((unsigned)(per * groups()));
+    const DevConst *dc = c->dc;
+    switch (u) {
+    case 8: return launch_kernel(ks_sum_kernel<DNUM, 8>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
+    case 4: return launch_kernel(ks_sum_kernel<DNUM, 4>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
+    case 2: return launch_kernel(ks_sum_kernel<DNUM, 2>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
+    default: return launch_kernel(ks_sum_kernel<DNUM, 1>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
+    }
+}
+static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t *dig, const HoistTab &T, uint32_t n_rot,
+                         double *acc, uint32_t batch)
+{
+    if (c->dry) return CG_OK;
+    ProfScope ps(c, s, KID_KSSUM, bytes, (double)batch);
+    switch (c->dnum) {
+    case 1: return launch_ks_sum_d<1>(c, s, dig, T, n_rot, acc, batch);
+    case 2: return launch_ks_sum_d<2>(c, s, dig, T, n_rot, acc, batch);
+    case 3: return launch_ks_sum_d<3>(c, s, dig, T, n_rot, acc, batch);
+    case 4: return launch_ks_sum_d<4>(c, s, dig, T, n_rot, acc, batch);
+    case 5: return launch_ks_sum_d<5>(c, s, dig, T, n_rot, acc, batch);
+    default: return launch_ks_sum_d<6>(c, s, dig, T, n_rot, acc, batch);
+    }
+}
+
 // mod-down of a summed series of rotations, one output row per workgroup
 static int launch_moddown_sum(cg_ctx *c, hipStream_t s, double bytes, size_t batch, const ModdownArgs &A,
                               const ModdownHoist &H)
@@ -633,12 +672,30 @@ static int launch_moddown_sum(cg_ctx *c, hipStream_t s, double bytes, size_t bat
     const dim3 block(1024);
     const size_t rows = batch * 2 * c->k;
     const DevConst *dc = c->dc;
-    switch (c->logn) {
-    case 12: return launch_kernel(moddown_sum_kernel<12>, dim3((unsigned)(rows * moddown_sum_split<12>())), block, s, A, H, dc);
-    case 13: return launch_kernel(moddown_sum_kernel<13>, dim3((unsigned)(rows * moddown_sum_split<13>())), block, s, A, H, dc);
-    case 14: return launch_kernel(moddown_sum_kernel<14>, dim3((unsigned)(rows * moddown_sum_split<14>())), block, s, A, H, dc);
+#define CG_MDS(LG, SP) \
+    return launch_kernel(moddown_sum_kernel<LG, SP>, dim3((unsigned)(rows * moddown_sum_split<LG>())), block, s, A, H, dc)
+    switch (c->logn * 10 + c->nsp) {
+    case 121: CG_MDS(12, 1);
+    case 122: CG_MDS(12, 2);
+    case 131: CG_MDS(13, 1);
+    case 132: CG_MDS(13, 2);
+    case 141: CG_MDS(14, 1);
+    case 142: CG_MDS(14, 2);
     default: return CG_EINVAL;
     }
+#undef CG_MDS
+}
+// mod-down per pair of coefficients; hoisted: the units are the rotations of a series
+template <bool HOIST>
+static int launch_moddown(cg_ctx *c, hipStream_t s, double bytes, size_t units, const ModdownArgs &A,
+                          const ModdownHoist &H)
+{
+    if (c->dry) return CG_OK;
+    ProfScope ps(c, s, KID_MODDOWN, bytes, (double)units);
+    const dim3 grid(pw_blocks(c, units * 2) / 2), block(PW_THREADS);
+    const DevConst *dc = c->dc;
+    return c->nsp == 1 ? launch_kernel(moddown_kernel<HOIST, 1>, grid, block, s, A, H, dc)
+                       : launch_kernel(moddown_kernel<HOIST, 2>, grid, block, s, A, H, dc);
 }
 
 // Every polynomial named by src -> its transform over the k ciphertext primes and the l auxiliary
@@ -704,13 +761,13 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
 }
 
 // Mod-up of one ring element per unit (src + b*src_stride, Galois map first when galois != 0): the
-// dnum digits extended to the k+nsp primes and transformed, rows dig[b][dnum][k+nsp][N]
+// dnum digits extended to the k+nsp primes and transformed, rows dig[b][dnum][k+nsp][N], canonical
 static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
-                        uint32_t batch, double *dig)
+                        uint32_t batch, uint64_t *dig)
 {
     const size_t nrows = (size_t)batch * c->dnum * c->L;
     const double mbytes = (double)limb_bytes(c) * (c->k + (double)c->dnum * c->L) * batch;
-    const StF64 st{dig, c->logn};
+    const StU64 st{dig, c->logn};
 #define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn}, st, KID_FWD_MODUP, mbytes)
     switch (c->alpha * 2 + (galois ? 1 : 0)) {
     case 2: CG_MODUP(false, 1);
@@ -725,13 +782,13 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 
 // key switch of one ring element per unit (src + b*src_stride), then the final additions
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
-                        const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
+                        const uint64_t *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
                         uint32_t galois_inv, int accumulate, uint32_t batch, void *ws,
                         const uint64_t *acc_add = nullptr, size_t acc_stride = 0)
 {
     if (!acc_add) { acc_add = add; acc_stride = add_stride; }
     Bump w = bump(c, ws);
-    double *dig = w.take<double>((size_t)c->dnum * c->L * batch);
+    uint64_t *dig = w.take<uint64_t>((size_t)c->dnum * c->L * batch);
     double *acc = w.take<double>((size_t)2 * c->L * batch);
     const double LB = (double)limb_bytes(c), B = batch;
     const double dig_rows = (double)c->dnum * c->L;
@@ -754,16 +811,14 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     CG_TRY(rc);
     ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
     const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
-    CG_LAUNCH_PW(KID_MODDOWN, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, B, moddown_kernel<false>,
-                 pw_blocks(c, (size_t)batch * 2) / 2, A, ModdownHoist{}, c->dc);
-    return CG_OK;
+    return launch_moddown<false>(c, s, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, batch, A, ModdownHoist{});
 }
 
 static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *out2, uint32_t batch,
                     void *ws)
 {
     const size_t ct3 = (size_t)3 * c->k * c->N;
-    return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
+    return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const uint64_t *>(rlk), out2,
                         (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws);
 }
 
@@ -784,7 +839,7 @@ static int do_rotate(cg_ctx *c, hipStream_t s, const uint64_t *in2, uint32_t g, 
     const size_t ct2 = (size_t)2 * c->k * c->N;
     if (!in_stride) in_stride = ct2;
     if (!out_stride) out_stride = ct2;
-    return do_keyswitch(c, s, in2 + (size_t)c->k * c->N, in_stride, g, static_cast<const double *>(gk), out2,
+    return do_keyswitch(c, s, in2 + (size_t)c->k * c->N, in_stride, g, static_cast<const uint64_t *>(gk), out2,
                         out_stride, in2, in_stride, inv_mod_pow2(g, 2u * c->N), accumulate, batch, ws, acc_add,
                         acc_stride);
 }
@@ -804,7 +859,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
     const double dig_rows = (double)c->dnum * c->L;
     const uint32_t round_max = n_rot < (uint32_t)MAXROT ? n_rot : (uint32_t)MAXROT;
     Bump w = bump(c, ws);
-    double *dig = w.take<double>((size_t)c->dnum * c->L * batch);
+    uint64_t *dig = w.take<uint64_t>((size_t)c->dnum * c->L * batch);
     double *acc = w.take<double>((size_t)2 * c->L * batch * round_max);
     int rc;
     CG_TRY(launch_modup(c, s, in2 + (size_t)c->k * c->N, in_stride, 0, batch, dig));
@@ -814,7 +869,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
         ModdownHoist H{};
         for (uint32_t i = 0; i < nr; i++) {
             T.g[i] = gs[i0 + i];
-            T.key[i] = static_cast<const double *>(keys[i0 + i]);
+            T.key[i] = static_cast<const uint64_t *>(keys[i0 + i]);
             H.ginv[i] = inv_mod_pow2(gs[i0 + i], 2u * c->N);
         }
         H.rot_batch = (int)batch;
@@ -835,8 +890,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
         CG_TRY(rc);
         // galois != 0 marks the rotation form; the element itself comes from the table
         ModdownArgs A{acc, out2 + (size_t)i0 * ct2, ct2, in2, in_stride, 1u, 0, (int)units, in2, in_stride};
-        CG_LAUNCH_PW(KID_MODDOWN, LB * ((2.0 * c->L + 2.0 * c->k) * units + c->k * B), (double)units,
-                     moddown_kernel<true>, pw_blocks(c, units * 2) / 2, A, H, c->dc);
+        CG_TRY(launch_moddown<true>(c, s, LB * ((2.0 * c->L + 2.0 * c->k) * units + c->k * B), units, A, H));
     }
     return CG_OK;
 }
@@ -854,32 +908,21 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     const double LB = (double)limb_bytes(c), B = batch;
     const double dig_rows = (double)c->dnum * c->L;
     Bump w = bump(c, ws);
-    double *dig = w.take<double>((size_t)c->dnum * c->L * batch);
+    uint64_t *dig = w.take<uint64_t>((size_t)c->dnum * c->L * batch);
     double *acc = w.take<double>((size_t)2 * c->L * batch);
-    int rc;
     CG_TRY(launch_modup(c, s, in2 + (size_t)c->k * c->N, in_stride, 0, batch, dig));
     HoistTab T{};
     ModdownHoist H{};
     for (uint32_t i = 0; i < n_rot; i++) {
         T.g[i] = gs[i];
-        T.key[i] = static_cast<const double *>(keys[i]);
+        T.key[i] = static_cast<const uint64_t *>(keys[i]);
         H.ginv[i] = inv_mod_pow2(gs[i], 2u * c->N);
     }
     H.n_sum = (int)n_rot;
+    const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
+    CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
     const size_t irows = (size_t)batch * 2 * c->L;
-    const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
-    const StInvF64 ist{acc, c->logn};
-#define CG_KSS(D) rc = launch_inv(c, s, irows, LdInvKsInnerSum<D>{dig, T, (int)n_rot, c->logn}, ist, KID_INV_KSSUM, ibytes)
-    switch (c->dnum) {
-    case 1: CG_KSS(1); break;
-    case 2: CG_KSS(2); break;
-    case 3: CG_KSS(3); break;
-    case 4: CG_KSS(4); break;
-    case 5: CG_KSS(5); break;
-    default: CG_KSS(6); break;
-    }
-#undef CG_KSS
-    CG_TRY(rc);
+    CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64, LB * 2.0 * irows));
     ModdownArgs A{acc, out2, out_stride, in2, in_stride, 1u, 1, (int)batch, in2, in_stride};
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
     return launch_moddown_sum(c, s, LB * (2.0 * c->L + 4.0 * c->k) * B, batch, A, H);
@@ -955,7 +998,7 @@ extern "C" int cg_ksk_prepare(cg_ctx *c, void *stream, const uint64_t *raw, void
 {
     CG_REQUIRE(c && ptrs_ok({raw, ksk}));
     return launch_fwd(c, static_cast<hipStream_t>(stream), (size_t)c->dnum * 2 * c->L,
-                      LdRowsU64{raw, nullptr, c->L, c->logn}, StF64Red{static_cast<double *>(ksk), c->logn},
+                      LdRowsU64{raw, nullptr, c->L, c->logn}, StU64{static_cast<uint64_t *>(ksk), c->logn},
                       KID_FWD_ROWS, 4.0 * limb_bytes(c) * c->dnum * c->L);
 }
 
@@ -1726,8 +1769,8 @@ static int warm_launch_table(cg_ctx *c)
     for (uint32_t batch : {1u, 4096u}) {
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0));
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0, 0, 0, nullptr, 1));
-        CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, batch, f));
-        CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, batch, f));
+        CG_TRY(do_keyswitch(c, s, u, 0, 0, u, u, 0, u, 0, 0, 0, batch, f));
+        CG_TRY(do_keyswitch(c, s, u, 0, 3, u, u, 0, u, 0, 3, 1, batch, f));
         {
             const uint32_t gs1[1] = {3};
             const void *const keys1[1] = {f};

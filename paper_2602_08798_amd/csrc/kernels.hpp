@@ -549,47 +549,12 @@ template <class LD> struct inv_wide { static constexpr bool value = false; };
 // ---------------------------------------------------------------------------
 // exact base conversion helpers (per coefficient, registers only)
 // ---------------------------------------------------------------------------
-// x[0..ns) canonical residues -> mixed-radix digits a[0..ns); returns true when
-// CENTRED and the integer exceeds floor(S/2) (its centred representative is x - S).
-template <bool CENTRED>
-__device__ __forceinline__ bool garner(const ConvTab &T, const DevConst *C, const double *x, double *a)
-{
-    a[0] = x[0];
-#pragma unroll
-    for (int j = 1; j < MAXS; j++) {
-        if (j < T.ns) {
-            const ModD mj = C->mod[T.sidx[j]];
-            double v = x[j];
-#pragma unroll
-            for (int i = 0; i < j; i++) v = mulmod(v - a[i], T.inv[i][j], mj);
-            a[j] = canon(v, mj);
-        }
-    }
-    bool gt = false;
-    if (CENTRED) {
-#pragma unroll
-        for (int i = 0; i < MAXS; i++)
-            if (i < T.ns) gt = (a[i] > T.half[i]) || (a[i] == T.half[i] && gt);
-    }
-    return gt;
-}
-// residue of the (optionally negative-shifted) integer modulo target jt; lazy, |.| < 3p
-__device__ __forceinline__ double horner(const ConvTab &T, const DevConst *C, const double *a, int jt,
-                                         bool neg)
-{
-    const ModD mt = C->mod[T.tidx[jt]];
-    double acc = 0.0;
-#pragma unroll
-    for (int i = MAXS - 1; i >= 0; i--) {
-        if (i < T.ns) acc = (i == T.ns - 1) ? a[i] : mulmod(acc, T.s_mod_t[i][jt], mt) + a[i];
-    }
-    if (neg) acc -= T.S_mod_t[jt];
-    return acc;
-}
-
-// compile-time-sized variants (source basis of exactly NS primes): fully unrolled, no guards
+// x[0..NS) canonical residues -> mixed-radix digits a[0..NS); returns true when CENTRED and the integer
+// exceeds floor(S/2) (its centred representative is x - S).  The size of the source basis is a
+// template argument everywhere: with a run-time size every step of these loops is a branch and
+// the scaled configuration's mod-down (two special primes) took four times as long.
 template <int NS, bool CENTRED>
-__device__ __forceinline__ bool garner_t(const ConvTab &T, const DevConst *C, const double (&x)[NS], double (&a)[NS])
+__device__ __forceinline__ bool garner(const ConvTab &T, const DevConst *C, const double (&x)[NS], double (&a)[NS])
 {
     a[0] = x[0];
 #pragma unroll
@@ -607,8 +572,9 @@ __device__ __forceinline__ bool garner_t(const ConvTab &T, const DevConst *C, co
     }
     return gt;
 }
+// residue of the (optionally negative-shifted) integer modulo target jt; lazy, |.| < 3p
 template <int NS>
-__device__ __forceinline__ double horner_t(const ConvTab &T, const DevConst *C, const double (&a)[NS], int jt, bool neg)
+__device__ __forceinline__ double horner(const ConvTab &T, const DevConst *C, const double (&a)[NS], int jt, bool neg)
 {
     const ModD mt = C->mod[T.tidx[jt]];
     double acc = a[NS - 1];
@@ -752,8 +718,8 @@ struct LdMulAux {
         double x[K], dg[K];
 #pragma unroll
         for (int i = 0; i < K; i++) x[i] = u64_to_f64(raw[i]);
-        const bool neg = garner_t<K, true>(C->q2b, C, x, dg);
-        return canon(horner_t<K>(C->q2b, C, dg, wg % C->l, neg), mb);
+        const bool neg = garner<K, true>(C->q2b, C, x, dg);
+        return canon(horner<K>(C->q2b, C, dg, wg % C->l, neg), mb);
     }
 };
 
@@ -793,7 +759,7 @@ struct LdModup {
         const int L = C->L, r = wg % L, j = (wg / L) % C->dnum;
         bool negate = false;
         if (GALOIS) negate = (((uint32_t)idx * galois) & ((2u << logn) - 1)) >= (1u << logn);
-        double x[MAXS], a[MAXS];
+        double x[ALPHA], a[ALPHA];
 #pragma unroll
         for (int s = 0; s < ALPHA; s++) {
             x[s] = u64_to_f64(raw[s]);
@@ -801,8 +767,8 @@ struct LdModup {
         }
         if (ALPHA == 1) return canon(x[0], mr);
         const ConvTab &T_ = C->dig[j];
-        garner<false>(T_, C, x, a);
-        return canon(horner(T_, C, a, r, false), mr);
+        garner<ALPHA, false>(T_, C, x, a);
+        return canon(horner<ALPHA>(T_, C, a, r, false), mr);
     }
 };
 
@@ -851,13 +817,24 @@ struct LdInvU64 {
 struct LdInvTensor;
 template <> struct inv_wide<LdInvTensor> { static constexpr bool value = true; };
 
+// Transformed digits and prepared keys are canonical uint64 residues: one form for the loaders that
+// take them as doubles and for the integer accumulation of ks_sum_kernel.  Two canonical factors
+// give products below 0.875 p, so up to six of them sum to less than 8 p.
+template <int DNUM> __device__ __forceinline__ double inner_product(const uint64_t *raw, const ModD m)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < DNUM; j++) s += mulmod(u64_to_f64(raw[2 * j]), u64_to_f64(raw[2 * j + 1]), m);
+    return s;
+}
+
 // element = sum_j digit_j[b][r] * key[j][c][r] (both in transform order); result row [b][c][r]
 template <int DNUM>
 struct LdInvKsInner {
     static constexpr int kRaw = 2 * DNUM;
     static constexpr bool kPrefetch = false;
-    const double *dig;   // [b][DNUM][L][N] lazy
-    const double *key;   // [DNUM][2][L][N] reduced
+    const uint64_t *dig;   // [b][DNUM][L][N]
+    const uint64_t *key;   // [DNUM][2][L][N]
     int logn;
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return (wg >> 1) % C->L; }
     __device__ __forceinline__ int share(const DevConst *) const { return 2; }
@@ -871,21 +848,13 @@ struct LdInvKsInner {
         const int L = C->L, r = (wg >> 1) % L, c = wg & 1, b = wg / (2 * L);
 #pragma unroll
         for (int j = 0; j < DNUM; j++) {
-            raw[2 * j] = f64_bits(dig[(((size_t)(b * DNUM + j) * L + r) << logn) + idx]);
-            raw[2 * j + 1] = f64_bits(key[(((size_t)(j * 2 + c) * L + r) << logn) + idx]);
+            raw[2 * j] = dig[(((size_t)(b * DNUM + j) * L + r) << logn) + idx];
+            raw[2 * j + 1] = key[(((size_t)(j * 2 + c) * L + r) << logn) + idx];
         }
     }
     __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
     {
-        // digits are lazy (|x| <= 7.5 p), keys reduced: each product is below 1.91 p, so up to four
-        // of them sum to less than 8 p without reducing the digits first
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < DNUM; j++) {
-            const double d = bits_f64(raw[2 * j]);
-            s += mulmod(DNUM <= 4 ? d : red(d, m), bits_f64(raw[2 * j + 1]), m);
-        }
-        return s;
+        return inner_product<DNUM>(raw, m);
     }
 };
 
@@ -895,8 +864,8 @@ struct LdInvKsInner {
 // psi^(2 bitrev(i) + 1), and sigma_g(a) takes there the value of a at psi^((2 bitrev(i) + 1) g).
 constexpr int MAXROT = 128;   // rotations per launch
 struct HoistTab {
-    uint32_t g[MAXROT];            // Galois element of rotation i (inner product), its inverse mod 2N (mod-down)
-    const double *key[MAXROT];     // prepared key of rotation i
+    uint32_t g[MAXROT];            // Galois element of rotation i
+    const uint64_t *key[MAXROT];   // prepared key of rotation i
 };
 // inner product of rotation i of unit b: workgroup -> (unit u = i * batch + b, prime r, component c);
 // element = sum_j digit_j[b][r][pi_g(idx)] * key_i[j][c][r][idx]; result row [u][c][r]
@@ -904,7 +873,7 @@ template <int DNUM>
 struct LdInvKsInnerHoisted {
     static constexpr int kRaw = 2 * DNUM;
     static constexpr bool kPrefetch = false;
-    const double *dig;   // [b][DNUM][L][N] lazy, transform order
+    const uint64_t *dig;   // [b][DNUM][L][N], transform order
     HoistTab T;
     int batch, logn;
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return (wg >> 1) % C->L; }
@@ -920,75 +889,37 @@ struct LdInvKsInnerHoisted {
         const int i = u / batch, b = u - i * batch;
         const uint32_t e = ((2u * (__brev((uint32_t)idx) >> (32 - logn)) + 1u) * T.g[i]) & ((2u << logn) - 1u);
         const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
-        const double *kb = T.key[i];
+        const uint64_t *kb = T.key[i];
 #pragma unroll
         for (int j = 0; j < DNUM; j++) {
-            raw[2 * j] = f64_bits(dig[(((size_t)(b * DNUM + j) * L + r) << logn) + sidx]);
-            raw[2 * j + 1] = f64_bits(kb[(((size_t)(j * 2 + c) * L + r) << logn) + idx]);
+            raw[2 * j] = dig[(((size_t)(b * DNUM + j) * L + r) << logn) + sidx];
+            raw[2 * j + 1] = kb[(((size_t)(j * 2 + c) * L + r) << logn) + idx];
         }
     }
     __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
     {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < DNUM; j++) {
-            const double d = bits_f64(raw[2 * j]);
-            s += mulmod(DNUM <= 4 ? d : red(d, m), bits_f64(raw[2 * j + 1]), m);
-        }
-        return s;
+        return inner_product<DNUM>(raw, m);
     }
 };
 
-// The sum of a series of rotations of one ciphertext, as one key-switch accumulator: workgroup ->
-// (unit b, prime r, component c); element = sum_i sum_j digit_j[b][r][pi_{g_i}(idx)] * key_i[j][c][r][idx];
-// result row [b][c][r].  Summing before the inverse transform and the division by P costs one
-// inverse transform and one mod-down per ciphertext instead of one per rotation.
-template <int DNUM>
-struct LdInvKsInnerSum {
-    static constexpr int kRaw = 2 * DNUM;
-    static constexpr bool kPrefetch = false;
-    const double *dig;   // [b][DNUM][L][N] lazy, transform order
-    HoistTab T;
-    int n_rot, logn;
-    __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return (wg >> 1) % C->L; }
-    __device__ __forceinline__ int share(const DevConst *) const { return 2; }
-    __device__ __forceinline__ int out_row(int wg, const DevConst *C) const
+// rows of doubles (lazy), transformed in place: row w is [unit][component][prime], nprimes of them
+struct LdInvF64 {
+    static constexpr int kRaw = 1;
+    static constexpr bool kPrefetch = true;
+    const double *src;
+    int nprimes, logn;
+    __device__ __forceinline__ int prime(int wg, const DevConst *) const { return wg % nprimes; }
+    __device__ __forceinline__ int share(const DevConst *) const { return 1; }
+    __device__ __forceinline__ int out_row(int wg, const DevConst *) const { return wg; }
+    __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *, uint64_t *raw) const
     {
-        const int L = C->L, r = (wg >> 1) % L, b = wg / (2 * L);
-        return (b * 2 + (wg & 1)) * L + r;
+        raw[0] = f64_bits(src[((size_t)wg << logn) + idx]);
     }
-    __device__ __forceinline__ int rounds() const { return n_rot; }
-    __device__ __forceinline__ void fetch_round(int wg, int idx, int i, const DevConst *C, uint64_t *raw) const
+    __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD, const DevConst *) const
     {
-        const int L = C->L, r = (wg >> 1) % L, c = wg & 1, b = wg / (2 * L);
-        const uint32_t e = ((2u * (__brev((uint32_t)idx) >> (32 - logn)) + 1u) * T.g[i]) & ((2u << logn) - 1u);
-        const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
-        const double *kb = T.key[i];
-#pragma unroll
-        for (int j = 0; j < DNUM; j++) {
-            raw[2 * j] = f64_bits(dig[(((size_t)(b * DNUM + j) * L + r) << logn) + sidx]);
-            raw[2 * j + 1] = f64_bits(kb[(((size_t)(j * 2 + c) * L + r) << logn) + idx]);
-        }
-    }
-    __device__ __forceinline__ void fetch(int, int, const DevConst *, uint64_t *) const {}
-    __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
-    {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < DNUM; j++) {
-            const double d = bits_f64(raw[2 * j]);
-            s += mulmod(DNUM <= 4 ? d : red(d, m), bits_f64(raw[2 * j + 1]), m);
-        }
-        return s;
-    }
-    // one rotation's products are below 1.91 DNUM p; with the running sum reduced to p/2 first the
-    // total stays below 8 p for DNUM <= 3, and for more digits the new term is reduced as well
-    __device__ __forceinline__ double join(double sum, double term, const ModD m) const
-    {
-        return red(sum, m) + (DNUM <= 3 ? term : red(term, m));
+        return bits_f64(raw[0]);
     }
 };
-template <int DNUM> struct ld_rounds<LdInvKsInnerSum<DNUM>> { static constexpr bool value = true; };
 
 // tensor product fused into the load: workgroup -> (unit u, prime r of the k+l, component c in 0..2),
 // the component running fastest so that the three rows reading the same four operand rows are
@@ -1259,19 +1190,19 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int to
     double x[K], dq[K], y[L], db[L];
 #pragma unroll
     for (int i = 0; i < K; i++) x[i] = canon(mulmod(e[i], t, C->mod[i]), C->mod[i]);
-    const bool neg = garner_t<K, true>(C->q2b, C, x, dq);
+    const bool neg = garner<K, true>(C->q2b, C, x, dq);
 #pragma unroll
     for (int j = 0; j < L; j++) {
         const ModD mb = C->mod[K + j];
         const double te = mulmod(e[K + j], t, mb);
-        const double rj = horner_t<K>(C->q2b, C, dq, j, neg);
+        const double rj = horner<K>(C->q2b, C, dq, j, neg);
         y[j] = canon(mulmod(red(te - rj, mb), C->Qinv_b[j], mb), mb);
     }
-    const bool neg2 = garner_t<L, true>(C->b2q, C, y, db);
+    const bool neg2 = garner<L, true>(C->b2q, C, y, db);
     uint64_t *o = out + (((size_t)bc * K) << logn) + n;
 #pragma unroll
     for (int i = 0; i < K; i++) {
-        double v = canon(horner_t<L>(C->b2q, C, db, i, neg2), C->mod[i]);
+        double v = canon(horner<L>(C->b2q, C, db, i, neg2), C->mod[i]);
         if (acc) v = addmod_canon(v, u64_to_f64(o[(size_t)i << logn]), C->mod[i]);
         o[(size_t)i << logn] = f64_to_u64(v);
     }
@@ -1302,13 +1233,13 @@ struct ModdownHoist {
     uint32_t ginv[MAXROT];
     int rot_batch, out_per_b, n_sum;
 };
-template <bool HOIST>
+template <bool HOIST, int NSP>
 __global__ void __launch_bounds__(PW_THREADS)
 moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 {
     // a thread takes two neighbouring coefficients: 16 bytes per row and lane on every read and
     // write that is not a permuted one
-    const int logn = C->logn, N = 1 << logn, k = C->k, nsp = C->nsp, L = C->L;
+    const int logn = C->logn, N = 1 << logn, k = C->k, L = C->L;
     // the N / (2 PW_THREADS) blocks of one (unit, component) run on one XCD: the permuted reads of a
     // c0 row touch all of its cache lines, which that XCD's L2 then fetches once instead of once
     // per XCD
@@ -1326,17 +1257,16 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
         A.galois = H.ginv[i];
     }
     const double *src = A.acc + (((size_t)bc * L) << logn) + n;
-    double xp[2][MAXS], dg[2][MAXS];
+    double xp[2][NSP], dg[2][NSP];
 #pragma unroll
-    for (int s = 0; s < 2; s++)
-        if (s < nsp) {
-            const ModD mp = C->mod[k + s];
-            const double2 x2 = *reinterpret_cast<const double2 *>(src + ((size_t)(k + s) << logn));
-            xp[0][s] = addmod_canon(canon(x2.x, mp), C->halfP[k + s], mp);
-            xp[1][s] = addmod_canon(canon(x2.y, mp), C->halfP[k + s], mp);
-        }
-    garner<false>(C->p2q, C, xp[0], dg[0]);
-    garner<false>(C->p2q, C, xp[1], dg[1]);
+    for (int s = 0; s < NSP; s++) {
+        const ModD mp = C->mod[k + s];
+        const double2 x2 = *reinterpret_cast<const double2 *>(src + ((size_t)(k + s) << logn));
+        xp[0][s] = addmod_canon(canon(x2.x, mp), C->halfP[k + s], mp);
+        xp[1][s] = addmod_canon(canon(x2.y, mp), C->halfP[k + s], mp);
+    }
+    garner<NSP, false>(C->p2q, C, xp[0], dg[0]);
+    garner<NSP, false>(C->p2q, C, xp[1], dg[1]);
     int src_idx[2] = {0, 0};
     bool negate[2] = {false, false};
     if (A.galois) {
@@ -1360,7 +1290,7 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 #pragma unroll
             for (int e2 = 0; e2 < 2; e2++) {
                 const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner(C->p2q, C, dg[e2], i, false);
+                const double ri = horner<NSP>(C->p2q, C, dg[e2], i, false);
                 v[e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
             }
             if (A.add) {
@@ -1400,7 +1330,7 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 // coefficients (and the un-permuted addend) from there.  Base conversion as in moddown_kernel,
 // for the one prime of the row; the special-prime rows are read by the k workgroups of a
 // (ciphertext, component), neighbours on one XCD.
-template <int LOGN>
+template <int LOGN, int NSP>
 __global__ void __launch_bounds__(1024, (LOGN <= 13 ? 8 : 4))
 moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 {
@@ -1409,7 +1339,7 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
     constexpr int N = 1 << LOGN, SPLIT = moddown_sum_split<LOGN>(), ROWP = N / 2048, PAIRS = ROWP / SPLIT;
     static_assert(PAIRS >= 1, "at least one pair of outputs per thread");
     __shared__ double row[N];
-    const int k = C->k, nsp = C->nsp, L = C->L, tid = threadIdx.x;
+    const int k = C->k, L = C->L, tid = threadIdx.x;
     const int blk = xcd_row((int)blockIdx.x, (int)gridDim.x, k * SPLIT);
     const int part = blk % SPLIT, i = (blk / SPLIT) % k, bc = blk / (SPLIT * k), c = bc & 1, b = bc >> 1;
     const ModD mq = C->mod[i];
@@ -1435,14 +1365,13 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
         }
     }
     constexpr int PB = PAIRS < 2 ? PAIRS : 2;
-    double2 xs[PB][2], as[PB];
+    double2 xs[PB][NSP], as[PB];
     auto request = [&](int j0) {
 #pragma unroll
         for (int j = 0; j < PB; j++) {
             const int n = pair_index(j0 + j);
 #pragma unroll
-            for (int s = 0; s < 2; s++)
-                if (s < nsp) xs[j][s] = *reinterpret_cast<const double2 *>(acc + ((size_t)(k + s) << LOGN) + n);
+            for (int s = 0; s < NSP; s++) xs[j][s] = *reinterpret_cast<const double2 *>(acc + ((size_t)(k + s) << LOGN) + n);
             as[j] = *reinterpret_cast<const double2 *>(acc + ((size_t)i << LOGN) + n);
         }
     };
@@ -1453,21 +1382,20 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
         double v[PB][2];
 #pragma unroll
         for (int j = 0; j < PB; j++) {
-            double xp[2][MAXS], dg[2][MAXS];
+            double xp[2][NSP], dg[2][NSP];
 #pragma unroll
-            for (int s = 0; s < 2; s++)
-                if (s < nsp) {
-                    const ModD mp = C->mod[k + s];
-                    xp[0][s] = addmod_canon(canon(xs[j][s].x, mp), C->halfP[k + s], mp);
-                    xp[1][s] = addmod_canon(canon(xs[j][s].y, mp), C->halfP[k + s], mp);
-                }
-            garner<false>(C->p2q, C, xp[0], dg[0]);
-            garner<false>(C->p2q, C, xp[1], dg[1]);
+            for (int s = 0; s < NSP; s++) {
+                const ModD mp = C->mod[k + s];
+                xp[0][s] = addmod_canon(canon(xs[j][s].x, mp), C->halfP[k + s], mp);
+                xp[1][s] = addmod_canon(canon(xs[j][s].y, mp), C->halfP[k + s], mp);
+            }
+            garner<NSP, false>(C->p2q, C, xp[0], dg[0]);
+            garner<NSP, false>(C->p2q, C, xp[1], dg[1]);
             const double ain[2] = {as[j].x, as[j].y};
 #pragma unroll
             for (int e2 = 0; e2 < 2; e2++) {
                 const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner(C->p2q, C, dg[e2], i, false);
+                const double ri = horner<NSP>(C->p2q, C, dg[e2], i, false);
                 v[j][e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
             }
         }
@@ -1491,6 +1419,98 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
             v[j][0] = addmod_canon(v[j][0], own.x, mq);
             v[j][1] = addmod_canon(v[j][1], own.y, mq);
             *reinterpret_cast<ulonglong2 *>(o + n) = make_ulonglong2(f64_to_u64(v[j][0]), f64_to_u64(v[j][1]));
+        }
+    }
+}
+
+// The sum of a series of rotations of every ciphertext of a batch, as key-switch accumulators in
+// transform order: acc[b][c][r] = sum_i sum_j digit_j[b][r][pi_{g_i}(.)] * key_i[j][c][r].  Summing
+// before the inverse transform and the division by P costs one inverse transform and one mod-down
+// per ciphertext instead of one per rotation.
+//
+// A thread owns one evaluation point of U ciphertexts, both components: a digit value is used for both
+// components and a key value for U ciphertexts, (2 + U) / (2 U) operands per product where the inverse
+// transform that formed the sum in its loader (one row per workgroup) read two; what bounds this is
+// the rate at which a compute unit takes operands in from L2.  The products are not reduced one
+// by one: with residues split as 2^25 hi + lo, hi hi', lo lo' and (hi + lo)(hi' + lo') accumulate
+// exactly in 64-bit integers over all terms (at most 128 * 6 of them, each below 2^52) by three
+// 32 x 32 + 64 multiply-adds, which run at the FP64 rate here, and one modular reduction ends it.
+// N = 8192, 7 rotations, with the inverse transforms: 48 ciphertexts 77 -> 54 us, 12: 33 -> 20 us,
+// one: 32 -> 14 us.
+template <int DNUM, int U>
+__global__ void __launch_bounds__(PW_THREADS)
+ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch,
+              const DevConst *__restrict__ C)
+{
+    const int logn = C->logn, L = C->L, chunks = (1 << logn) / PW_THREADS;
+    // Logical order: prime, ciphertext group, chunk of the row (fastest); XCD x takes the x-th eighth of
+    // it.  The gathers of a digit row then stay on one XCD, and an XCD works with the keys of one or
+    // two primes.  (chunks is a multiple of 8.)
+    const int per_xcd = (int)gridDim.x >> 3;
+    const int lg = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    const int groups = (batch + U - 1) / U;
+    const int idx = (lg % chunks) * PW_THREADS + (int)threadIdx.x;
+    const int ug = lg / chunks % groups, r = lg / (chunks * groups);
+    const uint64_t *d[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int b = ug * U + u < batch ? ug * U + u : batch - 1;      // a last group may be short
+        d[u] = dig + (((size_t)b * DNUM * L + r) << logn);
+    }
+    const size_t row = (size_t)L << logn, key_off = ((size_t)r << logn) + idx;
+    const uint32_t e0 = 2u * (__brev((uint32_t)idx) >> (32 - logn)) + 1u;
+    uint64_t lo[U][2], mid[U][2], hi[U][2];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int c = 0; c < 2; c++) lo[u][c] = mid[u][c] = hi[u][c] = 0;
+    for (int i = 0; i < n_rot; i++) {
+        const uint32_t e = (e0 * T.g[i]) & ((2u << logn) - 1u);
+        const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
+        const uint64_t *kb = T.key[i] + key_off;
+        uint64_t kv[DNUM][2], dv[U][DNUM];
+#pragma unroll
+        for (int j = 0; j < DNUM; j++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) kv[j][c] = kb[(size_t)(j * 2 + c) * row];
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int j = 0; j < DNUM; j++) dv[u][j] = d[u][(size_t)j * row + sidx];
+#pragma unroll
+        for (int j = 0; j < DNUM; j++) {
+            uint32_t kl[2], kh[2];
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                kl[c] = (uint32_t)kv[j][c] & 0x1FFFFFFu;
+                kh[c] = (uint32_t)(kv[j][c] >> 25);
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint32_t dl = (uint32_t)dv[u][j] & 0x1FFFFFFu, dh = (uint32_t)(dv[u][j] >> 25);
+#pragma unroll
+                for (int c = 0; c < 2; c++) {
+                    lo[u][c] += (uint64_t)dl * kl[c];
+                    hi[u][c] += (uint64_t)dh * kh[c];
+                    mid[u][c] += (uint64_t)(dl + dh) * (kl[c] + kh[c]);
+                }
+            }
+        }
+    }
+    const ModD m = C->mod[r];
+    const double t50 = C->two50[r], t81 = C->two81[r];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        if (ug * U + u >= batch) break;
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            // lo + 2^25 (mid - lo - hi) + 2^50 hi with the carries moved up, then modulo the prime
+            const uint64_t x = (lo[u][c] >> 25) + (mid[u][c] - lo[u][c] - hi[u][c]);
+            const uint64_t low = (lo[u][c] & 0x1FFFFFFu) | ((x & 0x1FFFFFFu) << 25);
+            const uint64_t top = hi[u][c] + (x >> 25);
+            const double v = u64_to_f64(low) + mulmod((double)((uint32_t)top & 0x7FFFFFFFu), t50, m) +
+                             mulmod((double)(uint32_t)(top >> 31), t81, m);
+            acc[(((size_t)((ug * U + u) * 2 + c) * L + r) << logn) + idx] = v;
         }
     }
 }

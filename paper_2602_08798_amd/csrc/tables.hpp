@@ -36,6 +36,8 @@ struct DevConst {
     double ninv[MAXPR];       // N^-1 mod prime (centred)
     double itw1_ninv[MAXPR];  // (first inverse twiddle) * N^-1 (centred)
     double tmod;              // plaintext modulus t
+    double two50[MAXPR];      // 2^50 mod prime (centred)
+    double two81[MAXPR];      // 2^81 mod prime (centred)
     ConvTab q2b;              // Q -> auxiliary basis, centred
     ConvTab b2q;              // auxiliary basis -> Q, centred
     double Qinv_b[MAXS];      // Q^-1 mod b_j (centred)
