@@ -730,21 +730,21 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     // inverse transform and the scaling; out3 then holds batch / sum_group results
     if (!b_group) { b_group = batch; b_stride = batch; }
     const uint32_t n_a = (batch + a_group - 1) / a_group;
+    const uint32_t n_out = sum_group ? batch / sum_group : batch;
     const size_t polys = 2 * ((size_t)n_a + (b_ext ? 0 : batch));
     Bump w = bump(c, ws);
     double *ntt = w.take<double>(polys * c->KL);
     double *tens = w.take<double>((size_t)3 * c->KL * batch);
     const double LB = (double)limb_bytes(c), B = batch;
-    const MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
-    CG_TRY(transform_ext(c, s, src, polys, ntt));
-    // tensor product fused into the inverse transform's load
-    const LdInvTensor ld{ntt, b_ext, (int)a_group, (int)n_a, (int)b_group, (int)b_stride, c->logn};
-    const uint32_t n_out = sum_group ? batch / sum_group : batch;
-    const size_t rows = (size_t)n_out * 3 * c->KL;
-    const double tbytes = LB * c->KL * (2.0 * ((double)n_a + B) + 3.0 * n_out);
-    if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StInvF64{tens, c->logn},
-                                     KID_INV_TENSORSUM, tbytes));
-    else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
+    MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
+        CG_TRY(transform_ext(c, s, src, polys, ntt));
+        // tensor product fused into the inverse transform's load
+        const LdInvTensor ld{ntt, b_ext, (int)a_group, (int)n_a, (int)b_group, (int)b_stride, c->logn};
+        const size_t rows = (size_t)n_out * 3 * c->KL;
+        const double tbytes = LB * c->KL * (2.0 * ((double)n_a + B) + 3.0 * n_out);
+        if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StInvF64{tens, c->logn},
+                                         KID_INV_TENSORSUM, tbytes));
+        else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
     const double sbytes = LB * (3.0 * c->KL + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);
 #define CG_SCALE(K) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, scale_kernel<K>, sblocks, tens, out3, (int)n_out * 3, accumulate, c->dc)
@@ -792,23 +792,23 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     double *acc = w.take<double>((size_t)2 * c->L * batch);
     const double LB = (double)limb_bytes(c), B = batch;
     const double dig_rows = (double)c->dnum * c->L;
-    int rc;
-    CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));
-    // inner product with the key fused into the inverse transform's load
-    const size_t irows = (size_t)batch * 2 * c->L;
-    const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows);
-    const StInvF64 ist{acc, c->logn};
+        CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));
+        // inner product with the key fused into the inverse transform's load
+        const size_t irows = (size_t)batch * 2 * c->L;
+        const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows);
+        const StInvF64 ist{acc, c->logn};
+        int rc;
 #define CG_KSI(D) launch_inv(c, s, irows, LdInvKsInner<D>{dig, key, c->logn}, ist, KID_INV_KSINNER, ibytes)
-    switch (c->dnum) {
-    case 1: rc = CG_KSI(1); break;
-    case 2: rc = CG_KSI(2); break;
-    case 3: rc = CG_KSI(3); break;
-    case 4: rc = CG_KSI(4); break;
-    case 5: rc = CG_KSI(5); break;
-    default: rc = CG_KSI(6); break;
-    }
+        switch (c->dnum) {
+        case 1: rc = CG_KSI(1); break;
+        case 2: rc = CG_KSI(2); break;
+        case 3: rc = CG_KSI(3); break;
+        case 4: rc = CG_KSI(4); break;
+        case 5: rc = CG_KSI(5); break;
+        default: rc = CG_KSI(6); break;
+        }
 #undef CG_KSI
-    CG_TRY(rc);
+        CG_TRY(rc);
     ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
     const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
     return launch_moddown<false>(c, s, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, batch, A, ModdownHoist{});

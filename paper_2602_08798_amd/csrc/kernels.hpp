@@ -47,11 +47,17 @@ template <int LOGN, int E, int PASS> __device__ __forceinline__ int group_index(
 {
     constexpr int R = Plan<LOGN, E>::R[PASS];
     if (PASS < Plan<LOGN, E>::NC) return tid + g * ((1 << LOGN) / E);
-    int lane = tid & 63;
-    // a radix-2 pass works on pairs of neighbours, 16 bytes per lane: which pair a lane takes is
-    // permuted as in chunk_elem, for the same reason (LDS banks)
-    if (R == 1) lane = (lane & 7) | (((lane >> 4) & 3) << 3) | (((lane >> 3) & 1) << 5);
-    return ((tid >> 6) << (chunk_log<E>() - R)) + lane + 64 * g;
+    // Wave-local passes are free in which groups a lane takes.  pad() gives the index bits 0 ... 8 the
+    // weights 1, 2, 4, 8, 16, 2, 4, 8, 16 modulo the 32 doubles that 32 lanes read at once (16 lanes write at
+    // once, and 16 lanes read or write 16 bytes each): lanes are put on index bits of different weights.
+    constexpr int L = LOGN - stage_start<LOGN, E, PASS>() - R;
+    const int lane = tid & 63;
+    int q = lane;
+    if (L == 4 && R == 3) q = (lane & 15) | ((lane & 16) << 1) | ((lane & 32) >> 1);                  // bits 0-3, 8, 7
+    if (L == 1 && R == 3) q = (lane & 33) | ((lane & 14) << 1) | ((lane & 16) >> 3);                  // bits 0, 5, 6, 7, 4, 8
+    if (L == 3 && R == 3) q = (lane & 7) | ((lane & 24) << 1) | ((lane & 32) >> 2);                   // bits 0-2, 7, 8, 6
+    if (L == 0 && R == 3) q = ((lane & 3) << 2) | ((lane & 12) >> 2) | (lane & 48);                   // bits 5, 6, 3, 4, 7, 8
+    return ((tid >> 6) << (chunk_log<E>() - R)) + q + 64 * g;
 }
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every
 // outstanding global load (vmcnt(0)), which would drain the next row's prefetch at each
@@ -77,15 +83,68 @@ constexpr double fwd_grow(double b, int stages)
     for (int i = 0; i < stages; i++) b = 1.1875 * b + 0.5;
     return b;
 }
-// Decide at compile time which forward passes start with a reduction.
+// Decide at compile time which forward passes start with a reduction.  Only the operands that are not
+// multiplied in the first stage (half of them) need it: a product of an operand below 8p is below 2p
+// anyway, |out| <= (0.51 + 0.5 + 0.1875 |in|) p after that stage.
+// (Bounds are in units of 2^50, above every prime: a product's quotient is off by 3/16 at most per 2^50
+// of the lazy operand whatever the prime, so they hold for primes of different sizes too.)
+constexpr double FWD_IN = 1.25;      // what loaders deliver
+constexpr double LAZY_MAX = 7.9;     // values must stay below 2^53
 template <int LOGN, int E, int PASS> struct FwdBound {
-    static constexpr double in_prev = FwdBound<LOGN, E, PASS - 1>::out;
-    static constexpr bool reduce = fwd_grow(in_prev, Plan<LOGN, E>::R[PASS]) > 7.5;
-    static constexpr double out = fwd_grow(reduce ? 0.51 : in_prev, Plan<LOGN, E>::R[PASS]);
+    static constexpr double in = FwdBound<LOGN, E, PASS - 1>::out;
+    static constexpr bool reduce = fwd_grow(in, Plan<LOGN, E>::R[PASS]) > LAZY_MAX;
+    static constexpr double out = reduce ? fwd_grow(1.01 + 0.1875 * in, Plan<LOGN, E>::R[PASS] - 1)
+                                         : fwd_grow(in, Plan<LOGN, E>::R[PASS]);
 };
 template <int LOGN, int E> struct FwdBound<LOGN, E, 0> {
-    static constexpr bool reduce = false;                       // loaders deliver |x| <= p
-    static constexpr double out = fwd_grow(1.0, Plan<LOGN, E>::R[0]);
+    static constexpr bool reduce = false;
+    static constexpr double out = fwd_grow(FWD_IN, Plan<LOGN, E>::R[0]);
+};
+
+// Inverse passes: a sum is as large as its operands together, a product (a - b) w at most
+// 0.5 + 0.1875 |a - b|.  The plan of a pass, from the bound of its inputs: which operands are reduced
+// before a stage (their sum would pass LAZY_MAX) and which results are reduced at its end, so that the
+// next pass starts from INV_OUT.  Of eight results of a three-stage pass two or three are reduced, and
+// two operands on the way, where reducing every input takes eight.
+constexpr double INV_OUT = 1.92;
+template <int R> struct InvPlan {
+    bool before[R][1 << R], after[1 << R];
+    double out;
+};
+template <int R> constexpr InvPlan<R> inv_plan(double in, bool last)
+{
+    InvPlan<R> P{};
+    double b[1 << R] = {};
+    for (int c = 0; c < (1 << R); c++) b[c] = in;
+    for (int s = 0; s < R; s++) {
+        const int half = 1 << s;
+        for (int c = 0; c < (1 << R); c++) {
+            if (c & half) continue;
+            if (b[c] + b[c + half] > LAZY_MAX)
+                for (int i : {c, c + half}) {
+                    P.before[s][i] = b[i] > 0.51;
+                    if (b[i] > 0.51) b[i] = 0.51;
+                }
+            const double sum = b[c] + b[c + half], prod = 0.5 + 0.1875 * sum;
+            b[c] = (last && s == R - 1) ? prod : sum;
+            b[c + half] = prod;
+        }
+    }
+    for (int c = 0; c < (1 << R); c++) {
+        P.after[c] = !last && b[c] > INV_OUT;
+        if (P.after[c]) b[c] = 0.51;
+        if (b[c] > P.out) P.out = b[c];
+    }
+    return P;
+}
+// the first pass (NP - 1) reduces what the loader delivers
+template <int LOGN, int E, int PASS, bool FIRST = PASS == Plan<LOGN, E>::NP - 1> struct InvBound {
+    static constexpr double in = InvBound<LOGN, E, PASS + 1>::out;
+    static constexpr double out = inv_plan<Plan<LOGN, E>::R[PASS]>(in, PASS == 0).out;
+};
+template <int LOGN, int E, int PASS> struct InvBound<LOGN, E, PASS, true> {
+    static constexpr double in = 0.51;
+    static constexpr double out = inv_plan<Plan<LOGN, E>::R[PASS]>(in, PASS == 0).out;
 };
 
 __device__ __forceinline__ void bfly_fwd(double &a, double &b, double w, const ModD m)
@@ -108,15 +167,46 @@ __device__ __forceinline__ void bfly_inv(double &a, double &b, double w, const M
 // ---------------------------------------------------------------------------
 constexpr int TWREGS = 16;
 
-// LDS layout: one pad double after every 8, so that a thread owning 8 (or 16)
-// consecutive elements is 9 doubles away from its neighbour lane and the
-// stride-1 passes are bank-conflict free.  For the index patterns used here
-// (base + (c << L), base = (hi << (L+R)) | lo with lo < 2^L) the pad of the sum
-// is the sum of the pads -- with L >= 3 the element part is a multiple of 8,
-// otherwise it never carries out of the group's aligned span -- so the
-// per-element part folds into instruction offsets.
-__device__ __forceinline__ constexpr int pad(int idx) { return idx + (idx >> 3); }
-template <int LOGN> constexpr int lds_doubles() { return (1 << LOGN) + (1 << (LOGN - 3)); }
+// LDS layout: two pad doubles after every 32.  What a compute unit's LDS does (probe, clocks per
+// instruction): ds_read_b64 2.65 when 32 lanes hit 32 different doubles modulo 32, 4.3 with two of them on
+// one; ds_write_b64 6.7 when 16 lanes hit different doubles modulo 16, 8.3 otherwise; and 16-byte
+// accesses read at 1.4 times the rate.  With this layout and the lanes of group_index every pass reads and writes
+// without conflicts, and neighbouring pairs stay 16-byte aligned.  (One pad after every 8, as before, made
+// the unit-stride passes conflict: 4.4 and 8.4 clocks.)  An index that is the sum of two with disjoint
+// bits has the sum of their positions, so the per-element part of a pass folds into instruction offsets.
+__device__ __forceinline__ constexpr int pad(int idx) { return idx + ((idx >> 5) << 1); }
+__device__ __forceinline__ double2 &pair_at(double *lds, int pos) { return *reinterpret_cast<double2 *>(lds + pos); }
+template <int LOGN> constexpr int lds_doubles() { return (1 << LOGN) + (1 << (LOGN - 4)); }
+
+// element `idx` of a row: a uniform base and a 32-bit byte offset per lane (one register instead of two,
+// no 64-bit address arithmetic)
+template <class T> __device__ __forceinline__ T at32(const T *base, int idx)
+{
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (uint32_t)idx * (uint32_t)sizeof(T));
+}
+
+template <class T> __device__ __forceinline__ void put32(T *base, int idx, T v)
+{
+    *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + (uint32_t)idx * (uint32_t)sizeof(T)) = v;
+}
+// Element tid of a row at a uniform address, in the form of a load that takes both: left to itself the compiler
+// adds the lane's offset first and carries one 64-bit vector address per row.
+template <class T> __device__ __forceinline__ T at_lane(const T *base, int tid)
+{
+    auto g = (const T __attribute__((address_space(1))) *)base;
+    uint32_t off = (uint32_t)tid * (uint32_t)sizeof(T);
+    asm("" : "+s"(g));
+    asm("" : "+v"(off));
+    return *(const T __attribute__((address_space(1))) *)((const char __attribute__((address_space(1))) *)g + off);
+}
+// Constants that are read where they are used: kept for a whole kernel with several transforms they do not
+// fit the scalar registers.
+template <class T> __device__ __forceinline__ const T *opaque_const(const T *p)
+{
+    auto g = (const T __attribute__((address_space(4))) *)p;
+    asm volatile("" : "+s"(g));
+    return (const T *)g;
+}
 
 template <int LOGN, int E, int PASS, bool HI_ZERO>
 __device__ __forceinline__ void load_tw(const double *__restrict__ tw, int tid, double *twr)
@@ -138,7 +228,7 @@ __device__ __forceinline__ void load_tw(const double *__restrict__ tw, int tid, 
         for (int u = 0; u < R; u++)
 #pragma unroll
             for (int j = 0; j < (1 << u); j++)
-                twr[g * PER + (1 << u) - 1 + j] = tw[(1 << (S0 + u)) + (hi << u) + j];
+                twr[g * PER + (1 << u) - 1 + j] = at32(tw + (1 << (S0 + u)) + j, hi << u);
     }
 }
 
@@ -171,7 +261,7 @@ __device__ __forceinline__ int xcd_row(int p, int nwg, int S)
 //   prime(wg, C)               prime index of row wg
 //   dst_limb(wg, C)            forward only: destination row
 //   fetch(wg, idx, C, raw)     issue the loads of element idx (no arithmetic on the loaded words)
-//   finish(raw, wg, idx, m, C) element value, |x| <= p (forward) or < 8p (inverse)
+//   finish(raw, wg, idx, m, C) element value, |x| <= FWD_IN 2^50 (forward) or < 2^53 (inverse)
 //
 // Element ownership: CHUNKED = false: element it of a thread is tid + it * T
 // (pass 0); CHUNKED = true: (wave << chunk_log) + lane + 64 * it (the wave's chunk).
@@ -179,16 +269,9 @@ __device__ __forceinline__ int xcd_row(int p, int nwg, int S)
 // ---------------------------------------------------------------------------
 // element `it` of a thread in the chunked ownership: a lane takes pairs of neighbouring elements of
 // its wave's chunk, so that every operand comes in (and every result goes out) 16 bytes per lane.
-// Which pair: lane bits 0-2 give pair bits 0-2, lane bit 3 pair bit 5, lane bits 4-5 pair bits 3-4,
-// the iteration the bits above.  Eight consecutive lanes then cover one 128-byte line in memory,
-// and in the padded LDS row (position = index + index / 8) any sixteen consecutive lanes land on
-// sixteen different 8-byte banks: pair u = a + 4 b sits at 2 a + 9 b, and b in {0, 1, 8, 9} gives
-// offsets 0, 9, 8, 1 modulo 16.  With lane l simply taking pair l, lanes l and l + 8 collide.
 template <int E> __device__ __forceinline__ int chunk_elem(int tid, int it)
 {
-    const int lane = tid & 63;
-    const int u = (lane & 7) | (((lane >> 4) & 3) << 3) | (((lane >> 3) & 1) << 5);
-    return ((tid >> 6) << chunk_log<E>()) + 2 * u + (it & 1) + 128 * (it >> 1);
+    return ((tid >> 6) << chunk_log<E>()) + 2 * (tid & 63) + (it & 1) + 128 * (it >> 1);
 }
 
 template <int LOGN, int E, bool CHUNKED, class LD>
@@ -203,6 +286,10 @@ __device__ __forceinline__ void fetch_row(const LD &ld, int wg, int tid, const D
 // Loaders whose element is a sum over several rounds of fetches (ld.rounds() of them, each with
 // ld.fetch_round / ld.finish, the partial sums joined by ld.join) are marked here.
 template <class LD> struct ld_rounds { static constexpr bool value = false; };
+
+// Loaders that lift kRaw consecutive residue rows to one (ld.row names the first of them) are marked here:
+// row addresses and the target are worked out once per row.
+template <class LD> struct ld_lifts { static constexpr bool value = false; };
 
 // Loaders that do not prefetch fetch and finish a row in slices, so that at most about 32 raw
 // words are live per thread however many words an element needs.
@@ -233,6 +320,27 @@ __device__ __forceinline__ void load_row_now(const LD &ld, int wg, int tid, cons
         }
         return;
     }
+    if constexpr (ld_lifts<LD>::value) {
+        static_assert(!CHUNKED, "pass-0 ownership");
+        const uint64_t *row = ld.row(wg, C);
+        const int j = ld.target(wg, C);
+#pragma unroll
+        for (int c0 = 0; c0 < E; c0 += CH) {
+            uint64_t rw[CH][LD::kRaw];
+#pragma unroll
+            for (int i = 0; i < CH; i++)
+#pragma unroll
+                for (int q = 0; q < LD::kRaw; q++)
+                    rw[i][q] = at_lane(row + ((size_t)q << LOGN) + (c0 + i) * T, tid);
+            // the constants are read anew for every slice: kept from slice to slice they do not fit the
+            // scalar registers and push the row out of the vector registers
+            const DevConst *Cs = opaque_const(C);
+#pragma unroll
+            for (int i = 0; i < CH; i++) sink(c0 + i, tid + (c0 + i) * T, ld.lift(rw[i], j, m, Cs));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
 #pragma unroll
     for (int c0 = 0; c0 < E; c0 += CH) {
         uint64_t rw[CH][LD::kRaw];
@@ -251,6 +359,14 @@ __device__ __forceinline__ void load_row_now(const LD &ld, int wg, int tid, cons
 // ---------------------------------------------------------------------------
 // storers that keep the row in LDS (told the element's number in chunk_elem order, not a row)
 template <class ST> struct st_in_place { static constexpr bool value = false; };
+// the storer of a transform whose results stay in registers, in chunk_elem order
+struct StRegs {
+    double *out;
+    __device__ __forceinline__ void store(int it, int, double v, const ModD) const { out[it] = v; }
+};
+template <> struct st_in_place<StRegs> { static constexpr bool value = true; };
+template <class ST> struct st_regs { static constexpr bool value = false; };
+template <> struct st_regs<StRegs> { static constexpr bool value = true; };
 
 template <int LOGN, int E, int PASS, bool FROM_REGS, class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
@@ -283,14 +399,19 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
         for (int c = 0; c < (1 << R); c++) {
             // first pass: element base + (c << L) = tid + (g + c*G) * T is fetched element g + c*G
             if (FROM_REGS) v[g][c] = in[g + c * G];
-            else v[g][c] = lds[pb + pad(c << L)];
+            else if (L > 0) v[g][c] = lds[pb + pad(c << L)];
+            else if (c % 2 == 0) {
+                const double2 w = pair_at(lds, pb + c);
+                v[g][c] = w.x;
+                v[g][c + 1] = w.y;
+            }
         }
     }
 #pragma unroll
     for (int g = 0; g < G; g++) {
         if (do_red) {
 #pragma unroll
-            for (int c = 0; c < (1 << R); c++) v[g][c] = red(v[g][c], m);
+            for (int c = 0; c < (1 << R) / 2; c++) v[g][c] = red(v[g][c], m);
         }
 #pragma unroll
         for (int u = 0; u < R; u++) {
@@ -302,13 +423,25 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
             }
         }
     }
+    // a last pass on pairs of neighbours leaves them where chunk_elem order has them: no trip to LDS
+    if constexpr (last && R == 1 && st_regs<ST>::value) {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            st.store(2 * g, 0, v[g][0], m);
+            st.store(2 * g + 1, 0, v[g][1], m);
+        }
+        return;
+    }
     // fetch the next pass's factors while this pass's results drain to LDS
     if constexpr (!last) load_tw<LOGN, E, PASS + 1, false>(tw, tid, twr_next);
 #pragma unroll
     for (int g = 0; g < G; g++) {
         const int pb = pad(base[g]);
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++) lds[pb + pad(c << L)] = v[g][c];
+        for (int c = 0; c < (1 << R); c++) {
+            if (L > 0) lds[pb + pad(c << L)] = v[g][c];
+            else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
+        }
     }
     if constexpr (cross) lds_barrier();
     else wave_sync();
@@ -317,10 +450,16 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
         // wave copies out its own chunk
         // (a lane takes pairs of neighbouring elements: 16 bytes per lane and store)
 #pragma unroll
-        for (int it = 0; it < E; it++) {
+        for (int it = 0; it < E; it += 2) {
             const int idx = chunk_elem<E>(tid, it);
-            if constexpr (st_in_place<ST>::value) st.store(it, idx, lds[pad(idx)], m);
-            else st.store(dst_limb, idx, lds[pad(idx)], m);
+            const double2 w = pair_at(lds, pad(idx));
+            if constexpr (st_in_place<ST>::value) {
+                st.store(it, idx, w.x, m);
+                st.store(it + 1, idx + 1, w.y, m);
+            } else {
+                st.store(dst_limb, idx, w.x, m);
+                st.store(dst_limb, idx + 1, w.y, m);
+            }
         }
     }
 }
@@ -329,7 +468,7 @@ template <int LOGN, int E, class LD, class ST>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *__restrict__ C, int nwg)
 {
-    __shared__ double lds[lds_doubles<LOGN>()];
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int T = (1 << LOGN) / E;
     constexpr int NP = Plan<LOGN, E>::NP;
@@ -348,7 +487,7 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
         const double *tw = tw_all + ((size_t)pr << LOGN);
         const int dl = ld.dst_limb(wg, C);
         double twa[TWREGS], twb[TWREGS];
-        load_tw<LOGN, E, 0, true>(tw, tid, twa);
+        if constexpr (PF) load_tw<LOGN, E, 0, true>(tw, tid, twa);
         double in[E];
         p += (int)gridDim.x;
         const bool more = p < nwg;
@@ -360,6 +499,7 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
             if (more) fetch_row<LOGN, E, CH>(ld, wg_next, tid, C, raw);
         } else {
             load_row_now<LOGN, E, CH>(ld, wg, tid, m, C, [&](int it, int, double v) { in[it] = v; });
+            load_tw<LOGN, E, 0, true>(tw, tid, twa);     // (scalar registers that the loader's constants need)
         }
         if constexpr (LD::kScatter) {
 #pragma unroll
@@ -385,10 +525,11 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
 // storers that add to what the destination holds (fetch() brings it in)
 template <class ST> struct st_adds { static constexpr bool value = false; };
 
+// from != null: the first pass takes its elements from registers, in chunk_elem order
 template <int LOGN, int E, int PASS, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
-                                         const ModD m, int pr, const DevConst *C)
+                                         const ModD m, int pr, const DevConst *C, const double *from = nullptr)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -398,6 +539,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     constexpr int PER = (1 << R) - 1;
     constexpr bool last = PASS == 0;
     constexpr bool cross = PASS < P::NC;
+    constexpr InvPlan<R> plan = inv_plan<R>(InvBound<LOGN, E, PASS>::in, last);
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     double v[G][1 << R];
     int base[G];
@@ -412,7 +554,15 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
         base[g] = (hi << (L + R)) | lo;
         const int pb = pad(base[g]);
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++) v[g][c] = lds[pb + pad(c << L)];
+        for (int c = 0; c < (1 << R); c++) {
+            if (R == 1 && from) v[g][c] = from[2 * g + c];
+            else if (L > 0) v[g][c] = lds[pb + pad(c << L)];
+            else if (c % 2 == 0) {
+                const double2 w = pair_at(lds, pb + c);
+                v[g][c] = w.x;
+                v[g][c + 1] = w.y;
+            }
+        }
     }
     // a storer that adds to what is there has it brought in eight elements at a time, the first eight
     // before the butterflies where registers allow: read one by one between the stores (which might
@@ -429,16 +579,16 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     if (E <= 8) fetch_old(0, 0);
 #pragma unroll
     for (int g = 0; g < G; g++) {
-        // every pass starts from |x| <= p/2: the sum path doubles per stage
+        if (PASS == P::NP - 1) {
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++) v[g][c] = red(v[g][c], m);
+            for (int c = 0; c < (1 << R); c++) v[g][c] = red(v[g][c], m);
+        }
 #pragma unroll
         for (int u = R - 1; u >= 0; u--) {
             const int half = 1 << (R - 1 - u);
-            if (R == 4 && u == 1) {   // after two stages of a four-stage pass: |x| <= 2p -> p/2
 #pragma unroll
-                for (int c = 0; c < (1 << R); c++) v[g][c] = red(v[g][c], m);
-            }
+            for (int c = 0; c < (1 << R); c++)
+                if (plan.before[R - 1 - u][c]) v[g][c] = red(v[g][c], m);
 #pragma unroll
             for (int c = 0; c < (1 << R); c++) {
                 if (c & half) continue;
@@ -452,6 +602,9 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
                 }
             }
         }
+#pragma unroll
+        for (int c = 0; c < (1 << R); c++)
+            if (plan.after[c]) v[g][c] = red(v[g][c], m);
     }
     if constexpr (!last) {
         if constexpr (PASS == 1) load_tw<LOGN, E, 0, true>(itw, tid, twr_next);
@@ -465,8 +618,10 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
             // the last pass pairs elements N/2 apart with consecutive lanes on consecutive
             // addresses: it stores straight to global memory
             if (adds && c % 8 == 0 && (E > 8 || g || c)) fetch_old(g, c);
-            if (!last) lds[pb + pad(c << L)] = v[g][c];
-            else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[g][c], old[c % 8], m, C);
+            if (!last) {
+                if (L > 0) lds[pb + pad(c << L)] = v[g][c];
+                else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
+            } else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[g][c], old[c % 8], m, C);
             else st.store(wg, base[g] + (c << L), v[g][c], m, C);
         }
     }
@@ -480,7 +635,7 @@ template <int LOGN, int E, class LD, class ST>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
-    __shared__ double lds[lds_doubles<LOGN>()];
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int NP = Plan<LOGN, E>::NP;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
@@ -501,12 +656,17 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
             // re-reads it from LDS in the stride-1 pattern of the first pass
             if constexpr (PF) {
 #pragma unroll
-                for (int it = 0; it < E; it++) {
+                for (int it = 0; it < E; it += 2) {
                     const int idx = chunk_elem<E>(tid, it);
-                    lds[pad(idx)] = ld.finish(raw[it], wg, idx, m, C);
+                    pair_at(lds, pad(idx)) =
+                        make_double2(ld.finish(raw[it], wg, idx, m, C), ld.finish(raw[it + 1], wg, idx + 1, m, C));
                 }
             } else {
-                load_row_now<LOGN, E, true>(ld, wg, tid, m, C, [&](int, int idx, double v) { lds[pad(idx)] = v; });
+                double first = 0.0;     // (elements come in pairs)
+                load_row_now<LOGN, E, true>(ld, wg, tid, m, C, [&](int it, int idx, double v) {
+                    if (it % 2 == 0) first = v;
+                    else pair_at(lds, pad(idx - 1)) = make_double2(first, v);
+                });
             }
         }
         p += (int)gridDim.x;
@@ -549,38 +709,50 @@ template <class LD> struct inv_wide { static constexpr bool value = false; };
 // ---------------------------------------------------------------------------
 // exact base conversion helpers (per coefficient, registers only)
 // ---------------------------------------------------------------------------
-// x[0..NS) canonical residues -> mixed-radix digits a[0..NS); returns true when CENTRED and the integer
-// exceeds floor(S/2) (its centred representative is x - S).  The size of the source basis is a
-// template argument everywhere: with a run-time size every step of these loops is a branch and
-// the scaled configuration's mod-down (two special primes) took four times as long.
-template <int NS, bool CENTRED>
-__device__ __forceinline__ bool garner(const ConvTab &T, const DevConst *C, const double (&x)[NS], double (&a)[NS])
+// The size of the source basis is a template argument everywhere: with a run-time size every step of
+// these loops is a branch and the scaled configuration's mod-down (two special primes) took four times
+// as long.
+//
+// ms: the source basis' moduli (consecutive ones of the context's).  x[0..NS) canonical residues -> mixed-radix digits 0 <= a_i < s_i of the integer in [0, S)
+template <int NS>
+__device__ __forceinline__ void garner(const ConvTab &T, const ModD *ms, const double (&x)[NS], double (&a)[NS])
 {
     a[0] = x[0];
 #pragma unroll
     for (int j = 1; j < NS; j++) {
-        const ModD mj = C->mod[T.sidx[j]];
+        const ModD mj = ms[j];
         double v = x[j];
 #pragma unroll
         for (int i = 0; i < j; i++) v = mulmod(v - a[i], T.inv[i][j], mj);
         a[j] = canon(v, mj);
     }
-    bool gt = false;
-    if (CENTRED) {
-#pragma unroll
-        for (int i = 0; i < NS; i++) gt = (a[i] > T.half[i]) || (a[i] == T.half[i] && gt);
-    }
-    return gt;
 }
-// residue of the (optionally negative-shifted) integer modulo target jt; lazy, |.| < 3p
+// x[0..NS) residues, |x_j| <= p -> digits |a_i| <= (s_i - 1)/2.  These balanced digits represent exactly
+// the integers of magnitude at most (S - 1)/2: the centred representative, without the comparison with
+// S/2 and without making the digits canonical.  red() picks the balanced residue exactly here: its
+// quotient x u is off by less than 2^-52 at |x u| = 1/2, and the residues next to p/2 are 2^-51 away.
 template <int NS>
-__device__ __forceinline__ double horner(const ConvTab &T, const DevConst *C, const double (&a)[NS], int jt, bool neg)
+__device__ __forceinline__ void garner_balanced(const ConvTab &T, const ModD *ms, const double (&x)[NS],
+                                                double (&a)[NS])
 {
-    const ModD mt = C->mod[T.tidx[jt]];
+    a[0] = red(x[0], ms[0]);
+#pragma unroll
+    for (int j = 1; j < NS; j++) {
+        const ModD mj = ms[j];
+        double v = x[j];
+#pragma unroll
+        for (int i = 0; i < j; i++) v = mulmod(v - a[i], T.inv[i][j], mj);
+        a[j] = red(v, mj);
+    }
+}
+// residue of the integer modulo target jt (mt); lazy, |.| < 1.25 * 2^50 with balanced digits, < 2.1 * 2^50 with
+// canonical ones
+template <int NS>
+__device__ __forceinline__ double horner(const ConvTab &T, const ModD mt, const double (&a)[NS], int jt)
+{
     double acc = a[NS - 1];
 #pragma unroll
     for (int i = NS - 2; i >= 0; i--) acc = mulmod(acc, T.s_mod_t[i][jt], mt) + a[i];
-    if (neg) acc -= T.S_mod_t[jt];
     return acc;
 }
 
@@ -662,14 +834,10 @@ struct MulSrc {
     }
     __device__ __forceinline__ const uint64_t *poly(int pp, int k) const
     {
-        const int ct = pp >> 1, comp = pp & 1;
-        const uint64_t *base;
-        if (ct < n_a) base = cta + (((size_t)ct * 2 * k) << logn);
-        else {
-            const int u = ct - n_a;
-            base = ctb + (((size_t)((u / b_group) * b_stride + u % b_group) * 2 * k) << logn);
-        }
-        return base + (((size_t)comp * k) << logn);
+        // (no branch: loaders ask for the row once per element and leave it to the compiler to do so once)
+        const int ct = pp >> 1, comp = pp & 1, u = ct < n_a ? 0 : ct - n_a;
+        const int idx = ct < n_a ? ct : (u / b_group) * b_stride + u % b_group;
+        return (ct < n_a ? cta : ctb) + (((size_t)(2 * idx + comp) * k) << logn);
     }
 };
 struct LdMulQ {     // workgroup -> (pp, ciphertext prime i)
@@ -698,7 +866,7 @@ struct LdMulQ {     // workgroup -> (pp, ciphertext prime i)
 template <int K>
 struct LdMulAux {
     static constexpr int kRaw = K;
-    static constexpr bool kPrefetch = false;   // K words per element: fetched in slices instead
+    static constexpr bool kPrefetch = false;
     static constexpr bool kScatter = false;
     MulSrc src;
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return C->k + wg % C->l; }
@@ -707,21 +875,20 @@ struct LdMulAux {
     {
         return src.dst_poly(wg / C->l) * C->KL + C->k + wg % C->l;
     }
-    __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *C, uint64_t *raw) const
-    {
-        const uint64_t *p = src.poly(wg / C->l, K) + idx;
-#pragma unroll
-        for (int i = 0; i < K; i++) raw[i] = p[(size_t)i << src.logn];
-    }
-    __device__ __forceinline__ double finish(const uint64_t *raw, int wg, int, const ModD mb, const DevConst *C) const
+    __device__ __forceinline__ const uint64_t *row(int wg, const DevConst *C) const { return src.poly(wg / C->l, K); }
+    __device__ __forceinline__ int target(int wg, const DevConst *C) const { return wg % C->l; }
+    static __device__ __forceinline__ double lift(const uint64_t *raw, int j, const ModD mb, const DevConst *C)
     {
         double x[K], dg[K];
 #pragma unroll
         for (int i = 0; i < K; i++) x[i] = u64_to_f64(raw[i]);
-        const bool neg = garner<K, true>(C->q2b, C, x, dg);
-        return canon(horner<K>(C->q2b, C, dg, wg % C->l, neg), mb);
+        garner_balanced<K>(C->q2b, C->mod, x, dg);
+        return horner<K>(C->q2b, mb, dg, j);
     }
+    __device__ __forceinline__ void fetch(int, int, const DevConst *, uint64_t *) const {}
+    __device__ __forceinline__ double finish(const uint64_t *, int, int, const ModD, const DevConst *) const { return 0.0; }
 };
+template <int K> struct ld_lifts<LdMulAux<K>> { static constexpr bool value = true; };
 
 // key-switch mod-up: workgroup -> (unit b, digit j, target prime r); the digit is
 // the integer in [0,Q_j) formed by ALPHA rows of the source ring element, reduced
@@ -765,10 +932,10 @@ struct LdModup {
             x[s] = u64_to_f64(raw[s]);
             if (negate) x[s] = (x[s] == 0.0) ? 0.0 : C->mod[j * ALPHA + s].p - x[s];
         }
-        if (ALPHA == 1) return canon(x[0], mr);
+        if (ALPHA == 1) return x[0];     // below 2^50 is all the transform asks for
         const ConvTab &T_ = C->dig[j];
-        garner<ALPHA, false>(T_, C, x, a);
-        return canon(horner<ALPHA>(T_, C, a, r, false), mr);
+        garner<ALPHA>(T_, C->mod + j * ALPHA, x, a);
+        return red(horner<ALPHA>(T_, mr, a, r), mr);
     }
 };
 
@@ -1049,7 +1216,7 @@ struct StInvF64 {
     int logn;
     __device__ __forceinline__ void store(int wg, int idx, double v, const ModD, const DevConst *) const
     {
-        dst[((size_t)wg << logn) + idx] = v;
+        put32(dst + ((size_t)wg << logn), idx, v);
     }
 };
 struct StInvU64 {
@@ -1057,7 +1224,7 @@ struct StInvU64 {
     int logn;
     __device__ __forceinline__ void store(int wg, int idx, double v, const ModD m, const DevConst *) const
     {
-        dst[((size_t)wg << logn) + idx] = f64_to_u64(canon(v, m));
+        put32(dst + ((size_t)wg << logn), idx, f64_to_u64(canon(v, m)));
     }
 };
 // cache append: workgroup -> (cache c, comp, prime); target row = cache + c*stride + row;
@@ -1106,7 +1273,7 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
                     const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                     const DevConst *__restrict__ C, int nwg)
 {
-    __shared__ double lds[lds_doubles<LOGN>()];
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr int T = (1 << LOGN) / E, NP = Plan<LOGN, E>::NP;
     // the plaintext row and the next row are brought in ahead where there are registers for it
     constexpr bool PF = prefetch_rows<LOGN, E>();
@@ -1123,7 +1290,7 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
         const int pr = wg % k;
         const ModD m = C->mod[pr];
         const double *tw = tw_all + ((size_t)pr << LOGN), *itw = itw_all + ((size_t)pr << LOGN);
-        const double *prow = plain + ((size_t)((wg / (2 * k)) * pstride + pofs) * k + pr << LOGN);
+        const double *prow = plain + ((size_t)(((wg / (2 * k)) * pstride + pofs) * k + pr) << LOGN);
         double twa[TWREGS], twb[TWREGS], in[E], pl[PF ? E : 1];
         load_tw<LOGN, E, 0, true>(tw, tid, twa);
         if constexpr (PF) {
@@ -1189,20 +1356,20 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int to
     for (int i = 0; i < K + L; i++) e[i] = src[(size_t)i << logn];
     double x[K], dq[K], y[L], db[L];
 #pragma unroll
-    for (int i = 0; i < K; i++) x[i] = canon(mulmod(e[i], t, C->mod[i]), C->mod[i]);
-    const bool neg = garner<K, true>(C->q2b, C, x, dq);
+    for (int i = 0; i < K; i++) x[i] = mulmod(e[i], t, C->mod[i]);
+    garner_balanced<K>(C->q2b, C->mod, x, dq);
 #pragma unroll
     for (int j = 0; j < L; j++) {
         const ModD mb = C->mod[K + j];
         const double te = mulmod(e[K + j], t, mb);
-        const double rj = horner<K>(C->q2b, C, dq, j, neg);
-        y[j] = canon(mulmod(red(te - rj, mb), C->Qinv_b[j], mb), mb);
+        const double rj = horner<K>(C->q2b, mb, dq, j);
+        y[j] = mulmod(te - rj, C->Qinv_b[j], mb);
     }
-    const bool neg2 = garner<L, true>(C->b2q, C, y, db);
+    garner_balanced<L>(C->b2q, C->mod + K, y, db);
     uint64_t *o = out + (((size_t)bc * K) << logn) + n;
 #pragma unroll
     for (int i = 0; i < K; i++) {
-        double v = canon(horner<L>(C->b2q, C, db, i, neg2), C->mod[i]);
+        double v = canon(horner<L>(C->b2q, C->mod[i], db, i), C->mod[i]);
         if (acc) v = addmod_canon(v, u64_to_f64(o[(size_t)i << logn]), C->mod[i]);
         o[(size_t)i << logn] = f64_to_u64(v);
     }
@@ -1265,8 +1432,8 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
         xp[0][s] = addmod_canon(canon(x2.x, mp), C->halfP[k + s], mp);
         xp[1][s] = addmod_canon(canon(x2.y, mp), C->halfP[k + s], mp);
     }
-    garner<NSP, false>(C->p2q, C, xp[0], dg[0]);
-    garner<NSP, false>(C->p2q, C, xp[1], dg[1]);
+    garner<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
+    garner<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
     int src_idx[2] = {0, 0};
     bool negate[2] = {false, false};
     if (A.galois) {
@@ -1290,7 +1457,7 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 #pragma unroll
             for (int e2 = 0; e2 < 2; e2++) {
                 const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner<NSP>(C->p2q, C, dg[e2], i, false);
+                const double ri = horner<NSP>(C->p2q, mq, dg[e2], i);
                 v[e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
             }
             if (A.add) {
@@ -1389,13 +1556,13 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
                 xp[0][s] = addmod_canon(canon(xs[j][s].x, mp), C->halfP[k + s], mp);
                 xp[1][s] = addmod_canon(canon(xs[j][s].y, mp), C->halfP[k + s], mp);
             }
-            garner<NSP, false>(C->p2q, C, xp[0], dg[0]);
-            garner<NSP, false>(C->p2q, C, xp[1], dg[1]);
+            garner<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
+            garner<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
             const double ain[2] = {as[j].x, as[j].y};
 #pragma unroll
             for (int e2 = 0; e2 < 2; e2++) {
                 const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner<NSP>(C->p2q, C, dg[e2], i, false);
+                const double ri = horner<NSP>(C->p2q, mq, dg[e2], i);
                 v[j][e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
             }
         }
