@@ -172,6 +172,7 @@ struct cg_ctx {
     std::mutex *occ_mu;
     std::unordered_map<const void *, int> *occ;
     bool dry;             // set-up pass: launches compute their grid and return without launching
+    bool dry_rows;                  // while dry: take the kernels of several transforms per workgroup
     int elems, elems_fwd; // elements per thread in the inverse / forward transform kernels (8 or 16)
     // workspace limbs (N * 8 bytes) per unit
     int ws_total;
@@ -193,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -717,6 +718,23 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
     }
 }
 
+// Whether the kernels that take a (unit, prime) through several transforms in one workgroup are worth their
+// launch: a round of them over all units takes as long for one row as for n_cu, so at most half the units
+// may idle in the last one (three quarters in an attention call, which runs beside other branches); from the third
+// round on it does not matter.  N = 8192, 3 + 1 primes, product and relinearisation, us by launches of single
+// transforms / by these (7 rows per product): 12 products 78 / 90, 20: 96 / 94, 32: 122 / 110, 42: 144 / 163,
+// 64: 205 / 178, 75: 268 / 251, 150: 503 / 438; chain step of 12 heads (48 products): 686 / 656.  At
+// N = 4096 a unit holds two workgroups and a second round costs less (20 products 52 / 51, 56: 74 / 75, 110:
+// 119 / 108).  A row of 16384 leaves no registers for what these kernels keep.
+static bool row_kernels_fit(const cg_ctx *c, size_t rows, bool beside = false)
+{
+    if (c->logn > 13) return false;
+    if (c->dry) return c->dry_rows;
+    const size_t n = (size_t)c->n_cu, rounds = (rows + n - 1) / n, idle = rounds * n - rows;
+    if (2 * rows < n) return false;
+    return c->logn < 13 || rounds > 2 || (rounds == 2 && beside ? 4 * idle <= 3 * n : 2 * idle <= n);
+}
+
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
 // launch for the roofline report; LB = bytes of one residue row.
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
@@ -780,6 +798,31 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 #undef CG_MODUP
 }
 
+// mod-up, inner product with the key and inverse transforms in one launch
+static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
+                         const uint64_t *key, double *acc, uint32_t batch)
+{
+    const size_t nwg = (size_t)batch * c->L;
+    const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L);
+    ProfScope ps(c, s, KID_KSROW, bytes, (double)nwg);
+#define CG_KSROW(LG, G, A)                                                                                    \
+    do {                                                                                                     \
+        const unsigned threads = (1u << LG) / 8;                                                             \
+        const unsigned grid = ntt_grid<ks_row_kernel<LG, 8, G, A>>(c, nwg, (int)threads);                    \
+        if (c->dry) return CG_OK;                                                                            \
+        return launch_kernel(ks_row_kernel<LG, 8, G, A>, dim3(grid), dim3(threads), s,                       \
+                             LdModup<G, A>{src, src_stride, galois, c->logn}, key, StInvF64{acc, c->logn},   \
+                             (const double *)c->tw, (const double *)c->itw, (const DevConst *)c->dc, (int)nwg); \
+    } while (0)
+    switch ((c->logn * 10 + c->alpha) * 2 + (galois ? 1 : 0)) {
+    case 242: CG_KSROW(12, false, 1);
+    case 243: CG_KSROW(12, true, 1);
+    case 262: CG_KSROW(13, false, 1);
+    case 263: CG_KSROW(13, true, 1);
+    default: return CG_EINVAL;
+    }
+#undef CG_KSROW
+}
 // key switch of one ring element per unit (src + b*src_stride), then the final additions
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                         const uint64_t *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
@@ -792,6 +835,9 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     double *acc = w.take<double>((size_t)2 * c->L * batch);
     const double LB = (double)limb_bytes(c), B = batch;
     const double dig_rows = (double)c->dnum * c->L;
+    if (c->alpha == 1 && row_kernels_fit(c, (size_t)batch * c->L)) {
+        CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
+    } else {
         CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));
         // inner product with the key fused into the inverse transform's load
         const size_t irows = (size_t)batch * 2 * c->L;
@@ -809,6 +855,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
         }
 #undef CG_KSI
         CG_TRY(rc);
+    }
     ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
     const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
     return launch_moddown<false>(c, s, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, batch, A, ModdownHoist{});
@@ -1766,6 +1813,10 @@ static int warm_launch_table(cg_ctx *c)
     uint64_t *u = reinterpret_cast<uint64_t *>(uintptr_t(1) << 20);
     double *f = reinterpret_cast<double *>(uintptr_t(1) << 20);
     const double LB = 0.0;
+    c->dry_rows = true;
+    CG_TRY(do_keyswitch(c, s, u, 0, 0, u, u, 0, u, 0, 0, 0, 1, f));
+    CG_TRY(do_keyswitch(c, s, u, 0, 3, u, u, 0, u, 0, 3, 1, 1, f));
+    c->dry_rows = false;
     for (uint32_t batch : {1u, 4096u}) {
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0));
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0, 0, 0, nullptr, 1));

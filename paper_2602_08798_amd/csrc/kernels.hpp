@@ -1250,6 +1250,130 @@ struct StInvAppend {
 template <> struct st_adds<StInvAppend> { static constexpr bool value = true; };
 
 // ---------------------------------------------------------------------------
+// Transforms of a row that is in registers already or stays there: the pass sequence only.
+// ---------------------------------------------------------------------------
+// in: pass-0 ownership (element tid + it * T), or, with SCATTERED, already in LDS; out: chunk_elem order
+template <int LOGN, int E, bool SCATTERED>
+__device__ __forceinline__ void fwd_row(double *lds, const double *in, double *out, int tid,
+                                        const double *__restrict__ tw, const ModD m)
+{
+    constexpr int NP = Plan<LOGN, E>::NP;
+    // addresses are formed here and now: hoisted out of the caller's loops they would take the registers
+    // that hold its rows
+    asm volatile("" : "+v"(tid));
+    double twa[TWREGS], twb[TWREGS];
+    const StRegs st{out};
+    load_tw<LOGN, E, 0, true>(tw, tid, twa);
+    fwd_pass<LOGN, E, 0, !SCATTERED>(lds, in, st, tid, tw, twa, twb, m, 0);
+    fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, 0);
+    fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, 0);
+    fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, 0);
+    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, 0);
+}
+// in: chunk_elem order, |x| < 8p; results leave through st as row `row`
+template <int LOGN, int E, class ST>
+__device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
+                                        const double *__restrict__ itw, const ModD m, int pr, const DevConst *C)
+{
+    constexpr int NP = Plan<LOGN, E>::NP;
+    asm volatile("" : "+v"(tid));
+    double twa[TWREGS], twb[TWREGS];
+    load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
+    if constexpr (Plan<LOGN, E>::R[NP - 1] != 1) {
+#pragma unroll
+        for (int it = 0; it < E; it += 2)
+            pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(in[it], in[it + 1]);
+        wave_sync();
+    }
+    inv_pass<LOGN, E, NP - 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, in);
+    if constexpr (NP > 4) {
+        inv_pass<LOGN, E, 3>(lds, st, row, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twa, twb, m, pr, C);
+        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twa, twb, m, pr, C);
+    } else {
+        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twa, twb, m, pr, C);
+        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twb, twa, m, pr, C);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Key switch of one (unit, prime) per workgroup: the dnum digits lifted and transformed one after the
+// other, each multiplied with its two key rows into two sums in registers, and the sums transformed back.
+// The transformed digits never reach memory (24 of 35 rows per unit of traffic less) and five transforms follow
+// each other without a launch between them.  Bound by vector issue (72 % busy; operands of the whole kernel
+// taken out it is 10 % faster): 1024 threads with eight elements each, because a row is then 16 registers and the
+// two sums, the row, its factors and the next digit's words fit 128.  768 units at N = 8192, three digits, four primes:
+// 284 + 376 us for the mod-up and inner product launches, 383 us here.
+// ---------------------------------------------------------------------------
+template <int LOGN, int E, bool GALOIS, int ALPHA>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const uint64_t *__restrict__ key, StInvF64 st,
+              const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C,
+              int nwg)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    constexpr int T = (1 << LOGN) / E;
+    const int tid = threadIdx.x, L = C->L, dnum = C->dnum;
+    int p = blockIdx.x;
+    int wg = xcd_row(p, nwg, L);
+    auto at = [&](int it) { return GALOIS ? chunk_elem<E>(tid, it) : tid + it * T; };
+    uint64_t raw[E][ALPHA];
+    auto fetch = [&](int b, int j) {
+        const uint64_t *e = ld.src + (size_t)b * ld.unit_stride + ((size_t)(j * ALPHA) << LOGN);
+#pragma unroll
+        for (int it = 0; it < E; it++)
+#pragma unroll
+            for (int s = 0; s < ALPHA; s++)
+                raw[it][s] = GALOIS ? at32(e + ((size_t)s << LOGN), at(it))
+                                    : at_lane(e + ((size_t)s << LOGN) + it * T, tid);
+    };
+    fetch(wg / L, 0);
+    for (;;) {
+        const int r = wg % L, b = wg / L;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        p += (int)gridDim.x;
+        const bool more = p < nwg;
+        const int wg_next = more ? xcd_row(p, nwg, L) : wg;
+        double s0[E], s1[E];
+#pragma unroll
+        for (int it = 0; it < E; it++) s0[it] = s1[it] = 0.0;
+        for (int j = 0; j < dnum; j++) {
+            double x[E];
+            const int row = (b * dnum + j) * L + r;
+#pragma unroll
+            for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, at(it), m, C);
+            fetch(j + 1 < dnum ? b : wg_next / L, j + 1 < dnum ? j + 1 : 0);    // (once too often at the very end)
+            if constexpr (GALOIS) {
+#pragma unroll
+                for (int it = 0; it < E; it++) lds[pad(ld.place(at(it), 1 << LOGN))] = x[it];
+                lds_barrier();
+            }
+            fwd_row<LOGN, E, GALOIS>(lds, x, x, tid, tw, m);
+            const uint64_t *k0 = key + ((size_t)(2 * j * L + r) << LOGN), *k1 = k0 + ((size_t)L << LOGN);
+            int tk = tid;
+            asm volatile("" : "+v"(tk));
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                const int idx = chunk_elem<E>(tk, it);
+                const double v = red(x[it], m);
+                s0[it] += mulmod(v, u64_to_f64(at32(k0, idx)), m);
+                s1[it] += mulmod(v, u64_to_f64(at32(k1, idx)), m);
+            }
+            if (j + 1 < dnum) lds_barrier();
+        }
+        inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
+        lds_barrier();
+        inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
+        if (!more) break;
+        wg = wg_next;
+        lds_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // ct x pt in one kernel: forward transform of a row, product with the prepared plaintext row, inverse
 // transform, the row staying in LDS throughout.  A row crosses memory once in each direction (plus
 // the plaintext row, which all ciphertexts of a call share or stream), where the transforms as two
