@@ -194,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -735,6 +735,36 @@ static bool row_kernels_fit(const cg_ctx *c, size_t rows, bool beside = false)
     return c->logn < 13 || rounds > 2 || (rounds == 2 && beside ? 4 * idle <= 3 * n : 2 * idle <= n);
 }
 
+// Transforms of the operands, tensor product and inverse transforms in one launch: x in coefficients, y in
+// coefficients or (A.yhat) transformed; x_cts, y_cts distinct ciphertexts of each
+template <bool HAT>
+static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t batch, double x_cts,
+                          double y_cts)
+{
+    const size_t nwg = (size_t)batch * c->KL;
+    const double bytes = (double)limb_bytes(c) *
+                         (2.0 * c->k * x_cts + 2.0 * (HAT ? c->KL : c->k) * y_cts + 3.0 * c->KL * batch);
+    ProfScope ps(c, s, KID_MULROW, bytes, (double)nwg);
+#define CG_MULROW(LG, K)                                                                                   \
+    do {                                                                                                  \
+        const unsigned threads = (1u << LG) / 8;                                                          \
+        const unsigned grid = ntt_grid<mul_row_kernel<LG, 8, K, HAT>>(c, nwg, (int)threads);              \
+        if (c->dry) return CG_OK;                                                                         \
+        return launch_kernel(mul_row_kernel<LG, 8, K, HAT>, dim3(grid), dim3(threads), s, A,              \
+                             StInvF64{tens, c->logn}, (const double *)c->tw, (const double *)c->itw,      \
+                             (const DevConst *)c->dc, (int)nwg);                                          \
+    } while (0)
+    switch (c->logn * 10 + c->k) {
+    case 121: CG_MULROW(12, 1);
+    case 122: CG_MULROW(12, 2);
+    case 123: CG_MULROW(12, 3);
+    case 131: CG_MULROW(13, 1);
+    case 132: CG_MULROW(13, 2);
+    case 133: CG_MULROW(13, 3);
+    default: return CG_EINVAL;
+    }
+#undef CG_MULROW
+}
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
 // launch for the roofline report; LB = bytes of one residue row.
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
@@ -746,6 +776,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     // only the a operands are transformed here
     // sum_group: the tensor products of every sum_group consecutive units are summed before the
     // inverse transform and the scaling; out3 then holds batch / sum_group results
+    const bool beside = b_group != 0;      // attention over a cache: beside the other branches of a step
     if (!b_group) { b_group = batch; b_stride = batch; }
     const uint32_t n_a = (batch + a_group - 1) / a_group;
     const uint32_t n_out = sum_group ? batch / sum_group : batch;
@@ -755,6 +786,21 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     double *tens = w.take<double>((size_t)3 * c->KL * batch);
     const double LB = (double)limb_bytes(c), B = batch;
     MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
+    const int all = 1 << 30;
+    if (!sum_group && !(b_ext && a_group > 1) && c->k <= 3 && row_kernels_fit(c, (size_t)batch * c->KL, beside)) {
+        MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
+        if (b_ext) {
+            A.yhat = b_ext;
+            CG_TRY(launch_mul_row<true>(c, s, A, tens, batch, B, B));
+        } else if (a_group == 1) {
+            CG_TRY(launch_mul_row<false>(c, s, A, tens, batch, B, B));
+        } else {
+            // the shared operand transformed once, the other one in the kernel
+            CG_TRY(transform_ext(c, s, src, 2 * (size_t)n_a, ntt));
+            A = MulRowArgs{b2, nullptr, ntt, (int)b_group, (int)b_stride, 1, all, 0, (int)a_group, c->k, c->logn};
+            CG_TRY(launch_mul_row<true>(c, s, A, tens, batch, B, n_a));
+        }
+    } else {
         CG_TRY(transform_ext(c, s, src, polys, ntt));
         // tensor product fused into the inverse transform's load
         const LdInvTensor ld{ntt, b_ext, (int)a_group, (int)n_a, (int)b_group, (int)b_stride, c->logn};
@@ -763,6 +809,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StInvF64{tens, c->logn},
                                          KID_INV_TENSORSUM, tbytes));
         else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
+    }
     const double sbytes = LB * (3.0 * c->KL + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);
 #define CG_SCALE(K) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, scale_kernel<K>, sblocks, tens, out3, (int)n_out * 3, accumulate, c->dc)
@@ -1814,6 +1861,8 @@ static int warm_launch_table(cg_ctx *c)
     double *f = reinterpret_cast<double *>(uintptr_t(1) << 20);
     const double LB = 0.0;
     c->dry_rows = true;
+    CG_TRY(do_mul(c, s, u, u, u, 1, 1, f, 0));
+    CG_TRY(do_mul(c, s, u, u, u, 2, 2, f, 0));
     CG_TRY(do_keyswitch(c, s, u, 0, 0, u, u, 0, u, 0, 0, 0, 1, f));
     CG_TRY(do_keyswitch(c, s, u, 0, 3, u, u, 0, u, 0, 3, 1, 1, f));
     c->dry_rows = false;

@@ -840,6 +840,30 @@ struct MulSrc {
         return (ct < n_a ? cta : ctb) + (((size_t)(2 * idx + comp) * k) << logn);
     }
 };
+// operands of mul_row_kernel: x in coefficients, unit u's at x + (u / x_group) * x_stride + u % x_group (in
+// ciphertexts); y likewise in coefficients, or transformed rows [ciphertext][2][k+l][N]
+struct MulRowArgs {
+    const uint64_t *x, *y;
+    const double *yhat;
+    int x_group, x_stride, x_div, y_group, y_stride, y_div, k, logn;
+    static __device__ __forceinline__ int index(int u, int group, int stride, int div)
+    {
+        u /= div;
+        return u / group * stride + u % group;
+    }
+    __device__ __forceinline__ const uint64_t *x_poly(int u, int c) const
+    {
+        return x + ((size_t)(index(u, x_group, x_stride, x_div) * 2 + c) * k << logn);
+    }
+    __device__ __forceinline__ const uint64_t *y_poly(int u, int c) const
+    {
+        return y + ((size_t)(index(u, y_group, y_stride, y_div) * 2 + c) * k << logn);
+    }
+    __device__ __forceinline__ const double *y_hat(int u, int r, int KL) const
+    {
+        return yhat + ((size_t)(index(u, y_group, y_stride, y_div) * 2 * KL + r) << logn);
+    }
+};
 struct LdMulQ {     // workgroup -> (pp, ciphertext prime i)
     static constexpr int kRaw = 1;
     static constexpr bool kPrefetch = true;
@@ -1367,6 +1391,145 @@ ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const uint64_t *__restrict__ key, StInv
         inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
         lds_barrier();
         inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
+        if (!more) break;
+        wg = wg_next;
+        lds_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Products of ciphertexts, one (unit, prime) per workgroup: transforms of the operands' four polynomials,
+// tensor product and the three inverse transforms in one kernel.  An operand that is there in transformed
+// form already (an a operand shared by several units, a cache with a transformed copy) is read in it.
+// Instead of 101 rows of traffic per product (three launches: ciphertext primes, auxiliary primes, tensor
+// product) 33 reach memory.  The order x0, y0, x1, y1 keeps at most two rows in registers during a transform: x0
+// waits in a second LDS buffer (one workgroup per unit at N = 8192, two at N = 4096), x0 y0 leaves before x1 is
+// transformed.  Bound by vector issue (66 % busy; the lifts to the auxiliary primes are an eighth of it).  768
+// products at N = 8192, three primes: 308 + 644 + 764 us for the three launches, 1119 us here.
+// ---------------------------------------------------------------------------
+// element rows of an operand in coefficients, modulo the prime of the workgroup; loads and arithmetic apart,
+// so that the loads of the next row can be on their way during a transform
+template <int LOGN, int E, int K>
+struct MulRowLoad {
+    static constexpr int T = (1 << LOGN) / E, H = E / 2;
+    uint64_t w[H][K];      // half a row
+    // words of elements it0 .. it0 + H of the polynomial at src.  Modulo a ciphertext prime (r < K) all K
+    // words are row r's: the same line, and the same code
+    __device__ __forceinline__ void fetch(const uint64_t *src, int r, int it0, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < H; i++)
+#pragma unroll
+            for (int q = 0; q < K; q++)
+                w[i][q] = at_lane(src + ((size_t)(r < K ? r : q) << LOGN) + (it0 + i) * T, tid);
+    }
+    __device__ __forceinline__ void finish(double *x, int r, const ModD m, const DevConst *C) const
+    {
+        C = opaque_const(C);
+#pragma unroll
+        for (int i = 0; i < H; i++) {
+            x[i] = r < K ? u64_to_f64(w[i][0]) : LdMulAux<K>::lift(w[i], r - K, m, C);
+        }
+    }
+};
+
+// HAT: 0 both operands in coefficients, 1 the first (x) in coefficients and the second (y) transformed
+template <int LOGN, int E, int K, bool HAT>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, const double *__restrict__ itw_all,
+               const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, H = E / 2;
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    __shared__ double park[HAT ? 1 : 1 << LOGN];
+    const int tid = threadIdx.x;
+    int p = blockIdx.x;
+    int wg = xcd_row(p, nwg, KL);
+    MulRowLoad<LOGN, E, K> ld;
+    // polynomials in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
+    auto poly = [&](int u, int t) {
+        return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
+    };
+    ld.fetch(poly(wg / KL, 0), wg % KL, 0, tid);
+    for (;;) {
+        const int r = wg % KL, u = wg / KL;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        p += (int)gridDim.x;
+        const bool more = p < nwg;
+        const int wg_next = more ? xcd_row(p, nwg, KL) : wg;
+        double keep[E], part[E];
+#pragma unroll
+        for (int it = 0; it < E; it++) keep[it] = part[it] = 0.0;
+        constexpr int NT = HAT ? 2 : 4;
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            double x[E];
+            {
+                MulRowLoad<LOGN, E, K> hi;
+                hi.fetch(poly(u, t), r, H, tid);
+                ld.finish(x, r, m, C);
+                hi.finish(x + H, r, m, C);
+            }
+            fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+            ld.fetch(t + 1 < NT ? poly(u, t + 1) : poly(wg_next / KL, 0), t + 1 < NT ? r : wg_next % KL, 0, tid);
+            double y[E], z[E];
+#pragma unroll
+            for (int it = 0; it < E; it++) x[it] = y[it] = z[it] = red(x[it], m);
+            int n_inv = 0;
+            if constexpr (!HAT) {
+                if (t == 0) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) park[tid + it * T] = x[it];
+                } else if (t == 1) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        y[it] = mulmod(park[tid + it * T], x[it], m);
+                        keep[it] = x[it];
+                    }
+                    n_inv = 1;
+                } else if (t == 2) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        part[it] = mulmod(x[it], keep[it], m);
+                        keep[it] = x[it];
+                    }
+                } else {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        y[it] = part[it] + mulmod(park[tid + it * T], x[it], m);
+                        z[it] = mulmod(keep[it], x[it], m);
+                    }
+                    n_inv = 2;
+                }
+            } else {
+                const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                if (t == 0) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        y[it] = mulmod(x[it], red(at32(y0, chunk_elem<E>(tk, it)), m), m);
+                        keep[it] = x[it];
+                    }
+                } else {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        const double b0 = red(at32(y0, chunk_elem<E>(tk, it)), m), b1 = red(at32(y1, chunk_elem<E>(tk, it)), m);
+                        z[it] = mulmod(x[it], b1, m);
+                        y[it] = mulmod(keep[it], b1, m) + mulmod(x[it], b0, m);
+                    }
+                }
+                n_inv = t + 1;
+            }
+            for (int i = 0; i < n_inv; i++) {
+                inv_row<LOGN, E>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, r, C);
+#pragma unroll
+                for (int it = 0; it < E; it++) y[it] = z[it];
+                if (i + 1 < n_inv) lds_barrier();
+            }
+            if (t + 1 < NT) lds_barrier();
+        }
         if (!more) break;
         wg = wg_next;
         lds_barrier();

@@ -1,0 +1,112 @@
+"""The kernels that take one (unit, prime) through several transforms in a workgroup, at the batches where
+the dispatch changes (a product has 2k + 1 rows, a key switch k + nsp, against 256 compute units) and over several rounds
+of workgroups: bit-compared with the oracle.  Units repeat a few distinct operands, so that every unit of
+a large batch is checked.  Parameter sets: the benchmark's, the smallest ones, and primes of different
+sizes (the lazily reduced values are bounded by the largest prime's size, not by the row's own prime)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from workloads import PRESETS
+from workloads.params import ParamSet
+
+from .bruteforce import ntt_primes
+from .test_gpu_parity import Env, say
+
+MIXED = ParamSet("mixed_n8192_k3", 13,
+                 q=tuple(p for b in (50, 43, 48) for p in ntt_primes(1 << b, 2 << 13, 1)),
+                 p=tuple(ntt_primes((1 << 50) - (1 << 45), 2 << 13, 1)), alpha=1)
+SETS = {"C1": PRESETS["C1"], "C2": PRESETS["C2"], "mixed": MIXED,
+        "k1": ParamSet("n8192_k1", 13, q=tuple(ntt_primes(1 << 50, 2 << 13, 1)),
+                       p=tuple(ntt_primes(1 << 49, 2 << 13, 1)), alpha=1),
+        "k3": ParamSet("n4096_k3", 12, q=tuple(ntt_primes(1 << 50, 2 << 12, 3)),
+                       p=tuple(ntt_primes(1 << 49, 2 << 12, 1)), alpha=1)}
+_envs = {}
+
+
+def _env(name):
+    if name not in _envs:
+        env = Env.__new__(Env)
+        import paper_2602_08798_amd as P
+        from oracle import Oracle
+        prm = SETS[name]
+        env.P, env.name, env.prm, env.ctx, env.orc = P, name, prm, P.Context(prm), Oracle(prm)
+        env.n, env.k, env.qp, env._keys = prm.n, prm.k, list(prm.q) + list(prm.p), {}
+        _envs[name] = env
+    return _envs[name]
+
+
+def _extremes(env, x):
+    """residues at the ends and around the middle of the range of the lift"""
+    Q = int(np.prod([int(p) for p in env.prm.q], dtype=object))
+    for i, m in enumerate(env.prm.q):
+        x[0, 0, i, :6] = [0, m - 1, (Q // 2) % m, (Q // 2 + 1) % m, (m - 1) // 2, (m + 1) // 2]
+        x[1, 1, i, :] = m - 1
+    return x
+
+
+def _tiled(env, x, batch):
+    return env.dev(np.ascontiguousarray(x[np.arange(batch) % len(x)]))
+
+
+# rows of a batch: C2 and mixed 7 per product and 4 per key switch, C1 5 and 3, k1 3 and 2, k3 7 and 4
+@pytest.mark.parametrize("name,batches", [("C2", (18, 19, 36, 37, 55, 63, 64, 74, 150)), ("C1", (25, 26, 43, 120)),
+                                          ("mixed", (19, 74)), ("k1", (43, 260)), ("k3", (37, 80))])
+def test_products_and_relinearisation_at_the_edges_of_the_dispatch(name, batches):
+    env = _env(name)
+    raw, rlk = env.key(20)
+    a, b = _extremes(env, env.cts(10, 3)), _extremes(env, env.cts(11, 2))
+    want = {(i, j): env.orc.mul(a[i], b[j]) for i in range(3) for j in range(2)}
+    relin = {key: env.orc.relin(w, raw) for key, w in want.items()}
+    for batch in batches:
+        say(f"mul and mul_relin {name} batch {batch}")
+        ad, bd = _tiled(env, a, batch), _tiled(env, b, batch)
+        got3 = env.host(env.ctx.mul(ad, bd, batch))
+        got2 = env.host(env.ctx.mul_relin(ad, bd, rlk, batch))
+        for u in range(batch):
+            assert np.array_equal(got3[u], want[u % 3, u % 2]), (name, batch, u)
+            assert np.array_equal(got2[u], relin[u % 3, u % 2]), (name, batch, u)
+
+
+@pytest.mark.parametrize("name,batch,group", [("C2", 66, 3), ("C2", 64, 64), ("C1", 60, 4), ("mixed", 20, 2)])
+def test_products_with_a_shared_operand(name, batch, group):
+    env = _env(name)
+    a, b = _extremes(env, env.cts(12, -(-batch // group))) if batch // group > 1 else env.cts(12, 1), env.cts(13, 2)
+    say(f"mul {name} batch {batch}, one a operand for {group}")
+    got = env.host(env.ctx.mul(env.dev(a), _tiled(env, b, batch), batch, a_group=group))
+    for u in range(batch):
+        assert np.array_equal(got[u], env.orc.mul(a[u // group], b[u % 2])), (name, batch, u)
+
+
+@pytest.mark.parametrize("name,batches", [("C2", (31, 32, 65, 96, 130)), ("C1", (42, 43, 100)), ("mixed", (33,))])
+def test_rotations_at_the_edges_of_the_dispatch(name, batches):
+    env = _env(name)
+    raw, gk = env.key(30)
+    x = _extremes(env, env.cts(31, 3))
+    x[2, :, :, :3] = 0
+    for g in (3, 2 * env.n - 1):
+        want = [env.orc.rotate(x[i], g, raw) for i in range(3)]
+        for batch in batches:
+            say(f"rotate {name} g={g} batch {batch}")
+            got = env.host(env.ctx.rotate(_tiled(env, x, batch), g, gk, batch))
+            for u in range(batch):
+                assert np.array_equal(got[u], want[u % 3]), (name, g, batch, u)
+
+
+def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
+    """one cache ciphertext per head: the query in coefficients times the transformed cache"""
+    from oracle import attention
+    env = _env("C2")
+    heads, d2 = 20, 2
+    raw_rlk, rlk = env.key(70)
+    g = attention.fold_generators(env.n, d2)[0]
+    raw_g, gk = env.key(71)
+    q, kc = env.cts(72, 2), env.cts(73, 3)
+    say(f"decode_scores_ext of {heads} heads, one ciphertext each")
+    ext = env.ctx.empty_ext(heads)
+    env.ctx.cache_extend(_tiled(env, kc, heads), heads, 1, 1, ext)
+    got = env.host(env.ctx.decode_scores_ext(_tiled(env, q, heads), ext, heads, 1, d2, rlk, [gk]))
+    for h in range(heads):
+        want = attention.decode_scores(env.orc, q[h % 2], kc[h % 3], raw_rlk, {g: raw_g}, d2)
+        assert np.array_equal(got[h, 0], want), h
