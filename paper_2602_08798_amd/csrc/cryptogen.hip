@@ -227,35 +227,14 @@ struct ProfScope {
 static void fill_conv(ConvTab &T, const uint64_t *pr, const int *sidx, int ns, const int *tidx, int nt)
 {
     memset(&T, 0, sizeof(T));
-    T.ns = ns;
-    T.nt = nt;
-    for (int i = 0; i < ns; i++) T.sidx[i] = sidx[i];
-    for (int j = 0; j < nt; j++) T.tidx[j] = tidx[j];
     for (int i = 0; i < ns; i++)
         for (int j = i + 1; j < ns; j++) {
             const uint64_t si = pr[sidx[i]], sj = pr[sidx[j]];
             T.inv[i][j] = h_centred(h_inv(si % sj, sj), sj);
         }
-    // digits of floor(S/2): its residue modulo s_i is (s_i - 1)/2 because S = 0 and 2 is invertible
-    uint64_t a[MAXS];
-    for (int j = 0; j < ns; j++) {
-        const uint64_t sj = pr[sidx[j]];
-        uint64_t v = (sj - 1) / 2;
-        for (int i = 0; i < j; i++) {
-            const uint64_t si = pr[sidx[i]];
-            v = h_mul((v + sj - a[i] % sj) % sj, h_inv(si % sj, sj), sj);
-        }
-        a[j] = v;
-        T.half[j] = (double)v;
-    }
     for (int j = 0; j < nt; j++) {
         const uint64_t tj = pr[tidx[j]];
-        uint64_t prod = 1;
-        for (int i = 0; i < ns; i++) {
-            T.s_mod_t[i][j] = h_centred(pr[sidx[i]] % tj, tj);
-            prod = h_mul(prod, pr[sidx[i]] % tj, tj);
-        }
-        T.S_mod_t[j] = h_centred(prod, tj);
+        for (int i = 0; i < ns; i++) T.s_mod_t[i][j] = h_centred(pr[sidx[i]] % tj, tj);
     }
 }
 
@@ -385,12 +364,11 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
     }
     for (int j = 0; j < c->dnum; j++) fill_conv(H.dig[j], c->pr, qi + j * c->alpha, c->alpha, all, c->L);
     fill_conv(H.p2q, c->pr, sp, c->nsp, qi, c->k);
-    for (int r = 0; r < c->L; r++) {
+    for (int r = 0; r < c->k; r++) {
         const uint64_t m = c->pr[r];
         uint64_t P = 1;
         for (int s = 0; s < c->nsp; s++) P = h_mul(P, c->pr[c->k + s] % m, m);
-        H.halfP[r] = (double)h_mul((P + m - 1) % m, h_inv(2, m), m);   // (P-1)/2 mod m, P odd
-        if (r < c->k) H.Pinv_q[r] = h_centred(h_inv(P, m), m);
+        H.Pinv_q[r] = h_centred(h_inv(P, m), m);
     }
     {
         // floor(Q/t) = (Q - (Q mod t)) / t, and Q = 0 modulo q_i: floor(Q/t) = -(Q mod t) t^-1 (mod q_i)

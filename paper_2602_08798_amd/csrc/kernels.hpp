@@ -727,10 +727,11 @@ __device__ __forceinline__ void garner(const ConvTab &T, const ModD *ms, const d
         a[j] = canon(v, mj);
     }
 }
-// x[0..NS) residues, |x_j| <= p -> digits |a_i| <= (s_i - 1)/2.  These balanced digits represent exactly
+// x[0..NS) residues, |x_j| <= 2p -> digits |a_i| <= (s_i - 1)/2.  These balanced digits represent exactly
 // the integers of magnitude at most (S - 1)/2: the centred representative, without the comparison with
 // S/2 and without making the digits canonical.  red() picks the balanced residue exactly here: its
-// quotient x u is off by less than 2^-52 at |x u| = 1/2, and the residues next to p/2 are 2^-51 away.
+// quotient x u is off by less than 1.25 * 2^-52 up to |x u| = 2, and the residues next to an odd multiple of p/2 are
+// 2^-51 away.
 template <int NS>
 __device__ __forceinline__ void garner_balanced(const ConvTab &T, const ModD *ms, const double (&x)[NS],
                                                 double (&a)[NS])
@@ -1663,7 +1664,8 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int to
 }
 
 // mod-down with rounding and the final additions of relinearisation / rotation:
-//   u = floor((A + floor(P/2)) / P) mod Q,  out[b][c] = u (+ add0) (+ add1)
+//   u = floor((A + floor(P/2)) / P) = (A - x) / P mod Q with x the centred residue of A modulo P, in balanced
+//   digits (garner_balanced takes the transforms' results, below 2p);  out[b][c] = u (+ add0) (+ add1)
 // add0: relin -> in3[b][c];  rotate -> sigma_g(in2[b][0]) for c = 0, nothing for c = 1
 // add1: rotate with accumulate -> acc_add[b][c] (the rotated ciphertext itself, or another one)
 struct ModdownArgs {
@@ -1714,13 +1716,12 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
     double xp[2][NSP], dg[2][NSP];
 #pragma unroll
     for (int s = 0; s < NSP; s++) {
-        const ModD mp = C->mod[k + s];
         const double2 x2 = *reinterpret_cast<const double2 *>(src + ((size_t)(k + s) << logn));
-        xp[0][s] = addmod_canon(canon(x2.x, mp), C->halfP[k + s], mp);
-        xp[1][s] = addmod_canon(canon(x2.y, mp), C->halfP[k + s], mp);
+        xp[0][s] = x2.x;
+        xp[1][s] = x2.y;
     }
-    garner<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
-    garner<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
+    garner_balanced<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
+    garner_balanced<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
     int src_idx[2] = {0, 0};
     bool negate[2] = {false, false};
     if (A.galois) {
@@ -1743,35 +1744,34 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
             double v[2];
 #pragma unroll
             for (int e2 = 0; e2 < 2; e2++) {
-                const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner<NSP>(C->p2q, mq, dg[e2], i);
-                v[e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
+                v[e2] = mulmod(ain[e2] - horner<NSP>(C->p2q, mq, dg[e2], i), C->Pinv_q[i], mq);
             }
+            // addends are canonical: with both the value stays below 2^52 until the one reduction at the end
             if (A.add) {
                 const uint64_t *ad = A.add + (size_t)b * A.add_stride;
                 if (A.galois) {
                     if (c == 0) {
 #pragma unroll
                         for (int e2 = 0; e2 < 2; e2++) {
-                            double w = u64_to_f64(ad[((size_t)i << logn) + src_idx[e2]]);
-                            if (negate[e2]) w = (w == 0.0) ? 0.0 : mq.p - w;
-                            v[e2] = addmod_canon(v[e2], w, mq);
+                            const double w = u64_to_f64(ad[((size_t)i << logn) + src_idx[e2]]);
+                            v[e2] += negate[e2] ? -w : w;
                         }
                     }
                     if (A.accumulate) {
                         const uint64_t *aa = A.acc_add + (size_t)b * A.acc_stride;
                         const ulonglong2 w2 =
                             *reinterpret_cast<const ulonglong2 *>(aa + ((size_t)(c * k + i) << logn) + n);
-                        v[0] = addmod_canon(v[0], u64_to_f64(w2.x), mq);
-                        v[1] = addmod_canon(v[1], u64_to_f64(w2.y), mq);
+                        v[0] += u64_to_f64(w2.x);
+                        v[1] += u64_to_f64(w2.y);
                     }
                 } else {
                     const ulonglong2 w2 = *reinterpret_cast<const ulonglong2 *>(ad + ((size_t)(c * k + i) << logn) + n);
-                    v[0] = addmod_canon(v[0], u64_to_f64(w2.x), mq);
-                    v[1] = addmod_canon(v[1], u64_to_f64(w2.y), mq);
+                    v[0] += u64_to_f64(w2.x);
+                    v[1] += u64_to_f64(w2.y);
                 }
             }
-            *reinterpret_cast<ulonglong2 *>(o + ((size_t)i << logn)) = make_ulonglong2(f64_to_u64(v[0]), f64_to_u64(v[1]));
+            *reinterpret_cast<ulonglong2 *>(o + ((size_t)i << logn)) =
+                make_ulonglong2(f64_to_u64(canon(v[0], mq)), f64_to_u64(canon(v[1], mq)));
         }
 }
 
@@ -1784,6 +1784,11 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 // coefficients (and the un-permuted addend) from there.  Base conversion as in moddown_kernel,
 // for the one prime of the row; the special-prime rows are read by the k workgroups of a
 // (ciphertext, component), neighbours on one XCD.
+// a + w or a - w as the top bit of s says
+__device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
+{
+    return a + bits_f64(f64_bits(w) ^ ((uint64_t)(s & 0x80000000u) << 32));
+}
 template <int LOGN, int NSP>
 __global__ void __launch_bounds__(1024, (LOGN <= 13 ? 8 : 4))
 moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
@@ -1839,19 +1844,15 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
             double xp[2][NSP], dg[2][NSP];
 #pragma unroll
             for (int s = 0; s < NSP; s++) {
-                const ModD mp = C->mod[k + s];
-                xp[0][s] = addmod_canon(canon(xs[j][s].x, mp), C->halfP[k + s], mp);
-                xp[1][s] = addmod_canon(canon(xs[j][s].y, mp), C->halfP[k + s], mp);
+                xp[0][s] = xs[j][s].x;
+                xp[1][s] = xs[j][s].y;
             }
-            garner<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
-            garner<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
+            garner_balanced<NSP>(C->p2q, C->mod + k, xp[0], dg[0]);
+            garner_balanced<NSP>(C->p2q, C->mod + k, xp[1], dg[1]);
             const double ain[2] = {as[j].x, as[j].y};
 #pragma unroll
-            for (int e2 = 0; e2 < 2; e2++) {
-                const double ai = addmod_canon(canon(ain[e2], mq), C->halfP[i], mq);
-                const double ri = horner<NSP>(C->p2q, mq, dg[e2], i);
-                v[j][e2] = canon(mulmod(red(ai - ri, mq), C->Pinv_q[i], mq), mq);
-            }
+            for (int e2 = 0; e2 < 2; e2++)
+                v[j][e2] = mulmod(ain[e2] - horner<NSP>(C->p2q, mq, dg[e2], i), C->Pinv_q[i], mq);
         }
         if (j0 + PB < PAIRS) request(j0 + PB);     // the next pairs' operands travel during the LDS reads
 #pragma unroll
@@ -1859,20 +1860,19 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
             const int n = pair_index(j0 + j);
             if (c == 0)
                 for (int r = 0; r < H.n_sum; r++) {
-                    const uint32_t gi = H.ginv[r];
-#pragma unroll
-                    for (int e2 = 0; e2 < 2; e2++) {
-                        const uint32_t e = ((uint32_t)(n + e2) * gi) & (2 * N - 1);
-                        const bool ng = e >= (uint32_t)N;
-                        double w = row[ng ? e - N : e];
-                        if (ng) w = (w == 0.0) ? 0.0 : mq.p - w;
-                        v[j][e2] = addmod_canon(v[j][e2], w, mq);
+                    // terms are canonical up to their sign: four of them between two reductions
+                    uint32_t e = (uint32_t)n * H.ginv[r];
+                    v[j][0] = signed_add(v[j][0], row[e & (N - 1)], e << (31 - LOGN));
+                    e += H.ginv[r];
+                    v[j][1] = signed_add(v[j][1], row[e & (N - 1)], e << (31 - LOGN));
+                    if ((r & 3) == 3) {
+                        v[j][0] = red(v[j][0], mq);
+                        v[j][1] = red(v[j][1], mq);
                     }
                 }
             const double2 own = *reinterpret_cast<const double2 *>(row + n);
-            v[j][0] = addmod_canon(v[j][0], own.x, mq);
-            v[j][1] = addmod_canon(v[j][1], own.y, mq);
-            *reinterpret_cast<ulonglong2 *>(o + n) = make_ulonglong2(f64_to_u64(v[j][0]), f64_to_u64(v[j][1]));
+            *reinterpret_cast<ulonglong2 *>(o + n) =
+                make_ulonglong2(f64_to_u64(canon(v[j][0] + own.x, mq)), f64_to_u64(canon(v[j][1] + own.y, mq)));
         }
     }
 }

@@ -13,17 +13,11 @@ constexpr int MAXDIG = 6;
 
 // Exact conversion of an integer known by its residues modulo the source basis
 // S = {s_0..s_{ns-1}} into residues modulo each target prime, through
-// mixed-radix (Garner) digits:  x = a_0 + s_0 (a_1 + s_1 (a_2 + ...)), 0 <= a_i < s_i.
-// The digits order integers lexicographically, so comparing them with the
-// digits of floor(S/2) decides the sign of the centred representative exactly.
+// mixed-radix (Garner) digits:  x = a_0 + s_0 (a_1 + s_1 (a_2 + ...)), 0 <= a_i < s_i for
+// the integer in [0, S), |a_i| <= (s_i - 1)/2 (all s_i odd) for the centred one.
 struct ConvTab {
-    int ns, nt;
-    int sidx[MAXS];              // prime index of s_i
-    int tidx[MAXT];              // prime index of target j
     double inv[MAXS][MAXS];      // inv[i][j] = s_i^-1 mod s_j for i < j (centred)
-    double half[MAXS];           // mixed-radix digits of floor(S/2)
     double s_mod_t[MAXS][MAXT];  // s_i mod t_j (centred)
-    double S_mod_t[MAXT];        // S mod t_j (centred)
 };
 
 struct DevConst {
@@ -42,8 +36,7 @@ struct DevConst {
     ConvTab b2q;              // auxiliary basis -> Q, centred
     double Qinv_b[MAXS];      // Q^-1 mod b_j (centred)
     ConvTab dig[MAXDIG];      // digit j (alpha primes) -> all k+nsp primes, non-centred
-    ConvTab p2q;              // special primes -> Q, non-centred
-    double halfP[MAXT];       // floor(P/2) mod each of the k+nsp primes (canonical)
+    ConvTab p2q;              // special primes -> Q, centred
     double Pinv_q[MAXS];      // P^-1 mod q_i (centred)
     double delta_q[MAXS];     // floor(Q/t) mod q_i (centred): the scale of a plaintext inside a ciphertext
 };
