@@ -194,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -642,6 +642,42 @@ static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t 
     }
 }
 
+// mod-up, summed inner products and inverse transforms in one launch
+static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T,
+                             uint32_t n_rot, double *acc, uint32_t batch)
+{
+    const size_t nwg = (size_t)batch * c->L;
+    const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L * n_rot);
+    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)nwg);
+#define CG_KSSUMROW(LG)                                                                                        \
+    do {                                                                                                      \
+        const unsigned threads = (1u << LG) / 8;                                                              \
+        const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8, 1>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
+        if (c->dry) return CG_OK;                                                                             \
+        return launch_kernel(ks_sum_row_kernel<LG, 8, 1>, dim3(grid), dim3(threads), s,                       \
+                             LdModup<false, 1>{src, src_stride, 0, c->logn}, T, (int)n_rot, (int)batch,       \
+                             StInvF64{acc, c->logn}, (const double *)c->tw, (const double *)c->itw,           \
+                             (const DevConst *)c->dc, (int)nwg);                                              \
+    } while (0)
+    switch (c->logn) {
+    case 12: CG_KSSUMROW(12);
+    case 13: CG_KSSUMROW(13);
+    default: return CG_EINVAL;
+    }
+#undef CG_KSSUMROW
+}
+// As row_kernels_fit, with two fifths of the units idle at most and from the fourth round on: the launches it
+// replaces spread over the chip in finer pieces.  N = 8192, us for 7 rotations and the mod-down, three launches / one:
+// 24 ciphertexts 50 / 67, 36: 68 / 71, 48: 85 / 76, 64: 100 / 83, 80: 125 / 148, 1536: 2179 / 1927; 3 rotations, 36: 56 / 55,
+// 48: 69 / 59, 1536: 1798 / 1503.  N = 4096, 7 rotations, 36: 33 / 34, 48: 38 / 36, 1536: 625 / 575.
+static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
+{
+    if (c->logn > 13 || c->alpha != 1) return false;
+    if (c->dry) return c->dry_rows;
+    const size_t n = (size_t)c->n_cu, rows = (size_t)batch * c->L, rounds = (rows + n - 1) / n, idle = rounds * n - rows;
+    return c->logn < 13 ? 2 * rows >= n : rounds > 3 || 5 * idle <= 2 * n;
+}
+
 // mod-down of a summed series of rotations, one output row per workgroup
 static int launch_moddown_sum(cg_ctx *c, hipStream_t s, double bytes, size_t batch, const ModdownArgs &A,
                               const ModdownHoist &H)
@@ -825,7 +861,7 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 
 // mod-up, inner product with the key and inverse transforms in one launch
 static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
-                         const uint64_t *key, double *acc, uint32_t batch)
+                         const double *key, double *acc, uint32_t batch)
 {
     const size_t nwg = (size_t)batch * c->L;
     const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L);
@@ -850,7 +886,7 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
 }
 // key switch of one ring element per unit (src + b*src_stride), then the final additions
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
-                        const uint64_t *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
+                        const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
                         uint32_t galois_inv, int accumulate, uint32_t batch, void *ws,
                         const uint64_t *acc_add = nullptr, size_t acc_stride = 0)
 {
@@ -890,7 +926,7 @@ static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *r
                     void *ws)
 {
     const size_t ct3 = (size_t)3 * c->k * c->N;
-    return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const uint64_t *>(rlk), out2,
+    return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
                         (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws);
 }
 
@@ -911,7 +947,7 @@ static int do_rotate(cg_ctx *c, hipStream_t s, const uint64_t *in2, uint32_t g, 
     const size_t ct2 = (size_t)2 * c->k * c->N;
     if (!in_stride) in_stride = ct2;
     if (!out_stride) out_stride = ct2;
-    return do_keyswitch(c, s, in2 + (size_t)c->k * c->N, in_stride, g, static_cast<const uint64_t *>(gk), out2,
+    return do_keyswitch(c, s, in2 + (size_t)c->k * c->N, in_stride, g, static_cast<const double *>(gk), out2,
                         out_stride, in2, in_stride, inv_mod_pow2(g, 2u * c->N), accumulate, batch, ws, acc_add,
                         acc_stride);
 }
@@ -941,7 +977,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
         ModdownHoist H{};
         for (uint32_t i = 0; i < nr; i++) {
             T.g[i] = gs[i0 + i];
-            T.key[i] = static_cast<const uint64_t *>(keys[i0 + i]);
+            T.key[i] = static_cast<const double *>(keys[i0 + i]);
             H.ginv[i] = inv_mod_pow2(gs[i0 + i], 2u * c->N);
         }
         H.rot_batch = (int)batch;
@@ -982,19 +1018,25 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     Bump w = bump(c, ws);
     uint64_t *dig = w.take<uint64_t>((size_t)c->dnum * c->L * batch);
     double *acc = w.take<double>((size_t)2 * c->L * batch);
-    CG_TRY(launch_modup(c, s, in2 + (size_t)c->k * c->N, in_stride, 0, batch, dig));
     HoistTab T{};
     ModdownHoist H{};
     for (uint32_t i = 0; i < n_rot; i++) {
         T.g[i] = gs[i];
-        T.key[i] = static_cast<const uint64_t *>(keys[i]);
+        T.key[i] = static_cast<const double *>(keys[i]);
         H.ginv[i] = inv_mod_pow2(gs[i], 2u * c->N);
     }
     H.n_sum = (int)n_rot;
-    const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
-    CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
-    const size_t irows = (size_t)batch * 2 * c->L;
-    CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64, LB * 2.0 * irows));
+    const uint64_t *c1 = in2 + (size_t)c->k * c->N;
+    if (ks_sum_row_wins(c, batch)) {
+        CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
+    } else {
+        CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig));
+        const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
+        CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
+        const size_t irows = (size_t)batch * 2 * c->L;
+        CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64,
+                          LB * 2.0 * irows));
+    }
     ModdownArgs A{acc, out2, out_stride, in2, in_stride, 1u, 1, (int)batch, in2, in_stride};
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
     return launch_moddown_sum(c, s, LB * (2.0 * c->L + 4.0 * c->k) * B, batch, A, H);
@@ -1070,7 +1112,7 @@ extern "C" int cg_ksk_prepare(cg_ctx *c, void *stream, const uint64_t *raw, void
 {
     CG_REQUIRE(c && ptrs_ok({raw, ksk}));
     return launch_fwd(c, static_cast<hipStream_t>(stream), (size_t)c->dnum * 2 * c->L,
-                      LdRowsU64{raw, nullptr, c->L, c->logn}, StU64{static_cast<uint64_t *>(ksk), c->logn},
+                      LdRowsU64{raw, nullptr, c->L, c->logn}, StF64Red{static_cast<double *>(ksk), c->logn},
                       KID_FWD_ROWS, 4.0 * limb_bytes(c) * c->dnum * c->L);
 }
 
@@ -1841,14 +1883,19 @@ static int warm_launch_table(cg_ctx *c)
     c->dry_rows = true;
     CG_TRY(do_mul(c, s, u, u, u, 1, 1, f, 0));
     CG_TRY(do_mul(c, s, u, u, u, 2, 2, f, 0));
-    CG_TRY(do_keyswitch(c, s, u, 0, 0, u, u, 0, u, 0, 0, 0, 1, f));
-    CG_TRY(do_keyswitch(c, s, u, 0, 3, u, u, 0, u, 0, 3, 1, 1, f));
+    CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, 1, f));
+    CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, 1, f));
+    {
+        const uint32_t gs1[1] = {3};
+        const void *const keys1[1] = {f};
+        CG_TRY(do_rotate_sum(c, s, u, 0, 1, gs1, keys1, u, 0, 1, f));
+    }
     c->dry_rows = false;
     for (uint32_t batch : {1u, 4096u}) {
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0));
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0, 0, 0, nullptr, 1));
-        CG_TRY(do_keyswitch(c, s, u, 0, 0, u, u, 0, u, 0, 0, 0, batch, f));
-        CG_TRY(do_keyswitch(c, s, u, 0, 3, u, u, 0, u, 0, 3, 1, batch, f));
+        CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, batch, f));
+        CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, batch, f));
         {
             const uint32_t gs1[1] = {3};
             const void *const keys1[1] = {f};

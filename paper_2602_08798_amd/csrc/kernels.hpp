@@ -185,6 +185,7 @@ template <class T> __device__ __forceinline__ T at32(const T *base, int idx)
     return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (uint32_t)idx * (uint32_t)sizeof(T));
 }
 
+typedef double cg_double2v __attribute__((ext_vector_type(2)));
 template <class T> __device__ __forceinline__ void put32(T *base, int idx, T v)
 {
     *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + (uint32_t)idx * (uint32_t)sizeof(T)) = v;
@@ -1009,14 +1010,14 @@ struct LdInvU64 {
 struct LdInvTensor;
 template <> struct inv_wide<LdInvTensor> { static constexpr bool value = true; };
 
-// Transformed digits and prepared keys are canonical uint64 residues: one form for the loaders that
-// take them as doubles and for the integer accumulation of ks_sum_kernel.  Two canonical factors
-// give products below 0.875 p, so up to six of them sum to less than 8 p.
+// Transformed digits in memory are canonical uint64 residues, prepared keys centred residues as doubles: the
+// kernels that sum in FP64 take keys as they are, and the integer accumulation of ks_sum_kernel makes integers of
+// them once for several ciphertexts.  A canonical times a centred factor gives a product below 0.7 p.
 template <int DNUM> __device__ __forceinline__ double inner_product(const uint64_t *raw, const ModD m)
 {
     double s = 0.0;
 #pragma unroll
-    for (int j = 0; j < DNUM; j++) s += mulmod(u64_to_f64(raw[2 * j]), u64_to_f64(raw[2 * j + 1]), m);
+    for (int j = 0; j < DNUM; j++) s += mulmod(u64_to_f64(raw[2 * j]), bits_f64(raw[2 * j + 1]), m);
     return s;
 }
 
@@ -1026,7 +1027,7 @@ struct LdInvKsInner {
     static constexpr int kRaw = 2 * DNUM;
     static constexpr bool kPrefetch = false;
     const uint64_t *dig;   // [b][DNUM][L][N]
-    const uint64_t *key;   // [DNUM][2][L][N]
+    const double *key;     // [DNUM][2][L][N]
     int logn;
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return (wg >> 1) % C->L; }
     __device__ __forceinline__ int share(const DevConst *) const { return 2; }
@@ -1041,7 +1042,7 @@ struct LdInvKsInner {
 #pragma unroll
         for (int j = 0; j < DNUM; j++) {
             raw[2 * j] = dig[(((size_t)(b * DNUM + j) * L + r) << logn) + idx];
-            raw[2 * j + 1] = key[(((size_t)(j * 2 + c) * L + r) << logn) + idx];
+            raw[2 * j + 1] = f64_bits(key[(((size_t)(j * 2 + c) * L + r) << logn) + idx]);
         }
     }
     __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
@@ -1057,7 +1058,7 @@ struct LdInvKsInner {
 constexpr int MAXROT = 128;   // rotations per launch
 struct HoistTab {
     uint32_t g[MAXROT];            // Galois element of rotation i
-    const uint64_t *key[MAXROT];   // prepared key of rotation i
+    const double *key[MAXROT];     // prepared key of rotation i
 };
 // inner product of rotation i of unit b: workgroup -> (unit u = i * batch + b, prime r, component c);
 // element = sum_j digit_j[b][r][pi_g(idx)] * key_i[j][c][r][idx]; result row [u][c][r]
@@ -1081,11 +1082,11 @@ struct LdInvKsInnerHoisted {
         const int i = u / batch, b = u - i * batch;
         const uint32_t e = ((2u * (__brev((uint32_t)idx) >> (32 - logn)) + 1u) * T.g[i]) & ((2u << logn) - 1u);
         const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
-        const uint64_t *kb = T.key[i];
+        const double *kb = T.key[i];
 #pragma unroll
         for (int j = 0; j < DNUM; j++) {
             raw[2 * j] = dig[(((size_t)(b * DNUM + j) * L + r) << logn) + sidx];
-            raw[2 * j + 1] = kb[(((size_t)(j * 2 + c) * L + r) << logn) + idx];
+            raw[2 * j + 1] = f64_bits(kb[(((size_t)(j * 2 + c) * L + r) << logn) + idx]);
         }
     }
     __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
@@ -1334,7 +1335,7 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
 // ---------------------------------------------------------------------------
 template <int LOGN, int E, bool GALOIS, int ALPHA>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const uint64_t *__restrict__ key, StInvF64 st,
+ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const double *__restrict__ key, StInvF64 st,
               const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C,
               int nwg)
 {
@@ -1377,15 +1378,19 @@ ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const uint64_t *__restrict__ key, StInv
                 lds_barrier();
             }
             fwd_row<LOGN, E, GALOIS>(lds, x, x, tid, tw, m);
-            const uint64_t *k0 = key + ((size_t)(2 * j * L + r) << LOGN), *k1 = k0 + ((size_t)L << LOGN);
+            const double *k0 = key + ((size_t)(2 * j * L + r) << LOGN), *k1 = k0 + ((size_t)L << LOGN);
             int tk = tid;
             asm volatile("" : "+v"(tk));
+            // a lazy value times a centred key is below 2 p: up to three of them need no reduction before
+            if (dnum > 3) {
+#pragma unroll
+                for (int it = 0; it < E; it++) x[it] = red(x[it], m);
+            }
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 const int idx = chunk_elem<E>(tk, it);
-                const double v = red(x[it], m);
-                s0[it] += mulmod(v, u64_to_f64(at32(k0, idx)), m);
-                s1[it] += mulmod(v, u64_to_f64(at32(k1, idx)), m);
+                s0[it] += mulmod(x[it], at32(k0, idx), m);
+                s1[it] += mulmod(x[it], at32(k1, idx), m);
             }
             if (j + 1 < dnum) lds_barrier();
         }
@@ -1395,6 +1400,100 @@ ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const uint64_t *__restrict__ key, StInv
         if (!more) break;
         wg = wg_next;
         lds_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Summed rotations of one (unit, prime) per workgroup: digits lifted and transformed one after the other; a
+// transformed digit lies in LDS, from where every rotation takes its permuted values, while the keys stream past;
+// the two sums in registers are transformed back.  With digits through memory (ks_sum_kernel) every rotation's
+// gather of every digit goes to L2, and half of them miss it; here the keys are what comes in, and an XCD works with
+// the keys of one or two primes.  Bound by vector issue (71 % busy).  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums and
+// inverse transforms 475 + 899 + 369 us in three launches, 1513 us here.
+// ---------------------------------------------------------------------------
+template <int LOGN, int E, int ALPHA>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ks_sum_row_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, StInvF64 st,
+                  const double *__restrict__ tw_all, const double *__restrict__ itw_all,
+                  const DevConst *__restrict__ C, int nwg)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    constexpr int TH = (1 << LOGN) / E;
+    const int tid = threadIdx.x, L = C->L, dnum = C->dnum;
+    // logical order: prime, then unit; XCD x takes the x-th eighth of it, so that an XCD works with the keys
+    // of one or two primes
+    const int per_xcd = (nwg + 7) >> 3;
+    auto logical = [&](int p) { return (p & 7) * per_xcd + (p >> 3); };
+    const int total = per_xcd * 8;
+    for (int p = blockIdx.x; p < total; p += (int)gridDim.x) {
+        const int wg = logical(p);
+        if (wg >= nwg) continue;
+        const int r = wg / batch, b = wg - r * batch;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        const uint64_t *src = ld.src + (size_t)b * ld.unit_stride;
+        uint64_t raw[E][ALPHA];
+        auto fetch = [&](int j) {
+#pragma unroll
+            for (int it = 0; it < E; it++)
+#pragma unroll
+                for (int s = 0; s < ALPHA; s++)
+                    raw[it][s] = at_lane(src + ((size_t)(j * ALPHA + s) << LOGN) + it * TH, tid);
+        };
+        fetch(0);
+        double s0[E], s1[E];
+#pragma unroll
+        for (int it = 0; it < E; it++) s0[it] = s1[it] = 0.0;
+        for (int j = 0; j < dnum; j++) {
+            {
+                double x[E];
+                const int row = (b * dnum + j) * L + r;
+#pragma unroll
+                for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, tid + it * TH, m, C);
+                fetch(j + 1 < dnum ? j + 1 : j);
+                lds_barrier();      // the previous digit's (or unit's) LDS reads
+                fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+#pragma unroll
+                for (int it = 0; it < E; it += 2)
+                    pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
+                lds_barrier();
+            }
+            int tk = tid;
+            asm volatile("" : "+v"(tk));
+            const int idx0 = chunk_elem<E>(tk, 0);
+            const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
+            for (int i = 0; i < n_rot; i++) {
+                const uint32_t g = T.g[i], eg = __umul24(e0, g);
+                const cg_double2v *k0 =
+                    reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN));
+                const cg_double2v *k1 = k0 + ((size_t)L << (LOGN - 1));
+#pragma unroll
+                for (int q = 0; q < E / 2; q++) {
+                    // evaluation point of the pair's first element under the map; its second's is the neighbour
+                    // that differs in the lowest bit.  (Bits above the row's fall out on the right.)
+                    const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+                    const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
+                    const double x0 = lds[at], x1 = lds[at ^ 1];
+                    const cg_double2v a = at_lane(k0 + 64 * q, idx0 / 2), c = at_lane(k1 + 64 * q, idx0 / 2);
+                    s0[2 * q] += mulmod(x0, a.x, m);
+                    s0[2 * q + 1] += mulmod(x1, a.y, m);
+                    s1[2 * q] += mulmod(x0, c.x, m);
+                    s1[2 * q + 1] += mulmod(x1, c.y, m);
+                }
+                // a term is below 0.6 p
+                if ((i & 7) == 7 || i + 1 == n_rot) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        s0[it] = red(s0[it], m);
+                        s1[it] = red(s1[it], m);
+                    }
+                }
+            }
+        }
+        lds_barrier();
+        inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
+        lds_barrier();
+        inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
     }
 }
 
@@ -1887,7 +1986,7 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
 // transform that formed the sum in its loader (one row per workgroup) read two; what bounds this is
 // the rate at which a compute unit takes operands in from L2.  The products are not reduced one
 // by one: with residues split as 2^25 hi + lo, hi hi', lo lo' and (hi + lo)(hi' + lo') accumulate
-// exactly in 64-bit integers over all terms (at most 128 * 6 of them, each below 2^52) by three
+// exactly in 64-bit integers over all terms (at most 128 * 6 of them, each below 2^53) by three
 // 32 x 32 + 64 multiply-adds, which run at the FP64 rate here, and one modular reduction ends it.
 // N = 8192, 7 rotations, with the inverse transforms: 48 ciphertexts 77 -> 54 us, 12: 33 -> 20 us,
 // one: 32 -> 14 us.
@@ -1913,6 +2012,7 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
     }
     const size_t row = (size_t)L << logn, key_off = ((size_t)r << logn) + idx;
     const uint32_t e0 = 2u * (__brev((uint32_t)idx) >> (32 - logn)) + 1u;
+    const ModD m = C->mod[r];
     uint64_t lo[U][2], mid[U][2], hi[U][2];
 #pragma unroll
     for (int u = 0; u < U; u++)
@@ -1921,12 +2021,12 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
     for (int i = 0; i < n_rot; i++) {
         const uint32_t e = (e0 * T.g[i]) & ((2u << logn) - 1u);
         const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
-        const uint64_t *kb = T.key[i] + key_off;
+        const double *kb = T.key[i] + key_off;
         uint64_t kv[DNUM][2], dv[U][DNUM];
 #pragma unroll
         for (int j = 0; j < DNUM; j++)
 #pragma unroll
-            for (int c = 0; c < 2; c++) kv[j][c] = kb[(size_t)(j * 2 + c) * row];
+            for (int c = 0; c < 2; c++) kv[j][c] = f64_bits(kb[(size_t)(j * 2 + c) * row]);
 #pragma unroll
         for (int u = 0; u < U; u++)
 #pragma unroll
@@ -1936,8 +2036,9 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
             uint32_t kl[2], kh[2];
 #pragma unroll
             for (int c = 0; c < 2; c++) {
-                kl[c] = (uint32_t)kv[j][c] & 0x1FFFFFFu;
-                kh[c] = (uint32_t)(kv[j][c] >> 25);
+                const uint64_t q = f64_to_u64(bits_f64(kv[j][c]) + m.p);     // positive, below 2^51
+                kl[c] = (uint32_t)q & 0x1FFFFFFu;
+                kh[c] = (uint32_t)(q >> 25);
             }
 #pragma unroll
             for (int u = 0; u < U; u++) {
@@ -1951,7 +2052,6 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
             }
         }
     }
-    const ModD m = C->mod[r];
     const double t50 = C->two50[r], t81 = C->two81[r];
 #pragma unroll
     for (int u = 0; u < U; u++) {

@@ -94,6 +94,24 @@ def test_rotations_at_the_edges_of_the_dispatch(name, batches):
                 assert np.array_equal(got[u], want[u % 3]), (name, g, batch, u)
 
 
+@pytest.mark.parametrize("name,batches,n_rot", [("C2", (38, 39, 64, 96, 103, 195), 3), ("C1", (42, 43, 90), 9),
+                                                ("mixed", (39,), 2), ("C2", (48,), 17)])
+def test_rotation_sums_at_the_edges_of_the_dispatch(name, batches, n_rot):
+    """also more rotations than are summed between two reductions"""
+    env = _env(name)
+    n = env.n
+    gs = ([2 * n - 1, 3, 1, 2 * n - 3] + [pow(3, 5 * i + 2, 2 * n) for i in range(n_rot)])[:n_rot]
+    keys = [env.key(40 + i % 3) for i in range(n_rot)]
+    x = _extremes(env, env.cts(41, 3))
+    x[2, :, :, ::3] = 0
+    want = [env.orc.rotate_sum_hoisted(x[i], gs, {g: keys[i][0] for i, g in enumerate(gs)}) for i in range(3)]
+    for batch in batches:
+        say(f"rotate_sum_hoisted {name} batch {batch}, {n_rot} rotations")
+        got = env.host(env.ctx.rotate_sum_hoisted(_tiled(env, x, batch), gs, [k[1] for k in keys], batch))
+        for u in range(batch):
+            assert np.array_equal(got[u], want[u % 3]), (name, batch, u)
+
+
 def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
     """one cache ciphertext per head: the query in coefficients times the transformed cache"""
     from oracle import attention
