@@ -194,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_FWD_MULEXT, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "ntt_fwd<mul,all-rows>"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -720,6 +720,20 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
     const double LB = (double)limb_bytes(c);
     const double in_rows = (double)polys * c->k;
     const StF64 st{dst, c->logn};
+    // Both kinds of rows in one launch while they are at most two per compute unit (one at N = 16384, where a row takes a
+    // unit's LDS): product and relinearisation, us in two launches / one: N = 8192, one product 61 / 52, 8: 72 / 63, 16:
+    // 84 / 80; N = 4096, 16: 47.7 / 43.1.  Large launches are faster apart (the lifts' code for the plain rows).
+    if (polys * c->KL <= (size_t)c->n_cu * (c->logn < 14 ? 2 : 1)) {
+        const double bytes = LB * (in_rows + (double)polys * c->KL);
+        switch (c->k) {
+        case 1: return launch_fwd(c, s, polys * c->KL, LdMulExt<1>{src}, st, KID_FWD_MULEXT, bytes);
+        case 2: return launch_fwd(c, s, polys * c->KL, LdMulExt<2>{src}, st, KID_FWD_MULEXT, bytes);
+        case 3: return launch_fwd(c, s, polys * c->KL, LdMulExt<3>{src}, st, KID_FWD_MULEXT, bytes);
+        case 4: return launch_fwd(c, s, polys * c->KL, LdMulExt<4>{src}, st, KID_FWD_MULEXT, bytes);
+        case 5: return launch_fwd(c, s, polys * c->KL, LdMulExt<5>{src}, st, KID_FWD_MULEXT, bytes);
+        default: return launch_fwd(c, s, polys * c->KL, LdMulExt<6>{src}, st, KID_FWD_MULEXT, bytes);
+        }
+    }
     CG_TRY(launch_fwd(c, s, polys * c->k, LdMulQ{src}, st, KID_FWD_MULQ, LB * 2.0 * in_rows));
     const double aux_bytes = LB * (in_rows + (double)polys * c->l);
     switch (c->k) {
@@ -801,6 +815,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     const double LB = (double)limb_bytes(c), B = batch;
     MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
     const int all = 1 << 30;
+    const uint32_t parts = 1;
     if (!sum_group && !(b_ext && a_group > 1) && c->k <= 3 && row_kernels_fit(c, (size_t)batch * c->KL, beside)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
         if (b_ext) {
@@ -824,9 +839,9 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
                                          KID_INV_TENSORSUM, tbytes));
         else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
     }
-    const double sbytes = LB * (3.0 * c->KL + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
+    const double sbytes = LB * (3.0 * c->KL * parts + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);
-#define CG_SCALE(K) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, scale_kernel<K>, sblocks, tens, out3, (int)n_out * 3, accumulate, c->dc)
+#define CG_SCALE(K) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, scale_kernel<K>, sblocks, tens, out3, (int)parts, accumulate, c->dc)
     switch (c->k) {
     case 1: CG_SCALE(1); break;
     case 2: CG_SCALE(2); break;

@@ -288,8 +288,8 @@ __device__ __forceinline__ void fetch_row(const LD &ld, int wg, int tid, const D
 // ld.fetch_round / ld.finish, the partial sums joined by ld.join) are marked here.
 template <class LD> struct ld_rounds { static constexpr bool value = false; };
 
-// Loaders that lift kRaw consecutive residue rows to one (ld.row names the first of them) are marked here:
-// row addresses and the target are worked out once per row.
+// Loaders that lift kRaw residue rows to one (row ld.source(target, q) counted from ld.row is word q) are marked
+// here: row addresses and the target are worked out once per row.
 template <class LD> struct ld_lifts { static constexpr bool value = false; };
 
 // Loaders that do not prefetch fetch and finish a row in slices, so that at most about 32 raw
@@ -332,7 +332,7 @@ __device__ __forceinline__ void load_row_now(const LD &ld, int wg, int tid, cons
             for (int i = 0; i < CH; i++)
 #pragma unroll
                 for (int q = 0; q < LD::kRaw; q++)
-                    rw[i][q] = at_lane(row + ((size_t)q << LOGN) + (c0 + i) * T, tid);
+                    rw[i][q] = at_lane(row + ((size_t)ld.source(j, q) << LOGN) + (c0 + i) * T, tid);
             // the constants are read anew for every slice: kept from slice to slice they do not fit the
             // scalar registers and push the row out of the vector registers
             const DevConst *Cs = opaque_const(C);
@@ -903,6 +903,7 @@ struct LdMulAux {
     }
     __device__ __forceinline__ const uint64_t *row(int wg, const DevConst *C) const { return src.poly(wg / C->l, K); }
     __device__ __forceinline__ int target(int wg, const DevConst *C) const { return wg % C->l; }
+    static __device__ __forceinline__ int source(int, int q) { return q; }
     static __device__ __forceinline__ double lift(const uint64_t *raw, int j, const ModD mb, const DevConst *C)
     {
         double x[K], dg[K];
@@ -915,6 +916,32 @@ struct LdMulAux {
     __device__ __forceinline__ double finish(const uint64_t *, int, int, const ModD, const DevConst *) const { return 0.0; }
 };
 template <int K> struct ld_lifts<LdMulAux<K>> { static constexpr bool value = true; };
+
+// Both kinds of rows in one launch, for launches that leave compute units free: workgroup -> (pp, prime r of the k + l).
+// All K words of a row modulo a ciphertext prime are that row's own: the same line, and the same code.
+template <int K>
+struct LdMulExt {
+    static constexpr int kRaw = K;
+    static constexpr bool kPrefetch = false;
+    static constexpr bool kScatter = false;
+    MulSrc src;
+    __device__ __forceinline__ int prime(int wg, const DevConst *) const { return wg % (2 * K + 1); }
+    __device__ __forceinline__ int share(const DevConst *) const { return 2 * K + 1; }
+    __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const
+    {
+        return src.dst_poly(wg / (2 * K + 1)) * (2 * K + 1) + wg % (2 * K + 1);
+    }
+    __device__ __forceinline__ const uint64_t *row(int wg, const DevConst *) const { return src.poly(wg / (2 * K + 1), K); }
+    __device__ __forceinline__ int target(int wg, const DevConst *) const { return wg % (2 * K + 1); }
+    static __device__ __forceinline__ int source(int r, int q) { return r < K ? r : q; }
+    static __device__ __forceinline__ double lift(const uint64_t *raw, int r, const ModD m, const DevConst *C)
+    {
+        return r < K ? u64_to_f64(raw[0]) : LdMulAux<K>::lift(raw, r - K, m, C);
+    }
+    __device__ __forceinline__ void fetch(int, int, const DevConst *, uint64_t *) const {}
+    __device__ __forceinline__ double finish(const uint64_t *, int, int, const ModD, const DevConst *) const { return 0.0; }
+};
+template <int K> struct ld_lifts<LdMulExt<K>> { static constexpr bool value = true; };
 
 // key-switch mod-up: workgroup -> (unit b, digit j, target prime r); the digit is
 // the integer in [0,Q_j) formed by ALPHA rows of the source ring element, reduced
@@ -1513,23 +1540,20 @@ template <int LOGN, int E, int K>
 struct MulRowLoad {
     static constexpr int T = (1 << LOGN) / E, H = E / 2;
     uint64_t w[H][K];      // half a row
-    // words of elements it0 .. it0 + H of the polynomial at src.  Modulo a ciphertext prime (r < K) all K
-    // words are row r's: the same line, and the same code
+    // words of elements it0 .. it0 + H of the polynomial at src, as LdMulExt takes them
     __device__ __forceinline__ void fetch(const uint64_t *src, int r, int it0, int tid)
     {
 #pragma unroll
         for (int i = 0; i < H; i++)
 #pragma unroll
             for (int q = 0; q < K; q++)
-                w[i][q] = at_lane(src + ((size_t)(r < K ? r : q) << LOGN) + (it0 + i) * T, tid);
+                w[i][q] = at_lane(src + ((size_t)LdMulExt<K>::source(r, q) << LOGN) + (it0 + i) * T, tid);
     }
     __device__ __forceinline__ void finish(double *x, int r, const ModD m, const DevConst *C) const
     {
         C = opaque_const(C);
 #pragma unroll
-        for (int i = 0; i < H; i++) {
-            x[i] = r < K ? u64_to_f64(w[i][0]) : LdMulAux<K>::lift(w[i], r - K, m, C);
-        }
+        for (int i = 0; i < H; i++) x[i] = LdMulExt<K>::lift(w[i], r, m, C);
     }
 };
 
@@ -1723,24 +1747,26 @@ constexpr int PW_THREADS = 256;
 // exact round(t e / Q) mod Q from e known modulo Q and the auxiliary basis:
 //   r = centred (t e mod Q);  y = (t e - r) / Q computed modulo each b_j;
 //   y is below B/2 in magnitude, so its centred lift from the auxiliary basis is exact.
-// tens[b*3+c][r][n] (lazy, coefficient order) -> out[b][c][i][n] canonical uint64;
+// tens[(b*parts+q)*3+c][r][n], summed over q (lazy, coefficient order) -> out[b][c][i][n] canonical uint64;
 // acc != 0 adds the result to what out already holds (sum of products).
 template <int K>
 __global__ void __launch_bounds__(PW_THREADS)
-scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int total_polys, int acc,
+scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int parts, int acc,
              const DevConst *__restrict__ C)
 {
     constexpr int L = K + 1;
-    const int logn = C->logn, N = 1 << logn;
-    const size_t gid = (size_t)blockIdx.x * PW_THREADS + threadIdx.x;
-    const int n = (int)(gid & (N - 1));
-    const int bc = (int)(gid >> logn);
-    if (bc >= total_polys) return;
-    const double *src = tens + (((size_t)bc * (K + L)) << logn) + n;
+    const int logn = C->logn, chunks = (1 << logn) / PW_THREADS;
+    const int bc = (int)blockIdx.x / chunks, n = ((int)blockIdx.x % chunks) * PW_THREADS + (int)threadIdx.x;
+    const double *src = tens + (((size_t)((bc / 3) * parts * 3 + bc % 3) * (K + L)) << logn);
     const double t = C->tmod;
     double e[K + L];
 #pragma unroll
-    for (int i = 0; i < K + L; i++) e[i] = src[(size_t)i << logn];
+    for (int i = 0; i < K + L; i++) e[i] = at32(src + ((size_t)i << logn), n);
+    for (int q = 1; q < parts; q++) {
+        src += (size_t)(3 * (K + L)) << logn;
+#pragma unroll
+        for (int i = 0; i < K + L; i++) e[i] = red(e[i], C->mod[i]) + at32(src + ((size_t)i << logn), n);
+    }
     double x[K], dq[K], y[L], db[L];
 #pragma unroll
     for (int i = 0; i < K; i++) x[i] = mulmod(e[i], t, C->mod[i]);
