@@ -194,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_FWD_MULEXT, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "ntt_fwd<mul,all-rows>"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -793,6 +793,55 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
     }
 #undef CG_MULROW
 }
+// Sums of products over groups of units in one launch; every group is taken in `parts` parts
+static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t groups,
+                              uint32_t group, uint32_t parts)
+{
+    const size_t nwg = (size_t)groups * parts * c->KL;
+    const double units = (double)groups * group;
+    ProfScope ps(c, s, KID_MULSUMROW, (double)limb_bytes(c) * (4.0 * c->k * units + 3.0 * nwg), units * c->KL);
+#define CG_MULSUMROW(LG, K)                                                                                \
+    do {                                                                                                  \
+        const unsigned threads = (1u << LG) / 8;                                                          \
+        const unsigned grid = ntt_grid<mul_sum_row_kernel<LG, 8, K>>(c, nwg, (int)threads);               \
+        if (c->dry) return CG_OK;                                                                         \
+        return launch_kernel(mul_sum_row_kernel<LG, 8, K>, dim3(grid), dim3(threads), s, A, (int)group,   \
+                             (int)parts, StInvF64{tens, c->logn}, (const double *)c->tw,                  \
+                             (const double *)c->itw, (const DevConst *)c->dc, (int)nwg);                  \
+    } while (0)
+    switch (c->logn * 10 + c->k) {
+    case 121: CG_MULSUMROW(12, 1);
+    case 122: CG_MULSUMROW(12, 2);
+    case 123: CG_MULSUMROW(12, 3);
+    case 131: CG_MULSUMROW(13, 1);
+    case 132: CG_MULSUMROW(13, 2);
+    case 133: CG_MULSUMROW(13, 3);
+    default: return CG_EINVAL;
+    }
+#undef CG_MULSUMROW
+}
+// Whether that beats the launches of single transforms and a tensor inverse that walks over the group, and in how many
+// parts.  In transforms of a row: six per unit and two besides in one launch, against four per row and unit spread
+// over the chip, a half per unit of the group in every round of the tensor inverse, 1.2 besides, and a quarter on
+// top for the traffic.  us at N = 8192, three primes, groups x units, three launches / one: 12 x 4 89 / 120, 12 x 8 158 / 170,
+// 16 x 8 235 / 212, 6 x 8 98 / 120, 3 x 8 80 / 76, 4 x 16 140 / 122, 8 x 100 1501 / 1222; N = 4096, two primes: 12 x 4 44 / 41,
+// 12 x 8 62 / 55, 12 x 64 438 / 295: the model has every one of these on the right side.
+static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint32_t &parts)
+{
+    if (c->logn > 13 || c->k > 3) return false;
+    if (c->dry) return c->dry_rows;
+    const double n = c->n_cu, base = (double)groups * c->KL;
+    double best = 1e30;
+    uint32_t best_parts = 1;
+    for (uint32_t q = 1; q <= group && q <= 64; q++) {
+        const double t = std::ceil(base * q / n) * (6.0 * ((group + q - 1) / q) + 2.0);
+        if (t < best) { best = t; best_parts = q; }
+    }
+    if (best >= 1.25 * (4.0 * base * group / n + 0.5 * group * std::ceil(3.0 * base / n) + 1.2)) return false;
+    parts = best_parts;
+    return true;
+}
+
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
 // launch for the roofline report; LB = bytes of one residue row.
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
@@ -815,8 +864,11 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     const double LB = (double)limb_bytes(c), B = batch;
     MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
     const int all = 1 << 30;
-    const uint32_t parts = 1;
-    if (!sum_group && !(b_ext && a_group > 1) && c->k <= 3 && row_kernels_fit(c, (size_t)batch * c->KL, beside)) {
+    uint32_t parts = 1;
+    if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
+        CG_TRY(launch_mul_sum_row(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
+                                  tens, n_out, sum_group, parts));
+    } else if (!sum_group && !(b_ext && a_group > 1) && c->k <= 3 && row_kernels_fit(c, (size_t)batch * c->KL, beside)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
         if (b_ext) {
             A.yhat = b_ext;
@@ -1898,6 +1950,7 @@ static int warm_launch_table(cg_ctx *c)
     c->dry_rows = true;
     CG_TRY(do_mul(c, s, u, u, u, 1, 1, f, 0));
     CG_TRY(do_mul(c, s, u, u, u, 2, 2, f, 0));
+    CG_TRY(do_mul(c, s, u, u, u, 2, 1, f, 0, 0, 0, nullptr, 2));
     CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, 1, f));
     CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, 1, f));
     {

@@ -1660,6 +1660,77 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
     }
 }
 
+// Sums of products over the units of a group, one (group, part of it, prime) per workgroup: the operands of a unit
+// transformed as in mul_row_kernel, the three components summed in registers over the units, one inverse transform of
+// each sum.  What the parts of a group leave is summed by scale_kernel.  The three sums take the registers in
+// which mul_row_kernel brings in the next polynomial, so the loads are exposed (about 50 us a unit at N = 8192, three primes,
+// against 43 there); what it saves is the transformed operands' way through memory, and its parts spread long
+// groups over the chip.  12 groups of 128: 2620 us in three launches, 2126 here; one group of 32: 178 / 75.
+template <int LOGN, int E, int K>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
+                   const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, H = E / 2;
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    __shared__ double park[1 << LOGN];
+    const int tid = threadIdx.x;
+    for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
+        const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
+        const int u_end = g * group + (part + 1) * group / parts;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        double d0[E], d1[E], d2[E];
+#pragma unroll
+        for (int it = 0; it < E; it++) d0[it] = d1[it] = d2[it] = 0.0;
+        for (int u = g * group + part * group / parts; u < u_end; u++) {
+            double keep[E];
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                double x[E];
+                {
+                    const uint64_t *src = (t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1);
+                    MulRowLoad<LOGN, E, K> lo, hi;
+                    lo.fetch(src, r, 0, tid);
+                    hi.fetch(src, r, H, tid);
+                    lo.finish(x, r, m, C);
+                    hi.finish(x + H, r, m, C);
+                }
+                lds_barrier();      // the previous transform's LDS reads
+                fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+#pragma unroll
+                for (int it = 0; it < E; it++) {
+                    x[it] = red(x[it], m);
+                    if (t == 0) park[tid + it * T] = x[it];
+                    if (t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
+                    if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
+                    if (t == 3) {
+                        d1[it] += mulmod(park[tid + it * T], x[it], m);
+                        d2[it] += mulmod(x[it], keep[it], m);
+                    }
+                    if (t == 1 || t == 2) keep[it] = x[it];
+                }
+            }
+            // a unit adds less than 1.2 p
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                d0[it] = red(d0[it], m);
+                d1[it] = red(d1[it], m);
+                d2[it] = red(d2[it], m);
+            }
+        }
+        for (int c = 0; c < 3; c++) {
+            lds_barrier();
+            inv_row<LOGN, E>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, r, C);
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                d0[it] = d1[it];
+                d1[it] = d2[it];
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // ct x pt in one kernel: forward transform of a row, product with the prepared plaintext row, inverse
 // transform, the row staying in LDS throughout.  A row crosses memory once in each direction (plus

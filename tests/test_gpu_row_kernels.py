@@ -79,6 +79,22 @@ def test_products_with_a_shared_operand(name, batch, group):
         assert np.array_equal(got[u], env.orc.mul(a[u // group], b[u % 2])), (name, batch, u)
 
 
+@pytest.mark.parametrize("name,shapes", [("C2", ((1, 32), (3, 7), (1, 75))), ("C1", ((4, 16), (12, 4))),
+                                         ("mixed", ((1, 20),)), ("k1", ((5, 9),)), ("k3", ((2, 11),))])
+def test_sums_of_products_in_parts(name, shapes):
+    """long groups cut into even and uneven parts, the largest residues in every third unit"""
+    env = _env(name)
+    a, b = _extremes(env, env.cts(14, 3)), _extremes(env, env.cts(15, 2))
+    a[1], b[1] = [[[m - 1] * env.n for m in env.prm.q]] * 2, [[[m - 1] * env.n for m in env.prm.q]] * 2
+    for groups, group in shapes:
+        say(f"mul_sum {name}: {groups} groups of {group}")
+        units = np.arange(groups * group)
+        got = env.host(env.ctx.mul_sum(_tiled(env, a, len(units)), _tiled(env, b, len(units)), groups, group))
+        for g in range(groups):
+            us = units[g * group:(g + 1) * group]
+            assert np.array_equal(got[g], env.orc.mul_sum([a[u % 3] for u in us], [b[u % 2] for u in us])), (name, groups, group, g)
+
+
 @pytest.mark.parametrize("name,batches", [("C2", (31, 32, 65, 96, 130)), ("C1", (42, 43, 100)), ("mixed", (33,))])
 def test_rotations_at_the_edges_of_the_dispatch(name, batches):
     env = _env(name)
