@@ -194,13 +194,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -1019,6 +1019,42 @@ static int do_rotate(cg_ctx *c, hipStream_t s, const uint64_t *in2, uint32_t g, 
                         acc_stride);
 }
 
+// inner products, inverse transforms and mod-down of the rotations of a hoisted series in one launch
+static int launch_rot_row(cg_ctx *c, hipStream_t s, const uint64_t *dig, const HoistTab &T, const ModdownArgs &A,
+                          const ModdownHoist &H, uint32_t n_rot)
+{
+    const size_t nwg = (size_t)2 * H.rot_batch * n_rot;
+    const double B = H.rot_batch;
+    ProfScope ps(c, s, KID_ROTROW, (double)limb_bytes(c) * ((c->dnum * c->L + c->k) * B + 2.0 * c->dnum * c->L * n_rot +
+                                                            2.0 * c->k * B * n_rot), (double)nwg);
+#define CG_ROTROW(LG, D)                                                                                   \
+    do {                                                                                                  \
+        const unsigned threads = (1u << LG) / 8;                                                          \
+        const unsigned grid = ntt_grid<rot_row_kernel<LG, 8, D>>(c, nwg, (int)threads);                               \
+        if (c->dry) return CG_OK;                                                                         \
+        return launch_kernel(rot_row_kernel<LG, 8, D>, dim3(grid), dim3(threads), s, dig, T, A, H,        \
+                             (const double *)c->itw, (const DevConst *)c->dc, (int)nwg);                  \
+    } while (0)
+    switch (c->logn * 10 + c->dnum) {
+    case 121: CG_ROTROW(12, 1);
+    case 122: CG_ROTROW(12, 2);
+    case 123: CG_ROTROW(12, 3);
+    case 131: CG_ROTROW(13, 1);
+    case 132: CG_ROTROW(13, 2);
+    case 133: CG_ROTROW(13, 3);
+    default: return CG_EINVAL;
+    }
+#undef CG_ROTROW
+}
+// From half as many workgroups as compute units on.  us, two launches / one: N = 8192, 31 rotations 36 / 55, 63: 59 / 59,
+// 127: 118 / 74; 12 ciphertexts, 3 rotations 41 / 56, 7: 65 / 59; N = 4096, 63 rotations 36 / 33.
+static bool rot_row_wins(const cg_ctx *c, size_t units)
+{
+    if (c->logn > 13 || c->dnum > 3 || c->nsp != 1) return false;
+    if (c->dry) return c->dry_rows;
+    return 4 * units >= (size_t)c->n_cu;
+}
+
 // A series of rotations of each of `batch` ciphertexts (in2 + b*in_stride): out2 + (b*out_per_b + i)
 // ciphertexts receives rotation i (Galois element gs[i], prepared key keys[i]) in the hoisted form:
 // one lift, extension and transform of the digits of c1, then per rotation a permuted inner
@@ -1049,7 +1085,13 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
         }
         H.rot_batch = (int)batch;
         H.out_per_b = (int)out_per_b;
+        // galois != 0 marks the rotation form; the element itself comes from the table
+        ModdownArgs A{acc, out2 + (size_t)i0 * ct2, ct2, in2, in_stride, 1u, 0, (int)((size_t)batch * nr), in2, in_stride};
         const size_t units = (size_t)batch * nr, irows = units * 2 * c->L;
+        if (rot_row_wins(c, units)) {
+            CG_TRY(launch_rot_row(c, s, dig, T, A, H, nr));
+            continue;
+        }
         const double ibytes = LB * (dig_rows * B + 2.0 * c->L * units + 2.0 * dig_rows * nr);
         const StInvF64 ist{acc, c->logn};
 #define CG_KSH(D) rc = launch_inv(c, s, irows, LdInvKsInnerHoisted<D>{dig, T, (int)batch, c->logn}, ist, KID_INV_KSINNER, ibytes)
@@ -1063,8 +1105,6 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
         }
 #undef CG_KSH
         CG_TRY(rc);
-        // galois != 0 marks the rotation form; the element itself comes from the table
-        ModdownArgs A{acc, out2 + (size_t)i0 * ct2, ct2, in2, in_stride, 1u, 0, (int)units, in2, in_stride};
         CG_TRY(launch_moddown<true>(c, s, LB * ((2.0 * c->L + 2.0 * c->k) * units + c->k * B), units, A, H));
     }
     return CG_OK;
@@ -1957,6 +1997,7 @@ static int warm_launch_table(cg_ctx *c)
         const uint32_t gs1[1] = {3};
         const void *const keys1[1] = {f};
         CG_TRY(do_rotate_sum(c, s, u, 0, 1, gs1, keys1, u, 0, 1, f));
+        CG_TRY(do_rotate_hoisted(c, s, u, 0, 1, gs1, keys1, u, 1, 1, f));
     }
     c->dry_rows = false;
     for (uint32_t batch : {1u, 4096u}) {

@@ -186,6 +186,7 @@ template <class T> __device__ __forceinline__ T at32(const T *base, int idx)
 }
 
 typedef double cg_double2v __attribute__((ext_vector_type(2)));
+typedef uint64_t cg_ulong2v __attribute__((ext_vector_type(2)));
 template <class T> __device__ __forceinline__ void put32(T *base, int idx, T v)
 {
     *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + (uint32_t)idx * (uint32_t)sizeof(T)) = v;
@@ -568,6 +569,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     // a storer that adds to what is there has it brought in eight elements at a time, the first eight
     // before the butterflies where registers allow: read one by one between the stores (which might
     // alias), every element would wait for its own trip to memory
+    static_assert(!(last && st_regs<ST>::value) || G == 1, "one group per thread in the last pass");
     constexpr bool adds = last && st_adds<ST>::value;
     static_assert(!adds || (1 << R) % 8 == 0, "eight elements of a group at a time");
     uint64_t old[adds ? 8 : 1];
@@ -623,6 +625,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
                 if (L > 0) lds[pb + pad(c << L)] = v[g][c];
                 else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
             } else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[g][c], old[c % 8], m, C);
+            else if constexpr (st_regs<ST>::value) st.store(c, 0, v[g][c], m);     // (element tid + c * T)
             else st.store(wg, base[g] + (c << L), v[g][c], m, C);
         }
     }
@@ -1885,6 +1888,11 @@ struct ModdownHoist {
     uint32_t ginv[MAXROT];
     int rot_batch, out_per_b, n_sum;
 };
+// a + w or a - w as the top bit of s says
+__device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
+{
+    return a + bits_f64(f64_bits(w) ^ ((uint64_t)(s & 0x80000000u) << 32));
+}
 template <bool HOIST, int NSP>
 __global__ void __launch_bounds__(PW_THREADS)
 moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
@@ -1980,11 +1988,6 @@ moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 // coefficients (and the un-permuted addend) from there.  Base conversion as in moddown_kernel,
 // for the one prime of the row; the special-prime rows are read by the k workgroups of a
 // (ciphertext, component), neighbours on one XCD.
-// a + w or a - w as the top bit of s says
-__device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
-{
-    return a + bits_f64(f64_bits(w) ^ ((uint64_t)(s & 0x80000000u) << 32));
-}
 template <int LOGN, int NSP>
 __global__ void __launch_bounds__(1024, (LOGN <= 13 ? 8 : 4))
 moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
@@ -2069,6 +2072,87 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
             const double2 own = *reinterpret_cast<const double2 *>(row + n);
             *reinterpret_cast<ulonglong2 *>(o + n) =
                 make_ulonglong2(f64_to_u64(canon(v[j][0] + own.x, mq)), f64_to_u64(canon(v[j][1] + own.y, mq)));
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// One component of one rotation of a hoisted series per workgroup, from the transformed digits to the finished
+// ciphertext rows: inner products and inverse transform modulo the special prime, then modulo every ciphertext
+// prime, the division by P following in registers.  The permuted c0 row goes through LDS.  The accumulators (8 rows
+// written and read per rotation at four primes) never reach memory.  Bound by vector issue and the gathers, 13 us a
+// row and compute unit; a serial chain of k + 1 transforms, so it needs half the chip to be busy to pay off.
+// N = 8192, 127 rotations, mod-down included: 12 ciphertexts 1164 -> 675 us, one 118 -> 74 us.
+// ---------------------------------------------------------------------------
+template <int LOGN, int E, int DNUM>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, ModdownHoist H,
+               const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    constexpr int TH = (1 << LOGN) / E, N = 1 << LOGN;
+    const int tid = threadIdx.x, L = C->L, k = C->k, batch = H.rot_batch;
+    for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
+        // a rotation's component for all ciphertexts on one XCD: the key rows come into one L2 and the digits stay in all
+        const int wg = xcd_row(p, nwg, batch), ic = wg / batch, b = wg - ic * batch, c = ic & 1, i = ic >> 1;
+        const uint32_t g = T.g[i], ginv = H.ginv[i];
+        const uint64_t *in = A.add + (size_t)b * A.add_stride;
+        uint64_t *out = A.out + (size_t)(b * H.out_per_b + i) * A.out_stride + ((size_t)(c * k) << LOGN);
+        double xs[E];
+        for (int step = 0; step < L; step++) {
+            const int r = step ? step - 1 : k;
+            const ModD m = C->mod[r];
+            const double *itw = itw_all + ((size_t)r << LOGN);
+            const uint64_t *db = dig + (((size_t)(b * DNUM) * L + r) << LOGN);
+            const cg_double2v *kb =
+                reinterpret_cast<const cg_double2v *>(T.key[i] + (((size_t)c * L + r) << LOGN));
+            double y[E];
+            int tk = tid;
+            asm volatile("" : "+v"(tk));
+            const int idx0 = chunk_elem<E>(tk, 0);
+            const uint32_t eg = __umul24(2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u, g);
+#pragma unroll
+            for (int q = 0; q < E / 2; q++) {
+                const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+                const int at = (int)((__brev(e) >> (31 - LOGN)) & (N - 1u));      // as in ks_sum_row_kernel
+                y[2 * q] = y[2 * q + 1] = 0.0;
+#pragma unroll
+                for (int j = 0; j < DNUM; j++) {
+                    const uint64_t *d = db + ((size_t)(j * L) << LOGN);
+                    const cg_double2v kv = at_lane(kb + ((size_t)(2 * j * L) << (LOGN - 1)) + 64 * q, idx0 / 2);
+                    const cg_ulong2v dv = at32(reinterpret_cast<const cg_ulong2v *>(d), at >> 1);
+                    y[2 * q] += mulmod(u64_to_f64((at & 1) ? dv.y : dv.x), kv.x, m);
+                    y[2 * q + 1] += mulmod(u64_to_f64((at & 1) ? dv.x : dv.y), kv.y, m);
+                }
+                if (DNUM > 1 && (q & 1)) asm volatile("" ::: "memory");      // two pairs' operands at a time: registers
+            }
+            lds_barrier();
+            inv_row<LOGN, E>(lds, y, StRegs{y}, 0, tid, itw, m, r, C);
+            asm volatile("" : "+v"(tk));
+            if (!step) {
+#pragma unroll
+                for (int it = 0; it < E; it++) xs[it] = red(y[it], m);     // centred residue modulo the special prime
+                continue;
+            }
+#pragma unroll
+            for (int it = 0; it < E; it++) y[it] = mulmod(y[it] - xs[it], C->Pinv_q[r], m);
+            if (c == 0) {
+                uint64_t own[E];
+#pragma unroll
+                for (int it = 0; it < E; it++) own[it] = at_lane(in + ((size_t)r << LOGN) + it * TH, tk);
+                lds_barrier();
+#pragma unroll
+                for (int it = 0; it < E; it++) lds[tk + it * TH] = u64_to_f64(own[it]);
+                lds_barrier();
+#pragma unroll
+                for (int it = 0; it < E; it++) {
+                    const uint32_t e = (uint32_t)(tk + it * TH) * ginv;
+                    y[it] = signed_add(y[it], lds[e & (N - 1)], e << (31 - LOGN));
+                }
+            }
+#pragma unroll
+            for (int it = 0; it < E; it++)
+                put32(out + ((size_t)r << LOGN) + it * TH, tk, f64_to_u64(canon(y[it], m)));
         }
     }
 }

@@ -128,6 +128,25 @@ def test_rotation_sums_at_the_edges_of_the_dispatch(name, batches, n_rot):
             assert np.array_equal(got[u], want[u % 3]), (name, batch, u)
 
 
+@pytest.mark.parametrize("name,shapes", [("C2", ((1, 63), (1, 64), (5, 13), (2, 127), (40, 7))), ("C1", ((9, 9), (3, 86))),
+                                         ("mixed", ((3, 22),)), ("k1", ((66, 1), (1, 130)))])
+def test_hoisted_series_at_the_edges_of_the_dispatch(name, shapes):
+    """more rotations than one launch takes, an output stride longer than the series, the largest residues"""
+    env = _env(name)
+    n = env.n
+    x = _extremes(env, env.cts(51, 3))
+    x[2, :, :, ::3] = 0
+    for batch, n_rot in shapes:
+        gs = ([2 * n - 1, 3, 1, 2 * n - 3] + [pow(3, 5 * i + 2, 2 * n) for i in range(n_rot)])[:n_rot]
+        keys = [env.key(40 + i % 3) for i in range(n_rot)]
+        say(f"rotate_hoisted {name} batch {batch}, {n_rot} rotations")
+        got = env.host(env.ctx.rotate_hoisted(_tiled(env, x, batch), gs, [k[1] for k in keys], batch))
+        for i in range(n_rot):
+            want = [env.orc.rotate_hoisted(x[j], gs[i], keys[i][0]) for j in range(min(batch, 3))]
+            for u in range(batch):
+                assert np.array_equal(got[u, i], want[u % 3]), (name, batch, n_rot, u, i)
+
+
 def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
     """one cache ciphertext per head: the query in coefficients times the transformed cache"""
     from oracle import attention
