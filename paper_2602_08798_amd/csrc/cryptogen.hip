@@ -172,6 +172,7 @@ struct cg_ctx {
     std::mutex *occ_mu;
     std::unordered_map<const void *, int> *occ;
     bool dry;             // set-up pass: launches compute their grid and return without launching
+    bool dry_units;                 // while dry: and of whole key switches
     bool dry_rows;                  // while dry: take the kernels of several transforms per workgroup
     int elems, elems_fwd; // elements per thread in the inverse / forward transform kernels (8 or 16)
     // workspace limbs (N * 8 bytes) per unit
@@ -194,13 +195,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -678,6 +679,43 @@ static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
     return c->logn < 13 ? 2 * rows >= n : rounds > 3 || 5 * idle <= 2 * n;
 }
 
+// whole key switches, summed rotations or not, in one launch
+template <int MODE>
+static int launch_ks_unit(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
+                          const HoistTab &T, const ModdownArgs &A, const ModdownHoist &H, double *scratch, double add_rows)
+{
+    const double bytes = (double)limb_bytes(c) * ((3.0 * c->k + add_rows) * A.batch +
+                                                  2.0 * c->dnum * c->L * (MODE == KS_SUM ? H.n_sum : 1));
+    ProfScope ps(c, s, KID_KSUNIT, bytes, (double)A.batch);
+#define CG_KSUNIT(LG)                                                                                         \
+    do {                                                                                                     \
+        const unsigned threads = (1u << LG) / 8;                                                             \
+        const unsigned grid = ntt_grid<ks_unit_kernel<LG, 8, MODE>>(c, (size_t)A.batch, (int)threads);       \
+        if (c->dry) return CG_OK;                                                                            \
+        return launch_kernel(ks_unit_kernel<LG, 8, MODE>, dim3(grid), dim3(threads), s,                      \
+                             LdModup<MODE == KS_ROTATE, 1>{src, src_stride, galois, c->logn}, T, A, H, scratch, \
+                             (const double *)c->tw, (const double *)c->itw, (const DevConst *)c->dc);        \
+    } while (0)
+    switch (c->logn) {
+    case 12: CG_KSUNIT(12);
+    case 13: CG_KSUNIT(13);
+    default: return CG_EINVAL;
+    }
+#undef CG_KSUNIT
+}
+// Whole units are coarse pieces: taken where the last round of workgroups leaves a tenth of the compute units idle at
+// most (N = 8192, relinearisation, us by row / by unit: 600 units 459 / 506, 700: 521 / 520, 900: 672 / 692, 1000: 739 / 711), from
+// two workgroups per unit on at N = 4096 (256 units: 56 / 65, 512: 105 / 96), and where the keys of a prime stay in an XCD's L2,
+// whose workgroups are at different primes (N = 8192, 7 rotations, 2.75 MB: 958 / 970).
+static bool ks_unit_wins(const cg_ctx *c, size_t batch, size_t n_rot)
+{
+    if (c->logn > 13 || c->alpha != 1 || c->nsp != 1) return false;
+    if (c->dry) return c->dry_units;
+    const size_t n = (size_t)c->n_cu, rounds = (batch + n - 1) / n;
+    return 10 * batch >= 9 * rounds * n && (c->logn == 13 || rounds > 1) &&
+           2 * c->dnum * n_rot * limb_bytes(c) <= (size_t)2 << 20;
+}
+
 // mod-down of a summed series of rotations, one output row per workgroup
 static int launch_moddown_sum(cg_ctx *c, hipStream_t s, double bytes, size_t batch, const ModdownArgs &A,
                               const ModdownHoist &H)
@@ -963,6 +1001,14 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     double *acc = w.take<double>((size_t)2 * c->L * batch);
     const double LB = (double)limb_bytes(c), B = batch;
     const double dig_rows = (double)c->dnum * c->L;
+    ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
+    const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
+    if (add && ks_unit_wins(c, batch, 1)) {
+        HoistTab T{};
+        T.key[0] = key;
+        return galois ? launch_ks_unit<KS_ROTATE>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows)
+                      : launch_ks_unit<KS_PLAIN>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows);
+    }
     if (c->alpha == 1 && row_kernels_fit(c, (size_t)batch * c->L)) {
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
@@ -984,8 +1030,6 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 #undef CG_KSI
         CG_TRY(rc);
     }
-    ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
-    const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
     return launch_moddown<false>(c, s, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, batch, A, ModdownHoist{});
 }
 
@@ -1134,6 +1178,8 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     }
     H.n_sum = (int)n_rot;
     const uint64_t *c1 = in2 + (size_t)c->k * c->N;
+    ModdownArgs A{acc, out2, out_stride, in2, in_stride, 1u, 1, (int)batch, in2, in_stride};
+    if (ks_unit_wins(c, batch, n_rot)) return launch_ks_unit<KS_SUM>(c, s, c1, in_stride, 0, T, A, H, acc, 2.0 * c->k);
     if (ks_sum_row_wins(c, batch)) {
         CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
     } else {
@@ -1144,7 +1190,6 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
         CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64,
                           LB * 2.0 * irows));
     }
-    ModdownArgs A{acc, out2, out_stride, in2, in_stride, 1u, 1, (int)batch, in2, in_stride};
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
     return launch_moddown_sum(c, s, LB * (2.0 * c->L + 4.0 * c->k) * B, batch, A, H);
 }
@@ -2000,6 +2045,15 @@ static int warm_launch_table(cg_ctx *c)
         CG_TRY(do_rotate_hoisted(c, s, u, 0, 1, gs1, keys1, u, 1, 1, f));
     }
     c->dry_rows = false;
+    c->dry_units = true;
+    CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, 1, f));
+    CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, 1, f));
+    {
+        const uint32_t gs1[1] = {3};
+        const void *const keys1[1] = {f};
+        CG_TRY(do_rotate_sum(c, s, u, 0, 1, gs1, keys1, u, 0, 1, f));
+    }
+    c->dry_units = false;
     for (uint32_t batch : {1u, 4096u}) {
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0));
         CG_TRY(do_mul(c, s, u, u, u, batch, 1, f, 0, 0, 0, nullptr, 1));

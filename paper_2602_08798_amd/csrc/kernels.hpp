@@ -1433,6 +1433,43 @@ ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const double *__restrict__ key, StInvF6
     }
 }
 
+// A transformed digit (reduced, in LDS) times the keys of n_rot rotations, each at its permuted evaluation points,
+// added to the two sums
+template <int LOGN, int E>
+__device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, int n_rot, int j, int r, int L, int tk,
+                                          const ModD m, double *s0, double *s1)
+{
+    const int idx0 = chunk_elem<E>(tk, 0);
+    const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
+    for (int i = 0; i < n_rot; i++) {
+        const uint32_t g = T.g[i], eg = __umul24(e0, g);
+        const cg_double2v *k0 =
+            reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN));
+        const cg_double2v *k1 = k0 + ((size_t)L << (LOGN - 1));
+#pragma unroll
+        for (int q = 0; q < E / 2; q++) {
+            // evaluation point of the pair's first element under the map; its second's is the neighbour
+            // that differs in the lowest bit.  (Bits above the row's fall out on the right.)
+            const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+            const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
+            const double x0 = lds[at], x1 = lds[at ^ 1];
+            const cg_double2v a = at_lane(k0 + 64 * q, idx0 / 2), c = at_lane(k1 + 64 * q, idx0 / 2);
+            s0[2 * q] += mulmod(x0, a.x, m);
+            s0[2 * q + 1] += mulmod(x1, a.y, m);
+            s1[2 * q] += mulmod(x0, c.x, m);
+            s1[2 * q + 1] += mulmod(x1, c.y, m);
+        }
+        // a term is below 0.6 p
+        if ((i & 7) == 7 || i + 1 == n_rot) {
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                s0[it] = red(s0[it], m);
+                s1[it] = red(s1[it], m);
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Summed rotations of one (unit, prime) per workgroup: digits lifted and transformed one after the other; a
 // transformed digit lies in LDS, from where every rotation takes its permuted values, while the keys stream past;
@@ -1490,35 +1527,7 @@ ks_sum_row_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, St
             }
             int tk = tid;
             asm volatile("" : "+v"(tk));
-            const int idx0 = chunk_elem<E>(tk, 0);
-            const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
-            for (int i = 0; i < n_rot; i++) {
-                const uint32_t g = T.g[i], eg = __umul24(e0, g);
-                const cg_double2v *k0 =
-                    reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN));
-                const cg_double2v *k1 = k0 + ((size_t)L << (LOGN - 1));
-#pragma unroll
-                for (int q = 0; q < E / 2; q++) {
-                    // evaluation point of the pair's first element under the map; its second's is the neighbour
-                    // that differs in the lowest bit.  (Bits above the row's fall out on the right.)
-                    const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
-                    const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
-                    const double x0 = lds[at], x1 = lds[at ^ 1];
-                    const cg_double2v a = at_lane(k0 + 64 * q, idx0 / 2), c = at_lane(k1 + 64 * q, idx0 / 2);
-                    s0[2 * q] += mulmod(x0, a.x, m);
-                    s0[2 * q + 1] += mulmod(x1, a.y, m);
-                    s1[2 * q] += mulmod(x0, c.x, m);
-                    s1[2 * q + 1] += mulmod(x1, c.y, m);
-                }
-                // a term is below 0.6 p
-                if ((i & 7) == 7 || i + 1 == n_rot) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        s0[it] = red(s0[it], m);
-                        s1[it] = red(s1[it], m);
-                    }
-                }
-            }
+            sum_digit<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1);
         }
         lds_barrier();
         inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
@@ -2153,6 +2162,141 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
 #pragma unroll
             for (int it = 0; it < E; it++)
                 put32(out + ((size_t)r << LOGN) + it * TH, tk, f64_to_u64(canon(y[it], m)));
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Key switch of one unit per workgroup, from the ring element to the finished ciphertext: as ks_row_kernel and
+// ks_sum_row_kernel, special prime first, then every ciphertext prime with the division by P and the additions in
+// registers.  The accumulators (L rows of each component written and read again) never reach memory but for the two
+// rows modulo the special prime, and the mod-down launch is gone.  Bound as those kernels are, by vector issue; the
+// addends, asked for after the inverse transform, are exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
+// 588 -> 537, 3 summed rotations 761 -> 680; N = 4096: 166 -> 141, 163 -> 139, 207 -> 160, 7 summed 259 -> 212.
+// ---------------------------------------------------------------------------
+enum KsMode { KS_PLAIN, KS_ROTATE, KS_SUM };
+template <int LOGN, int E, int MODE>
+__global__ void __launch_bounds__((1 << LOGN) / E, (MODE == KS_ROTATE ? 4 : min_waves<LOGN, E>()))
+ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist H, double *scratch,
+               const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    constexpr int TH = (1 << LOGN) / E, N = 1 << LOGN;
+    constexpr bool GALOIS = MODE == KS_ROTATE;
+    const int tid = threadIdx.x, k = C->k, L = C->L, dnum = C->dnum;
+    auto at = [&](int it) { return GALOIS ? chunk_elem<E>(tid, it) : tid + it * TH; };
+    uint64_t raw[E][1];
+    auto fetch = [&](int b, int j) {
+        const uint64_t *e = ld.src + (size_t)b * ld.unit_stride + ((size_t)j << LOGN);
+#pragma unroll
+        for (int it = 0; it < E; it++) raw[it][0] = GALOIS ? at32(e, at(it)) : at_lane(e + it * TH, tid);
+    };
+    fetch(blockIdx.x, 0);
+    for (int b = blockIdx.x; b < A.batch; b += (int)gridDim.x) {
+        const int b_next = b + (int)gridDim.x < A.batch ? b + (int)gridDim.x : b;
+        double *keep = scratch + ((size_t)(2 * b) << LOGN);
+        for (int step = 0; step < L; step++) {
+            const int r = step ? step - 1 : k;
+            const ModD m = C->mod[r];
+            const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+            double s[2][E];
+#pragma unroll
+            for (int it = 0; it < E; it++) s[0][it] = s[1][it] = 0.0;
+            for (int j = 0; j < dnum; j++) {
+                double x[E];
+                const int row = (b * dnum + j) * L + r;
+#pragma unroll
+                for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, at(it), m, C);
+                fetch(j + 1 < dnum || step + 1 < L ? b : b_next, j + 1 < dnum ? j + 1 : 0);
+                lds_barrier();      // the previous reads of other waves' elements
+                if constexpr (GALOIS) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) lds[pad(ld.place(at(it), N))] = x[it];
+                    lds_barrier();
+                }
+                fwd_row<LOGN, E, GALOIS>(lds, x, x, tid, tw, m);
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                if constexpr (MODE != KS_SUM) {
+                    const double *k0 = T.key[0] + ((size_t)(2 * j * L + r) << LOGN), *k1 = k0 + ((size_t)L << LOGN);
+                    if (dnum > 3) {     // as in ks_row_kernel
+#pragma unroll
+                        for (int it = 0; it < E; it++) x[it] = red(x[it], m);
+                    }
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        const int idx = chunk_elem<E>(tk, it);
+                        s[0][it] += mulmod(x[it], at32(k0, idx), m);
+                        s[1][it] += mulmod(x[it], at32(k1, idx), m);
+                    }
+                } else {
+#pragma unroll
+                    for (int it = 0; it < E; it += 2)
+                        pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
+                    lds_barrier();
+                    sum_digit<LOGN, E>(lds, T, H.n_sum, j, r, L, tk, m, s[0], s[1]);
+                }
+            }
+            const uint64_t *own_rows = (MODE == KS_ROTATE ? A.acc_add + (size_t)b * A.acc_stride
+                                                          : A.add + (size_t)b * A.add_stride) + ((size_t)r << LOGN);
+            const uint64_t *c0 = A.add + (size_t)b * A.add_stride + ((size_t)r << LOGN);
+            uint64_t *out = A.out + (size_t)b * A.out_stride + ((size_t)r << LOGN);
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                double xs[E];
+                uint64_t own[E];
+                const bool adds = MODE != KS_ROTATE || A.accumulate;
+                if (MODE == KS_SUM || c) lds_barrier();
+                inv_row<LOGN, E>(lds, s[c], StRegs{s[c]}, 0, tid, itw, m, r, C);
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                if (!step) {        // centred residues modulo the special prime; every thread reads its own back
+#pragma unroll
+                    for (int it = 0; it < E; it++) put32(keep + ((size_t)c << LOGN) + it * TH, tk, red(s[c][it], m));
+                    continue;
+                }
+                // (asked for before the inverse transform they spill)
+#pragma unroll
+                for (int it = 0; it < E; it++) xs[it] = at_lane(keep + ((size_t)c << LOGN) + it * TH, tk);
+                const size_t crow = (size_t)(c * k) << LOGN;
+                if (adds) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) own[it] = at_lane(own_rows + crow + it * TH, tk);
+                }
+                double v[E];
+#pragma unroll
+                for (int it = 0; it < E; it++) v[it] = mulmod(s[c][it] - xs[it], C->Pinv_q[r], m);
+                if (MODE != KS_PLAIN && c == 0) {
+                    uint64_t w[E];
+                    if (MODE == KS_ROTATE) {
+#pragma unroll
+                        for (int it = 0; it < E; it++) w[it] = at_lane(c0 + it * TH, tk);
+                    }
+                    lds_barrier();
+#pragma unroll
+                    for (int it = 0; it < E; it++) lds[tk + it * TH] = u64_to_f64(MODE == KS_ROTATE ? w[it] : own[it]);
+                    lds_barrier();
+                    const int n_sum = MODE == KS_SUM ? H.n_sum : 1;
+                    for (int i = 0; i < n_sum; i++) {
+                        // terms are canonical up to their sign: four of them between two reductions
+                        const uint32_t ginv = MODE == KS_SUM ? H.ginv[i] : A.galois, e0 = (uint32_t)tk * ginv;
+#pragma unroll
+                        for (int it = 0; it < E; it++) {
+                            const uint32_t e = e0 + (uint32_t)(it * TH) * ginv;
+                            v[it] = signed_add(v[it], lds[e & (N - 1)], e << (31 - LOGN));
+                        }
+                        if (MODE == KS_SUM && (i & 3) == 3) {
+#pragma unroll
+                            for (int it = 0; it < E; it++) v[it] = red(v[it], m);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int it = 0; it < E; it++) {
+                    if (adds) v[it] += u64_to_f64(own[it]);
+                    put32(out + crow + it * TH, tk, f64_to_u64(canon(v[it], m)));
+                }
+            }
         }
     }
 }

@@ -147,6 +147,36 @@ def test_hoisted_series_at_the_edges_of_the_dispatch(name, shapes):
                 assert np.array_equal(got[u, i], want[u % 3]), (name, batch, n_rot, u, i)
 
 
+# units against 256 compute units: whole key switches per workgroup from 231 (N = 8192) and 461 (N = 4096) on
+@pytest.mark.parametrize("name,batches", [("C2", (230, 231, 480)), ("C1", (256, 460, 461, 700)), ("mixed", (256,)),
+                                          ("k1", (250,)), ("k3", (512,))])
+def test_key_switches_at_the_edges_of_the_dispatch(name, batches):
+    env = _env(name)
+    n, k = env.n, env.k
+    x = _extremes(env, env.cts(61, 3))
+    x[2, :, :, ::3] = 0
+    y = env.cts(62, 2)
+    d = np.stack([np.concatenate([x[i], y[i % 2, :1]]) for i in range(3)])
+    raw, key = env.key(60)
+    gs = [2 * n - 1, 3, 2 * n - 3, 9, 27][:5 if name == "C1" else 3]
+    keys = [env.key(40 + i % 3) for i in range(len(gs))]
+    g = 5
+    want = {"relin": [env.orc.relin(v, raw) for v in d], "rotate": [env.orc.rotate(v, g, raw) for v in x],
+            "sum": [env.orc.rotate_sum_hoisted(v, gs, {g: keys[i][0] for i, g in enumerate(gs)}) for v in x]}
+    q = np.array(env.prm.q, dtype=np.uint64)[None, None, :, None]
+    want["add"] = [(a + v) % q[0] for a, v in zip(want["rotate"], x)]
+    for batch in batches:
+        say(f"key switches {name} batch {batch}")
+        xd = _tiled(env, x, batch)
+        got = {"relin": env.ctx.relin(_tiled(env, d, batch), key, batch), "rotate": env.ctx.rotate(xd, g, key, batch),
+               "add": env.ctx.rotate(xd, g, key, batch, accumulate=True),
+               "sum": env.ctx.rotate_sum_hoisted(xd, gs, [v[1] for v in keys], batch)}
+        for op, out in got.items():
+            out = env.host(out)
+            for u in range(batch):
+                assert np.array_equal(out[u], want[op][u % 3]), (name, op, batch, u)
+
+
 def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
     """one cache ciphertext per head: the query in coefficients times the transformed cache"""
     from oracle import attention
