@@ -33,9 +33,11 @@
  *   aliasing    outputs must not overlap inputs unless stated.
  *   threads     a context may be used from several host threads as long as
  *               concurrent calls use distinct workspaces; cg_decode_step,
- *               cg_decode_step_ext and cg_decode_step_hoisted use streams and events owned by the context,
+ *               cg_decode_step_ext and cg_decode_step_hoisted use events (and, on any stream but the
+ *               default one, internal streams) owned by the context,
  *               and cg_ntt_forward / cg_ntt_inverse an index table owned by it,
- *               so a context runs one of each of these at a time.
+ *               so a context runs one of each of these at a time.  No call is ordered behind
+ *               another context's call on another stream.
  *
  * Where the paper is cited: "section 4.3" is Auto-Regressive
  * Ciphertext-Ciphertext Multiplication (ARCC), "section 4.4" Encrypted
@@ -282,7 +284,9 @@ int cg_decode_context(cg_ctx *ctx, void *stream, const uint64_t *a_dev, const ui
  * The appended ciphertext is visible to the products when tau / (N/d2) < n_cts.
  * Independent branches run side by side on two internal streams (default priority) that
  * fork from and join back into `stream`, so the call is ordered on `stream` like any other;
- * results are bit-identical to the three calls in sequence.  A context runs one such call
+ * results are bit-identical to the three calls in sequence.  The internal streams are the context's
+ * own; only for calls on the default stream (NULL) they are one pair per GPU, common to its
+ * contexts, whose calls that stream orders already.  A context runs one such call
  * at a time.  ws_dev: cg_decode_step_workspace_bytes(ctx, heads, n_cts) bytes. */
 size_t cg_decode_step_workspace_bytes(const cg_ctx *ctx, uint32_t heads, uint32_t n_cts);
 int cg_decode_step(cg_ctx *ctx, void *stream, const uint64_t *q_dev, const uint64_t *a_dev,

@@ -42,15 +42,18 @@ static int static_scratch_address(int device, void **out)
     return CG_OK;
 }
 
-// Side streams of the one-call decode step, one pair per GPU for all contexts.  The runtime maps
-// streams onto four hardware queues: with a pair per context, the pairs of the third and later
-// contexts of a process landed on the queue of the caller's own stream and the step's branches ran
-// one after the other (12 heads, 512 tokens, N = 8192, four contexts alive: 0.725 ms a step, against
-// 0.515 with one pair).  The pair is created by a device's first context and destroyed with its
-// last.  Calls of several contexts and threads may share it: every call waits for its own fork
-// event and is joined by its own join events, so sharing only orders the branches of different
-// calls.  A call on a capturing stream must not share (the capture would take in other callers'
-// work) and uses the context's own pair.
+// Side streams of the one-call decode step.  Calls on the default stream of a GPU use one pair for all of its
+// contexts, calls on any other stream a pair of the context's own.
+// Why a common pair: the runtime maps streams onto four hardware queues, and with a pair per context the pairs of the
+// third and later contexts of a process came to lie on the queue of the caller's own stream, so that the step's
+// branches ran one after the other (12 heads, 512 tokens, N = 8192, four contexts alive: 0.725 ms a step, against 0.515
+// with one pair).
+// Why only there: a branch waits for everything ahead of it on its side stream, so a common pair puts a call behind
+// whatever earlier users' fork events wait for.  On one and the same stream that is no new order: the
+// stream itself has the later call wait for the earlier one.  Across streams it would be (a step on an idle stream
+// held up, or blocked for good, by what another context's stream waits for), and a capture would take in
+// other callers' work.  The default stream cannot be captured, is there once per GPU and never destroyed.
+// The common pair is created by a device's first context and destroyed with its last.
 struct SidePair {
     hipStream_t stream[2];
     int users;
@@ -177,10 +180,9 @@ struct cg_ctx {
     int elems, elems_fwd; // elements per thread in the inverse / forward transform kernels (8 or 16)
     // workspace limbs (N * 8 bytes) per unit
     int ws_total;
-    // side streams (default priority) and fork/join events for entry points that run independent
-    // branches side by side: the device's shared pair, and a pair of the context's own for calls
-    // on a capturing stream
-    hipStream_t side[2], side_own[2];
+    // side streams (default priority) and fork/join events for entry points that run independent branches side by
+    // side: the device's pair for calls on its default stream, the context's own pair for calls on others
+    hipStream_t side_default[2], side_own[2];
     hipEvent_t ev_fork, ev_join[2];
     // optional per-launch timing with HIP events (benchmark support)
     bool prof_on;
@@ -411,7 +413,7 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         return CG_EHIP;
     }
     bool ok = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;
-    ok = ok && side_acquire(c->device, c->side) && create_pair(c->side_own);
+    ok = ok && side_acquire(c->device, c->side_default) && create_pair(c->side_own);
     for (int i = 0; i < 2 && ok; i++)
         ok = hipEventCreateWithFlags(&c->ev_join[i], hipEventDisableTiming) == hipSuccess;
     if (!ok) {
@@ -438,7 +440,7 @@ extern "C" int cg_destroy(cg_ctx *c)
     for (int i = 0; i < 2; i++)
         if (c->ev_join[i]) (void)hipEventDestroy(c->ev_join[i]);
     destroy_pair(c->side_own);
-    if (c->side[0]) side_release(c->device);
+    if (c->side_default[0]) side_release(c->device);
     if (c->dc) (void)hipFree(c->dc);
     if (c->tw) (void)hipFree(c->tw);
     if (c->itw) (void)hipFree(c->itw);
@@ -1674,9 +1676,7 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     // n_cts: then the append goes first on the caller's stream; otherwise it is a third branch.
     const bool append_first = tau / ((uint32_t)c->N / d2) < n_cts;
     if (append_first) CG_TRY(append(s));
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    CG_HIP(hipStreamIsCapturing(s, &cap));
-    hipStream_t *side = cap == hipStreamCaptureStatusNone ? c->side : c->side_own;
+    hipStream_t *side = s ? c->side_own : c->side_default;
     CG_HIP(hipEventRecord(c->ev_fork, s));
     CG_HIP(hipStreamWaitEvent(side[0], c->ev_fork, 0));
     if (!append_first) CG_HIP(hipStreamWaitEvent(side[1], c->ev_fork, 0));
