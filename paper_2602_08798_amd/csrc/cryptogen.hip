@@ -645,6 +645,19 @@ static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t 
     }
 }
 
+// The kernels that take a (unit, prime) through several transforms in one workgroup work in rounds of one row per compute
+// unit, and a round takes as long for one row as for all of them; the launches of single transforms that they replace
+// spread over the chip in finer pieces.  Taken while no more units than this stay idle in the last round, in 256ths
+// of the compute units, with one, two and three rounds; from the fourth round on it does not matter.
+struct IdleLimits {
+    int one, two, three;
+};
+static bool rounds_pay(const cg_ctx *c, size_t rows, IdleLimits lim)
+{
+    const size_t n = (size_t)c->n_cu, rounds = (rows + n - 1) / n, idle = rounds * n - rows;
+    return rounds > 3 || 256 * idle <= n * (size_t)(rounds == 1 ? lim.one : rounds == 2 ? lim.two : lim.three);
+}
+
 // mod-up, summed inner products and inverse transforms in one launch
 static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T,
                              uint32_t n_rot, double *acc, uint32_t batch)
@@ -669,16 +682,17 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
     }
 #undef CG_KSSUMROW
 }
-// As row_kernels_fit, with two fifths of the units idle at most and from the fourth round on: the launches it
-// replaces spread over the chip in finer pieces.  N = 8192, us for 7 rotations and the mod-down, three launches / one:
-// 24 ciphertexts 50 / 67, 36: 68 / 71, 48: 85 / 76, 64: 100 / 83, 80: 125 / 148, 1536: 2179 / 1927; 3 rotations, 36: 56 / 55,
-// 48: 69 / 59, 1536: 1798 / 1503.  N = 4096, 7 rotations, 36: 33 / 34, 48: 38 / 36, 1536: 625 / 575.
+// us with the mod-down and other keys on every call, three launches / one.  N = 8192, three digits, 7 rotations: 40
+// ciphertexts (96 units idle) 68.9 / 71.7, 42 (88): 75.5 / 72.1, 64: 98 / 81, 107 (84): 165 / 148; 3 rotations, 40: 56.7 / 55.4,
+// 42: 61.4 / 56.6.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 43 (127 idle): 37.7 / 35.3, 86 (254):
+// 50.3 / 52.5, 107 (191): 55.7 / 54.6.  Three digits, 7 rotations: 33 (124 idle) 41.2 / 43.7, 42 (88): 44.8 / 43.0, 72 (224):
+// 62.2 / 67.1, 90 (152): 73.0 / 69.9; six digits: 20 (116) 61.8 / 70.0, 26 (74): 84.0 / 72.7.
 static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
     if (c->dry) return c->dry_rows;
-    const size_t n = (size_t)c->n_cu, rows = (size_t)batch * c->L, rounds = (rows + n - 1) / n, idle = rounds * n - rows;
-    return c->logn < 13 ? 2 * rows >= n : rounds > 3 || 5 * idle <= 2 * n;
+    return rounds_pay(c, (size_t)batch * c->L, c->logn == 13 ? IdleLimits{89, 102, 102}
+                                             : c->dnum <= 2 ? IdleLimits{128, 256, 256} : IdleLimits{84, 176, 256});
 }
 
 // whole key switches, summed rotations or not, in one launch
@@ -786,21 +800,33 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
     }
 }
 
-// Whether the kernels that take a (unit, prime) through several transforms in one workgroup are worth their
-// launch: a round of them over all units takes as long for one row as for n_cu, so at most half the units
-// may idle in the last one (three quarters in an attention call, which runs beside other branches); from the third
-// round on it does not matter.  N = 8192, 3 + 1 primes, product and relinearisation, us by launches of single
-// transforms / by these (7 rows per product): 12 products 78 / 90, 20: 96 / 94, 32: 122 / 110, 42: 144 / 163,
-// 64: 205 / 178, 75: 268 / 251, 150: 503 / 438; chain step of 12 heads (48 products): 686 / 656.  At
-// N = 4096 a unit holds two workgroups and a second round costs less (20 products 52 / 51, 56: 74 / 75, 110:
-// 119 / 108).  A row of 16384 leaves no registers for what these kernels keep.
-static bool row_kernels_fit(const cg_ctx *c, size_t rows, bool beside = false)
+// mul_row_kernel; beside: in an attention call, which runs beside other branches.  us of a product with its scaling, three
+// launches / one.  N = 8192, three primes: 19 products (123 units idle) 66.5 / 63.7, 42 (218): 103 / 119, 52 (148): 125 / 122, 55
+// (127): 130 / 123.  N = 4096, three primes: 20 (116) 37.9 / 39.7, 23 (95): 40.4 / 39.9, 42 (218): 54.9 / 60.5, 49 (169): 67.4 / 62.0;
+// two: 27 (121) 35.8 / 35.6, 58 (222): 51.7 / 53.3, 68 (172): 58.4 / 54.2.  Chain step of 12 heads (48 products, 176 idle in
+// the second round) 686 / 656.  A row of 16384 leaves no registers for what these kernels keep.
+static bool mul_row_wins(const cg_ctx *c, size_t rows, bool beside)
 {
-    if (c->logn > 13) return false;
+    if (c->logn > 13 || c->k > 3) return false;
     if (c->dry) return c->dry_rows;
-    const size_t n = (size_t)c->n_cu, rounds = (rows + n - 1) / n, idle = rounds * n - rows;
-    if (2 * rows < n) return false;
-    return c->logn < 13 || rounds > 2 || (rounds == 2 && beside ? 4 * idle <= 3 * n : 2 * idle <= n);
+    return rounds_pay(c, rows, c->logn == 13 ? IdleLimits{128, beside ? 192 : 128, 256}
+                             : c->k == 3 ? IdleLimits{102, 176, 256} : IdleLimits{128, 256, 256});
+}
+// ks_row_kernel.  A rotation gains less than a relinearisation: its digits are scattered through LDS, with two barriers
+// each and nothing else on the unit to fill them, where the mod-up launch has two workgroups to a unit.  us with the mod-down and
+// another key on every call, three launches / two, rotation and relinearisation.  N = 8192, three digits: 32 units (128 compute
+// units idle) 39.9 / 50.2 and 36.5 / 39.8, 36 (112): 49.1 / 50.9 and 45.3 / 40.6, 42 (88): 51.3 / 52.7, 44 (80): 55.1 / 52.8, 48: 55.6 / 53.4
+// and 51.2 / 42.7, 96 (128): 91 / 99 and 85 / 79, 98 (120): 98.9 / 99.3, 129 (252): 134 / 142 and 129 / 113, 141 (204): 145 / 144, 193:
+// 208 / 192.  Two digits at N = 8192 gain from 44 units (124 idle) on, 44.8 / 41.6.  N = 4096, two digits: 43 (127) 25.6 / 26.4 and
+// 22.9 / 22.3, 44 (124): 27.8 / 26.3, 88 (248): 35.2 / 37.0 and 32.0 / 32.6, 107 (191): 36.8 / 38.0 and 33.6 / 33.2, 128 (128): 39.5 / 39.5,
+// 131: 48 / 40; three digits: 34 (120) 30.8 / 32.3, 42 (88): 30.9 / 32.0, 44 (80): 32.5 / 32.0.
+static bool ks_row_wins(const cg_ctx *c, size_t rows, bool rotation)
+{
+    if (c->logn > 13 || c->alpha != 1) return false;
+    if (c->dry) return c->dry_rows;
+    const int one = !rotation ? 127 : c->dnum <= 2 ? 124 : 84;
+    return rounds_pay(c, rows, c->logn == 13 ? IdleLimits{one, rotation ? 127 : 128, rotation ? 204 : 256}
+                                             : IdleLimits{one, rotation ? 140 : 256, 256});
 }
 
 // Transforms of the operands, tensor product and inverse transforms in one launch: x in coefficients, y in
@@ -908,7 +934,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
         CG_TRY(launch_mul_sum_row(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                   tens, n_out, sum_group, parts));
-    } else if (!sum_group && !(b_ext && a_group > 1) && c->k <= 3 && row_kernels_fit(c, (size_t)batch * c->KL, beside)) {
+    } else if (!sum_group && !(b_ext && a_group > 1) && mul_row_wins(c, (size_t)batch * c->KL, beside)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
         if (b_ext) {
             A.yhat = b_ext;
@@ -1011,7 +1037,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
         return galois ? launch_ks_unit<KS_ROTATE>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows)
                       : launch_ks_unit<KS_PLAIN>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows);
     }
-    if (c->alpha == 1 && row_kernels_fit(c, (size_t)batch * c->L)) {
+    if (ks_row_wins(c, (size_t)batch * c->L, galois != 0)) {
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
         CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));

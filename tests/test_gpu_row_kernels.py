@@ -177,6 +177,27 @@ def test_key_switches_at_the_edges_of_the_dispatch(name, batches):
                 assert np.array_equal(out[u], want[op][u % 3]), (name, op, batch, u)
 
 
+# both sides of the limits for idle units where a rotation's and a sum's differ from a relinearisation's
+@pytest.mark.parametrize("name,batches", [("C2", (42, 43, 97, 140, 141)), ("C1", (43, 44, 123, 124)), ("k3", (42, 44, 83, 90))])
+def test_rotations_and_sums_at_the_limits_for_idle_units(name, batches):
+    env = _env(name)
+    raw, gk = env.key(30)
+    raw2, gk2 = env.key(31)
+    x = _extremes(env, env.cts(33, 3))
+    x[2, :, :, ::3] = 0
+    gs = [2 * env.n - 1, 3]
+    want = {"rotate": [env.orc.rotate(v, 9, raw) for v in x],
+            "sum": [env.orc.rotate_sum_hoisted(v, gs, {gs[0]: raw, gs[1]: raw2}) for v in x]}
+    for batch in batches:
+        say(f"rotate and rotate_sum_hoisted {name} batch {batch}")
+        xd = _tiled(env, x, batch)
+        got = {"rotate": env.host(env.ctx.rotate(xd, 9, gk, batch)),
+               "sum": env.host(env.ctx.rotate_sum_hoisted(xd, gs, [gk, gk2], batch))}
+        for op, out in got.items():
+            for u in range(batch):
+                assert np.array_equal(out[u], want[op][u % 3]), (name, op, batch, u)
+
+
 def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
     """one cache ciphertext per head: the query in coefficients times the transformed cache"""
     from oracle import attention

@@ -1,80 +1,43 @@
 """Which streams the one-call decode step puts its branches on, and what they wait for.  Runs without a GPU: the library's
-host code against a recording stand-in for the runtime (tests/host/hip_runtime_stub.cpp), in a process of its own."""
-import ctypes as C
+host code against a recording stand-in for the runtime."""
 import json
-import os
-import subprocess
 import sys
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from tests.stubbed import DEV as d, Stubbed, run, u32, vp
+
 S1, S2 = 0x1000, 0x2000          # callers' streams (never dereferenced)
 
 
-def _record(stub_path, lib_path):
+def _record(lib):
     """steps of two contexts on several streams -> {name: [(kind, stream, event), ...]}"""
-    stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
-    stub.stub_log_size.restype = C.c_size_t
-    lib = C.CDLL(lib_path)
-    vp, u32 = C.c_void_p, C.c_uint32
-
-    class Params(C.Structure):
-        _fields_ = [("log2n", u32), ("k", u32), ("nsp", u32), ("alpha", u32), ("t", C.c_uint64),
-                    ("q", C.POINTER(C.c_uint64)), ("p", C.POINTER(C.c_uint64))]
-
     from workloads import PRESETS
     prm = PRESETS["C1"]
-    q, p = (C.c_uint64 * prm.k)(*prm.q), (C.c_uint64 * prm.nsp)(*prm.p)
-    raw = Params(prm.log2n, prm.k, prm.nsp, prm.alpha, prm.t, q, p)
-    ctx = []
-    for _ in range(2):
-        h = vp()
-        assert lib.cg_create(C.byref(h), C.byref(raw)) == 0
-        ctx.append(h)
-    d = vp(1 << 20)              # a device address: passed on, never read
+    ctx = [lib.create(prm) for _ in range(2)]
     keys = (vp * 64)(*[1 << 20] * 64)
     d2, blocks = 64, prm.n // 64
 
     def step(c, stream, opens, hoisted):
         heads, n_cts, stride = 2, 1, 2
         tau = blocks if opens else blocks - 1
-        stub.stub_log_clear()
         common = [ctx[c], vp(stream), d, d, d]
         geometry = [u32(heads), u32(n_cts), u32(stride), u32(d2), u32(tau), d, d, d]
         if hoisted:
-            rc = lib.cg_decode_step_hoisted(*common, d, *geometry, u32(3), keys, u32(3), 1, keys, d, d, d)
-        else:
-            rc = lib.cg_decode_step(*common, *geometry, keys, keys, d, d, d)
-        assert rc == 0, rc
-        out = []
-        for i in range(stub.stub_log_size()):
-            kind, s, e = C.c_int(), vp(), vp()
-            stub.stub_log_get(C.c_size_t(i), C.byref(kind), C.byref(s), C.byref(e))
-            out.append((kind.value, s.value or 0, e.value or 0))
-        return out
+            return lib.lib.cg_decode_step_hoisted(*common, d, *geometry, u32(3), keys, u32(3), 1, keys, d, d, d)
+        return lib.lib.cg_decode_step(*common, *geometry, keys, keys, d, d, d)
 
-    got = {}
-    for c in range(2):
-        for stream in (0, S1, S2):
-            for opens in (False, True):
-                for hoisted in (False, True):
-                    got[f"{c},{stream},{int(opens)},{int(hoisted)}"] = step(c, stream, opens, hoisted)
+    got = {f"{c},{stream},{int(opens)},{int(hoisted)}": lib.log(lambda: step(c, stream, opens, hoisted))
+           for c in range(2) for stream in (0, S1, S2) for opens in (False, True) for hoisted in (False, True)}
     for h in ctx:
-        assert lib.cg_destroy(h) == 0
+        assert lib.lib.cg_destroy(h) == 0
     return got
 
 
 @pytest.fixture(scope="module")
 def log(tmp_path_factory):
-    from paper_2602_08798_amd import binding
-    so = str(tmp_path_factory.mktemp("stub") / "stub.so")
-    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so,
-                    os.path.join(ROOT, "tests", "host", "hip_runtime_stub.cpp")], check=True)
-    run = subprocess.run([sys.executable, os.path.abspath(__file__), so, binding._LIB_PATH], capture_output=True,
-                         text=True, cwd=ROOT, env={**os.environ, "PYTHONPATH": ROOT})
-    assert run.returncode == 0, run.stderr
-    return {tuple(int(v) for v in k.split(",")): [tuple(e) for e in v] for k, v in json.loads(run.stdout).items()}
+    got = run(__file__, tmp_path_factory.mktemp("stub"))
+    return {tuple(int(v) for v in k.split(",")): [tuple(e) for e in v] for k, v in got.items()}
 
 
 def _streams(entries, but=None):
@@ -119,4 +82,4 @@ def test_branches_fork_from_and_join_the_callers_stream(log):
 
 
 if __name__ == "__main__":
-    print(json.dumps(_record(sys.argv[1], sys.argv[2])))
+    print(json.dumps(_record(Stubbed(*sys.argv[1:]))))
