@@ -720,14 +720,19 @@ static int launch_ks_unit(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
 #undef CG_KSUNIT
 }
 // Whole units are coarse pieces: taken where the last round of workgroups leaves a tenth of the compute units idle at
-// most (N = 8192, relinearisation, us by row / by unit: 600 units 459 / 506, 700: 521 / 520, 900: 672 / 692, 1000: 739 / 711), from
-// two workgroups per unit on at N = 4096 (256 units: 56 / 65, 512: 105 / 96), and where the keys of a prime stay in an XCD's L2,
-// whose workgroups are at different primes (N = 8192, 7 rotations, 2.75 MB: 958 / 970).
-static bool ks_unit_wins(const cg_ctx *c, size_t batch, size_t n_rot)
+// most, from two workgroups per unit on at N = 4096, and where the keys of a prime stay in an XCD's L2, whose
+// workgroups are at different primes.  us by row / by unit with another key on every call.  N = 8192, three digits, rotations:
+// 231 units 214 / 196, 300: 276 / 369, 461: 450 / 394, 600: 568 / 573, 693: 634 / 581, 768: 699 / 597; 7 summed rotations of 2.75 MB of
+// keys 958 / 970.  N = 4096, two digits, relinearisation: 461 units 99 / 87, 768: 155 / 139.
+// A relinearisation by row is cheaper (no digits scattered, no permuted addend) and has more to lose: three digits at N = 8192,
+// 231 units 168 / 178, 256: 176 / 184, 461: 362 / 356, 512: 380 / 372, 693: 515 / 533, 720: 543 / 538, 768: 565 / 551; two digits,
+// 231 units 105 / 105, 461: 221 / 211; one digit 58 / 52.
+static bool ks_unit_wins(const cg_ctx *c, size_t batch, size_t n_rot, bool relin = false)
 {
     if (c->logn > 13 || c->alpha != 1 || c->nsp != 1) return false;
     if (c->dry) return c->dry_units;
     const size_t n = (size_t)c->n_cu, rounds = (batch + n - 1) / n;
+    if (relin && c->logn == 13 && c->dnum > 2 && (rounds == 1 || (rounds > 2 && 16 * batch < 15 * rounds * n))) return false;
     return 10 * batch >= 9 * rounds * n && (c->logn == 13 || rounds > 1) &&
            2 * c->dnum * n_rot * limb_bytes(c) <= (size_t)2 << 20;
 }
@@ -1031,7 +1036,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     const double dig_rows = (double)c->dnum * c->L;
     ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
     const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
-    if (add && ks_unit_wins(c, batch, 1)) {
+    if (add && ks_unit_wins(c, batch, 1, galois == 0)) {
         HoistTab T{};
         T.key[0] = key;
         return galois ? launch_ks_unit<KS_ROTATE>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows)
@@ -1118,13 +1123,14 @@ static int launch_rot_row(cg_ctx *c, hipStream_t s, const uint64_t *dig, const H
     }
 #undef CG_ROTROW
 }
-// From half as many workgroups as compute units on.  us, two launches / one: N = 8192, 31 rotations 36 / 55, 63: 59 / 59,
-// 127: 118 / 74; 12 ciphertexts, 3 rotations 41 / 56, 7: 65 / 59; N = 4096, 63 rotations 36 / 33.
+// From half as many workgroups as compute units on.  us with the mod-up, two launches / one.  N = 8192, three digits: one
+// ciphertext, 31 rotations 37 / 55, 64: 57 / 57, 80: 70 / 58, 127: 94 / 62; 4 x 16: 54 / 57, 8 x 8: 53 / 59, 12 x 5: 53 / 59, 12 x 6:
+// 65 / 60, 36 x 3: 91 / 65.  N = 4096, three digits: 8 x 8 32 / 35, 12 x 6: 37 / 36; two digits: 2 x 32 26.9 / 25.0, 8 x 8: 25.7 / 25.5.
 static bool rot_row_wins(const cg_ctx *c, size_t units)
 {
     if (c->logn > 13 || c->dnum > 3 || c->nsp != 1) return false;
     if (c->dry) return c->dry_rows;
-    return 4 * units >= (size_t)c->n_cu;
+    return c->dnum > 2 ? 4 * units > (size_t)c->n_cu : 4 * units >= (size_t)c->n_cu;
 }
 
 // A series of rotations of each of `batch` ciphertexts (in2 + b*in_stride): out2 + (b*out_per_b + i)
