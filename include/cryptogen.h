@@ -70,7 +70,7 @@ typedef struct {
     uint32_t log2n;       /* ring degree N = 2^log2n, 12 <= log2n <= 14 */
     uint32_t k;           /* number of ciphertext primes, 1..6 */
     uint32_t nsp;         /* number of special (key-switching) primes, 1..2 */
-    uint32_t alpha;       /* ciphertext primes per key-switch digit; divides k; <= min(3, nsp): with
+    uint32_t alpha;       /* ciphertext primes per key-switch digit; divides k; <= nsp: with
                              fewer special primes than digit primes P < Q_j and every key switch
                              would add noise of the size of a whole prime */
     uint64_t t;           /* plaintext modulus, odd, < 2^20 */

@@ -277,7 +277,7 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
     *out = nullptr;
     CG_REQUIRE(prm->log2n >= 12 && prm->log2n <= 14);
     CG_REQUIRE(prm->k >= 1 && prm->k <= 6 && prm->nsp >= 1 && prm->nsp <= 2);
-    CG_REQUIRE(prm->alpha >= 1 && prm->alpha <= 3 && prm->k % prm->alpha == 0);
+    CG_REQUIRE(prm->alpha >= 1 && prm->alpha <= 2 && prm->k % prm->alpha == 0);
     // a digit of alpha primes against fewer special primes makes P smaller than Q_j by a whole prime:
     // every result would still match its definition, but a key switch would add noise of the size of
     // a prime and silently use up the decryption budget
@@ -668,9 +668,9 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
 #define CG_KSSUMROW(LG)                                                                                        \
     do {                                                                                                      \
         const unsigned threads = (1u << LG) / 8;                                                              \
-        const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8, 1>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
+        const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
         if (c->dry) return CG_OK;                                                                             \
-        return launch_kernel(ks_sum_row_kernel<LG, 8, 1>, dim3(grid), dim3(threads), s,                       \
+        return launch_kernel(ks_sum_row_kernel<LG, 8>, dim3(grid), dim3(threads), s,                       \
                              LdModup<false, 1>{src, src_stride, 0, c->logn}, T, (int)n_rot, (int)batch,       \
                              StInvF64{acc, c->logn}, (const double *)c->tw, (const double *)c->itw,           \
                              (const DevConst *)c->dc, (int)nwg);                                              \
@@ -990,9 +990,7 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     case 2: CG_MODUP(false, 1);
     case 3: CG_MODUP(true, 1);
     case 4: CG_MODUP(false, 2);
-    case 5: CG_MODUP(true, 2);
-    case 6: CG_MODUP(false, 3);
-    default: CG_MODUP(true, 3);
+    default: CG_MODUP(true, 2);
     }
 #undef CG_MODUP
 }
@@ -1004,20 +1002,20 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
     const size_t nwg = (size_t)batch * c->L;
     const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L);
     ProfScope ps(c, s, KID_KSROW, bytes, (double)nwg);
-#define CG_KSROW(LG, G, A)                                                                                    \
+#define CG_KSROW(LG, G)                                                                                       \
     do {                                                                                                     \
         const unsigned threads = (1u << LG) / 8;                                                             \
-        const unsigned grid = ntt_grid<ks_row_kernel<LG, 8, G, A>>(c, nwg, (int)threads);                    \
+        const unsigned grid = ntt_grid<ks_row_kernel<LG, 8, G>>(c, nwg, (int)threads);                       \
         if (c->dry) return CG_OK;                                                                            \
-        return launch_kernel(ks_row_kernel<LG, 8, G, A>, dim3(grid), dim3(threads), s,                       \
-                             LdModup<G, A>{src, src_stride, galois, c->logn}, key, StInvF64{acc, c->logn},   \
+        return launch_kernel(ks_row_kernel<LG, 8, G>, dim3(grid), dim3(threads), s,                          \
+                             LdModup<G, 1>{src, src_stride, galois, c->logn}, key, StInvF64{acc, c->logn},   \
                              (const double *)c->tw, (const double *)c->itw, (const DevConst *)c->dc, (int)nwg); \
     } while (0)
-    switch ((c->logn * 10 + c->alpha) * 2 + (galois ? 1 : 0)) {
-    case 242: CG_KSROW(12, false, 1);
-    case 243: CG_KSROW(12, true, 1);
-    case 262: CG_KSROW(13, false, 1);
-    case 263: CG_KSROW(13, true, 1);
+    switch (c->logn * 2 + (galois ? 1 : 0)) {
+    case 24: CG_KSROW(12, false);
+    case 25: CG_KSROW(12, true);
+    case 26: CG_KSROW(13, false);
+    case 27: CG_KSROW(13, true);
     default: return CG_EINVAL;
     }
 #undef CG_KSROW

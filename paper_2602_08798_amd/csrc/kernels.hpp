@@ -1355,7 +1355,7 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
 }
 
 // ---------------------------------------------------------------------------
-// Key switch of one (unit, prime) per workgroup: the dnum digits lifted and transformed one after the
+// Key switch of one (unit, prime) per workgroup (digits of one prime): the digits lifted and transformed one after the
 // other, each multiplied with its two key rows into two sums in registers, and the sums transformed back.
 // The transformed digits never reach memory (24 of 35 rows per unit of traffic less) and five transforms follow
 // each other without a launch between them.  Bound by vector issue (72 % busy; operands of the whole kernel
@@ -1363,9 +1363,9 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
 // two sums, the row, its factors and the next digit's words fit 128.  768 units at N = 8192, three digits, four primes:
 // 284 + 376 us for the mod-up and inner product launches, 383 us here.
 // ---------------------------------------------------------------------------
-template <int LOGN, int E, bool GALOIS, int ALPHA>
+template <int LOGN, int E, bool GALOIS>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const double *__restrict__ key, StInvF64 st,
+ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st,
               const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C,
               int nwg)
 {
@@ -1375,15 +1375,11 @@ ks_row_kernel(LdModup<GALOIS, ALPHA> ld, const double *__restrict__ key, StInvF6
     int p = blockIdx.x;
     int wg = xcd_row(p, nwg, L);
     auto at = [&](int it) { return GALOIS ? chunk_elem<E>(tid, it) : tid + it * T; };
-    uint64_t raw[E][ALPHA];
+    uint64_t raw[E][1];
     auto fetch = [&](int b, int j) {
-        const uint64_t *e = ld.src + (size_t)b * ld.unit_stride + ((size_t)(j * ALPHA) << LOGN);
+        const uint64_t *e = ld.src + (size_t)b * ld.unit_stride + ((size_t)j << LOGN);
 #pragma unroll
-        for (int it = 0; it < E; it++)
-#pragma unroll
-            for (int s = 0; s < ALPHA; s++)
-                raw[it][s] = GALOIS ? at32(e + ((size_t)s << LOGN), at(it))
-                                    : at_lane(e + ((size_t)s << LOGN) + it * T, tid);
+        for (int it = 0; it < E; it++) raw[it][0] = GALOIS ? at32(e, at(it)) : at_lane(e + it * T, tid);
     };
     fetch(wg / L, 0);
     for (;;) {
@@ -1478,9 +1474,9 @@ __device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, 
 // the keys of one or two primes.  Bound by vector issue (71 % busy).  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums and
 // inverse transforms 475 + 899 + 369 us in three launches, 1513 us here.
 // ---------------------------------------------------------------------------
-template <int LOGN, int E, int ALPHA>
+template <int LOGN, int E>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-ks_sum_row_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, StInvF64 st,
+ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF64 st,
                   const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                   const DevConst *__restrict__ C, int nwg)
 {
@@ -1499,13 +1495,10 @@ ks_sum_row_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, St
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         const uint64_t *src = ld.src + (size_t)b * ld.unit_stride;
-        uint64_t raw[E][ALPHA];
+        uint64_t raw[E][1];
         auto fetch = [&](int j) {
 #pragma unroll
-            for (int it = 0; it < E; it++)
-#pragma unroll
-                for (int s = 0; s < ALPHA; s++)
-                    raw[it][s] = at_lane(src + ((size_t)(j * ALPHA + s) << LOGN) + it * TH, tid);
+            for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + ((size_t)j << LOGN) + it * TH, tid);
         };
         fetch(0);
         double s0[E], s1[E];
