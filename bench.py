@@ -36,6 +36,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -45,37 +46,42 @@ HBM_PEAK_GBS = 8000.0               # MI355X published HBM3E bandwidth
 FP64_VALU_PEAK_TFLOPS = 78.6        # MI355X published vector FP64 (an FMA counts as two operations)
 FP64_PEAK_LANE_INSTR = FP64_VALU_PEAK_TFLOPS * 1e12 / 2.0   # lane-instructions per second
 
-# FP64 vector instructions (per lane) that one work item of each kernel class executes at N = 8192
-# with three ciphertext primes: instructions per thread counted in the generated code of each
-# instantiation, times the threads of a workgroup (transform kernels: one item = one residue row);
-# for the pointwise kernels instructions per thread on the path taken, times the threads per batch
-# unit.  The table and its derivation are in profiles/fp64_instruction_counts.txt.
+# FP64 vector instructions (per lane) that one work item of each kernel class executes at N = 8192 with three
+# ciphertext primes: additions, products, fused products and roundings per thread as the counters read them, times the
+# threads of an item (transform and row kernels: one item = one residue row, for the row kernels with all of its
+# transforms; pointwise kernels: one batch unit).  The readings and their derivation are in
+# profiles/fp64_instruction_counts.txt.
 FP64_LANE_INSTR_PER_ITEM = {
-    "ntt_fwd<mul,q-rows>": 472 * 1024,
-    "ntt_fwd<mul,aux-rows>": 936 * 1024,
-    "ntt_fwd<modup>": 528 * 1024,
+    "ntt_fwd<mul,q-rows>": 448 * 1024,
+    "ntt_fwd<mul,aux-rows>": 816 * 1024,
+    "ntt_fwd<mul,all-rows>": 658 * 1024,
+    "ntt_fwd<modup>": 488 * 1024,
     "ntt_fwd<rows>": 472 * 1024,
-    "ntt_fwd<plain>": 514 * 1024,
-    "ntt_inv<tensor>": 760 * 1024,
-    # tensor products of the n units of a group summed on the way in: 560 outside the loop over the units,
-    # per unit 136 (components 0 and 2) or 232 (component 1), 168 on average
-    "ntt_inv<tensor_sum>": 560 * 1024,
-    "ntt_inv<tensor_sum> per unit": 168 * 1024,
-    "ntt_inv<u64>": 616 * 1024,
-    "ntt_inv<mul_plain>": 688 * 1024,
-    "ntt_fwd_inv<mul_plain>": (472 + 624) * 1024,
-    "ntt_inv<ks_inner>": 728 * 1024,
-    # summed inner products of n_rot rotations, per ciphertext: the accumulation is in integers, its final
-    # reduction about 18 FP64 instructions per output value
-    "ks_sum": 18 * 2 * 4 * 8192,
-    "ntt_inv<f64>": 560 * 1024,
-    "scale": 373 * 3 * 8192,
-    "moddown": 320 * 8192,
-    # one thread per pair of coefficients and prime: about 100 outside the rotation loop, 10 per rotation
-    # on the c0 half
-    "moddown<sum>": 100 * 3 * 8192,
-    "moddown<sum> per rotation": 10 * 3 * 4096,
-    "sum_groups": 16 * 9 * 8192,
+    "ntt_fwd<rows> to integers": 488 * 1024,
+    "ntt_fwd<plain>": 482 * 1024,
+    "ntt_inv<tensor>": 634 * 1024,
+    # tensor products of the n units of a group summed on the way in: 506 besides the units
+    "ntt_inv<tensor_sum>": 506 * 1024,
+    "ntt_inv<tensor_sum> per unit": 163 * 1024,
+    "ntt_inv<u64>": 554 * 1024,
+    "ntt_inv<mul_plain>": 594 * 1024,
+    "ntt_fwd_inv<mul_plain>": 1058 * 1024,
+    "ntt_inv<ks_inner>": 698 * 1024,
+    "ntt_inv<f64>": 506 * 1024,
+    # rows of products and key switches (averages over the rows modulo ciphertext and auxiliary primes); mul_row with one
+    # operand transformed already, as the scores have it
+    "mul_row": 3154 * 1024,
+    "ks_row": 2692 * 1024,
+    "ks_sum_row": 2572 * 1024,
+    "ks_sum_row per rotation": 336 * 1024,
+    # the accumulation is in integers: FP64 makes integers of the keys and reduces the sums
+    "ks_sum": 60 * 4 * 4096,
+    "ks_sum per rotation": 12 * 4 * 4096,
+    "scale": 288 * 3 * 8192,
+    "moddown": 90 * 8192,
+    "moddown<sum>": 35 * 3 * 8192,
+    "moddown<sum> per rotation": 1.75 * 3 * 8192,
+    "sum_groups": 11 * 9 * 8192,
     "add": 6 * 8192,
 }
 
@@ -85,12 +91,12 @@ FORMS = ("plain", "ext", "hoisted", "hoisted_ext")
 
 
 def kernel_sources_digest():
-    """SHA-256 over the device code (the kernel headers): stored counter readings are only quoted for
-    the kernels they were taken on."""
+    """SHA-256 over the device code (the kernel headers without comments and blanks): stored counter
+    readings are only quoted for the kernels they were taken on."""
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2602_08798_amd", "csrc")
     for f in ("kernels.hpp", "modarith.hpp", "tables.hpp"):
-        h.update(open(os.path.join(d, f), "rb").read())
+        h.update("".join(re.sub(r"//[^\n]*", "", open(os.path.join(d, f)).read()).split()).encode())
     return h.hexdigest()
 
 
@@ -181,6 +187,17 @@ class DecodeStep:
         assert sum(sizes) == len(self.g_block_rounds if which else self.g_fold_rounds)
         return sizes
 
+    def rotation_items(self, items):
+        """Items x rotations, per step, of a kernel class that works through `items` items (ciphertexts, or their
+        rows modulo the k + nsp primes) in the rounds of the scores, of the context or of both."""
+        H, C, L = self.heads, self.n_cts, self.prm.k + self.prm.nsp
+        rounds = [(H * C, self.round_sizes(0)), (H, self.round_sizes(1))]
+        for per in (1, L):
+            for some in (rounds, rounds[:1], rounds[1:]):
+                if per * sum(units * len(sizes) for units, sizes in some) == items:
+                    return per * sum(units * sum(sizes) for units, sizes in some)
+        return 0
+
     def step_serial(self):
         """The same work as three calls in sequence (used for per-kernel timing: a kernel's
         duration only describes the kernel when it has the device to itself)."""
@@ -242,7 +259,7 @@ def transform_rate(torch, ws, rows=16384, reps=5):
     st = [s for s in ws.ctx.profile_end() if s["name"] == "ntt_fwd<rows>"][0]
     ms = st["total_ms"] / st["launches"]
     gbs = rows * prm.n * 16 / (ms * 1e-3) / 1e9
-    fp64 = rows * 520 * 1024 / (ms * 1e-3)          # the uint64-out storer: 520 instructions per thread
+    fp64 = rows * FP64_LANE_INSTR_PER_ITEM["ntt_fwd<rows> to integers"] / (ms * 1e-3)
     return {"metric": "negacyclic NTT rows/s at N=8192 (%d rows per launch, kernel time)" % rows,
             "value": round(rows / (ms * 1e-3), 1), "unit": "1/s", "avg_launch_us": round(ms * 1e3, 1),
             "algo_GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
@@ -471,9 +488,7 @@ def main():
         for _ in range(args.steps):
             serial_fn()
         stats = ws.ctx.profile_end()
-        H, C = ws.heads, ws.n_cts
-        # rotation-units of the summed mod-down, per step
-        rot_units = sum(H * C * r for r in ws.round_sizes(0)) + sum(H * r for r in ws.round_sizes(1))
+        C = ws.n_cts
         fp64_step = 0.0
         for s in stats:
             sec = s["total_ms"] * 1e-3
@@ -481,8 +496,9 @@ def main():
             fp64 = s["work_items"] * FP64_LANE_INSTR_PER_ITEM.get(s["name"], 0)
             if s["name"] == "ntt_inv<tensor_sum>":     # its rows each take in the n_cts units of a head
                 fp64 += s["work_items"] * C * FP64_LANE_INSTR_PER_ITEM["ntt_inv<tensor_sum> per unit"]
-            if s["name"] == "moddown<sum>":
-                fp64 += args.steps * rot_units * FP64_LANE_INSTR_PER_ITEM["moddown<sum> per rotation"]
+            if s["name"] + " per rotation" in FP64_LANE_INSTR_PER_ITEM:
+                fp64 += args.steps * ws.rotation_items(s["work_items"] / args.steps) \
+                    * FP64_LANE_INSTR_PER_ITEM[s["name"] + " per rotation"]
             fp64_step += fp64 / args.steps
             kernels.append({"name": s["name"], "launches_per_step": s["launches"] / args.steps,
                             "avg_us": round(s["total_ms"] * 1e3 / s["launches"], 2),

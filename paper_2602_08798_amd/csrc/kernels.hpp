@@ -167,13 +167,14 @@ __device__ __forceinline__ void bfly_inv(double &a, double &b, double w, const M
 // ---------------------------------------------------------------------------
 constexpr int TWREGS = 16;
 
-// LDS layout: two pad doubles after every 32.  What a compute unit's LDS does (probe, clocks per
-// instruction): ds_read_b64 2.65 when 32 lanes hit 32 different doubles modulo 32, 4.3 with two of them on
-// one; ds_write_b64 6.7 when 16 lanes hit different doubles modulo 16, 8.3 otherwise; and 16-byte
-// accesses read at 1.4 times the rate.  With this layout and the lanes of group_index every pass reads and writes
-// without conflicts, and neighbouring pairs stay 16-byte aligned.  (One pad after every 8, as before, made
-// the unit-stride passes conflict: 4.4 and 8.4 clocks.)  An index that is the sum of two with disjoint
-// bits has the sum of their positions, so the per-element part of a pass folds into instruction offsets.
+// LDS layout: two pad doubles after every 32.  What a compute unit's LDS does (probe with 1024-thread workgroups, clocks
+// at 2.4 GHz per wave instruction): ds_read_b64 2.4 when 32 lanes hit 32 different doubles modulo 32, 4.3 with two
+// of them on one; ds_write_b64 6.6 when 16 lanes hit different doubles modulo 16, 8.1 otherwise; ds_read_b128 4.3,
+// ds_write_b128 14.  With this layout and the lanes of group_index the butterfly passes are free of conflicts on paper and
+// neighbouring pairs stay 16-byte aligned; the counters show 0.3 to 2 % of LDS cycles lost where 6 to 11 % were with one pad
+// after every 8 (what is left is highest in the kernels that permute by a Galois map, 3 to 5 %).  An index that is
+// the sum of two with disjoint bits has the sum of their positions, so the per-element part of a pass folds into
+// instruction offsets.
 __device__ __forceinline__ constexpr int pad(int idx) { return idx + ((idx >> 5) << 1); }
 __device__ __forceinline__ double2 &pair_at(double *lds, int pos) { return *reinterpret_cast<double2 *>(lds + pos); }
 template <int LOGN> constexpr int lds_doubles() { return (1 << LOGN) + (1 << (LOGN - 4)); }
@@ -1358,10 +1359,10 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
 // Key switch of one (unit, prime) per workgroup (digits of one prime): the digits lifted and transformed one after the
 // other, each multiplied with its two key rows into two sums in registers, and the sums transformed back.
 // The transformed digits never reach memory (24 of 35 rows per unit of traffic less) and five transforms follow
-// each other without a launch between them.  Bound by vector issue (72 % busy; operands of the whole kernel
-// taken out it is 10 % faster): 1024 threads with eight elements each, because a row is then 16 registers and the
-// two sums, the row, its factors and the next digit's words fit 128.  768 units at N = 8192, three digits, four primes:
-// 284 + 376 us for the mod-up and inner product launches, 383 us here.
+// each other without a launch between them.  Bound by vector issue (70 % busy on 700 units): 1024 threads with
+// eight elements each, because a row is then 16 registers and the two sums, the row, its factors and the next
+// digit's words fit 128.  768 units at N = 8192, three digits, four primes: 284 + 376 us for the mod-up and inner product
+// launches, 383 us here.
 // ---------------------------------------------------------------------------
 template <int LOGN, int E, bool GALOIS>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
@@ -1471,7 +1472,7 @@ __device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, 
 // transformed digit lies in LDS, from where every rotation takes its permuted values, while the keys stream past;
 // the two sums in registers are transformed back.  With digits through memory (ks_sum_kernel) every rotation's
 // gather of every digit goes to L2, and half of them miss it; here the keys are what comes in, and an XCD works with
-// the keys of one or two primes.  Bound by vector issue (71 % busy).  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums and
+// the keys of one or two primes.  Bound by vector issue (68 % busy).  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums and
 // inverse transforms 475 + 899 + 369 us in three launches, 1513 us here.
 // ---------------------------------------------------------------------------
 template <int LOGN, int E>
@@ -1536,7 +1537,7 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 // Instead of 101 rows of traffic per product (three launches: ciphertext primes, auxiliary primes, tensor
 // product) 33 reach memory.  The order x0, y0, x1, y1 keeps at most two rows in registers during a transform: x0
 // waits in a second LDS buffer (one workgroup per unit at N = 8192, two at N = 4096), x0 y0 leaves before x1 is
-// transformed.  Bound by vector issue (66 % busy; the lifts to the auxiliary primes are an eighth of it).  768
+// transformed.  Bound by vector issue (66 to 68 % busy; the lifts to the auxiliary primes are an eighth of it).  768
 // products at N = 8192, three primes: 308 + 644 + 764 us for the three launches, 1119 us here.
 // ---------------------------------------------------------------------------
 // element rows of an operand in coefficients, modulo the prime of the workgroup; loads and arithmetic apart,
@@ -1670,7 +1671,8 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
 // each sum.  What the parts of a group leave is summed by scale_kernel.  The three sums take the registers in
 // which mul_row_kernel brings in the next polynomial, so the loads are exposed (about 50 us a unit at N = 8192, three primes,
 // against 43 there); what it saves is the transformed operands' way through memory, and its parts spread long
-// groups over the chip.  12 groups of 128: 2620 us in three launches, 2126 here; one group of 32: 178 / 75.
+// groups over the chip.  The vector unit is 45 % busy.  12 groups of 128: 2620 us in three launches, 2126 here; one group of
+// 32: 178 / 75.
 template <int LOGN, int E, int K>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
@@ -2082,8 +2084,9 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
 // One component of one rotation of a hoisted series per workgroup, from the transformed digits to the finished
 // ciphertext rows: inner products and inverse transform modulo the special prime, then modulo every ciphertext
 // prime, the division by P following in registers.  The permuted c0 row goes through LDS.  The accumulators (8 rows
-// written and read per rotation at four primes) never reach memory.  Bound by vector issue and the gathers, 13 us a
-// row and compute unit; a serial chain of k + 1 transforms, so it needs half the chip to be busy to pay off.
+// written and read per rotation at four primes) never reach memory.  14 us a row and compute unit, the vector unit 51 %
+// busy: one workgroup to a unit, and nothing covers the gathers; a serial chain of k + 1 transforms, so it needs half
+// the chip to be busy to pay off.
 // N = 8192, 127 rotations, mod-down included: 12 ciphertexts 1164 -> 675 us, one 118 -> 74 us.
 // ---------------------------------------------------------------------------
 template <int LOGN, int E, int DNUM>
@@ -2163,8 +2166,8 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
 // Key switch of one unit per workgroup, from the ring element to the finished ciphertext: as ks_row_kernel and
 // ks_sum_row_kernel, special prime first, then every ciphertext prime with the division by P and the additions in
 // registers.  The accumulators (L rows of each component written and read again) never reach memory but for the two
-// rows modulo the special prime, and the mod-down launch is gone.  Bound as those kernels are, by vector issue; the
-// addends, asked for after the inverse transform, are exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
+// rows modulo the special prime, and the mod-down launch is gone.  The vector unit is 52 to 56 % busy, less than in those
+// kernels: the addends, asked for after the inverse transform, are exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
 // 588 -> 537, 3 summed rotations 761 -> 680; N = 4096: 166 -> 141, 163 -> 139, 207 -> 160, 7 summed 259 -> 212.
 // ---------------------------------------------------------------------------
 enum KsMode { KS_PLAIN, KS_ROTATE, KS_SUM };
