@@ -1666,50 +1666,85 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
     }
 }
 
+// The polynomial at src modulo the workgroup's prime, in pass-0 ownership, W elements' words on their way while one is lifted.
+template <int LOGN, int E, int K, int W>
+__device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, int tid, const ModD m, const DevConst *C)
+{
+    constexpr int T = (1 << LOGN) / E;
+    uint64_t w[W][K];
+    auto get = [&](int it) {
+#pragma unroll
+        for (int q = 0; q < K; q++)
+            w[it % W][q] = at_lane(src + ((size_t)LdMulExt<K>::source(r, q) << LOGN) + it * T, tid);
+    };
+#pragma unroll
+    for (int it = 0; it < W; it++) get(it);
+    C = opaque_const(C);
+#pragma unroll
+    for (int it = 0; it < E; it++) {
+        // (kept apart: the compiler would ask for the whole row first and spill what the caller holds)
+        __builtin_amdgcn_sched_barrier(0);
+        x[it] = LdMulExt<K>::lift(w[it % W], r, m, C);
+        __builtin_amdgcn_sched_barrier(0);
+        if (it + W < E) get(it + W);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Sums of products over the units of a group, one (group, part of it, prime) per workgroup: the operands of a unit
-// transformed as in mul_row_kernel, the three components summed in registers over the units, one inverse transform of
-// each sum.  What the parts of a group leave is summed by scale_kernel.  The three sums take the registers in
-// which mul_row_kernel brings in the next polynomial, so the loads are exposed (about 50 us a unit at N = 8192, three primes,
-// against 43 there); what it saves is the transformed operands' way through memory, and its parts spread long
-// groups over the chip.  The vector unit is 45 % busy.  12 groups of 128: 2620 us in three launches, 2126 here; one group of
-// 32: 178 / 75.
+// transformed as in mul_row_kernel, the three components summed over the units, one inverse transform of each sum.  What
+// the parts of a group leave is summed by scale_kernel.  It saves the transformed operands' way through memory, and
+// its parts spread long groups over the chip.
+// Registers set the pace at N = 8192: three sums, a kept row, the row in work and its factors do not fit 128 and spilled 48
+// of them, 200 bytes a thread and transform.  There (FAR) two sums stay in registers; the first component's, needed
+// once per unit, waits in its own output row, a thread's own 64 bytes of it, from L2.  The words of a polynomial come in through a
+// window of a few elements instead of in two halves at once.  Kernel, 12 groups of 128, N = 8192, three primes: 2100 us with everything
+// in registers, 1890 with the halves one after the other, 1760 with the first sum in memory too, 1640 with the window (2 to 5
+// elements within 3 %).  At N = 4096 registers suffice, and the sum in memory costs 3 % of A V, 12 heads (419 us; 406 in registers).
 template <int LOGN, int E, int K>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
                    const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
-    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, H = E / 2;
+    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, W = K == 1 ? 8 : K == 2 ? 4 : 3;
+    constexpr bool FAR = LOGN > 12;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     __shared__ double park[1 << LOGN];
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
         const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
-        const int u_end = g * group + (part + 1) * group / parts;
+        const int u_first = g * group + part * group / parts, u_end = g * group + (part + 1) * group / parts;
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        // the first component's sum: pair q of a thread at far[q * T + tid]
+        cg_double2v *far = reinterpret_cast<cg_double2v *>(st.dst + ((size_t)(gp * 3 * KL + r) << LOGN));
         double d0[E], d1[E], d2[E];
 #pragma unroll
         for (int it = 0; it < E; it++) d0[it] = d1[it] = d2[it] = 0.0;
-        for (int u = g * group + part * group / parts; u < u_end; u++) {
+        for (int u = u_first; u < u_end; u++) {
             double keep[E];
 #pragma unroll
             for (int t = 0; t < 4; t++) {
                 double x[E];
-                {
-                    const uint64_t *src = (t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1);
-                    MulRowLoad<LOGN, E, K> lo, hi;
-                    lo.fetch(src, r, 0, tid);
-                    hi.fetch(src, r, H, tid);
-                    lo.finish(x, r, m, C);
-                    hi.finish(x + H, r, m, C);
-                }
+                lift_row<LOGN, E, K, W>(x, (t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1), r, tid, m, C);
                 lds_barrier();      // the previous transform's LDS reads
                 fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                cg_double2v s0[E / 2];
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                if (FAR && t == 1) {
+#pragma unroll
+                    for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
+                    if (u != u_first) {
+#pragma unroll
+                        for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
+                    }
+                }
 #pragma unroll
                 for (int it = 0; it < E; it++) {
                     x[it] = red(x[it], m);
                     if (t == 0) park[tid + it * T] = x[it];
-                    if (t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
+                    if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
                     if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
                     if (t == 3) {
                         d1[it] += mulmod(park[tid + it * T], x[it], m);
@@ -1717,16 +1752,32 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     }
                     if (t == 1 || t == 2) keep[it] = x[it];
                 }
+                // (a unit adds less than 1.2 p)
+                if (FAR && t == 1) {
+#pragma unroll
+                    for (int q = 0; q < E / 2; q++) {
+                        const double a = mulmod(park[tid + 2 * q * T], x[2 * q], m),
+                                     b = mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m);
+                        put32(far + q * T, tk, cg_double2v{red(s0[q].x + a, m), red(s0[q].y + b, m)});
+                    }
+                }
             }
-            // a unit adds less than 1.2 p
 #pragma unroll
             for (int it = 0; it < E; it++) {
-                d0[it] = red(d0[it], m);
+                if (!FAR) d0[it] = red(d0[it], m);
                 d1[it] = red(d1[it], m);
                 d2[it] = red(d2[it], m);
             }
         }
+#pragma unroll
+        for (int q = 0; FAR && q < E / 2; q++) {
+            const cg_double2v v = at_lane(far + q * T, tid);
+            d0[2 * q] = v.x;
+            d0[2 * q + 1] = v.y;
+        }
         for (int c = 0; c < 3; c++) {
+            // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
+            // registers before any thread stores results over it)
             lds_barrier();
             inv_row<LOGN, E>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, r, C);
 #pragma unroll
