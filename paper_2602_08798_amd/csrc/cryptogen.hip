@@ -165,6 +165,7 @@ struct cg_ctx {
     DevConst hc;
     DevConst *dc;
     double *tw, *itw;     // [np][N] forward / inverse twiddles (centred doubles, bit-reversed order)
+    double *tw2, *itw2;   // N = 16384: [np][2][N/2], those of the two half rows
     uint32_t *tab;        // scratch prime-index table for the public transform entry points
     uint32_t tab_cap;
     int device, n_cu;
@@ -197,13 +198,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_LIFT, KID_FWD_HALF, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit", "lift", "ntt_fwd<mul,half-rows>"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -348,6 +349,30 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         H.ninv[r] = h_centred(ninv, p);
         H.itw1_ninv[r] = h_centred(h_mul(h_inv(pw[h_bitrev(1, c->logn)], p), ninv, p), p);
     }
+    std::vector<double> tw2, itw2;
+    if (c->logn == 14) {
+        // factors of half h: those of the whole row's stages from the second on, blocks h 2^s ... of stage s + 1
+        const size_t half = N / 2;
+        tw2.resize((size_t)np * N);
+        itw2.resize((size_t)np * N);
+        for (int r = 0; r < np; r++) {
+            const uint64_t p = c->pr[r], ninv = h_inv(N % p, p);
+            const double *t = &tw[(size_t)r * N], *it = &itw[(size_t)r * N];
+            for (size_t h = 0; h < 2; h++) {
+                double *t2 = &tw2[(size_t)r * N + h * half], *it2 = &itw2[(size_t)r * N + h * half];
+                for (size_t w = 1; w < half; w *= 2)
+                    for (size_t j = 0; j < w; j++) {
+                        t2[w + j] = t[2 * w + h * w + j];
+                        it2[w + j] = it[2 * w + h * w + j];
+                    }
+                const uint64_t w1 = it[2 + h] < 0 ? p - (uint64_t)-it[2 + h] : (uint64_t)it[2 + h];
+                H.ninv[MAXPR + 2 * r + h] = H.ninv[r];
+                H.itw1_ninv[MAXPR + 2 * r + h] = h_centred(h_mul(w1, ninv, p), p);
+            }
+            H.tw1[r] = t[1];
+            H.itw1[r] = it[1];
+        }
+    }
     for (int r = 0; r < np; r++) {
         H.two50[r] = h_centred(h_pow(2, 50, c->pr[r]), c->pr[r]);
         H.two81[r] = h_centred(h_pow(2, 81, c->pr[r]), c->pr[r]);
@@ -401,6 +426,7 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
     c->tab_cap = 1u << 16;
     if (hipMalloc(&c->dc, sizeof(DevConst)) != hipSuccess || hipMalloc(&c->tw, tbytes) != hipSuccess ||
         hipMalloc(&c->itw, tbytes) != hipSuccess ||
+        (!tw2.empty() && (hipMalloc(&c->tw2, tbytes) != hipSuccess || hipMalloc(&c->itw2, tbytes) != hipSuccess)) ||
         hipMalloc(&c->tab, c->tab_cap * sizeof(uint32_t)) != hipSuccess) {
         cg_destroy(c);
         return CG_ENOMEM;
@@ -408,6 +434,8 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
     if (hipMemcpy(c->dc, &H, sizeof(DevConst), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->tw, tw.data(), tbytes, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->itw, itw.data(), tbytes, hipMemcpyHostToDevice) != hipSuccess ||
+        (!tw2.empty() && (hipMemcpy(c->tw2, tw2.data(), tbytes, hipMemcpyHostToDevice) != hipSuccess ||
+                          hipMemcpy(c->itw2, itw2.data(), tbytes, hipMemcpyHostToDevice) != hipSuccess)) ||
         hipDeviceSynchronize() != hipSuccess) {
         cg_destroy(c);
         return CG_EHIP;
@@ -444,6 +472,8 @@ extern "C" int cg_destroy(cg_ctx *c)
     if (c->dc) (void)hipFree(c->dc);
     if (c->tw) (void)hipFree(c->tw);
     if (c->itw) (void)hipFree(c->itw);
+    if (c->tw2) (void)hipFree(c->tw2);
+    if (c->itw2) (void)hipFree(c->itw2);
     if (c->tab) (void)hipFree(c->tab);
     for (uint32_t i = 0; i < 2 * c->prof_cap; i++) (void)hipEventDestroy(c->prof_ev[i]);
     delete[] c->prof_ev;
@@ -536,7 +566,9 @@ static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
                              (const double *)c->tw, (const DevConst *)c->dc, (int)nwg);         \
     } while (0)
     switch (c->logn * 100 + e) {
-    case 1416: CG_FWD(14, 16);
+    case 1416:
+        if constexpr (ld_no_16384<LD>::value) return CG_EINVAL;
+        else CG_FWD(14, 16);
     case 1208: CG_FWD(12, 8);
     case 1308: CG_FWD(13, 8);
     case 1316: CG_FWD(13, 16);
@@ -559,7 +591,9 @@ static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
                              (const double *)c->itw, (const DevConst *)c->dc, (int)nwg);        \
     } while (0)
     switch (c->logn * 100 + e) {
-    case 1416: CG_INV(14, 16);
+    case 1416:
+        if constexpr (ld_no_16384<LD>::value) return CG_EINVAL;
+        else CG_INV(14, 16);
     case 1208: CG_INV(12, 8);
     case 1308: CG_INV(13, 8);
     case 1316: CG_INV(13, 16);
@@ -772,17 +806,53 @@ static int launch_moddown(cg_ctx *c, hipStream_t s, double bytes, size_t units, 
                        : launch_kernel(moddown_kernel<HOIST, 2>, grid, block, s, A, H, dc);
 }
 
+// N = 16384: operands lifted to all k + l primes, first transform stage taken, in half rows
+static int launch_lift(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t polys, double *dst)
+{
+    const double bytes = (double)limb_bytes(c) * polys * (c->k + c->KL);
+    const unsigned blocks = (unsigned)(polys * (size_t)(c->N / 2 / PW_THREADS));
+#define CG_LIFT(K) CG_LAUNCH_PW(KID_LIFT, bytes, (double)polys, lift_kernel<K>, blocks, src, dst, c->dc)
+    switch (c->k) {
+    case 1: CG_LIFT(1); break;
+    case 2: CG_LIFT(2); break;
+    case 3: CG_LIFT(3); break;
+    case 4: CG_LIFT(4); break;
+    case 5: CG_LIFT(5); break;
+    default: CG_LIFT(6); break;
+    }
+#undef CG_LIFT
+    return CG_OK;
+}
+// the half rows of lifted operands transformed in place; up to one per compute unit on 1024 threads (launch_fwd)
+static int launch_fwd_half(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t polys, double *dst)
+{
+    const size_t nwg = polys * 2 * c->KL;
+    ProfScope ps(c, s, KID_FWD_HALF, (double)limb_bytes(c) * nwg, (double)nwg);
+#define CG_HALF(EL)                                                                                            \
+    do {                                                                                                      \
+        const unsigned threads = 8192 / EL, grid = ntt_grid<ntt_fwd_kernel<13, EL, LdHalf, StF64>>(c, nwg, (int)threads); \
+        if (c->dry) return CG_OK;                                                                             \
+        return launch_kernel(ntt_fwd_kernel<13, EL, LdHalf, StF64>, dim3(grid), dim3(threads), s,             \
+                             LdHalf{dst, src}, StF64{dst, 13}, (const double *)c->tw2, (const DevConst *)c->dc, (int)nwg); \
+    } while (0)
+    if (nwg <= (size_t)c->n_cu) CG_HALF(8);
+    CG_HALF(16);
+#undef CG_HALF
+}
 // Every polynomial named by src -> its transform over the k ciphertext primes and the l auxiliary
 // primes (centred lift), rows dst[poly][k+l][N], lazy.
 static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t polys, double *dst)
 {
+    if (c->logn == 14) {
+        CG_TRY(launch_lift(c, s, src, polys, dst));
+        return launch_fwd_half(c, s, src, polys, dst);
+    }
     const double LB = (double)limb_bytes(c);
     const double in_rows = (double)polys * c->k;
     const StF64 st{dst, c->logn};
-    // Both kinds of rows in one launch while they are at most two per compute unit (one at N = 16384, where a row takes a
-    // unit's LDS): product and relinearisation, us in two launches / one: N = 8192, one product 61 / 52, 8: 72 / 63, 16:
+    // Both kinds of rows in one launch while they are at most two per compute unit: product and relinearisation, us in two launches / one: N = 8192, one product 61 / 52, 8: 72 / 63, 16:
     // 84 / 80; N = 4096, 16: 47.7 / 43.1.  Large launches are faster apart (the lifts' code for the plain rows).
-    if (polys * c->KL <= (size_t)c->n_cu * (c->logn < 14 ? 2 : 1)) {
+    if (polys * c->KL <= (size_t)c->n_cu * 2) {
         const double bytes = LB * (in_rows + (double)polys * c->KL);
         switch (c->k) {
         case 1: return launch_fwd(c, s, polys * c->KL, LdMulExt<1>{src}, st, KID_FWD_MULEXT, bytes);
@@ -840,9 +910,10 @@ template <bool HAT>
 static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t batch, double x_cts,
                           double y_cts)
 {
-    const size_t nwg = (size_t)batch * c->KL;
-    const double bytes = (double)limb_bytes(c) *
-                         (2.0 * c->k * x_cts + 2.0 * (HAT ? c->KL : c->k) * y_cts + 3.0 * c->KL * batch);
+    const bool half = c->logn == 14;
+    const size_t nwg = (size_t)batch * c->KL * (half ? 2 : 1);
+    const int x_rows = half ? c->KL : c->k, y_rows = HAT ? c->KL : x_rows;
+    const double bytes = (double)limb_bytes(c) * (2.0 * x_rows * x_cts + 2.0 * y_rows * y_cts + 3.0 * c->KL * batch);
     ProfScope ps(c, s, KID_MULROW, bytes, (double)nwg);
 #define CG_MULROW(LG, K)                                                                                   \
     do {                                                                                                  \
@@ -850,9 +921,10 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
         const unsigned grid = ntt_grid<mul_row_kernel<LG, 8, K, HAT>>(c, nwg, (int)threads);              \
         if (c->dry) return CG_OK;                                                                         \
         return launch_kernel(mul_row_kernel<LG, 8, K, HAT>, dim3(grid), dim3(threads), s, A,              \
-                             StInvF64{tens, c->logn}, (const double *)c->tw, (const double *)c->itw,      \
-                             (const DevConst *)c->dc, (int)nwg);                                          \
+                             StInvF64{tens, LG}, (const double *)(K ? c->tw : c->tw2),                    \
+                             (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
+    if (c->logn == 14) CG_MULROW(13, 0);
     switch (c->logn * 10 + c->k) {
     case 121: CG_MULROW(12, 1);
     case 122: CG_MULROW(12, 2);
@@ -864,31 +936,37 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
     }
 #undef CG_MULROW
 }
-// Sums of products over groups of units in one launch; every group is taken in `parts` parts
+// Sums of products over groups of units in one launch; every group is taken in `parts` parts.  HAT: y transformed (N = 16384)
+template <bool HAT>
 static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t groups,
                               uint32_t group, uint32_t parts)
 {
-    const size_t nwg = (size_t)groups * parts * c->KL;
+    const bool half = c->logn == 14;
+    const size_t nwg = (size_t)groups * parts * c->KL * (half ? 2 : 1);
     const double units = (double)groups * group;
-    ProfScope ps(c, s, KID_MULSUMROW, (double)limb_bytes(c) * (4.0 * c->k * units + 3.0 * nwg), units * c->KL);
-#define CG_MULSUMROW(LG, K)                                                                                \
+    ProfScope ps(c, s, KID_MULSUMROW, (double)limb_bytes(c) * (4.0 * (half ? c->KL : c->k) * units + 3.0 * groups * parts * c->KL),
+                 units * c->KL * (half ? 2 : 1));
+#define CG_MULSUMROW(LG, K, H)                                                                             \
     do {                                                                                                  \
         const unsigned threads = (1u << LG) / 8;                                                          \
-        const unsigned grid = ntt_grid<mul_sum_row_kernel<LG, 8, K>>(c, nwg, (int)threads);               \
+        const unsigned grid = ntt_grid<mul_sum_row_kernel<LG, 8, K, H>>(c, nwg, (int)threads);            \
         if (c->dry) return CG_OK;                                                                         \
-        return launch_kernel(mul_sum_row_kernel<LG, 8, K>, dim3(grid), dim3(threads), s, A, (int)group,   \
-                             (int)parts, StInvF64{tens, c->logn}, (const double *)c->tw,                  \
-                             (const double *)c->itw, (const DevConst *)c->dc, (int)nwg);                  \
+        return launch_kernel(mul_sum_row_kernel<LG, 8, K, H>, dim3(grid), dim3(threads), s, A, (int)group, \
+                             (int)parts, StInvF64{tens, LG}, (const double *)(K ? c->tw : c->tw2),        \
+                             (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
-    switch (c->logn * 10 + c->k) {
-    case 121: CG_MULSUMROW(12, 1);
-    case 122: CG_MULSUMROW(12, 2);
-    case 123: CG_MULSUMROW(12, 3);
-    case 131: CG_MULSUMROW(13, 1);
-    case 132: CG_MULSUMROW(13, 2);
-    case 133: CG_MULSUMROW(13, 3);
-    default: return CG_EINVAL;
+    if (half) CG_MULSUMROW(13, 0, HAT);
+    if constexpr (!HAT) {
+        switch (c->logn * 10 + c->k) {
+        case 121: CG_MULSUMROW(12, 1, false);
+        case 122: CG_MULSUMROW(12, 2, false);
+        case 123: CG_MULSUMROW(12, 3, false);
+        case 131: CG_MULSUMROW(13, 1, false);
+        case 132: CG_MULSUMROW(13, 2, false);
+        case 133: CG_MULSUMROW(13, 3, false);
+        }
     }
+    return CG_EINVAL;
 #undef CG_MULSUMROW
 }
 // Whether that beats the launches of single transforms and a tensor inverse that walks over the group, and in how many
@@ -911,6 +989,20 @@ static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint
     if (best >= 1.25 * (4.0 * base * group / n + 0.5 * group * std::ceil(3.0 * base / n) + 1.2)) return false;
     parts = best_parts;
     return true;
+}
+
+// Parts of a group at N = 16384: as above, in transforms of a half row, four per unit (three with y transformed) and three
+// besides; the fewest parts that are as fast, since scale_kernel reads every part.
+static uint32_t mul_sum_parts_half(const cg_ctx *c, uint32_t groups, uint32_t group, bool hat)
+{
+    const double n = c->n_cu, base = (double)groups * 2 * c->KL, per = hat ? 3.0 : 4.0;
+    double best = 1e30;
+    uint32_t parts = 1;
+    for (uint32_t q = 1; q <= group && q <= 64; q++) {
+        const double t = std::ceil(base * q / n) * (per * ((group + q - 1) / q) + 3.0);
+        if (t < 0.97 * best) { best = t; parts = q; }
+    }
+    return parts;
 }
 
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
@@ -936,8 +1028,29 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
     const int all = 1 << 30;
     uint32_t parts = 1;
-    if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
-        CG_TRY(launch_mul_sum_row(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
+    if (c->logn == 14) {
+        // operands lifted by a launch of its own, then half rows through the product in one launch: with a shared a
+        // operand that is transformed once, or with the b operands given transformed, as the second operand
+        const bool shared = a_group > 1 && !b_ext;
+        MulRowArgs A{reinterpret_cast<const uint64_t *>(ntt), nullptr, b_ext, all, 0, (int)a_group, (int)b_group, (int)b_stride, 1,
+                     2 * c->KL, 13};
+        const size_t ct = (size_t)2 * c->KL * c->N;
+        if (!b_ext) A.y = reinterpret_cast<const uint64_t *>(ntt + n_a * ct), A.y_group = all, A.y_stride = 0;
+        if (shared) A = MulRowArgs{reinterpret_cast<const uint64_t *>(ntt + n_a * ct), nullptr, ntt, all, 0, 1, all, 0, (int)a_group,
+                                   2 * c->KL, 13};
+        CG_TRY(launch_lift(c, s, src, polys, ntt));
+        if (shared) CG_TRY(launch_fwd_half(c, s, src, 2 * (size_t)n_a, ntt));
+        if (sum_group) {
+            CG_REQUIRE(a_group == 1);
+            parts = mul_sum_parts_half(c, n_out, sum_group, b_ext != nullptr);
+            CG_TRY(b_ext ? launch_mul_sum_row<true>(c, s, A, tens, n_out, sum_group, parts)
+                         : launch_mul_sum_row<false>(c, s, A, tens, n_out, sum_group, parts));
+        } else {
+            CG_TRY(b_ext || shared ? launch_mul_row<true>(c, s, A, tens, batch, shared ? B : n_a, shared ? n_a : B)
+                                   : launch_mul_row<false>(c, s, A, tens, batch, B, B));
+        }
+    } else if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
+        CG_TRY(launch_mul_sum_row<false>(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                   tens, n_out, sum_group, parts));
     } else if (!sum_group && !(b_ext && a_group > 1) && mul_row_wins(c, (size_t)batch * c->KL, beside)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
@@ -964,7 +1077,13 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     }
     const double sbytes = LB * (3.0 * c->KL * parts + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);
-#define CG_SCALE(K) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, scale_kernel<K>, sblocks, tens, out3, (int)parts, accumulate, c->dc)
+#define CG_SCALE(K)                                                                                                  \
+    do {                                                                                                             \
+        if (c->logn == 14) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, (scale_kernel<K, true>), sblocks, tens, out3, \
+                                        (int)parts, accumulate, c->dc);                                              \
+        else CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, (scale_kernel<K, false>), sblocks, tens, out3, (int)parts, \
+                          accumulate, c->dc);                                                                        \
+    } while (0)
     switch (c->k) {
     case 1: CG_SCALE(1); break;
     case 2: CG_SCALE(2); break;
@@ -2066,6 +2185,8 @@ static int warm_launch_table(cg_ctx *c)
     CG_TRY(do_mul(c, s, u, u, u, 1, 1, f, 0));
     CG_TRY(do_mul(c, s, u, u, u, 2, 2, f, 0));
     CG_TRY(do_mul(c, s, u, u, u, 2, 1, f, 0, 0, 0, nullptr, 2));
+    CG_TRY(do_mul(c, s, u, u, u, 2, 2, f, 0, 2, 2, f));
+    CG_TRY(do_mul(c, s, u, u, u, 2, 1, f, 0, 2, 2, f, 2));
     CG_TRY(do_keyswitch(c, s, u, 0, 0, f, u, 0, u, 0, 0, 0, 1, f));
     CG_TRY(do_keyswitch(c, s, u, 0, 3, f, u, 0, u, 0, 3, 1, 1, f));
     {
@@ -2095,6 +2216,7 @@ static int warm_launch_table(cg_ctx *c)
             CG_TRY(do_rotate_hoisted(c, s, u, 0, 1, gs1, keys1, u, 1, batch, f));
             CG_TRY(do_rotate_sum(c, s, u, 0, 1, gs1, keys1, u, 0, batch, f));
         }
+        CG_TRY(transform_ext(c, s, MulSrc{nullptr, u, 0, 1, 1, c->logn, 1}, 2 * (size_t)batch, f));
         const size_t rows = (size_t)batch * 2 * c->k;
         const LdRowsU64 ld{u, nullptr, c->k, c->logn};
         CG_TRY(launch_fwd(c, s, rows, ld, StU64{u, c->logn}, KID_FWD_ROWS, LB));

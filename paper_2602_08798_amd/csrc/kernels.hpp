@@ -17,6 +17,9 @@ namespace cg {
 //   workgroups share a compute unit and cover each other's loads; no register prefetch), which
 //   measured 5-10 % faster than E = 8; the inverse kernels keep E = 8 (their fused loaders spill
 //   at 128 registers).  E = 16 is the only choice at N = 16384 (1024 threads).
+//   Products at N = 16384 work on half rows: the first stage, which pairs coefficients N / 2 apart, is taken by
+//   lift_kernel, which has both in registers, its inverse by scale_kernel, and the two halves of a row are
+//   transforms of 8192 with tables of their own (row 2 r + h of prime r).
 // ---------------------------------------------------------------------------
 template <int LOGN, int E> struct Plan;
 template <> struct Plan<14, 16> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {4, 4, 3, 3, 0}; };
@@ -294,6 +297,11 @@ template <class LD> struct ld_rounds { static constexpr bool value = false; };
 // here: row addresses and the target are worked out once per row.
 template <class LD> struct ld_lifts { static constexpr bool value = false; };
 
+// Loaders of half rows are marked here: prime() is 2 r + h, half h of prime r.
+template <class LD> struct ld_half { static constexpr bool value = false; };
+// Loaders of products' operands: those of N = 16384 are half rows.
+template <class LD> struct ld_no_16384 { static constexpr bool value = false; };
+
 // Loaders that do not prefetch fetch and finish a row in slices, so that at most about 32 raw
 // words are live per thread however many words an element needs.
 template <int LOGN, int E, bool CHUNKED, class LD, class F>
@@ -486,7 +494,7 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
     if constexpr (PF) fetch_row<LOGN, E, CH>(ld, wg, tid, C, raw);
     for (;;) {
         const int pr = ld.prime(wg, C);
-        const ModD m = C->mod[pr];
+        const ModD m = C->mod[ld_half<LD>::value ? pr >> 1 : pr];
         const double *tw = tw_all + ((size_t)pr << LOGN);
         const int dl = ld.dst_limb(wg, C);
         double twa[TWREGS], twb[TWREGS];
@@ -847,7 +855,8 @@ struct MulSrc {
     }
 };
 // operands of mul_row_kernel: x in coefficients, unit u's at x + (u / x_group) * x_stride + u % x_group (in
-// ciphertexts); y likewise in coefficients, or transformed rows [ciphertext][2][k+l][N]
+// ciphertexts); y likewise in coefficients, or transformed rows [ciphertext][2][k+l][N].  Lifted operands: rows of
+// doubles, k = 2 (k + l) half rows of 2^logn to a polynomial.
 struct MulRowArgs {
     const uint64_t *x, *y;
     const double *yhat;
@@ -920,6 +929,8 @@ struct LdMulAux {
     __device__ __forceinline__ double finish(const uint64_t *, int, int, const ModD, const DevConst *) const { return 0.0; }
 };
 template <int K> struct ld_lifts<LdMulAux<K>> { static constexpr bool value = true; };
+template <> struct ld_no_16384<LdMulQ> { static constexpr bool value = true; };
+template <int K> struct ld_no_16384<LdMulAux<K>> { static constexpr bool value = true; };
 
 // Both kinds of rows in one launch, for launches that leave compute units free: workgroup -> (pp, prime r of the k + l).
 // All K words of a row modulo a ciphertext prime are that row's own: the same line, and the same code.
@@ -946,6 +957,32 @@ struct LdMulExt {
     __device__ __forceinline__ double finish(const uint64_t *, int, int, const ModD, const DevConst *) const { return 0.0; }
 };
 template <int K> struct ld_lifts<LdMulExt<K>> { static constexpr bool value = true; };
+template <int K> struct ld_no_16384<LdMulExt<K>> { static constexpr bool value = true; };
+
+// half rows that lift_kernel left, transformed in place: workgroup -> (pp, row 2 r + h of 2 (k + l))
+struct LdHalf {
+    static constexpr int kRaw = 1;
+    static constexpr bool kPrefetch = true;
+    static constexpr bool kScatter = false;
+    const double *rows;
+    MulSrc src;
+    __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % (2 * C->KL); }
+    __device__ __forceinline__ int share(const DevConst *) const { return 1; }
+    __device__ __forceinline__ int dst_limb(int wg, const DevConst *C) const
+    {
+        const int per = 2 * C->KL;
+        return src.dst_poly(wg / per) * per + wg % per;
+    }
+    __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *C, uint64_t *raw) const
+    {
+        raw[0] = f64_bits(rows[((size_t)dst_limb(wg, C) << (src.logn - 1)) + idx]);
+    }
+    __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD, const DevConst *) const
+    {
+        return bits_f64(raw[0]);
+    }
+};
+template <> struct ld_half<LdHalf> { static constexpr bool value = true; };
 
 // key-switch mod-up: workgroup -> (unit b, digit j, target prime r); the digit is
 // the integer in [0,Q_j) formed by ALPHA rows of the source ring element, reduced
@@ -1213,6 +1250,8 @@ struct LdInvTensorSum {
     __device__ __forceinline__ double join(double sum, double term, const ModD m) const { return red(sum, m) + term; }
 };
 template <> struct ld_rounds<LdInvTensorSum> { static constexpr bool value = true; };
+template <> struct ld_no_16384<LdInvTensor> { static constexpr bool value = true; };
+template <> struct ld_no_16384<LdInvTensorSum> { static constexpr bool value = true; };
 
 // transformed ciphertext row times prepared plaintext row (ct x pt fused into the load):
 // workgroup -> (unit b, comp c, prime i); ciphertext = ctf[b / ct_group], plaintext =
@@ -1544,6 +1583,7 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 // so that the loads of the next row can be on their way during a transform
 template <int LOGN, int E, int K>
 struct MulRowLoad {
+    static constexpr bool kWhole = false;      // all of a row's words fit
     static constexpr int T = (1 << LOGN) / E, H = E / 2;
     uint64_t w[H][K];      // half a row
     // words of elements it0 .. it0 + H of the polynomial at src, as LdMulExt takes them
@@ -1563,19 +1603,43 @@ struct MulRowLoad {
     }
 };
 
-// HAT: 0 both operands in coefficients, 1 the first (x) in coefficients and the second (y) transformed
+// K = 0: operands that lift_kernel has lifted, a word per element
+template <int LOGN, int E>
+struct MulRowLoad<LOGN, E, 0> {
+    static constexpr bool kWhole = true;
+    static constexpr int T = (1 << LOGN) / E;
+    uint64_t w[E];
+    __device__ __forceinline__ void fetch(const uint64_t *src, int r, int, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < E; i++) w[i] = at_lane(src + ((size_t)r << LOGN) + i * T, tid);
+    }
+    __device__ __forceinline__ void finish(double *x, int, const ModD, const DevConst *) const
+    {
+#pragma unroll
+        for (int i = 0; i < E; i++) x[i] = bits_f64(w[i]);
+    }
+};
+
+// HAT: 0 both operands in coefficients, 1 the first (x) in coefficients and the second (y) transformed.
+// K = 0: half rows at N = 16384, lifted ahead by lift_kernel, which shares a coefficient's mixed-radix digits between the
+// auxiliary primes (lifted per prime in a transform's loader, the digits of six primes took twice the transform itself).  The
+// whole next row travels during a transform.  96 products, six primes: 165 + 438 + 404 us for the transforms of ciphertext and
+// auxiliary rows and the tensor product's inverse, 161 + 501 us for lift_kernel and this.
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                const DevConst *__restrict__ C, int nwg)
 {
-    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, H = E / 2;
+    using LD = MulRowLoad<LOGN, E, K>;
+    constexpr int T = (1 << LOGN) / E, H = E / 2;
+    const int KL = K ? 2 * K + 1 : A.k;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     __shared__ double park[HAT ? 1 : 1 << LOGN];
     const int tid = threadIdx.x;
     int p = blockIdx.x;
     int wg = xcd_row(p, nwg, KL);
-    MulRowLoad<LOGN, E, K> ld;
+    LD ld;
     // polynomials in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
     auto poly = [&](int u, int t) {
         return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
@@ -1583,7 +1647,8 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
     ld.fetch(poly(wg / KL, 0), wg % KL, 0, tid);
     for (;;) {
         const int r = wg % KL, u = wg / KL;
-        const ModD m = C->mod[r];
+        const ModD m = C->mod[K ? r : r >> 1];
+        const int pr = K ? r : MAXPR + r;
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         p += (int)gridDim.x;
         const bool more = p < nwg;
@@ -1595,14 +1660,20 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
 #pragma unroll
         for (int t = 0; t < NT; t++) {
             double x[E];
-            {
-                MulRowLoad<LOGN, E, K> hi;
+            auto fetch_next = [&]() {
+                ld.fetch(t + 1 < NT ? poly(u, t + 1) : poly(wg_next / KL, 0), t + 1 < NT ? r : wg_next % KL, 0, tid);
+            };
+            if constexpr (LD::kWhole) {
+                ld.finish(x, r, m, C);
+                fetch_next();
+            } else {
+                LD hi;
                 hi.fetch(poly(u, t), r, H, tid);
                 ld.finish(x, r, m, C);
                 hi.finish(x + H, r, m, C);
             }
             fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
-            ld.fetch(t + 1 < NT ? poly(u, t + 1) : poly(wg_next / KL, 0), t + 1 < NT ? r : wg_next % KL, 0, tid);
+            if constexpr (!LD::kWhole) fetch_next();
             double y[E], z[E];
 #pragma unroll
             for (int it = 0; it < E; it++) x[it] = y[it] = z[it] = red(x[it], m);
@@ -1653,7 +1724,7 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
                 n_inv = t + 1;
             }
             for (int i = 0; i < n_inv; i++) {
-                inv_row<LOGN, E>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, r, C);
+                inv_row<LOGN, E>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, pr, C);
 #pragma unroll
                 for (int it = 0; it < E; it++) y[it] = z[it];
                 if (i + 1 < n_inv) lds_barrier();
@@ -1701,64 +1772,106 @@ __device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, 
 // window of a few elements instead of in two halves at once.  Kernel, 12 groups of 128, N = 8192, three primes: 2100 us with everything
 // in registers, 1890 with the halves one after the other, 1760 with the first sum in memory too, 1640 with the window (2 to 5
 // elements within 3 %).  At N = 4096 registers suffice, and the sum in memory costs 3 % of A V, 12 heads (419 us; 406 in registers).
-template <int LOGN, int E, int K>
+template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
                    const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
-    constexpr int T = (1 << LOGN) / E, KL = 2 * K + 1, W = K == 1 ? 8 : K == 2 ? 4 : 3;
-    constexpr bool FAR = LOGN > 12;
+    constexpr int T = (1 << LOGN) / E, W = K == 1 ? 8 : K == 2 ? 4 : 3;
+    const int KL = K ? 2 * K + 1 : A.k;
+    constexpr bool FAR = LOGN > 12 && !HAT;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
-    __shared__ double park[1 << LOGN];
+    __shared__ double park[HAT ? 1 : 1 << LOGN];
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
         const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
         const int u_first = g * group + part * group / parts, u_end = g * group + (part + 1) * group / parts;
-        const ModD m = C->mod[r];
+        const ModD m = C->mod[K ? r : r >> 1];
+        const int pr = K ? r : MAXPR + r;
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         // the first component's sum: pair q of a thread at far[q * T + tid]
         cg_double2v *far = reinterpret_cast<cg_double2v *>(st.dst + ((size_t)(gp * 3 * KL + r) << LOGN));
         double d0[E], d1[E], d2[E];
 #pragma unroll
         for (int it = 0; it < E; it++) d0[it] = d1[it] = d2[it] = 0.0;
+        // polynomials of a unit in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
+        constexpr int NT = HAT ? 2 : 4;
+        auto poly = [&](int u, int t) {
+            return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
+        };
+        MulRowLoad<LOGN, E, 0> whole;
+        if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, 0, tid);
         for (int u = u_first; u < u_end; u++) {
-            double keep[E];
+            auto row = [&](double *x, int t) {
+                if constexpr (K == 0) {
+                    whole.finish(x, r, m, C);
+                    whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, 0, tid);
+                } else {
+                    lift_row<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
+                }
+            };
+            if constexpr (HAT) {
+                const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
 #pragma unroll
-            for (int t = 0; t < 4; t++) {
-                double x[E];
-                lift_row<LOGN, E, K, W>(x, (t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1), r, tid, m, C);
-                lds_barrier();      // the previous transform's LDS reads
-                fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
-                cg_double2v s0[E / 2];
-                int tk = tid;
-                asm volatile("" : "+v"(tk));
-                if (FAR && t == 1) {
+                for (int t = 0; t < 2; t++) {
+                    double x[E];
+                    row(x, t);
+                    lds_barrier();      // the previous transform's LDS reads
+                    fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                    int tk = tid;
+                    asm volatile("" : "+v"(tk));
 #pragma unroll
-                    for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
-                    if (u != u_first) {
-#pragma unroll
-                        for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
+                    for (int it = 0; it < E; it++) {
+                        const double b0 = red(at32(y0, chunk_elem<E>(tk, it)), m), b1 = red(at32(y1, chunk_elem<E>(tk, it)), m);
+                        x[it] = red(x[it], m);
+                        if (t == 0) {
+                            d0[it] += mulmod(x[it], b0, m);
+                            d1[it] += mulmod(x[it], b1, m);
+                        } else {
+                            d1[it] += mulmod(x[it], b0, m);
+                            d2[it] += mulmod(x[it], b1, m);
+                        }
                     }
                 }
+            } else {
+                double keep[E];
 #pragma unroll
-                for (int it = 0; it < E; it++) {
-                    x[it] = red(x[it], m);
-                    if (t == 0) park[tid + it * T] = x[it];
-                    if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
-                    if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
-                    if (t == 3) {
-                        d1[it] += mulmod(park[tid + it * T], x[it], m);
-                        d2[it] += mulmod(x[it], keep[it], m);
+                for (int t = 0; t < 4; t++) {
+                    double x[E];
+                    row(x, t);
+                    lds_barrier();      // the previous transform's LDS reads
+                    fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                    cg_double2v s0[E / 2];
+                    int tk = tid;
+                    asm volatile("" : "+v"(tk));
+                    if (FAR && t == 1) {
+#pragma unroll
+                        for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
+                        if (u != u_first) {
+#pragma unroll
+                            for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
+                        }
                     }
-                    if (t == 1 || t == 2) keep[it] = x[it];
-                }
-                // (a unit adds less than 1.2 p)
-                if (FAR && t == 1) {
 #pragma unroll
-                    for (int q = 0; q < E / 2; q++) {
-                        const double a = mulmod(park[tid + 2 * q * T], x[2 * q], m),
-                                     b = mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m);
-                        put32(far + q * T, tk, cg_double2v{red(s0[q].x + a, m), red(s0[q].y + b, m)});
+                    for (int it = 0; it < E; it++) {
+                        x[it] = red(x[it], m);
+                        if (t == 0) park[tid + it * T] = x[it];
+                        if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
+                        if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
+                        if (t == 3) {
+                            d1[it] += mulmod(park[tid + it * T], x[it], m);
+                            d2[it] += mulmod(x[it], keep[it], m);
+                        }
+                        if (t == 1 || t == 2) keep[it] = x[it];
+                    }
+                    // (a unit adds less than 1.2 p)
+                    if (FAR && t == 1) {
+#pragma unroll
+                        for (int q = 0; q < E / 2; q++) {
+                            const double a = mulmod(park[tid + 2 * q * T], x[2 * q], m),
+                                         b = mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m);
+                            put32(far + q * T, tk, cg_double2v{red(s0[q].x + a, m), red(s0[q].y + b, m)});
+                        }
                     }
                 }
             }
@@ -1779,7 +1892,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
             // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
             // registers before any thread stores results over it)
             lds_barrier();
-            inv_row<LOGN, E>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, r, C);
+            inv_row<LOGN, E>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 d0[it] = d1[it];
@@ -1878,24 +1991,41 @@ constexpr int PW_THREADS = 256;
 //   y is below B/2 in magnitude, so its centred lift from the auxiliary basis is exact.
 // tens[(b*parts+q)*3+c][r][n], summed over q (lazy, coefficient order) -> out[b][c][i][n] canonical uint64;
 // acc != 0 adds the result to what out already holds (sum of products).
-template <int K>
+// HALF: rows of two half rows whose last inverse stage is still to be taken: the workgroup's waves 0 and 1 take 128
+// coefficients of the first half, waves 2 and 3 those of the second that they pair with, and read the same lines.
+// 96 products, six primes: 199 us (175 from whole rows, 213 with one thread for both of a pair).
+template <int K, bool HALF>
 __global__ void __launch_bounds__(PW_THREADS)
 scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int parts, int acc,
              const DevConst *__restrict__ C)
 {
     constexpr int L = K + 1;
-    const int logn = C->logn, chunks = (1 << logn) / PW_THREADS;
-    const int bc = (int)blockIdx.x / chunks, n = ((int)blockIdx.x % chunks) * PW_THREADS + (int)threadIdx.x;
+    const int logn = C->logn, chunks = (1 << logn) / PW_THREADS, tid = (int)threadIdx.x;
+    const int bc = (int)blockIdx.x / chunks, chunk = (int)blockIdx.x % chunks;
+    const int n = HALF ? chunk * (PW_THREADS / 2) + (tid & (PW_THREADS / 2 - 1)) : chunk * PW_THREADS + tid;
+    const bool upper = HALF && __builtin_amdgcn_readfirstlane(tid) >= PW_THREADS / 2;
+    const size_t half = HALF ? (size_t)1 << (logn - 1) : 0;
     const double *src = tens + (((size_t)((bc / 3) * parts * 3 + bc % 3) * (K + L)) << logn);
-    const double t = C->tmod;
     double e[K + L];
+    // element n; HALF: the pair's sum or difference
+    auto at = [&](int i) {
+        const double *row = src + ((size_t)i << logn);
+        if (!HALF) return at32(row, n);
+        const double b = at32(row + half, n);
+        return at32(row, n) + (upper ? -b : b);
+    };
 #pragma unroll
-    for (int i = 0; i < K + L; i++) e[i] = at32(src + ((size_t)i << logn), n);
+    for (int i = 0; i < K + L; i++) e[i] = at(i);
     for (int q = 1; q < parts; q++) {
         src += (size_t)(3 * (K + L)) << logn;
 #pragma unroll
-        for (int i = 0; i < K + L; i++) e[i] = red(e[i], C->mod[i]) + at32(src + ((size_t)i << logn), n);
+        for (int i = 0; i < K + L; i++) e[i] = red(e[i], C->mod[i]) + at(i);
     }
+    if (upper) {
+#pragma unroll
+        for (int i = 0; i < K + L; i++) e[i] = mulmod(e[i], C->itw1[i], C->mod[i]);
+    }
+    const double t = C->tmod;
     double x[K], dq[K], y[L], db[L];
 #pragma unroll
     for (int i = 0; i < K; i++) x[i] = mulmod(e[i], t, C->mod[i]);
@@ -1908,12 +2038,50 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int pa
         y[j] = mulmod(te - rj, C->Qinv_b[j], mb);
     }
     garner_balanced<L>(C->b2q, C->mod + K, y, db);
-    uint64_t *o = out + (((size_t)bc * K) << logn) + n;
+    uint64_t *o = out + (((size_t)bc * K) << logn) + (upper ? half : 0) + n;
 #pragma unroll
     for (int i = 0; i < K; i++) {
         double v = canon(horner<L>(C->b2q, C->mod[i], db, i), C->mod[i]);
         if (acc) v = addmod_canon(v, u64_to_f64(o[(size_t)i << logn]), C->mod[i]);
         o[(size_t)i << logn] = f64_to_u64(v);
+    }
+}
+
+// Operands of products at N = 16384: every polynomial named by src -> its residues modulo the k ciphertext primes and (centred
+// lift) the l auxiliary ones, first transform stage taken: rows dst[poly][k+l][2][N/2] of two half rows each, |x| <= FWD_IN 2^50.
+// One thread has coefficients n and n + N/2 and shares their mixed-radix digits between the auxiliary primes.
+template <int K>
+__global__ void __launch_bounds__(PW_THREADS)
+lift_kernel(MulSrc src, double *__restrict__ dst, const DevConst *__restrict__ C)
+{
+    constexpr int L = K + 1;
+    const int logn = C->logn, half = 1 << (logn - 1), chunks = half / PW_THREADS;
+    const int pp = (int)blockIdx.x / chunks, n = ((int)blockIdx.x % chunks) * PW_THREADS + (int)threadIdx.x;
+    const uint64_t *row = src.poly(pp, K);
+    double *o = dst + (((size_t)src.dst_poly(pp) * (K + L)) << logn);
+    double x[2][K], dg[2][K];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int i = 0; i < K; i++) x[h][i] = u64_to_f64(at32(row + ((size_t)i << logn) + h * half, n));
+    garner_balanced<K>(C->q2b, C->mod, x[0], dg[0]);
+    garner_balanced<K>(C->q2b, C->mod, x[1], dg[1]);
+#pragma unroll
+    for (int r = 0; r < K + L; r++) {
+        const ModD m = C->mod[r];
+        double a, b;
+        if (r < K) {
+            a = x[0][r < K ? r : 0];
+            b = x[1][r < K ? r : 0];
+        } else {
+            a = horner<K>(C->q2b, m, dg[0], r - K);
+            b = horner<K>(C->q2b, m, dg[1], r - K);
+        }
+        // |a| <= 0.51, |b w| <= 0.5 + 0.1875 * 1.25: together below 1.25
+        a = red(a, m);
+        const double t = mulmod(b, C->tw1[r], m);
+        put32(o + ((size_t)r << logn), n, a + t);
+        put32(o + ((size_t)r << logn) + half, n, a - t);
     }
 }
 
