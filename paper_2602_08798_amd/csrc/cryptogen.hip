@@ -936,7 +936,7 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
     }
 #undef CG_MULROW
 }
-// Sums of products over groups of units in one launch; every group is taken in `parts` parts.  HAT: y transformed (N = 16384)
+// Sums of products over groups of units in one launch; every group is taken in `parts` parts.  HAT: y transformed (N = 4096 and 16384)
 template <bool HAT>
 static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t groups,
                               uint32_t group, uint32_t parts)
@@ -956,14 +956,18 @@ static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, dou
                              (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
     if (half) CG_MULSUMROW(13, 0, HAT);
+    switch (c->logn * 10 + c->k) {
+    case 121: CG_MULSUMROW(12, 1, HAT);
+    case 122: CG_MULSUMROW(12, 2, HAT);
+    case 123: CG_MULSUMROW(12, 3, HAT);
+    default: break;
+    }
     if constexpr (!HAT) {
         switch (c->logn * 10 + c->k) {
-        case 121: CG_MULSUMROW(12, 1, false);
-        case 122: CG_MULSUMROW(12, 2, false);
-        case 123: CG_MULSUMROW(12, 3, false);
         case 131: CG_MULSUMROW(13, 1, false);
         case 132: CG_MULSUMROW(13, 2, false);
         case 133: CG_MULSUMROW(13, 3, false);
+        default: break;
         }
     }
     return CG_EINVAL;
@@ -975,18 +979,23 @@ static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, dou
 // top for the traffic.  us at N = 8192, three primes, groups x units, three launches / one: 12 x 4 89 / 120, 12 x 8 158 / 170,
 // 16 x 8 235 / 212, 6 x 8 98 / 120, 3 x 8 80 / 76, 4 x 16 140 / 122, 8 x 100 1501 / 1222; N = 4096, two primes: 12 x 4 44 / 41,
 // 12 x 8 62 / 55, 12 x 64 438 / 295: the model has every one of these on the right side.
-static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint32_t &parts)
+//
+// With one operand transformed already (hat) a unit has half the work in one launch, and two launches and an operand's way through
+// memory fewer.  At N = 4096 that wins throughout (decode step with a copy of the cache, heads x ciphertexts: 2 x 2 161.9 / 158.7 us,
+// 12 x 4 176.9 / 173.4, 16 x 8 308 / 288).  At N = 8192 the sums spill beside the transform: 1 x 1 187 / 201, 4 x 2 212 / 222, 12 x 4
+// 423 / 438, 16 x 8 925 / 903.
+static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint32_t &parts, bool hat = false)
 {
-    if (c->logn > 13 || c->k > 3) return false;
+    if (c->logn > (hat ? 12 : 13) || c->k > 3) return false;
     if (c->dry) return c->dry_rows;
     const double n = c->n_cu, base = (double)groups * c->KL;
     double best = 1e30;
     uint32_t best_parts = 1;
     for (uint32_t q = 1; q <= group && q <= 64; q++) {
-        const double t = std::ceil(base * q / n) * (6.0 * ((group + q - 1) / q) + 2.0);
+        const double t = std::ceil(base * q / n) * ((hat ? 3.0 : 6.0) * ((group + q - 1) / q) + 2.0);
         if (t < best) { best = t; best_parts = q; }
     }
-    if (best >= 1.25 * (4.0 * base * group / n + 0.5 * group * std::ceil(3.0 * base / n) + 1.2)) return false;
+    if (!hat && best >= 1.25 * (4.0 * base * group / n + 0.5 * group * std::ceil(3.0 * base / n) + 1.2)) return false;
     parts = best_parts;
     return true;
 }
@@ -1049,6 +1058,9 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
             CG_TRY(b_ext || shared ? launch_mul_row<true>(c, s, A, tens, batch, shared ? B : n_a, shared ? n_a : B)
                                    : launch_mul_row<false>(c, s, A, tens, batch, B, B));
         }
+    } else if (sum_group && a_group == 1 && b_ext && mul_sum_parts(c, n_out, sum_group, parts, true)) {
+        CG_TRY(launch_mul_sum_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
+                                        tens, n_out, sum_group, parts));
     } else if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
         CG_TRY(launch_mul_sum_row<false>(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                   tens, n_out, sum_group, parts));

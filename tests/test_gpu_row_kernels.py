@@ -214,3 +214,29 @@ def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
     for h in range(heads):
         want = attention.decode_scores(env.orc, q[h % 2], kc[h % 3], raw_rlk, {g: raw_g}, d2)
         assert np.array_equal(got[h, 0], want), h
+
+
+@pytest.mark.parametrize("name,shapes", [("C1", ((1, 1), (3, 7), (52, 2))), ("k3", ((2, 5),))])
+def test_context_sums_with_a_transformed_copy_in_parts(name, shapes):
+    """N = 4096: products with a transformed cache summed in one launch (one part per group, several, several rounds)"""
+    from oracle import attention
+    env = _env(name)
+    d2 = env.n // 4
+    raw_rlk, rlk = env.key(80)
+    gs = env.ctx.round_galois(1, d2, 1)
+    raws, keys = zip(*[env.key(81 + i) for i in range(len(gs))])
+    a, vc = _extremes(env, env.cts(90, 3)), _extremes(env, env.cts(91, 2))
+    for heads, n_cts in shapes:
+        say(f"decode_context_hoisted {name}: {heads} heads of {n_cts} ciphertexts, transformed copy")
+        n = heads * n_cts
+        ext = env.ctx.cache_extend(_tiled(env, vc, n), heads, n_cts, n_cts, env.ctx.empty_ext(n))
+        got = env.host(env.ctx.decode_context_hoisted(_tiled(env, a, n), None, heads, n_cts, d2, 1, rlk, list(keys), vext=ext,
+                                                      sum_before_scaling=True))
+        want = {}
+        for h in range(heads):
+            us = range(h * n_cts, (h + 1) * n_cts)
+            first = us[0] % 6
+            if first not in want:
+                want[first] = attention.decode_context_hoisted(env.orc, [a[u % 3] for u in us], [vc[u % 2] for u in us], raw_rlk,
+                                                               dict(zip(gs, raws)), d2, 1, sum_first=True)
+            assert np.array_equal(got[h], want[first]), (name, heads, n_cts, h)
