@@ -1364,6 +1364,16 @@ static int do_add(cg_ctx *c, hipStream_t s, const uint64_t *a, const uint64_t *b
     return CG_OK;
 }
 
+// One launch for all of them: a copy per ciphertext through the runtime takes 4.7 us each, one after the other (A V of 12 heads
+// 2306 -> 2282 us a call; N = 4096, 6 heads 216 -> 208).
+static int do_copy(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint64_t *dst, size_t dst_stride, uint32_t cts)
+{
+    const unsigned per = (unsigned)(2 * c->k * (c->N / (2 * PW_THREADS)));
+    CG_LAUNCH_PW(KID_ADD, (double)limb_bytes(c) * 4.0 * c->k * cts, (double)2 * c->k * cts, copy_kernel, cts * per, src, src_stride, dst,
+                 dst_stride, (int)per);
+    return CG_OK;
+}
+
 static bool ptrs_ok(std::initializer_list<const void *> ps)
 {
     for (const void *p : ps) if (!p || !aligned16(p)) return false;
@@ -1958,8 +1968,7 @@ static int rotated_copies(cg_ctx *c, hipStream_t s, const uint64_t *src, uint32_
 {
     const uint32_t m = (uint32_t)c->N / d2, H = m / 2;
     const size_t ct2 = (size_t)2 * c->k * c->N;
-    for (uint32_t h = 0; h < heads; h++)
-        CG_HIP(hipMemcpyAsync(kp + (size_t)h * m * ct2, src + (size_t)h * ct2, ct2 * 8, hipMemcpyDeviceToDevice, s));
+    CG_TRY(do_copy(c, s, src, ct2, kp, m * ct2, heads));
     const uint32_t g_blk = pow3_mod(d2, 2u * c->N), g_swap = 2u * c->N - 1;
     for (uint32_t r = 1; r < H; r++)
         CG_TRY(do_rotate(c, s, kp + (size_t)(r - 1) * ct2, g_blk, gk_blk, kp + (size_t)r * ct2, heads, 0, ws,
@@ -1976,8 +1985,7 @@ static int rotated_copies_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *src,
 {
     const uint32_t m = (uint32_t)c->N / d2, H = m / 2, two_n = 2u * c->N;
     const size_t ct2 = (size_t)2 * c->k * c->N;
-    for (uint32_t h = 0; h < heads; h++)
-        CG_HIP(hipMemcpyAsync(kp + (size_t)h * m * ct2, src + (size_t)h * ct2, ct2 * 8, hipMemcpyDeviceToDevice, s));
+    CG_TRY(do_copy(c, s, src, ct2, kp, m * ct2, heads));
     std::vector<uint32_t> gs(m - 1);
     for (uint32_t u = 1; u < m; u++) {
         const uint64_t g = pow3_mod(d2 * (u % H), two_n);
@@ -2087,7 +2095,6 @@ extern "C" int cg_prefill_repack(cg_ctx *c, void *stream, const uint64_t *x, uin
     const uint32_t m = (uint32_t)c->N / d2, H = m / 2, batch = heads * m;
     CG_REQUIRE(batch_ok(batch));
     const uint32_t wdt = H < d2 ? H : d2;        // diagonals packed into one output
-    const uint32_t n_out = batch / wdt;
     int levels = 0;
     for (uint32_t sh = 1; sh < wdt; sh <<= 1) {
         CG_REQUIRE(gk_right[levels] && aligned16(gk_right[levels]));
@@ -2104,15 +2111,14 @@ extern "C" int cg_prefill_repack(cg_ctx *c, void *stream, const uint64_t *x, uin
                            LB * (2.0 * rows + c->k)));
     // pairwise tree inside every group of wdt consecutive units: at level l (shift 2^l)
     // y[j 2^(l+1)] += rotate_right(y[j 2^(l+1) + 2^l], 2^l); rotate right by sh = Galois 3^(N/2 - sh)
+    // (the last level leaves one ciphertext per group: straight to the output)
     for (int l = 0; l < levels; l++) {
         const uint32_t sh = 1u << l;
         const size_t stride = (size_t)2 * sh * ct2;
-        CG_TRY(do_rotate(c, s, y + (size_t)sh * ct2, pow3_mod((uint32_t)c->N / 2 - sh, 2u * c->N), gk_right[l], y,
-                         batch / (2 * sh), 1, w.p, stride, stride, y, stride));
+        const bool last = l + 1 == levels;
+        CG_TRY(do_rotate(c, s, y + (size_t)sh * ct2, pow3_mod((uint32_t)c->N / 2 - sh, 2u * c->N), gk_right[l], last ? out : y,
+                         batch / (2 * sh), 1, w.p, stride, last ? ct2 : stride, y, stride));
     }
-    // gather the group leaders
-    for (uint32_t o = 0; o < n_out; o++)
-        CG_HIP(hipMemcpyAsync(out + (size_t)o * ct2, y + (size_t)o * wdt * ct2, ct2 * 8, hipMemcpyDeviceToDevice, s));
     return CG_OK;
 }
 
@@ -2150,8 +2156,10 @@ static int cpvm_impl(cg_ctx *c, void *stream, const uint64_t *x, const void *dia
     uint64_t *copies = w.take<uint64_t>((size_t)2 * c->k * n_diag);
     double *f = w.take<double>((size_t)2 * c->k * n_diag);
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * units), *xb = w.take<uint64_t>((size_t)2 * c->k * units);
-    CG_HIP(hipMemcpyAsync(copies, x, ct2 * 8, hipMemcpyDeviceToDevice, s));
-    if (gk_copies && n_diag > 1) {
+    // (hoisted: copy 0 is x itself and stays where it is)
+    const bool hoisted = gk_copies && n_diag > 1;
+    if (!hoisted) CG_TRY(do_copy(c, s, x, ct2, copies, ct2, 1));
+    if (hoisted) {
         uint32_t cg[64];
         for (uint32_t cc = 1; cc < n_diag; cc++) cg[cc - 1] = pow3_mod(cc, 2u * c->N);
         CG_TRY(do_rotate_hoisted(c, s, x, ct2, n_diag - 1, cg, gk_copies, copies + ct2, n_diag, 1, w.p));
@@ -2161,8 +2169,9 @@ static int cpvm_impl(cg_ctx *c, void *stream, const uint64_t *x, const void *dia
             CG_TRY(do_rotate(c, s, copies, pow3_mod(sh, 2u * c->N), gk_shift[l], copies + (size_t)sh * ct2, sh, 0, w.p));
     }
     const size_t crows = (size_t)n_diag * 2 * c->k, rows = (size_t)units * 2 * c->k;
-    CG_TRY(launch_fwd(c, s, crows, LdRowsU64{copies, nullptr, c->k, c->logn}, StF64Red{f, c->logn}, KID_FWD_ROWS,
-                      LB * 2.0 * crows));
+    const int x_rows = 2 * c->k;
+    CG_TRY(launch_fwd(c, s, crows, LdRowsFirst{hoisted ? x : copies, copies + ct2, x_rows, c->k, c->logn}, StF64Red{f, c->logn},
+                      KID_FWD_ROWS, LB * 2.0 * crows));
     CG_TRY(launch_inv(c, s, rows, LdInvPlainSum{f, static_cast<const double *>(diags), (int)n_diag, c->logn},
                       StInvU64{xa, c->logn}, KID_INV_MULPLAIN,
                       LB * (crows + (double)units * n_diag * c->k + rows)));
@@ -2234,6 +2243,7 @@ static int warm_launch_table(cg_ctx *c)
         CG_TRY(launch_fwd(c, s, rows, ld, StU64{u, c->logn}, KID_FWD_ROWS, LB));
         CG_TRY(launch_fwd(c, s, rows, ld, StF64{f, c->logn}, KID_FWD_ROWS, LB));
         CG_TRY(launch_fwd(c, s, rows, ld, StF64Red{f, c->logn}, KID_FWD_ROWS, LB));
+        CG_TRY(launch_fwd(c, s, rows, LdRowsFirst{u, u, 1, c->k, c->logn}, StF64Red{f, c->logn}, KID_FWD_ROWS, LB));
         CG_TRY(launch_fwd(c, s, rows, LdPlain{u, c->logn}, StF64Red{f, c->logn}, KID_FWD_PLAIN, LB));
         CG_TRY(launch_inv(c, s, rows, LdInvU64{u, nullptr, c->k, c->logn}, StInvU64{u, c->logn}, KID_INV_U64, LB));
         const LdInvMulPlain mp{f, f, 1, 1, 0, 0, c->logn};

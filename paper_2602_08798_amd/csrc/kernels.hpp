@@ -832,6 +832,26 @@ struct LdRowsU64 {
     }
 };
 
+// the same with the first n_first rows from `first` and the others, counted from there on, from `src`
+struct LdRowsFirst {
+    static constexpr int kRaw = 1;
+    static constexpr bool kPrefetch = true;
+    static constexpr bool kScatter = false;
+    const uint64_t *first, *src;
+    int n_first, pmod, logn;
+    __device__ __forceinline__ int prime(int wg, const DevConst *) const { return wg % pmod; }
+    __device__ __forceinline__ int share(const DevConst *) const { return 1; }
+    __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const { return wg; }
+    __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *, uint64_t *raw) const
+    {
+        raw[0] = (wg < n_first ? first + ((size_t)wg << logn) : src + ((size_t)(wg - n_first) << logn))[idx];
+    }
+    __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD, const DevConst *) const
+    {
+        return u64_to_f64(raw[0]);
+    }
+};
+
 // Inputs of a batch of tensor products.  The source ciphertexts are the n_a "a" operands followed
 // by the `batch` "b" operands; polynomial pp = 2 * ciphertext + component.  Every polynomial is
 // transformed once over the k ciphertext primes (LdMulQ) and the l auxiliary primes (LdMulAux) into
@@ -2607,6 +2627,14 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
             acc[(((size_t)((ug * U + u) * 2 + c) * L + r) << logn) + idx] = v;
         }
     }
+}
+
+// ciphertext u of `src` (src_stride words apart) to dst + u * dst_stride, two words per thread
+__global__ void __launch_bounds__(PW_THREADS)
+copy_kernel(const uint64_t *__restrict__ src, size_t src_stride, uint64_t *__restrict__ dst, size_t dst_stride, int blocks_per_ct)
+{
+    const int u = (int)blockIdx.x / blocks_per_ct, at = (((int)blockIdx.x % blocks_per_ct) * PW_THREADS + (int)threadIdx.x) * 2;
+    *reinterpret_cast<ulonglong2 *>(dst + u * dst_stride + at) = *reinterpret_cast<const ulonglong2 *>(src + u * src_stride + at);
 }
 
 // out = a + b over `rows` rows of N residues, row w modulo q_(w % k)
