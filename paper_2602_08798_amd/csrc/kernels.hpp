@@ -535,12 +535,16 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
 // ---------------------------------------------------------------------------
 // storers that add to what the destination holds (fetch() brings it in)
 template <class ST> struct st_adds { static constexpr bool value = false; };
+template <class ST> struct st_adds<const ST> : st_adds<ST> {};
+template <class ST> struct st_adds<const ST &> : st_adds<ST> {};
 
 // from != null: the first pass takes its elements from registers, in chunk_elem order
+// early: the first eight words that a storer adds to
 template <int LOGN, int E, int PASS, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
-                                         const ModD m, int pr, const DevConst *C, const double *from = nullptr)
+                                         const ModD m, int pr, const DevConst *C, const double *from = nullptr,
+                                         const uint64_t *early = nullptr)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -575,20 +579,10 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
             }
         }
     }
-    // a storer that adds to what is there has it brought in eight elements at a time, the first eight
-    // before the butterflies where registers allow: read one by one between the stores (which might
-    // alias), every element would wait for its own trip to memory
     static_assert(!(last && st_regs<ST>::value) || G == 1, "one group per thread in the last pass");
     constexpr bool adds = last && st_adds<ST>::value;
-    static_assert(!adds || (1 << R) % 8 == 0, "eight elements of a group at a time");
+    static_assert(!adds || (G == 1 && (1 << R) % 8 == 0), "eight elements of the one group at a time");
     uint64_t old[adds ? 8 : 1];
-    auto fetch_old = [&](int g, int c0) {
-        if constexpr (adds) {
-#pragma unroll
-            for (int c = 0; c < 8; c++) old[c] = st.fetch(wg, base[g] + ((c0 + c) << L), C);
-        }
-    };
-    if (E <= 8) fetch_old(0, 0);
 #pragma unroll
     for (int g = 0; g < G; g++) {
         if (PASS == P::NP - 1) {
@@ -629,7 +623,14 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
         for (int c = 0; c < (1 << R); c++) {
             // the last pass pairs elements N/2 apart with consecutive lanes on consecutive
             // addresses: it stores straight to global memory
-            if (adds && c % 8 == 0 && (E > 8 || g || c)) fetch_old(g, c);
+            if constexpr (adds) {
+                if (c == 0) {
+#pragma unroll
+                    for (int i = 0; i < 8; i++) old[i] = early[i];
+                } else if (c % 8 == 0) {
+                    st.template fetch<(1 << LOGN) / E>(old, tid, c);
+                }
+            }
             if (!last) {
                 if (L > 0) lds[pb + pad(c << L)] = v[g][c];
                 else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
@@ -1342,28 +1343,41 @@ struct StInvU64 {
     {
         put32(dst + ((size_t)wg << logn), idx, f64_to_u64(canon(v, m)));
     }
+    __device__ __forceinline__ const StInvU64 &at_row(int, int) const { return *this; }
 };
 // cache append: workgroup -> (cache c, comp, prime); target row = cache + c*stride + row;
 // fresh != 0 stores, otherwise adds to what is there
+struct StAppendRow {        // for one row
+    uint64_t *row;
+    int fresh;
+    // the words of elements tid + c T, c = c0 .. c0 + 7: one branch around all the loads.  (A test per element became a
+    // block per two loads with a wait in each, four trips to memory one after the other in every append: 24 caches of
+    // N = 8192, 128 appends 2113 us, now 1982.)
+    template <int T> __device__ __forceinline__ void fetch(uint64_t *old, int tid, int c0) const
+    {
+#pragma unroll
+        for (int c = 0; c < 8; c++) old[c] = 0;
+        if (!fresh) {
+#pragma unroll
+            for (int c = 0; c < 8; c++) old[c] = at_lane(row + (c0 + c) * T, tid);
+        }
+    }
+    __device__ __forceinline__ void store(int, int idx, double v, uint64_t old, const ModD m, const DevConst *) const
+    {
+        put32(row, idx, f64_to_u64(addmod_canon(canon(v, m), u64_to_f64(old), m)));
+    }
+};
 struct StInvAppend {
     uint64_t *cache;        // first target ciphertext (cache 0)
     size_t cache_stride;    // uint64 between consecutive caches' target ciphertexts
     int fresh, logn;
-    __device__ __forceinline__ uint64_t *at(int wg, int idx, const DevConst *C) const
+    __device__ __forceinline__ StAppendRow at_row(int wg, int k) const
     {
-        const int rows = 2 * C->k, c = wg / rows, row = wg % rows;
-        return cache + (size_t)c * cache_stride + ((size_t)row << logn) + idx;
-    }
-    __device__ __forceinline__ uint64_t fetch(int wg, int idx, const DevConst *C) const
-    {
-        return fresh ? 0 : *at(wg, idx, C);
-    }
-    __device__ __forceinline__ void store(int wg, int idx, double v, uint64_t old, const ModD m, const DevConst *C) const
-    {
-        *at(wg, idx, C) = f64_to_u64(addmod_canon(canon(v, m), u64_to_f64(old), m));
+        const int rows = 2 * k, c = wg / rows, row = wg % rows;
+        return StAppendRow{cache + (size_t)c * cache_stride + ((size_t)row << logn), fresh};
     }
 };
-template <> struct st_adds<StInvAppend> { static constexpr bool value = true; };
+template <> struct st_adds<StAppendRow> { static constexpr bool value = true; };
 
 // ---------------------------------------------------------------------------
 // Transforms of a row that is in registers already or stays there: the pass sequence only.
@@ -1962,6 +1976,7 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
     for (;;) {
         const int pr = wg % k;
         const ModD m = C->mod[pr];
+        const auto str = st.at_row(wg, k);
         const double *tw = tw_all + ((size_t)pr << LOGN), *itw = itw_all + ((size_t)pr << LOGN);
         const double *prow = plain + ((size_t)(((wg / (2 * k)) * pstride + pofs) * k + pr) << LOGN);
         double twa[TWREGS], twb[TWREGS], in[E], pl[PF ? E : 1];
@@ -1983,18 +1998,25 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
         load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
         wave_sync();
         if constexpr (NP > 4) {
-            inv_pass<LOGN, E, 4>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 3>(lds, st, wg, tid, itw, twb, twa, m, pr, C);
+            inv_pass<LOGN, E, 4>(lds, str, wg, tid, itw, twa, twb, m, pr, C);
+            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twb, twa, m, pr, C);
         } else {
-            inv_pass<LOGN, E, 3>(lds, st, wg, tid, itw, twa, twa, m, pr, C);
+            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twa, twa, m, pr, C);
         }
-        inv_pass<LOGN, E, 2>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
-        inv_pass<LOGN, E, 1>(lds, st, wg, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 2>(lds, str, wg, tid, itw, twa, twb, m, pr, C);
+        // What the storer adds to is asked for late: loads return in order, so ahead of the passes' factors it would hold
+        // these up (the factors of the last two passes are scalar loads).  24 caches of N = 8192: 2008 us before the
+        // last pass but one, 1982 before the last; N = 16384: 2059 and 1892; twelve caches of N = 4096: 526 and 537.
+        constexpr bool adds = st_adds<decltype(str)>::value, ahead = LOGN <= 12;
+        uint64_t old[8];
+        if constexpr (adds && ahead) str.template fetch<T>(old, tid, 0);
+        inv_pass<LOGN, E, 1>(lds, str, wg, tid, itw, twb, twa, m, pr, C);
         const int next = wg + (int)gridDim.x;
         if constexpr (PF) {
             if (next < nwg) fetch(next);
         }
-        inv_pass<LOGN, E, 0>(lds, st, wg, tid, itw, twa, twb, m, pr, C);
+        if constexpr (adds && !ahead) str.template fetch<T>(old, tid, 0);
+        inv_pass<LOGN, E, 0>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, old);
         if (next >= nwg) break;
         wg = next;
         lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes

@@ -145,3 +145,22 @@ def test_plain_products_and_appends(name):
         env.ctx.kv_append(cache, 1, 3, tau, env.dev(x), masks, n // 2)
         before = [(env.orc.mul_plain(v, pt[tau]) + (old if tau else 0)) % q for v, old in zip(x, before)]
         _check(env, cache.view(3, 2, env.k, n), before, ("kv_append", tau))
+
+
+# rows of all caches: one to a workgroup, and several (512 workgroups of N = 8192 fill the chip, 256 of N = 16384)
+@pytest.mark.parametrize("name,batches", [("n4096_k2_a2", (1, 300)), ("n8192_k4_a2", (1, 80)), ("n16384_k3", (2, 50))])
+def test_appends_to_many_caches(name, batches):
+    env = _env(name)
+    x, old = _operands(env, 40), _operands(env, 41)
+    pt = np.random.default_rng(42).integers(0, env.prm.t, (2, env.n), dtype=np.uint64)
+    masks = env.ctx.plain_prepare(env.dev(pt))
+    q = np.array(env.prm.q, dtype=np.uint64)[None, :, None]
+    first = [env.orc.mul_plain(v, pt[0]) for v in x]
+    more = [(env.orc.mul_plain(v, pt[1]) + w) % q for v, w in zip(x, old)]
+    for batch in batches:
+        say(f"kv_append {name}: {batch} caches")
+        cache, rows = _tiled(env, old, batch), _tiled(env, x, batch)
+        env.ctx.kv_append(cache, 1, batch, 1, rows, masks, env.n // 2)
+        _check(env, cache, more, ("added", batch))
+        env.ctx.kv_append(cache, 1, batch, 0, rows, masks, env.n // 2)
+        _check(env, cache, first, ("fresh", batch))
