@@ -308,7 +308,8 @@ template <int LOGN, int E, bool CHUNKED, class LD, class F>
 __device__ __forceinline__ void load_row_now(const LD &ld, int wg, int tid, const ModD m, const DevConst *C, F &&sink)
 {
     constexpr int T = (1 << LOGN) / E;
-    constexpr int CH0 = LD::kRaw <= 2 ? 16 : (LD::kRaw <= 4 ? (E >= 16 && CHUNKED ? 4 : 8) : (E >= 16 && CHUNKED ? 2 : 4));
+    constexpr int CH0 = LD::kRaw <= 2 ? (ld_rounds<LD>::value ? 8 : 16)
+                                      : (LD::kRaw <= 4 ? (E >= 16 && CHUNKED ? 4 : 8) : (E >= 16 && CHUNKED ? 2 : 4));
     constexpr int CH = CH0 < E ? CH0 : E;
     auto at = [&](int it) { return CHUNKED ? chunk_elem<E>(tid, it) : tid + it * T; };
     if constexpr (ld_rounds<LD>::value) {
@@ -1300,11 +1301,13 @@ struct LdInvMulPlain {
 
 // sum of ciphertext-plaintext products fused into the load (the decode step's vector-matrix
 // product): workgroup -> (unit u, comp c2, prime i); element = sum over the cn rotated copies of
-// the token of copy_c[c2][i] * diagonal_(u, c)[i].  The 2 cn operands of an element are read
-// where they are used (they would not fit the register slices of the other loaders); the copies
-// are stored reduced, so every product is below 0.6 p and eight of them sum to less than 5 p.
+// the token of copy_c[c2][i] * diagonal_(u, c)[i].  Eight elements' words of one copy are asked for together; a
+// loop over the copies inside an element had its two words' trip to memory to wait for at every step.  36 matrices
+// of 8 diagonals, N = 8192, 37 us in this launch: the call 245 -> 233 us; 96 of 16: 655 -> 555 us.  (Rows of a unit on one
+// XCD, so that its L2 serves both components' reads of a diagonal: 243 us.  The next copy's words asked for ahead: 235,
+// registers spilled.)
 struct LdInvPlainSum {
-    static constexpr int kRaw = 1;
+    static constexpr int kRaw = 2;
     static constexpr bool kPrefetch = false;
     const double *ctf;     // transformed copies [cn][2][k][N], |x| <= p/2
     const double *plain;   // prepared plaintexts [units][cn][k][N]
@@ -1312,21 +1315,22 @@ struct LdInvPlainSum {
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % C->k; }
     __device__ __forceinline__ int share(const DevConst *) const { return 1; }
     __device__ __forceinline__ int out_row(int wg, const DevConst *) const { return wg; }
-    __device__ __forceinline__ void fetch(int, int, const DevConst *, uint64_t *raw) const { raw[0] = 0; }
-    __device__ __forceinline__ double finish(const uint64_t *, int wg, int idx, const ModD m, const DevConst *C) const
+    __device__ __forceinline__ int rounds() const { return cn; }
+    __device__ __forceinline__ void fetch_round(int wg, int idx, int c, const DevConst *C, uint64_t *raw) const
     {
         const int k = C->k, i = wg % k, c2 = (wg / k) & 1, u = wg / (2 * k);
-        const double *a = ctf + ((size_t)(c2 * k + i) << logn) + idx;
-        const double *b = plain + ((((size_t)u * cn) * k + i) << logn) + idx;
-        const size_t sa = (size_t)(2 * k) << logn, sb = (size_t)k << logn;
-        double s = 0.0;
-        for (int c = 0; c < cn; c++) {
-            s += mulmod(a[c * sa], b[c * sb], m);
-            if ((c & 7) == 7) s = red(s, m);
-        }
-        return s;
+        raw[0] = f64_bits(at32(ctf + ((size_t)((c * 2 + c2) * k + i) << logn), idx));
+        raw[1] = f64_bits(at32(plain + ((((size_t)u * cn + c) * k + i) << logn), idx));
     }
+    __device__ __forceinline__ void fetch(int, int, const DevConst *, uint64_t *) const {}
+    __device__ __forceinline__ double finish(const uint64_t *raw, int, int, const ModD m, const DevConst *) const
+    {
+        return mulmod(bits_f64(raw[0]), bits_f64(raw[1]), m);
+    }
+    // the copies are stored reduced: a product is below 0.6 p
+    __device__ __forceinline__ double join(double sum, double term, const ModD m) const { return red(sum, m) + term; }
 };
+template <> struct ld_rounds<LdInvPlainSum> { static constexpr bool value = true; };
 
 struct StInvF64 {
     double *dst;

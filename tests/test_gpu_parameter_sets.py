@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 from workloads.params import ParamSet
 
 from .bruteforce import ntt_primes
-from .test_gpu_parity import Env, say
+from .test_gpu_parity import Env, _block_keys, say
 
 
 def _set(name, log2n, k, nsp, alpha):
@@ -164,3 +164,26 @@ def test_appends_to_many_caches(name, batches):
         _check(env, cache, more, ("added", batch))
         env.ctx.kv_append(cache, 1, batch, 0, rows, masks, env.n // 2)
         _check(env, cache, first, ("fresh", batch))
+
+
+# sums over one copy of the token, and many; rows of all matrices: below a workgroup each, and several
+@pytest.mark.parametrize("name,n_diag,units", [("n4096_k6", 1, 2), ("n4096_k2_a2", 16, 300), ("n8192_k4_a2", 32, 3),
+                                               ("n8192_k4", 2, 80), ("n16384_k3", 1, 50), ("n16384_k3", 8, 2)])
+def test_vector_matrix_products(name, n_diag, units):
+    from oracle import attention
+    env = _env(name)
+    n, d2 = env.n, env.n // 4
+    x = _operands(env, 50)[1]
+    pt = np.random.default_rng(51).integers(0, env.prm.t, (2, n_diag, n), dtype=np.uint64)
+    pt[0, :, ::2] = env.prm.t - 1
+    shift = [pow(3, sh, 2 * n) for sh in attention.cpvm_shifts(n_diag)]
+    block = _block_keys(env, d2)
+    keys = {g: env.key(60 + i) for i, g in enumerate(sorted(set(shift + block)))}
+    raw = {g: keys[g][0] for g in keys}
+    say(f"cpvm {name}: {units} matrices of {n_diag} diagonals")
+    diags = env.ctx.plain_prepare(env.dev(np.ascontiguousarray(pt[np.arange(units) % 2].reshape(-1, n))))
+    got = env.host(env.ctx.cpvm(env.dev(x[None]), diags, units, n_diag, d2, [keys[g][1] for g in shift],
+                                [keys[g][1] for g in block]))
+    want = [attention.cpvm(env.orc, x, list(pt[i]), raw, d2) for i in range(2)]
+    for u in range(units):
+        assert np.array_equal(got[u], want[u % 2]), (name, u)
