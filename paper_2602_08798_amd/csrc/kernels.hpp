@@ -715,9 +715,9 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
     }
 }
 
-// Inverse loaders marked here run with 16 elements per thread at N = 8192, like the forward
-// transforms (two co-resident 512-thread workgroups per compute unit).  It pays for the tensor
-// product, whose launches are large; the key-switch inner product is launched over a few hundred
+// Inverse loaders marked here run with 16 elements per thread at N = 8192 where there are more rows than compute units,
+// like the forward transforms (two co-resident 512-thread workgroups per compute unit).  It pays for the tensor
+// product, whose launches are large then; the key-switch inner product is launched over a few hundred
 // rows at a time and finishes a row sooner on 1024 threads.
 template <class LD> struct inv_wide { static constexpr bool value = false; };
 

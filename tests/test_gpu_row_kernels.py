@@ -240,3 +240,16 @@ def test_context_sums_with_a_transformed_copy_in_parts(name, shapes):
                 want[first] = attention.decode_context_hoisted(env.orc, [a[u % 3] for u in us], [vc[u % 2] for u in us], raw_rlk,
                                                                dict(zip(gs, raws)), d2, 1, sum_first=True)
             assert np.array_equal(got[h], want[first]), (name, heads, n_cts, h)
+
+
+# three rows a product and prime in the transform that forms them: with no more rows than compute units, and just more
+@pytest.mark.parametrize("name,batches", [("C2", (12, 13)), ("mixed", (1, 12)), ("k1", (28, 29))])
+def test_products_of_few_rows(name, batches):
+    env = _env(name)
+    a, b = _extremes(env, env.cts(94, 3)), _extremes(env, env.cts(95, 2))
+    want = {(i, j): env.orc.mul(a[i], b[j]) for i in range(3) for j in range(2)}
+    for batch in batches:
+        say(f"products {name} batch {batch}")
+        got = env.host(env.ctx.mul(_tiled(env, a, batch), _tiled(env, b, batch), batch))
+        for u in range(batch):
+            assert np.array_equal(got[u], want[u % 3, u % 2]), (name, batch, u)
