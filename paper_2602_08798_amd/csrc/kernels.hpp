@@ -301,6 +301,8 @@ template <class LD> struct ld_lifts { static constexpr bool value = false; };
 template <class LD> struct ld_half { static constexpr bool value = false; };
 // Loaders of products' operands: those of N = 16384 are half rows.
 template <class LD> struct ld_no_16384 { static constexpr bool value = false; };
+// Transforms on their own (callers' rows in, rows out), which may use priorities (fwd_pass).
+template <class LD, class ST> struct row_alone { static constexpr bool value = false; };
 
 // Loaders that do not prefetch fetch and finish a row in slices, so that at most about 32 raw
 // words are live per thread however many words an element needs.
@@ -380,10 +382,14 @@ template <> struct st_in_place<StRegs> { static constexpr bool value = true; };
 template <class ST> struct st_regs { static constexpr bool value = false; };
 template <> struct st_regs<StRegs> { static constexpr bool value = true; };
 
+// prio: a wave's priority falls from pass to pass between two barriers, so that those behind catch up and all reach the
+// barrier about together.  (Equal priorities let the oldest wave issue first: it runs ahead and then waits.)  Worth 2 to 7 %
+// where nothing but such rows is on the chip; beside other kernels, whose priority is 0, it holds these up (a step of
+// twelve heads with priorities in every transform: 422 -> 430 us), so callers say where.
 template <int LOGN, int E, int PASS, bool FROM_REGS, class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
                                          const double *__restrict__ tw, const double *twr, double *twr_next,
-                                         const ModD m, int dst_limb)
+                                         const ModD m, int dst_limb, bool prio = false)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -398,6 +404,7 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
     static_assert(!FROM_REGS || (first && L + R == LOGN), "register input only for the first pass");
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     static_assert(!last || !cross, "the last pass must be wave-local (chunk-wise copy-out)");
+    if (prio) __builtin_amdgcn_s_setprio(PASS <= 1 ? 3 : last ? 1 : 2);
     double v[G][1 << R];
     int base[G];
 #pragma unroll
@@ -484,6 +491,10 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int T = (1 << LOGN) / E;
     constexpr int NP = Plan<LOGN, E>::NP;
+    // Rows for a round and a half of workgroups (us, N = 8192: 1000 rows 32.0 -> 31.1, 4000: 132 -> 123, 16384: 488 -> 471;
+    // 1500 rows of 4096: 22.8 -> 21.5; 1000 of 16384: 66.2 -> 63.3).  Below, a gain and a loss by turns, as what is left
+    // over runs on nearly idle units: 60 rows of 8192 7.9 -> 7.5, 250: 8.9 -> 9.3, 512: 17.3 -> 17.0, 600: 21.3 -> 22.5.
+    const bool prio = row_alone<LD, ST>::value && 2 * nwg >= 3 * (int)gridDim.x;
     const int tid = threadIdx.x;
     const int S = ld.share(C);
     int p = blockIdx.x;
@@ -517,14 +528,14 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
 #pragma unroll
             for (int it = 0; it < E; it++) lds[pad(ld.place(chunk_elem<E>(tid, it), 1 << LOGN))] = in[it];
             lds_barrier();
-            fwd_pass<LOGN, E, 0, false>(lds, in, st, tid, tw, twa, twb, m, dl);
+            fwd_pass<LOGN, E, 0, false>(lds, in, st, tid, tw, twa, twb, m, dl, prio);
         } else {
-            fwd_pass<LOGN, E, 0, true>(lds, in, st, tid, tw, twa, twb, m, dl);
+            fwd_pass<LOGN, E, 0, true>(lds, in, st, tid, tw, twa, twb, m, dl, prio);
         }
-        fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, dl);
-        fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, dl);
-        if constexpr (NP > 3) fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, dl);
-        if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, dl);
+        fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, dl, prio);
+        fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, dl, prio);
+        if constexpr (NP > 3) fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, dl, prio);
+        if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, dl, prio);
         if (!more) break;
         wg = wg_next;
         lds_barrier();   // the copy-out reads of this row precede the next row's LDS writes
@@ -545,7 +556,7 @@ template <int LOGN, int E, int PASS, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
                                          const ModD m, int pr, const DevConst *C, const double *from = nullptr,
-                                         const uint64_t *early = nullptr)
+                                         const uint64_t *early = nullptr, bool prio = false)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -557,6 +568,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     constexpr bool cross = PASS < P::NC;
     constexpr InvPlan<R> plan = inv_plan<R>(InvBound<LOGN, E, PASS>::in, last);
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
+    if (prio) __builtin_amdgcn_s_setprio(PASS < 2 ? 3 : PASS == P::NP - 1 ? 2 : PASS == P::NP - 2 ? 1 : 0);
     double v[G][1 << R];
     int base[G];
 #pragma unroll
@@ -654,6 +666,9 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int NP = Plan<LOGN, E>::NP;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
+    // (N = 4096, 1500 rows: 24.9 -> 23.6 us, 4096: 57 -> 55.  N = 8192, 1024 threads: 1000 rows 35.7 -> 37.0, 4000 the same;
+    // 3000 of 16384: 209 -> 217.)
+    const bool prio = LOGN <= 12 && row_alone<LD, ST>::value && 2 * nwg >= 3 * (int)gridDim.x;
     const int tid = threadIdx.x;
     const int S = ld.share(C);
     int p = blockIdx.x;
@@ -694,20 +709,20 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
         wave_sync();
         // passes NP-1 ... 0; the twiddle buffers alternate
         if constexpr (NP == 5) {
-            inv_pass<LOGN, E, 4>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twb, twa, m, pr, C);
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
+            inv_pass<LOGN, E, 4>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
         } else if constexpr (NP == 4) {
-            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twb, twa, m, pr, C);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twb, twa, m, pr, C);
+            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
         } else {
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C);
+            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
         }
         if (!more) break;
         wg = wg_next;
@@ -833,6 +848,7 @@ struct LdRowsU64 {
         return u64_to_f64(raw[0]);
     }
 };
+template <> struct row_alone<LdRowsU64, StU64> { static constexpr bool value = true; };
 
 // the same with the first n_first rows from `first` and the others, counted from there on, from `src`
 struct LdRowsFirst {
@@ -1095,6 +1111,8 @@ struct LdInvU64 {
         return u64_to_f64(raw[0]);
     }
 };
+struct StInvU64;
+template <> struct row_alone<LdInvU64, StInvU64> { static constexpr bool value = true; };
 // key-switch inner product fused into the load: workgroup -> (unit b, prime r, component c), the
 // component running fastest so that the two rows reading the same digits are neighbours;
 struct LdInvTensor;
@@ -1387,7 +1405,7 @@ template <> struct st_adds<StAppendRow> { static constexpr bool value = true; };
 // Transforms of a row that is in registers already or stays there: the pass sequence only.
 // ---------------------------------------------------------------------------
 // in: pass-0 ownership (element tid + it * T), or, with SCATTERED, already in LDS; out: chunk_elem order
-template <int LOGN, int E, bool SCATTERED>
+template <int LOGN, int E, bool SCATTERED, bool PRIO = false>
 __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *out, int tid,
                                         const double *__restrict__ tw, const ModD m)
 {
@@ -1398,14 +1416,14 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
     double twa[TWREGS], twb[TWREGS];
     const StRegs st{out};
     load_tw<LOGN, E, 0, true>(tw, tid, twa);
-    fwd_pass<LOGN, E, 0, !SCATTERED>(lds, in, st, tid, tw, twa, twb, m, 0);
-    fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, 0);
-    fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, 0);
-    fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, 0);
-    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, 0);
+    fwd_pass<LOGN, E, 0, !SCATTERED>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
 }
 // in: chunk_elem order, |x| < 8p; results leave through st as row `row`
-template <int LOGN, int E, class ST>
+template <int LOGN, int E, bool PRIO = false, class ST>
 __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
                                         const double *__restrict__ itw, const ModD m, int pr, const DevConst *C)
 {
@@ -1419,16 +1437,16 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
             pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(in[it], in[it + 1]);
         wave_sync();
     }
-    inv_pass<LOGN, E, NP - 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, in);
+    inv_pass<LOGN, E, NP - 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO);
     if constexpr (NP > 4) {
-        inv_pass<LOGN, E, 3>(lds, st, row, tid, itw, twb, twa, m, pr, C);
-        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twa, twb, m, pr, C);
-        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twb, twa, m, pr, C);
-        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twa, twb, m, pr, C);
+        inv_pass<LOGN, E, 3>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
     } else {
-        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twb, twa, m, pr, C);
-        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twa, twb, m, pr, C);
-        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
     }
 }
 
@@ -1710,7 +1728,8 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
                 ld.finish(x, r, m, C);
                 hi.finish(x + H, r, m, C);
             }
-            fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+            // (half rows: priorities take 96 products from 1238 to 1224 us, 5 from 115.3 to 113.4; whole rows: no difference)
+            fwd_row<LOGN, E, false, (K == 0)>(lds, x, x, tid, tw, m);
             if constexpr (!LD::kWhole) fetch_next();
             double y[E], z[E];
 #pragma unroll
@@ -1762,7 +1781,7 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
                 n_inv = t + 1;
             }
             for (int i = 0; i < n_inv; i++) {
-                inv_row<LOGN, E>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, pr, C);
+                inv_row<LOGN, E, (K == 0)>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, pr, C);
 #pragma unroll
                 for (int it = 0; it < E; it++) y[it] = z[it];
                 if (i + 1 < n_inv) lds_barrier();
@@ -1855,7 +1874,8 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     double x[E];
                     row(x, t);
                     lds_barrier();      // the previous transform's LDS reads
-                    fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                    // (priorities: prompt context of twelve heads 2303 -> 2284 us)
+                    fwd_row<LOGN, E, false, !HAT>(lds, x, x, tid, tw, m);
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
 #pragma unroll
@@ -1878,7 +1898,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     double x[E];
                     row(x, t);
                     lds_barrier();      // the previous transform's LDS reads
-                    fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                    fwd_row<LOGN, E, false, !HAT>(lds, x, x, tid, tw, m);
                     cg_double2v s0[E / 2];
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
@@ -1930,7 +1950,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
             // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
             // registers before any thread stores results over it)
             lds_barrier();
-            inv_row<LOGN, E>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
+            inv_row<LOGN, E, !HAT>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 d0[it] = d1[it];
@@ -1969,6 +1989,8 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
     // the plaintext row and the next row are brought in ahead where there are registers for it
     constexpr bool PF = prefetch_rows<LOGN, E>();
     static_assert(NP == 4 || NP == 5, "pass sequence below");
+    // 128 appends of 24 ciphertexts, N = 8192: 1981 -> 1928 us; 64 of 24, N = 4096: 524 -> 506; N = 16384: 1895 -> 1976
+    constexpr bool PRIO = LOGN <= 13;
     const int tid = threadIdx.x, k = C->k;
     uint64_t raw[E];
     int wg = blockIdx.x;
@@ -1994,33 +2016,33 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
 #pragma unroll
         for (int it = 0; it < E; it++) in[it] = u64_to_f64(raw[it]);
         const StTimesPlain<E, PF> times{lds, prow, pl};
-        fwd_pass<LOGN, E, 0, true>(lds, in, times, tid, tw, twa, twb, m, 0);
-        fwd_pass<LOGN, E, 1, false>(lds, in, times, tid, tw, twb, twa, m, 0);
-        fwd_pass<LOGN, E, 2, false>(lds, in, times, tid, tw, twa, twb, m, 0);
-        fwd_pass<LOGN, E, 3, false>(lds, in, times, tid, tw, twb, twa, m, 0);
-        if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, times, tid, tw, twa, twb, m, 0);
+        fwd_pass<LOGN, E, 0, true>(lds, in, times, tid, tw, twa, twb, m, 0, PRIO);
+        fwd_pass<LOGN, E, 1, false>(lds, in, times, tid, tw, twb, twa, m, 0, PRIO);
+        fwd_pass<LOGN, E, 2, false>(lds, in, times, tid, tw, twa, twb, m, 0, PRIO);
+        fwd_pass<LOGN, E, 3, false>(lds, in, times, tid, tw, twb, twa, m, 0, PRIO);
+        if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, times, tid, tw, twa, twb, m, 0, PRIO);
         load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
         wave_sync();
         if constexpr (NP > 4) {
-            inv_pass<LOGN, E, 4>(lds, str, wg, tid, itw, twa, twb, m, pr, C);
-            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twb, twa, m, pr, C);
+            inv_pass<LOGN, E, 4>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
         } else {
-            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twa, twa, m, pr, C);
+            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twa, twa, m, pr, C, nullptr, nullptr, PRIO);
         }
-        inv_pass<LOGN, E, 2>(lds, str, wg, tid, itw, twa, twb, m, pr, C);
+        inv_pass<LOGN, E, 2>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
         // What the storer adds to is asked for late: loads return in order, so ahead of the passes' factors it would hold
         // these up (the factors of the last two passes are scalar loads).  24 caches of N = 8192: 2008 us before the
         // last pass but one, 1982 before the last; N = 16384: 2059 and 1892; twelve caches of N = 4096: 526 and 537.
         constexpr bool adds = st_adds<decltype(str)>::value, ahead = LOGN <= 12;
         uint64_t old[8];
         if constexpr (adds && ahead) str.template fetch<T>(old, tid, 0);
-        inv_pass<LOGN, E, 1>(lds, str, wg, tid, itw, twb, twa, m, pr, C);
+        inv_pass<LOGN, E, 1>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
         const int next = wg + (int)gridDim.x;
         if constexpr (PF) {
             if (next < nwg) fetch(next);
         }
         if constexpr (adds && !ahead) str.template fetch<T>(old, tid, 0);
-        inv_pass<LOGN, E, 0>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, old);
+        inv_pass<LOGN, E, 0>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, old, PRIO);
         if (next >= nwg) break;
         wg = next;
         lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes

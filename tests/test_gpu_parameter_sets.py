@@ -187,3 +187,23 @@ def test_vector_matrix_products(name, n_diag, units):
     want = [attention.cpvm(env.orc, x, list(pt[i]), raw, d2) for i in range(2)]
     for u in range(units):
         assert np.array_equal(got[u], want[u % 2]), (name, u)
+
+
+# rows for one round and a half of workgroups (from there on waves have priorities), and a row less: 4, 2 and 1 workgroups to
+# each of 256 compute units, forward; inverse N = 8192 has one
+@pytest.mark.parametrize("name,rows", [("n4096_k6", (1535, 1536)), ("n8192_k4", (383, 384, 767, 768)), ("n16384_k3", (383, 384))])
+def test_transforms_of_many_rows(name, rows):
+    env = _env(name)
+    primes = len(env.qp)
+    base = np.stack([np.random.default_rng(70 + i).integers(0, m, env.n, dtype=np.uint64) for i, m in enumerate(env.qp)])
+    base[:, 0] = 0
+    base[:, 1::2] = np.array(env.qp, dtype=np.uint64)[:, None] - 1
+    from oracle import bfv
+    want = np.stack([bfv.ntt_forward(base[i], m) for i, m in enumerate(env.qp)])
+    for n in rows:
+        say(f"ntt {name}: {n} rows")
+        idx = [i % primes for i in range(n)]
+        x = env.dev(base[idx])
+        got = env.ctx.ntt_forward(x, idx)
+        assert np.array_equal(env.host(got), want[idx]), (name, n)
+        assert np.array_equal(env.host(env.ctx.ntt_inverse(got, idx)), base[idx]), (name, n)
