@@ -694,26 +694,45 @@ static bool rounds_pay(const cg_ctx *c, size_t rows, IdleLimits lim)
     return rounds > 3 || 256 * idle <= n * (size_t)(rounds == 1 ? lim.one : rounds == 2 ? lim.two : lim.three);
 }
 
+// Two units to a workgroup of ks_sum_row_kernel at N = 8192, where a round of pairs takes the time of 1.84 rounds of one and there are
+// few enough of them.  us, one unit / two, three digits, 7 rotations: 64 ciphertexts (one round / one) 82 / 119, 107 (two / one)
+// 148 / 131, 128: 158 / 142, 192 (three / two) 237 / 256, 193 (four / two) 283 / 251, 320 (five / three) 411 / 414, 768: 979 / 901;
+// 3 rotations, 128: 122 / 111, 384: 388 / 361; six digits, 7 rotations, 111: 486 / 429.  At N = 4096, where a compute unit holds
+// two workgroups of one unit, pairs gain nothing: two digits, 7 rotations, 256: 88 / 95, 512: 150 / 150, 1536: 462 / 463.
+static bool ks_sum_pairs(const cg_ctx *c, uint32_t batch)
+{
+    if (c->logn != 13) return false;
+    const size_t n = (size_t)c->n_cu, one = ((size_t)batch * c->L + n - 1) / n;
+    const size_t two = ((size_t)((batch + 1) / 2) * c->L + n - 1) / n;
+    return 184 * two < 100 * one;
+}
 // mod-up, summed inner products and inverse transforms in one launch
 static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T,
                              uint32_t n_rot, double *acc, uint32_t batch)
 {
-    const size_t nwg = (size_t)batch * c->L;
     const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L * n_rot);
-    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)nwg);
-#define CG_KSSUMROW(LG)                                                                                        \
+    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)batch * c->L);
+    const bool pairs = ks_sum_pairs(c, batch);
+#define CG_KSSUMROW(LG, U)                                                                                    \
     do {                                                                                                      \
+        const size_t nwg = (size_t)((batch + U - 1) / U) * c->L;                                              \
         const unsigned threads = (1u << LG) / 8;                                                              \
-        const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
-        if (c->dry) return CG_OK;                                                                             \
-        return launch_kernel(ks_sum_row_kernel<LG, 8>, dim3(grid), dim3(threads), s,                       \
+        const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8, U>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
+        if (c->dry) break;                                                                                    \
+        return launch_kernel(ks_sum_row_kernel<LG, 8, U>, dim3(grid), dim3(threads), s,                       \
                              LdModup<false, 1>{src, src_stride, 0, c->logn}, T, (int)n_rot, (int)batch,       \
                              StInvF64{acc, c->logn}, (const double *)c->tw, (const double *)c->itw,           \
                              (const DevConst *)c->dc, (int)nwg);                                              \
     } while (0)
     switch (c->logn) {
-    case 12: CG_KSSUMROW(12);
-    case 13: CG_KSSUMROW(13);
+    case 12:
+        if (pairs || c->dry) CG_KSSUMROW(12, 2);
+        if (!pairs) CG_KSSUMROW(12, 1);
+        return CG_OK;
+    case 13:
+        if (pairs || c->dry) CG_KSSUMROW(13, 2);
+        if (!pairs) CG_KSSUMROW(13, 1);
+        return CG_OK;
     default: return CG_EINVAL;
     }
 #undef CG_KSSUMROW
@@ -723,10 +742,14 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
 // 42: 61.4 / 56.6.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 43 (127 idle): 37.7 / 35.3, 86 (254):
 // 50.3 / 52.5, 107 (191): 55.7 / 54.6.  Three digits, 7 rotations: 33 (124 idle) 41.2 / 43.7, 42 (88): 44.8 / 43.0, 72 (224):
 // 62.2 / 67.1, 90 (152): 73.0 / 69.9; six digits: 20 (116) 61.8 / 70.0, 26 (74): 84.0 / 72.7.
+// Pairs of units (ks_sum_pairs) pay from a quarter more rows than compute units on, N = 8192, 7 rotations: three digits, 68
+// ciphertexts (272 rows) 118 / 122, 80 (320): 124 / 123, 96: 143 / 128, 102: 160 / 130; two, 89 (267): 91 / 94, 106 (318): 99 / 97;
+// six, 37 (259): 192 / 200, 45 (315): 232 / 204; four, 81 (405): 266 / 157; one, 160 (320): 75 / 69.
 static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
     if (c->dry) return c->dry_rows;
+    if (ks_sum_pairs(c, batch) && 4 * (size_t)batch * c->L >= 5 * (size_t)c->n_cu) return true;
     return rounds_pay(c, (size_t)batch * c->L, c->logn == 13 ? IdleLimits{89, 102, 102}
                                              : c->dnum <= 2 ? IdleLimits{128, 256, 256} : IdleLimits{84, 176, 256});
 }

@@ -1562,23 +1562,78 @@ __device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, 
     }
 }
 
+// The same for two units, their digits ROW doubles apart in LDS: a key is read once for both, a pair of elements ahead of its use
+template <int LOGN, int E>
+__device__ __forceinline__ void sum_digits(const double *lds, const HoistTab &T, int n_rot, int j, int r, int L, int tk,
+                                           const ModD m, double *s0, double *s1, double *s2, double *s3)
+{
+    constexpr int ROW = lds_doubles<LOGN>();
+    const int idx0 = chunk_elem<E>(tk, 0);
+    const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
+    const size_t comp = (size_t)L << (LOGN - 1);
+    auto rows = [&](int i) { return reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN)); };
+    const cg_double2v *k0 = rows(0);
+    uint32_t g = T.g[0];
+    cg_double2v a[2], c[2];
+    a[0] = at_lane(k0, idx0 / 2);
+    c[0] = at_lane(k0 + comp, idx0 / 2);
+    for (int i = 0; i < n_rot; i++) {
+        const int i_next = i + 1 < n_rot ? i + 1 : i;
+        const cg_double2v *kn = rows(i_next);
+        const uint32_t gn = T.g[i_next], eg = __umul24(e0, g);
+#pragma unroll
+        for (int q = 0; q < E / 2; q++) {
+            const cg_double2v *kq = q + 1 < E / 2 ? k0 + 64 * (q + 1) : kn;
+            a[(q + 1) & 1] = at_lane(kq, idx0 / 2);
+            c[(q + 1) & 1] = at_lane(kq + comp, idx0 / 2);
+            __builtin_amdgcn_sched_barrier(0);
+            const cg_double2v ka = a[q & 1], kc = c[q & 1];
+            const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+            const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
+            const double x0 = lds[at], x1 = lds[at ^ 1], y0 = lds[ROW + at], y1 = lds[ROW + (at ^ 1)];
+            s0[2 * q] += mulmod(x0, ka.x, m);
+            s0[2 * q + 1] += mulmod(x1, ka.y, m);
+            s1[2 * q] += mulmod(x0, kc.x, m);
+            s1[2 * q + 1] += mulmod(x1, kc.y, m);
+            s2[2 * q] += mulmod(y0, ka.x, m);
+            s2[2 * q + 1] += mulmod(y1, ka.y, m);
+            s3[2 * q] += mulmod(y0, kc.x, m);
+            s3[2 * q + 1] += mulmod(y1, kc.y, m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        k0 = kn;
+        g = gn;
+        if ((i & 7) == 7 || i + 1 == n_rot) {
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                s0[it] = red(s0[it], m);
+                s1[it] = red(s1[it], m);
+                s2[it] = red(s2[it], m);
+                s3[it] = red(s3[it], m);
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
-// Summed rotations of one (unit, prime) per workgroup: digits lifted and transformed one after the other; a
+// Summed rotations of one (unit, prime), or of two units, per workgroup: digits lifted and transformed one after the other; a
 // transformed digit lies in LDS, from where every rotation takes its permuted values, while the keys stream past;
 // the two sums in registers are transformed back.  With digits through memory (ks_sum_kernel) every rotation's
 // gather of every digit goes to L2, and half of them miss it; here the keys are what comes in, and an XCD works with
-// the keys of one or two primes.  Bound by vector issue (68 % busy).  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums and
-// inverse transforms 475 + 899 + 369 us in three launches, 1513 us here.
+// the keys of one or two primes.  Bound by the keys' way from L2 (128 KB a rotation and digit, 39 bytes a clock and compute unit) and
+// by vector issue (68 % busy); two units to a workgroup halve the first.  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums
+// and inverse transforms 475 + 899 + 369 us in three launches, 1513 us here with one unit, 1391 with two.
 // ---------------------------------------------------------------------------
-template <int LOGN, int E>
+template <int LOGN, int E, int U>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF64 st,
                   const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                   const DevConst *__restrict__ C, int nwg)
 {
-    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
-    constexpr int TH = (1 << LOGN) / E;
-    const int tid = threadIdx.x, L = C->L, dnum = C->dnum;
+    static_assert(U == 1 || U == 2, "units of a workgroup");
+    constexpr int TH = (1 << LOGN) / E, ROW = lds_doubles<LOGN>();
+    __shared__ __align__(16) double lds[U * ROW];
+    const int tid = threadIdx.x, L = C->L, dnum = C->dnum, sets = (batch + U - 1) / U;
     // logical order: prime, then unit; XCD x takes the x-th eighth of it, so that an XCD works with the keys
     // of one or two primes
     const int per_xcd = (nwg + 7) >> 3;
@@ -1587,41 +1642,54 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
     for (int p = blockIdx.x; p < total; p += (int)gridDim.x) {
         const int wg = logical(p);
         if (wg >= nwg) continue;
-        const int r = wg / batch, b = wg - r * batch;
+        const int r = wg / sets, b = (wg - r * sets) * U;
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
-        const uint64_t *src = ld.src + (size_t)b * ld.unit_stride;
         uint64_t raw[E][1];
-        auto fetch = [&](int j) {
+        // (an odd batch's last workgroup takes its one unit twice and stores it once)
+        auto fetch = [&](int u, int j) {
+            const uint64_t *src = ld.src + (size_t)(b + u < batch ? b + u : b) * ld.unit_stride + ((size_t)j << LOGN);
 #pragma unroll
-            for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + ((size_t)j << LOGN) + it * TH, tid);
+            for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + it * TH, tid);
         };
-        fetch(0);
-        double s0[E], s1[E];
+        fetch(0, 0);
+        double s0[E], s1[E], s2[U > 1 ? E : 1], s3[U > 1 ? E : 1];
 #pragma unroll
-        for (int it = 0; it < E; it++) s0[it] = s1[it] = 0.0;
+        for (int it = 0; it < E; it++) {
+            s0[it] = s1[it] = 0.0;
+            if (U > 1) s2[it % (U > 1 ? E : 1)] = s3[it % (U > 1 ? E : 1)] = 0.0;
+        }
         for (int j = 0; j < dnum; j++) {
-            {
+#pragma unroll
+            for (int u = 0; u < U; u++) {
                 double x[E];
-                const int row = (b * dnum + j) * L + r;
+                const int row = ((b + u) * dnum + j) * L + r;
 #pragma unroll
                 for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, tid + it * TH, m, C);
-                fetch(j + 1 < dnum ? j + 1 : j);
-                lds_barrier();      // the previous digit's (or unit's) LDS reads
-                fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m);
+                if (U == 1) fetch(0, j + 1 < dnum ? j + 1 : j);     // (with four sums there are no registers for it here)
+                if (u == 0) lds_barrier();      // the previous digit's (or unit's) LDS reads
+                fwd_row<LOGN, E, false>(lds + u * ROW, x, x, tid, tw, m);
+                if (U > 1) fetch(u + 1 < U ? u + 1 : 0, u + 1 < U || j + 1 == dnum ? j : j + 1);
 #pragma unroll
                 for (int it = 0; it < E; it += 2)
-                    pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
-                lds_barrier();
+                    pair_at(lds + u * ROW, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
             }
+            lds_barrier();
             int tk = tid;
             asm volatile("" : "+v"(tk));
-            sum_digit<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1);
+            if constexpr (U == 1) sum_digit<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1);
+            else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1, s2, s3);
         }
         lds_barrier();
         inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
         lds_barrier();
         inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
+        if (U > 1 && b + 1 < batch) {
+            lds_barrier();
+            inv_row<LOGN, E>(lds, s2, st, (b * 2 + 2) * L + r, tid, itw, m, r, C);
+            lds_barrier();
+            inv_row<LOGN, E>(lds, s3, st, (b * 2 + 3) * L + r, tid, itw, m, r, C);
+        }
     }
 }
 

@@ -253,3 +253,21 @@ def test_products_of_few_rows(name, batches):
         got = env.host(env.ctx.mul(_tiled(env, a, batch), _tiled(env, b, batch), batch))
         for u in range(batch):
             assert np.array_equal(got[u], want[u % 3, u % 2]), (name, batch, u)
+
+
+# pairs of units at N = 8192, from 5/4 x 256 rows of (unit, prime) on where whole rounds of pairs are few enough; an odd batch's
+# last unit is alone; keys are read ahead over the end of a rotation, sums reduced after eight
+@pytest.mark.parametrize("name,batches", [("C2", (79, 80, 107, 193, 385)), ("mixed", (81, 128)), ("k1", (160, 255, 385))])
+def test_summed_rotations_of_pairs_of_units(name, batches):
+    env = _env(name)
+    n = env.n
+    gs = [2 * n - 1, 3, 2 * n - 3, 9, 27, 2 * n - 9, 81, 5, 25]
+    raws, keys = zip(*[env.key(100 + i) for i in range(len(gs))])
+    x = _extremes(env, env.cts(96, 3))
+    for n_rot in (1, 8, 9):
+        want = [env.orc.rotate_sum_hoisted(v, gs[:n_rot], dict(zip(gs, raws))) for v in x]
+        for batch in batches:
+            say(f"{n_rot} rotations summed {name} batch {batch}")
+            got = env.host(env.ctx.rotate_sum_hoisted(_tiled(env, x, batch), gs[:n_rot], keys[:n_rot], batch))
+            for u in range(batch):
+                assert np.array_equal(got[u], want[u % 3]), (name, n_rot, batch, u)
