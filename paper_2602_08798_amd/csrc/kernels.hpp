@@ -1405,9 +1405,11 @@ template <> struct st_adds<StAppendRow> { static constexpr bool value = true; };
 // Transforms of a row that is in registers already or stays there: the pass sequence only.
 // ---------------------------------------------------------------------------
 // in: pass-0 ownership (element tid + it * T), or, with SCATTERED, already in LDS; out: chunk_elem order
-template <int LOGN, int E, bool SCATTERED, bool PRIO = false>
+// ahead: run before the last pass, for loads that nothing before it waits for
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int LOGN, int E, bool SCATTERED, bool PRIO = false, class F = Nothing>
 __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *out, int tid,
-                                        const double *__restrict__ tw, const ModD m)
+                                        const double *__restrict__ tw, const ModD m, F ahead = F())
 {
     constexpr int NP = Plan<LOGN, E>::NP;
     // addresses are formed here and now: hoisted out of the caller's loops they would take the registers
@@ -1419,7 +1421,9 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
     fwd_pass<LOGN, E, 0, !SCATTERED>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
     fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
     fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    if (NP == 4) ahead();
     fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    if (NP > 4) ahead();
     if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
 }
 // in: chunk_elem order, |x| < 8p; results leave through st as row `row`
@@ -2517,6 +2521,40 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
     }
 }
 
+// A digit's transformed values times its two key rows, added to two sums.  Keys are asked for a pair of elements ahead, the first
+// one before the transform's last pass: all of them asked for after the transform, every wave waited there for the
+// 128 KB that a compute unit takes in at 39 bytes a clock.  768 products and relinearisations at N = 8192 1925 -> 1877 us,
+// at N = 4096 572 -> 562.  (The next digit's words asked for as late as that: 1901.  In ks_row_kernel
+// and for rotations it gains nothing: the step's launches of 48 units are 0.6 % slower.)
+template <int LOGN, int E>
+struct DigitKeys {
+    const cg_double2v *k0, *k1;
+    int lane;
+    cg_double2v a[2], c[2];
+    __device__ __forceinline__ DigitKeys(const double *key, size_t comp, int tid)
+        : k0(reinterpret_cast<const cg_double2v *>(key)), k1(reinterpret_cast<const cg_double2v *>(key + comp)),
+          lane(chunk_elem<E>(tid, 0) / 2) {}
+    __device__ __forceinline__ void ask(int q)
+    {
+        a[q & 1] = at32(k0, lane + 64 * q);
+        c[q & 1] = at32(k1, lane + 64 * q);
+    }
+    __device__ __forceinline__ void add(const double *x, const ModD m, double *s0, double *s1)
+    {
+#pragma unroll
+        for (int q = 0; q < E / 2; q++) {
+            if (q + 1 < E / 2) ask(q + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const cg_double2v ka = a[q & 1], kc = c[q & 1];
+            s0[2 * q] += mulmod(x[2 * q], ka.x, m);
+            s0[2 * q + 1] += mulmod(x[2 * q + 1], ka.y, m);
+            s1[2 * q] += mulmod(x[2 * q], kc.x, m);
+            s1[2 * q + 1] += mulmod(x[2 * q + 1], kc.y, m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Key switch of one unit per workgroup, from the ring element to the finished ciphertext: as ks_row_kernel and
 // ks_sum_row_kernel, special prime first, then every ciphertext prime with the division by P and the additions in
@@ -2560,6 +2598,18 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
                 for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, at(it), m, C);
                 fetch(j + 1 < dnum || step + 1 < L ? b : b_next, j + 1 < dnum ? j + 1 : 0);
                 lds_barrier();      // the previous reads of other waves' elements
+                if constexpr (MODE == KS_PLAIN) {
+                    int tk = tid;
+                    asm volatile("" : "+v"(tk));
+                    DigitKeys<LOGN, E> keys(T.key[0] + ((size_t)(2 * j * L + r) << LOGN), (size_t)L << LOGN, tk);
+                    fwd_row<LOGN, E, false>(lds, x, x, tid, tw, m, [&] { keys.ask(0); });
+                    if (dnum > 3) {     // as in ks_row_kernel
+#pragma unroll
+                        for (int it = 0; it < E; it++) x[it] = red(x[it], m);
+                    }
+                    keys.add(x, m, s[0], s[1]);
+                    continue;
+                }
                 if constexpr (GALOIS) {
 #pragma unroll
                     for (int it = 0; it < E; it++) lds[pad(ld.place(at(it), N))] = x[it];
@@ -2568,7 +2618,7 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
                 fwd_row<LOGN, E, GALOIS>(lds, x, x, tid, tw, m);
                 int tk = tid;
                 asm volatile("" : "+v"(tk));
-                if constexpr (MODE != KS_SUM) {
+                if constexpr (GALOIS) {
                     const double *k0 = T.key[0] + ((size_t)(2 * j * L + r) << LOGN), *k1 = k0 + ((size_t)L << LOGN);
                     if (dnum > 3) {     // as in ks_row_kernel
 #pragma unroll
