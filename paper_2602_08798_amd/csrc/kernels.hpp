@@ -1911,6 +1911,9 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
     constexpr bool FAR = LOGN > 12 && !HAT;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     __shared__ double park[HAT ? 1 : 1 << LOGN];
+    // prompt context of twelve heads 2303 -> 2284 us; at N = 4096 these launches run beside other branches, a step of sixteen heads
+    // 175 -> 190
+    constexpr bool PRIO = LOGN == 13 && !HAT;
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
         const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
@@ -1946,8 +1949,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     double x[E];
                     row(x, t);
                     lds_barrier();      // the previous transform's LDS reads
-                    // (priorities: prompt context of twelve heads 2303 -> 2284 us)
-                    fwd_row<LOGN, E, false, !HAT>(lds, x, x, tid, tw, m);
+                    fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
 #pragma unroll
@@ -1970,7 +1972,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     double x[E];
                     row(x, t);
                     lds_barrier();      // the previous transform's LDS reads
-                    fwd_row<LOGN, E, false, !HAT>(lds, x, x, tid, tw, m);
+                    fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
                     cg_double2v s0[E / 2];
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
@@ -2022,7 +2024,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
             // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
             // registers before any thread stores results over it)
             lds_barrier();
-            inv_row<LOGN, E, !HAT>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
+            inv_row<LOGN, E, PRIO>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 d0[it] = d1[it];
