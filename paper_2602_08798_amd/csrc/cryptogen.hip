@@ -742,14 +742,13 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
 // 42: 61.4 / 56.6.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 43 (127 idle): 37.7 / 35.3, 86 (254):
 // 50.3 / 52.5, 107 (191): 55.7 / 54.6.  Three digits, 7 rotations: 33 (124 idle) 41.2 / 43.7, 42 (88): 44.8 / 43.0, 72 (224):
 // 62.2 / 67.1, 90 (152): 73.0 / 69.9; six digits: 20 (116) 61.8 / 70.0, 26 (74): 84.0 / 72.7.
-// Pairs of units (ks_sum_pairs) pay from a quarter more rows than compute units on, N = 8192, 7 rotations: three digits, 68
-// ciphertexts (272 rows) 118 / 122, 80 (320): 124 / 123, 96: 143 / 128, 102: 160 / 130; two, 89 (267): 91 / 94, 106 (318): 99 / 97;
-// six, 37 (259): 192 / 200, 45 (315): 232 / 204; four, 81 (405): 266 / 157; one, 160 (320): 75 / 69.
+// Pairs of units (ks_sum_pairs), four digits and more: from a quarter more rows than compute units on.  N = 8192, 7 rotations: four
+// digits, 63 ciphertexts (315 rows) 191 / 151, 81 (405): 266 / 157; six, 37 (259): 192 / 200, 45 (315): 232 / 204, 54: 269 / 209.
 static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
     if (c->dry) return c->dry_rows;
-    if (ks_sum_pairs(c, batch) && 4 * (size_t)batch * c->L >= 5 * (size_t)c->n_cu) return true;
+    if (c->dnum > 3 && ks_sum_pairs(c, batch) && 4 * (size_t)batch * c->L >= 5 * (size_t)c->n_cu) return true;
     return rounds_pay(c, (size_t)batch * c->L, c->logn == 13 ? IdleLimits{89, 102, 102}
                                              : c->dnum <= 2 ? IdleLimits{128, 256, 256} : IdleLimits{84, 176, 256});
 }
@@ -1006,14 +1005,17 @@ static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, dou
 // 12 x 8 62 / 55, 12 x 64 438 / 295: the model has every one of these on the right side.
 //
 // With one operand transformed already (hat) a unit has half the work in one launch, and two launches and an operand's way through
-// memory fewer.  At N = 4096 that wins throughout (decode step with a copy of the cache, heads x ciphertexts: 2 x 2 161.9 / 158.7 us,
-// 12 x 4 176.9 / 173.4, 16 x 8 308 / 288).  At N = 8192 the sums spill beside the transform: 1 x 1 187 / 201, 4 x 2 212 / 222, 12 x 4
-// 423 / 438, 16 x 8 925 / 903.
+// memory fewer.  At N = 4096 that wins up to 5 n / 3 rows of (unit, prime), beyond which the other branches' launches fill the chip too
+// and pieces as large as these no longer fit in beside them (decode step with a copy of the cache, two primes, heads x
+// ciphertexts: 12 x 4 177 / 171, 8 x 8 197 / 182, 16 x 5 213 / 209, 12 x 7 214 / 211, 11 x 8 235 / 245, 15 x 6 242 / 250,
+// 16 x 6 248 / 261, 14 x 7 250 / 277).  At N = 8192 the sums spill beside the transform: 1 x 1 187 / 201, 4 x 2 212 / 222,
+// 12 x 4 423 / 438, 16 x 8 925 / 903.
 static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint32_t &parts, bool hat = false)
 {
     if (c->logn > (hat ? 12 : 13) || c->k > 3) return false;
     if (c->dry) return c->dry_rows;
     const double n = c->n_cu, base = (double)groups * c->KL;
+    if (hat && 3.0 * base * group > 5.0 * n) return false;
     double best = 1e30;
     uint32_t best_parts = 1;
     for (uint32_t q = 1; q <= group && q <= 64; q++) {

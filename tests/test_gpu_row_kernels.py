@@ -216,9 +216,10 @@ def test_scores_of_single_ciphertext_caches_with_a_transformed_copy():
         assert np.array_equal(got[h, 0], want), h
 
 
-@pytest.mark.parametrize("name,shapes", [("C1", ((1, 1), (3, 7), (52, 2))), ("k3", ((2, 5),))])
+@pytest.mark.parametrize("name,shapes", [("C1", ((1, 1), (3, 7), (85, 1), (43, 2))), ("k3", ((2, 5),))])
 def test_context_sums_with_a_transformed_copy_in_parts(name, shapes):
-    """N = 4096: products with a transformed cache summed in one launch (one part per group, several, several rounds)"""
+    """N = 4096: products with a transformed cache summed in one launch (one part per group, several, several rounds), and just
+    more of them than that is taken for"""
     from oracle import attention
     env = _env(name)
     d2 = env.n // 4
