@@ -1029,6 +1029,11 @@ static bool mul_sum_parts(const cg_ctx *c, uint32_t groups, uint32_t group, uint
 
 // Parts of a group at N = 16384: as above, in transforms of a half row, four per unit (three with y transformed) and three
 // besides; the fewest parts that are as fast, since scale_kernel reads every part.
+// us of a context call with y transformed, six primes, heads x ciphertexts (all launches; keys the same in every call): a tensor
+// inverse that walks over the group / mul_sum_row_kernel with three sums in registers, 16 of these spilled / with one in memory /
+// mul_row_kernel with a part for every unit: 1 x 4 274 / 237 / 235 / 229, 3 x 2 296 / 278 / 275 / 270, 16 x 1 629 / 611 / 608 / 590;
+// 4 x 4 348 / 327 / 327 / 339, 8 x 3 483 / 418 / 416 / 450, 16 x 3 784 / 722 / 709 / 750, 16 x 4 862 / 774 / 764 / 837.  The first
+// three are those whose parts hold one unit each: nothing to sum, so do_mul has mul_row_kernel take these.
 static uint32_t mul_sum_parts_half(const cg_ctx *c, uint32_t groups, uint32_t group, bool hat)
 {
     const double n = c->n_cu, base = (double)groups * 2 * c->KL, per = hat ? 3.0 : 4.0;
@@ -1079,8 +1084,10 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         if (sum_group) {
             CG_REQUIRE(a_group == 1);
             parts = mul_sum_parts_half(c, n_out, sum_group, b_ext != nullptr);
-            CG_TRY(b_ext ? launch_mul_sum_row<true>(c, s, A, tens, n_out, sum_group, parts)
-                         : launch_mul_sum_row<false>(c, s, A, tens, n_out, sum_group, parts));
+            // (while dry: the occupancy of the kernel that sums)
+            if (b_ext && parts == sum_group && !c->dry) CG_TRY(launch_mul_row<true>(c, s, A, tens, batch, n_a, B));
+            else CG_TRY(b_ext ? launch_mul_sum_row<true>(c, s, A, tens, n_out, sum_group, parts)
+                              : launch_mul_sum_row<false>(c, s, A, tens, n_out, sum_group, parts));
         } else {
             CG_TRY(b_ext || shared ? launch_mul_row<true>(c, s, A, tens, batch, shared ? B : n_a, shared ? n_a : B)
                                    : launch_mul_row<false>(c, s, A, tens, batch, B, B));

@@ -1901,6 +1901,8 @@ __device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, 
 // window of a few elements instead of in two halves at once.  Kernel, 12 groups of 128, N = 8192, three primes: 2100 us with everything
 // in registers, 1890 with the halves one after the other, 1760 with the first sum in memory too, 1640 with the window (2 to 5
 // elements within 3 %).  At N = 4096 registers suffice, and the sum in memory costs 3 % of A V, 12 heads (419 us; 406 in registers).
+// With y transformed at N = 16384 three sums beside the row, its factors and y's words spilled 16 registers; with the first one in
+// memory none (mul_sum_parts_half has both sides).
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
@@ -1908,7 +1910,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
 {
     constexpr int T = (1 << LOGN) / E, W = K == 1 ? 8 : K == 2 ? 4 : 3;
     const int KL = K ? 2 * K + 1 : A.k;
-    constexpr bool FAR = LOGN > 12 && !HAT;
+    constexpr bool FAR = LOGN > 12;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     __shared__ double park[HAT ? 1 : 1 << LOGN];
     // prompt context of twelve heads 2303 -> 2284 us; at N = 4096 these launches run beside other branches, a step of sixteen heads
@@ -1931,6 +1933,18 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
         auto poly = [&](int u, int t) {
             return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
         };
+        // the first component's sum before unit u, and put back with a pair of that unit's products (below 1.2 p)
+        auto far_put = [&](const cg_double2v s, double a, double b, int q, int tk) {
+            put32(far + q * T, tk, cg_double2v{red(s.x + a, m), red(s.y + b, m)});
+        };
+        auto far_get = [&](cg_double2v *s0, int u, int tk) {
+#pragma unroll
+            for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
+            if (u != u_first) {
+#pragma unroll
+                for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
+            }
+        };
         MulRowLoad<LOGN, E, 0> whole;
         if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, 0, tid);
         for (int u = u_first; u < u_end; u++) {
@@ -1952,13 +1966,17 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
+                    cg_double2v s0[E / 2];
+                    if (FAR && t == 0) far_get(s0, u, tk);
 #pragma unroll
                     for (int it = 0; it < E; it++) {
                         const double b0 = red(at32(y0, chunk_elem<E>(tk, it)), m), b1 = red(at32(y1, chunk_elem<E>(tk, it)), m);
                         x[it] = red(x[it], m);
                         if (t == 0) {
-                            d0[it] += mulmod(x[it], b0, m);
                             d1[it] += mulmod(x[it], b1, m);
+                            x[it] = mulmod(x[it], b0, m);
+                            if (!FAR) d0[it] += x[it];
+                            else if (it & 1) far_put(s0[it / 2], x[it - 1], x[it], it / 2, tk);
                         } else {
                             d1[it] += mulmod(x[it], b0, m);
                             d2[it] += mulmod(x[it], b1, m);
@@ -1976,14 +1994,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     cg_double2v s0[E / 2];
                     int tk = tid;
                     asm volatile("" : "+v"(tk));
-                    if (FAR && t == 1) {
-#pragma unroll
-                        for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
-                        if (u != u_first) {
-#pragma unroll
-                            for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
-                        }
-                    }
+                    if (FAR && t == 1) far_get(s0, u, tk);
 #pragma unroll
                     for (int it = 0; it < E; it++) {
                         x[it] = red(x[it], m);
@@ -1996,14 +2007,11 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                         }
                         if (t == 1 || t == 2) keep[it] = x[it];
                     }
-                    // (a unit adds less than 1.2 p)
                     if (FAR && t == 1) {
 #pragma unroll
-                        for (int q = 0; q < E / 2; q++) {
-                            const double a = mulmod(park[tid + 2 * q * T], x[2 * q], m),
-                                         b = mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m);
-                            put32(far + q * T, tk, cg_double2v{red(s0[q].x + a, m), red(s0[q].y + b, m)});
-                        }
+                        for (int q = 0; q < E / 2; q++)
+                            far_put(s0[q], mulmod(park[tid + 2 * q * T], x[2 * q], m),
+                                    mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m), q, tk);
                     }
                 }
             }

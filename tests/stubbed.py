@@ -21,7 +21,8 @@ class Stubbed:
 
     def __init__(self, stub_path, lib_path):
         self.stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
-        self.stub.stub_log_size.restype = C.c_size_t
+        self.stub.stub_log_size.restype = self.stub.stub_kernel_count.restype = C.c_size_t
+        self.stub.stub_log_kernel.restype = self.stub.stub_kernel_name.restype = C.c_char_p
         self.lib = C.CDLL(lib_path)
 
     def create(self, prm):
@@ -41,6 +42,32 @@ class Stubbed:
             self.stub.stub_log_get(C.c_size_t(i), C.byref(kind), C.byref(s), C.byref(e))
             out.append((kind.value, s.value or 0, e.value or 0))
         return out
+
+
+    def kernels(self, call):
+        """the kernels `call` launches: [[name with its template arguments, blocks, threads], ...]"""
+        out = []
+        for i in range(len(self.log(call))):
+            blocks, threads = u32(), u32()
+            name = self.stub.stub_log_kernel(C.c_size_t(i), C.byref(blocks), C.byref(threads)).decode()
+            if name:
+                out.append([short(name), blocks.value, threads.value])
+        return out
+
+    def compiled(self):
+        """every kernel of the library"""
+        return [short(self.stub.stub_kernel_name(C.c_size_t(i)).decode()) for i in range(self.stub.stub_kernel_count())]
+
+
+def short(name):
+    """void cg::scale_kernel<2, false>(...) -> scale_kernel<2, false>"""
+    depth = 0
+    for i, ch in enumerate(name):
+        depth += {"<": 1, ">": -1}.get(ch, 0)
+        if ch == "(" and not depth:
+            name = name[:i]
+            break
+    return name.removeprefix("void ").replace("cg::", "")
 
 
 def run(script, tmp):

@@ -70,3 +70,31 @@ def test_sums_of_products_in_parts(name, shapes):
                 us = range(g * group, (g + 1) * group)
                 want[key] = env.orc.mul_sum([a[u % 3] for u in us], [b[u % 2] for u in us])
             assert np.array_equal(got[g], want[key]), (name, groups, group, g)
+
+
+# parts of one unit each (1 x 1, 3 x 2 and, one prime, 1 x 5), of several (44 x 2, 14 x 3, 10 x 2: a whole group), of several and
+# uneven (3 x 7, 1 x 70, 1 x 24)
+@pytest.mark.parametrize("name,shapes", [("k1", ((1, 5), (1, 70), (44, 2))), ("k4", ((1, 1), (14, 3))),
+                                         ("C5", ((3, 2), (10, 2), (1, 24))), ("mixed", ((3, 7),))])
+def test_context_sums_with_a_transformed_copy(name, shapes):
+    from oracle import attention
+    env = _env(name)
+    d2 = env.n // 4
+    raw_rlk, rlk = env.key(80)
+    gs = env.ctx.round_galois(1, d2, 1)
+    raws, keys = zip(*[env.key(81 + i) for i in range(len(gs))])
+    a, vc = _extremes(env, env.cts(90, 3)), _extremes(env, env.cts(91, 2))
+    for heads, n_cts in shapes:
+        say(f"decode_context_hoisted {name}: {heads} heads of {n_cts} ciphertexts, transformed copy")
+        n = heads * n_cts
+        ext = env.ctx.cache_extend(_tiled(env, vc, n), heads, n_cts, n_cts, env.ctx.empty_ext(n))
+        got = env.host(env.ctx.decode_context_hoisted(_tiled(env, a, n), None, heads, n_cts, d2, 1, rlk, list(keys), vext=ext,
+                                                      sum_before_scaling=True))
+        want = {}
+        for h in range(heads):
+            us = range(h * n_cts, (h + 1) * n_cts)
+            first = us[0] % 6
+            if first not in want:
+                want[first] = attention.decode_context_hoisted(env.orc, [a[u % 3] for u in us], [vc[u % 2] for u in us], raw_rlk,
+                                                               dict(zip(gs, raws)), d2, 1, sum_first=True)
+            assert np.array_equal(got[h], want[first]), (name, heads, n_cts, h)
