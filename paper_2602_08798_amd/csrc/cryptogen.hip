@@ -198,13 +198,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_LIFT, KID_FWD_HALF, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_LIFT, KID_FWD_HALF, KID_COPY, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit", "lift", "ntt_fwd<mul,half-rows>"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit", "lift", "ntt_fwd<mul,half-rows>", "copy"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -1403,7 +1403,7 @@ static int do_add(cg_ctx *c, hipStream_t s, const uint64_t *a, const uint64_t *b
 static int do_copy(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint64_t *dst, size_t dst_stride, uint32_t cts)
 {
     const unsigned per = (unsigned)(2 * c->k * (c->N / (2 * PW_THREADS)));
-    CG_LAUNCH_PW(KID_ADD, (double)limb_bytes(c) * 4.0 * c->k * cts, (double)2 * c->k * cts, copy_kernel, cts * per, src, src_stride, dst,
+    CG_LAUNCH_PW(KID_COPY, (double)limb_bytes(c) * 4.0 * c->k * cts, (double)cts, copy_kernel, cts * per, src, src_stride, dst,
                  dst_stride, (int)per);
     return CG_OK;
 }
