@@ -556,7 +556,7 @@ static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
     // N = 8192: a launch with no more rows than compute units finishes a row sooner on 1024 threads
-    const int e = (c->logn == 13 && nwg <= (size_t)c->n_cu) ? c->elems : c->elems_fwd;
+    const int e = (c->logn == 13 && !fwd_many<LD>::value && nwg <= (size_t)c->n_cu) ? c->elems : c->elems_fwd;
     const int threads = c->N / e;
 #define CG_FWD(LG, EL)                                                                          \
     do {                                                                                        \
@@ -570,7 +570,9 @@ static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
         if constexpr (ld_no_16384<LD>::value) return CG_EINVAL;
         else CG_FWD(14, 16);
     case 1208: CG_FWD(12, 8);
-    case 1308: CG_FWD(13, 8);
+    case 1308:
+        if constexpr (fwd_many<LD>::value) return CG_EINVAL;
+        else CG_FWD(13, 8);
     case 1316: CG_FWD(13, 16);
     default: return CG_EINVAL;
     }
@@ -598,7 +600,9 @@ static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
         else CG_INV(14, 16);
     case 1208: CG_INV(12, 8);
     case 1308: CG_INV(13, 8);
-    case 1316: CG_INV(13, 16);
+    case 1316:
+        if constexpr (inv_wide<LD>::value) CG_INV(13, 16);
+        else return CG_EINVAL;
     default: return CG_EINVAL;
     }
 #undef CG_INV
@@ -726,8 +730,7 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
     } while (0)
     switch (c->logn) {
     case 12:
-        if (pairs || c->dry) CG_KSSUMROW(12, 2);
-        if (!pairs) CG_KSSUMROW(12, 1);
+        CG_KSSUMROW(12, 1);
         return CG_OK;
     case 13:
         if (pairs || c->dry) CG_KSSUMROW(13, 2);

@@ -301,6 +301,8 @@ template <class LD> struct ld_lifts { static constexpr bool value = false; };
 template <class LD> struct ld_half { static constexpr bool value = false; };
 // Loaders of products' operands: those of N = 16384 are half rows.
 template <class LD> struct ld_no_16384 { static constexpr bool value = false; };
+// Loaders whose launches always have more rows than compute units.
+template <class LD> struct fwd_many { static constexpr bool value = false; };
 // Transforms on their own (callers' rows in, rows out), which may use priorities (fwd_pass).
 template <class LD, class ST> struct row_alone { static constexpr bool value = false; };
 
@@ -969,6 +971,8 @@ struct LdMulAux {
 template <int K> struct ld_lifts<LdMulAux<K>> { static constexpr bool value = true; };
 template <> struct ld_no_16384<LdMulQ> { static constexpr bool value = true; };
 template <int K> struct ld_no_16384<LdMulAux<K>> { static constexpr bool value = true; };
+// (taken with more than two rows of k + l per compute unit, l > k of which are more than one per unit)
+template <int K> struct fwd_many<LdMulAux<K>> { static constexpr bool value = true; };
 
 // Both kinds of rows in one launch, for launches that leave compute units free: workgroup -> (pp, prime r of the k + l).
 // All K words of a row modulo a ciphertext prime are that row's own: the same line, and the same code.
