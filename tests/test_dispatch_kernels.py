@@ -16,9 +16,36 @@ class _KernelStat(C.Structure):
 
 
 # name -> log2 N, primes, special primes, primes of a digit
-SETS = {"n8192_k3": (13, 3, 1, 1), "n16384_k6": (14, 6, 2, 2)}
+SETS = {"n8192_k3": (13, 3, 1, 1), "n8192_k4": (13, 4, 1, 1), "n4096_k2": (12, 2, 1, 1), "n16384_k6": (14, 6, 2, 2)}
+TENSOR, SUMS = "ntt_inv_kernel<13, {}, LdInvTensor, StInvF64>", "mul_sum_row_kernel<13, 8, 3, false>"
 # set, call, its sizes -> the kernel among its launches that tells the routes apart
 WANT = {
+    # 7 summed rotations: pairs of units where 1.84 rounds of pairs are less than the rounds of one unit ...
+    **{("n8192_k3", "sum", b): "ks_sum_row_kernel<13, 8, 1>" for b in (64, 192, 320)},
+    **{("n8192_k3", "sum", b): "ks_sum_row_kernel<13, 8, 2>" for b in (107, 128, 193, 256, 321)},
+    # ... with four digits from 5 rows on 4 compute units, launches of single transforms below
+    ("n8192_k4", "sum", 51): "ks_sum_row_kernel<13, 8, 1>", ("n8192_k4", "sum", 52): "ks_sum_kernel<4, ",
+    ("n8192_k4", "sum", 63): "ks_sum_kernel<4, ", ("n8192_k4", "sum", 64): "ks_sum_row_kernel<13, 8, 2>",
+    **{("n4096_k2", "sum", b): "ks_sum_row_kernel<12, 8, 1>" for b in (64, 200, 400)},
+    # the tensor product of no more rows than compute units on 1024 threads
+    ("n8192_k3", "mul", 12): TENSOR.format(8), ("n8192_k3", "mul", 13): TENSOR.format(16),
+    # operands: no more rows than compute units on 1024 threads; both kinds of rows in one launch up to two per unit
+    ("n8192_k3", "extend", 18): "ntt_fwd_kernel<13, 8, LdMulExt<3>, StF64>",
+    ("n8192_k3", "extend", 19): "ntt_fwd_kernel<13, 16, LdMulExt<3>, StF64>",
+    ("n8192_k3", "extend", 36): "ntt_fwd_kernel<13, 16, LdMulExt<3>, StF64>",
+    ("n8192_k3", "extend", 37): "ntt_fwd_kernel<13, 16, LdMulAux<3>, StF64>",
+    ("n16384_k6", "extend", 4): "ntt_fwd_kernel<13, 8, LdHalf, StF64>",
+    ("n16384_k6", "extend", 5): "ntt_fwd_kernel<13, 16, LdHalf, StF64>",
+    # products of a step, beside its other branches, with more units idle than alone
+    ("n8192_k3", "scores", 12, 4): "mul_row_kernel<13, 8, 3, true>", ("n8192_k3", "scores", 11, 4): TENSOR.format(16),
+    ("n8192_k3", "mul", 48): TENSOR.format(16),
+    # sums of products by the model of both routes
+    **{("n8192_k3", "mul_sum", g, u): SUMS for g, u in ((3, 8), (16, 8), (4, 16), (8, 100))},
+    **{("n8192_k3", "mul_sum", g, u): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for g, u in ((12, 4), (12, 8), (6, 8))},
+    # with a transformed cache at N = 4096 up to 5/3 rows of (unit, prime) per compute unit, at N = 8192 never
+    **{("n4096_k2", "context_ext", h, c): "mul_sum_row_kernel<12, 8, 2, true>" for h, c in ((17, 5), (85, 1), (12, 7))},
+    **{("n4096_k2", "context_ext", h, c): "ntt_inv_kernel<12, 8, LdInvTensorSum, StInvF64>" for h, c in ((43, 2), (86, 1), (11, 8))},
+    ("n8192_k3", "context_ext", 1, 1): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
     **{("n16384_k6", "context_ext", h, c): "mul_sum_row_kernel<13, 8, 0, true>" for h, c in ((4, 4), (8, 3), (12, 2), (16, 3))},
@@ -41,9 +68,14 @@ def _launches(lib):
     for name, (log2n, k, nsp, alpha) in SETS.items():
         p = ntt_primes(1 << 50, 2 << log2n, k + nsp)
         ctx = lib.create(ParamSet(name, log2n, q=tuple(p[:k]), p=tuple(p[k:]), alpha=alpha))
-        calls = {"context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
-            ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d)}
-        for (s, op, *sizes), _ in WANT.items():
+        calls = {"mul": lambda b: lib.lib.cg_mul(ctx, None, d, d, out, u32(b), u32(1), d),
+                 "mul_sum": lambda g, u: lib.lib.cg_mul_sum(ctx, None, d, d, out, u32(g), u32(u), d),
+                 "sum": lambda b: lib.lib.cg_rotate_sum_hoisted(ctx, None, d, u32(7), gs, keys, out, u32(b), d),
+                 "extend": lambda n: lib.lib.cg_cache_extend(ctx, None, d, u32(n), u32(1), u32(1), out),
+                 "scores": lambda h, c: lib.lib.cg_decode_scores(ctx, None, d, d, u32(h), u32(c), u32(c), u32(64), d, keys, out, d),
+                 "context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
+                     ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d)}
+        for s, op, *sizes in WANT:
             if s == name:
                 got[" ".join(map(str, (s, op, *sizes)))] = lib.kernels(lambda: calls[op](*sizes))
         if name == "n8192_k3":
@@ -61,7 +93,7 @@ def launches(tmp_path_factory):
 @pytest.mark.parametrize("case", WANT, ids=lambda c: " ".join(map(str, c)))
 def test_kernel(launches, case):
     names = [k[0] for k in launches[" ".join(map(str, case))]]
-    assert WANT[case] in names, names
+    assert any(n.startswith(WANT[case]) for n in names), names
 
 
 def test_copies_are_not_timed_as_sums(launches):

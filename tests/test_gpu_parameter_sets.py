@@ -107,6 +107,21 @@ def test_key_switches(name, batches):
                 _check(env, got[:, i].contiguous(), series[i], ("hoisted", batch, i))
 
 
+# pairs of units from 5/4 x 256 rows on with four digits and more (64 and 65 ciphertexts of five rows, 40 and 41 of eight; in
+# launches of single transforms just below), and two rounds of pairs, the last unit alone (155)
+@pytest.mark.parametrize("name,batches", [("n8192_k4", (63, 64, 65, 155)), ("n8192_k6_2sp", (39, 40, 41))])
+def test_summed_rotations_of_pairs_of_units(name, batches):
+    env = _env(name)
+    x = _operands(env, 20)
+    gs = [2 * env.n - 1, 3, 2 * env.n - 3, 9, 27, 2 * env.n - 9, 81, 5, 25]
+    raws, keys = zip(*[env.key(23 + i) for i in range(len(gs))])
+    for n_rot in (1, 9):
+        want = [env.orc.rotate_sum_hoisted(v, gs[:n_rot], dict(zip(gs, raws))) for v in x]
+        for batch in batches:
+            say(f"{n_rot} rotations summed {name} batch {batch}")
+            _check(env, env.ctx.rotate_sum_hoisted(_tiled(env, x, batch), gs[:n_rot], keys[:n_rot], batch), want, (n_rot, batch))
+
+
 @pytest.mark.parametrize("name,batches", [("n4096_k6", (1, 40)), ("n8192_k6_2sp", (1,))])
 def test_the_longest_sum_of_the_largest_values(name, batches):
     """128 rotations of six digits, every transformed digit and key value as large as it gets: constants are their own

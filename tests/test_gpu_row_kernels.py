@@ -256,8 +256,8 @@ def test_products_of_few_rows(name, batches):
             assert np.array_equal(got[u], want[u % 3, u % 2]), (name, batch, u)
 
 
-# pairs of units at N = 8192, from 5/4 x 256 rows of (unit, prime) on where whole rounds of pairs are few enough; an odd batch's
-# last unit is alone; keys are read ahead over the end of a rotation, sums reduced after eight
+# pairs of units at N = 8192 (107 and 193, 128, 255 and 385: where whole rounds of pairs are few enough), and what is taken around
+# them; an odd batch's last unit is alone; keys are read ahead over the end of a rotation, sums reduced after eight
 @pytest.mark.parametrize("name,batches", [("C2", (79, 80, 107, 193, 385)), ("mixed", (81, 128)), ("k1", (160, 255, 385))])
 def test_summed_rotations_of_pairs_of_units(name, batches):
     env = _env(name)
