@@ -386,8 +386,12 @@ template <> struct st_regs<StRegs> { static constexpr bool value = true; };
 
 // prio: a wave's priority falls from pass to pass between two barriers, so that those behind catch up and all reach the
 // barrier about together.  (Equal priorities let the oldest wave issue first: it runs ahead and then waits.)  Worth 2 to 7 %
-// where nothing but such rows is on the chip; beside other kernels, whose priority is 0, it holds these up (a step of
-// twelve heads with priorities in every transform: 422 -> 430 us), so callers say where.
+// where nothing but such rows is on the chip, so callers' transforms (row_alone), plaintext products and appends, sums of
+// products and half rows have it.  Beside other kernels, whose priority is 0, it can hold these up: with priorities in every transform
+// a step of twelve heads went from 422 to 430 us, with those of the sums at N = 4096 one of sixteen from 175 to 190, and neither has
+// it.  The appends, the sums at N = 8192 and the half rows run beside a step's other branches too, where it is neither gain
+// nor loss: steps of 4 to 16 heads at all three N, with each of them on and off, differ by less than 1 % either way, as two runs of
+// one library do (12 x 4 in rounds 449 / 449 us, chains 674 / 674; 16 x 3 at N = 16384 1890 / 1902, chains 3219 / 3234).
 template <int LOGN, int E, int PASS, bool FROM_REGS, class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
                                          const double *__restrict__ tw, const double *twr, double *twr_next,
@@ -1917,8 +1921,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
     constexpr bool FAR = LOGN > 12;
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     __shared__ double park[HAT ? 1 : 1 << LOGN];
-    // prompt context of twelve heads 2303 -> 2284 us; at N = 4096 these launches run beside other branches, a step of sixteen heads
-    // 175 -> 190
+    // prompt context of twelve heads 2303 -> 2284 us; at N = 4096 a step of sixteen heads 175 -> 190 (fwd_pass)
     constexpr bool PRIO = LOGN == 13 && !HAT;
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
