@@ -181,6 +181,16 @@ constexpr int TWREGS = 16;
 __device__ __forceinline__ constexpr int pad(int idx) { return idx + ((idx >> 5) << 1); }
 __device__ __forceinline__ double2 &pair_at(double *lds, int pos) { return *reinterpret_cast<double2 *>(lds + pos); }
 template <int LOGN> constexpr int lds_doubles() { return (1 << LOGN) + (1 << (LOGN - 4)); }
+// position `pos` of row w of rows that lie one after the other.  A row is more than the 64 KB that an instruction's offset reaches:
+// left to itself the compiler adds the distance for every element.
+template <int LOGN> __device__ __forceinline__ int row_pos(int w, int pos)
+{
+    if (w) {
+        pos += w * lds_doubles<LOGN>();
+        asm("" : "+v"(pos));
+    }
+    return pos;
+}
 
 // element `idx` of a row: a uniform base and a 32-bit byte offset per lane (one register instead of two,
 // no 64-bit address arithmetic)
@@ -204,6 +214,12 @@ template <class T> __device__ __forceinline__ T at_lane(const T *base, int tid)
     asm("" : "+s"(g));
     asm("" : "+v"(off));
     return *(const T __attribute__((address_space(1))) *)((const char __attribute__((address_space(1))) *)g + off);
+}
+// a uniform value, kept in scalar registers from here on
+__device__ __forceinline__ double pinned(double x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
 }
 // Constants that are read where they are used: kept for a whole kernel with several transforms they do not
 // fit the scalar registers.
@@ -392,7 +408,9 @@ template <> struct st_regs<StRegs> { static constexpr bool value = true; };
 // it.  The appends, the sums at N = 8192 and the half rows run beside a step's other branches too, where it is neither gain
 // nor loss: steps of 4 to 16 heads at all three N, with each of them on and off, differ by less than 1 % either way, as two runs of
 // one library do (12 x 4 in rounds 449 / 449 us, chains 674 / 674; 16 x 3 at N = 16384 1890 / 1902, chains 3219 / 3234).
-template <int LOGN, int E, int PASS, bool FROM_REGS, class ST>
+// U: rows of one prime taken through the pass together, row u in in[u E ...] or u * lds_doubles() further on in LDS.  They share the
+// pass's factors and its barrier.
+template <int LOGN, int E, int PASS, bool FROM_REGS, int U = 1, class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
                                          const double *__restrict__ tw, const double *twr, double *twr_next,
                                          const ModD m, int dst_limb, bool prio = false)
@@ -410,8 +428,10 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
     static_assert(!FROM_REGS || (first && L + R == LOGN), "register input only for the first pass");
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     static_assert(!last || !cross, "the last pass must be wave-local (chunk-wise copy-out)");
+    static_assert(U == 1 || st_regs<ST>::value, "rows together stay in registers");
+    constexpr int ROW = lds_doubles<LOGN>();
     if (prio) __builtin_amdgcn_s_setprio(PASS <= 1 ? 3 : last ? 1 : 2);
-    double v[G][1 << R];
+    double v[U][G][1 << R];
     int base[G];
 #pragma unroll
     for (int g = 0; g < G; g++) {
@@ -419,55 +439,67 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
         const int lo = gidx & ((1 << L) - 1);
         const int hi = first ? 0 : (gidx >> L);
         base[g] = (hi << (L + R)) | lo;
-        const int pb = pad(base[g]);
-#pragma unroll
-        for (int c = 0; c < (1 << R); c++) {
-            // first pass: element base + (c << L) = tid + (g + c*G) * T is fetched element g + c*G
-            if (FROM_REGS) v[g][c] = in[g + c * G];
-            else if (L > 0) v[g][c] = lds[pb + pad(c << L)];
-            else if (c % 2 == 0) {
-                const double2 w = pair_at(lds, pb + c);
-                v[g][c] = w.x;
-                v[g][c + 1] = w.y;
-            }
-        }
     }
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        if (do_red) {
+    for (int w = 0; w < U; w++)
 #pragma unroll
-            for (int c = 0; c < (1 << R) / 2; c++) v[g][c] = red(v[g][c], m);
-        }
-#pragma unroll
-        for (int u = 0; u < R; u++) {
-            const int half = 1 << (R - 1 - u);
+        for (int g = 0; g < G; g++) {
+            const int pb = row_pos<LOGN>(w, pad(base[g]));
 #pragma unroll
             for (int c = 0; c < (1 << R); c++) {
-                if (c & half) continue;
-                bfly_fwd(v[g][c], v[g][c + half], twr[g * PER + (1 << u) - 1 + (c >> (R - u))], m);
+                // first pass: element base + (c << L) = tid + (g + c*G) * T is fetched element g + c*G
+                if (FROM_REGS) v[w][g][c] = in[w * E + g + c * G];
+                else if (L > 0) v[w][g][c] = lds[pb + pad(c << L)];
+                else if (c % 2 == 0) {
+                    const double2 x = pair_at(lds, pb + c);
+                    v[w][g][c] = x.x;
+                    v[w][g][c + 1] = x.y;
+                }
             }
         }
-    }
+#pragma unroll
+    for (int w = 0; w < U; w++)
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            if (do_red) {
+#pragma unroll
+                for (int c = 0; c < (1 << R) / 2; c++) v[w][g][c] = red(v[w][g][c], m);
+            }
+#pragma unroll
+            for (int u = 0; u < R; u++) {
+                const int half = 1 << (R - 1 - u);
+#pragma unroll
+                for (int c = 0; c < (1 << R); c++) {
+                    if (c & half) continue;
+                    bfly_fwd(v[w][g][c], v[w][g][c + half], twr[g * PER + (1 << u) - 1 + (c >> (R - u))], m);
+                }
+            }
+        }
     // a last pass on pairs of neighbours leaves them where chunk_elem order has them: no trip to LDS
     if constexpr (last && R == 1 && st_regs<ST>::value) {
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            st.store(2 * g, 0, v[g][0], m);
-            st.store(2 * g + 1, 0, v[g][1], m);
-        }
+        for (int w = 0; w < U; w++)
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                st.store(w * E + 2 * g, 0, v[w][g][0], m);
+                st.store(w * E + 2 * g + 1, 0, v[w][g][1], m);
+            }
         return;
     }
     // fetch the next pass's factors while this pass's results drain to LDS
+    if constexpr (U > 1) __builtin_amdgcn_sched_barrier(0);     // (sooner they take registers that two rows need)
     if constexpr (!last) load_tw<LOGN, E, PASS + 1, false>(tw, tid, twr_next);
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        const int pb = pad(base[g]);
+    for (int w = 0; w < U; w++)
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++) {
-            if (L > 0) lds[pb + pad(c << L)] = v[g][c];
-            else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
+        for (int g = 0; g < G; g++) {
+            const int pb = row_pos<LOGN>(w, pad(base[g]));
+#pragma unroll
+            for (int c = 0; c < (1 << R); c++) {
+                if (L > 0) lds[pb + pad(c << L)] = v[w][g][c];
+                else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[w][g][c], v[w][g][c + 1]);
+            }
         }
-    }
     if constexpr (cross) lds_barrier();
     else wave_sync();
     if constexpr (last) {
@@ -475,9 +507,9 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
         // wave copies out its own chunk
         // (a lane takes pairs of neighbouring elements: 16 bytes per lane and store)
 #pragma unroll
-        for (int it = 0; it < E; it += 2) {
-            const int idx = chunk_elem<E>(tid, it);
-            const double2 w = pair_at(lds, pad(idx));
+        for (int it = 0; it < U * E; it += 2) {
+            const int idx = chunk_elem<E>(tid, it % E);
+            const double2 w = pair_at(lds, it / E * ROW + pad(idx));
             if constexpr (st_in_place<ST>::value) {
                 st.store(it, idx, w.x, m);
                 st.store(it + 1, idx + 1, w.y, m);
@@ -558,11 +590,12 @@ template <class ST> struct st_adds<const ST &> : st_adds<ST> {};
 
 // from != null: the first pass takes its elements from registers, in chunk_elem order
 // early: the first eight words that a storer adds to
-template <int LOGN, int E, int PASS, class ST>
+// U: rows of one prime together, as in fwd_pass; results of row u leave as row wg + u * row_step, or to out[u E ...]
+template <int LOGN, int E, int PASS, int U = 1, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
                                          const ModD m, int pr, const DevConst *C, const double *from = nullptr,
-                                         const uint64_t *early = nullptr, bool prio = false)
+                                         const uint64_t *early = nullptr, bool prio = false, int row_step = 0)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -575,7 +608,8 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     constexpr InvPlan<R> plan = inv_plan<R>(InvBound<LOGN, E, PASS>::in, last);
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     if (prio) __builtin_amdgcn_s_setprio(PASS < 2 ? 3 : PASS == P::NP - 1 ? 2 : PASS == P::NP - 2 ? 1 : 0);
-    double v[G][1 << R];
+    constexpr int ROW = lds_doubles<LOGN>();
+    double v[U][G][1 << R];
     int base[G];
 #pragma unroll
     for (int g = 0; g < G; g++) {
@@ -586,78 +620,88 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
         const int lo = gidx & ((1 << L) - 1);
         const int hi = last ? 0 : (gidx >> L);
         base[g] = (hi << (L + R)) | lo;
-        const int pb = pad(base[g]);
-#pragma unroll
-        for (int c = 0; c < (1 << R); c++) {
-            if (R == 1 && from) v[g][c] = from[2 * g + c];
-            else if (L > 0) v[g][c] = lds[pb + pad(c << L)];
-            else if (c % 2 == 0) {
-                const double2 w = pair_at(lds, pb + c);
-                v[g][c] = w.x;
-                v[g][c + 1] = w.y;
-            }
-        }
     }
-    static_assert(!(last && st_regs<ST>::value) || G == 1, "one group per thread in the last pass");
-    constexpr bool adds = last && st_adds<ST>::value;
-    static_assert(!adds || (G == 1 && (1 << R) % 8 == 0), "eight elements of the one group at a time");
-    uint64_t old[adds ? 8 : 1];
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        if (PASS == P::NP - 1) {
+    for (int w = 0; w < U; w++)
 #pragma unroll
-            for (int c = 0; c < (1 << R); c++) v[g][c] = red(v[g][c], m);
-        }
-#pragma unroll
-        for (int u = R - 1; u >= 0; u--) {
-            const int half = 1 << (R - 1 - u);
-#pragma unroll
-            for (int c = 0; c < (1 << R); c++)
-                if (plan.before[R - 1 - u][c]) v[g][c] = red(v[g][c], m);
+        for (int g = 0; g < G; g++) {
+            const int pb = row_pos<LOGN>(w, pad(base[g]));
 #pragma unroll
             for (int c = 0; c < (1 << R); c++) {
-                if (c & half) continue;
-                if (last && u == 0) {
-                    // stage 0: single twiddle; fold N^-1 into both outputs
-                    const double d = v[g][c] - v[g][c + half];
-                    v[g][c] = mulmod(v[g][c] + v[g][c + half], C->ninv[pr], m);
-                    v[g][c + half] = mulmod(d, C->itw1_ninv[pr], m);
-                } else {
-                    bfly_inv(v[g][c], v[g][c + half], twr[g * PER + (1 << u) - 1 + (c >> (R - u))], m);
+                if (R == 1 && from) v[w][g][c] = from[w * E + 2 * g + c];
+                else if (L > 0) v[w][g][c] = lds[pb + pad(c << L)];
+                else if (c % 2 == 0) {
+                    const double2 x = pair_at(lds, pb + c);
+                    v[w][g][c] = x.x;
+                    v[w][g][c + 1] = x.y;
                 }
             }
         }
+    static_assert(!(last && st_regs<ST>::value) || G == 1, "one group per thread in the last pass");
+    constexpr bool adds = last && st_adds<ST>::value;
+    static_assert(!adds || (U == 1 && G == 1 && (1 << R) % 8 == 0), "eight elements of the one group at a time");
+    uint64_t old[adds ? 8 : 1];
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++)
-            if (plan.after[c]) v[g][c] = red(v[g][c], m);
-    }
+    for (int w = 0; w < U; w++)
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            double (&x)[1 << R] = v[w][g];
+            if (PASS == P::NP - 1) {
+#pragma unroll
+                for (int c = 0; c < (1 << R); c++) x[c] = red(x[c], m);
+            }
+#pragma unroll
+            for (int u = R - 1; u >= 0; u--) {
+                const int half = 1 << (R - 1 - u);
+#pragma unroll
+                for (int c = 0; c < (1 << R); c++)
+                    if (plan.before[R - 1 - u][c]) x[c] = red(x[c], m);
+#pragma unroll
+                for (int c = 0; c < (1 << R); c++) {
+                    if (c & half) continue;
+                    if (last && u == 0) {
+                        // stage 0: single twiddle; fold N^-1 into both outputs
+                        const double d = x[c] - x[c + half];
+                        x[c] = mulmod(x[c] + x[c + half], C->ninv[pr], m);
+                        x[c + half] = mulmod(d, C->itw1_ninv[pr], m);
+                    } else {
+                        bfly_inv(x[c], x[c + half], twr[g * PER + (1 << u) - 1 + (c >> (R - u))], m);
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < (1 << R); c++)
+                if (plan.after[c]) x[c] = red(x[c], m);
+        }
     if constexpr (!last) {
         if constexpr (PASS == 1) load_tw<LOGN, E, 0, true>(itw, tid, twr_next);
         else load_tw<LOGN, E, PASS - 1, false>(itw, tid, twr_next);
     }
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        const int pb = pad(base[g]);
+    for (int w = 0; w < U; w++)
 #pragma unroll
-        for (int c = 0; c < (1 << R); c++) {
-            // the last pass pairs elements N/2 apart with consecutive lanes on consecutive
-            // addresses: it stores straight to global memory
-            if constexpr (adds) {
-                if (c == 0) {
+        for (int g = 0; g < G; g++) {
+            const int pb = row_pos<LOGN>(w, pad(base[g]));
 #pragma unroll
-                    for (int i = 0; i < 8; i++) old[i] = early[i];
-                } else if (c % 8 == 0) {
-                    st.template fetch<(1 << LOGN) / E>(old, tid, c);
+            for (int c = 0; c < (1 << R); c++) {
+                // the last pass pairs elements N/2 apart with consecutive lanes on consecutive
+                // addresses: it stores straight to global memory
+                if constexpr (adds) {
+                    if (c == 0) {
+#pragma unroll
+                        for (int i = 0; i < 8; i++) old[i] = early[i];
+                    } else if (c % 8 == 0) {
+                        st.template fetch<(1 << LOGN) / E>(old, tid, c);
+                    }
                 }
+                if (!last) {
+                    if (L > 0) lds[pb + pad(c << L)] = v[w][g][c];
+                    else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[w][g][c], v[w][g][c + 1]);
+                } else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[w][g][c], old[c % 8], m, C);
+                else if constexpr (st_regs<ST>::value) st.store(w * E + c, 0, v[w][g][c], m);     // (element tid + c * T)
+                else st.store(wg + w * row_step, base[g] + (c << L), v[w][g][c], m, C);
             }
-            if (!last) {
-                if (L > 0) lds[pb + pad(c << L)] = v[g][c];
-                else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[g][c], v[g][c + 1]);
-            } else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[g][c], old[c % 8], m, C);
-            else if constexpr (st_regs<ST>::value) st.store(c, 0, v[g][c], m);     // (element tid + c * T)
-            else st.store(wg, base[g] + (c << L), v[g][c], m, C);
         }
-    }
     if constexpr (!last) {
         if constexpr (PASS - 1 < P::NC) lds_barrier();   // the next pass reads other waves' elements
         else wave_sync();
@@ -768,9 +812,8 @@ __device__ __forceinline__ void garner(const ConvTab &T, const ModD *ms, const d
 // S/2 and without making the digits canonical.  red() picks the balanced residue exactly here: its
 // quotient x u is off by less than 1.25 * 2^-52 up to |x u| = 2, and the residues next to an odd multiple of p/2 are
 // 2^-51 away.
-template <int NS>
-__device__ __forceinline__ void garner_balanced(const ConvTab &T, const ModD *ms, const double (&x)[NS],
-                                                double (&a)[NS])
+template <int NS, class TAB>
+__device__ __forceinline__ void garner_balanced(const TAB &T, const ModD *ms, const double (&x)[NS], double (&a)[NS])
 {
     a[0] = red(x[0], ms[0]);
 #pragma unroll
@@ -784,8 +827,8 @@ __device__ __forceinline__ void garner_balanced(const ConvTab &T, const ModD *ms
 }
 // residue of the integer modulo target jt (mt); lazy, |.| < 1.25 * 2^50 with balanced digits, < 2.1 * 2^50 with
 // canonical ones
-template <int NS>
-__device__ __forceinline__ double horner(const ConvTab &T, const ModD mt, const double (&a)[NS], int jt)
+template <int NS, class TAB>
+__device__ __forceinline__ double horner(const TAB &T, const ModD mt, const double (&a)[NS], int jt)
 {
     double acc = a[NS - 1];
 #pragma unroll
@@ -1415,7 +1458,8 @@ template <> struct st_adds<StAppendRow> { static constexpr bool value = true; };
 // in: pass-0 ownership (element tid + it * T), or, with SCATTERED, already in LDS; out: chunk_elem order
 // ahead: run before the last pass, for loads that nothing before it waits for
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
-template <int LOGN, int E, bool SCATTERED, bool PRIO = false, class F = Nothing>
+// U: rows of one prime together, row u in in[u E ...], its LDS u * lds_doubles() further on
+template <int LOGN, int E, bool SCATTERED, bool PRIO = false, int U = 1, class F = Nothing>
 __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *out, int tid,
                                         const double *__restrict__ tw, const ModD m, F ahead = F())
 {
@@ -1426,18 +1470,20 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
     double twa[TWREGS], twb[TWREGS];
     const StRegs st{out};
     load_tw<LOGN, E, 0, true>(tw, tid, twa);
-    fwd_pass<LOGN, E, 0, !SCATTERED>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
-    fwd_pass<LOGN, E, 1, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
-    fwd_pass<LOGN, E, 2, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    fwd_pass<LOGN, E, 0, !SCATTERED, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    fwd_pass<LOGN, E, 1, false, U>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    fwd_pass<LOGN, E, 2, false, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
     if (NP == 4) ahead();
-    fwd_pass<LOGN, E, 3, false>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    fwd_pass<LOGN, E, 3, false, U>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
     if (NP > 4) ahead();
-    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
 }
 // in: chunk_elem order, |x| < 8p; results leave through st as row `row`
-template <int LOGN, int E, bool PRIO = false, class ST>
+// U: rows together as in fwd_row, results as rows `row` + u * row_step
+template <int LOGN, int E, bool PRIO = false, int U = 1, class ST>
 __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
-                                        const double *__restrict__ itw, const ModD m, int pr, const DevConst *C)
+                                        const double *__restrict__ itw, const ModD m, int pr, const DevConst *C,
+                                        int row_step = 0)
 {
     constexpr int NP = Plan<LOGN, E>::NP;
     asm volatile("" : "+v"(tid));
@@ -1445,20 +1491,20 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
     load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
     if constexpr (Plan<LOGN, E>::R[NP - 1] != 1) {
 #pragma unroll
-        for (int it = 0; it < E; it += 2)
-            pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(in[it], in[it + 1]);
+        for (int it = 0; it < U * E; it += 2)
+            pair_at(lds, it / E * lds_doubles<LOGN>() + pad(chunk_elem<E>(tid, it % E))) = make_double2(in[it], in[it + 1]);
         wave_sync();
     }
-    inv_pass<LOGN, E, NP - 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO);
+    inv_pass<LOGN, E, NP - 1, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO, row_step);
     if constexpr (NP > 4) {
-        inv_pass<LOGN, E, 3>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
-        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
-        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
-        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 3, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 2, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 0, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
     } else {
-        inv_pass<LOGN, E, 2>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
-        inv_pass<LOGN, E, 1>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
-        inv_pass<LOGN, E, 0>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 2, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 0, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
     }
 }
 
@@ -1710,173 +1756,158 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 // tensor product and the three inverse transforms in one kernel.  An operand that is there in transformed
 // form already (an a operand shared by several units, a cache with a transformed copy) is read in it.
 // Instead of 101 rows of traffic per product (three launches: ciphertext primes, auxiliary primes, tensor
-// product) 33 reach memory.  The order x0, y0, x1, y1 keeps at most two rows in registers during a transform: x0
-// waits in a second LDS buffer (one workgroup per unit at N = 8192, two at N = 4096), x0 y0 leaves before x1 is
-// transformed.  Bound by vector issue (66 to 68 % busy; the lifts to the auxiliary primes are an eighth of it).  768
-// products at N = 8192, three primes: 308 + 644 + 764 us for the three launches, 1119 us here.
+// product) 33 reach memory.  An operand's two polynomials go through the forward transform together, the first two components of
+// the product through the inverse one: two rows of one prime share the factors and every barrier (seven rows, four walks instead of
+// seven), and each has the other's arithmetic to cover its trips to LDS.  Both operands' four rows then lie in registers (114 of 128).
+// Bound by vector issue (77 % of the clocks) and what the operands' words and the stores keep it waiting (16 and 6 %, by leaving them out); the
+// clock under this load is 2.0 GHz.  768 products at N = 8192, three primes: 308 + 644 + 764 us for the three launches, 1195 us with
+// one row at a time, 1180 in pairs, 1100 with the lift's constants read once besides (in walks of one row these gain nothing: the
+// constants' scalar registers are spilled).  Measured without gain: the next rows' first words asked for before the last pass, more of a row's
+// words on their way (registers spilled), the stores of all three rows at the end.
 // ---------------------------------------------------------------------------
-// element rows of an operand in coefficients, modulo the prime of the workgroup; loads and arithmetic apart,
-// so that the loads of the next row can be on their way during a transform
-template <int LOGN, int E, int K>
-struct MulRowLoad {
-    static constexpr bool kWhole = false;      // all of a row's words fit
-    static constexpr int T = (1 << LOGN) / E, H = E / 2;
-    uint64_t w[H][K];      // half a row
-    // words of elements it0 .. it0 + H of the polynomial at src, as LdMulExt takes them
-    __device__ __forceinline__ void fetch(const uint64_t *src, int r, int it0, int tid)
-    {
-#pragma unroll
-        for (int i = 0; i < H; i++)
-#pragma unroll
-            for (int q = 0; q < K; q++)
-                w[i][q] = at_lane(src + ((size_t)LdMulExt<K>::source(r, q) << LOGN) + (it0 + i) * T, tid);
-    }
-    __device__ __forceinline__ void finish(double *x, int r, const ModD m, const DevConst *C) const
-    {
-        C = opaque_const(C);
-#pragma unroll
-        for (int i = 0; i < H; i++) x[i] = LdMulExt<K>::lift(w[i], r, m, C);
-    }
-};
-
-// K = 0: operands that lift_kernel has lifted, a word per element
+// operands that lift_kernel has lifted, a word per element; loads and conversion apart, so that the words of the next row can be on their way
+// during a transform
 template <int LOGN, int E>
-struct MulRowLoad<LOGN, E, 0> {
-    static constexpr bool kWhole = true;
+struct LiftedRow {
     static constexpr int T = (1 << LOGN) / E;
     uint64_t w[E];
-    __device__ __forceinline__ void fetch(const uint64_t *src, int r, int, int tid)
+    __device__ __forceinline__ void fetch(const uint64_t *src, int r, int tid)
     {
 #pragma unroll
         for (int i = 0; i < E; i++) w[i] = at_lane(src + ((size_t)r << LOGN) + i * T, tid);
     }
-    __device__ __forceinline__ void finish(double *x, int, const ModD, const DevConst *) const
+    __device__ __forceinline__ void finish(double *x) const
     {
 #pragma unroll
         for (int i = 0; i < E; i++) x[i] = bits_f64(w[i]);
     }
 };
 
+// The constants of a lift to one auxiliary prime, read once and kept in scalar registers.  Read where they are used they were
+// asked for anew for every element, six trips to the scalar cache one after the other that nothing covered.
+template <int K> struct LiftTab {
+    double inv[K][K], s_mod_t[K][1];
+    ModD ms[K];
+    __device__ __forceinline__ LiftTab(const DevConst *C, int j)
+    {
+        C = opaque_const(C);
+#pragma unroll
+        for (int b = 0; b < K; b++) {
+            ms[b] = ModD{pinned(C->mod[b].p), pinned(C->mod[b].u)};
+            s_mod_t[b][0] = b + 1 < K ? pinned(C->q2b.s_mod_t[b][j]) : 0.0;
+#pragma unroll
+            for (int a = 0; a < b; a++) inv[a][b] = pinned(C->q2b.inv[a][b]);
+        }
+    }
+};
+// The polynomial at src modulo the workgroup's prime (of the k + l), in pass-0 ownership.  A row modulo an auxiliary prime: a pair of elements
+// is lifted while the next pair's words are on their way.
+template <int LOGN, int E, int K>
+__device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, int tid, const ModD m, const DevConst *C)
+{
+    constexpr int T = (1 << LOGN) / E;
+    if (r < K) {
+#pragma unroll
+        for (int it = 0; it < E; it++) x[it] = u64_to_f64(at_lane(src + ((size_t)r << LOGN) + it * T, tid));
+        return;
+    }
+    uint64_t w[2][2][K];
+    auto get = [&](int it) {
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int q = 0; q < K; q++) w[(it >> 1) & 1][i][q] = at_lane(src + ((size_t)q << LOGN) + (it + i) * T, tid);
+    };
+    get(0);
+    const LiftTab<K> tab(C, r - K);
+#pragma unroll
+    for (int it = 0; it < E; it += 2) {
+        // (kept apart: the compiler would ask for the whole row first and spill what the caller holds)
+        if (it + 2 < E) get(it + 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            double v[K], dg[K];
+#pragma unroll
+            for (int q = 0; q < K; q++) v[q] = u64_to_f64(w[(it >> 1) & 1][i][q]);
+            garner_balanced<K>(tab, tab.ms, v, dg);
+            x[it + i] = horner<K>(tab, m, dg, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // HAT: 0 both operands in coefficients, 1 the first (x) in coefficients and the second (y) transformed.
 // K = 0: half rows at N = 16384, lifted ahead by lift_kernel, which shares a coefficient's mixed-radix digits between the
-// auxiliary primes (lifted per prime in a transform's loader, the digits of six primes took twice the transform itself).  The
-// whole next row travels during a transform.  96 products, six primes: 165 + 438 + 404 us for the transforms of ciphertext and
-// auxiliary rows and the tensor product's inverse, 161 + 501 us for lift_kernel and this.
+// auxiliary primes (lifted per prime in a transform's loader, the digits of six primes took twice the transform itself).  96
+// products, six primes: 165 + 438 + 404 us for the transforms of ciphertext and auxiliary rows and the tensor product's inverse,
+// 161 + 501 us for lift_kernel and this.
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                const DevConst *__restrict__ C, int nwg)
 {
-    using LD = MulRowLoad<LOGN, E, K>;
-    constexpr int T = (1 << LOGN) / E, H = E / 2;
+    constexpr int T = (1 << LOGN) / E;
+    // half rows: priorities take 96 products from 1238 to 1224 us, 5 from 115.3 to 113.4; whole rows: no difference
+    constexpr bool PRIO = K == 0;
     const int KL = K ? 2 * K + 1 : A.k;
-    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
-    __shared__ double park[HAT ? 1 : 1 << LOGN];
+    __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
     const int tid = threadIdx.x;
-    int p = blockIdx.x;
-    int wg = xcd_row(p, nwg, KL);
-    LD ld;
-    // polynomials in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
-    auto poly = [&](int u, int t) {
-        return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
-    };
-    ld.fetch(poly(wg / KL, 0), wg % KL, 0, tid);
-    for (;;) {
-        const int r = wg % KL, u = wg / KL;
+    for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
+        const int wg = xcd_row(p, nwg, KL), r = wg % KL, u = wg / KL;
         const ModD m = C->mod[K ? r : r >> 1];
         const int pr = K ? r : MAXPR + r;
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
-        p += (int)gridDim.x;
-        const bool more = p < nwg;
-        const int wg_next = more ? xcd_row(p, nwg, KL) : wg;
-        double keep[E], part[E];
+        auto load = [&](double *x, const uint64_t *p0, const uint64_t *p1) {
+            if constexpr (K == 0) {
 #pragma unroll
-        for (int it = 0; it < E; it++) keep[it] = part[it] = 0.0;
-        constexpr int NT = HAT ? 2 : 4;
-#pragma unroll
-        for (int t = 0; t < NT; t++) {
-            double x[E];
-            auto fetch_next = [&]() {
-                ld.fetch(t + 1 < NT ? poly(u, t + 1) : poly(wg_next / KL, 0), t + 1 < NT ? r : wg_next % KL, 0, tid);
-            };
-            if constexpr (LD::kWhole) {
-                ld.finish(x, r, m, C);
-                fetch_next();
-            } else {
-                LD hi;
-                hi.fetch(poly(u, t), r, H, tid);
-                ld.finish(x, r, m, C);
-                hi.finish(x + H, r, m, C);
-            }
-            // (half rows: priorities take 96 products from 1238 to 1224 us, 5 from 115.3 to 113.4; whole rows: no difference)
-            fwd_row<LOGN, E, false, (K == 0)>(lds, x, x, tid, tw, m);
-            if constexpr (!LD::kWhole) fetch_next();
-            double y[E], z[E];
-#pragma unroll
-            for (int it = 0; it < E; it++) x[it] = y[it] = z[it] = red(x[it], m);
-            int n_inv = 0;
-            if constexpr (!HAT) {
-                if (t == 0) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) park[tid + it * T] = x[it];
-                } else if (t == 1) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        y[it] = mulmod(park[tid + it * T], x[it], m);
-                        keep[it] = x[it];
-                    }
-                    n_inv = 1;
-                } else if (t == 2) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        part[it] = mulmod(x[it], keep[it], m);
-                        keep[it] = x[it];
-                    }
-                } else {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        y[it] = part[it] + mulmod(park[tid + it * T], x[it], m);
-                        z[it] = mulmod(keep[it], x[it], m);
-                    }
-                    n_inv = 2;
+                for (int it = 0; it < E; it++) {
+                    x[it] = bits_f64(at_lane(p0 + ((size_t)r << LOGN) + it * T, tid));
+                    x[E + it] = bits_f64(at_lane(p1 + ((size_t)r << LOGN) + it * T, tid));
                 }
             } else {
-                const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
-                int tk = tid;
-                asm volatile("" : "+v"(tk));
-                if (t == 0) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        y[it] = mulmod(x[it], red(at32(y0, chunk_elem<E>(tk, it)), m), m);
-                        keep[it] = x[it];
-                    }
-                } else {
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        const double b0 = red(at32(y0, chunk_elem<E>(tk, it)), m), b1 = red(at32(y1, chunk_elem<E>(tk, it)), m);
-                        z[it] = mulmod(x[it], b1, m);
-                        y[it] = mulmod(keep[it], b1, m) + mulmod(x[it], b0, m);
-                    }
-                }
-                n_inv = t + 1;
+                lift_row<LOGN, E, K>(x, p0, r, tid, m, C);
+                lift_row<LOGN, E, K>(x + E, p1, r, tid, m, C);
             }
-            for (int i = 0; i < n_inv; i++) {
-                inv_row<LOGN, E, (K == 0)>(lds, y, st, (u * 3 + t / (NT / 2) + i) * KL + r, tid, itw, m, pr, C);
+        };
+        double x[2 * E], y[2 * E], e[2 * E], z[E];
+        load(x, A.x_poly(u, 0), A.x_poly(u, 1));
+        if (p != (int)blockIdx.x) lds_barrier();
+        fwd_row<LOGN, E, false, PRIO, 2>(lds, x, x, tid, tw, m);
 #pragma unroll
-                for (int it = 0; it < E; it++) y[it] = z[it];
-                if (i + 1 < n_inv) lds_barrier();
+        for (int it = 0; it < 2 * E; it++) x[it] = red(x[it], m);
+        if constexpr (HAT) {
+            const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
+            int tk = tid;
+            asm volatile("" : "+v"(tk));
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                y[it] = at32(y0, chunk_elem<E>(tk, it));
+                y[E + it] = at32(y1, chunk_elem<E>(tk, it));
             }
-            if (t + 1 < NT) lds_barrier();
+        } else {
+            load(y, A.y_poly(u, 0), A.y_poly(u, 1));
+            lds_barrier();
+            fwd_row<LOGN, E, false, PRIO, 2>(lds, y, y, tid, tw, m);
         }
-        if (!more) break;
-        wg = wg_next;
+#pragma unroll
+        for (int it = 0; it < E; it++) {
+            const double b0 = red(y[it], m), b1 = red(y[E + it], m);
+            e[it] = mulmod(x[it], b0, m);
+            e[E + it] = mulmod(x[it], b1, m) + mulmod(x[E + it], b0, m);
+            z[it] = mulmod(x[E + it], b1, m);
+        }
+        inv_row<LOGN, E, PRIO, 2>(lds, e, st, (u * 3) * KL + r, tid, itw, m, pr, C, KL);
         lds_barrier();
+        inv_row<LOGN, E, PRIO>(lds, z, st, (u * 3 + 2) * KL + r, tid, itw, m, pr, C);
     }
 }
 
-// The polynomial at src modulo the workgroup's prime, in pass-0 ownership, W elements' words on their way while one is lifted.
+// The same for mul_sum_row_kernel, W elements' words on their way while one is lifted.  All workgroups of a round walk over the same
+// units, and those of a unit share its words in one L2: lift_row, which is done sooner with rows modulo ciphertext primes, lets them
+// drift apart (12 groups of 128, N = 8192: 1590 us here, 1650 with lift_row, 1695 with a branch for the ciphertext primes here).
 template <int LOGN, int E, int K, int W>
-__device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, int tid, const ModD m, const DevConst *C)
+__device__ __forceinline__ void lift_window(double *x, const uint64_t *src, int r, int tid, const ModD m, const DevConst *C)
 {
     constexpr int T = (1 << LOGN) / E;
     uint64_t w[W][K];
@@ -1952,15 +1983,15 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                 for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
             }
         };
-        MulRowLoad<LOGN, E, 0> whole;
-        if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, 0, tid);
+        LiftedRow<LOGN, E> whole;
+        if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, tid);
         for (int u = u_first; u < u_end; u++) {
             auto row = [&](double *x, int t) {
                 if constexpr (K == 0) {
-                    whole.finish(x, r, m, C);
-                    whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, 0, tid);
+                    whole.finish(x);
+                    whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, tid);
                 } else {
-                    lift_row<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
+                    lift_window<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
                 }
             };
             if constexpr (HAT) {
