@@ -347,6 +347,7 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         }
         const uint64_t ninv = h_inv(N % p, p);
         H.ninv[r] = h_centred(ninv, p);
+        H.t_ninv[r] = h_centred(h_mul(c->t % p, ninv, p), p);
         H.itw1_ninv[r] = h_centred(h_mul(h_inv(pw[h_bitrev(1, c->logn)], p), ninv, p), p);
     }
     std::vector<double> tw2, itw2;
@@ -356,7 +357,6 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
         tw2.resize((size_t)np * N);
         itw2.resize((size_t)np * N);
         for (int r = 0; r < np; r++) {
-            const uint64_t p = c->pr[r], ninv = h_inv(N % p, p);
             const double *t = &tw[(size_t)r * N], *it = &itw[(size_t)r * N];
             for (size_t h = 0; h < 2; h++) {
                 double *t2 = &tw2[(size_t)r * N + h * half], *it2 = &itw2[(size_t)r * N + h * half];
@@ -365,9 +365,6 @@ extern "C" int cg_create(cg_ctx **out, const cg_params *prm)
                         t2[w + j] = t[2 * w + h * w + j];
                         it2[w + j] = it[2 * w + h * w + j];
                     }
-                const uint64_t w1 = it[2 + h] < 0 ? p - (uint64_t)-it[2 + h] : (uint64_t)it[2 + h];
-                H.ninv[MAXPR + 2 * r + h] = H.ninv[r];
-                H.itw1_ninv[MAXPR + 2 * r + h] = h_centred(h_mul(w1, ninv, p), p);
             }
             H.tw1[r] = t[1];
             H.itw1[r] = it[1];
@@ -950,7 +947,7 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
         const unsigned grid = ntt_grid<mul_row_kernel<LG, 8, K, HAT>>(c, nwg, (int)threads);              \
         if (c->dry) return CG_OK;                                                                         \
         return launch_kernel(mul_row_kernel<LG, 8, K, HAT>, dim3(grid), dim3(threads), s, A,              \
-                             StInvF64{tens, LG}, (const double *)(K ? c->tw : c->tw2),                    \
+                             StTens<K == 0>{{tens, LG}}, (const double *)(K ? c->tw : c->tw2),            \
                              (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
     if (c->logn == 14) CG_MULROW(13, 0);
@@ -981,7 +978,7 @@ static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, dou
         const unsigned grid = ntt_grid<mul_sum_row_kernel<LG, 8, K, H>>(c, nwg, (int)threads);            \
         if (c->dry) return CG_OK;                                                                         \
         return launch_kernel(mul_sum_row_kernel<LG, 8, K, H>, dim3(grid), dim3(threads), s, A, (int)group, \
-                             (int)parts, StInvF64{tens, LG}, (const double *)(K ? c->tw : c->tw2),        \
+                             (int)parts, StTens<K == 0>{{tens, LG}}, (const double *)(K ? c->tw : c->tw2), \
                              (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
     if (half) CG_MULSUMROW(13, 0, HAT);
@@ -1122,9 +1119,9 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         const LdInvTensor ld{ntt, b_ext, (int)a_group, (int)n_a, (int)b_group, (int)b_stride, c->logn};
         const size_t rows = (size_t)n_out * 3 * c->KL;
         const double tbytes = LB * c->KL * (2.0 * ((double)n_a + B) + 3.0 * n_out);
-        if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StInvF64{tens, c->logn},
+        if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StTens<false>{{tens, c->logn}},
                                          KID_INV_TENSORSUM, tbytes));
-        else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
+        else CG_TRY(launch_inv(c, s, rows, ld, StTens<false>{{tens, c->logn}}, KID_INV_TENSOR, tbytes));
     }
     const double sbytes = LB * (3.0 * c->KL * parts + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);

@@ -109,46 +109,73 @@ template <int LOGN, int E> struct FwdBound<LOGN, E, 0> {
 // before a stage (their sum would pass LAZY_MAX) and which results are reduced at its end, so that the
 // next pass starts from INV_OUT.  Of eight results of a three-stage pass two or three are reduced, and
 // two operands on the way, where reducing every input takes eight.
+// last: the stage that ends the transform, 1 with N^-1 folded into both of its products, 2 without: its sums stay below last_max.
 constexpr double INV_OUT = 1.92;
 template <int R> struct InvPlan {
     bool before[R][1 << R], after[1 << R];
     double out;
+    int reds;
 };
-template <int R> constexpr InvPlan<R> inv_plan(double in, bool last)
+// both: of two operands whose sum is too large both are reduced, else the larger one alone where that is enough
+template <int R> constexpr InvPlan<R> inv_plan(double in, int last, double last_max, bool both)
 {
     InvPlan<R> P{};
     double b[1 << R] = {};
     for (int c = 0; c < (1 << R); c++) b[c] = in;
     for (int s = 0; s < R; s++) {
         const int half = 1 << s;
+        const double max = last == 2 && s == R - 1 ? last_max : LAZY_MAX;
         for (int c = 0; c < (1 << R); c++) {
             if (c & half) continue;
-            if (b[c] + b[c + half] > LAZY_MAX)
+            if (b[c] + b[c + half] > max) {
+                const bool low = b[c] > b[c + half], one = !both && (low ? b[c + half] : b[c]) + 0.51 <= max;
                 for (int i : {c, c + half}) {
-                    P.before[s][i] = b[i] > 0.51;
-                    if (b[i] > 0.51) b[i] = 0.51;
+                    P.before[s][i] = b[i] > 0.51 && (!one || (i == c) == low);
+                    if (P.before[s][i]) {
+                        b[i] = 0.51;
+                        P.reds++;
+                    }
                 }
+            }
             const double sum = b[c] + b[c + half], prod = 0.5 + 0.1875 * sum;
-            b[c] = (last && s == R - 1) ? prod : sum;
+            b[c] = (last == 1 && s == R - 1) ? prod : sum;
             b[c + half] = prod;
         }
     }
     for (int c = 0; c < (1 << R); c++) {
         P.after[c] = !last && b[c] > INV_OUT;
-        if (P.after[c]) b[c] = 0.51;
+        if (P.after[c]) {
+            b[c] = 0.51;
+            P.reds++;
+        }
         if (b[c] > P.out) P.out = b[c];
     }
     return P;
 }
-// the first pass (NP - 1) reduces what the loader delivers
-template <int LOGN, int E, int PASS, bool FIRST = PASS == Plan<LOGN, E>::NP - 1> struct InvBound {
-    static constexpr double in = InvBound<LOGN, E, PASS + 1>::out;
-    static constexpr double out = inv_plan<Plan<LOGN, E>::R[PASS]>(in, PASS == 0).out;
+template <int R> constexpr InvPlan<R> inv_plan(double in, int last, double last_max)
+{
+    const InvPlan<R> two = inv_plan<R>(in, last, last_max, true), one = inv_plan<R>(in, last, last_max, false);
+    return one.reds < two.reds ? one : two;
+}
+// IN: bound of what the loader delivers, in hundredths; 0: the first pass (NP - 1) reduces it
+template <int LOGN, int E, int PASS, int IN, bool FIRST = PASS == Plan<LOGN, E>::NP - 1> struct InvBound {
+    static constexpr double in = inv_plan<Plan<LOGN, E>::R[PASS + 1]>(InvBound<LOGN, E, PASS + 1, IN>::in, 0, 0.0).out;
 };
-template <int LOGN, int E, int PASS> struct InvBound<LOGN, E, PASS, true> {
-    static constexpr double in = 0.51;
-    static constexpr double out = inv_plan<Plan<LOGN, E>::R[PASS]>(in, PASS == 0).out;
+template <int LOGN, int E, int PASS, int IN> struct InvBound<LOGN, E, PASS, IN, true> {
+    static constexpr double in = IN ? 0.01 * IN : 0.51;
 };
+// Products of transformed rows: the first factor reduced, the second as a forward transform (of whatever width) leaves it
+template <int LOGN> constexpr double fwd_out()
+{
+    const double a = FwdBound<LOGN, 8, Plan<LOGN, 8>::NP - 1>::out;
+    if constexpr (LOGN == 13) {
+        const double b = FwdBound<LOGN, 16, Plan<LOGN, 16>::NP - 1>::out;
+        return a > b ? a : b;
+    }
+    return a;
+}
+constexpr double prod_of(double lazy) { return 0.5 + 0.375 * 0.51 * lazy; }
+constexpr int hundredths(double x) { return (int)(100.0 * x) + 1; }
 
 __device__ __forceinline__ void bfly_fwd(double &a, double &b, double w, const ModD m)
 {
@@ -214,6 +241,14 @@ template <class T> __device__ __forceinline__ T at_lane(const T *base, int tid)
     asm("" : "+s"(g));
     asm("" : "+v"(off));
     return *(const T __attribute__((address_space(1))) *)((const char __attribute__((address_space(1))) *)g + off);
+}
+template <class T> __device__ __forceinline__ void put_lane(T *base, int tid, T v)
+{
+    auto g = (T __attribute__((address_space(1))) *)base;
+    uint32_t off = (uint32_t)tid * (uint32_t)sizeof(T);
+    asm("" : "+s"(g));
+    asm("" : "+v"(off));
+    *(T __attribute__((address_space(1))) *)((char __attribute__((address_space(1))) *)g + off) = v;
 }
 // a uniform value, kept in scalar registers from here on
 __device__ __forceinline__ double pinned(double x)
@@ -587,11 +622,20 @@ ntt_fwd_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *
 template <class ST> struct st_adds { static constexpr bool value = false; };
 template <class ST> struct st_adds<const ST> : st_adds<ST> {};
 template <class ST> struct st_adds<const ST &> : st_adds<ST> {};
+// storers of rows without the factor N^-1 (scale_kernel has it among its constants): bound of the results, in hundredths
+template <class ST> struct st_unscaled { static constexpr int value = 0; };
+template <class ST> struct st_unscaled<const ST> : st_unscaled<ST> {};
+// Loaders of inverse transforms: bound of what they deliver (InvBound's IN).  With it the first pass reduces what its plan asks for, and a
+// factor of a product need not be reduced to keep the other bounds: with N^-1 left to the scaling a product's workgroup (mul_row_kernel,
+// three primes) has 5110 FP64 instructions a thread -> 4978, one of a sum 4162 -> 4066, a plaintext product 1066 -> 1046.
+// 768 products and relinearisations at N = 8192 1830 -> 1780 us, 128 appends of 24 caches (with the stores' addresses in scalar
+// registers and one reduction for sum and result) 1928 -> 1882.
+template <class LD> struct ld_in { static constexpr int value = 0; };
 
 // from != null: the first pass takes its elements from registers, in chunk_elem order
 // early: the first eight words that a storer adds to
 // U: rows of one prime together, as in fwd_pass; results of row u leave as row wg + u * row_step, or to out[u E ...]
-template <int LOGN, int E, int PASS, int U = 1, class ST>
+template <int LOGN, int E, int PASS, int IN = 0, int U = 1, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
                                          const ModD m, int pr, const DevConst *C, const double *from = nullptr,
@@ -605,7 +649,9 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     constexpr int PER = (1 << R) - 1;
     constexpr bool last = PASS == 0;
     constexpr bool cross = PASS < P::NC;
-    constexpr InvPlan<R> plan = inv_plan<R>(InvBound<LOGN, E, PASS>::in, last);
+    constexpr int unscaled = st_unscaled<ST>::value;
+    constexpr InvPlan<R> plan = inv_plan<R>(InvBound<LOGN, E, PASS, IN>::in, !last ? 0 : unscaled ? 2 : 1, 0.01 * unscaled);
+    static_assert(plan.out <= LAZY_MAX, "lazy bound exceeds 2^53");
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     if (prio) __builtin_amdgcn_s_setprio(PASS < 2 ? 3 : PASS == P::NP - 1 ? 2 : PASS == P::NP - 2 ? 1 : 0);
     constexpr int ROW = lds_doubles<LOGN>();
@@ -646,7 +692,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
 #pragma unroll
         for (int g = 0; g < G; g++) {
             double (&x)[1 << R] = v[w][g];
-            if (PASS == P::NP - 1) {
+            if (PASS == P::NP - 1 && !IN) {
 #pragma unroll
                 for (int c = 0; c < (1 << R); c++) x[c] = red(x[c], m);
             }
@@ -659,7 +705,7 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
 #pragma unroll
                 for (int c = 0; c < (1 << R); c++) {
                     if (c & half) continue;
-                    if (last && u == 0) {
+                    if (last && u == 0 && !unscaled) {
                         // stage 0: single twiddle; fold N^-1 into both outputs
                         const double d = x[c] - x[c + half];
                         x[c] = mulmod(x[c] + x[c + half], C->ninv[pr], m);
@@ -697,9 +743,10 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
                 if (!last) {
                     if (L > 0) lds[pb + pad(c << L)] = v[w][g][c];
                     else if (c % 2 == 0) pair_at(lds, pb + c) = make_double2(v[w][g][c], v[w][g][c + 1]);
-                } else if constexpr (st_adds<ST>::value) st.store(wg, base[g] + (c << L), v[w][g][c], old[c % 8], m, C);
+                } else if constexpr (st_adds<ST>::value) st.store(c << L, base[g], v[w][g][c], old[c % 8], m);
                 else if constexpr (st_regs<ST>::value) st.store(w * E + c, 0, v[w][g][c], m);     // (element tid + c * T)
-                else st.store(wg + w * row_step, base[g] + (c << L), v[w][g][c], m, C);
+                else if constexpr (G == 1) st.store_lane(wg + w * row_step, c << L, base[g], v[w][g][c], m);
+                else st.store(wg + w * row_step, base[g] + (c << L), v[w][g][c], m);
             }
         }
     if constexpr (!last) {
@@ -714,7 +761,7 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
 {
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
-    constexpr int NP = Plan<LOGN, E>::NP;
+    constexpr int NP = Plan<LOGN, E>::NP, IN = ld_in<LD>::value;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
     // (N = 4096, 1500 rows: 24.9 -> 23.6 us, 4096: 57 -> 55.  N = 8192, 1024 threads: 1000 rows 35.7 -> 37.0, 4000 the same;
     // 3000 of 16384: 209 -> 217.)
@@ -759,20 +806,20 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
         wave_sync();
         // passes NP-1 ... 0; the twiddle buffers alternate
         if constexpr (NP == 5) {
-            inv_pass<LOGN, E, 4>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 4, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 3, IN>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 2, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1, IN>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
         } else if constexpr (NP == 4) {
-            inv_pass<LOGN, E, 3>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 3, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 2, IN>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0, IN>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
         } else {
-            inv_pass<LOGN, E, 2>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 1>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
-            inv_pass<LOGN, E, 0>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 2, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 1, IN>(lds, st, orow, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, prio);
+            inv_pass<LOGN, E, 0, IN>(lds, st, orow, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, prio);
         }
         if (!more) break;
         wg = wg_next;
@@ -1210,6 +1257,8 @@ struct LdInvKsInner {
     }
 };
 
+template <int DNUM> struct ld_in<LdInvKsInner<DNUM>> { static constexpr int value = 70 * DNUM; };
+
 // A series of rotations of the same ciphertexts ("hoisted" rotations): the digits of c1 are lifted,
 // extended and transformed once, and every Galois element is applied to the transformed digits,
 // where it is a permutation of the evaluation points: row element i is the value at
@@ -1253,6 +1302,8 @@ struct LdInvKsInnerHoisted {
         return inner_product<DNUM>(raw, m);
     }
 };
+
+template <int DNUM> struct ld_in<LdInvKsInnerHoisted<DNUM>> { static constexpr int value = 70 * DNUM; };
 
 // rows of doubles (lazy), transformed in place: row w is [unit][component][prime], nprimes of them
 struct LdInvF64 {
@@ -1307,9 +1358,9 @@ struct LdInvTensor {
     }
     __device__ __forceinline__ double finish(const uint64_t *raw, int wg, int, const ModD m, const DevConst *) const
     {
-        // forward outputs are lazy: bring them to p/2 so that the two-term sum stays far below 2^53
-        double s = mulmod(red(bits_f64(raw[0]), m), red(bits_f64(raw[1]), m), m);
-        if (wg % 3 == 1) s += mulmod(red(bits_f64(raw[2]), m), red(bits_f64(raw[3]), m), m);
+        // forward outputs are lazy: with one factor brought to p/2 the two-term sum stays below 2^52
+        double s = mulmod(red(bits_f64(raw[0]), m), bits_f64(raw[1]), m);
+        if (wg % 3 == 1) s += mulmod(red(bits_f64(raw[2]), m), bits_f64(raw[3]), m);
         return s;
     }
 };
@@ -1337,10 +1388,13 @@ struct LdInvTensorSum {
     {
         return one.finish(raw, wg, idx, m, C);     // only wg % 3 matters there
     }
-    // a unit's term is below 1.2 p (two products of operands reduced to p/2)
+    // a unit's term is below 4 p
     __device__ __forceinline__ double join(double sum, double term, const ModD m) const { return red(sum, m) + term; }
 };
 template <> struct ld_rounds<LdInvTensorSum> { static constexpr bool value = true; };
+// (N = 4096's transforms end lower than those of 8192)
+template <> struct ld_in<LdInvTensor> { static constexpr int value = hundredths(2.0 * prod_of(fwd_out<13>())); };
+template <> struct ld_in<LdInvTensorSum> { static constexpr int value = hundredths(0.51 + 2.0 * prod_of(fwd_out<13>())); };
 template <> struct ld_no_16384<LdInvTensor> { static constexpr bool value = true; };
 template <> struct ld_no_16384<LdInvTensorSum> { static constexpr bool value = true; };
 
@@ -1404,17 +1458,30 @@ template <> struct ld_rounds<LdInvPlainSum> { static constexpr bool value = true
 struct StInvF64 {
     double *dst;
     int logn;
-    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD, const DevConst *) const
+    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD) const
     {
         put32(dst + ((size_t)wg << logn), idx, v);
     }
+    // element `at` + `lane` of the row, `at` uniform
+    __device__ __forceinline__ void store_lane(int wg, int at, int lane, double v, const ModD) const
+    {
+        put_lane(dst + ((size_t)wg << logn) + at, lane, v);
+    }
 };
+// rows of a tensor product without N^-1.  HALF: half rows, whose sums and differences the scaling takes.  (scale_kernel adds a reduced
+// value to a result, or to such a sum: below 2^53 together.)
+template <bool HALF> struct StTens : StInvF64 {};
+template <bool HALF> struct st_unscaled<StTens<HALF>> { static constexpr int value = HALF ? 365 : 730; };
 struct StInvU64 {
     uint64_t *dst;
     int logn;
-    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD m, const DevConst *) const
+    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD m) const
     {
         put32(dst + ((size_t)wg << logn), idx, f64_to_u64(canon(v, m)));
+    }
+    __device__ __forceinline__ void store_lane(int wg, int at, int lane, double v, const ModD m) const
+    {
+        put_lane(dst + ((size_t)wg << logn) + at, lane, f64_to_u64(canon(v, m)));
     }
     __device__ __forceinline__ const StInvU64 &at_row(int, int) const { return *this; }
 };
@@ -1435,9 +1502,10 @@ struct StAppendRow {        // for one row
             for (int c = 0; c < 8; c++) old[c] = at_lane(row + (c0 + c) * T, tid);
         }
     }
-    __device__ __forceinline__ void store(int, int idx, double v, uint64_t old, const ModD m, const DevConst *) const
+    // (v is below 2 p and old below p: one reduction of the sum)
+    __device__ __forceinline__ void store(int at, int lane, double v, uint64_t old, const ModD m) const
     {
-        put32(row, idx, f64_to_u64(addmod_canon(canon(v, m), u64_to_f64(old), m)));
+        put_lane(row + at, lane, f64_to_u64(canon(v + u64_to_f64(old), m)));
     }
 };
 struct StInvAppend {
@@ -1478,9 +1546,9 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
     if (NP > 4) ahead();
     if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
 }
-// in: chunk_elem order, |x| < 8p; results leave through st as row `row`
+// in: chunk_elem order, |x| < 8p (or the bound IN in hundredths); results leave through st as row `row`
 // U: rows together as in fwd_row, results as rows `row` + u * row_step
-template <int LOGN, int E, bool PRIO = false, int U = 1, class ST>
+template <int LOGN, int E, bool PRIO = false, int IN = 0, int U = 1, class ST>
 __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
                                         const double *__restrict__ itw, const ModD m, int pr, const DevConst *C,
                                         int row_step = 0)
@@ -1495,16 +1563,16 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
             pair_at(lds, it / E * lds_doubles<LOGN>() + pad(chunk_elem<E>(tid, it % E))) = make_double2(in[it], in[it + 1]);
         wave_sync();
     }
-    inv_pass<LOGN, E, NP - 1, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO, row_step);
+    inv_pass<LOGN, E, NP - 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO, row_step);
     if constexpr (NP > 4) {
-        inv_pass<LOGN, E, 3, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 2, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 1, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 0, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 3, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
     } else {
-        inv_pass<LOGN, E, 2, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 1, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 0, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
     }
 }
 
@@ -1844,19 +1912,19 @@ __device__ __forceinline__ void lift_row(double *x, const uint64_t *src, int r, 
 // 161 + 501 us for lift_kernel and this.
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, const double *__restrict__ itw_all,
+mul_row_kernel(MulRowArgs A, StTens<K == 0> st, const double *__restrict__ tw_all, const double *__restrict__ itw_all,
                const DevConst *__restrict__ C, int nwg)
 {
     constexpr int T = (1 << LOGN) / E;
     // half rows: priorities take 96 products from 1238 to 1224 us, 5 from 115.3 to 113.4; whole rows: no difference
     constexpr bool PRIO = K == 0;
+    constexpr double ONE = prod_of(fwd_out<LOGN>());        // bound of a product
     const int KL = K ? 2 * K + 1 : A.k;
     __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
         const int wg = xcd_row(p, nwg, KL), r = wg % KL, u = wg / KL;
         const ModD m = C->mod[K ? r : r >> 1];
-        const int pr = K ? r : MAXPR + r;
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         auto load = [&](double *x, const uint64_t *p0, const uint64_t *p1) {
             if constexpr (K == 0) {
@@ -1892,14 +1960,13 @@ mul_row_kernel(MulRowArgs A, StInvF64 st, const double *__restrict__ tw_all, con
         }
 #pragma unroll
         for (int it = 0; it < E; it++) {
-            const double b0 = red(y[it], m), b1 = red(y[E + it], m);
-            e[it] = mulmod(x[it], b0, m);
-            e[E + it] = mulmod(x[it], b1, m) + mulmod(x[E + it], b0, m);
-            z[it] = mulmod(x[E + it], b1, m);
+            e[it] = mulmod(x[it], y[it], m);
+            e[E + it] = mulmod(x[it], y[E + it], m) + mulmod(x[E + it], y[it], m);
+            z[it] = mulmod(x[E + it], y[E + it], m);
         }
-        inv_row<LOGN, E, PRIO, 2>(lds, e, st, (u * 3) * KL + r, tid, itw, m, pr, C, KL);
+        inv_row<LOGN, E, PRIO, hundredths(2.0 * ONE), 2>(lds, e, st, (u * 3) * KL + r, tid, itw, m, 0, C, KL);
         lds_barrier();
-        inv_row<LOGN, E, PRIO>(lds, z, st, (u * 3 + 2) * KL + r, tid, itw, m, pr, C);
+        inv_row<LOGN, E, PRIO, hundredths(ONE)>(lds, z, st, (u * 3 + 2) * KL + r, tid, itw, m, 0, C);
     }
 }
 
@@ -1944,7 +2011,7 @@ __device__ __forceinline__ void lift_window(double *x, const uint64_t *src, int 
 // memory none (mul_sum_parts_half has both sides).
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double *__restrict__ tw_all,
+mul_sum_row_kernel(MulRowArgs A, int group, int parts, StTens<K == 0> st, const double *__restrict__ tw_all,
                    const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
     constexpr int T = (1 << LOGN) / E, W = K == 1 ? 8 : K == 2 ? 4 : 3;
@@ -1959,7 +2026,6 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
         const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
         const int u_first = g * group + part * group / parts, u_end = g * group + (part + 1) * group / parts;
         const ModD m = C->mod[K ? r : r >> 1];
-        const int pr = K ? r : MAXPR + r;
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         // the first component's sum: pair q of a thread at far[q * T + tid]
         cg_double2v *far = reinterpret_cast<cg_double2v *>(st.dst + ((size_t)(gp * 3 * KL + r) << LOGN));
@@ -1971,7 +2037,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
         auto poly = [&](int u, int t) {
             return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
         };
-        // the first component's sum before unit u, and put back with a pair of that unit's products (below 1.2 p)
+        // the first component's sum before unit u, and put back with a pair of that unit's products (below 2 p)
         auto far_put = [&](const cg_double2v s, double a, double b, int q, int tk) {
             put32(far + q * T, tk, cg_double2v{red(s.x + a, m), red(s.y + b, m)});
         };
@@ -2008,7 +2074,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     if (FAR && t == 0) far_get(s0, u, tk);
 #pragma unroll
                     for (int it = 0; it < E; it++) {
-                        const double b0 = red(at32(y0, chunk_elem<E>(tk, it)), m), b1 = red(at32(y1, chunk_elem<E>(tk, it)), m);
+                        const double b0 = at32(y0, chunk_elem<E>(tk, it)), b1 = at32(y1, chunk_elem<E>(tk, it));
                         x[it] = red(x[it], m);
                         if (t == 0) {
                             d1[it] += mulmod(x[it], b1, m);
@@ -2035,7 +2101,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
                     if (FAR && t == 1) far_get(s0, u, tk);
 #pragma unroll
                     for (int it = 0; it < E; it++) {
-                        x[it] = red(x[it], m);
+                        if (t % 2 == 0) x[it] = red(x[it], m);      // (one factor of every product)
                         if (t == 0) park[tid + it * T] = x[it];
                         if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
                         if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
@@ -2070,7 +2136,7 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StInvF64 st, const double
             // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
             // registers before any thread stores results over it)
             lds_barrier();
-            inv_row<LOGN, E, PRIO>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, pr, C);
+            inv_row<LOGN, E, PRIO, 52>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, 0, C);
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 d0[it] = d1[it];
@@ -2106,6 +2172,7 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
 {
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr int T = (1 << LOGN) / E, NP = Plan<LOGN, E>::NP;
+    constexpr int IN = hundredths(prod_of(FwdBound<LOGN, E, NP - 1>::out));
     // the plaintext row and the next row are brought in ahead where there are registers for it
     constexpr bool PF = prefetch_rows<LOGN, E>();
     static_assert(NP == 4 || NP == 5, "pass sequence below");
@@ -2116,7 +2183,7 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
     int wg = blockIdx.x;
     auto fetch = [&](int w) {
 #pragma unroll
-        for (int it = 0; it < E; it++) raw[it] = src[((size_t)w << LOGN) + tid + it * T];
+        for (int it = 0; it < E; it++) raw[it] = at_lane(src + ((size_t)w << LOGN) + it * T, tid);
     };
     if constexpr (PF) fetch(wg);
     for (;;) {
@@ -2129,7 +2196,11 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
         load_tw<LOGN, E, 0, true>(tw, tid, twa);
         if constexpr (PF) {
 #pragma unroll
-            for (int it = 0; it < E; it++) pl[it] = prow[chunk_elem<E>(tid, it)];
+            for (int it = 0; it < E; it += 2) {
+                const cg_double2v w = at_lane(reinterpret_cast<const cg_double2v *>(prow) + 32 * it, chunk_elem<E>(tid, 0) / 2);
+                pl[it] = w.x;
+                pl[it + 1] = w.y;
+            }
         } else {
             fetch(wg);
         }
@@ -2144,25 +2215,25 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
         load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
         wave_sync();
         if constexpr (NP > 4) {
-            inv_pass<LOGN, E, 4>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
-            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+            inv_pass<LOGN, E, 4, IN>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+            inv_pass<LOGN, E, 3, IN>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
         } else {
-            inv_pass<LOGN, E, 3>(lds, str, wg, tid, itw, twa, twa, m, pr, C, nullptr, nullptr, PRIO);
+            inv_pass<LOGN, E, 3, IN>(lds, str, wg, tid, itw, twa, twa, m, pr, C, nullptr, nullptr, PRIO);
         }
-        inv_pass<LOGN, E, 2>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 2, IN>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO);
         // What the storer adds to is asked for late: loads return in order, so ahead of the passes' factors it would hold
         // these up (the factors of the last two passes are scalar loads).  24 caches of N = 8192: 2008 us before the
         // last pass but one, 1982 before the last; N = 16384: 2059 and 1892; twelve caches of N = 4096: 526 and 537.
         constexpr bool adds = st_adds<decltype(str)>::value, ahead = LOGN <= 12;
         uint64_t old[8];
         if constexpr (adds && ahead) str.template fetch<T>(old, tid, 0);
-        inv_pass<LOGN, E, 1>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
+        inv_pass<LOGN, E, 1, IN>(lds, str, wg, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO);
         const int next = wg + (int)gridDim.x;
         if constexpr (PF) {
             if (next < nwg) fetch(next);
         }
         if constexpr (adds && !ahead) str.template fetch<T>(old, tid, 0);
-        inv_pass<LOGN, E, 0>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, old, PRIO);
+        inv_pass<LOGN, E, 0, IN>(lds, str, wg, tid, itw, twa, twb, m, pr, C, nullptr, old, PRIO);
         if (next >= nwg) break;
         wg = next;
         lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes
@@ -2177,7 +2248,7 @@ constexpr int PW_THREADS = 256;
 // exact round(t e / Q) mod Q from e known modulo Q and the auxiliary basis:
 //   r = centred (t e mod Q);  y = (t e - r) / Q computed modulo each b_j;
 //   y is below B/2 in magnitude, so its centred lift from the auxiliary basis is exact.
-// tens[(b*parts+q)*3+c][r][n], summed over q (lazy, coefficient order) -> out[b][c][i][n] canonical uint64;
+// tens[(b*parts+q)*3+c][r][n], summed over q (lazy, coefficient order, without the inverse transforms' N^-1) -> out[b][c][i][n] canonical uint64;
 // acc != 0 adds the result to what out already holds (sum of products).
 // HALF: rows of two half rows whose last inverse stage is still to be taken: the workgroup's waves 0 and 1 take 128
 // coefficients of the first half, waves 2 and 3 those of the second that they pair with, and read the same lines.
@@ -2213,15 +2284,14 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int pa
 #pragma unroll
         for (int i = 0; i < K + L; i++) e[i] = mulmod(e[i], C->itw1[i], C->mod[i]);
     }
-    const double t = C->tmod;
     double x[K], dq[K], y[L], db[L];
 #pragma unroll
-    for (int i = 0; i < K; i++) x[i] = mulmod(e[i], t, C->mod[i]);
+    for (int i = 0; i < K; i++) x[i] = mulmod(e[i], C->t_ninv[i], C->mod[i]);
     garner_balanced<K>(C->q2b, C->mod, x, dq);
 #pragma unroll
     for (int j = 0; j < L; j++) {
         const ModD mb = C->mod[K + j];
-        const double te = mulmod(e[K + j], t, mb);
+        const double te = mulmod(e[K + j], C->t_ninv[K + j], mb);
         const double rj = horner<K>(C->q2b, mb, dq, j);
         y[j] = mulmod(te - rj, C->Qinv_b[j], mb);
     }
@@ -2539,7 +2609,7 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
                 if (DNUM > 1 && (q & 1)) asm volatile("" ::: "memory");      // two pairs' operands at a time: registers
             }
             lds_barrier();
-            inv_row<LOGN, E>(lds, y, StRegs{y}, 0, tid, itw, m, r, C);
+            inv_row<LOGN, E, false, 70 * DNUM>(lds, y, StRegs{y}, 0, tid, itw, m, r, C);
             asm volatile("" : "+v"(tk));
             if (!step) {
 #pragma unroll

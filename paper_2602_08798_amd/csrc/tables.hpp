@@ -27,11 +27,12 @@ struct DevConst {
     int np;   // distinct primes in mod[]: q_0..q_{k-1}, then the auxiliary basis
               // (special primes first, then private extra primes)
     ModD mod[MAXPR];
-    // the last inverse stage, N^-1 folded in, of rows [prime] and (from MAXPR on, N = 16384) of half rows [prime][half]
-    double ninv[3 * MAXPR];       // N^-1 mod prime (centred)
-    double itw1_ninv[3 * MAXPR];  // (first inverse twiddle) * N^-1 (centred)
+    // the last inverse stage, N^-1 folded in
+    double ninv[MAXPR];       // N^-1 mod prime (centred)
+    double itw1_ninv[MAXPR];  // (first inverse twiddle) * N^-1 (centred)
     double tw1[MAXPR], itw1[MAXPR];   // factor of the stage that joins two half rows, forward and inverse (centred)
     double tmod;              // plaintext modulus t
+    double t_ninv[MAXPR];     // t N^-1 mod prime (centred): the scaling's factor t, and the N^-1 that tensor products leave out
     double two50[MAXPR];      // 2^50 mod prime (centred)
     double two81[MAXPR];      // 2^81 mod prime (centred)
     ConvTab q2b;              // Q -> auxiliary basis, centred
