@@ -1548,10 +1548,11 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
 }
 // in: chunk_elem order, |x| < 8p (or the bound IN in hundredths); results leave through st as row `row`
 // U: rows together as in fwd_row, results as rows `row` + u * row_step
-template <int LOGN, int E, bool PRIO = false, int IN = 0, int U = 1, class ST>
+// ahead: run before the last two passes, whose factors are scalar loads: nothing in them waits behind the loads it asks for
+template <int LOGN, int E, bool PRIO = false, int IN = 0, int U = 1, class ST, class F = Nothing>
 __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
                                         const double *__restrict__ itw, const ModD m, int pr, const DevConst *C,
-                                        int row_step = 0)
+                                        int row_step = 0, F ahead = F())
 {
     constexpr int NP = Plan<LOGN, E>::NP;
     asm volatile("" : "+v"(tid));
@@ -1567,10 +1568,12 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
     if constexpr (NP > 4) {
         inv_pass<LOGN, E, 3, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
         inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        ahead();
         inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
         inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
     } else {
         inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        ahead();
         inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
         inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
     }
@@ -1591,7 +1594,7 @@ ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st
               const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C,
               int nwg)
 {
-    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
     constexpr int T = (1 << LOGN) / E;
     const int tid = threadIdx.x, L = C->L, dnum = C->dnum;
     int p = blockIdx.x;
@@ -1611,9 +1614,9 @@ ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st
         p += (int)gridDim.x;
         const bool more = p < nwg;
         const int wg_next = more ? xcd_row(p, nwg, L) : wg;
-        double s0[E], s1[E];
+        double s[2 * E];
 #pragma unroll
-        for (int it = 0; it < E; it++) s0[it] = s1[it] = 0.0;
+        for (int it = 0; it < 2 * E; it++) s[it] = 0.0;
         for (int j = 0; j < dnum; j++) {
             double x[E];
             const int row = (b * dnum + j) * L + r;
@@ -1637,14 +1640,12 @@ ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st
 #pragma unroll
             for (int it = 0; it < E; it++) {
                 const int idx = chunk_elem<E>(tk, it);
-                s0[it] += mulmod(x[it], at32(k0, idx), m);
-                s1[it] += mulmod(x[it], at32(k1, idx), m);
+                s[it] += mulmod(x[it], at32(k0, idx), m);
+                s[E + it] += mulmod(x[it], at32(k1, idx), m);
             }
             if (j + 1 < dnum) lds_barrier();
         }
-        inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
-        lds_barrier();
-        inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
+        inv_row<LOGN, E, false, 0, 2>(lds, s, st, (b * 2) * L + r, tid, itw, m, r, C, L);
         if (!more) break;
         wg = wg_next;
         lds_barrier();
@@ -1758,7 +1759,7 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 {
     static_assert(U == 1 || U == 2, "units of a workgroup");
     constexpr int TH = (1 << LOGN) / E, ROW = lds_doubles<LOGN>();
-    __shared__ __align__(16) double lds[U * ROW];
+    __shared__ __align__(16) double lds[2 * ROW];
     const int tid = threadIdx.x, L = C->L, dnum = C->dnum, sets = (batch + U - 1) / U;
     // logical order: prime, then unit; XCD x takes the x-th eighth of it, so that an XCD works with the keys
     // of one or two primes
@@ -1807,14 +1808,20 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
             else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1, s2, s3);
         }
         lds_barrier();
-        inv_row<LOGN, E>(lds, s0, st, (b * 2) * L + r, tid, itw, m, r, C);
-        lds_barrier();
-        inv_row<LOGN, E>(lds, s1, st, (b * 2 + 1) * L + r, tid, itw, m, r, C);
+        // both components of a unit
+        auto inverse = [&](const double *a, const double *c, int unit) {
+            double s[2 * E];
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                s[it] = a[it];
+                s[E + it] = c[it];
+            }
+            inv_row<LOGN, E, false, 0, 2>(lds, s, st, (unit * 2) * L + r, tid, itw, m, r, C, L);
+        };
+        inverse(s0, s1, b);
         if (U > 1 && b + 1 < batch) {
             lds_barrier();
-            inv_row<LOGN, E>(lds, s2, st, (b * 2 + 2) * L + r, tid, itw, m, r, C);
-            lds_barrier();
-            inv_row<LOGN, E>(lds, s3, st, (b * 2 + 3) * L + r, tid, itw, m, r, C);
+            inverse(s2, s3, b + 1);
         }
     }
 }
@@ -2687,7 +2694,7 @@ __global__ void __launch_bounds__((1 << LOGN) / E, (MODE == KS_ROTATE ? 4 : min_
 ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist H, double *scratch,
                const double *__restrict__ tw_all, const double *__restrict__ itw_all, const DevConst *__restrict__ C)
 {
-    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
     constexpr int TH = (1 << LOGN) / E, N = 1 << LOGN;
     constexpr bool GALOIS = MODE == KS_ROTATE;
     const int tid = threadIdx.x, k = C->k, L = C->L, dnum = C->dnum;
@@ -2706,9 +2713,9 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
             const int r = step ? step - 1 : k;
             const ModD m = C->mod[r];
             const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
-            double s[2][E];
+            double s[2 * E], y[2 * E];
 #pragma unroll
-            for (int it = 0; it < E; it++) s[0][it] = s[1][it] = 0.0;
+            for (int it = 0; it < 2 * E; it++) s[it] = 0.0;
             for (int j = 0; j < dnum; j++) {
                 double x[E];
                 const int row = (b * dnum + j) * L + r;
@@ -2725,7 +2732,7 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
 #pragma unroll
                         for (int it = 0; it < E; it++) x[it] = red(x[it], m);
                     }
-                    keys.add(x, m, s[0], s[1]);
+                    keys.add(x, m, s, s + E);
                     continue;
                 }
                 if constexpr (GALOIS) {
@@ -2745,46 +2752,64 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
 #pragma unroll
                     for (int it = 0; it < E; it++) {
                         const int idx = chunk_elem<E>(tk, it);
-                        s[0][it] += mulmod(x[it], at32(k0, idx), m);
-                        s[1][it] += mulmod(x[it], at32(k1, idx), m);
+                        s[it] += mulmod(x[it], at32(k0, idx), m);
+                        s[E + it] += mulmod(x[it], at32(k1, idx), m);
                     }
                 } else {
 #pragma unroll
                     for (int it = 0; it < E; it += 2)
                         pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
                     lds_barrier();
-                    sum_digit<LOGN, E>(lds, T, H.n_sum, j, r, L, tk, m, s[0], s[1]);
+                    sum_digit<LOGN, E>(lds, T, H.n_sum, j, r, L, tk, m, s, s + E);
                 }
             }
             const uint64_t *own_rows = (MODE == KS_ROTATE ? A.acc_add + (size_t)b * A.acc_stride
                                                           : A.add + (size_t)b * A.add_stride) + ((size_t)r << LOGN);
             const uint64_t *c0 = A.add + (size_t)b * A.add_stride + ((size_t)r << LOGN);
             uint64_t *out = A.out + (size_t)b * A.out_stride + ((size_t)r << LOGN);
+            const size_t comp = (size_t)k << LOGN;
+            const bool adds = MODE != KS_ROTATE || A.accumulate;
+            // residues modulo the special prime, addends
+            double xs[2 * E];
+            uint64_t own[E];
+#pragma unroll
+            for (int it = 0; it < E; it++) xs[it] = xs[E + it] = 0.0, own[it] = 0;
+            auto ask_own = [&](int c, int tk) {
+                if (adds) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) own[it] = at_lane(own_rows + c * comp + it * TH, tk);
+                }
+            };
+            auto ask_xs = [&](int c, int tk) {
+#pragma unroll
+                for (int it = 0; it < E; it++) xs[c * E + it] = at_lane(keep + ((size_t)c << LOGN) + it * TH, tk);
+            };
+            // (rotations have no registers for them before the transform is done)
+            auto ask = [&] {
+                if (!step || MODE == KS_ROTATE) return;
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                ask_xs(0, tk);
+                ask_xs(1, tk);
+                ask_own(0, tk);
+            };
+            if (MODE == KS_SUM) lds_barrier();
+            inv_row<LOGN, E, false, 0, 2>(lds, s, StRegs{y}, 0, tid, itw, m, r, C, 0, ask);
 #pragma unroll
             for (int c = 0; c < 2; c++) {
-                double xs[E];
-                uint64_t own[E];
-                const bool adds = MODE != KS_ROTATE || A.accumulate;
-                if (MODE == KS_SUM || c) lds_barrier();
-                inv_row<LOGN, E>(lds, s[c], StRegs{s[c]}, 0, tid, itw, m, r, C);
                 int tk = tid;
                 asm volatile("" : "+v"(tk));
                 if (!step) {        // centred residues modulo the special prime; every thread reads its own back
 #pragma unroll
-                    for (int it = 0; it < E; it++) put32(keep + ((size_t)c << LOGN) + it * TH, tk, red(s[c][it], m));
+                    for (int it = 0; it < E; it++) put_lane(keep + ((size_t)c << LOGN) + it * TH, tk, red(y[c * E + it], m));
                     continue;
                 }
-                // (asked for before the inverse transform they spill)
-#pragma unroll
-                for (int it = 0; it < E; it++) xs[it] = at_lane(keep + ((size_t)c << LOGN) + it * TH, tk);
-                const size_t crow = (size_t)(c * k) << LOGN;
-                if (adds) {
-#pragma unroll
-                    for (int it = 0; it < E; it++) own[it] = at_lane(own_rows + crow + it * TH, tk);
-                }
+                const size_t crow = c * comp;
+                if (MODE == KS_ROTATE) ask_xs(c, tk);
+                if (c || MODE == KS_ROTATE) ask_own(c, tk);
                 double v[E];
 #pragma unroll
-                for (int it = 0; it < E; it++) v[it] = mulmod(s[c][it] - xs[it], C->Pinv_q[r], m);
+                for (int it = 0; it < E; it++) v[it] = mulmod(y[c * E + it] - xs[c * E + it], C->Pinv_q[r], m);
                 if (MODE != KS_PLAIN && c == 0) {
                     uint64_t w[E];
                     if (MODE == KS_ROTATE) {
@@ -2813,7 +2838,7 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
 #pragma unroll
                 for (int it = 0; it < E; it++) {
                     if (adds) v[it] += u64_to_f64(own[it]);
-                    put32(out + crow + it * TH, tk, f64_to_u64(canon(v[it], m)));
+                    put_lane(out + crow + it * TH, tk, f64_to_u64(canon(v[it], m)));
                 }
             }
         }
