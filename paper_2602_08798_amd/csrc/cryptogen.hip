@@ -547,11 +547,52 @@ static unsigned ntt_grid(cg_ctx *c, size_t nwg, int threads)
 // elements per thread for this context's transforms
 static int ntt_elems(const cg_ctx *c) { return c->elems; }
 
+// Parts of a row in which a launch of `rows` rows is taken (ntt_fwd_part_kernel, ntt_inv_part_kernel), as a power of two: as many as
+// have a compute unit each, four at most, two in an inverse transform at N = 8192 and none at N = 4096.  us a launch, whole rows / parts.
+// Forward, N = 4096: 12 rows 6.0 / 5.5 (four), 100: 6.2 / 5.5 (two); N = 8192: 12 7.5 / 5.5, 64 7.8 / 5.6, 65 ... 128 rows 8.2 / 6.4 ... 8.4 / 6.9;
+// N = 16384: 12 11.8 / 6.4, 64 12.6 / 8.2, 128 13.8 / 11.0.  Inverse, N = 4096: 12 rows 6.0 / 6.6, 100: 6.0 / 5.7 (two); N = 8192: 12 7.7 / 6.0 (four:
+// 7.4), 64 8.1 / 6.5; N = 16384: 12 13.5 / 10.1, 64 14.5 / 11.3 (four), 100 15.1 / 12.2 (two).  Inverse transforms only up to a third of
+// the compute units at N = 8192 and a quarter at N = 16384: they are the summed rotations' of a step, whose other branches the work
+// done twice holds up (12 heads, 96 rows: 420.3 us a step whole, 423.5 in parts; alone 8.3 / 7.1 a launch).
+static int row_parts(const cg_ctx *c, size_t rows, bool inverse)
+{
+    const size_t n = (size_t)c->n_cu;
+    if (c->dry) return 0;
+    if (inverse) return c->logn == 13 && 3 * rows <= n ? 1 : c->logn == 14 && 4 * rows <= n ? 2 : 0;
+    return 4 * rows <= n ? 2 : 2 * rows <= n ? 1 : 0;
+}
+// two device ranges share at least one byte
+static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
+static bool overlap(const void *a, const void *b, size_t bytes) { return overlap(a, bytes, b, bytes); }
+// The parts of a row read all of it, each in its own time: not where the results land on the rows that are read.
+template <class LD, class ST> static bool apart(const LD &, const ST &, size_t) { return true; }
+static bool apart(const LdRowsU64 &ld, const StU64 &st, size_t bytes) { return !overlap(ld.src, st.base, bytes); }
+static bool apart(const LdInvU64 &ld, const StInvU64 &st, size_t bytes) { return !overlap(ld.src, st.dst, bytes); }
+static bool apart(const LdInvF64 &ld, const StInvF64 &st, size_t bytes) { return !overlap(ld.src, st.dst, bytes); }
+#define CG_PART(KERNEL, LG, LS, TW)                                                                            \
+    return launch_kernel(KERNEL<LG, LS, LD, ST>, dim3((unsigned)nwg << LS), dim3(1u << (LG - LS - 3)), s, ld, st, \
+                         (const double *)TW, (const DevConst *)c->dc, (int)nwg)
+
 template <class LD, class ST>
 static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes)
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
+    if constexpr (in_parts<LD, ST>::value) {
+        switch (c->logn * 10 + (apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, false) : 0)) {
+        case 121: CG_PART(ntt_fwd_part_kernel, 12, 1, c->tw);
+        case 122: CG_PART(ntt_fwd_part_kernel, 12, 2, c->tw);
+        case 131: CG_PART(ntt_fwd_part_kernel, 13, 1, c->tw);
+        case 132: CG_PART(ntt_fwd_part_kernel, 13, 2, c->tw);
+        case 141: CG_PART(ntt_fwd_part_kernel, 14, 1, c->tw);
+        case 142: CG_PART(ntt_fwd_part_kernel, 14, 2, c->tw);
+        default: break;
+        }
+    }
     // N = 8192: a launch with no more rows than compute units finishes a row sooner on 1024 threads
     const int e = (c->logn == 13 && !fwd_many<LD>::value && nwg <= (size_t)c->n_cu) ? c->elems : c->elems_fwd;
     const int threads = c->N / e;
@@ -580,6 +621,13 @@ static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
+    if constexpr (in_parts<LD, ST>::value) {
+        switch (c->logn * 10 + (apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, true) : 0)) {
+        case 131: CG_PART(ntt_inv_part_kernel, 13, 1, c->itw);
+        case 142: CG_PART(ntt_inv_part_kernel, 14, 2, c->itw);
+        default: break;
+        }
+    }
     // N = 8192, as forward: no more rows than compute units, and a row is done sooner on 1024 threads (product and
     // relinearisation: 1 unit 52.4 -> 48.6 us, 8 units 62.0 -> 58.5).  In a step, beside other branches, heads x ciphertexts: chains
     // 2 x 2 306 -> 298, 6 x 2 351 -> 337, 4 x 3 346 -> 332, 6 x 1 317 -> 320 (30 shapes of up to 12 products: -1.7 % on average); in rounds
@@ -1144,6 +1192,13 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     return CG_OK;
 }
 
+static uint32_t inv_mod_pow2(uint32_t g, uint32_t two_n)
+{
+    uint32_t x = g;   // Newton iteration: correct to 3 bits, doubles each step
+    for (int i = 0; i < 5; i++) x *= 2 - g * x;
+    return x & (two_n - 1);
+}
+
 // Mod-up of one ring element per unit (src + b*src_stride, Galois map first when galois != 0): the
 // dnum digits extended to the k+nsp primes and transformed, rows dig[b][dnum][k+nsp][N], canonical
 static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
@@ -1152,7 +1207,7 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     const size_t nrows = (size_t)batch * c->dnum * c->L;
     const double mbytes = (double)limb_bytes(c) * (c->k + (double)c->dnum * c->L) * batch;
     const StU64 st{dig, c->logn};
-#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn}, st, KID_FWD_MODUP, mbytes)
+#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes)
     switch (c->alpha * 2 + (galois ? 1 : 0)) {
     case 2: CG_MODUP(false, 1);
     case 3: CG_MODUP(true, 1);
@@ -1237,13 +1292,6 @@ static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *r
     const size_t ct3 = (size_t)3 * c->k * c->N;
     return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
                         (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws);
-}
-
-static uint32_t inv_mod_pow2(uint32_t g, uint32_t two_n)
-{
-    uint32_t x = g;   // Newton iteration: correct to 3 bits, doubles each step
-    for (int i = 0; i < 5; i++) x *= 2 - g * x;
-    return x & (two_n - 1);
 }
 
 // in_stride / out_stride: uint64 between consecutive units (0 = densely packed ciphertexts)
@@ -1386,8 +1434,11 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
         const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
         CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
         const size_t irows = (size_t)batch * 2 * c->L;
-        CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64,
+        // few rows are transformed in parts, and so not in place: two digits' rows have room for the results
+        double *to = c->dnum >= 2 && row_parts(c, irows, true) ? reinterpret_cast<double *>(dig) : acc;
+        CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{to, c->logn}, KID_INV_F64,
                           LB * 2.0 * irows));
+        A.acc = to;
     }
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
     return launch_moddown_sum(c, s, LB * (2.0 * c->L + 4.0 * c->k) * B, batch, A, H);
@@ -1415,13 +1466,6 @@ static bool ptrs_ok(std::initializer_list<const void *> ps)
     for (const void *p : ps) if (!p || !aligned16(p)) return false;
     return true;
 }
-// two device ranges share at least one byte
-static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
-{
-    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return x < y + b_bytes && y < x + a_bytes;
-}
-static bool overlap(const void *a, const void *b, size_t bytes) { return overlap(a, bytes, b, bytes); }
 static bool batch_ok(uint32_t batch) { return batch >= 1 && batch <= (1u << 16); }
 static bool galois_ok(const cg_ctx *c, uint32_t g) { return (g & 1) && g > 0 && g < 2u * c->N; }
 

@@ -23,6 +23,8 @@ namespace cg {
 // ---------------------------------------------------------------------------
 template <int LOGN, int E> struct Plan;
 template <> struct Plan<14, 16> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {4, 4, 3, 3, 0}; };
+template <> struct Plan<10, 8> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {3, 3, 3, 1, 0}; };      // (parts of rows)
+template <> struct Plan<11, 8> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {3, 3, 3, 2, 0}; };
 template <> struct Plan<12, 8> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {3, 3, 3, 3, 0}; };
 template <> struct Plan<13, 8> { static constexpr int NP = 5, NC = 2; static constexpr int R[5] = {3, 3, 3, 3, 1}; };
 template <> struct Plan<13, 16> { static constexpr int NP = 4, NC = 1; static constexpr int R[5] = {4, 3, 3, 3, 0}; };
@@ -93,15 +95,16 @@ constexpr double fwd_grow(double b, int stages)
 // of the lazy operand whatever the prime, so they hold for primes of different sizes too.)
 constexpr double FWD_IN = 1.25;      // what loaders deliver
 constexpr double LAZY_MAX = 7.9;     // values must stay below 2^53
-template <int LOGN, int E, int PASS> struct FwdBound {
-    static constexpr double in = FwdBound<LOGN, E, PASS - 1>::out;
+// IN: bound of the transform's input, in hundredths
+template <int LOGN, int E, int PASS, int IN = (int)(100 * FWD_IN)> struct FwdBound {
+    static constexpr double in = FwdBound<LOGN, E, PASS - 1, IN>::out;
     static constexpr bool reduce = fwd_grow(in, Plan<LOGN, E>::R[PASS]) > LAZY_MAX;
     static constexpr double out = reduce ? fwd_grow(1.01 + 0.1875 * in, Plan<LOGN, E>::R[PASS] - 1)
                                          : fwd_grow(in, Plan<LOGN, E>::R[PASS]);
 };
-template <int LOGN, int E> struct FwdBound<LOGN, E, 0> {
+template <int LOGN, int E, int IN> struct FwdBound<LOGN, E, 0, IN> {
     static constexpr bool reduce = false;
-    static constexpr double out = fwd_grow(FWD_IN, Plan<LOGN, E>::R[0]);
+    static constexpr double out = fwd_grow(0.01 * IN, Plan<LOGN, E>::R[0]);
 };
 
 // Inverse passes: a sum is as large as its operands together, a product (a - b) w at most
@@ -164,18 +167,18 @@ template <int LOGN, int E, int PASS, int IN, bool FIRST = PASS == Plan<LOGN, E>:
 template <int LOGN, int E, int PASS, int IN> struct InvBound<LOGN, E, PASS, IN, true> {
     static constexpr double in = IN ? 0.01 * IN : 0.51;
 };
-// Products of transformed rows: the first factor reduced, the second as a forward transform (of whatever width) leaves it
+// Products of transformed rows: the first factor reduced, the second as a forward transform (of whatever width, in parts or not) leaves it
+constexpr int hundredths(double x) { return (int)(100.0 * x) + 1; }
+template <int LOGN, int E, int IN> constexpr double fwd_end() { return FwdBound<LOGN, E, Plan<LOGN, E>::NP - 1, IN>::out; }
 template <int LOGN> constexpr double fwd_out()
 {
-    const double a = FwdBound<LOGN, 8, Plan<LOGN, 8>::NP - 1>::out;
-    if constexpr (LOGN == 13) {
-        const double b = FwdBound<LOGN, 16, Plan<LOGN, 16>::NP - 1>::out;
-        return a > b ? a : b;
-    }
-    return a;
+    constexpr int in = (int)(100 * FWD_IN), in1 = hundredths(fwd_grow(FWD_IN, 1)), in2 = hundredths(fwd_grow(FWD_IN, 2));
+    const double ends[] = {fwd_end<LOGN, 8, in>(), fwd_end<LOGN, LOGN == 13 ? 16 : 8, in>(), fwd_end<LOGN - 1, 8, in1>(), fwd_end<LOGN - 2, 8, in2>()};
+    double most = 0.0;
+    for (double e : ends) most = e > most ? e : most;
+    return most;
 }
 constexpr double prod_of(double lazy) { return 0.5 + 0.375 * 0.51 * lazy; }
-constexpr int hundredths(double x) { return (int)(100.0 * x) + 1; }
 
 __device__ __forceinline__ void bfly_fwd(double &a, double &b, double w, const ModD m)
 {
@@ -265,8 +268,9 @@ template <class T> __device__ __forceinline__ const T *opaque_const(const T *p)
     return (const T *)g;
 }
 
+// root: the sub-transform at node `root` of the forward transform's tree (1: a whole row)
 template <int LOGN, int E, int PASS, bool HI_ZERO>
-__device__ __forceinline__ void load_tw(const double *__restrict__ tw, int tid, double *twr)
+__device__ __forceinline__ void load_tw(const double *__restrict__ tw, int tid, double *twr, int root = 1)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -285,7 +289,7 @@ __device__ __forceinline__ void load_tw(const double *__restrict__ tw, int tid, 
         for (int u = 0; u < R; u++)
 #pragma unroll
             for (int j = 0; j < (1 << u); j++)
-                twr[g * PER + (1 << u) - 1 + j] = at32(tw + (1 << (S0 + u)) + j, hi << u);
+                twr[g * PER + (1 << u) - 1 + j] = at32(tw + (root << (S0 + u)) + j, hi << u);
     }
 }
 
@@ -445,10 +449,10 @@ template <> struct st_regs<StRegs> { static constexpr bool value = true; };
 // one library do (12 x 4 in rounds 449 / 449 us, chains 674 / 674; 16 x 3 at N = 16384 1890 / 1902, chains 3219 / 3234).
 // U: rows of one prime taken through the pass together, row u in in[u E ...] or u * lds_doubles() further on in LDS.  They share the
 // pass's factors and its barrier.
-template <int LOGN, int E, int PASS, bool FROM_REGS, int U = 1, class ST>
+template <int LOGN, int E, int PASS, bool FROM_REGS, int U = 1, int IN = (int)(100 * FWD_IN), class ST>
 __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST &st, int tid,
                                          const double *__restrict__ tw, const double *twr, double *twr_next,
-                                         const ModD m, int dst_limb, bool prio = false)
+                                         const ModD m, int dst_limb, bool prio = false, int root = 1)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -458,8 +462,8 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
     constexpr int PER = (1 << R) - 1;
     constexpr bool first = PASS == 0, last = PASS == P::NP - 1;
     constexpr bool cross = PASS < P::NC;      // pairs elements owned by different waves
-    constexpr bool do_red = FwdBound<LOGN, E, PASS>::reduce;
-    static_assert(FwdBound<LOGN, E, PASS>::out < 8.0, "lazy bound exceeds 2^53");
+    constexpr bool do_red = FwdBound<LOGN, E, PASS, IN>::reduce;
+    static_assert(FwdBound<LOGN, E, PASS, IN>::out < 8.0, "lazy bound exceeds 2^53");
     static_assert(!FROM_REGS || (first && L + R == LOGN), "register input only for the first pass");
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     static_assert(!last || !cross, "the last pass must be wave-local (chunk-wise copy-out)");
@@ -523,7 +527,7 @@ __device__ __forceinline__ void fwd_pass(double *lds, const double *in, const ST
     }
     // fetch the next pass's factors while this pass's results drain to LDS
     if constexpr (U > 1) __builtin_amdgcn_sched_barrier(0);     // (sooner they take registers that two rows need)
-    if constexpr (!last) load_tw<LOGN, E, PASS + 1, false>(tw, tid, twr_next);
+    if constexpr (!last) load_tw<LOGN, E, PASS + 1, false>(tw, tid, twr_next, root);
 #pragma unroll
     for (int w = 0; w < U; w++)
 #pragma unroll
@@ -1144,6 +1148,9 @@ struct LdModup {
     size_t unit_stride;      // in uint64
     uint32_t galois;
     int logn;
+    uint32_t ginv;           // galois^-1 mod 2N (for parts of rows)
+    // the element that lands at place(idx) = pos
+    __device__ __forceinline__ int source_of(int pos, int n) const { return (int)(((uint32_t)pos * ginv) & (n - 1u)); }
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % C->L; }
     __device__ __forceinline__ int share(const DevConst *C) const { return C->L; }
     __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const { return wg; }
@@ -1401,7 +1408,7 @@ struct LdInvTensorSum {
     __device__ __forceinline__ double join(double sum, double term, const ModD m) const { return red(sum, m) + term; }
 };
 template <> struct ld_rounds<LdInvTensorSum> { static constexpr bool value = true; };
-// (N = 4096's transforms end lower than those of 8192)
+static_assert(fwd_out<12>() <= fwd_out<13>(), "the bound of both");
 template <> struct ld_tens<LdInvTensor> { static constexpr bool value = true; };
 template <> struct ld_tens<LdInvTensorSum> { static constexpr bool value = true; };
 template <> struct ld_in<LdInvTensor> { static constexpr int value = hundredths(2.0 * prod_of(fwd_out<13>())); };
@@ -2257,6 +2264,145 @@ ntt_mulplain_kernel(const uint64_t *__restrict__ src, const double *__restrict__
         lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes
     }
 }
+
+// ---------------------------------------------------------------------------
+// Rows in parts, for launches of few rows: a row of 8192 keeps the four SIMDs of a compute unit busy for 4.6 us while most of the chip
+// idles.  2^LS workgroups share a row without exchanging anything: of a forward transform part h computes the outputs whose highest index
+// bits are h, of an inverse one those whose lowest bits are h, from the first LS stages taken in registers, which every part does for itself
+// (at most three products per element), and a transform of N / 2^LS.  The inverse transform's results land 2^LS words apart.
+// One product with relinearisation at N = 8192 48.5 -> 44.9 us, at N = 16384 99.9 -> 89.7, a step of one head 171 -> 152 to 167.
+// ---------------------------------------------------------------------------
+template <class LD, class ST> struct in_parts { static constexpr bool value = false; };
+template <class ST> struct StPart {        // forward: the row's part from `at` on
+    ST st;
+    int at;
+    __device__ __forceinline__ void store(int limb, int idx, double v, const ModD m) const { st.store(limb, at + idx, v, m); }
+};
+template <int LS, class ST> struct StEvery {        // inverse: every 2^LS-th element from `at` on
+    ST st;
+    int at;
+    __device__ __forceinline__ void store(int wg, int idx, double v, const ModD m) const { st.store(wg, (idx << LS) + at, v, m); }
+    __device__ __forceinline__ void store_lane(int wg, int idx, int lane, double v, const ModD m) const
+    {
+        st.store_lane(wg, (idx << LS) + at, lane << LS, v, m);
+    }
+};
+
+template <int LOGN, int LS, class LD, class ST>
+__global__ void __launch_bounds__(1 << (LOGN - LS - 3))
+ntt_fwd_part_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int SUB = LOGN - LS, E = 8, T = (1 << SUB) / E, NP = Plan<SUB, E>::NP, PARTS = 1 << LS;
+    constexpr int IN = hundredths(fwd_grow(FWD_IN, LS));
+    static_assert(LS == 1 || LS == 2, "two or four parts");
+    __shared__ __align__(16) double lds[lds_doubles<SUB>()];
+    const int tid = threadIdx.x;
+    // the parts of a row are neighbours on one XCD
+    const int q0 = xcd_row((int)blockIdx.x, nwg << LS, PARTS), wg = q0 >> LS, h = q0 & (PARTS - 1), root = PARTS + h;
+    const int pr = ld.prime(wg, C);
+    const ModD m = C->mod[pr];
+    const double *tw = tw_all + ((size_t)pr << LOGN);
+    const int dl = ld.dst_limb(wg, C);
+    // factors of the first stages, with the sign of this part's outputs
+    const double w0 = (h >> (LS - 1)) ? -tw[1] : tw[1], w1 = LS < 2 ? 0.0 : (h & 1) ? -tw[2 + (h >> 1)] : tw[2 + (h >> 1)];
+    double in[E], twa[TWREGS], twb[TWREGS];
+    auto first = [&](int it, const double *x) {
+        if (LS == 1) in[it] = x[0] + mulmod(x[1], w0, m);
+        else in[it] = x[0] + mulmod(x[PARTS / 2], w0, m) + mulmod(x[1] + mulmod(x[PARTS - 1], w0, m), w1, m);
+    };
+    uint64_t raw[E][PARTS][LD::kRaw];
+    auto at = [&](int it, int q) {
+        const int pos = tid + it * T + (q << SUB);
+        if constexpr (LD::kScatter) return ld.source_of(pos, 1 << LOGN);
+        else return pos;
+    };
+#pragma unroll
+    for (int it = 0; it < E; it++)
+#pragma unroll
+        for (int q = 0; q < PARTS; q++) ld.fetch(wg, at(it, q), C, raw[it][q]);
+#pragma unroll
+    for (int it = 0; it < E; it++) {
+        double x[PARTS];
+#pragma unroll
+        for (int q = 0; q < PARTS; q++) x[q] = ld.finish(raw[it][q], wg, at(it, q), m, C);
+        first(it, x);
+    }
+    const StPart<ST> part{st, h << SUB};
+    load_tw<SUB, E, 0, true>(tw, tid, twa, root);
+    fwd_pass<SUB, E, 0, true, 1, IN>(lds, in, part, tid, tw, twa, twb, m, dl, false, root);
+    fwd_pass<SUB, E, 1, false, 1, IN>(lds, in, part, tid, tw, twb, twa, m, dl, false, root);
+    fwd_pass<SUB, E, 2, false, 1, IN>(lds, in, part, tid, tw, twa, twb, m, dl, false, root);
+    fwd_pass<SUB, E, 3, false, 1, IN>(lds, in, part, tid, tw, twb, twa, m, dl, false, root);
+    if constexpr (NP > 4) fwd_pass<SUB, E, 4, false, 1, IN>(lds, in, part, tid, tw, twa, twb, m, dl, false, root);
+}
+
+template <int LOGN, int LS, class LD, class ST>
+__global__ void __launch_bounds__(1 << (LOGN - LS - 3))
+ntt_inv_part_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int SUB = LOGN - LS, E = 8, NP = Plan<SUB, E>::NP, PARTS = 1 << LS, N = 1 << LOGN;
+    constexpr int IN = hundredths(0.51 * PARTS);       // (a product of sums is smaller)
+    static_assert(LS == 1 || LS == 2, "two or four parts");
+    __shared__ __align__(16) double lds[lds_doubles<SUB>()];
+    const int tid = threadIdx.x;
+    const int q0 = xcd_row((int)blockIdx.x, nwg << LS, PARTS), wg = q0 >> LS, h = q0 & (PARTS - 1);
+    const int pr = ld.prime(wg, C), orow = __builtin_amdgcn_readfirstlane(ld.out_row(wg, C));
+    const ModD m = C->mod[pr];
+    const double *itw = itw_all + ((size_t)pr << LOGN);
+    const bool low = h & 1, high = LS > 1 && (h & 2);
+    double twa[TWREGS], twb[TWREGS];
+    load_tw<SUB, E, NP - 1, false>(itw, tid, twa);
+    // the first stages' factors, asked for before anything waits
+    double f[E][3];
+#pragma unroll
+    for (int it = 0; it < E; it++) {
+        const int j = chunk_elem<E>(tid, it);
+        f[it][0] = at32(itw + N / 2, (PARTS / 2) * j);
+        f[it][1] = LS > 1 ? at32(itw + N / 2 + 1, 2 * j) : 0.0;
+        f[it][2] = LS > 1 ? at32(itw + N / 4, j) : 0.0;
+    }
+    auto first = [&](int it, const double *x) {
+        double a = low ? mulmod(x[0] - x[1], f[it][0], m) : x[0] + x[1];
+        if (LS == 1) return a;
+        double b = low ? mulmod(x[PARTS - 2] - x[PARTS - 1], f[it][1], m) : x[PARTS - 2] + x[PARTS - 1];
+        return high ? mulmod(a - b, f[it][2], m) : a + b;
+    };
+    uint64_t raw[E][PARTS][LD::kRaw];
+#pragma unroll
+    for (int it = 0; it < E; it++)
+#pragma unroll
+        for (int q = 0; q < PARTS; q++) ld.fetch(wg, (chunk_elem<E>(tid, it) << LS) + q, C, raw[it][q]);
+    double y[E];
+#pragma unroll
+    for (int it = 0; it < E; it++) {
+        double x[PARTS];
+#pragma unroll
+        for (int q = 0; q < PARTS; q++) x[q] = red(ld.finish(raw[it][q], wg, (chunk_elem<E>(tid, it) << LS) + q, m, C), m);
+        y[it] = first(it, x);
+    }
+#pragma unroll
+    for (int it = 0; it < E; it += 2) pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(y[it], y[it + 1]);
+    wave_sync();
+    const StEvery<LS, ST> every{st, h};
+    if constexpr (NP > 4) {
+        inv_pass<SUB, E, 4, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+        inv_pass<SUB, E, 3, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
+        inv_pass<SUB, E, 2, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+        inv_pass<SUB, E, 1, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
+        inv_pass<SUB, E, 0, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+    } else {
+        inv_pass<SUB, E, 3, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+        inv_pass<SUB, E, 2, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
+        inv_pass<SUB, E, 1, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+        inv_pass<SUB, E, 0, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
+    }
+}
+// Loaders that bring in a word or two per element.  Those that work for an element (lifts, tensor and inner products) would do so 2^LS
+// times: one product at N = 8192, four parts, operands 13.7 -> 13.1 us, tensor product 12.6 -> 15.3, inner product 11.1 -> 12.9.
+template <> struct in_parts<LdRowsU64, StU64> { static constexpr bool value = true; };
+template <bool G, int A> struct in_parts<LdModup<G, A>, StU64> { static constexpr bool value = true; };
+template <> struct in_parts<LdInvU64, StInvU64> { static constexpr bool value = true; };
+template <> struct in_parts<LdInvF64, StInvF64> { static constexpr bool value = true; };
 
 // ---------------------------------------------------------------------------
 // pointwise kernels

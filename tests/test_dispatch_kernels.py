@@ -29,6 +29,17 @@ WANT = {
     **{("n4096_k2", "sum", b): "ks_sum_row_kernel<12, 8, 1>" for b in (64, 200, 400)},
     # the tensor product of no more rows than compute units on 1024 threads
     ("n8192_k3", "mul", 12): TENSOR.format(8), ("n8192_k3", "mul", 13): TENSOR.format(16),
+    # transforms: rows in four parts up to a quarter of the compute units, in two up to half; inverse at N = 8192 in two up to a
+    # third, at N = 16384 in four up to a quarter
+    **{("n8192_k3", "fwd", r): f"ntt_fwd_part_kernel<13, {p}, LdRowsU64, StU64>" for r, p in ((1, 2), (64, 2), (65, 1), (128, 1))},
+    ("n8192_k3", "fwd", 129): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
+    **{("n8192_k3", "inv", r): "ntt_inv_part_kernel<13, 1, LdInvU64, StInvU64>" for r in (1, 85)},
+    ("n8192_k3", "inv", 86): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
+    ("n4096_k2", "fwd", 64): "ntt_fwd_part_kernel<12, 2, LdRowsU64, StU64>", ("n4096_k2", "inv", 1): "ntt_inv_kernel<12, 8, LdInvU64, StInvU64>",
+    ("n16384_k6", "inv", 64): "ntt_inv_part_kernel<14, 2, LdInvU64, StInvU64>", ("n16384_k6", "inv", 65): "ntt_inv_kernel<14, 16, LdInvU64, StInvU64>",
+    # ... not where the results land on the rows that are read
+    ("n8192_k3", "fwd_in_place", 12): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
+    ("n8192_k3", "inv_in_place", 12): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
     # operands: no more rows than compute units on 1024 threads; both kinds of rows in one launch up to two per unit
     ("n8192_k3", "extend", 18): "ntt_fwd_kernel<13, 8, LdMulExt<3>, StF64>",
     ("n8192_k3", "extend", 19): "ntt_fwd_kernel<13, 16, LdMulExt<3>, StF64>",
@@ -72,6 +83,8 @@ def _launches(lib):
                  "mul_sum": lambda g, u: lib.lib.cg_mul_sum(ctx, None, d, d, out, u32(g), u32(u), d),
                  "sum": lambda b: lib.lib.cg_rotate_sum_hoisted(ctx, None, d, u32(7), gs, keys, out, u32(b), d),
                  "extend": lambda n: lib.lib.cg_cache_extend(ctx, None, d, u32(n), u32(1), u32(1), out),
+                 **{name + at: lambda r, f=f, to=to: getattr(lib.lib, f)(ctx, None, d, to, (u32 * r)(*[i % k for i in range(r)]), u32(r))
+                    for name, f in (("fwd", "cg_ntt_forward"), ("inv", "cg_ntt_inverse")) for at, to in (("", out), ("_in_place", d))},
                  "scores": lambda h, c: lib.lib.cg_decode_scores(ctx, None, d, d, u32(h), u32(c), u32(c), u32(64), d, keys, out, d),
                  "context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
                      ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d)}
