@@ -803,6 +803,41 @@ static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
                                              : c->dnum <= 2 ? IdleLimits{128, 256, 256} : IdleLimits{84, 176, 256});
 }
 
+// the same at N = 16384; a relinearisation is the series of one rotation by g = 1
+static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T, uint32_t n_rot,
+                          double *acc, uint32_t batch)
+{
+    const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L * n_rot);
+    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)batch * c->L);
+    const size_t nwg = (size_t)batch * c->L;
+#define CG_KSWIDE(A)                                                                                          \
+    do {                                                                                                      \
+        const unsigned grid = ntt_grid<ks_wide_kernel<A>>(c, (nwg + 7) / 8 * 8, 1024);                        \
+        if (c->dry) return CG_OK;                                                                             \
+        return launch_kernel(ks_wide_kernel<A>, dim3(grid), dim3(1024), s, LdModup<false, A>{src, src_stride, 0, c->logn}, T, \
+                             (int)n_rot, (int)batch, StInvF64{acc, c->logn}, (const double *)c->tw, (const double *)c->itw, \
+                             (const DevConst *)c->dc, (int)nwg);                                              \
+    } while (0)
+    if (c->alpha == 1) CG_KSWIDE(1);
+    CG_KSWIDE(2);
+#undef CG_KSWIDE
+}
+// us with the mod-down, N = 16384, six primes, two special ones, three launches / one; 1, 3 and 7 rotations: 16 units (128 compute units
+// idle) 91 / 97, 101 / 113, 127 / 145, 20 (96): 111 / 105, 128 / 121, 161 / 154, 32: 159 / 127, 188 / 143, 240 / 184; 36 (224): 197 / 197,
+// 227 / 230, 286 / 299, 40 (192): 210 / 203, 238 / 237, 300 / 309, 44 (160): 238 / 209, 268 / 242, 343 / 319, 64: 321 / 268, 369 / 309,
+// 473 / 394; 80 (128): 416 / 361, 468 / 417, 595 / 535.
+// beside: in an attention call, beside a step's other branches, heads x ciphertexts.  Summed rotations of one round of workgroups pay sooner
+// there (16 x 1, 128 idle, 1043 / 1024, 12 x 2 1123 / 1115) and those of two later (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555); relinearisations
+// only from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205).
+static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, bool beside)
+{
+    if (c->logn != 14) return false;
+    if (c->dry) return c->dry_rows;
+    const size_t rows = (size_t)batch * c->L;
+    if (relin && beside && rows <= (size_t)c->n_cu) return false;
+    return rounds_pay(c, rows, IdleLimits{beside ? 128 : 96, 144, 160});
+}
+
 // whole key switches, summed rotations or not, in one launch
 template <int MODE>
 static int launch_ks_unit(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
@@ -1246,7 +1281,7 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                         const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
                         uint32_t galois_inv, int accumulate, uint32_t batch, void *ws,
-                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0)
+                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0, bool beside = false)
 {
     if (!acc_add) { acc_add = add; acc_stride = add_stride; }
     Bump w = bump(c, ws);
@@ -1262,7 +1297,12 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
         return galois ? launch_ks_unit<KS_ROTATE>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows)
                       : launch_ks_unit<KS_PLAIN>(c, s, src, src_stride, galois, T, A, ModdownHoist{}, acc, add_rows);
     }
-    if (ks_row_wins(c, (size_t)batch * c->L, galois != 0)) {
+    if (!galois && ks_wide_wins(c, batch, true, beside)) {
+        HoistTab T{};
+        T.g[0] = 1;
+        T.key[0] = key;
+        CG_TRY(launch_ks_wide(c, s, src, src_stride, T, 1, acc, batch));
+    } else if (ks_row_wins(c, (size_t)batch * c->L, galois != 0)) {
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
         CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));
@@ -1287,11 +1327,11 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 }
 
 static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *out2, uint32_t batch,
-                    void *ws)
+                    void *ws, bool beside = false)
 {
     const size_t ct3 = (size_t)3 * c->k * c->N;
     return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
-                        (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws);
+                        (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws, nullptr, 0, beside);
 }
 
 // in_stride / out_stride: uint64 between consecutive units (0 = densely packed ciphertexts)
@@ -1406,7 +1446,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
 // out_stride as in do_rotate.  ws: (dnum + 2)(k+nsp) rows per ciphertext.
 static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t in_stride, uint32_t n_rot,
                          const uint32_t *gs, const void *const *keys, uint64_t *out2, size_t out_stride,
-                         uint32_t batch, void *ws)
+                         uint32_t batch, void *ws, bool beside = false)
 {
     const size_t ct2 = (size_t)2 * c->k * c->N;
     if (!in_stride) in_stride = ct2;
@@ -1427,7 +1467,9 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     const uint64_t *c1 = in2 + (size_t)c->k * c->N;
     ModdownArgs A{acc, out2, out_stride, in2, in_stride, 1u, 1, (int)batch, in2, in_stride};
     if (ks_unit_wins(c, batch, n_rot)) return launch_ks_unit<KS_SUM>(c, s, c1, in_stride, 0, T, A, H, acc, 2.0 * c->k);
-    if (ks_sum_row_wins(c, batch)) {
+    if (ks_wide_wins(c, batch, false, beside)) {
+        CG_TRY(launch_ks_wide(c, s, c1, in_stride, T, n_rot, acc, batch));
+    } else if (ks_sum_row_wins(c, batch)) {
         CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
     } else {
         CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig));
@@ -1725,13 +1767,13 @@ static bool fold_keys_ok(const FoldRounds &R, const void *const *keys)
 }
 // x0 holds the start value; rounds ping-pong between x0 and x1, the last result lands in `out`
 static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint64_t *out, const FoldRounds &R,
-                      const void *const *keys, uint32_t batch, void *ws)
+                      const void *const *keys, uint32_t batch, void *ws, bool beside = false)
 {
     uint64_t *cur = x0, *nxt = x1;
     for (int r = 0; r < R.n_rounds; r++) {
         uint64_t *dst = (r == R.n_rounds - 1) ? out : nxt;
         CG_TRY(do_rotate_sum(c, s, cur, 0, (uint32_t)R.count[r], R.g.data() + R.first[r], keys + R.first[r], dst, 0,
-                             batch, ws));
+                             batch, ws, beside));
         nxt = cur;
         cur = dst;
     }
@@ -1790,8 +1832,8 @@ static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_
     uint64_t *d3 = w.take<uint64_t>((size_t)3 * c->k * batch);
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * batch), *xb = w.take<uint64_t>((size_t)2 * c->k * batch);
     CG_TRY(do_mul(c, s, q, kc, d3, batch, n_cts, w.p, 0, n_cts, cache_stride_cts, kext));
-    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p));
-    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p);
+    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, true));
+    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, true);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
 }
 extern "C" int cg_decode_scores(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, uint32_t heads,
@@ -1842,8 +1884,8 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
         CG_LAUNCH_PW(KID_SUM_GROUPS, (double)limb_bytes(c) * rows * (batch + heads), (double)batch, sum_groups_kernel,
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
-    CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p));
-    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p);
+    CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, true));
+    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, true);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p);
 }
 extern "C" int cg_decode_context(cg_ctx *c, void *stream, const uint64_t *a, const uint64_t *vc, uint32_t heads,

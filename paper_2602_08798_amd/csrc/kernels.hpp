@@ -438,6 +438,9 @@ struct StRegs {
 template <> struct st_in_place<StRegs> { static constexpr bool value = true; };
 template <class ST> struct st_regs { static constexpr bool value = false; };
 template <> struct st_regs<StRegs> { static constexpr bool value = true; };
+// results of a half row of an inverse transform, whose last stage is still to come
+struct StHalfRegs : StRegs {};
+template <> struct st_regs<StHalfRegs> { static constexpr bool value = true; };
 
 // prio: a wave's priority falls from pass to pass between two barriers, so that those behind catch up and all reach the
 // barrier about together.  (Equal priorities let the oldest wave issue first: it runs ahead and then waits.)  Worth 2 to 7 %
@@ -629,6 +632,7 @@ template <class ST> struct st_adds<const ST &> : st_adds<ST> {};
 // storers of rows without the factor N^-1 (scale_kernel has it among its constants): bound of the results, in hundredths
 template <class ST> struct st_unscaled { static constexpr int value = 0; };
 template <class ST> struct st_unscaled<const ST> : st_unscaled<ST> {};
+template <> struct st_unscaled<StHalfRegs> { static constexpr int value = 365; };
 // Loaders of inverse transforms: bound of what they deliver (InvBound's IN).  With it the first pass reduces what its plan asks for, and a
 // factor of a product need not be reduced to keep the other bounds: with N^-1 left to the scaling a product's workgroup (mul_row_kernel,
 // three primes) has 5110 FP64 instructions a thread -> 4978, one of a sum 4162 -> 4066, a plaintext product 1066 -> 1046.
@@ -651,7 +655,8 @@ template <int LOGN, int E, int PASS, int IN = 0, int U = 1, class ST>
 __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int tid,
                                          const double *__restrict__ itw, const double *twr, double *twr_next,
                                          const ModD m, int pr, const DevConst *C, const double *from = nullptr,
-                                         const uint64_t *early = nullptr, bool prio = false, int row_step = 0)
+                                         const uint64_t *early = nullptr, bool prio = false, int row_step = 0,
+                                         int root = 1)
 {
     using P = Plan<LOGN, E>;
     constexpr int R = P::R[PASS];
@@ -732,8 +737,8 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
                 if (plan.after[c]) x[c] = red(x[c], m);
         }
     if constexpr (!last) {
-        if constexpr (PASS == 1) load_tw<LOGN, E, 0, true>(itw, tid, twr_next);
-        else load_tw<LOGN, E, PASS - 1, false>(itw, tid, twr_next);
+        if constexpr (PASS == 1) load_tw<LOGN, E, 0, true>(itw, tid, twr_next, root);
+        else load_tw<LOGN, E, PASS - 1, false>(itw, tid, twr_next, root);
     }
 #pragma unroll
     for (int w = 0; w < U; w++)
@@ -1545,9 +1550,9 @@ template <> struct st_adds<StAppendRow> { static constexpr bool value = true; };
 // ahead: run before the last pass, for loads that nothing before it waits for
 struct Nothing { __device__ __forceinline__ void operator()() const {} };
 // U: rows of one prime together, row u in in[u E ...], its LDS u * lds_doubles() further on
-template <int LOGN, int E, bool SCATTERED, bool PRIO = false, int U = 1, class F = Nothing>
+template <int LOGN, int E, bool SCATTERED, bool PRIO = false, int U = 1, int IN = (int)(100 * FWD_IN), class F = Nothing>
 __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *out, int tid,
-                                        const double *__restrict__ tw, const ModD m, F ahead = F())
+                                        const double *__restrict__ tw, const ModD m, F ahead = F(), int root = 1)
 {
     constexpr int NP = Plan<LOGN, E>::NP;
     // addresses are formed here and now: hoisted out of the caller's loops they would take the registers
@@ -1555,14 +1560,14 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
     asm volatile("" : "+v"(tid));
     double twa[TWREGS], twb[TWREGS];
     const StRegs st{out};
-    load_tw<LOGN, E, 0, true>(tw, tid, twa);
-    fwd_pass<LOGN, E, 0, !SCATTERED, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
-    fwd_pass<LOGN, E, 1, false, U>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
-    fwd_pass<LOGN, E, 2, false, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    load_tw<LOGN, E, 0, true>(tw, tid, twa, root);
+    fwd_pass<LOGN, E, 0, !SCATTERED, U, IN>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO, root);
+    fwd_pass<LOGN, E, 1, false, U, IN>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO, root);
+    fwd_pass<LOGN, E, 2, false, U, IN>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO, root);
     if (NP == 4) ahead();
-    fwd_pass<LOGN, E, 3, false, U>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO);
+    fwd_pass<LOGN, E, 3, false, U, IN>(lds, in, st, tid, tw, twb, twa, m, 0, PRIO, root);
     if (NP > 4) ahead();
-    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false, U>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO);
+    if constexpr (NP > 4) fwd_pass<LOGN, E, 4, false, U, IN>(lds, in, st, tid, tw, twa, twb, m, 0, PRIO, root);
 }
 // in: chunk_elem order, |x| < 8p (or the bound IN in hundredths); results leave through st as row `row`
 // U: rows together as in fwd_row, results as rows `row` + u * row_step
@@ -1570,30 +1575,30 @@ __device__ __forceinline__ void fwd_row(double *lds, const double *in, double *o
 template <int LOGN, int E, bool PRIO = false, int IN = 0, int U = 1, class ST, class F = Nothing>
 __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST &st, int row, int tid,
                                         const double *__restrict__ itw, const ModD m, int pr, const DevConst *C,
-                                        int row_step = 0, F ahead = F())
+                                        int row_step = 0, F ahead = F(), int root = 1)
 {
     constexpr int NP = Plan<LOGN, E>::NP;
     asm volatile("" : "+v"(tid));
     double twa[TWREGS], twb[TWREGS];
-    load_tw<LOGN, E, NP - 1, false>(itw, tid, twa);
+    load_tw<LOGN, E, NP - 1, false>(itw, tid, twa, root);
     if constexpr (Plan<LOGN, E>::R[NP - 1] != 1) {
 #pragma unroll
         for (int it = 0; it < U * E; it += 2)
             pair_at(lds, it / E * lds_doubles<LOGN>() + pad(chunk_elem<E>(tid, it % E))) = make_double2(in[it], in[it + 1]);
         wave_sync();
     }
-    inv_pass<LOGN, E, NP - 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO, row_step);
+    inv_pass<LOGN, E, NP - 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, in, nullptr, PRIO, row_step, root);
     if constexpr (NP > 4) {
-        inv_pass<LOGN, E, 3, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 3, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
+        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
         ahead();
-        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
+        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
     } else {
-        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 2, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
         ahead();
-        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step);
-        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step);
+        inv_pass<LOGN, E, 1, IN, U>(lds, st, row, tid, itw, twa, twb, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
+        inv_pass<LOGN, E, 0, IN, U>(lds, st, row, tid, itw, twb, twa, m, pr, C, nullptr, nullptr, PRIO, row_step, root);
     }
 }
 
@@ -1841,6 +1846,159 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
             lds_barrier();
             inverse(s2, s3, b + 1);
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same at N = 16384, for digits of one or two primes: a row is two half rows of 8192 that one workgroup takes through LDS one after the
+// other (the first stage, which joins them, in registers; half h is the sub-transform at node 2 + h), and both lie there when the rotations
+// take their values, which come from either half.  A relinearisation is the series of one rotation by 1.  What three launches moved through
+// memory (a unit's transformed digits out and in, its accumulators out, in and out again: 104 rows of 142 per key switch) never leaves the compute
+// unit, and memory is what bounds a step at this size.  Registers: four sums and a half row, as with two units at N = 8192.  Bound by
+// vector issue and the keys' way from L2 (5.4 MB a row with 7 rotations).  32 ciphertexts, six primes, two special ones, 7 rotations:
+// mod-up, sums and inverse transforms 61 + 101 + 39 us, 135 here.
+// ---------------------------------------------------------------------------
+// The constants of a digit's lift to one prime, in scalar registers (as LiftTab)
+template <int ALPHA> struct DigitTab {
+    ModD ms;
+    double inv, s_mod_t;
+    __device__ __forceinline__ DigitTab(const DevConst *C, int j, int r) : ms{0.0, 0.0}, inv(0.0), s_mod_t(0.0)
+    {
+        if constexpr (ALPHA == 2) {
+            C = opaque_const(C);
+            ms = ModD{pinned(C->mod[2 * j + 1].p), pinned(C->mod[2 * j + 1].u)};
+            inv = pinned(C->dig[j].inv[0][1]);
+            s_mod_t = pinned(C->dig[j].s_mod_t[0][r]);
+        }
+    }
+    // the digit (an integer in [0, Q_j)) modulo m, below 1.7 * 2^50
+    __device__ __forceinline__ double lift(const uint64_t *w, const ModD m) const
+    {
+        const double x0 = u64_to_f64(w[0]);
+        if constexpr (ALPHA == 1) return x0;
+        else return mulmod(canon(mulmod(u64_to_f64(w[ALPHA - 1]) - x0, inv, ms), ms), s_mod_t, m) + x0;
+    }
+};
+template <int ALPHA>
+__global__ void __launch_bounds__(1024, 4)
+ks_wide_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, StInvF64 st, const double *__restrict__ tw_all,
+               const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int LOGN = 14, E = 8, TH = 1024, HALF = 1 << 13, ROW = lds_doubles<13>();
+    constexpr int IN = hundredths(1.7 + 0.5 + 0.1875 * 1.7);
+    static_assert(2 * ROW == lds_doubles<14>(), "both halves as one padded row");
+    __shared__ __align__(16) double lds[2 * ROW];
+    const int tid = threadIdx.x, L = C->L, dnum = C->dnum;
+    // as in ks_sum_row_kernel
+    const int per_xcd = (nwg + 7) >> 3, total = per_xcd * 8;
+    for (int p = blockIdx.x; p < total; p += (int)gridDim.x) {
+        const int wg = (p & 7) * per_xcd + (p >> 3);
+        if (wg >= nwg) continue;
+        const int r = wg / batch, b = wg - r * batch;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        const double w1 = tw[1];
+        // half and component
+        double s00[E], s01[E], s10[E], s11[E];
+#pragma unroll
+        for (int it = 0; it < E; it++) s00[it] = s01[it] = s10[it] = s11[it] = 0.0;
+        for (int j = 0; j < dnum; j++) {
+            const uint64_t *src = ld.src + (size_t)b * ld.unit_stride + ((size_t)(j * ALPHA) << LOGN);
+            const DigitTab<ALPHA> tab(C, j, r);
+            uint64_t w[2][2][ALPHA];
+            auto get = [&](int it) {
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int a = 0; a < ALPHA; a++) w[it & 1][h][a] = at_lane(src + ((size_t)a << LOGN) + h * HALF + it * TH, tid);
+            };
+            double x[E];
+            get(0);
+            lds_barrier();      // the previous digit's (or unit's) LDS reads
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                if (it + 1 < E) get(it + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const double a = tab.lift(w[it & 1][0], m), t = mulmod(tab.lift(w[it & 1][1], m), w1, m);
+                x[it] = a + t;
+                lds[row_pos<13>(1, pad(tid)) + pad(it * TH)] = a - t;      // where the second half's first pass has it
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                double *row = lds + h * ROW;
+                if (h) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) x[it] = row[pad(tid) + pad(it * TH)];
+                }
+                fwd_row<13, E, false, false, 1, IN>(row, x, x, tid, tw, m, Nothing(), 2 + h);
+#pragma unroll
+                for (int it = 0; it < E; it += 2)
+                    pair_at(row, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
+            }
+            lds_barrier();
+            int tk = tid;
+            asm volatile("" : "+v"(tk));
+            const int idx0 = chunk_elem<E>(tk, 0);
+            const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
+            const size_t comp = (size_t)L << (LOGN - 1);
+            auto rows = [&](int i) { return reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN)); };
+            const cg_double2v *k0 = rows(0);
+            uint32_t g = T.g[0];
+            cg_double2v ka[2], kc[2];
+            ka[0] = at_lane(k0, idx0 / 2);
+            kc[0] = at_lane(k0 + comp, idx0 / 2);
+            for (int i = 0; i < n_rot; i++) {
+                const int i_next = i + 1 < n_rot ? i + 1 : i;
+                const cg_double2v *kn = rows(i_next);
+                const uint32_t gn = T.g[i_next], eg = __umul24(e0, g);
+#pragma unroll
+                for (int f = 0; f < E; f++) {       // pair f % 4 of half f / 4, its keys asked for one ahead
+                    const cg_double2v *kf = f + 1 < E ? k0 + (f + 1) / 4 * (HALF / 2) + 64 * ((f + 1) % 4) : kn;
+                    ka[(f + 1) & 1] = at_lane(kf, idx0 / 2);
+                    kc[(f + 1) & 1] = at_lane(kf + comp, idx0 / 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const cg_double2v a = ka[f & 1], c = kc[f & 1];
+                    const int q = f % 4;
+                    const uint32_t e = eg + (2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) + 2u * (f / 4)) * g;
+                    const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
+                    const double x0 = lds[at], x1 = lds[at ^ 1];
+                    double (&d0)[E] = f < 4 ? s00 : s10, (&d1)[E] = f < 4 ? s01 : s11;
+                    d0[2 * q] += mulmod(x0, a.x, m);
+                    d0[2 * q + 1] += mulmod(x1, a.y, m);
+                    d1[2 * q] += mulmod(x0, c.x, m);
+                    d1[2 * q + 1] += mulmod(x1, c.y, m);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                k0 = kn;
+                g = gn;
+                // a term is below 0.6 p
+                if ((i & 7) == 7 || i + 1 == n_rot) {
+#pragma unroll
+                    for (int it = 0; it < E; it++) {
+                        s00[it] = red(s00[it], m);
+                        s01[it] = red(s01[it], m);
+                        s10[it] = red(s10[it], m);
+                        s11[it] = red(s11[it], m);
+                    }
+                }
+            }
+        }
+        const double n0 = C->ninv[r], n1 = C->itw1_ninv[r];
+        auto inverse = [&](const double *lo, const double *hi, int c) {
+            double a[E], d[E];
+            lds_barrier();
+            inv_row<13, E, false, 52>(lds, lo, StHalfRegs{{a}}, 0, tid, itw, m, 0, C, 0, Nothing(), 2);
+            inv_row<13, E, false, 52>(lds + ROW, hi, StHalfRegs{{d}}, 0, tid, itw, m, 0, C, 0, Nothing(), 3);
+            double *o = st.dst + ((size_t)((b * 2 + c) * L + r) << LOGN);
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                put_lane(o + it * TH, tid, mulmod(a[it] + d[it], n0, m));
+                put_lane(o + HALF + it * TH, tid, mulmod(a[it] - d[it], n1, m));
+            }
+        };
+        inverse(s00, s10, 0);
+        inverse(s01, s11, 1);
     }
 }
 

@@ -40,6 +40,12 @@ WANT = {
     # ... not where the results land on the rows that are read
     ("n8192_k3", "fwd_in_place", 12): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
     ("n8192_k3", "inv_in_place", 12): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
+    # key switches at N = 16384: single transforms' launches while more than 3/8 of the compute units would idle in one round, 9/16 in two
+    **{("n16384_k6", "sum", b): "ks_sum_kernel<3, " for b in (4, 19, 33, 45)},
+    **{("n16384_k6", "sum", b): "ks_wide_kernel<2>" for b in (20, 32, 46, 64, 80)},
+    # ... in an attention call half of them idle in one round, and relinearisations from the second round on
+    ("n16384_k6", "scores_rounds", 15, 1): "ks_sum_kernel<3, ", ("n16384_k6", "scores_rounds", 16, 1): "ks_wide_kernel<2>",
+    ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",
     # operands: no more rows than compute units on 1024 threads; both kinds of rows in one launch up to two per unit
     ("n8192_k3", "extend", 18): "ntt_fwd_kernel<13, 8, LdMulExt<3>, StF64>",
     ("n8192_k3", "extend", 19): "ntt_fwd_kernel<13, 16, LdMulExt<3>, StF64>",
@@ -85,6 +91,8 @@ def _launches(lib):
                  "extend": lambda n: lib.lib.cg_cache_extend(ctx, None, d, u32(n), u32(1), u32(1), out),
                  **{name + at: lambda r, f=f, to=to: getattr(lib.lib, f)(ctx, None, d, to, (u32 * r)(*[i % k for i in range(r)]), u32(r))
                     for name, f in (("fwd", "cg_ntt_forward"), ("inv", "cg_ntt_inverse")) for at, to in (("", out), ("_in_place", d))},
+                 "scores_rounds": lambda h, c: lib.lib.cg_decode_scores_hoisted(
+                     ctx, None, d, d, None, u32(h), u32(c), u32(c), u32(64), u32(3), d, keys, out, d),
                  "scores": lambda h, c: lib.lib.cg_decode_scores(ctx, None, d, d, u32(h), u32(c), u32(c), u32(64), d, keys, out, d),
                  "context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
                      ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d)}
