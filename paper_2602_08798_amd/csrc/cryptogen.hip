@@ -1131,6 +1131,17 @@ static uint32_t mul_sum_parts_half(const cg_ctx *c, uint32_t groups, uint32_t gr
     return parts;
 }
 
+// Sums of products with a transformed cache at N = 8192: the products one by one in mul_row_kernel, added up by scale_kernel, instead of the
+// transforms of the operands and a tensor inverse that walks over the group.  With half the compute units busy or more, while an eighth are
+// left to a step's other branches.  us a step, three primes, heads x ciphertexts (products x primes of 256): 6 x 2 (84) 221 / 224,
+// 16 x 1 (112) 300 / 283, 2 x 8 (112) 244 / 220, 10 x 2 (140) 291 / 287, 12 x 2 (168) 329 / 315, 14 x 2 (196) 373 / 353, 8 x 4 (224) 344 / 339,
+// 4 x 8 (224) 328 / 318, 9 x 4 (252) 368 / 375, 12 x 4 (336) 424 / 431, 12 x 6 (504) 590 / 600.
+static bool mul_row_sums_win(const cg_ctx *c, size_t rows)
+{
+    const size_t n = (size_t)c->n_cu;
+    return c->logn == 13 && c->k <= 3 && !c->dry && 16 * rows >= 7 * n && 8 * rows <= 7 * n;
+}
+
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
 // launch for the roofline report; LB = bytes of one residue row.
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
@@ -1180,6 +1191,10 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     } else if (sum_group && a_group == 1 && b_ext && mul_sum_parts(c, n_out, sum_group, parts, true)) {
         CG_TRY(launch_mul_sum_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                         tens, n_out, sum_group, parts));
+    } else if (sum_group && a_group == 1 && b_ext && mul_row_sums_win(c, (size_t)batch * c->KL)) {
+        parts = sum_group;
+        CG_TRY(launch_mul_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
+                                    tens, batch, B, B));
     } else if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
         CG_TRY(launch_mul_sum_row<false>(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                   tens, n_out, sum_group, parts));

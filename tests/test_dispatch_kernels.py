@@ -63,6 +63,9 @@ WANT = {
     **{("n4096_k2", "context_ext", h, c): "mul_sum_row_kernel<12, 8, 2, true>" for h, c in ((17, 5), (85, 1), (12, 7))},
     **{("n4096_k2", "context_ext", h, c): "ntt_inv_kernel<12, 8, LdInvTensorSum, StInvF64>" for h, c in ((43, 2), (86, 1), (11, 8))},
     ("n8192_k3", "context_ext", 1, 1): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
+    # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8
+    **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
+    **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
     **{("n16384_k6", "context_ext", h, c): "mul_sum_row_kernel<13, 8, 0, true>" for h, c in ((4, 4), (8, 3), (12, 2), (16, 3))},

@@ -312,6 +312,25 @@ def test_sum_of_products_with_one_scaling_matches_oracle(name):
         env.ctx.mul_sum(env.dev(a), env.dev(b), 3, 0)
 
 
+@pytest.mark.parametrize("heads,n_cts", [(16, 1), (2, 8), (3, 6)])
+def test_context_with_a_transformed_cache_product_by_product(heads, n_cts):
+    """Enough (product, prime) pairs for the product kernel, whose results the scaling adds up"""
+    from oracle import attention
+    env = _env("C2")
+    d2, w_block = 64, 3
+    raw_rlk, rlk = env.key(70)
+    _, raw_b, dev_b = _round_keys(env, 1, d2, w_block, 1200)
+    say(f"decode_context_hoisted C2, {heads} x {n_cts}, transformed cache")
+    a, vc = env.cts(85, heads * n_cts), env.cts(86, heads * n_cts)
+    ext = env.ctx.cache_extend(env.dev(vc), heads, n_cts, n_cts, env.ctx.empty_ext(heads * n_cts))
+    got = env.host(env.ctx.decode_context_hoisted(env.dev(a), None, heads, n_cts, d2, w_block, rlk, dev_b, vext=ext,
+                                                  sum_before_scaling=True))
+    for h in (0, heads - 1):
+        sl = slice(h * n_cts, (h + 1) * n_cts)
+        want = attention.decode_context_hoisted(env.orc, list(a[sl]), list(vc[sl]), raw_rlk, raw_b, d2, w_block, sum_first=True)
+        assert np.array_equal(got[h], want), h
+
+
 @pytest.mark.parametrize("name,with_copy", [("C1", True), ("C2", False), ("C5", False)])
 def test_decode_context_and_step_with_products_summed_before_scaling_match_oracle(name, with_copy):
     from oracle import attention
