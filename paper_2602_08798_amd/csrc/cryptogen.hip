@@ -553,12 +553,15 @@ static int ntt_elems(const cg_ctx *c) { return c->elems; }
 // N = 16384: 12 11.8 / 6.4, 64 12.6 / 8.2, 128 13.8 / 11.0.  Inverse, N = 4096: 12 rows 6.0 / 6.6, 100: 6.0 / 5.7 (two); N = 8192: 12 7.7 / 6.0 (four:
 // 7.4), 64 8.1 / 6.5; N = 16384: 12 13.5 / 10.1, 64 14.5 / 11.3 (four), 100 15.1 / 12.2 (two).  Inverse transforms only up to a third of
 // the compute units at N = 8192 and a quarter at N = 16384: they are the summed rotations' of a step, whose other branches the work
-// done twice holds up (12 heads, 96 rows: 420.3 us a step whole, 423.5 in parts; alone 8.3 / 7.1 a launch).
+// done twice holds up (12 heads, 96 rows: 420.3 us a step whole, 423.5 in parts; alone 8.3 / 7.1 a launch).  At N = 8192 also where whole rows
+// would take a second round for up to 3/8 of the compute units, and halves take one and a half: 260 rows 16.7 / 15.4, 340: 17.3 / 15.9,
+// 384: 17.7 / 17.0, 448: 17.8 / 19.8; 36 matrices of a projection (288 rows) 241 / 236 a call.
 static int row_parts(const cg_ctx *c, size_t rows, bool inverse)
 {
     const size_t n = (size_t)c->n_cu;
     if (c->dry) return 0;
-    if (inverse) return c->logn == 13 && 3 * rows <= n ? 1 : c->logn == 14 && 4 * rows <= n ? 2 : 0;
+    if (inverse && c->logn == 13) return 3 * rows <= n || (rows > n && 8 * rows <= 11 * n) ? 1 : 0;
+    if (inverse) return c->logn == 14 && 4 * rows <= n ? 2 : 0;
     return 4 * rows <= n ? 2 : 2 * rows <= n ? 1 : 0;
 }
 // two device ranges share at least one byte

@@ -30,11 +30,11 @@ WANT = {
     # the tensor product of no more rows than compute units on 1024 threads
     ("n8192_k3", "mul", 12): TENSOR.format(8), ("n8192_k3", "mul", 13): TENSOR.format(16),
     # transforms: rows in four parts up to a quarter of the compute units, in two up to half; inverse at N = 8192 in two up to a
-    # third, at N = 16384 in four up to a quarter
+    # third and from one row per unit to 11/8, at N = 16384 in four up to a quarter
     **{("n8192_k3", "fwd", r): f"ntt_fwd_part_kernel<13, {p}, LdRowsU64, StU64>" for r, p in ((1, 2), (64, 2), (65, 1), (128, 1))},
     ("n8192_k3", "fwd", 129): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
-    **{("n8192_k3", "inv", r): "ntt_inv_part_kernel<13, 1, LdInvU64, StInvU64>" for r in (1, 85)},
-    ("n8192_k3", "inv", 86): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
+    **{("n8192_k3", "inv", r): "ntt_inv_part_kernel<13, 1, LdInvU64, StInvU64>" for r in (1, 85, 257, 352)},
+    **{("n8192_k3", "inv", r): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>" for r in (86, 256, 353)},
     ("n4096_k2", "fwd", 64): "ntt_fwd_part_kernel<12, 2, LdRowsU64, StU64>", ("n4096_k2", "inv", 1): "ntt_inv_kernel<12, 8, LdInvU64, StInvU64>",
     ("n16384_k6", "inv", 64): "ntt_inv_part_kernel<14, 2, LdInvU64, StInvU64>", ("n16384_k6", "inv", 65): "ntt_inv_kernel<14, 16, LdInvU64, StInvU64>",
     # ... not where the results land on the rows that are read

@@ -42,7 +42,7 @@ def test_transforms_of_few_rows(name):
     few[0, :], few[1, ::2] = env.qp[0] - 1, env.qp[1] - 1
     fwd = [bfv.ntt_forward(few[i], int(env.qp[i])) for i in range(L)]
     inv = [bfv.ntt_inverse(few[i], int(env.qp[i])) for i in range(L)]
-    for rows in (1, 3, 63, 64, 65, 85, 86, 128, 129):
+    for rows in (1, 3, 63, 64, 65, 85, 86, 128, 129) + ((257, 352, 353) if name == "C2" else ()):
         say(f"transforms {name}, {rows} rows")
         idx = [i % L for i in range(rows)]
         x = env.dev(np.ascontiguousarray(few[idx]))
@@ -53,7 +53,7 @@ def test_transforms_of_few_rows(name):
 
 
 # rows of the mod-up, then of the inverse transforms, per unit: C1 6 and 6, C2 12 and 8, C5 24 and 16, pairs 4 and 8, one 2 and 4
-@pytest.mark.parametrize("name,batches", [("C1", (1, 10, 11, 21, 22)), ("C2", (1, 5, 6, 10, 11)), ("C5", (1, 2, 3, 4, 5)),
+@pytest.mark.parametrize("name,batches", [("C1", (1, 10, 11, 21, 22)), ("C2", (1, 5, 6, 10, 11, 33, 40)), ("C5", (1, 2, 3, 4, 5)),
                                           ("pairs", (2, 10, 11, 16, 17)), ("one", (1, 21, 22, 32, 33))])
 def test_key_switches_of_few_units(name, batches):
     env = _env(name)
