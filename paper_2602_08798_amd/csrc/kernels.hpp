@@ -1502,10 +1502,8 @@ struct StInvU64 {
     {
         put32(dst + ((size_t)wg << logn), idx, f64_to_u64(canon(v, m)));
     }
-    __device__ __forceinline__ void store_lane(int wg, int at, int lane, double v, const ModD m) const
-    {
-        put_lane(dst + ((size_t)wg << logn) + at, lane, f64_to_u64(canon(v, m)));
-    }
+    // (with the row's address in scalar registers 4323 rows of 8192 take 157.4 us instead of 155.8, 1025 of 16384 75.6 instead of 74.3)
+    __device__ __forceinline__ void store_lane(int wg, int at, int lane, double v, const ModD m) const { store(wg, at + lane, v, m); }
     __device__ __forceinline__ const StInvU64 &at_row(int, int) const { return *this; }
 };
 // cache append: workgroup -> (cache c, comp, prime); target row = cache + c*stride + row;
