@@ -1993,10 +1993,22 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     if (!append_first) CG_HIP(hipStreamWaitEvent(side[1], c->ev_fork, 0));
     // Branches are always joined, also after a failed launch, so that the caller's stream never
     // runs ahead of work this call started.
-    int rc = scores_impl(c, s, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores,
-                         fold_w);
-    const int rc1 = context_impl(c, side[0], a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block,
-                                 context, ws_context, block_w, sum_first);
+    // The longer chain runs on the caller's stream, where it waits for no event and none waits for it, and is issued first.  That is the
+    // context's where it has no fewer key switches, until the scores' take more than one round of workgroups each.  us a step with
+    // the scores there / the context, d2 = 64, heads x ciphertexts: N = 8192, chains 12 x 4 (192 rows) 652 / 619, 1 x 1 297 / 284, rounds 12 x 4
+    // 423 / 411, 8 x 1 210 / 202, 12 x 6 (288) 585 / 590, 12 x 8 700 / 698 ... 695 / 702; N = 4096, 12 x 4 (144) 188 / 176, 12 x 8 (288) 259 / 266;
+    // N = 16384, 1 x 1 281 / 261, 4 x 1 396 / 386, 16 x 3 (384) 1770 / 1777.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
+    auto switches = [](uint32_t slots, uint32_t w) { const uint32_t bits = 31 - __builtin_clz(slots); return w ? (bits + w - 1) / w : bits; };
+    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (size_t)heads * n_cts * c->L <= (size_t)c->n_cu;
+    auto scores_on = [&](hipStream_t st) {
+        return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w);
+    };
+    auto context_on = [&](hipStream_t st) {
+        return context_impl(c, st, a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block, context, ws_context,
+                            block_w, sum_first);
+    };
+    int rc = context_first ? context_on(s) : scores_on(s);
+    const int rc1 = context_first ? scores_on(side[0]) : context_on(side[0]);
     if (rc == CG_OK) rc = rc1;
     if (!append_first) {
         const int rc2 = append(side[1]);
