@@ -1050,21 +1050,20 @@ static int launch_mul_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double 
 }
 // Sums of products over groups of units in one launch; every group is taken in `parts` parts.  HAT: y transformed (N = 4096 and 16384)
 template <bool HAT>
-static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t groups,
-                              uint32_t group, uint32_t parts)
+static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, double *tens, uint32_t groups, const SumParts &S)
 {
     const bool half = c->logn == 14;
-    const size_t nwg = (size_t)groups * parts * c->KL * (half ? 2 : 1);
-    const double units = (double)groups * group;
-    ProfScope ps(c, s, KID_MULSUMROW, (double)limb_bytes(c) * (4.0 * (half ? c->KL : c->k) * units + 3.0 * groups * parts * c->KL),
+    const size_t nwg = (size_t)(S.ranges ? S.ranges : groups * S.stride) * c->KL * (half ? 2 : 1);
+    const double units = S.units;
+    ProfScope ps(c, s, KID_MULSUMROW, (double)limb_bytes(c) * (4.0 * (half ? c->KL : c->k) * units + 3.0 * groups * S.stride * c->KL),
                  units * c->KL * (half ? 2 : 1));
 #define CG_MULSUMROW(LG, K, H)                                                                             \
     do {                                                                                                  \
         const unsigned threads = (1u << LG) / 8;                                                          \
         const unsigned grid = ntt_grid<mul_sum_row_kernel<LG, 8, K, H>>(c, nwg, (int)threads);            \
         if (c->dry) return CG_OK;                                                                         \
-        return launch_kernel(mul_sum_row_kernel<LG, 8, K, H>, dim3(grid), dim3(threads), s, A, (int)group, \
-                             (int)parts, StTens<K == 0>{{tens, LG}}, (const double *)(K ? c->tw : c->tw2), \
+        return launch_kernel(mul_sum_row_kernel<LG, 8, K, H>, dim3(grid), dim3(threads), s, A, S, \
+                             StTens<K == 0>{{tens, LG}}, (const double *)(K ? c->tw : c->tw2), \
                              (const double *)(K ? c->itw : c->itw2), (const DevConst *)c->dc, (int)nwg);  \
     } while (0)
     if (half) CG_MULSUMROW(13, 0, HAT);
@@ -1145,6 +1144,26 @@ static bool mul_row_sums_win(const cg_ctx *c, size_t rows)
     return c->logn == 13 && c->k <= 3 && !c->dry && 16 * rows >= 7 * n && 8 * rows <= 7 * n;
 }
 
+// Ranges of units that end where groups do not (SumParts), one round of workgroups of them, where parts of whole groups
+// would leave many workgroups idle: in the model above, a range that meets a second group has its transforms back twice
+// (+ 4).  At N = 8192 and three primes, contexts of 8 groups of 128 units 1695 -> 1572 us, 10: 2021 -> 1910, 11: 2253 ->
+// 2122, 16: 3250 -> 3061, 5: 1017 -> 997; 6, 9 and 12 groups, which parts fill as well, measure alike and stay.  At N = 4096, where two
+// workgroups share a compute unit and fill each other's gaps, ranges lose: 97 -> 106 us for one group, 376 -> 404 for 12.
+static bool sum_ranges(const cg_ctx *c, uint32_t groups, uint32_t group, SumParts &S)
+{
+    const int n = c->n_cu / c->KL, units = (int)(groups * group);
+    if (c->dry || c->logn != 13 || n < 1) return false;
+    const uint32_t parts = (uint32_t)S.stride;
+    const double even = std::ceil((double)groups * parts * c->KL / c->n_cu) * (6.0 * ((group + parts - 1) / parts) + 2.0);
+    if (6.0 * ((units + n - 1) / n) + 4.0 >= 0.99 * even) return false;
+    // (a group of G units meets (G - 1) n / units + 2 ranges at most)
+    const uint32_t most = (uint32_t)((uint64_t)(group - 1) * n / units) + 2;
+    if (most > group) return false;
+    S.stride = (int)most;
+    S.ranges = n;
+    return true;
+}
+
 // Algorithmic bytes (distinct inputs read once + outputs written once) are attached to every
 // launch for the roofline report; LB = bytes of one residue row.
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
@@ -1168,6 +1187,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     MulSrc src{a2, b2, (int)n_a, (int)b_group, (int)b_stride, c->logn, 0};
     const int all = 1 << 30;
     uint32_t parts = 1;
+    SumParts S{1, (int)(sum_group ? sum_group : 1), (int)batch, 0};
     if (c->logn == 14) {
         // operands lifted by a launch of its own, then half rows through the product in one launch: with a shared a
         // operand that is transformed once, or with the b operands given transformed, as the second operand
@@ -1185,22 +1205,28 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
             parts = mul_sum_parts_half(c, n_out, sum_group, b_ext != nullptr);
             // (while dry: the occupancy of the kernel that sums)
             if (b_ext && parts == sum_group && !c->dry) CG_TRY(launch_mul_row<true>(c, s, A, tens, batch, n_a, B));
-            else CG_TRY(b_ext ? launch_mul_sum_row<true>(c, s, A, tens, n_out, sum_group, parts)
-                              : launch_mul_sum_row<false>(c, s, A, tens, n_out, sum_group, parts));
+            else {
+                S.stride = (int)parts;
+                CG_TRY(b_ext ? launch_mul_sum_row<true>(c, s, A, tens, n_out, S) : launch_mul_sum_row<false>(c, s, A, tens, n_out, S));
+            }
         } else {
             CG_TRY(b_ext || shared ? launch_mul_row<true>(c, s, A, tens, batch, shared ? B : n_a, shared ? n_a : B)
                                    : launch_mul_row<false>(c, s, A, tens, batch, B, B));
         }
     } else if (sum_group && a_group == 1 && b_ext && mul_sum_parts(c, n_out, sum_group, parts, true)) {
+        S.stride = (int)parts;
         CG_TRY(launch_mul_sum_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
-                                        tens, n_out, sum_group, parts));
+                                        tens, n_out, S));
     } else if (sum_group && a_group == 1 && b_ext && mul_row_sums_win(c, (size_t)batch * c->KL)) {
         parts = sum_group;
         CG_TRY(launch_mul_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                     tens, batch, B, B));
     } else if (sum_group && a_group == 1 && !b_ext && mul_sum_parts(c, n_out, sum_group, parts)) {
+        S.stride = (int)parts;
+        (void)sum_ranges(c, n_out, sum_group, S);
         CG_TRY(launch_mul_sum_row<false>(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
-                                  tens, n_out, sum_group, parts));
+                                         tens, n_out, S));
+        parts = (uint32_t)S.stride;
     } else if (!sum_group && !(b_ext && a_group > 1) && mul_row_wins(c, (size_t)batch * c->KL, beside)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
         if (b_ext) {
@@ -1224,13 +1250,14 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
                                          KID_INV_TENSORSUM, tbytes));
         else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
     }
+    S.stride = (int)parts;
     const double sbytes = LB * (3.0 * c->KL * parts + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;
     const unsigned sblocks = pw_blocks(c, (size_t)n_out * 3);
 #define CG_SCALE(K)                                                                                                  \
     do {                                                                                                             \
         if (c->logn == 14) CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, (scale_kernel<K, true>), sblocks, tens, out3, \
-                                        (int)parts, accumulate, c->dc);                                              \
-        else CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, (scale_kernel<K, false>), sblocks, tens, out3, (int)parts, \
+                                        S, accumulate, c->dc);                                              \
+        else CG_LAUNCH_PW(KID_SCALE, sbytes, (double)n_out, (scale_kernel<K, false>), sblocks, tens, out3, S, \
                           accumulate, c->dc);                                                                        \
     } while (0)
     switch (c->k) {

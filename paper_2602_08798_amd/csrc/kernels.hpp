@@ -2178,6 +2178,19 @@ __device__ __forceinline__ void lift_window(double *x, const uint64_t *src, int 
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// How sums' units are divided over the workgroups of a prime.  ranges = 0: every group of `group` units in `stride` parts.  Else the units of
+// all groups form one row, cut into as many ranges of one length wherever groups end: the piece of group g that lies in range w is its part
+// w - first range of the group.  Results of part q of group g are at slot g * stride + q.
+struct SumParts {
+    int stride, group, units, ranges;
+    // the range that unit x lies in (range w starts at w * units / ranges, rounded down)
+    __device__ __forceinline__ int range_of(int x) const { return ((x + 1) * ranges - 1) / units; }
+    __device__ __forceinline__ int count(int g) const
+    {
+        return ranges ? range_of((g + 1) * group - 1) - range_of(g * group) + 1 : stride;
+    }
+};
+
 // Sums of products over the units of a group, one (group, part of it, prime) per workgroup: the operands of a unit
 // transformed as in mul_row_kernel, the three components summed over the units, one inverse transform of each sum.  What
 // the parts of a group leave is summed by scale_kernel.  It saves the transformed operands' way through memory, and
@@ -2192,7 +2205,7 @@ __device__ __forceinline__ void lift_window(double *x, const uint64_t *src, int 
 // memory none (mul_sum_parts_half has both sides).
 template <int LOGN, int E, int K, bool HAT>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-mul_sum_row_kernel(MulRowArgs A, int group, int parts, StTens<K == 0> st, const double *__restrict__ tw_all,
+mul_sum_row_kernel(MulRowArgs A, SumParts S, StTens<K == 0> st, const double *__restrict__ tw_all,
                    const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
     constexpr int T = (1 << LOGN) / E, W = K == 1 ? 8 : K == 2 ? 4 : 3;
@@ -2204,124 +2217,131 @@ mul_sum_row_kernel(MulRowArgs A, int group, int parts, StTens<K == 0> st, const 
     constexpr bool PRIO = LOGN == 13 && !HAT;
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
-        const int wg = xcd_row(p, nwg, KL), r = wg % KL, gp = wg / KL, g = gp / parts, part = gp - g * parts;
-        const int u_first = g * group + part * group / parts, u_end = g * group + (part + 1) * group / parts;
+        // (a prime's ranges, or the parts of its groups, one after the other)
+        const int wg = xcd_row(p, nwg, KL), r = wg % KL, w = wg / KL, g0 = w / S.stride, part = w - g0 * S.stride;
+        int u0 = S.ranges ? w * S.units / S.ranges : g0 * S.group + part * S.group / S.stride;
+        const int end = S.ranges ? (w + 1) * S.units / S.ranges : g0 * S.group + (part + 1) * S.group / S.stride;
         const ModD m = C->mod[K ? r : r >> 1];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
-        // the first component's sum: pair q of a thread at far[q * T + tid]
-        cg_double2v *far = reinterpret_cast<cg_double2v *>(st.dst + ((size_t)(gp * 3 * KL + r) << LOGN));
-        double d0[E], d1[E], d2[E];
+        while (u0 < end) {
+            const int u_first = u0, g = u0 / S.group, u_end = end < (g + 1) * S.group ? end : (g + 1) * S.group;
+            const int gp = S.ranges ? g * S.stride + w - S.range_of(g * S.group) : w;
+            u0 = u_end;
+            // the first component's sum: pair q of a thread at far[q * T + tid]
+            cg_double2v *far = reinterpret_cast<cg_double2v *>(st.dst + ((size_t)(gp * 3 * KL + r) << LOGN));
+            double d0[E], d1[E], d2[E];
 #pragma unroll
-        for (int it = 0; it < E; it++) d0[it] = d1[it] = d2[it] = 0.0;
-        // polynomials of a unit in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
-        constexpr int NT = HAT ? 2 : 4;
-        auto poly = [&](int u, int t) {
-            return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
-        };
-        // the first component's sum before unit u, and put back with a pair of that unit's products (below 2 p)
-        auto far_put = [&](const cg_double2v s, double a, double b, int q, int tk) {
-            put32(far + q * T, tk, cg_double2v{red(s.x + a, m), red(s.y + b, m)});
-        };
-        auto far_get = [&](cg_double2v *s0, int u, int tk) {
+            for (int it = 0; it < E; it++) d0[it] = d1[it] = d2[it] = 0.0;
+            // polynomials of a unit in the order they are transformed: x0, y0, x1, y1 (HAT: x0, x1)
+            constexpr int NT = HAT ? 2 : 4;
+            auto poly = [&](int u, int t) {
+                return HAT ? A.x_poly(u, t) : ((t & 1) ? A.y_poly(u, t >> 1) : A.x_poly(u, t >> 1));
+            };
+            // the first component's sum before unit u, and put back with a pair of that unit's products (below 2 p)
+            auto far_put = [&](const cg_double2v s, double a, double b, int q, int tk) {
+                put32(far + q * T, tk, cg_double2v{red(s.x + a, m), red(s.y + b, m)});
+            };
+            auto far_get = [&](cg_double2v *s0, int u, int tk) {
 #pragma unroll
-            for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
-            if (u != u_first) {
+                for (int q = 0; q < E / 2; q++) s0[q] = cg_double2v{0.0, 0.0};
+                if (u != u_first) {
 #pragma unroll
-                for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
-            }
-        };
-        LiftedRow<LOGN, E> whole;
-        if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, tid);
-        for (int u = u_first; u < u_end; u++) {
-            auto row = [&](double *x, int t) {
-                if constexpr (K == 0) {
-                    whole.finish(x);
-                    whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, tid);
-                } else {
-                    lift_window<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
+                    for (int q = 0; q < E / 2; q++) s0[q] = at_lane(far + q * T, tk);
                 }
             };
-            if constexpr (HAT) {
-                const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
+            LiftedRow<LOGN, E> whole;
+            if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, tid);
+            for (int u = u_first; u < u_end; u++) {
+                auto row = [&](double *x, int t) {
+                    if constexpr (K == 0) {
+                        whole.finish(x);
+                        whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, tid);
+                    } else {
+                        lift_window<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
+                    }
+                };
+                if constexpr (HAT) {
+                    const double *y0 = A.y_hat(u, r, KL), *y1 = y0 + ((size_t)KL << LOGN);
 #pragma unroll
-                for (int t = 0; t < 2; t++) {
-                    double x[E];
-                    row(x, t);
-                    lds_barrier();      // the previous transform's LDS reads
-                    fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
-                    int tk = tid;
-                    asm volatile("" : "+v"(tk));
-                    cg_double2v s0[E / 2];
-                    if (FAR && t == 0) far_get(s0, u, tk);
+                    for (int t = 0; t < 2; t++) {
+                        double x[E];
+                        row(x, t);
+                        lds_barrier();      // the previous transform's LDS reads
+                        fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
+                        int tk = tid;
+                        asm volatile("" : "+v"(tk));
+                        cg_double2v s0[E / 2];
+                        if (FAR && t == 0) far_get(s0, u, tk);
 #pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        const double b0 = at32(y0, chunk_elem<E>(tk, it)), b1 = at32(y1, chunk_elem<E>(tk, it));
-                        x[it] = red(x[it], m);
-                        if (t == 0) {
-                            d1[it] += mulmod(x[it], b1, m);
-                            x[it] = mulmod(x[it], b0, m);
-                            if (!FAR) d0[it] += x[it];
-                            else if (it & 1) far_put(s0[it / 2], x[it - 1], x[it], it / 2, tk);
-                        } else {
-                            d1[it] += mulmod(x[it], b0, m);
-                            d2[it] += mulmod(x[it], b1, m);
+                        for (int it = 0; it < E; it++) {
+                            const double b0 = at32(y0, chunk_elem<E>(tk, it)), b1 = at32(y1, chunk_elem<E>(tk, it));
+                            x[it] = red(x[it], m);
+                            if (t == 0) {
+                                d1[it] += mulmod(x[it], b1, m);
+                                x[it] = mulmod(x[it], b0, m);
+                                if (!FAR) d0[it] += x[it];
+                                else if (it & 1) far_put(s0[it / 2], x[it - 1], x[it], it / 2, tk);
+                            } else {
+                                d1[it] += mulmod(x[it], b0, m);
+                                d2[it] += mulmod(x[it], b1, m);
+                            }
+                        }
+                    }
+                } else {
+                    double keep[E];
+#pragma unroll
+                    for (int t = 0; t < 4; t++) {
+                        double x[E];
+                        row(x, t);
+                        lds_barrier();      // the previous transform's LDS reads
+                        fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
+                        cg_double2v s0[E / 2];
+                        int tk = tid;
+                        asm volatile("" : "+v"(tk));
+                        if (FAR && t == 1) far_get(s0, u, tk);
+#pragma unroll
+                        for (int it = 0; it < E; it++) {
+                            if (t % 2 == 0) x[it] = red(x[it], m);      // (one factor of every product)
+                            if (t == 0) park[tid + it * T] = x[it];
+                            if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
+                            if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
+                            if (t == 3) {
+                                d1[it] += mulmod(park[tid + it * T], x[it], m);
+                                d2[it] += mulmod(x[it], keep[it], m);
+                            }
+                            if (t == 1 || t == 2) keep[it] = x[it];
+                        }
+                        if (FAR && t == 1) {
+#pragma unroll
+                            for (int q = 0; q < E / 2; q++)
+                                far_put(s0[q], mulmod(park[tid + 2 * q * T], x[2 * q], m),
+                                        mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m), q, tk);
                         }
                     }
                 }
-            } else {
-                double keep[E];
 #pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    double x[E];
-                    row(x, t);
-                    lds_barrier();      // the previous transform's LDS reads
-                    fwd_row<LOGN, E, false, PRIO>(lds, x, x, tid, tw, m);
-                    cg_double2v s0[E / 2];
-                    int tk = tid;
-                    asm volatile("" : "+v"(tk));
-                    if (FAR && t == 1) far_get(s0, u, tk);
-#pragma unroll
-                    for (int it = 0; it < E; it++) {
-                        if (t % 2 == 0) x[it] = red(x[it], m);      // (one factor of every product)
-                        if (t == 0) park[tid + it * T] = x[it];
-                        if (!FAR && t == 1) d0[it] += mulmod(park[tid + it * T], x[it], m);
-                        if (t == 2) d1[it] += mulmod(x[it], keep[it], m);
-                        if (t == 3) {
-                            d1[it] += mulmod(park[tid + it * T], x[it], m);
-                            d2[it] += mulmod(x[it], keep[it], m);
-                        }
-                        if (t == 1 || t == 2) keep[it] = x[it];
-                    }
-                    if (FAR && t == 1) {
-#pragma unroll
-                        for (int q = 0; q < E / 2; q++)
-                            far_put(s0[q], mulmod(park[tid + 2 * q * T], x[2 * q], m),
-                                    mulmod(park[tid + (2 * q + 1) * T], x[2 * q + 1], m), q, tk);
-                    }
+                for (int it = 0; it < E; it++) {
+                    if (!FAR) d0[it] = red(d0[it], m);
+                    d1[it] = red(d1[it], m);
+                    d2[it] = red(d2[it], m);
                 }
             }
 #pragma unroll
-            for (int it = 0; it < E; it++) {
-                if (!FAR) d0[it] = red(d0[it], m);
-                d1[it] = red(d1[it], m);
-                d2[it] = red(d2[it], m);
+            for (int q = 0; FAR && q < E / 2; q++) {
+                const cg_double2v v = at_lane(far + q * T, tid);
+                d0[2 * q] = v.x;
+                d0[2 * q + 1] = v.y;
             }
-        }
+            for (int c = 0; c < 3; c++) {
+                // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
+                // registers before any thread stores results over it)
+                lds_barrier();
+                inv_row<LOGN, E, PRIO, 52>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, 0, C);
 #pragma unroll
-        for (int q = 0; FAR && q < E / 2; q++) {
-            const cg_double2v v = at_lane(far + q * T, tid);
-            d0[2 * q] = v.x;
-            d0[2 * q + 1] = v.y;
-        }
-        for (int c = 0; c < 3; c++) {
-            // (before the first one: the previous transform's LDS reads; every thread has its part of the first sum in
-            // registers before any thread stores results over it)
-            lds_barrier();
-            inv_row<LOGN, E, PRIO, 52>(lds, d0, st, (gp * 3 + c) * KL + r, tid, itw, m, 0, C);
-#pragma unroll
-            for (int it = 0; it < E; it++) {
-                d0[it] = d1[it];
-                d1[it] = d2[it];
+                for (int it = 0; it < E; it++) {
+                    d0[it] = d1[it];
+                    d1[it] = d2[it];
+                }
             }
         }
     }
@@ -2575,7 +2595,7 @@ constexpr int PW_THREADS = 256;
 // 96 products, six primes: 199 us (175 from whole rows, 213 with one thread for both of a pair).
 template <int K, bool HALF>
 __global__ void __launch_bounds__(PW_THREADS)
-scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int parts, int acc,
+scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, SumParts S, int acc,
              const DevConst *__restrict__ C)
 {
     constexpr int L = K + 1;
@@ -2584,7 +2604,8 @@ scale_kernel(const double *__restrict__ tens, uint64_t *__restrict__ out, int pa
     const int n = HALF ? chunk * (PW_THREADS / 2) + (tid & (PW_THREADS / 2 - 1)) : chunk * PW_THREADS + tid;
     const bool upper = HALF && __builtin_amdgcn_readfirstlane(tid) >= PW_THREADS / 2;
     const size_t half = HALF ? (size_t)1 << (logn - 1) : 0;
-    const double *src = tens + (((size_t)((bc / 3) * parts * 3 + bc % 3) * (K + L)) << logn);
+    const double *src = tens + (((size_t)((bc / 3) * S.stride * 3 + bc % 3) * (K + L)) << logn);
+    const int parts = S.count(bc / 3);
     double e[K + L];
     // element n; HALF: the pair's sum or difference
     auto at = [&](int i) {

@@ -95,6 +95,25 @@ def test_sums_of_products_in_parts(name, shapes):
             assert np.array_equal(got[g], env.orc.mul_sum([a[u % 3] for u in us], [b[u % 2] for u in us])), (name, groups, group, g)
 
 
+@pytest.mark.parametrize("name,shapes", [("C2", ((13, 8), (16, 9), (5, 36), (8, 25))), ("mixed", ((13, 8), (3, 60))),
+                                         ("k1", ((34, 7), (3, 86)))])
+def test_sums_of_products_in_ranges_across_groups(name, shapes):
+    """units of all groups in equal ranges: groups inside one range, ends of groups and of ranges together and apart"""
+    env = _env(name)
+    a, b = _extremes(env, env.cts(16, 3)), _extremes(env, env.cts(17, 2))
+    for groups, group in shapes:
+        say(f"mul_sum {name}: {groups} groups of {group}")
+        units = np.arange(groups * group)
+        got = env.host(env.ctx.mul_sum(_tiled(env, a, len(units)), _tiled(env, b, len(units)), groups, group))
+        want = {}
+        for g in range(groups):
+            us = units[g * group:(g + 1) * group]
+            key = us[0] % 6                                     # (the operands repeat every six units)
+            if key not in want:
+                want[key] = env.orc.mul_sum([a[u % 3] for u in us], [b[u % 2] for u in us])
+            assert np.array_equal(got[g], want[key]), (name, groups, group, g)
+
+
 @pytest.mark.parametrize("name,batches", [("C2", (31, 32, 65, 96, 130)), ("C1", (42, 43, 100)), ("mixed", (33,))])
 def test_rotations_at_the_edges_of_the_dispatch(name, batches):
     env = _env(name)
