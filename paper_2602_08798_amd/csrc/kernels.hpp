@@ -2154,29 +2154,39 @@ mul_row_kernel(MulRowArgs A, StTens<K == 0> st, const double *__restrict__ tw_al
 // The same for mul_sum_row_kernel, W elements' words on their way while one is lifted.  All workgroups of a round walk over the same
 // units, and those of a unit share its words in one L2: lift_row, which is done sooner with rows modulo ciphertext primes, lets them
 // drift apart (12 groups of 128, N = 8192: 1590 us here, 1650 with lift_row, 1695 with a branch for the ciphertext primes here).
-template <int LOGN, int E, int K, int W>
-__device__ __forceinline__ void lift_window(double *x, const uint64_t *src, int r, int tid, const ModD m, const DevConst *C)
-{
-    constexpr int T = (1 << LOGN) / E;
+// fetch asks for the first W elements, and can do so before the products of the row before, which have the registers to spare: contexts
+// of 12 heads over 128 products, N = 8192, 2282 -> 2267 us, 10: 1902 -> 1892 (W = 5, which fills the registers: 2288); N = 4096,
+// four heads over 64 173.5 -> 167.5, 16: 558 -> 547.
+template <int LOGN, int E, int K, int W> struct LiftedWindow {
+    static constexpr int T = (1 << LOGN) / E;
     uint64_t w[W][K];
-    auto get = [&](int it) {
+    const uint64_t *src;
+    __device__ __forceinline__ void get(int it, int r, int tid)
+    {
 #pragma unroll
-        for (int q = 0; q < K; q++)
-            w[it % W][q] = at_lane(src + ((size_t)LdMulExt<K>::source(r, q) << LOGN) + it * T, tid);
-    };
-#pragma unroll
-    for (int it = 0; it < W; it++) get(it);
-    C = opaque_const(C);
-#pragma unroll
-    for (int it = 0; it < E; it++) {
-        // (kept apart: the compiler would ask for the whole row first and spill what the caller holds)
-        __builtin_amdgcn_sched_barrier(0);
-        x[it] = LdMulExt<K>::lift(w[it % W], r, m, C);
-        __builtin_amdgcn_sched_barrier(0);
-        if (it + W < E) get(it + W);
+        for (int q = 0; q < K; q++) w[it % W][q] = at_lane(src + ((size_t)LdMulExt<K>::source(r, q) << LOGN) + it * T, tid);
     }
-    __builtin_amdgcn_sched_barrier(0);
-}
+    __device__ __forceinline__ void fetch(const uint64_t *poly, int r, int tid)
+    {
+        src = poly;
+#pragma unroll
+        for (int it = 0; it < W; it++) get(it, r, tid);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void finish(double *x, int r, int tid, const ModD m, const DevConst *C)
+    {
+        C = opaque_const(C);
+#pragma unroll
+        for (int it = 0; it < E; it++) {
+            // (kept apart: the compiler would ask for the whole row first and spill what the caller holds)
+            __builtin_amdgcn_sched_barrier(0);
+            x[it] = LdMulExt<K>::lift(w[it % W], r, m, C);
+            __builtin_amdgcn_sched_barrier(0);
+            if (it + W < E) get(it + W, r, tid);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
 
 // How sums' units are divided over the workgroups of a prime.  ranges = 0: every group of `group` units in `stride` parts.  Else the units of
 // all groups form one row, cut into as many ranges of one length wherever groups end: the piece of group g that lies in range w is its part
@@ -2215,6 +2225,7 @@ mul_sum_row_kernel(MulRowArgs A, SumParts S, StTens<K == 0> st, const double *__
     __shared__ double park[HAT ? 1 : 1 << LOGN];
     // prompt context of twelve heads 2303 -> 2284 us; at N = 4096 a step of sixteen heads 175 -> 190 (fwd_pass)
     constexpr bool PRIO = LOGN == 13 && !HAT;
+    constexpr bool AHEAD = K != 0 && !HAT;
     const int tid = threadIdx.x;
     for (int p = blockIdx.x; p < nwg; p += (int)gridDim.x) {
         // (a prime's ranges, or the parts of its groups, one after the other)
@@ -2250,14 +2261,17 @@ mul_sum_row_kernel(MulRowArgs A, SumParts S, StTens<K == 0> st, const double *__
                 }
             };
             LiftedRow<LOGN, E> whole;
+            LiftedWindow<LOGN, E, K ? K : 1, W> part;
             if constexpr (K == 0) whole.fetch(poly(u_first, 0), r, tid);
+            else if constexpr (AHEAD) part.fetch(poly(u_first, 0), r, tid);
             for (int u = u_first; u < u_end; u++) {
                 auto row = [&](double *x, int t) {
                     if constexpr (K == 0) {
                         whole.finish(x);
                         whole.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, tid);
                     } else {
-                        lift_window<LOGN, E, K, W>(x, poly(u, t), r, tid, m, C);
+                        if constexpr (!AHEAD) part.fetch(poly(u, t), r, tid);
+                        part.finish(x, r, tid, m, C);
                     }
                 };
                 if constexpr (HAT) {
@@ -2299,6 +2313,7 @@ mul_sum_row_kernel(MulRowArgs A, SumParts S, StTens<K == 0> st, const double *__
                         int tk = tid;
                         asm volatile("" : "+v"(tk));
                         if (FAR && t == 1) far_get(s0, u, tk);
+                        if constexpr (AHEAD) part.fetch(t + 1 < NT ? poly(u, t + 1) : poly(u + 1 < u_end ? u + 1 : u, 0), r, tid);
 #pragma unroll
                         for (int it = 0; it < E; it++) {
                             if (t % 2 == 0) x[it] = red(x[it], m);      // (one factor of every product)
