@@ -59,18 +59,18 @@ FP64_LANE_INSTR_PER_ITEM = {
     "ntt_fwd<rows>": 472 * 1024,
     "ntt_fwd<rows> to integers": 488 * 1024,
     "ntt_fwd<plain>": 482 * 1024,
-    "ntt_inv<tensor>": 634 * 1024,
-    # tensor products of the n units of a group summed on the way in: 506 besides the units
-    "ntt_inv<tensor_sum>": 506 * 1024,
-    "ntt_inv<tensor_sum> per unit": 163 * 1024,
+    "ntt_inv<tensor>": 581 * 1024,
+    # tensor products of the n units of a group summed on the way in: 482 besides the units
+    "ntt_inv<tensor_sum>": 482 * 1024,
+    "ntt_inv<tensor_sum> per unit": 131 * 1024,
     "ntt_inv<u64>": 554 * 1024,
     "ntt_inv<mul_plain>": 594 * 1024,
-    "ntt_fwd_inv<mul_plain>": 1058 * 1024,
-    "ntt_inv<ks_inner>": 698 * 1024,
+    "ntt_fwd_inv<mul_plain>": 1038 * 1024,
+    "ntt_inv<ks_inner>": 686 * 1024,
     "ntt_inv<f64>": 506 * 1024,
     # rows of products and key switches (averages over the rows modulo ciphertext and auxiliary primes); mul_row with one
     # operand transformed already, as the scores have it
-    "mul_row": 3154 * 1024,
+    "mul_row": 2999 * 1024,
     "ks_row": 2692 * 1024,
     "ks_sum_row": 2572 * 1024,
     "ks_sum_row per rotation": 336 * 1024,

@@ -1604,7 +1604,9 @@ __device__ __forceinline__ void inv_row(double *lds, const double *in, const ST 
 // Key switch of one (unit, prime) per workgroup (digits of one prime): the digits lifted and transformed one after the
 // other, each multiplied with its two key rows into two sums in registers, and the sums transformed back.
 // The transformed digits never reach memory (24 of 35 rows per unit of traffic less) and five transforms follow
-// each other without a launch between them.  Bound by vector issue (70 % busy on 700 units): 1024 threads with
+// each other without a launch between them.  The sums go back together: each wait at a barrier and each factor serves both
+// (with ks_sum_row_kernel and ks_unit_kernel: 768 products with relinearisation 1780 -> 1760 us, a chain step of 12 heads 659 -> 652,
+// scores of 12 heads 9150 -> 9041).  Bound by vector issue (71 % busy on 700 units): 1024 threads with
 // eight elements each, because a row is then 16 registers and the two sums, the row, its factors and the next
 // digit's words fit 128.  768 units at N = 8192, three digits, four primes: 284 + 376 us for the mod-up and inner product
 // launches, 383 us here.
@@ -1769,8 +1771,9 @@ __device__ __forceinline__ void sum_digits(const double *lds, const HoistTab &T,
 // the two sums in registers are transformed back.  With digits through memory (ks_sum_kernel) every rotation's
 // gather of every digit goes to L2, and half of them miss it; here the keys are what comes in, and an XCD works with
 // the keys of one or two primes.  Bound by the keys' way from L2 (128 KB a rotation and digit, 39 bytes a clock and compute unit) and
-// by vector issue (68 % busy); two units to a workgroup halve the first.  N = 8192, 7 rotations, 1536 ciphertexts: mod-up, sums
-// and inverse transforms 475 + 899 + 369 us in three launches, 1513 us here with one unit, 1391 with two.
+// by vector issue (74 % busy with two units); two units to a workgroup halve the first.  N = 8192, 7 rotations, 1536 ciphertexts:
+// mod-up, sums and inverse transforms 475 + 899 + 369 us in three launches, 1513 us here with one unit, 1391 with two (1314
+// since the two sums of a unit are transformed back together).
 // ---------------------------------------------------------------------------
 template <int LOGN, int E, int U>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
@@ -2201,7 +2204,7 @@ struct SumParts {
     }
 };
 
-// Sums of products over the units of a group, one (group, part of it, prime) per workgroup: the operands of a unit
+// Sums of products over the units of a group, one (group, part of it, prime) or (range, prime) per workgroup (SumParts): the operands of a unit
 // transformed as in mul_row_kernel, the three components summed over the units, one inverse transform of each sum.  What
 // the parts of a group leave is summed by scale_kernel.  It saves the transformed operands' way through memory, and
 // its parts spread long groups over the chip.
@@ -2210,7 +2213,7 @@ struct SumParts {
 // once per unit, waits in its own output row, a thread's own 64 bytes of it, from L2.  The words of a polynomial come in through a
 // window of a few elements instead of in two halves at once.  Kernel, 12 groups of 128, N = 8192, three primes: 2100 us with everything
 // in registers, 1890 with the halves one after the other, 1760 with the first sum in memory too, 1640 with the window (2 to 5
-// elements within 3 %).  At N = 4096 registers suffice, and the sum in memory costs 3 % of A V, 12 heads (419 us; 406 in registers).
+// elements within 3 %), 1561 with N^-1 left to the scaling and the window's first words asked for ahead; the vector unit is 62 % busy.  At N = 4096 registers suffice, and the sum in memory costs 3 % of A V, 12 heads (419 us; 406 in registers).
 // With y transformed at N = 16384 three sums beside the row, its factors and y's words spilled 16 registers; with the first one in
 // memory none (mul_sum_parts_half has both sides).
 template <int LOGN, int E, int K, bool HAT>
@@ -3033,8 +3036,9 @@ struct DigitKeys {
 // Key switch of one unit per workgroup, from the ring element to the finished ciphertext: as ks_row_kernel and
 // ks_sum_row_kernel, special prime first, then every ciphertext prime with the division by P and the additions in
 // registers.  The accumulators (L rows of each component written and read again) never reach memory but for the two
-// rows modulo the special prime, and the mod-down launch is gone.  The vector unit is 52 to 56 % busy, less than in those
-// kernels: the addends, asked for after the inverse transform, are exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
+// rows modulo the special prime, and the mod-down launch is gone.  The vector unit is 53 to 56 % busy in rotations and 63 to 66 % in
+// relinearisations, less than in those kernels: the addends, asked for before the last two passes of the inverse transforms
+// (after them, and with one sum at a time: 768 relinearisations 522 us, now 495), are in part exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
 // 588 -> 537, 3 summed rotations 761 -> 680; N = 4096: 166 -> 141, 163 -> 139, 207 -> 160, 7 summed 259 -> 212.
 // ---------------------------------------------------------------------------
 enum KsMode { KS_PLAIN, KS_ROTATE, KS_SUM };
