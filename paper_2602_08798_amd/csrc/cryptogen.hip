@@ -581,12 +581,12 @@ static bool apart(const LdInvF64 &ld, const StInvF64 &st, size_t bytes) { return
                          (const double *)TW, (const DevConst *)c->dc, (int)nwg)
 
 template <class LD, class ST>
-static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes)
+static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, bool whole = false)
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
     if constexpr (in_parts<LD, ST>::value) {
-        switch (c->logn * 10 + (apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, false) : 0)) {
+        switch (c->logn * 10 + (!whole && apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, false) : 0)) {
         case 121: CG_PART(ntt_fwd_part_kernel, 12, 1, c->tw);
         case 122: CG_PART(ntt_fwd_part_kernel, 12, 2, c->tw);
         case 131: CG_PART(ntt_fwd_part_kernel, 13, 1, c->tw);
@@ -620,12 +620,12 @@ static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
 #undef CG_FWD
 }
 template <class LD, class ST>
-static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes)
+static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, bool whole = false)
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
     if constexpr (in_parts<LD, ST>::value) {
-        switch (c->logn * 10 + (apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, true) : 0)) {
+        switch (c->logn * 10 + (!whole && apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, true) : 0)) {
         case 131: CG_PART(ntt_inv_part_kernel, 13, 1, c->itw);
         case 142: CG_PART(ntt_inv_part_kernel, 14, 2, c->itw);
         default: break;
@@ -825,20 +825,25 @@ static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
     CG_KSWIDE(2);
 #undef CG_KSWIDE
 }
+// What runs while a key switch does: nothing, the other branches of a step, or branches whose own mod-ups have a row for every compute
+// unit.  Beside the last, rows are not taken in parts: these repeat a row's first stages on units that the others have work for.  us a step with
+// whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192, 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726;
+// N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
+enum Beside { ALONE = 0, BESIDE, CROWDED };
 // us with the mod-down, N = 16384, six primes, two special ones, three launches / one; 1, 3 and 7 rotations: 16 units (128 compute units
 // idle) 91 / 97, 101 / 113, 127 / 145, 20 (96): 111 / 105, 128 / 121, 161 / 154, 32: 159 / 127, 188 / 143, 240 / 184; 36 (224): 197 / 197,
 // 227 / 230, 286 / 299, 40 (192): 210 / 203, 238 / 237, 300 / 309, 44 (160): 238 / 209, 268 / 242, 343 / 319, 64: 321 / 268, 369 / 309,
 // 473 / 394; 80 (128): 416 / 361, 468 / 417, 595 / 535.
 // beside: in an attention call, beside a step's other branches, heads x ciphertexts.  Summed rotations of one round of workgroups pay sooner
-// there (16 x 1, 128 idle, 1043 / 1024, 12 x 2 1123 / 1115) and those of two later (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555); relinearisations
+// there (12 x 2, 64 idle, 1123 / 1115; at 128 idle the scores of 8 x 2 750 / 790, but the context of 16 x 3, beside 48 units, 1839 / 1724) and those of two later (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555); relinearisations
 // only from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205).
-static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, bool beside)
+static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, Beside beside)
 {
     if (c->logn != 14) return false;
     if (c->dry) return c->dry_rows;
     const size_t rows = (size_t)batch * c->L;
     if (relin && beside && rows <= (size_t)c->n_cu) return false;
-    return rounds_pay(c, rows, IdleLimits{beside ? 128 : 96, 144, 160});
+    return rounds_pay(c, rows, IdleLimits{beside == CROWDED ? 128 : beside ? 112 : 96, 144, 160});
 }
 
 // whole key switches, summed rotations or not, in one launch
@@ -1282,12 +1287,12 @@ static uint32_t inv_mod_pow2(uint32_t g, uint32_t two_n)
 // Mod-up of one ring element per unit (src + b*src_stride, Galois map first when galois != 0): the
 // dnum digits extended to the k+nsp primes and transformed, rows dig[b][dnum][k+nsp][N], canonical
 static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
-                        uint32_t batch, uint64_t *dig)
+                        uint32_t batch, uint64_t *dig, bool whole = false)
 {
     const size_t nrows = (size_t)batch * c->dnum * c->L;
     const double mbytes = (double)limb_bytes(c) * (c->k + (double)c->dnum * c->L) * batch;
     const StU64 st{dig, c->logn};
-#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes)
+#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes, whole)
     switch (c->alpha * 2 + (galois ? 1 : 0)) {
     case 2: CG_MODUP(false, 1);
     case 3: CG_MODUP(true, 1);
@@ -1326,7 +1331,7 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                         const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
                         uint32_t galois_inv, int accumulate, uint32_t batch, void *ws,
-                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0, bool beside = false)
+                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0, Beside beside = ALONE)
 {
     if (!acc_add) { acc_add = add; acc_stride = add_stride; }
     Bump w = bump(c, ws);
@@ -1350,7 +1355,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     } else if (ks_row_wins(c, (size_t)batch * c->L, galois != 0)) {
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
-        CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig));
+        CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig, beside == CROWDED));
         // inner product with the key fused into the inverse transform's load
         const size_t irows = (size_t)batch * 2 * c->L;
         const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows);
@@ -1372,7 +1377,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 }
 
 static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *out2, uint32_t batch,
-                    void *ws, bool beside = false)
+                    void *ws, Beside beside = ALONE)
 {
     const size_t ct3 = (size_t)3 * c->k * c->N;
     return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
@@ -1491,7 +1496,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
 // out_stride as in do_rotate.  ws: (dnum + 2)(k+nsp) rows per ciphertext.
 static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t in_stride, uint32_t n_rot,
                          const uint32_t *gs, const void *const *keys, uint64_t *out2, size_t out_stride,
-                         uint32_t batch, void *ws, bool beside = false)
+                         uint32_t batch, void *ws, Beside beside = ALONE)
 {
     const size_t ct2 = (size_t)2 * c->k * c->N;
     if (!in_stride) in_stride = ct2;
@@ -1517,14 +1522,15 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     } else if (ks_sum_row_wins(c, batch)) {
         CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
     } else {
-        CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig));
+        const bool whole = beside == CROWDED;
+        CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig, whole));
         const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
         CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
         const size_t irows = (size_t)batch * 2 * c->L;
         // few rows are transformed in parts, and so not in place: two digits' rows have room for the results
-        double *to = c->dnum >= 2 && row_parts(c, irows, true) ? reinterpret_cast<double *>(dig) : acc;
+        double *to = !whole && c->dnum >= 2 && row_parts(c, irows, true) ? reinterpret_cast<double *>(dig) : acc;
         CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{to, c->logn}, KID_INV_F64,
-                          LB * 2.0 * irows));
+                          LB * 2.0 * irows, whole));
         A.acc = to;
     }
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
@@ -1812,7 +1818,7 @@ static bool fold_keys_ok(const FoldRounds &R, const void *const *keys)
 }
 // x0 holds the start value; rounds ping-pong between x0 and x1, the last result lands in `out`
 static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint64_t *out, const FoldRounds &R,
-                      const void *const *keys, uint32_t batch, void *ws, bool beside = false)
+                      const void *const *keys, uint32_t batch, void *ws, Beside beside = ALONE)
 {
     uint64_t *cur = x0, *nxt = x1;
     for (int r = 0; r < R.n_rounds; r++) {
@@ -1877,8 +1883,8 @@ static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_
     uint64_t *d3 = w.take<uint64_t>((size_t)3 * c->k * batch);
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * batch), *xb = w.take<uint64_t>((size_t)2 * c->k * batch);
     CG_TRY(do_mul(c, s, q, kc, d3, batch, n_cts, w.p, 0, n_cts, cache_stride_cts, kext));
-    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, true));
-    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, true);
+    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, BESIDE));
+    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, BESIDE);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
 }
 extern "C" int cg_decode_scores(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, uint32_t heads,
@@ -1929,8 +1935,9 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
         CG_LAUNCH_PW(KID_SUM_GROUPS, (double)limb_bytes(c) * rows * (batch + heads), (double)batch, sum_groups_kernel,
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
-    CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, true));
-    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, true);
+    const Beside beside = (size_t)batch * c->dnum * c->L > (size_t)c->n_cu ? CROWDED : BESIDE;
+    CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, beside));
+    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p);
 }
 extern "C" int cg_decode_context(cg_ctx *c, void *stream, const uint64_t *a, const uint64_t *vc, uint32_t heads,
@@ -2021,12 +2028,16 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     // Branches are always joined, also after a failed launch, so that the caller's stream never
     // runs ahead of work this call started.
     // The longer chain runs on the caller's stream, where it waits for no event and none waits for it, and is issued first.  That is the
-    // context's where it has no fewer key switches, until the scores' take more than one round of workgroups each.  us a step with
-    // the scores there / the context, d2 = 64, heads x ciphertexts: N = 8192, chains 12 x 4 (192 rows) 652 / 619, 1 x 1 297 / 284, rounds 12 x 4
-    // 423 / 411, 8 x 1 210 / 202, 12 x 6 (288) 585 / 590, 12 x 8 700 / 698 ... 695 / 702; N = 4096, 12 x 4 (144) 188 / 176, 12 x 8 (288) 259 / 266;
-    // N = 16384, 1 x 1 281 / 261, 4 x 1 396 / 386, 16 x 3 (384) 1770 / 1777.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
+    // context's where it has no fewer key switches and the launches of both chains are short (few), or where its own fill the chip as well (full);
+    // else the scores', of n_cts times the units.  us a step with the scores there / the context, d2 = 64, heads x ciphertexts: few, N = 8192,
+    // 8 x 1 (32 rows) 212 / 202, 4 x 4 (64) 370 / 352, 16 x 2 (128) 378 / 370; N = 16384, 1 x 1 278 / 262, 4 x 1 386 / 382, but 8 x 2 (128) 766 / 800; full,
+    // N = 8192, 12 x 4 (192) chains 652 / 619, rounds 423 / 411, 12 x 5 rounds 530 / 514, 14 x 3 (168) 427 / 412; between them 12 x 3 (144) 365 / 380,
+    // 4 x 12 (192) 375 / 394, 11 x 4 (176) 400 / 422, 6 x 7 (168) 373 / 402; above 12 x 6 (288) 585 / 590; N = 4096, 3 x 28 (252) 206 / 218,
+    // 12 x 7 (252) 225 / 233.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
     auto switches = [](uint32_t slots, uint32_t w) { const uint32_t bits = 31 - __builtin_clz(slots); return w ? (bits + w - 1) / w : bits; };
-    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (size_t)heads * n_cts * c->L <= (size_t)c->n_cu;
+    const size_t srows = (size_t)heads * n_cts * c->L, own = (size_t)heads * c->dnum * c->L, n = (size_t)c->n_cu;
+    const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, full = c->logn == 13 && 16 * own >= 9 * n && 8 * srows >= 5 * n && srows <= n;
+    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || full);
     auto scores_on = [&](hipStream_t st) {
         return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w);
     };

@@ -2594,7 +2594,9 @@ ntt_inv_part_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevC
 // Loaders that bring in a word or two per element.  Those that work for an element (lifts, tensor and inner products) would do so 2^LS
 // times: one product at N = 8192, four parts, operands 13.7 -> 13.1 us, tensor product 12.6 -> 15.3, inner product 11.1 -> 12.9.
 template <> struct in_parts<LdRowsU64, StU64> { static constexpr bool value = true; };
-template <bool G, int A> struct in_parts<LdModup<G, A>, StU64> { static constexpr bool value = true; };
+// (not mod-ups with a map: chains of rotations of 4 x 4 ciphertexts, N = 8192, 353 us a step with whole rows, 371 in parts; 4 x 1, N = 16384,
+// 653 / 738)
+template <int A> struct in_parts<LdModup<false, A>, StU64> { static constexpr bool value = true; };
 template <> struct in_parts<LdInvU64, StInvU64> { static constexpr bool value = true; };
 template <> struct in_parts<LdInvF64, StInvF64> { static constexpr bool value = true; };
 

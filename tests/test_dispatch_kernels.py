@@ -43,8 +43,8 @@ WANT = {
     # key switches at N = 16384: single transforms' launches while more than 3/8 of the compute units would idle in one round, 9/16 in two
     **{("n16384_k6", "sum", b): "ks_sum_kernel<3, " for b in (4, 19, 33, 45)},
     **{("n16384_k6", "sum", b): "ks_wide_kernel<2>" for b in (20, 32, 46, 64, 80)},
-    # ... in an attention call half of them idle in one round, and relinearisations from the second round on
-    ("n16384_k6", "scores_rounds", 15, 1): "ks_sum_kernel<3, ", ("n16384_k6", "scores_rounds", 16, 1): "ks_wide_kernel<2>",
+    # ... in an attention call 7/16 of them idle in one round, and relinearisations from the second round on
+    ("n16384_k6", "scores_rounds", 17, 1): "ks_sum_kernel<3, ", ("n16384_k6", "scores_rounds", 18, 1): "ks_wide_kernel<2>",
     ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",
     # operands: no more rows than compute units on 1024 threads; both kinds of rows in one launch up to two per unit
     ("n8192_k3", "extend", 18): "ntt_fwd_kernel<13, 8, LdMulExt<3>, StF64>",
