@@ -66,6 +66,12 @@ WANT = {
     # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8
     **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
     **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
+    # the context's key switches in parts until the scores' mod-ups have a row for every compute unit; one launch for 16 at N = 16384 beside these
+    ("n8192_k3", "context_ext", 7, 3): "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>, StU64>",
+    ("n8192_k3", "context_ext", 7, 4): "ntt_fwd_kernel<13, 8, LdModup<false, 1>, StU64>",
+    ("n8192_k3", "context_ext", 6, 3): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>",
+    ("n8192_k3", "context_ext", 6, 4): "ntt_inv_kernel<13, 8, LdInvF64, StInvF64>",
+    ("n16384_k6", "context_ext", 16, 2): "ks_wide_kernel<2>",
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
     **{("n16384_k6", "context_ext", h, c): "mul_sum_row_kernel<13, 8, 0, true>" for h, c in ((4, 4), (8, 3), (12, 2), (16, 3))},
