@@ -825,8 +825,8 @@ static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
     CG_KSWIDE(2);
 #undef CG_KSWIDE
 }
-// What runs while a key switch does: nothing, the other branches of a step, or branches whose own mod-ups have a row for every compute
-// unit.  Beside the last, rows are not taken in parts: these repeat a row's first stages on units that the others have work for.  us a step with
+// What runs while a key switch does: nothing (a call made alone, of whatever kind), the other branches of a step, or branches whose own mod-ups
+// have a row for every compute unit; step_impl says which.  Beside the last, rows are not taken in parts: these repeat a row's first stages on units that the others have work for.  us a step with
 // whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192, 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726;
 // N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
 enum Beside { ALONE = 0, BESIDE, CROWDED };
@@ -834,7 +834,8 @@ enum Beside { ALONE = 0, BESIDE, CROWDED };
 // idle) 91 / 97, 101 / 113, 127 / 145, 20 (96): 111 / 105, 128 / 121, 161 / 154, 32: 159 / 127, 188 / 143, 240 / 184; 36 (224): 197 / 197,
 // 227 / 230, 286 / 299, 40 (192): 210 / 203, 238 / 237, 300 / 309, 44 (160): 238 / 209, 268 / 242, 343 / 319, 64: 321 / 268, 369 / 309,
 // 473 / 394; 80 (128): 416 / 361, 468 / 417, 595 / 535.
-// beside: in an attention call, beside a step's other branches, heads x ciphertexts.  Summed rotations of one round of workgroups pay sooner
+// Alone, contexts of 16 heads in rounds, 1, 2, 3 ciphertexts: 630 / 715, 698 / 791, 770 / 861; scores of 18 products 589 / 621.
+// beside: in a step, heads x ciphertexts.  Summed rotations of one round of workgroups pay sooner
 // there (12 x 2, 64 idle, 1123 / 1115; at 128 idle the scores of 8 x 2 750 / 790, but the context of 16 x 3, beside 48 units, 1839 / 1724) and those of two later (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555); relinearisations
 // only from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205).
 static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, Beside beside)
@@ -1863,7 +1864,7 @@ extern "C" int cg_round_galois(const cg_ctx *c, int which, uint32_t d2, uint32_t
 // w != 0: the folding sum in rounds of w bits (fold_rounds), gk_fold holding the rounds' keys
 static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, const double *kext,
                        uint32_t heads, uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
-                       const void *const *gk_fold, uint64_t *out, void *ws, uint32_t fold_w = 0)
+                       const void *const *gk_fold, uint64_t *out, void *ws, uint32_t fold_w = 0, Beside beside = ALONE)
 {
     CG_REQUIRE(c && ptrs_ok({q, kext ? (const void *)kext : (const void *)kc, rlk, out, ws}) && gk_fold &&
                heads >= 1 && n_cts >= 1 && pow2_d(c, d2));
@@ -1883,8 +1884,8 @@ static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_
     uint64_t *d3 = w.take<uint64_t>((size_t)3 * c->k * batch);
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * batch), *xb = w.take<uint64_t>((size_t)2 * c->k * batch);
     CG_TRY(do_mul(c, s, q, kc, d3, batch, n_cts, w.p, 0, n_cts, cache_stride_cts, kext));
-    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, BESIDE));
-    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, BESIDE);
+    CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, beside));
+    if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
 }
 extern "C" int cg_decode_scores(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, uint32_t heads,
@@ -1905,7 +1906,7 @@ extern "C" int cg_decode_scores_ext(cg_ctx *c, void *stream, const uint64_t *q, 
 static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64_t *vc, const double *vext,
                         uint32_t heads, uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
                         const void *const *gk_block, uint64_t *out, void *ws, uint32_t fold_w = 0,
-                        bool sum_first = false)
+                        bool sum_first = false, Beside beside = ALONE)
 {
     CG_REQUIRE(c && ptrs_ok({a, vext ? (const void *)vext : (const void *)vc, rlk, out, ws}) && gk_block &&
                heads >= 1 && n_cts >= 1 && pow2_d(c, d2));
@@ -1935,7 +1936,6 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
         CG_LAUNCH_PW(KID_SUM_GROUPS, (double)limb_bytes(c) * rows * (batch + heads), (double)batch, sum_groups_kernel,
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
-    const Beside beside = (size_t)batch * c->dnum * c->L > (size_t)c->n_cu ? CROWDED : BESIDE;
     CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p);
@@ -2039,11 +2039,11 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, full = c->logn == 13 && 16 * own >= 9 * n && 8 * srows >= 5 * n && srows <= n;
     const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || full);
     auto scores_on = [&](hipStream_t st) {
-        return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w);
+        return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, BESIDE);
     };
     auto context_on = [&](hipStream_t st) {
         return context_impl(c, st, a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block, context, ws_context,
-                            block_w, sum_first);
+                            block_w, sum_first, (size_t)heads * n_cts * c->dnum * c->L > n ? CROWDED : BESIDE);
     };
     int rc = context_first ? context_on(s) : scores_on(s);
     const int rc1 = context_first ? scores_on(side[0]) : context_on(side[0]);

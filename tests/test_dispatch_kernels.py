@@ -43,9 +43,11 @@ WANT = {
     # key switches at N = 16384: single transforms' launches while more than 3/8 of the compute units would idle in one round, 9/16 in two
     **{("n16384_k6", "sum", b): "ks_sum_kernel<3, " for b in (4, 19, 33, 45)},
     **{("n16384_k6", "sum", b): "ks_wide_kernel<2>" for b in (20, 32, 46, 64, 80)},
-    # ... in an attention call 7/16 of them idle in one round, and relinearisations from the second round on
-    ("n16384_k6", "scores_rounds", 17, 1): "ks_sum_kernel<3, ", ("n16384_k6", "scores_rounds", 18, 1): "ks_wide_kernel<2>",
-    ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",
+    # ... in calls made alone as well (other limits beside a step's branches)
+    **{("n16384_k6", "scores_rounds", b, 1): "ks_sum_kernel<3, " for b in (16, 17, 18, 19)}, ("n16384_k6", "scores_rounds", 16, 2): "ks_wide_kernel<2>",
+    **{("n16384_k6", "context_ext", 16, c): "ks_sum_kernel<3, " for c in (1, 2, 3)}, ("n16384_k6", "context_ext", 19, 1): "ks_sum_kernel<3, ",
+    # ... where relinearisations stay with them up to one round
+    ("n16384_k6", "step", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",
     # operands: no more rows than compute units on 1024 threads; both kinds of rows in one launch up to two per unit
     ("n8192_k3", "extend", 18): "ntt_fwd_kernel<13, 8, LdMulExt<3>, StF64>",
     ("n8192_k3", "extend", 19): "ntt_fwd_kernel<13, 16, LdMulExt<3>, StF64>",
@@ -66,15 +68,20 @@ WANT = {
     # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8
     **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
     **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
-    # the context's key switches in parts until the scores' mod-ups have a row for every compute unit; one launch for 16 at N = 16384 beside these
-    ("n8192_k3", "context_ext", 7, 3): "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>, StU64>",
-    ("n8192_k3", "context_ext", 7, 4): "ntt_fwd_kernel<13, 8, LdModup<false, 1>, StU64>",
-    ("n8192_k3", "context_ext", 6, 3): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>",
-    ("n8192_k3", "context_ext", 6, 4): "ntt_inv_kernel<13, 8, LdInvF64, StInvF64>",
-    ("n16384_k6", "context_ext", 16, 2): "ks_wide_kernel<2>",
+    # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; one launch for 16 at N = 16384 beside these
+    **{("n8192_k3", op, 7, c): "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>, StU64>" for op, c in (("context_ext", 3), ("context_ext", 4), ("step", 3))},
+    **{("n8192_k3", op, 6, c): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>" for op, c in (("context_ext", 3), ("context_ext", 4), ("step", 3))},
+    ("n16384_k6", "step", 16, 3): "ks_wide_kernel<2>",
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
     **{("n16384_k6", "context_ext", h, c): "mul_sum_row_kernel<13, 8, 0, true>" for h, c in ((4, 4), (8, 3), (12, 2), (16, 3))},
+}
+# ... -> kernels that are not among them
+NEVER = {
+    **{("n16384_k6", "scores_rounds", b, 1): "ks_wide_kernel" for b in (16, 17, 18, 19)}, **{("n16384_k6", "context_ext", 16, c): "ks_wide_kernel" for c in (1, 2, 3)},
+    ("n16384_k6", "context_ext", 19, 1): "ks_wide_kernel",
+    ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",      # (its relinearisation)
+    ("n8192_k3", "step", 7, 4): "ntt_fwd_part_kernel", ("n8192_k3", "step", 6, 4): "ntt_inv_part_kernel",
 }
 
 
@@ -104,8 +111,11 @@ def _launches(lib):
                      ctx, None, d, d, None, u32(h), u32(c), u32(c), u32(64), u32(3), d, keys, out, d),
                  "scores": lambda h, c: lib.lib.cg_decode_scores(ctx, None, d, d, u32(h), u32(c), u32(c), u32(64), d, keys, out, d),
                  "context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
-                     ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d)}
-        for s, op, *sizes in WANT:
+                     ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d),
+                 "step": lambda h, c: lib.lib.cg_decode_step_hoisted(
+                     ctx, None, d, d, d, d, u32(h), u32(c), u32(c + 1), u32(64), u32(c * (1 << log2n) // 64 - 1), d, d, d, u32(3), keys, u32(3),
+                     1, keys, out, out, d)}
+        for s, op, *sizes in {**WANT, **NEVER}:
             if s == name:
                 got[" ".join(map(str, (s, op, *sizes)))] = lib.kernels(lambda: calls[op](*sizes))
         if name == "n8192_k3":
@@ -124,6 +134,12 @@ def launches(tmp_path_factory):
 def test_kernel(launches, case):
     names = [k[0] for k in launches[" ".join(map(str, case))]]
     assert any(n.startswith(WANT[case]) for n in names), names
+
+
+@pytest.mark.parametrize("case", NEVER, ids=lambda c: " ".join(map(str, c)))
+def test_other_kernels(launches, case):
+    names = [k[0] for k in launches[" ".join(map(str, case))]]
+    assert names and not any(n.startswith(NEVER[case]) for n in names), names
 
 
 def test_copies_are_not_timed_as_sums(launches):
