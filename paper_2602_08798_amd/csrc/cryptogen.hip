@@ -831,7 +831,8 @@ static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
 // N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
 enum Beside { ALONE = 0, BESIDE, CROWDED };
 // us with the mod-down, N = 16384, six primes, two special ones, three launches / one; 1, 3 and 7 rotations: 16 units (128 compute units
-// idle) 91 / 97, 101 / 113, 127 / 145, 20 (96): 111 / 105, 128 / 121, 161 / 154, 32: 159 / 127, 188 / 143, 240 / 184; 36 (224): 197 / 197,
+// idle) 88 / 99, 101 / 122, 126 / 165, 20 (96): 108 / 108, 126 / 130, 160 / 172, 21 (88): 111 / 109, 130 / 131, 164 / 175, 22 (80): 128 / 113, 146 / 135,
+// 181 / 178, 26 (48): 136 / 119, 158 / 141, 210 / 184, relinearisations of 21 and 22 101 / 101, 113 / 102; 36 (224): 197 / 197,
 // 227 / 230, 286 / 299, 40 (192): 210 / 203, 238 / 237, 300 / 309, 44 (160): 238 / 209, 268 / 242, 343 / 319, 64: 321 / 268, 369 / 309,
 // 473 / 394; 80 (128): 416 / 361, 468 / 417, 595 / 535.
 // Alone, contexts of 16 heads in rounds, 1, 2, 3 ciphertexts: 630 / 715, 698 / 791, 770 / 861; scores of 18 products 589 / 621.
@@ -844,7 +845,7 @@ static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, Beside bes
     if (c->dry) return c->dry_rows;
     const size_t rows = (size_t)batch * c->L;
     if (relin && beside && rows <= (size_t)c->n_cu) return false;
-    return rounds_pay(c, rows, IdleLimits{beside == CROWDED ? 128 : beside ? 112 : 96, 144, 160});
+    return rounds_pay(c, rows, IdleLimits{beside == CROWDED ? 128 : beside ? 112 : 80, 144, 160});
 }
 
 // whole key switches, summed rotations or not, in one launch

@@ -40,9 +40,9 @@ WANT = {
     # ... not where the results land on the rows that are read
     ("n8192_k3", "fwd_in_place", 12): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
     ("n8192_k3", "inv_in_place", 12): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
-    # key switches at N = 16384: single transforms' launches while more than 3/8 of the compute units would idle in one round, 9/16 in two
-    **{("n16384_k6", "sum", b): "ks_sum_kernel<3, " for b in (4, 19, 33, 45)},
-    **{("n16384_k6", "sum", b): "ks_wide_kernel<2>" for b in (20, 32, 46, 64, 80)},
+    # key switches at N = 16384: single transforms' launches while more than 5/16 of the compute units would idle in one round, 9/16 in two
+    **{("n16384_k6", "sum", b): "ks_sum_kernel<3, " for b in (4, 20, 21, 33, 45)},
+    **{("n16384_k6", "sum", b): "ks_wide_kernel<2>" for b in (22, 32, 46, 64, 80)},
     # ... in calls made alone as well (other limits beside a step's branches)
     **{("n16384_k6", "scores_rounds", b, 1): "ks_sum_kernel<3, " for b in (16, 17, 18, 19)}, ("n16384_k6", "scores_rounds", 16, 2): "ks_wide_kernel<2>",
     **{("n16384_k6", "context_ext", 16, c): "ks_sum_kernel<3, " for c in (1, 2, 3)}, ("n16384_k6", "context_ext", 19, 1): "ks_sum_kernel<3, ",

@@ -17,8 +17,8 @@ SETS = {"C5": PRESETS["C5"],
                                 p=tuple(ntt_primes(1 << 49, 2 << 14, 1)), alpha=1)}
 
 
-# rows per unit: C5 8, one_special 3; one round of 256 compute units from 160 rows on, two from 368
-@pytest.mark.parametrize("name,batches", [("C5", (19, 20, 32, 46, 80)), ("one_special", (53, 54, 85, 125))])
+# rows per unit: C5 8, one_special 3; one round of 256 compute units from 176 rows on, two from 368
+@pytest.mark.parametrize("name,batches", [("C5", (21, 22, 32, 46, 80)), ("one_special", (58, 59, 85, 125))])
 def test_summed_rotations_and_relinearisations(name, batches):
     import paper_2602_08798_amd as P
     from oracle import Oracle
