@@ -825,27 +825,35 @@ static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
     CG_KSWIDE(2);
 #undef CG_KSWIDE
 }
-// What runs while a key switch does: nothing (a call made alone, of whatever kind), the other branches of a step, or branches whose own mod-ups
-// have a row for every compute unit; step_impl says which.  Beside the last, rows are not taken in parts: these repeat a row's first stages on units that the others have work for.  us a step with
-// whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192, 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726;
-// N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
-enum Beside { ALONE = 0, BESIDE, CROWDED };
+// What runs while a key switch does: nothing (a call made alone, of whatever kind), or the other branches of a step; step_impl says which.
+// crowd: their mod-ups have a row for every compute unit.  Beside such, rows are not taken in parts: these repeat a row's first stages on units
+// that the others have work for.  us a step with whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192,
+// 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726; N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
+// wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
+struct Beside {
+    bool others = false, crowd = false, wide = false;
+};
 // us with the mod-down, N = 16384, six primes, two special ones, three launches / one; 1, 3 and 7 rotations: 16 units (128 compute units
 // idle) 88 / 99, 101 / 122, 126 / 165, 20 (96): 108 / 108, 126 / 130, 160 / 172, 21 (88): 111 / 109, 130 / 131, 164 / 175, 22 (80): 128 / 113, 146 / 135,
 // 181 / 178, 26 (48): 136 / 119, 158 / 141, 210 / 184, relinearisations of 21 and 22 101 / 101, 113 / 102; 36 (224): 197 / 197,
 // 227 / 230, 286 / 299, 40 (192): 210 / 203, 238 / 237, 300 / 309, 44 (160): 238 / 209, 268 / 242, 343 / 319, 64: 321 / 268, 369 / 309,
 // 473 / 394; 80 (128): 416 / 361, 468 / 417, 595 / 535.
 // Alone, contexts of 16 heads in rounds, 1, 2, 3 ciphertexts: 630 / 715, 698 / 791, 770 / 861; scores of 18 products 589 / 621.
-// beside: in a step, heads x ciphertexts.  Summed rotations of one round of workgroups pay sooner
-// there (12 x 2, 64 idle, 1123 / 1115; at 128 idle the scores of 8 x 2 750 / 790, but the context of 16 x 3, beside 48 units, 1839 / 1724) and those of two later (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555); relinearisations
-// only from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205).
+// In a step, us of the whole step, heads x ciphertexts; six primes unless said.  The scores' summed rotations of one round pay a little sooner: 10 x 2
+// (96 idle) 977 / 942, 7 x 3 (88) 872 / 859, 5 x 4 833 / 837, 2 x 10 772 / 784, four primes 9 x 3 (94) 745 / 730; at 104 and 112 idle as many lose (3 x 6 733 / 755,
+// 6 x 3 815 / 830, 18 x 1 1165 / 1180) as gain (9 x 2 871 / 846).  The context's sooner still where the scores' take whole units already (wide): 15 x 2 (136 idle)
+// 1365 / 1333, with a transformed cache 1382 / 1408, 15 x 4 2085 / 2055, 16 x 2 (128) 1409 / 1381, 16 x 3 1853 / 1768, 16 x 4 2273 / 2218, 17 x 5 (120) 2945 / 2813, four primes 20 x 2
+// (136) 1130 / 1108, 21 x 3 (130) 1466 / 1439; 14 x 2 (144) 1289 / 1291, with a transformed cache 1289 / 1329.  Where they do not, never: 16 x 1 1015 / 1085, 17 x 1 1113 / 1152,
+// four primes 22 x 2 1202 / 1250, 23 x 2 1260 / 1280, two 43 x 2 1172 / 1202, 47 x 2 1249 / 1286.  Relinearisations only
+// from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205); two rounds no sooner than
+// at 144 idle (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555).
 static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, Beside beside)
 {
     if (c->logn != 14) return false;
     if (c->dry) return c->dry_rows;
     const size_t rows = (size_t)batch * c->L;
-    if (relin && beside && rows <= (size_t)c->n_cu) return false;
-    return rounds_pay(c, rows, IdleLimits{beside == CROWDED ? 128 : beside ? 112 : 80, 144, 160});
+    if (relin && beside.others && rows <= (size_t)c->n_cu) return false;
+    return rounds_pay(c, rows, IdleLimits{beside.wide ? 136 : beside.others ? 96 : 80, 144, 160});
 }
 
 // whole key switches, summed rotations or not, in one launch
@@ -1333,7 +1341,7 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                         const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
                         uint32_t galois_inv, int accumulate, uint32_t batch, void *ws,
-                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0, Beside beside = ALONE)
+                        const uint64_t *acc_add = nullptr, size_t acc_stride = 0, Beside beside = {})
 {
     if (!acc_add) { acc_add = add; acc_stride = add_stride; }
     Bump w = bump(c, ws);
@@ -1357,7 +1365,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     } else if (ks_row_wins(c, (size_t)batch * c->L, galois != 0)) {
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
-        CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig, beside == CROWDED));
+        CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig, beside.crowd));
         // inner product with the key fused into the inverse transform's load
         const size_t irows = (size_t)batch * 2 * c->L;
         const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows);
@@ -1379,7 +1387,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 }
 
 static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *out2, uint32_t batch,
-                    void *ws, Beside beside = ALONE)
+                    void *ws, Beside beside = {})
 {
     const size_t ct3 = (size_t)3 * c->k * c->N;
     return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
@@ -1498,7 +1506,7 @@ static int do_rotate_hoisted(cg_ctx *c, hipStream_t s, const uint64_t *in2, size
 // out_stride as in do_rotate.  ws: (dnum + 2)(k+nsp) rows per ciphertext.
 static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t in_stride, uint32_t n_rot,
                          const uint32_t *gs, const void *const *keys, uint64_t *out2, size_t out_stride,
-                         uint32_t batch, void *ws, Beside beside = ALONE)
+                         uint32_t batch, void *ws, Beside beside = {})
 {
     const size_t ct2 = (size_t)2 * c->k * c->N;
     if (!in_stride) in_stride = ct2;
@@ -1524,7 +1532,7 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     } else if (ks_sum_row_wins(c, batch)) {
         CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
     } else {
-        const bool whole = beside == CROWDED;
+        const bool whole = beside.crowd;
         CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig, whole));
         const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
         CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
@@ -1820,7 +1828,7 @@ static bool fold_keys_ok(const FoldRounds &R, const void *const *keys)
 }
 // x0 holds the start value; rounds ping-pong between x0 and x1, the last result lands in `out`
 static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint64_t *out, const FoldRounds &R,
-                      const void *const *keys, uint32_t batch, void *ws, Beside beside = ALONE)
+                      const void *const *keys, uint32_t batch, void *ws, Beside beside = {})
 {
     uint64_t *cur = x0, *nxt = x1;
     for (int r = 0; r < R.n_rounds; r++) {
@@ -1865,7 +1873,7 @@ extern "C" int cg_round_galois(const cg_ctx *c, int which, uint32_t d2, uint32_t
 // w != 0: the folding sum in rounds of w bits (fold_rounds), gk_fold holding the rounds' keys
 static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, const double *kext,
                        uint32_t heads, uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
-                       const void *const *gk_fold, uint64_t *out, void *ws, uint32_t fold_w = 0, Beside beside = ALONE)
+                       const void *const *gk_fold, uint64_t *out, void *ws, uint32_t fold_w = 0, Beside beside = {})
 {
     CG_REQUIRE(c && ptrs_ok({q, kext ? (const void *)kext : (const void *)kc, rlk, out, ws}) && gk_fold &&
                heads >= 1 && n_cts >= 1 && pow2_d(c, d2));
@@ -1907,7 +1915,7 @@ extern "C" int cg_decode_scores_ext(cg_ctx *c, void *stream, const uint64_t *q, 
 static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64_t *vc, const double *vext,
                         uint32_t heads, uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
                         const void *const *gk_block, uint64_t *out, void *ws, uint32_t fold_w = 0,
-                        bool sum_first = false, Beside beside = ALONE)
+                        bool sum_first = false, Beside beside = {})
 {
     CG_REQUIRE(c && ptrs_ok({a, vext ? (const void *)vext : (const void *)vc, rlk, out, ws}) && gk_block &&
                heads >= 1 && n_cts >= 1 && pow2_d(c, d2));
@@ -2039,12 +2047,14 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const size_t srows = (size_t)heads * n_cts * c->L, own = (size_t)heads * c->dnum * c->L, n = (size_t)c->n_cu;
     const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, full = c->logn == 13 && 16 * own >= 9 * n && 8 * srows >= 5 * n && srows <= n;
     const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || full);
+    const Beside by_context{true}, by_scores{true, (size_t)heads * n_cts * c->dnum * c->L > n,
+                                             fold_w && ks_wide_wins(c, heads * n_cts, false, by_context)};
     auto scores_on = [&](hipStream_t st) {
-        return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, BESIDE);
+        return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, by_context);
     };
     auto context_on = [&](hipStream_t st) {
         return context_impl(c, st, a, vcache, vext, heads, n_cts, cache_stride_cts, d2, rlk, gk_block, context, ws_context,
-                            block_w, sum_first, (size_t)heads * n_cts * c->dnum * c->L > n ? CROWDED : BESIDE);
+                            block_w, sum_first, by_scores);
     };
     int rc = context_first ? context_on(s) : scores_on(s);
     const int rc1 = context_first ? scores_on(side[0]) : context_on(side[0]);
