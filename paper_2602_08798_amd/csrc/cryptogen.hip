@@ -2036,17 +2036,23 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     if (!append_first) CG_HIP(hipStreamWaitEvent(side[1], c->ev_fork, 0));
     // Branches are always joined, also after a failed launch, so that the caller's stream never
     // runs ahead of work this call started.
-    // The longer chain runs on the caller's stream, where it waits for no event and none waits for it, and is issued first.  That is the
-    // context's where it has no fewer key switches and the launches of both chains are short (few), or where its own fill the chip as well (full);
-    // else the scores', of n_cts times the units.  us a step with the scores there / the context, d2 = 64, heads x ciphertexts: few, N = 8192,
-    // 8 x 1 (32 rows) 212 / 202, 4 x 4 (64) 370 / 352, 16 x 2 (128) 378 / 370; N = 16384, 1 x 1 278 / 262, 4 x 1 386 / 382, but 8 x 2 (128) 766 / 800; full,
-    // N = 8192, 12 x 4 (192) chains 652 / 619, rounds 423 / 411, 12 x 5 rounds 530 / 514, 14 x 3 (168) 427 / 412; between them 12 x 3 (144) 365 / 380,
-    // 4 x 12 (192) 375 / 394, 11 x 4 (176) 400 / 422, 6 x 7 (168) 373 / 402; above 12 x 6 (288) 585 / 590; N = 4096, 3 x 28 (252) 206 / 218,
-    // 12 x 7 (252) 225 / 233.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
+    // One branch runs on the caller's stream, where it waits for no event and none waits for it, and is issued first: the scores, of n_cts times
+    // the units, or the context, where it has no fewer key switches and the launches of both chains are short (few), or where the scores' key switches
+    // (a workgroup per unit and prime) take one round and leave the context's mod-ups no room beside them (over: both together 5/4 of the compute
+    // units and more), so that what is issued behind waits.  us a step with the scores there / the context, heads x ciphertexts (rows of the
+    // scores + of the context's mod-ups): few, N = 8192, 8 x 1 (32) 212 / 202, 4 x 4 (64) 370 / 352, 16 x 2 (128) 378 / 370; N = 16384, 1 x 1
+    // 278 / 262, 4 x 1 386 / 382, but 8 x 2 (128) 766 / 800.  over, N = 8192, three primes, rounds, with a transformed cache, chains:
+    // 8 x 7 (224 + 96) 465 / 444, 447 / 432, 665 / 654; 10 x 5 (200 + 120) 442 / 436, 440 / 433, 643 / 648; 12 x 4 (192 + 144) 429 / 429,
+    // 429 / 419, 640 / 632; 13 x 4 (208 + 156) 481 / 463, 476 / 463, 679 / 669; 16 x 4 (256 + 192) 531 / 523, 553 / 542, 763 / 752.  Below: 11 x 4 (176 + 132)
+    // 407 / 431, 405 / 402, 632 / 633; 9 x 5 (180 + 108) 402 / 429, 389 / 390, 609 / 624; 6 x 8 (192 + 72) 395 / 400, 383 / 392, 573 / 587; beyond a round
+    // of the scores 11 x 6 (264) 570 / 589, 563 / 574, 832 / 846; 12 x 6 (288) 594 / 619, 587 / 604, 873 / 883.  Two primes 14 x 6 (252 + 84) 471 / 442, 454 / 436,
+    // 612 / 615; four 10 x 4 (200 + 200) 545 / 536, 527 / 522, 827 / 809, 7 x 5 (175 + 140) 457 / 492, 437 / 445, 683 / 701, but 11 x 3 (165 + 220) 559 / 575, 550 / 553,
+    // 761 / 753; in digits of two primes 1 % either way.  N = 4096, where two workgroups share a unit, 8 x 8 (192 + 48) 198 / 185, 183 / 188, 305 / 301, 12 x 7 (252)
+    // 225 / 233.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
     auto switches = [](uint32_t slots, uint32_t w) { const uint32_t bits = 31 - __builtin_clz(slots); return w ? (bits + w - 1) / w : bits; };
     const size_t srows = (size_t)heads * n_cts * c->L, own = (size_t)heads * c->dnum * c->L, n = (size_t)c->n_cu;
-    const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, full = c->logn == 13 && 16 * own >= 9 * n && 8 * srows >= 5 * n && srows <= n;
-    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || full);
+    const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, over = c->logn == 13 && 4 * (srows + own) >= 5 * n && srows <= n;
+    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || over);
     const Beside by_context{true}, by_scores{true, (size_t)heads * n_cts * c->dnum * c->L > n,
                                              fold_w && ks_wide_wins(c, heads * n_cts, false, by_context)};
     auto scores_on = [&](hipStream_t st) {

@@ -1,5 +1,6 @@
 """Which streams the one-call decode step puts its branches on, and what they wait for.  Runs without a GPU: the library's
 host code against a recording stand-in for the runtime."""
+import ctypes as C
 import json
 import sys
 
@@ -31,12 +32,41 @@ def _record(lib):
            for c in range(2) for stream in (0, S1, S2) for opens in (False, True) for hoisted in (False, True)}
     for h in ctx:
         assert lib.lib.cg_destroy(h) == 0
+    got["context first"] = _context_first(lib)
+    return got
+
+
+# heads x ciphertexts at N = 8192 -> the context on the caller's stream: few rows of the scores (units x 4 primes, up to half of 256 compute units), or these in
+# one round and with the context's mod-ups (heads x 12 rows) 5/4 of the units
+ORDER = {True: ((4, 4), (16, 2), (8, 7), (8, 8), (9, 6), (10, 5), (12, 4), (14, 3), (16, 4)),
+         False: ((3, 11), (11, 3), (11, 4), (9, 5), (8, 6), (6, 8), (13, 3), (9, 8), (11, 6), (13, 5))}
+
+
+def _context_first(lib):
+    from workloads import PRESETS
+    prm, keys, got = PRESETS["C2"], (vp * 64)(*[1 << 20] * 64), []
+    ctx = lib.create(prm)
+    for h, c in ORDER[True] + ORDER[False]:
+        entries = lib.log(lambda: lib.lib.cg_decode_step_hoisted(
+            ctx, vp(S1), d, d, d, None, u32(h), u32(c), u32(c), u32(64), u32(c * prm.n // 64 - 1), d, d, d, u32(3), keys, u32(3), 1, keys, d, d, d))
+        scaled = {}                  # blocks of a scaling (more with more results) -> stream
+        for i, (_, stream, _) in enumerate(entries):
+            blocks, threads = u32(), u32()
+            if b"scale_kernel" in lib.stub.stub_log_kernel(C.c_size_t(i), C.byref(blocks), C.byref(threads)):
+                scaled[blocks.value] = stream
+        got.append([h, c, scaled[min(scaled)] == S1 and scaled[max(scaled)] != S1])
+    assert lib.lib.cg_destroy(ctx) == 0
     return got
 
 
 @pytest.fixture(scope="module")
-def log(tmp_path_factory):
-    got = run(__file__, tmp_path_factory.mktemp("stub"))
+def recorded(tmp_path_factory):
+    return run(__file__, tmp_path_factory.mktemp("stub"))
+
+
+@pytest.fixture(scope="module")
+def log(recorded):
+    got = {k: v for k, v in recorded.items() if k != "context first"}
     return {tuple(int(v) for v in k.split(",")): [tuple(e) for e in v] for k, v in got.items()}
 
 
@@ -79,6 +109,10 @@ def test_branches_fork_from_and_join_the_callers_stream(log):
         assert joined == _streams(entries, stream)
         assert all(i < entries.index(next(x for x in entries if x[0] == 2 and x[1] == stream)) for s, i in
                    last_work.items() if s != stream)
+
+
+def test_which_branch_runs_on_the_callers_stream(recorded):
+    assert [x for x in recorded["context first"] if x[2] != ((x[0], x[1]) in ORDER[True])] == []
 
 
 if __name__ == "__main__":
