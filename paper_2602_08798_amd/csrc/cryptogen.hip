@@ -551,18 +551,27 @@ static int ntt_elems(const cg_ctx *c) { return c->elems; }
 // have a compute unit each, four at most, two in an inverse transform at N = 8192 and none at N = 4096.  us a launch, whole rows / parts.
 // Forward, N = 4096: 12 rows 6.0 / 5.5 (four), 100: 6.2 / 5.5 (two); N = 8192: 12 7.5 / 5.5, 64 7.8 / 5.6, 65 ... 128 rows 8.2 / 6.4 ... 8.4 / 6.9;
 // N = 16384: 12 11.8 / 6.4, 64 12.6 / 8.2, 128 13.8 / 11.0.  Inverse, N = 4096: 12 rows 6.0 / 6.6, 100: 6.0 / 5.7 (two); N = 8192: 12 7.7 / 6.0 (four:
-// 7.4), 64 8.1 / 6.5; N = 16384: 12 13.5 / 10.1, 64 14.5 / 11.3 (four), 100 15.1 / 12.2 (two).  Inverse transforms only up to a third of
-// the compute units at N = 8192 and a quarter at N = 16384: they are the summed rotations' of a step, whose other branches the work
-// done twice holds up (12 heads, 96 rows: 420.3 us a step whole, 423.5 in parts; alone 8.3 / 7.1 a launch).  At N = 8192 also where whole rows
-// would take a second round for up to 3/8 of the compute units, and halves take one and a half: 260 rows 16.7 / 15.4, 340: 17.3 / 15.9,
-// 384: 17.7 / 17.0, 448: 17.8 / 19.8; 36 matrices of a projection (288 rows) 241 / 236 a call.
+// 7.4), 64 8.1 / 6.5, 88 8.6 / 7.0, 128 8.7 / 7.6, 136 8.8 / 10.0; N = 16384: 12 13.5 / 10.1, 64 14.3 / 11.7 (four), 72 14.7 / 15.6.  At N = 8192 also where
+// whole rows would take a second round for up to 3/8 of the compute units, and halves take one and a half: 260 rows 16.7 / 15.4, 340: 17.3 / 15.9,
+// 384: 17.7 / 17.0, 448: 17.8 / 19.8.
 static int row_parts(const cg_ctx *c, size_t rows, bool inverse)
 {
     const size_t n = (size_t)c->n_cu;
     if (c->dry) return 0;
-    if (inverse && c->logn == 13) return 3 * rows <= n || (rows > n && 8 * rows <= 11 * n) ? 1 : 0;
+    if (inverse && c->logn == 13) return 2 * rows <= n || (rows > n && 8 * rows <= 11 * n) ? 1 : 0;
     if (inverse) return c->logn == 14 && 4 * rows <= n ? 2 : 0;
     return 4 * rows <= n ? 2 : 2 * rows <= n ? 1 : 0;
+}
+// The same for the accumulators of summed rotations: written a launch before they come from L2, where every part's own gather of them
+// costs more than for callers' rows.  us a series, 7 rotations, N = 8192: 1 ciphertext (8 rows) 24.1 / 23.7, 4 (32) 27.0 / 26.8, 6 (48) 30.1 / 30.4,
+// 8 (64) 31.5 / 33.3, 10 (80) 33.6 / 36.0, 12 (96) 35.8 / 37.5; 36 (288) 69.6 / 66.7, 41 (328) 75.9 / 73.8.  N = 16384: 1 (16) 40.2 / 38.8, 4 (64)
+// 54.8 / 53.7; beside a step's other branches, which the work done twice holds up, 1 x 1 274 / 268, 3 x 1 361 / 361, 3 x 3 (48) 520 / 530, 4 x 1 (64)
+// 377 / 384.
+static int acc_parts(const cg_ctx *c, size_t rows, bool others)
+{
+    const size_t n = (size_t)c->n_cu;
+    if (c->logn == 13 && !c->dry) return 8 * rows <= n || (rows > n && 8 * rows <= 11 * n) ? 1 : 0;
+    return c->logn == 14 && !c->dry && (others ? 8 : 4) * rows <= n ? 2 : 0;
 }
 // two device ranges share at least one byte
 static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
@@ -580,13 +589,14 @@ static bool apart(const LdInvF64 &ld, const StInvF64 &st, size_t bytes) { return
     return launch_kernel(KERNEL<LG, LS, LD, ST>, dim3((unsigned)nwg << LS), dim3(1u << (LG - LS - 3)), s, ld, st, \
                          (const double *)TW, (const DevConst *)c->dc, (int)nwg)
 
+// parts: of a row (row_parts), where loader and storer allow them
 template <class LD, class ST>
-static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, bool whole = false)
+static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, int parts = 0)
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
     if constexpr (in_parts<LD, ST>::value) {
-        switch (c->logn * 10 + (!whole && apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, false) : 0)) {
+        switch (c->logn * 10 + (parts && apart(ld, st, nwg * limb_bytes(c)) ? parts : 0)) {
         case 121: CG_PART(ntt_fwd_part_kernel, 12, 1, c->tw);
         case 122: CG_PART(ntt_fwd_part_kernel, 12, 2, c->tw);
         case 131: CG_PART(ntt_fwd_part_kernel, 13, 1, c->tw);
@@ -620,12 +630,12 @@ static int launch_fwd(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
 #undef CG_FWD
 }
 template <class LD, class ST>
-static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, bool whole = false)
+static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int kid, double bytes, int parts = 0)
 {
     if (nwg == 0) return CG_OK;
     ProfScope ps(c, s, kid, bytes, (double)nwg);
     if constexpr (in_parts<LD, ST>::value) {
-        switch (c->logn * 10 + (!whole && apart(ld, st, nwg * limb_bytes(c)) ? row_parts(c, nwg, true) : 0)) {
+        switch (c->logn * 10 + (parts && apart(ld, st, nwg * limb_bytes(c)) ? parts : 0)) {
         case 131: CG_PART(ntt_inv_part_kernel, 13, 1, c->itw);
         case 142: CG_PART(ntt_inv_part_kernel, 14, 2, c->itw);
         default: break;
@@ -1302,7 +1312,7 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     const size_t nrows = (size_t)batch * c->dnum * c->L;
     const double mbytes = (double)limb_bytes(c) * (c->k + (double)c->dnum * c->L) * batch;
     const StU64 st{dig, c->logn};
-#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes, whole)
+#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes, whole ? 0 : row_parts(c, nrows, false))
     switch (c->alpha * 2 + (galois ? 1 : 0)) {
     case 2: CG_MODUP(false, 1);
     case 3: CG_MODUP(true, 1);
@@ -1538,9 +1548,10 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
         CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
         const size_t irows = (size_t)batch * 2 * c->L;
         // few rows are transformed in parts, and so not in place: two digits' rows have room for the results
-        double *to = !whole && c->dnum >= 2 && row_parts(c, irows, true) ? reinterpret_cast<double *>(dig) : acc;
+        const int parts = !whole && c->dnum >= 2 ? acc_parts(c, irows, beside.others) : 0;
+        double *to = parts ? reinterpret_cast<double *>(dig) : acc;
         CG_TRY(launch_inv(c, s, irows, LdInvF64{acc, c->L, c->logn}, StInvF64{to, c->logn}, KID_INV_F64,
-                          LB * 2.0 * irows, whole));
+                          LB * 2.0 * irows, parts));
         A.acc = to;
     }
     // reads: the accumulators and the ciphertext (the permuted reads of c0 come from LDS)
@@ -1601,9 +1612,9 @@ static int public_transform(cg_ctx *c, void *stream, const uint64_t *in, uint64_
     }
     if (!inverse)
         return launch_fwd(c, s, n_limbs, LdRowsU64{in, tab, (int)period, c->logn}, StU64{out, c->logn}, KID_FWD_ROWS,
-                          2.0 * limb_bytes(c) * n_limbs);
+                          2.0 * limb_bytes(c) * n_limbs, row_parts(c, n_limbs, false));
     return launch_inv(c, s, n_limbs, LdInvU64{in, tab, (int)period, c->logn}, StInvU64{out, c->logn}, KID_INV_U64,
-                      2.0 * limb_bytes(c) * n_limbs);
+                      2.0 * limb_bytes(c) * n_limbs, row_parts(c, n_limbs, true));
 }
 extern "C" int cg_ntt_forward(cg_ctx *c, void *stream, const uint64_t *in, uint64_t *out, const uint32_t *idx,
                               uint32_t n_limbs)

@@ -29,14 +29,19 @@ WANT = {
     **{("n4096_k2", "sum", b): "ks_sum_row_kernel<12, 8, 1>" for b in (64, 200, 400)},
     # the tensor product of no more rows than compute units on 1024 threads
     ("n8192_k3", "mul", 12): TENSOR.format(8), ("n8192_k3", "mul", 13): TENSOR.format(16),
-    # transforms: rows in four parts up to a quarter of the compute units, in two up to half; inverse at N = 8192 in two up to a
-    # third and from one row per unit to 11/8, at N = 16384 in four up to a quarter
+    # transforms: rows in four parts up to a quarter of the compute units, in two up to half; inverse at N = 8192 in two up to
+    # half and from one row per unit to 11/8, at N = 16384 in four up to a quarter
     **{("n8192_k3", "fwd", r): f"ntt_fwd_part_kernel<13, {p}, LdRowsU64, StU64>" for r, p in ((1, 2), (64, 2), (65, 1), (128, 1))},
     ("n8192_k3", "fwd", 129): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
-    **{("n8192_k3", "inv", r): "ntt_inv_part_kernel<13, 1, LdInvU64, StInvU64>" for r in (1, 85, 257, 352)},
-    **{("n8192_k3", "inv", r): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>" for r in (86, 256, 353)},
+    **{("n8192_k3", "inv", r): "ntt_inv_part_kernel<13, 1, LdInvU64, StInvU64>" for r in (1, 86, 128, 257, 352)},
+    **{("n8192_k3", "inv", r): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>" for r in (129, 256, 353)},
     ("n4096_k2", "fwd", 64): "ntt_fwd_part_kernel<12, 2, LdRowsU64, StU64>", ("n4096_k2", "inv", 1): "ntt_inv_kernel<12, 8, LdInvU64, StInvU64>",
     ("n16384_k6", "inv", 64): "ntt_inv_part_kernel<14, 2, LdInvU64, StInvU64>", ("n16384_k6", "inv", 65): "ntt_inv_kernel<14, 16, LdInvU64, StInvU64>",
+    # ... accumulators of summed rotations (8 and 16 rows a unit) up to an eighth, at N = 16384 alone up to a quarter
+    **{("n8192_k3", "sum", b): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>" for b in (1, 4, 33, 41)},
+    **{("n8192_k3", "sum", b): "ntt_inv_kernel<13, 8, LdInvF64, StInvF64>" for b in (5, 10, 32)},
+    ("n16384_k6", "sum", 3): "ntt_inv_part_kernel<14, 2, LdInvF64, StInvF64>", ("n16384_k6", "sum", 5): "ntt_inv_kernel<14, 16, LdInvF64, StInvF64>",
+    ("n16384_k6", "step", 2, 1): "ntt_inv_part_kernel<14, 2, LdInvF64, StInvF64>",
     # ... not where the results land on the rows that are read
     ("n8192_k3", "fwd_in_place", 12): "ntt_fwd_kernel<13, 8, LdRowsU64, StU64>",
     ("n8192_k3", "inv_in_place", 12): "ntt_inv_kernel<13, 8, LdInvU64, StInvU64>",
@@ -71,7 +76,7 @@ WANT = {
     # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; at N = 16384 in one launch, up to 17/32 idle, where
     # the scores' take one launch (up to 3/8)
     **{("n8192_k3", op, 7, c): "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>, StU64>" for op, c in (("context_ext", 3), ("context_ext", 4), ("step", 3))},
-    **{("n8192_k3", op, 6, c): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>" for op, c in (("context_ext", 3), ("context_ext", 4), ("step", 3))},
+    **{("n8192_k3", op, 4, c): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>" for op, c in (("context_ext", 5), ("context_ext", 6), ("step", 5))},
     **{("n16384_k6", "step", h, c): "ks_wide_kernel<2>" for h, c in ((16, 3), (10, 2))}, ("n16384_k6", "step", 14, 2): "ks_sum_kernel<3, ",
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
@@ -84,7 +89,7 @@ NEVER = {
     ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",      # (its relinearisation)
     **{("n16384_k6", "step", h, c): "ks_wide_kernel" for h, c in ((16, 1), (17, 1), (17, 2), (19, 1), (9, 2))},
     **{("n16384_k6", "step", h, c): "ks_sum_kernel" for h, c in ((15, 2), (16, 2), (16, 3))},
-    ("n8192_k3", "step", 7, 4): "ntt_fwd_part_kernel", ("n8192_k3", "step", 6, 4): "ntt_inv_part_kernel",
+    ("n8192_k3", "step", 7, 4): "ntt_fwd_part_kernel", ("n8192_k3", "step", 4, 6): "ntt_inv_part_kernel", ("n16384_k6", "step", 3, 1): "ntt_inv_part_kernel",
 }
 
 
