@@ -851,9 +851,9 @@ struct Beside {
 // Alone, contexts of 16 heads in rounds, 1, 2, 3 ciphertexts: 630 / 715, 698 / 791, 770 / 861; scores of 18 products 589 / 621.
 // In a step, us of the whole step, heads x ciphertexts; six primes unless said.  The scores' summed rotations of one round pay a little sooner: 10 x 2
 // (96 idle) 977 / 942, 7 x 3 (88) 872 / 859, 5 x 4 833 / 837, 2 x 10 772 / 784, four primes 9 x 3 (94) 745 / 730; at 104 and 112 idle as many lose (3 x 6 733 / 755,
-// 6 x 3 815 / 830, 18 x 1 1165 / 1180) as gain (9 x 2 871 / 846).  The context's sooner still where the scores' take whole units already (wide): 15 x 2 (136 idle)
-// 1365 / 1333, with a transformed cache 1382 / 1408, 15 x 4 2085 / 2055, 16 x 2 (128) 1409 / 1381, 16 x 3 1853 / 1768, 16 x 4 2273 / 2218, 17 x 5 (120) 2945 / 2813, four primes 20 x 2
-// (136) 1130 / 1108, 21 x 3 (130) 1466 / 1439; 14 x 2 (144) 1289 / 1291, with a transformed cache 1289 / 1329.  Where they do not, never: 16 x 1 1015 / 1085, 17 x 1 1113 / 1152,
+// 6 x 3 815 / 830, 18 x 1 1165 / 1180) as gain (9 x 2 871 / 846).  The context's sooner still where the scores' take whole units already (wide): 16 x 2 (128
+// idle) 1409 / 1381, with a transformed cache 1419 / 1400, 16 x 3 1853 / 1768, 16 x 4 2273 / 2218, 17 x 5 (120) 2945 / 2813, 18 x 3 (112) 2056 / 2027; mixed above: 15 x 2 (136)
+// 1365 / 1333, with a transformed cache 1382 / 1408, 15 x 4 2085 / 2055, 2009 / 2021, 14 x 2 (144) 1289 / 1291, 1289 / 1329.  Where they do not, never: 16 x 1 1015 / 1085, 17 x 1 1113 / 1152,
 // four primes 22 x 2 1202 / 1250, 23 x 2 1260 / 1280, two 43 x 2 1172 / 1202, 47 x 2 1249 / 1286.  Relinearisations only
 // from the second round on (14 x 2, 32 idle, 1269 / 1300, 16 x 2 1372 / 1411; 16 x 3, 128 in the second, 1797 / 1766, 16 x 4 2279 / 2205); two rounds no sooner than
 // at 144 idle (11 x 4, 160 idle, 1675 / 1684, 10 x 4 1506 / 1555).
@@ -863,7 +863,7 @@ static bool ks_wide_wins(const cg_ctx *c, uint32_t batch, bool relin, Beside bes
     if (c->dry) return c->dry_rows;
     const size_t rows = (size_t)batch * c->L;
     if (relin && beside.others && rows <= (size_t)c->n_cu) return false;
-    return rounds_pay(c, rows, IdleLimits{beside.wide ? 136 : beside.others ? 96 : 80, 144, 160});
+    return rounds_pay(c, rows, IdleLimits{beside.wide ? 128 : beside.others ? 96 : 80, 144, 160});
 }
 
 // whole key switches, summed rotations or not, in one launch

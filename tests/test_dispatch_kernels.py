@@ -73,11 +73,11 @@ WANT = {
     # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8
     **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
     **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
-    # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; at N = 16384 in one launch, up to 17/32 idle, where
+    # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; at N = 16384 in one launch, up to half idle, where
     # the scores' take one launch (up to 3/8)
     **{("n8192_k3", op, 7, c): "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>, StU64>" for op, c in (("context_ext", 3), ("context_ext", 4), ("step", 3))},
     **{("n8192_k3", op, 4, c): "ntt_inv_part_kernel<13, 1, LdInvF64, StInvF64>" for op, c in (("context_ext", 5), ("context_ext", 6), ("step", 5))},
-    **{("n16384_k6", "step", h, c): "ks_wide_kernel<2>" for h, c in ((16, 3), (10, 2))}, ("n16384_k6", "step", 14, 2): "ks_sum_kernel<3, ",
+    **{("n16384_k6", "step", h, c): "ks_wide_kernel<2>" for h, c in ((16, 3), (10, 2))}, ("n16384_k6", "step", 15, 2): "ks_sum_kernel<3, ",
     # a transformed cache at N = 16384: parts of one unit each (the fewest that are as fast), and of several
     **{("n16384_k6", "context_ext", h, c): "mul_row_kernel<13, 8, 0, true>" for h, c in ((1, 1), (1, 4), (2, 4), (3, 2), (16, 1))},
     **{("n16384_k6", "context_ext", h, c): "mul_sum_row_kernel<13, 8, 0, true>" for h, c in ((4, 4), (8, 3), (12, 2), (16, 3))},
@@ -88,7 +88,7 @@ NEVER = {
     ("n16384_k6", "context_ext", 19, 1): "ks_wide_kernel",
     ("n16384_k6", "scores_rounds", 16, 2): "ntt_inv_kernel<14, 16, LdInvKsInner<3>, StInvF64>",      # (its relinearisation)
     **{("n16384_k6", "step", h, c): "ks_wide_kernel" for h, c in ((16, 1), (17, 1), (17, 2), (19, 1), (9, 2))},
-    **{("n16384_k6", "step", h, c): "ks_sum_kernel" for h, c in ((15, 2), (16, 2), (16, 3))},
+    **{("n16384_k6", "step", h, c): "ks_sum_kernel" for h, c in ((16, 2), (16, 3), (16, 5))},
     ("n8192_k3", "step", 7, 4): "ntt_fwd_part_kernel", ("n8192_k3", "step", 4, 6): "ntt_inv_part_kernel", ("n16384_k6", "step", 3, 1): "ntt_inv_part_kernel",
 }
 
