@@ -2048,7 +2048,7 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     // Branches are always joined, also after a failed launch, so that the caller's stream never
     // runs ahead of work this call started.
     // One branch runs on the caller's stream, where it waits for no event and none waits for it, and is issued first: the scores, of n_cts times
-    // the units, or the context, where it has no fewer key switches and the launches of both chains are short (few), or where the scores' key switches
+    // the units, or the context, where it has more dependent key switches and the launches of both chains are short (few), or where the scores' key switches
     // (a workgroup per unit and prime) take one round and leave the context's mod-ups no room beside them (over: both together 5/4 of the compute
     // units and more), so that what is issued behind waits.  us a step with the scores there / the context, heads x ciphertexts (rows of the
     // scores + of the context's mod-ups): few, N = 8192, 8 x 1 (32) 212 / 202, 4 x 4 (64) 370 / 352, 16 x 2 (128) 378 / 370; N = 16384, 1 x 1
@@ -2059,11 +2059,14 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     // of the scores 11 x 6 (264) 570 / 589, 563 / 574, 832 / 846; 12 x 6 (288) 594 / 619, 587 / 604, 873 / 883.  Two primes 14 x 6 (252 + 84) 471 / 442, 454 / 436,
     // 612 / 615; four 10 x 4 (200 + 200) 545 / 536, 527 / 522, 827 / 809, 7 x 5 (175 + 140) 457 / 492, 437 / 445, 683 / 701, but 11 x 3 (165 + 220) 559 / 575, 550 / 553,
     // 761 / 753; in digits of two primes 1 % either way.  N = 4096, where two workgroups share a unit, 8 x 8 (192 + 48) 198 / 185, 183 / 188, 305 / 301, 12 x 7 (252)
-    // 225 / 233.  d2 = 128 (a key switch less than the scores): chains 2 x 5 318 / 327.
+    // 225 / 233.  As many key switches in both (longer): N = 8192, rounds of 4 bits, 6 x 3 229 / 249, 4 x 4 with a transformed cache 208 / 223, 16 x 1 275 / 286,
+    // but 2 x 4 181 / 169; N = 16384, d2 = 128, 2 x 3 407 / 430, 3 x 3 512 / 548, 4 x 3 666 / 679, but 1 x 1 282 / 270.  N = 4096 (d2 = 64), where the host's pace counts,
+    // 10 x 3 156 / 149, 14 x 3 171 / 161, on a slower one 167 / 167, 172 / 167.  A key switch less than the scores (d2 = 128): chains 2 x 5 318 / 327.
     auto switches = [](uint32_t slots, uint32_t w) { const uint32_t bits = 31 - __builtin_clz(slots); return w ? (bits + w - 1) / w : bits; };
     const size_t srows = (size_t)heads * n_cts * c->L, own = (size_t)heads * c->dnum * c->L, n = (size_t)c->n_cu;
     const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, over = c->logn == 13 && 4 * (srows + own) >= 5 * n && srows <= n;
-    const bool context_first = switches(c->N / d2, block_w) >= switches(d2, fold_w) && (few || over);
+    const uint32_t own_switches = switches(c->N / d2, block_w), their = switches(d2, fold_w);
+    const bool longer = own_switches > their || (c->logn == 12 && own_switches == their), context_first = longer && (few || over);
     const Beside by_context{true}, by_scores{true, (size_t)heads * n_cts * c->dnum * c->L > n,
                                              fold_w && ks_wide_wins(c, heads * n_cts, false, by_context)};
     auto scores_on = [&](hipStream_t st) {

@@ -40,22 +40,27 @@ def _record(lib):
 # one round and with the context's mod-ups (heads x 12 rows) 5/4 of the units
 ORDER = {True: ((4, 4), (16, 2), (8, 7), (8, 8), (9, 6), (10, 5), (12, 4), (14, 3), (16, 4)),
          False: ((3, 11), (11, 3), (11, 4), (9, 5), (8, 6), (6, 8), (13, 3), (9, 8), (11, 6), (13, 5))}
+# ... while the context has more key switches one after the other: parameters, heads, ciphertexts, d2, bits of a round -> whether it has
+LONGER = {("C2", 6, 3, 64, 3): True, ("C2", 6, 3, 64, 4): False, ("C2", 6, 3, 128, 3): False, ("C2", 12, 4, 64, 4): False, ("C5", 3, 3, 64, 3): True,
+          ("C5", 3, 3, 128, 3): False, ("C1", 4, 4, 64, 3): True, ("C1", 4, 4, 128, 3): False}
 
 
 def _context_first(lib):
     from workloads import PRESETS
-    prm, keys, got = PRESETS["C2"], (vp * 64)(*[1 << 20] * 64), []
-    ctx = lib.create(prm)
-    for h, c in ORDER[True] + ORDER[False]:
+    keys, got = (vp * 64)(*[1 << 20] * 64), []
+    ctx = {name: lib.create(PRESETS[name]) for name in ("C1", "C2", "C5")}
+    for name, h, c, d2, bits in [("C2", h, c, 64, 3) for h, c in ORDER[True] + ORDER[False]] + list(LONGER):
         entries = lib.log(lambda: lib.lib.cg_decode_step_hoisted(
-            ctx, vp(S1), d, d, d, None, u32(h), u32(c), u32(c), u32(64), u32(c * prm.n // 64 - 1), d, d, d, u32(3), keys, u32(3), 1, keys, d, d, d))
+            ctx[name], vp(S1), d, d, d, None, u32(h), u32(c), u32(c), u32(d2), u32(c * PRESETS[name].n // d2 - 1), d, d, d, u32(bits), keys, u32(bits), 1,
+            keys, d, d, d))
         scaled = {}                  # blocks of a scaling (more with more results) -> stream
         for i, (_, stream, _) in enumerate(entries):
             blocks, threads = u32(), u32()
             if b"scale_kernel" in lib.stub.stub_log_kernel(C.c_size_t(i), C.byref(blocks), C.byref(threads)):
                 scaled[blocks.value] = stream
-        got.append([h, c, scaled[min(scaled)] == S1 and scaled[max(scaled)] != S1])
-    assert lib.lib.cg_destroy(ctx) == 0
+        got.append([[name, h, c, d2, bits], scaled[min(scaled)] == S1 and scaled[max(scaled)] != S1])
+    for h in ctx.values():
+        assert lib.lib.cg_destroy(h) == 0
     return got
 
 
@@ -112,7 +117,8 @@ def test_branches_fork_from_and_join_the_callers_stream(log):
 
 
 def test_which_branch_runs_on_the_callers_stream(recorded):
-    assert [x for x in recorded["context first"] if x[2] != ((x[0], x[1]) in ORDER[True])] == []
+    want = {**{("C2", *shape, 64, 3): first for first in ORDER for shape in ORDER[first]}, **LONGER}
+    assert {tuple(case): first for case, first in recorded["context first"]} == want
 
 
 if __name__ == "__main__":
