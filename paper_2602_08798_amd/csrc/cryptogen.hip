@@ -544,6 +544,16 @@ static unsigned ntt_grid(cg_ctx *c, size_t nwg, int threads)
     const size_t resident = (size_t)per_cu * (size_t)c->n_cu;
     return (unsigned)(nwg < resident ? nwg : resident);
 }
+// What runs beside a product or a key switch: nothing (a call made alone, of whatever kind), or the other branches of a step; step_impl says which.
+// crowd: their mod-ups have a row for every compute unit.  Beside such, rows are not taken in parts: these repeat a row's first stages on units
+// that the others have work for.  us a step with whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192,
+// 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726; N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
+// longer: theirs is the chain with more dependent key switches, which the step waits for.
+// wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
+struct Beside {
+    bool others = false, crowd = false, wide = false, longer = false;
+};
+
 // elements per thread for this context's transforms
 static int ntt_elems(const cg_ctx *c) { return c->elems; }
 
@@ -835,14 +845,6 @@ static int launch_ks_wide(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
     CG_KSWIDE(2);
 #undef CG_KSWIDE
 }
-// What runs while a key switch does: nothing (a call made alone, of whatever kind), or the other branches of a step; step_impl says which.
-// crowd: their mod-ups have a row for every compute unit.  Beside such, rows are not taken in parts: these repeat a row's first stages on units
-// that the others have work for.  us a step with whole rows / parts in the context's key switches, heads x ciphertexts: N = 8192,
-// 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726; N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
-// wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
-struct Beside {
-    bool others = false, crowd = false, wide = false;
-};
 // us with the mod-down, N = 16384, six primes, two special ones, three launches / one; 1, 3 and 7 rotations: 16 units (128 compute units
 // idle) 88 / 99, 101 / 122, 126 / 165, 20 (96): 108 / 108, 126 / 130, 160 / 172, 21 (88): 111 / 109, 130 / 131, 164 / 175, 22 (80): 128 / 113, 146 / 135,
 // 181 / 178, 26 (48): 136 / 119, 158 / 141, 210 / 184, relinearisations of 21 and 22 101 / 101, 113 / 102; 36 (224): 197 / 197,
@@ -1012,16 +1014,16 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
     }
 }
 
-// mul_row_kernel; beside: in an attention call, which runs beside other branches.  us of a product with its scaling, three
+// mul_row_kernel; cached: in an attention call, where it pays with more units idle, beside other branches and alone.  us of a product with its scaling, three
 // launches / one.  N = 8192, three primes: 19 products (123 units idle) 66.5 / 63.7, 42 (218): 103 / 119, 52 (148): 125 / 122, 55
 // (127): 130 / 123.  N = 4096, three primes: 20 (116) 37.9 / 39.7, 23 (95): 40.4 / 39.9, 42 (218): 54.9 / 60.5, 49 (169): 67.4 / 62.0;
-// two: 27 (121) 35.8 / 35.6, 58 (222): 51.7 / 53.3, 68 (172): 58.4 / 54.2.  Chain step of 12 heads (48 products, 176 idle in
-// the second round) 686 / 656.  A row of 16384 leaves no registers for what these kernels keep.
-static bool mul_row_wins(const cg_ctx *c, size_t rows, bool beside)
+// two: 27 (121) 35.8 / 35.6, 58 (222): 51.7 / 53.3, 68 (172): 58.4 / 54.2.  48 products over a cache (176 idle in
+// the second round): chain step of 12 heads 686 / 656, scores alone 307 / 294; 49 (169) 340 / 315, 44 (204) 295 / 294.  A row of 16384 leaves no registers for what these kernels keep.
+static bool mul_row_wins(const cg_ctx *c, size_t rows, bool cached)
 {
     if (c->logn > 13 || c->k > 3) return false;
     if (c->dry) return c->dry_rows;
-    return rounds_pay(c, rows, c->logn == 13 ? IdleLimits{128, beside ? 192 : 128, 256}
+    return rounds_pay(c, rows, c->logn == 13 ? IdleLimits{128, cached ? 192 : 128, 256}
                              : c->k == 3 ? IdleLimits{102, 176, 256} : IdleLimits{128, 256, 256});
 }
 // ks_row_kernel.  A rotation gains less than a relinearisation: its digits are scattered through LDS, with two barriers
@@ -1159,14 +1161,16 @@ static uint32_t mul_sum_parts_half(const cg_ctx *c, uint32_t groups, uint32_t gr
 }
 
 // Sums of products with a transformed cache at N = 8192: the products one by one in mul_row_kernel, added up by scale_kernel, instead of the
-// transforms of the operands and a tensor inverse that walks over the group.  With half the compute units busy or more, while an eighth are
-// left to a step's other branches.  us a step, three primes, heads x ciphertexts (products x primes of 256): 6 x 2 (84) 221 / 224,
-// 16 x 1 (112) 300 / 283, 2 x 8 (112) 244 / 220, 10 x 2 (140) 291 / 287, 12 x 2 (168) 329 / 315, 14 x 2 (196) 373 / 353, 8 x 4 (224) 344 / 339,
-// 4 x 8 (224) 328 / 318, 9 x 4 (252) 368 / 375, 12 x 4 (336) 424 / 431, 12 x 6 (504) 590 / 600.
-static bool mul_row_sums_win(const cg_ctx *c, size_t rows)
+// transforms of the operands and a tensor inverse that walks over the group.  us of a context alone, three primes, heads x ciphertexts (products x primes,
+// 256 compute units): 16 x 1 (112) 178 / 179, 2 x 8 (112) 146 / 131, 3 x 6 (126) 143 / 135, 12 x 2 (168) 176 / 174, 14 x 2 (196) 191 / 178, 4 x 8 (224) 161 / 140,
+// 8 x 4 (224) 163 / 157 (steps on both sides: 6 x 2 (84) 221 / 224, 9 x 4 (252) 368 / 375).  In a step only up to 2/3 of the units, which leaves the scores' some: 2 x 8 233 / 223,
+// 5 x 4 (140) 258 / 256, 3 x 8 (168) 280 / 265, 6 x 4 283 / 278, but 14 x 2 356 / 356, 5 x 6 (210) 312 / 318, 8 x 4 333 / 337; and not where the scores are the
+// longer chain, which it holds up (d2 = 128): 5 x 4 256 / 277, 7 x 3 (147) 270 / 290, 6 x 4 288 / 305; 2 x 8 237 / 231.
+static bool mul_row_sums_win(const cg_ctx *c, size_t rows, const Beside &beside)
 {
     const size_t n = (size_t)c->n_cu;
-    return c->logn == 13 && c->k <= 3 && !c->dry && 16 * rows >= 7 * n && 8 * rows <= 7 * n;
+    if (c->logn != 13 || c->k > 3 || c->dry || beside.longer) return false;
+    return 16 * rows >= 7 * n && (beside.others ? 3 * rows <= 2 * n : 8 * rows <= 7 * n);
 }
 
 // Ranges of units that end where groups do not (SumParts), one round of workgroups of them, where parts of whole groups
@@ -1194,13 +1198,13 @@ static bool sum_ranges(const cg_ctx *c, uint32_t groups, uint32_t group, SumPart
 // b ciphertext of unit u sits at index (u / b_group) * b_stride + u % b_group (b_group = 0: dense)
 static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *b2, uint64_t *out3,
                   uint32_t batch, uint32_t a_group, void *ws, int accumulate, uint32_t b_group = 0,
-                  uint32_t b_stride = 0, const double *b_ext = nullptr, uint32_t sum_group = 0)
+                  uint32_t b_stride = 0, const double *b_ext = nullptr, uint32_t sum_group = 0, const Beside &beside = {})
 {
     // b_ext: the b operands are already in transformed extended-basis form (cg_cache_extend);
     // only the a operands are transformed here
     // sum_group: the tensor products of every sum_group consecutive units are summed before the
     // inverse transform and the scaling; out3 then holds batch / sum_group results
-    const bool beside = b_group != 0;      // attention over a cache: beside the other branches of a step
+    const bool cached = b_group != 0;      // attention over a cache
     if (!b_group) { b_group = batch; b_stride = batch; }
     const uint32_t n_a = (batch + a_group - 1) / a_group;
     const uint32_t n_out = sum_group ? batch / sum_group : batch;
@@ -1242,7 +1246,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         S.stride = (int)parts;
         CG_TRY(launch_mul_sum_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                         tens, n_out, S));
-    } else if (sum_group && a_group == 1 && b_ext && mul_row_sums_win(c, (size_t)batch * c->KL)) {
+    } else if (sum_group && a_group == 1 && b_ext && mul_row_sums_win(c, (size_t)batch * c->KL, beside)) {
         parts = sum_group;
         CG_TRY(launch_mul_row<true>(c, s, MulRowArgs{a2, nullptr, b_ext, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                     tens, batch, B, B));
@@ -1252,7 +1256,7 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         CG_TRY(launch_mul_sum_row<false>(c, s, MulRowArgs{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn},
                                          tens, n_out, S));
         parts = (uint32_t)S.stride;
-    } else if (!sum_group && !(b_ext && a_group > 1) && mul_row_wins(c, (size_t)batch * c->KL, beside)) {
+    } else if (!sum_group && !(b_ext && a_group > 1) && mul_row_wins(c, (size_t)batch * c->KL, cached)) {
         MulRowArgs A{a2, b2, nullptr, all, 0, 1, (int)b_group, (int)b_stride, 1, c->k, c->logn};
         if (b_ext) {
             A.yhat = b_ext;
@@ -1948,7 +1952,7 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * heads), *xb = w.take<uint64_t>((size_t)2 * c->k * heads);
     if (sum_first) {
         // y[h] = one scaling of the sum over c of the tensor products
-        CG_TRY(do_mul(c, s, a, vc, y, batch, 1, w.p, 0, n_cts, cache_stride_cts, vext, n_cts));
+        CG_TRY(do_mul(c, s, a, vc, y, batch, 1, w.p, 0, n_cts, cache_stride_cts, vext, n_cts, beside));
     } else {
         CG_TRY(do_mul(c, s, a, vc, d3, batch, 1, w.p, 0, n_cts, cache_stride_cts, vext));
         // y[h] = sum_c d3[h][c]  (three components)
@@ -2068,7 +2072,7 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const uint32_t own_switches = switches(c->N / d2, block_w), their = switches(d2, fold_w);
     const bool longer = own_switches > their || (c->logn == 12 && own_switches == their), context_first = longer && (few || over);
     const Beside by_context{true}, by_scores{true, (size_t)heads * n_cts * c->dnum * c->L > n,
-                                             fold_w && ks_wide_wins(c, heads * n_cts, false, by_context)};
+                                             fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches};
     auto scores_on = [&](hipStream_t st) {
         return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, by_context);
     };

@@ -70,7 +70,9 @@ WANT = {
     **{("n4096_k2", "context_ext", h, c): "mul_sum_row_kernel<12, 8, 2, true>" for h, c in ((17, 5), (85, 1), (12, 7))},
     **{("n4096_k2", "context_ext", h, c): "ntt_inv_kernel<12, 8, LdInvTensorSum, StInvF64>" for h, c in ((43, 2), (86, 1), (11, 8))},
     ("n8192_k3", "context_ext", 1, 1): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
-    # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8
+    # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8, in a step to 2/3 and not beside the longer chain
+    ("n8192_k3", "step", 8, 3, 64): "mul_row_kernel<13, 8, 3, true>", ("n8192_k3", "step", 8, 3, 128): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
+    ("n8192_k3", "step", 5, 5, 64): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
     **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
     **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
     # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; at N = 16384 in one launch, up to half idle, where
@@ -120,8 +122,8 @@ def _launches(lib):
                  "scores": lambda h, c: lib.lib.cg_decode_scores(ctx, None, d, d, u32(h), u32(c), u32(c), u32(64), d, keys, out, d),
                  "context_ext": lambda h, c: lib.lib.cg_decode_context_hoisted(
                      ctx, None, d, d, d, u32(h), u32(c), u32(c), u32(64), u32(3), 1, d, keys, out, d),
-                 "step": lambda h, c: lib.lib.cg_decode_step_hoisted(
-                     ctx, None, d, d, d, d, u32(h), u32(c), u32(c + 1), u32(64), u32(c * (1 << log2n) // 64 - 1), d, d, d, u32(3), keys, u32(3),
+                 "step": lambda h, c, d2=64: lib.lib.cg_decode_step_hoisted(
+                     ctx, None, d, d, d, d, u32(h), u32(c), u32(c + 1), u32(d2), u32(c * (1 << log2n) // d2 - 1), d, d, d, u32(3), keys, u32(3),
                      1, keys, out, out, d)}
         for s, op, *sizes in {**WANT, **NEVER}:
             if s == name:
