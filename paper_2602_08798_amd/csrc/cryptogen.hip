@@ -1301,13 +1301,6 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
     return CG_OK;
 }
 
-static uint32_t inv_mod_pow2(uint32_t g, uint32_t two_n)
-{
-    uint32_t x = g;   // Newton iteration: correct to 3 bits, doubles each step
-    for (int i = 0; i < 5; i++) x *= 2 - g * x;
-    return x & (two_n - 1);
-}
-
 // Mod-up of one ring element per unit (src + b*src_stride, Galois map first when galois != 0): the
 // dnum digits extended to the k+nsp primes and transformed, rows dig[b][dnum][k+nsp][N], canonical
 static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
@@ -1316,7 +1309,7 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     const size_t nrows = (size_t)batch * c->dnum * c->L;
     const double mbytes = (double)limb_bytes(c) * (c->k + (double)c->dnum * c->L) * batch;
     const StU64 st{dig, c->logn};
-#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn, G ? inv_mod_pow2(galois, 2u * c->N) : 1u}, st, KID_FWD_MODUP, mbytes, whole ? 0 : row_parts(c, nrows, false))
+#define CG_MODUP(G, A) return launch_fwd(c, s, nrows, LdModup<G, A>{src, src_stride, galois, c->logn}, st, KID_FWD_MODUP, mbytes, whole ? 0 : row_parts(c, nrows, false))
     switch (c->alpha * 2 + (galois ? 1 : 0)) {
     case 2: CG_MODUP(false, 1);
     case 3: CG_MODUP(true, 1);
@@ -1406,6 +1399,13 @@ static int do_relin(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *r
     const size_t ct3 = (size_t)3 * c->k * c->N;
     return do_keyswitch(c, s, in3 + (size_t)2 * c->k * c->N, ct3, 0, static_cast<const double *>(rlk), out2,
                         (size_t)2 * c->k * c->N, in3, ct3, 0, 0, batch, ws, nullptr, 0, beside);
+}
+
+static uint32_t inv_mod_pow2(uint32_t g, uint32_t two_n)
+{
+    uint32_t x = g;   // Newton iteration: correct to 3 bits, doubles each step
+    for (int i = 0; i < 5; i++) x *= 2 - g * x;
+    return x & (two_n - 1);
 }
 
 // in_stride / out_stride: uint64 between consecutive units (0 = densely packed ciphertexts)

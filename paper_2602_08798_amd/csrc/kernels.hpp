@@ -671,7 +671,6 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     static_assert(plan.out <= LAZY_MAX, "lazy bound exceeds 2^53");
     static_assert(cross || L + R <= chunk_log<E>(), "wave-local passes must stay inside one chunk");
     if (prio) __builtin_amdgcn_s_setprio(PASS < 2 ? 3 : PASS == P::NP - 1 ? 2 : PASS == P::NP - 2 ? 1 : 0);
-    constexpr int ROW = lds_doubles<LOGN>();
     double v[U][G][1 << R];
     int base[G];
 #pragma unroll
@@ -1153,9 +1152,6 @@ struct LdModup {
     size_t unit_stride;      // in uint64
     uint32_t galois;
     int logn;
-    uint32_t ginv;           // galois^-1 mod 2N (for parts of rows)
-    // the element that lands at place(idx) = pos
-    __device__ __forceinline__ int source_of(int pos, int n) const { return (int)(((uint32_t)pos * ginv) & (n - 1u)); }
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % C->L; }
     __device__ __forceinline__ int share(const DevConst *C) const { return C->L; }
     __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const { return wg; }
@@ -2505,11 +2501,8 @@ ntt_fwd_part_kernel(LD ld, ST st, const double *__restrict__ tw_all, const DevCo
         else in[it] = x[0] + mulmod(x[PARTS / 2], w0, m) + mulmod(x[1] + mulmod(x[PARTS - 1], w0, m), w1, m);
     };
     uint64_t raw[E][PARTS][LD::kRaw];
-    auto at = [&](int it, int q) {
-        const int pos = tid + it * T + (q << SUB);
-        if constexpr (LD::kScatter) return ld.source_of(pos, 1 << LOGN);
-        else return pos;
-    };
+    static_assert(!LD::kScatter, "elements in the order of their places");
+    auto at = [&](int it, int q) { return tid + it * T + (q << SUB); };
 #pragma unroll
     for (int it = 0; it < E; it++)
 #pragma unroll
@@ -2578,18 +2571,11 @@ ntt_inv_part_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevC
     for (int it = 0; it < E; it += 2) pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(y[it], y[it + 1]);
     wave_sync();
     const StEvery<LS, ST> every{st, h};
-    if constexpr (NP > 4) {
-        inv_pass<SUB, E, 4, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
-        inv_pass<SUB, E, 3, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
-        inv_pass<SUB, E, 2, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
-        inv_pass<SUB, E, 1, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
-        inv_pass<SUB, E, 0, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
-    } else {
-        inv_pass<SUB, E, 3, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
-        inv_pass<SUB, E, 2, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
-        inv_pass<SUB, E, 1, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
-        inv_pass<SUB, E, 0, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
-    }
+    static_assert(NP == 4, "parts of 4096");
+    inv_pass<SUB, E, 3, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+    inv_pass<SUB, E, 2, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
+    inv_pass<SUB, E, 1, IN>(lds, every, orow, tid, itw, twa, twb, m, pr, C);
+    inv_pass<SUB, E, 0, IN>(lds, every, orow, tid, itw, twb, twa, m, pr, C);
 }
 // Loaders that bring in a word or two per element.  Those that work for an element (lifts, tensor and inner products) would do so 2^LS
 // times: one product at N = 8192, four parts, operands 13.7 -> 13.1 us, tensor product 12.6 -> 15.3, inner product 11.1 -> 12.9.
