@@ -1275,9 +1275,9 @@ static int do_mul(cg_ctx *c, hipStream_t s, const uint64_t *a2, const uint64_t *
         const LdInvTensor ld{ntt, b_ext, (int)a_group, (int)n_a, (int)b_group, (int)b_stride, c->logn};
         const size_t rows = (size_t)n_out * 3 * c->KL;
         const double tbytes = LB * c->KL * (2.0 * ((double)n_a + B) + 3.0 * n_out);
-        if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StInvF64{tens, c->logn},
+        if (sum_group) CG_TRY(launch_inv(c, s, rows, LdInvTensorSum{ld, (int)sum_group}, StTens<false>{{tens, c->logn}},
                                          KID_INV_TENSORSUM, tbytes));
-        else CG_TRY(launch_inv(c, s, rows, ld, StInvF64{tens, c->logn}, KID_INV_TENSOR, tbytes));
+        else CG_TRY(launch_inv(c, s, rows, ld, StTens<false>{{tens, c->logn}}, KID_INV_TENSOR, tbytes));
     }
     S.stride = (int)parts;
     const double sbytes = LB * (3.0 * c->KL * parts + 3.0 * c->k * (accumulate ? 2 : 1)) * n_out;

@@ -639,14 +639,6 @@ template <> struct st_unscaled<StHalfRegs> { static constexpr int value = 365; }
 // 768 products and relinearisations at N = 8192 1830 -> 1780 us, 128 appends of 24 caches (with the stores' addresses in scalar
 // registers and one reduction for sum and result) 1928 -> 1882.
 template <class LD> struct ld_in { static constexpr int value = 0; };
-// loaders of tensor products, whose rows leave without N^-1 (StTens)
-template <class LD> struct ld_tens { static constexpr bool value = false; };
-template <bool HALF> struct StTens;
-template <class LD, class ST> __device__ __forceinline__ auto row_storer(const ST &st)
-{
-    if constexpr (ld_tens<LD>::value) return StTens<false>{st};
-    else return st;
-}
 
 // from != null: the first pass takes its elements from registers, in chunk_elem order
 // early: the first eight words that a storer adds to
@@ -773,10 +765,9 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
 
 template <int LOGN, int E, class LD, class ST>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-ntt_inv_kernel(LD ld, ST st_, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
 {
     __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
-    const auto st = row_storer<LD>(st_);
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int NP = Plan<LOGN, E>::NP, IN = ld_in<LD>::value;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
@@ -1410,8 +1401,6 @@ struct LdInvTensorSum {
 };
 template <> struct ld_rounds<LdInvTensorSum> { static constexpr bool value = true; };
 static_assert(fwd_out<12>() <= fwd_out<13>(), "the bound of both");
-template <> struct ld_tens<LdInvTensor> { static constexpr bool value = true; };
-template <> struct ld_tens<LdInvTensorSum> { static constexpr bool value = true; };
 template <> struct ld_in<LdInvTensor> { static constexpr int value = hundredths(2.0 * prod_of(fwd_out<13>())); };
 template <> struct ld_in<LdInvTensorSum> { static constexpr int value = hundredths(0.51 + 2.0 * prod_of(fwd_out<13>())); };
 template <> struct ld_no_16384<LdInvTensor> { static constexpr bool value = true; };

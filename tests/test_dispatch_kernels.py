@@ -17,7 +17,7 @@ class _KernelStat(C.Structure):
 
 # name -> log2 N, primes, special primes, primes of a digit
 SETS = {"n8192_k3": (13, 3, 1, 1), "n8192_k4": (13, 4, 1, 1), "n4096_k2": (12, 2, 1, 1), "n16384_k6": (14, 6, 2, 2)}
-TENSOR, SUMS = "ntt_inv_kernel<13, {}, LdInvTensor, StInvF64>", "mul_sum_row_kernel<13, 8, 3, false>"
+TENSOR, SUMS = "ntt_inv_kernel<13, {}, LdInvTensor, StTens<false> >", "mul_sum_row_kernel<13, 8, 3, false>"
 # set, call, its sizes -> the kernel among its launches that tells the routes apart
 WANT = {
     # 7 summed rotations: pairs of units where 1.84 rounds of pairs are less than the rounds of one unit ...
@@ -65,15 +65,15 @@ WANT = {
     ("n8192_k3", "mul", 48): TENSOR.format(16),
     # sums of products by the model of both routes
     **{("n8192_k3", "mul_sum", g, u): SUMS for g, u in ((3, 8), (16, 8), (4, 16), (8, 100))},
-    **{("n8192_k3", "mul_sum", g, u): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for g, u in ((12, 4), (12, 8), (6, 8))},
+    **{("n8192_k3", "mul_sum", g, u): "ntt_inv_kernel<13, 8, LdInvTensorSum, StTens<false> >" for g, u in ((12, 4), (12, 8), (6, 8))},
     # with a transformed cache at N = 4096 up to 5/3 rows of (unit, prime) per compute unit, at N = 8192 never
     **{("n4096_k2", "context_ext", h, c): "mul_sum_row_kernel<12, 8, 2, true>" for h, c in ((17, 5), (85, 1), (12, 7))},
-    **{("n4096_k2", "context_ext", h, c): "ntt_inv_kernel<12, 8, LdInvTensorSum, StInvF64>" for h, c in ((43, 2), (86, 1), (11, 8))},
-    ("n8192_k3", "context_ext", 1, 1): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
+    **{("n4096_k2", "context_ext", h, c): "ntt_inv_kernel<12, 8, LdInvTensorSum, StTens<false> >" for h, c in ((43, 2), (86, 1), (11, 8))},
+    ("n8192_k3", "context_ext", 1, 1): "ntt_inv_kernel<13, 8, LdInvTensorSum, StTens<false> >",
     # ... at N = 8192 product by product from 7/16 rows of (unit, prime) per compute unit to 7/8, in a step to 2/3 and not beside the longer chain
-    ("n8192_k3", "step", 8, 3, 64): "mul_row_kernel<13, 8, 3, true>", ("n8192_k3", "step", 8, 3, 128): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
-    ("n8192_k3", "step", 5, 5, 64): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>",
-    **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StInvF64>" for h, c in ((15, 1), (11, 3), (12, 4))},
+    ("n8192_k3", "step", 8, 3, 64): "mul_row_kernel<13, 8, 3, true>", ("n8192_k3", "step", 8, 3, 128): "ntt_inv_kernel<13, 8, LdInvTensorSum, StTens<false> >",
+    ("n8192_k3", "step", 5, 5, 64): "ntt_inv_kernel<13, 8, LdInvTensorSum, StTens<false> >",
+    **{("n8192_k3", "context_ext", h, c): "ntt_inv_kernel<13, 8, LdInvTensorSum, StTens<false> >" for h, c in ((15, 1), (11, 3), (12, 4))},
     **{("n8192_k3", "context_ext", h, c): "mul_row_kernel<13, 8, 3, true>" for h, c in ((16, 1), (2, 8), (8, 4))},
     # the context's key switches in parts, in a step until the scores' mod-ups have a row for every compute unit; at N = 16384 in one launch, up to half idle, where
     # the scores' take one launch (up to 3/8)
