@@ -1,4 +1,4 @@
-"""Launches of few rows take every row in two or four parts: transforms, key switches and summed rotations on both sides of the
+"""Launches of few rows take every row in two or four parts: transforms, relinearisations and summed rotations (and rotations, whose rows stay whole) on both sides of the
 row counts where the number of parts changes (256 compute units), bit-compared with the oracle.  Rows and units repeat
 a few distinct ones; the largest residues are among them."""
 import numpy as np
@@ -61,13 +61,17 @@ def test_key_switches_of_few_units(name, batches):
     x[1, 1] = np.array(env.prm.q, dtype=np.uint64)[:, None] - 1
     gs = [3, 2 * env.n - 1, pow(3, 5, 2 * env.n)]
     keys = [env.key(30 + i) for i in range(3)]
+    d3 = np.concatenate([x, x[::-1, 1:]], axis=1)
     rot = [env.orc.rotate(x[b], gs[0], keys[0][0]) for b in range(2)]
+    relin = [env.orc.relin(d3[b], keys[1][0]) for b in range(2)]
     sums = [env.orc.rotate_sum_hoisted(x[b], gs, {g: k[0] for g, k in zip(gs, keys)}) for b in range(2)]
     for batch in batches:
         say(f"key switches {name}, {batch} units")
         xd = env.dev(np.ascontiguousarray(x[np.arange(batch) % 2]))
         got = env.host(env.ctx.rotate(xd, gs[0], keys[0][1], batch))
+        got_relin = env.host(env.ctx.relin(env.dev(np.ascontiguousarray(d3[np.arange(batch) % 2])), keys[1][1], batch))
         got_sum = env.host(env.ctx.rotate_sum_hoisted(xd, gs, [k[1] for k in keys], batch))
         for b in range(batch):
             assert np.array_equal(got[b], rot[b % 2]), (name, batch, b)
+            assert np.array_equal(got_relin[b], relin[b % 2]), (name, batch, b)
             assert np.array_equal(got_sum[b], sums[b % 2]), (name, batch, b)
