@@ -769,10 +769,10 @@ static bool rounds_pay(const cg_ctx *c, size_t rows, IdleLimits lim)
 }
 
 // Two units to a workgroup of ks_sum_row_kernel at N = 8192, where a round of pairs takes the time of 1.84 rounds of one and there are
-// few enough of them.  us, one unit / two, three digits, 7 rotations: 64 ciphertexts (one round / one) 82 / 119, 107 (two / one)
-// 148 / 131, 128: 158 / 142, 192 (three / two) 237 / 256, 193 (four / two) 283 / 251, 320 (five / three) 411 / 414, 768: 979 / 901;
-// 3 rotations, 128: 122 / 111, 384: 388 / 361; six digits, 7 rotations, 111: 486 / 429.  At N = 4096, where a compute unit holds
-// two workgroups of one unit, pairs gain nothing: two digits, 7 rotations, 256: 88 / 95, 512: 150 / 150, 1536: 462 / 463.
+// few enough of them.  us, one unit / two, three digits, 7 rotations: 64 ciphertexts (one round / one) 83 / 116, 107 (two / one)
+// 155 / 139, 128: 166 / 150, 192 (three / two) 246 / 268, 193 (four / two) 295 / 267, 320 (five / three) 404 / 415, 321 (six / three) 450 / 410, 768: 945 / 872;
+// 3 rotations, 128: 131 / 120, 192: 193 / 211, 384: 381 / 352; two digits, 7 rotations, 128: 111 / 100, 256 (three / two) 192 / 205; six, 111: 492 / 430.  At N = 4096,
+// where a compute unit holds two workgroups of one unit, pairs gain nothing: two digits, 7 rotations, 256: 88 / 95, 512: 150 / 150, 1536: 462 / 463.
 static bool ks_sum_pairs(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn != 13) return false;
@@ -810,13 +810,16 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
     }
 #undef CG_KSSUMROW
 }
-// us with the mod-down and other keys on every call, three launches / one.  N = 8192, three digits, 7 rotations: 40
-// ciphertexts (96 units idle) 68.9 / 71.7, 42 (88): 75.5 / 72.1, 64: 98 / 81, 107 (84): 165 / 148; 3 rotations, 40: 56.7 / 55.4,
-// 42: 61.4 / 56.6.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 43 (127 idle): 37.7 / 35.3, 86 (254):
-// 50.3 / 52.5, 107 (191): 55.7 / 54.6.  Three digits, 7 rotations: 33 (124 idle) 41.2 / 43.7, 42 (88): 44.8 / 43.0, 72 (224):
-// 62.2 / 67.1, 90 (152): 73.0 / 69.9; six digits: 20 (116) 61.8 / 70.0, 26 (74): 84.0 / 72.7.
+// us with the mod-down and other keys on every call, three launches / one.  N = 8192, three digits, 7 rotations: 36 ciphertexts (112 units idle)
+// 67.2 / 69.1, 40 (96): 68.2 / 69.8, 41 (92): 73.7 / 72.2, 42 (88): 74.5 / 70.3, 64: 102 / 81; 3 rotations, 32 (128): 47.3 / 51.7, 36: 55.7 / 53.1, 42: 61.1 / 55.0;
+// 15 rotations, 42: 102 / 104, 48 (64): 114 / 108.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 42 (130 idle): 33.0 / 33.8, 43 (127): 36.8 / 34.0,
+// 86 (254): 49.6 / 51.3, 107 (191): 55.1 / 53.2.  Three digits, 7 rotations: 33 (124 idle) 40.7 / 42.5, 42 (88): 44.2 / 42.3, 72 (224):
+// 61.6 / 66.1, 84 (176): 66.2 / 67.0, 90 (152): 71.9 / 69.0; six digits: 20 (116) 61.5 / 68.5, 24 (88): 69.6 / 70.6, 26 (74): 79.9 / 70.5.
+// The limits of the second and third round at N = 8192 are older than these figures, which would have them at about 3/4 and 5/8 of the units: 7 rotations, 65
+// (252 idle) 120 / 118, 80 (192): 131 / 123, 96 (128): 152 / 133, 103 (100): 170 / 138, 129 (252) 214 / 219, 150 (168): 241 / 228, 166 (104): 259 / 234; 3 rotations, 80:
+// 106 / 94, 150: 191 / 178; two digits, 7 rotations, 110 (182): 103 / 96, 136 (104): 134 / 103, and in one round 48 (112): 58 / 54.
 // Pairs of units (ks_sum_pairs), four digits and more: from a quarter more rows than compute units on.  N = 8192, 7 rotations: four
-// digits, 63 ciphertexts (315 rows) 191 / 151, 81 (405): 266 / 157; six, 37 (259): 192 / 200, 45 (315): 232 / 204, 54: 269 / 209.
+// digits, 63 ciphertexts (315 rows) 200 / 155, 81 (405): 278 / 169; six, 37 (259): 204 / 209, 45 (315): 241 / 215, 54: 275 / 223.
 static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
@@ -895,11 +898,12 @@ static int launch_ks_unit(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
 // Whole units are coarse pieces: taken where the last round of workgroups leaves a tenth of the compute units idle at
 // most, from two workgroups per unit on at N = 4096, and where the keys of a prime stay in an XCD's L2, whose
 // workgroups are at different primes.  us by row / by unit with another key on every call.  N = 8192, three digits, rotations:
-// 231 units 214 / 196, 300: 276 / 369, 461: 450 / 394, 600: 568 / 573, 693: 634 / 581, 768: 699 / 597; 7 summed rotations of 2.75 MB of
-// keys 958 / 970.  N = 4096, two digits, relinearisation: 461 units 99 / 87, 768: 155 / 139.
-// A relinearisation by row is cheaper (no digits scattered, no permuted addend) and has more to lose: three digits at N = 8192,
-// 231 units 168 / 178, 256: 176 / 184, 461: 362 / 356, 512: 380 / 372, 693: 515 / 533, 720: 543 / 538, 768: 565 / 551; two digits,
-// 231 units 105 / 105, 461: 221 / 211; one digit 58 / 52.
+// 231 units 181 / 182, 256: 188 / 187, 300: 234 / 344, 450: 372 / 353, 600: 474 / 515, 693: 529 / 525, 768: 580 / 537; 3 summed rotations, 231: 227 / 238, 256: 237 / 245,
+// 461: 446 / 450, 768: 700 / 698; two digits, rotations, 231: 114 / 106, 420: 191 / 204, 461: 218 / 208.  N = 4096, two digits, relinearisation: 420 units 86 / 79,
+// 461: 99 / 84, 768: 154 / 128; rotation, 256: 55 / 67, 461: 106 / 91; 7 summed rotations, 256: 87 / 89, 461: 163 / 138.
+// Relinearisations of three digits at N = 8192 go by unit in the second round, and from the third on with a sixteenth idle at most.  That line is older than the
+// kernel, which has since transformed both sums back together and gains wherever the rule for the others holds: 231 units 163 / 151,
+// 256: 171 / 160, 420 (which that leaves out) 313 / 292, 461: 353 / 298, 512: 372 / 311, 693: 501 / 439, 720: 532 / 446, 768: 553 / 459; two digits, 231: 104 / 93, 461: 215 / 184.
 static bool ks_unit_wins(const cg_ctx *c, size_t batch, size_t n_rot, bool relin = false)
 {
     if (c->logn > 13 || c->alpha != 1 || c->nsp != 1) return false;
@@ -989,8 +993,8 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
     const double LB = (double)limb_bytes(c);
     const double in_rows = (double)polys * c->k;
     const StF64 st{dst, c->logn};
-    // Both kinds of rows in one launch while they are at most two per compute unit: product and relinearisation, us in two launches / one: N = 8192, one product 61 / 52, 8: 72 / 63, 16:
-    // 84 / 80; N = 4096, 16: 47.7 / 43.1.  Large launches are faster apart (the lifts' code for the plain rows).
+    // Both kinds of rows in one launch while they are at most two per compute unit: product and relinearisation, us in two launches / one: N = 8192, one product 55 / 46, 8: 65 / 57, 16:
+    // 83 / 79, 18 (504 rows) 92 / 82; N = 4096, 1: 36 / 30, 16: 45.6 / 43.3, 25 (500) 54 / 48.  Large launches are faster apart (the lifts' code for the plain rows).
     if (polys * c->KL <= (size_t)c->n_cu * 2) {
         const double bytes = LB * (in_rows + (double)polys * c->KL);
         switch (c->k) {
@@ -1015,10 +1019,12 @@ static int transform_ext(cg_ctx *c, hipStream_t s, const MulSrc &src, size_t pol
 }
 
 // mul_row_kernel; cached: in an attention call, where it pays with more units idle, beside other branches and alone.  us of a product with its scaling, three
-// launches / one.  N = 8192, three primes: 19 products (123 units idle) 66.5 / 63.7, 42 (218): 103 / 119, 52 (148): 125 / 122, 55
-// (127): 130 / 123.  N = 4096, three primes: 20 (116) 37.9 / 39.7, 23 (95): 40.4 / 39.9, 42 (218): 54.9 / 60.5, 49 (169): 67.4 / 62.0;
-// two: 27 (121) 35.8 / 35.6, 58 (222): 51.7 / 53.3, 68 (172): 58.4 / 54.2.  48 products over a cache (176 idle in
-// the second round): chain step of 12 heads 686 / 656, scores alone 307 / 294; 49 (169) 340 / 315, 44 (204) 295 / 294.  A row of 16384 leaves no registers for what these kernels keep.
+// launches / one.  N = 8192, three primes: 18 products (130 units idle) 55.2 / 57.3, 19 (123): 65.8 / 57.6, 42 (218): 103 / 109, 55 (127): 130 / 114; two: 25 (131)
+// 50.5 / 51.5, 26 (126): 60.7 / 51.4.  N = 4096, three primes: 16 (144) 32.2 / 34.6, 20 (116): 37.8 / 36.4, 23 (95): 40.1 / 36.3, 42 (218): 54.5 / 55.3, 49 (169): 66.5 / 57.6;
+// two: 16 (176) 26.7 / 29.2, 24 (136): 29.6 / 31.9, 26 (126): 35.5 / 32.9, 52 (252): 50.8 / 46.9, 58 (222): 51.6 / 50.7, 68 (172): 58.2 / 52.2.  48 products over a cache (176 idle in
+// the second round): chain step of 12 heads 686 / 656, scores alone 307 / 294; 49 (169) 340 / 315, 44 (204) 295 / 294.  The second round's limit for other products, and
+// the first one's with three primes at N = 4096, are older than these figures and could lie where the cache's does: N = 8192, 44 products (204) 109 / 110, 48 (176): 113 / 111, 50 (162):
+// 126 / 112, 52 (148): 128 / 112; two primes, 60 (212) 95.7 / 95.9, 70 (162): 119 / 98.  A row of 16384 leaves no registers for what these kernels keep.
 static bool mul_row_wins(const cg_ctx *c, size_t rows, bool cached)
 {
     if (c->logn > 13 || c->k > 3) return false;
@@ -1029,11 +1035,13 @@ static bool mul_row_wins(const cg_ctx *c, size_t rows, bool cached)
 // ks_row_kernel.  A rotation gains less than a relinearisation: its digits are scattered through LDS, with two barriers
 // each and nothing else on the unit to fill them, where the mod-up launch has two workgroups to a unit.  us with the mod-down and
 // another key on every call, three launches / two, rotation and relinearisation.  N = 8192, three digits: 32 units (128 compute
-// units idle) 39.9 / 50.2 and 36.5 / 39.8, 36 (112): 49.1 / 50.9 and 45.3 / 40.6, 42 (88): 51.3 / 52.7, 44 (80): 55.1 / 52.8, 48: 55.6 / 53.4
-// and 51.2 / 42.7, 96 (128): 91 / 99 and 85 / 79, 98 (120): 98.9 / 99.3, 129 (252): 134 / 142 and 129 / 113, 141 (204): 145 / 144, 193:
-// 208 / 192.  Two digits at N = 8192 gain from 44 units (124 idle) on, 44.8 / 41.6.  N = 4096, two digits: 43 (127) 25.6 / 26.4 and
-// 22.9 / 22.3, 44 (124): 27.8 / 26.3, 88 (248): 35.2 / 37.0 and 32.0 / 32.6, 107 (191): 36.8 / 38.0 and 33.6 / 33.2, 128 (128): 39.5 / 39.5,
-// 131: 48 / 40; three digits: 34 (120) 30.8 / 32.3, 42 (88): 30.9 / 32.0, 44 (80): 32.5 / 32.0.
+// units idle) 37.4 / 45.2 and 36.3 / 38.9, 33 (124): relinearisation 44.5 / 39.0, 42 (88): 47.8 / 46.2 and 46.6 / 41.0, 44 (80): 52.1 / 46.5, 48: 52.6 / 47.4
+// and 51.3 / 42.2, 80 (192): 81.3 / 83.8, 96 (128): 91.9 / 87.2 and 89.5 / 81.3, 97 (124): 100.6 / 90.8, 129 (252): 129 / 129 and 128 / 118, 141 (204): 134 / 131, 193:
+// 186 / 173.  Two digits at N = 8192: 42 units (130 idle) 31.4 / 37.4 and 30.4 / 32.8, 43 (127): 40.1 / 33.2, 44 (124): 42.6 / 36.9, 100 (212): 63.3 / 68.1, 128 (128): 74.0 / 71.3 and
+// 73.6 / 67.6.  N = 4096, two digits: 43 (127) 24.5 / 25.2 and 23.0 / 21.9, 44 (124): 27.9 / 25.2, 88 (248): 33.1 / 34.8 and 31.9 / 32.2, 107 (191): 34.3 / 35.7
+// and 33.5 / 32.3, 128 (128): 37.3 / 37.2, 131: 46 / 38; three digits: 34 (120) 30.4 / 31.0, 42 (88): 29.9 / 31.1, 44 (80): 30.9 / 31.0.
+// Older than these figures, N = 8192: the second round's limit for relinearisations, which gain throughout (three digits, 65 units, 252 idle, 75.9 / 72.5, 80: 81.6 / 77.1, 90: 88.3 / 79.7;
+// two, 86 (254): 59.3 / 59.1, 107 (191): 67.2 / 62.0), and the rotations' with three digits, even from 36 units (112 idle, 46.2 / 45.2) and from 90 (152, 90.5 / 87.8) on.
 static bool ks_row_wins(const cg_ctx *c, size_t rows, bool rotation)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
@@ -1114,9 +1122,10 @@ static int launch_mul_sum_row(cg_ctx *c, hipStream_t s, const MulRowArgs &A, dou
 // Whether that beats the launches of single transforms and a tensor inverse that walks over the group, and in how many
 // parts.  In transforms of a row: six per unit and two besides in one launch, against four per row and unit spread
 // over the chip, a half per unit of the group in every round of the tensor inverse, 1.2 besides, and a quarter on
-// top for the traffic.  us at N = 8192, three primes, groups x units, three launches / one: 12 x 4 89 / 120, 12 x 8 158 / 170,
-// 16 x 8 235 / 212, 6 x 8 98 / 120, 3 x 8 80 / 76, 4 x 16 140 / 122, 8 x 100 1501 / 1222; N = 4096, two primes: 12 x 4 44 / 41,
-// 12 x 8 62 / 55, 12 x 64 438 / 295: the model has every one of these on the right side.
+// top for the traffic.  us at N = 8192, three primes, groups x units, three launches / one: 12 x 4 88 / 96, 12 x 2 60.5 / 62.3, 2 x 8 66.8 / 60.6, 8 x 8 112 / 98,
+// 16 x 8 232 / 171, 3 x 8 81 / 62, 4 x 16 140 / 100, 8 x 100 1487 / 861; N = 4096, two primes: 12 x 4 43 / 39, 4 x 4 30.2 / 33.6, 16 x 4 44.6 / 52.6, 8 x 8 50.3 / 52.0,
+// 12 x 8 61 / 50, 12 x 64 431 / 286.  The model is older than the kernel (a row's words asked for ahead, N^-1 in the scaling) and than sum_ranges, which it does not know of; it still takes three
+// launches for 12 x 8 156 / 139, 6 x 8 97 / 95 and 12 x 16 324 / 248 (cut into ranges), at N = 4096 for 16 x 8 71 / 65, 9 x 12 75 / 67, 1 x 8 34.1 / 32.5 and 3 x 6 36.1 / 34.6.
 //
 // With one operand transformed already (hat) a unit has half the work in one launch, and two launches and an operand's way through
 // memory fewer.  At N = 4096 that wins up to 5 n / 3 rows of (unit, prime), beyond which the other branches' launches fill the chip too

@@ -1996,7 +1996,7 @@ ks_wide_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, StInv
 // product) 33 reach memory.  An operand's two polynomials go through the forward transform together, the first two components of
 // the product through the inverse one: two rows of one prime share the factors and every barrier (seven rows, four walks instead of
 // seven), and each has the other's arithmetic to cover its trips to LDS.  Both operands' four rows then lie in registers (114 of 128).
-// Bound by vector issue (77 % of the clocks) and what the operands' words and the stores keep it waiting (16 and 6 %, by leaving them out); the
+// Bound by vector issue (70 to 73 % of the clocks) and what the operands' words and the stores keep it waiting (16 and 6 %, by leaving them out); the
 // clock under this load is 2.0 GHz.  768 products at N = 8192, three primes: 308 + 644 + 764 us for the three launches, 1195 us with
 // one row at a time, 1180 in pairs, 1100 with the lift's constants read once besides (in walks of one row these gain nothing: the
 // constants' scalar registers are spilled).  Measured without gain: the next rows' first words asked for before the last pass, more of a row's
@@ -3015,8 +3015,8 @@ struct DigitKeys {
 // registers.  The accumulators (L rows of each component written and read again) never reach memory but for the two
 // rows modulo the special prime, and the mod-down launch is gone.  The vector unit is 53 to 56 % busy in rotations and 63 to 66 % in
 // relinearisations, less than in those kernels: the addends, asked for before the last two passes of the inverse transforms
-// (after them, and with one sum at a time: 768 relinearisations 522 us, now 495), are in part exposed.  N = 8192, 768 units: relinearisation 562 -> 545 us, rotation
-// 588 -> 537, 3 summed rotations 761 -> 680; N = 4096: 166 -> 141, 163 -> 139, 207 -> 160, 7 summed 259 -> 212.
+// (after them, and with one sum at a time: 768 relinearisations 522 us against 495), are in part exposed.  us by row / by unit, N = 8192, 768 units: relinearisation 553 / 459, rotation
+// 580 / 537, 3 summed rotations 700 / 698; N = 4096: 154 / 128, 158 / 144, 7 summed 259 / 215.
 // ---------------------------------------------------------------------------
 enum KsMode { KS_PLAIN, KS_ROTATE, KS_SUM };
 template <int LOGN, int E, int MODE>
