@@ -655,7 +655,7 @@ static int launch_inv(cg_ctx *c, hipStream_t s, size_t nwg, LD ld, ST st, int ki
     // relinearisation: 1 unit 52.4 -> 48.6 us, 8 units 62.0 -> 58.5).  In a step, beside other branches, heads x ciphertexts: chains
     // 2 x 2 306 -> 298, 6 x 2 351 -> 337, 4 x 3 346 -> 332, 6 x 1 317 -> 320 (30 shapes of up to 12 products: -1.7 % on average); in rounds
     // 8 x 1 211 -> 206, 4 x 3 229 -> 223, 5 x 1 189 -> 194, with a transformed cache 4 x 3 219 -> 228, 11 x 1 250 -> 246 (60: no difference).
-    const int e = (c->logn == 13 && inv_wide<LD>::value && nwg > (size_t)c->n_cu) ? 16 : ntt_elems(c);
+    const int e = (c->logn == 13 && inv_wide<LD>::value && 2 * nwg > (size_t)inv_wide<LD>::value * c->n_cu) ? 16 : ntt_elems(c);
     const int threads = c->N / e;
 #define CG_INV(LG, EL)                                                                          \
     do {                                                                                        \

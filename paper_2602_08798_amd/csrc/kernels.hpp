@@ -771,9 +771,9 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int NP = Plan<LOGN, E>::NP, IN = ld_in<LD>::value;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
-    // (N = 4096, 1500 rows: 24.9 -> 23.6 us, 4096: 57 -> 55.  N = 8192, 1024 threads: 1000 rows 35.7 -> 37.0, 4000 the same;
-    // 3000 of 16384: 209 -> 217.)
-    const bool prio = LOGN <= 12 && row_alone<LD, ST>::value && 2 * nwg >= 3 * (int)gridDim.x;
+    // (N = 4096, 1500 rows: 24.9 -> 23.6 us, 4096: 57 -> 55.  N = 8192, 512 threads: inv_wide; 1024 threads: 1000 rows 35.7 -> 37.0, 4000 the
+    // same; 4000 of 16384: 274 -> 286.)
+    const bool prio = (LOGN <= 12 || (LOGN == 13 && E == 16)) && row_alone<LD, ST>::value && 2 * nwg >= 3 * (int)gridDim.x;
     const int tid = threadIdx.x;
     const int S = ld.share(C);
     int p = blockIdx.x;
@@ -835,11 +835,12 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
     }
 }
 
-// Inverse loaders marked here run with 16 elements per thread at N = 8192 where there are more rows than compute units,
+// Inverse loaders marked here run with 16 elements per thread at N = 8192 where there are more rows than this many halves of the compute units,
 // like the forward transforms (two co-resident 512-thread workgroups per compute unit).  It pays for the tensor
-// product, whose launches are large then; the key-switch inner product is launched over a few hundred
-// rows at a time and finishes a row sooner on 1024 threads.
-template <class LD> struct inv_wide { static constexpr bool value = false; };
+// product, whose launches are large then, and for callers' rows (us, 1024 threads / 512: 400 rows 16.9 / 15.6, 512: 18.8 / 17.8, 700: 25.9 / 23.8,
+// 1000: 35.5 / 33.0, 2000: 72 / 65, 4323: 155 / 136, 16384: 565 / 488, without priorities 522); the key-switch inner product is
+// launched over a few hundred rows at a time and finishes a row sooner on 1024 threads.
+template <class LD> struct inv_wide { static constexpr int value = 0; };
 
 // ---------------------------------------------------------------------------
 // exact base conversion helpers (per coefficient, registers only)
@@ -1217,12 +1218,13 @@ struct LdInvU64 {
         return u64_to_f64(raw[0]);
     }
 };
+template <> struct inv_wide<LdInvU64> { static constexpr int value = 3; };
 struct StInvU64;
 template <> struct row_alone<LdInvU64, StInvU64> { static constexpr bool value = true; };
 // key-switch inner product fused into the load: workgroup -> (unit b, prime r, component c), the
 // component running fastest so that the two rows reading the same digits are neighbours;
 struct LdInvTensor;
-template <> struct inv_wide<LdInvTensor> { static constexpr bool value = true; };
+template <> struct inv_wide<LdInvTensor> { static constexpr int value = 2; };
 
 // Transformed digits in memory are canonical uint64 residues, prepared keys centred residues as doubles: the
 // kernels that sum in FP64 take keys as they are, and the integer accumulation of ks_sum_kernel makes integers of
