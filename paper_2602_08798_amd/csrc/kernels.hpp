@@ -1662,41 +1662,114 @@ ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st
     }
 }
 
-// A transformed digit (reduced, in LDS) times the keys of n_rot rotations, each at its permuted evaluation points,
-// added to the two sums
-template <int LOGN, int E>
-__device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, int n_rot, int j, int r, int L, int tk,
-                                          const ModD m, double *s0, double *s1)
+// A sum of products reduced once: `a` adds up the products' multiples of 2^50 (from 1.5 * 2^102 on, where an FP64 number's last bit is worth
+// 2^50), `l` what each addition rounded away, which the next FMA returns exactly.  Four instructions a product where one that is
+// reduced and added takes seven; close() takes six.  Up to eight products of centred residues (below 2^98 each) between open and close: a stays
+// within 2^102 ... 2^103, l within 4 * 2^50 of what it was opened with.  close(): the quotient of a sum of 2^101 at most is off by 1/4 for
+// rounding h + l, the reciprocal and the product each, so the result is below 1.25 * 2^50, and fma(-c, p, h) = result - l below
+// 2^53: exact.
+struct DotSum {
+    static constexpr double ZERO = 0x1.8p102, OUT = 1.26;
+    double a, l;
+    __device__ __forceinline__ void open(double start) { a = ZERO, l = start; }
+    __device__ __forceinline__ void add(double x, double w)
+    {
+        const double t = __builtin_fma(x, w, a);
+        l += __builtin_fma(x, w, a - t);
+        a = t;
+    }
+    __device__ __forceinline__ double close(const ModD m) const
+    {
+        const double h = a - ZERO, c = __builtin_rint((h + l) * m.u);
+        return __builtin_fma(-c, m.p, h) + l;
+    }
+};
+
+// A transformed digit (reduced, in LDS) times the keys of n_rot rotations, each at its permuted evaluation points, added to the two sums
+// s[0 ... E) and s[E ... 2 E).  W pairs of elements are taken through all rotations before the next ones, so that only their sums are open; keys are asked
+// for a pair ahead, their addresses and Galois elements read a rotation ahead.  us a series of 7 rotations, N = 8192, three digits: with products reduced
+// one by one 64 ciphertexts 80.3, now 76.7; 15 rotations 119 / 111.  (For two units and at N = 16384, where four sums leave no registers for
+// open ones but a pair at a time, even at 7 rotations and 3 to 12 % slower at one.)
+struct RotWalk {
+    const HoistTab &T;
+    int n, at;                          // rotation of g_next, key_next
+    size_t row;
+    uint32_t g, g_next;
+    const double *key, *key_next;
+    __device__ __forceinline__ void look()
+    {
+        g_next = T.g[at];
+        key_next = T.key[at] + row;
+    }
+    __device__ __forceinline__ void step()
+    {
+        g = g_next;
+        key = key_next;
+        at = at + 1 == n ? 0 : at + 1;
+        look();
+    }
+    __device__ __forceinline__ RotWalk(const HoistTab &T_, int n_, size_t row_) : T(T_), n(n_), at(0), row(row_)
+    {
+        look();
+        step();
+    }
+};
+__device__ __forceinline__ void ask_pair(const double *key, size_t comp, int lane, cg_double2v (&k)[2])
 {
-    const int idx0 = chunk_elem<E>(tk, 0);
-    const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
-    for (int i = 0; i < n_rot; i++) {
-        const uint32_t g = T.g[i], eg = __umul24(e0, g);
-        const cg_double2v *k0 =
-            reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN));
-        const cg_double2v *k1 = k0 + ((size_t)L << (LOGN - 1));
+    const cg_double2v *k0 = reinterpret_cast<const cg_double2v *>(key);
+    k[0] = at_lane(k0, lane);
+    k[1] = at_lane(k0 + comp, lane);
+}
+// pairs F ... F + W - 1, and those behind; k[0]: the first one's keys
+template <int LOGN, int E, int W, int F>
+__device__ __forceinline__ void sum_pairs(const double *lds, RotWalk &way, size_t comp, int lane, uint32_t e0, const ModD m, double (&s)[2 * E],
+                                          cg_double2v (&k)[2][2])
+{
+    static_assert(W % 2 == 0, "the two sets of keys keep their registers");
+    constexpr int NEXT = F + W < E / 2 ? F + W : F;
+    DotSum d[4 * W];        // [pair][component][element]
 #pragma unroll
-        for (int q = 0; q < E / 2; q++) {
-            // evaluation point of the pair's first element under the map; its second's is the neighbour
-            // that differs in the lowest bit.  (Bits above the row's fall out on the right.)
-            const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+    for (int x = 0; x < 4 * W; x++) d[x].open(s[x / 2 % 2 * E + 2 * (F + x / 4) + x % 2]);
+    int i = 0;
+    do {
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            // (behind the last pair the next rotation's first one, behind the last rotation that of the next pairs)
+            if (w + 1 < W) ask_pair(way.key + 128 * (F + w + 1), comp, lane, k[(w + 1) & 1]);
+            else ask_pair(way.key_next + 128 * (i + 1 < way.n ? F : NEXT), comp, lane, k[(w + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            // evaluation point of the pair's first element under the map; its second's is the neighbour that differs in the
+            // lowest bit.  (Bits above the row's fall out on the right.)
+            const uint32_t e = __umul24(e0 + 2u * (__brev((uint32_t)(128 * (F + w))) >> (32 - LOGN)), way.g);
             const int at = pad((int)((__brev(e) >> (31 - LOGN)) & ((1u << LOGN) - 1u)));
             const double x0 = lds[at], x1 = lds[at ^ 1];
-            const cg_double2v a = at_lane(k0 + 64 * q, idx0 / 2), c = at_lane(k1 + 64 * q, idx0 / 2);
-            s0[2 * q] += mulmod(x0, a.x, m);
-            s0[2 * q + 1] += mulmod(x1, a.y, m);
-            s1[2 * q] += mulmod(x0, c.x, m);
-            s1[2 * q + 1] += mulmod(x1, c.y, m);
-        }
-        // a term is below 0.6 p
-        if ((i & 7) == 7 || i + 1 == n_rot) {
 #pragma unroll
-            for (int it = 0; it < E; it++) {
-                s0[it] = red(s0[it], m);
-                s1[it] = red(s1[it], m);
+            for (int c = 0; c < 2; c++) {
+                d[4 * w + 2 * c].add(x0, k[w & 1][c].x);
+                d[4 * w + 2 * c + 1].add(x1, k[w & 1][c].y);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
+        way.step();
+        i++;
+        if ((i & 7) == 0 && i < way.n) {
+#pragma unroll
+            for (int x = 0; x < 4 * W; x++) d[x].open(d[x].close(m));
+        }
+    } while (i < way.n);
+#pragma unroll
+    for (int x = 0; x < 4 * W; x++) s[x / 2 % 2 * E + 2 * (F + x / 4) + x % 2] = d[x].close(m);
+    if constexpr (F + W < E / 2) sum_pairs<LOGN, E, W, F + W>(lds, way, comp, lane, e0, m, s, k);
+}
+template <int LOGN, int E, int W>
+__device__ __forceinline__ void sum_digit(const double *lds, const HoistTab &T, int n_rot, int j, int r, int L, int tk, const ModD m, double (&s)[2 * E])
+{
+    const int idx0 = chunk_elem<E>(tk, 0);
+    const size_t comp = (size_t)L << (LOGN - 1);
+    RotWalk way(T, n_rot, (size_t)(2 * j * L + r) << LOGN);
+    cg_double2v k[2][2];
+    ask_pair(way.key, comp, idx0 / 2, k[0]);
+    sum_pairs<LOGN, E, W, 0>(lds, way, comp, idx0 / 2, 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u, m, s, k);
 }
 
 // The same for two units, their digits ROW doubles apart in LDS: a key is read once for both, a pair of elements ahead of its use
@@ -1791,10 +1864,10 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
             for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + it * TH, tid);
         };
         fetch(0, 0);
-        double s0[E], s1[E], s2[U > 1 ? E : 1], s3[U > 1 ? E : 1];
+        double s[2 * E], s2[U > 1 ? E : 1], s3[U > 1 ? E : 1];
 #pragma unroll
         for (int it = 0; it < E; it++) {
-            s0[it] = s1[it] = 0.0;
+            s[it] = s[E + it] = 0.0;
             if (U > 1) s2[it % (U > 1 ? E : 1)] = s3[it % (U > 1 ? E : 1)] = 0.0;
         }
         for (int j = 0; j < dnum; j++) {
@@ -1804,7 +1877,6 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
                 const int row = ((b + u) * dnum + j) * L + r;
 #pragma unroll
                 for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, tid + it * TH, m, C);
-                if (U == 1) fetch(0, j + 1 < dnum ? j + 1 : j);     // (with four sums there are no registers for it here)
                 if (u == 0) lds_barrier();      // the previous digit's (or unit's) LDS reads
                 fwd_row<LOGN, E, false>(lds + u * ROW, x, x, tid, tw, m);
                 if (U > 1) fetch(u + 1 < U ? u + 1 : 0, u + 1 < U || j + 1 == dnum ? j : j + 1);
@@ -1815,21 +1887,22 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
             lds_barrier();
             int tk = tid;
             asm volatile("" : "+v"(tk));
-            if constexpr (U == 1) sum_digit<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1);
-            else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s0, s1, s2, s3);
+            if constexpr (U == 1) sum_digit<LOGN, E, 4>(lds, T, n_rot, j, r, L, tk, m, s);
+            else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s, s + E, s2, s3);
+            if (U == 1) fetch(0, j + 1 < dnum ? j + 1 : j);     // (sooner there are no registers for it: 77.9 us there, 79.5 before the transform)
         }
         lds_barrier();
         // both components of a unit
         auto inverse = [&](const double *a, const double *c, int unit) {
-            double s[2 * E];
+            double y[2 * E];
 #pragma unroll
             for (int it = 0; it < E; it++) {
-                s[it] = a[it];
-                s[E + it] = c[it];
+                y[it] = a[it];
+                y[E + it] = c[it];
             }
-            inv_row<LOGN, E, false, 0, 2>(lds, s, st, (unit * 2) * L + r, tid, itw, m, r, C, L);
+            inv_row<LOGN, E, false, (U > 1 ? 52 : hundredths(DotSum::OUT)), 2>(lds, y, st, (unit * 2) * L + r, tid, itw, m, r, C, L);
         };
-        inverse(s0, s1, b);
+        inverse(s, s + E, b);
         if (U > 1 && b + 1 < batch) {
             lds_barrier();
             inverse(s2, s3, b + 1);
@@ -3092,7 +3165,7 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
                     for (int it = 0; it < E; it += 2)
                         pair_at(lds, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
                     lds_barrier();
-                    sum_digit<LOGN, E>(lds, T, H.n_sum, j, r, L, tk, m, s, s + E);
+                    sum_digit<LOGN, E, 2>(lds, T, H.n_sum, j, r, L, tk, m, s);
                 }
             }
             const uint64_t *own_rows = (MODE == KS_ROTATE ? A.acc_add + (size_t)b * A.acc_stride
@@ -3126,7 +3199,7 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
                 ask_own(0, tk);
             };
             if (MODE == KS_SUM) lds_barrier();
-            inv_row<LOGN, E, false, 0, 2>(lds, s, StRegs{y}, 0, tid, itw, m, r, C, 0, ask);
+            inv_row<LOGN, E, false, (MODE == KS_SUM ? hundredths(DotSum::OUT) : 0), 2>(lds, s, StRegs{y}, 0, tid, itw, m, r, C, 0, ask);
 #pragma unroll
             for (int c = 0; c < 2; c++) {
                 int tk = tid;
