@@ -1917,7 +1917,7 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 // memory (a unit's transformed digits out and in, its accumulators out, in and out again: 104 rows of 142 per key switch) never leaves the compute
 // unit, and memory is what bounds a step at this size.  Registers: four sums and a half row, as with two units at N = 8192.  Bound by
 // vector issue and the keys' way from L2 (5.4 MB a row with 7 rotations).  32 ciphertexts, six primes, two special ones, 7 rotations:
-// mod-up, sums and inverse transforms 61 + 101 + 39 us, 135 here.
+// mod-up, sums and inverse transforms 61 + 101 + 39 us, 135 here, 123 where workgroups begin with different rotations.
 // ---------------------------------------------------------------------------
 // The constants of a digit's lift to one prime, in scalar registers (as LiftTab)
 template <int ALPHA> struct DigitTab {
@@ -2004,15 +2004,18 @@ ks_wide_kernel(LdModup<false, ALPHA> ld, HoistTab T, int n_rot, int batch, StInv
             const uint32_t e0 = 2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u;
             const size_t comp = (size_t)L << (LOGN - 1);
             auto rows = [&](int i) { return reinterpret_cast<const cg_double2v *>(T.key[i] + ((size_t)(2 * j * L + r) << LOGN)); };
-            const cg_double2v *k0 = rows(0);
-            uint32_t g = T.g[0];
+            // Workgroups begin with different rotations: all at the same one, every key's first trip from memory held all of them up.  Series of 7
+            // rotations, 32 ciphertexts 208 -> 195 us, 48: 354 -> 340; 15, 32: 305 -> 286.  (At N = 8192 no difference.)
+            int at_rot = b % n_rot;
+            const cg_double2v *k0 = rows(at_rot);
+            uint32_t g = T.g[at_rot];
             cg_double2v ka[2], kc[2];
             ka[0] = at_lane(k0, idx0 / 2);
             kc[0] = at_lane(k0 + comp, idx0 / 2);
             for (int i = 0; i < n_rot; i++) {
-                const int i_next = i + 1 < n_rot ? i + 1 : i;
-                const cg_double2v *kn = rows(i_next);
-                const uint32_t gn = T.g[i_next], eg = __umul24(e0, g);
+                at_rot = at_rot + 1 < n_rot ? at_rot + 1 : 0;
+                const cg_double2v *kn = rows(at_rot);
+                const uint32_t gn = T.g[at_rot], eg = __umul24(e0, g);
 #pragma unroll
                 for (int f = 0; f < E; f++) {       // pair f % 4 of half f / 4, its keys asked for one ahead
                     const cg_double2v *kf = f + 1 < E ? k0 + (f + 1) / 4 * (HALF / 2) + 64 * ((f + 1) % 4) : kn;
