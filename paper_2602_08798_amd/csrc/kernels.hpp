@@ -2975,10 +2975,12 @@ moddown_sum_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C
 // One component of one rotation of a hoisted series per workgroup, from the transformed digits to the finished
 // ciphertext rows: inner products and inverse transform modulo the special prime, then modulo every ciphertext
 // prime, the division by P following in registers.  The permuted c0 row goes through LDS.  The accumulators (8 rows
-// written and read per rotation at four primes) never reach memory.  14 us a row and compute unit, the vector unit 51 %
-// busy: one workgroup to a unit, and nothing covers the gathers; a serial chain of k + 1 transforms, so it needs half
-// the chip to be busy to pay off.
-// N = 8192, 127 rotations, mod-down included: 12 ciphertexts 1164 -> 675 us, one 118 -> 74 us.
+// written and read per rotation at four primes) never reach memory.  A serial chain of k + 1 transforms, so it needs half
+// the chip to be busy to pay off.  N = 8192, 127 rotations, mod-down included: 12 ciphertexts 1164 us in two launches, 675 here, one 118 / 69, with
+// digits gathered where they are multiplied, which nothing covered (one workgroup to a unit, 14 us a row, the vector unit
+// 51 % busy).  Digits side by side through LDS and words asked for ahead: 657 and 63.6, four 247 -> 225; products added up unreduced besides (DotSum):
+// 633, 62.7, 217.  (Words asked for before the whole transform, whose factors then wait behind them: 834; the special prime's residues in memory, which
+// leaves registers for 16 elements on 512 threads, two workgroups to a unit: 698.  One digit: 68.5 gathered, 74 through LDS.)
 // ---------------------------------------------------------------------------
 template <int LOGN, int E, int DNUM>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
@@ -2994,36 +2996,90 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
         const uint32_t g = T.g[i], ginv = H.ginv[i];
         const uint64_t *in = A.add + (size_t)b * A.add_stride;
         uint64_t *out = A.out + (size_t)(b * H.out_per_b + i) * A.out_stride + ((size_t)(c * k) << LOGN);
+        // The map takes every aligned block of 2^m values to such a block: a pair of elements of a wave's lanes reads 128 neighbours.  With several digits these
+        // come in side by side, as the keys do, and are permuted in the wave's own part of LDS.
+        constexpr bool AHEAD = DNUM > 1;
+        const int idx0 = chunk_elem<E>(tid, 0);
+        const uint32_t eg = __umul24(2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u, g);
+        int at[E / 2], from[E / 2];
+#pragma unroll
+        for (int q = 0; q < E / 2; q++) {
+            const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+            const int full = (int)((__brev(e) >> (31 - LOGN)) & (N - 1u));      // as in sum_pairs
+            at[q] = pad((idx0 & ~127) + 128 * q + (full & 127));
+            from[q] = __builtin_amdgcn_readfirstlane(full) & ~127;
+        }
+        cg_ulong2v dv[E / 2];
+        cg_double2v kv[E / 2];
+        auto ask_digit = [&](int r, int j, int tk) {
+            const cg_ulong2v *d = reinterpret_cast<const cg_ulong2v *>(dig + (((size_t)(b * DNUM + j) * L + r) << LOGN));
+#pragma unroll
+            for (int q = 0; q < E / 2; q++) dv[q] = at_lane(d + from[q] / 2, tk & 63);
+        };
+        auto ask_key = [&](int r, int j, int tk) {
+            const cg_double2v *kb = reinterpret_cast<const cg_double2v *>(T.key[i] + (((size_t)(2 * j + c) * L + r) << LOGN));
+#pragma unroll
+            for (int q = 0; q < E / 2; q++) kv[q] = at_lane(kb + 64 * q, chunk_elem<E>(tk, 0) / 2);
+        };
+        if (AHEAD) {
+            ask_digit(k, 0, tid);
+            ask_key(k, 0, tid);
+        }
         double xs[E];
         for (int step = 0; step < L; step++) {
-            const int r = step ? step - 1 : k;
+            const int r = step ? step - 1 : k, r_next = step + 1 < L ? step : r;
             const ModD m = C->mod[r];
             const double *itw = itw_all + ((size_t)r << LOGN);
-            const uint64_t *db = dig + (((size_t)(b * DNUM) * L + r) << LOGN);
-            const cg_double2v *kb =
-                reinterpret_cast<const cg_double2v *>(T.key[i] + (((size_t)c * L + r) << LOGN));
             double y[E];
             int tk = tid;
             asm volatile("" : "+v"(tk));
-            const int idx0 = chunk_elem<E>(tk, 0);
-            const uint32_t eg = __umul24(2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u, g);
+            if constexpr (AHEAD) {
+                DotSum sum[E];
 #pragma unroll
-            for (int q = 0; q < E / 2; q++) {
-                const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
-                const int at = (int)((__brev(e) >> (31 - LOGN)) & (N - 1u));      // as in ks_sum_row_kernel
-                y[2 * q] = y[2 * q + 1] = 0.0;
+                for (int it = 0; it < E; it++) sum[it].open(0.0);
+                lds_barrier();      // the previous reads of this wave's part
+                // a digit's words are asked for as soon as the last one's have left their registers
 #pragma unroll
                 for (int j = 0; j < DNUM; j++) {
-                    const uint64_t *d = db + ((size_t)(j * L) << LOGN);
-                    const cg_double2v kv = at_lane(kb + ((size_t)(2 * j * L) << (LOGN - 1)) + 64 * q, idx0 / 2);
-                    const cg_ulong2v dv = at32(reinterpret_cast<const cg_ulong2v *>(d), at >> 1);
-                    y[2 * q] += mulmod(u64_to_f64((at & 1) ? dv.y : dv.x), kv.x, m);
-                    y[2 * q + 1] += mulmod(u64_to_f64((at & 1) ? dv.x : dv.y), kv.y, m);
+#pragma unroll
+                    for (int q = 0; q < E / 2; q++)
+                        pair_at(lds, pad(chunk_elem<E>(tk, 0)) + pad(128 * q)) = make_double2(u64_to_f64(dv[q].x), u64_to_f64(dv[q].y));
+                    if (j + 1 < DNUM) ask_digit(r, j + 1, tk);
+                    wave_sync();
+#pragma unroll
+                    for (int q = 0; q < E / 2; q++) {
+                        sum[2 * q].add(lds[at[q]], kv[q].x);
+                        sum[2 * q + 1].add(lds[at[q] ^ 1], kv[q].y);
+                    }
+                    if (j + 1 < DNUM) ask_key(r, j + 1, tk);
+                    wave_sync();
                 }
-                if (DNUM > 1 && (q & 1)) asm volatile("" ::: "memory");      // two pairs' operands at a time: registers
+#pragma unroll
+                for (int it = 0; it < E; it++) y[it] = sum[it].close(m);
+            } else {
+                const cg_ulong2v *d = reinterpret_cast<const cg_ulong2v *>(dig + (((size_t)b * L + r) << LOGN));
+                const cg_double2v *kb = reinterpret_cast<const cg_double2v *>(T.key[i] + (((size_t)c * L + r) << LOGN));
+                const int idx = chunk_elem<E>(tk, 0);
+                const uint32_t ek = __umul24(2u * (__brev((uint32_t)idx) >> (32 - LOGN)) + 1u, g);
+#pragma unroll
+                for (int q = 0; q < E / 2; q++) {
+                    const uint32_t e = ek + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
+                    const int full = (int)((__brev(e) >> (31 - LOGN)) & (N - 1u));
+                    const cg_double2v kq = at_lane(kb + 64 * q, idx / 2);
+                    const cg_ulong2v dq = at32(d, full >> 1);
+                    y[2 * q] = mulmod(u64_to_f64((full & 1) ? dq.y : dq.x), kq.x, m);
+                    y[2 * q + 1] = mulmod(u64_to_f64((full & 1) ? dq.x : dq.y), kq.y, m);
+                }
+                lds_barrier();
             }
-            lds_barrier();
-            inv_row<LOGN, E, false, 70 * DNUM>(lds, y, StRegs{y}, 0, tid, itw, m, r, C);
+            // the next prime's first words travel during the last two passes and the division
+            inv_row<LOGN, E, false, AHEAD ? hundredths(DotSum::OUT) : 70>(lds, y, StRegs{y}, 0, tid, itw, m, r, C, 0, [&] {
+                if (!AHEAD) return;
+                int ta = tid;
+                asm volatile("" : "+v"(ta));
+                ask_digit(r_next, 0, ta);
+                ask_key(r_next, 0, ta);
+            });
             asm volatile("" : "+v"(tk));
             if (!step) {
 #pragma unroll
