@@ -1,5 +1,5 @@
-"""Summed rotations whose products are added up unreduced, eight between two reductions: one to 17 rotations, by rows (one unit to a workgroup) and
-by whole units, with the largest and the middle residues in ciphertexts and keys; bit-compared with the oracle.  Units repeat two
+"""Summed rotations whose products are added up unreduced, eight between two reductions: one to 17 rotations, by rows (one unit to a workgroup), by
+whole units, and from digits in memory, whose words are asked for a rotation ahead (odd and even numbers), with the largest and the middle residues in ciphertexts and keys; bit-compared with the oracle.  Units repeat two
 distinct ones."""
 import numpy as np
 import pytest
@@ -14,8 +14,9 @@ _envs = {}
 
 
 # 256 compute units, N = 8192: 48 units take 192 workgroups of one (unit, prime) each, 256 units one workgroup each (up to five rotations: keys of a
-# prime fit an L2); N = 4096: 100 units 300 workgroups, 470 units one each
-@pytest.mark.parametrize("name,batch,counts", [("C2", 48, (1, 2, 7, 8, 9, 16, 17)), ("C2", 256, (1, 2, 5)), ("C1", 100, (7, 8, 9)), ("C1", 470, (1, 8, 9))])
+# prime fit an L2); N = 4096: 100 units 300 workgroups, 470 units one each.  1 and 2 units: sums from digits in memory, one ciphertext to a thread, 12: two
+@pytest.mark.parametrize("name,batch,counts", [("C2", 48, (1, 2, 7, 8, 9, 16, 17)), ("C2", 256, (1, 2, 5)), ("C1", 100, (7, 8, 9)), ("C1", 470, (1, 8, 9)),
+                                               ("C2", 1, (1, 2, 3, 6, 9)), ("C2", 12, (2, 5)), ("C5", 2, (2, 3))])
 def test_numbers_of_rotations(name, batch, counts):
     if name not in _envs:
         _envs[name] = Env(name)
