@@ -3001,12 +3001,14 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
         constexpr bool AHEAD = DNUM > 1;
         const int idx0 = chunk_elem<E>(tid, 0);
         const uint32_t eg = __umul24(2u * (__brev((uint32_t)idx0) >> (32 - LOGN)) + 1u, g);
-        int at[E / 2], from[E / 2];
+        uint32_t at[E / 4];     // two to a register: with them apart the kernel for three digits spilled two
+        int from[E / 2];
 #pragma unroll
         for (int q = 0; q < E / 2; q++) {
             const uint32_t e = eg + 2u * (__brev((uint32_t)(128 * q)) >> (32 - LOGN)) * g;
             const int full = (int)((__brev(e) >> (31 - LOGN)) & (N - 1u));      // as in sum_pairs
-            at[q] = pad((idx0 & ~127) + 128 * q + (full & 127));
+            const uint32_t to = (uint32_t)pad((idx0 & ~127) + 128 * q + (full & 127));
+            at[q / 2] = q % 2 ? at[q / 2] | to << 16 : to;
             from[q] = __builtin_amdgcn_readfirstlane(full) & ~127;
         }
         cg_ulong2v dv[E / 2];
@@ -3048,8 +3050,9 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
                     wave_sync();
 #pragma unroll
                     for (int q = 0; q < E / 2; q++) {
-                        sum[2 * q].add(lds[at[q]], kv[q].x);
-                        sum[2 * q + 1].add(lds[at[q] ^ 1], kv[q].y);
+                        const uint32_t to = q % 2 ? at[q / 2] >> 16 : at[q / 2] & 0xFFFFu;
+                        sum[2 * q].add(lds[to], kv[q].x);
+                        sum[2 * q + 1].add(lds[to ^ 1], kv[q].y);
                     }
                     if (j + 1 < DNUM) ask_key(r, j + 1, tk);
                     wave_sync();
