@@ -198,13 +198,13 @@ struct cg_ctx {
 enum KernelId {
     KID_FWD_MULQ = 0, KID_FWD_MULB, KID_FWD_MODUP, KID_FWD_ROWS, KID_FWD_PLAIN,
     KID_INV_TENSOR, KID_INV_U64, KID_INV_MULPLAIN, KID_SCALE, KID_INV_KSINNER, KID_MODDOWN,
-    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_LIFT, KID_FWD_HALF, KID_COPY, KID_COUNT
+    KID_ADD, KID_SUM_GROUPS, KID_KSSUM, KID_MODDOWN_SUM, KID_INV_TENSORSUM, KID_MULPLAIN, KID_INV_F64, KID_KSROW, KID_MULROW, KID_KSSUMROW, KID_MULSUMROW, KID_FWD_MULEXT, KID_ROTROW, KID_KSUNIT, KID_LIFT, KID_FWD_HALF, KID_COPY, KID_KSSUMDOWN, KID_COUNT
 };
 static const char *const kKernelNames[KID_COUNT] = {
     "ntt_fwd<mul,q-rows>", "ntt_fwd<mul,aux-rows>", "ntt_fwd<modup>", "ntt_fwd<rows>",
     "ntt_fwd<plain>", "ntt_inv<tensor>", "ntt_inv<u64>", "ntt_inv<mul_plain>", "scale",
     "ntt_inv<ks_inner>", "moddown", "add", "sum_groups", "ks_sum", "moddown<sum>",
-    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit", "lift", "ntt_fwd<mul,half-rows>", "copy"};
+    "ntt_inv<tensor_sum>", "ntt_fwd_inv<mul_plain>", "ntt_inv<f64>", "ks_row", "mul_row", "ks_sum_row", "mul_sum_row", "ntt_fwd<mul,all-rows>", "rot_row", "ks_unit", "lift", "ntt_fwd<mul,half-rows>", "copy", "ks_sum_down"};
 
 // Brackets one launch with two events when profiling is on.
 struct ProfScope {
@@ -780,23 +780,24 @@ static bool ks_sum_pairs(const cg_ctx *c, uint32_t batch)
     const size_t two = ((size_t)((batch + 1) / 2) * c->L + n - 1) / n;
     return 184 * two < 100 * one;
 }
-// mod-up, summed inner products and inverse transforms in one launch
+// mod-up, summed inner products and inverse transforms in one launch, modulo the primes from r0 on
 static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T,
-                             uint32_t n_rot, double *acc, uint32_t batch)
+                             uint32_t n_rot, double *acc, uint32_t batch, int r0 = 0)
 {
-    const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * c->L) * batch + 2.0 * c->dnum * c->L * n_rot);
-    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)batch * c->L);
+    const int primes = c->L - r0;
+    const double bytes = (double)limb_bytes(c) * ((c->k + 2.0 * primes) * batch + 2.0 * c->dnum * primes * n_rot);
+    ProfScope ps(c, s, KID_KSSUMROW, bytes, (double)batch * primes);
     const bool pairs = ks_sum_pairs(c, batch);
 #define CG_KSSUMROW(LG, U)                                                                                    \
     do {                                                                                                      \
-        const size_t nwg = (size_t)((batch + U - 1) / U) * c->L;                                              \
+        const size_t nwg = (size_t)((batch + U - 1) / U) * primes;                                            \
         const unsigned threads = (1u << LG) / 8;                                                              \
         const unsigned grid = ntt_grid<ks_sum_row_kernel<LG, 8, U>>(c, (nwg + 7) / 8 * 8, (int)threads);      \
         if (c->dry) break;                                                                                    \
         return launch_kernel(ks_sum_row_kernel<LG, 8, U>, dim3(grid), dim3(threads), s,                       \
                              LdModup<false, 1>{src, src_stride, 0, c->logn}, T, (int)n_rot, (int)batch,       \
                              StInvF64{acc, c->logn}, (const double *)c->tw, (const double *)c->itw,           \
-                             (const DevConst *)c->dc, (int)nwg);                                              \
+                             (const DevConst *)c->dc, (int)nwg, r0);                                          \
     } while (0)
     switch (c->logn) {
     case 12:
@@ -809,6 +810,33 @@ static int launch_ks_sum_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size
     default: return CG_EINVAL;
     }
 #undef CG_KSSUMROW
+}
+// the same modulo the ciphertext primes, with the mod-down
+static int launch_ks_sum_down(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, const HoistTab &T, const ModdownArgs &A,
+                              const ModdownHoist &H)
+{
+    const double bytes = (double)limb_bytes(c) * ((7.0 * c->k + 2.0) * A.batch + 2.0 * c->dnum * c->k * H.n_sum);
+    ProfScope ps(c, s, KID_KSSUMDOWN, bytes, (double)A.batch * c->k);
+    const size_t nwg = (size_t)(A.batch + 1) / 2 * c->k;
+    const unsigned grid = ntt_grid<ks_sum_down_kernel<13, 8>>(c, (nwg + 7) / 8 * 8, 1024);
+    if (c->dry) return CG_OK;
+    return launch_kernel(ks_sum_down_kernel<13, 8>, dim3(grid), dim3(1024), s, LdModup<false, 1>{src, src_stride, 0, c->logn}, T, A, H,
+                         (const double *)c->tw, (const double *)c->itw, (const DevConst *)c->dc, (int)nwg);
+}
+// Pairs of units: the accumulators modulo the special prime in a launch of their own, those of the ciphertext primes with the mod-down behind them in
+// the kernel, where the two launches take no more rounds of workgroups together than the one (their last rounds are both partly empty), or, with
+// up to three digits and eight rotations, from four units per compute unit on, where a round more costs less than the mod-down's way through
+// memory.  us, one launch and mod-down / two, 7 rotations, three digits: 460 ciphertexts 557 / 487, 512 584 / 510, 900 1095 / 972, 1024 1153 / 1046, 1536 1723 / 1568; a round
+// more: 256 296 / 348, 384 441 / 472, 600 703 / 714, 640 728 / 719, 1100 1266 / 1219, 1280 1434 / 1361 and with 15 rotations 1100 1816 / 1840; four digits, 400 681 / 730,
+// 512 863 / 776, 640 1143 / 1032; six, 500 1635 / 1500.
+static bool ks_sum_down_wins(const cg_ctx *c, uint32_t batch, uint32_t n_rot)
+{
+    if (c->logn != 13 || c->nsp != 1 || c->alpha != 1) return false;
+    if (c->dry) return c->dry_rows;
+    if (!ks_sum_pairs(c, batch)) return false;
+    const size_t n = (size_t)c->n_cu, sets = (batch + 1) / 2;
+    auto rounds = [&](size_t primes) { return (sets * primes + n - 1) / n; };
+    return rounds(1) + rounds(c->k) <= rounds(c->L) || (c->dnum <= 3 && n_rot <= 8 && batch >= 4 * n);
 }
 // us with the mod-down and other keys on every call, three launches / one.  N = 8192, three digits, 7 rotations: 36 ciphertexts (112 units idle)
 // 67.2 / 69.1, 40 (96): 68.2 / 69.8, 41 (92): 73.7 / 72.2, 42 (88): 74.5 / 70.3, 64: 102 / 81; 3 rotations, 32 (128): 47.3 / 51.7, 36: 55.7 / 53.1, 42: 61.1 / 55.0;
@@ -1553,7 +1581,12 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
     if (ks_wide_wins(c, batch, false, beside)) {
         CG_TRY(launch_ks_wide(c, s, c1, in_stride, T, n_rot, acc, batch));
     } else if (ks_sum_row_wins(c, batch)) {
-        CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch));
+        const bool down = ks_sum_down_wins(c, batch, n_rot);
+        CG_TRY(launch_ks_sum_row(c, s, c1, in_stride, T, n_rot, acc, batch, down ? c->k : 0));
+        if (down) {
+            CG_TRY(launch_ks_sum_down(c, s, c1, in_stride, T, A, H));
+            if (!c->dry) return CG_OK;
+        }
     } else {
         const bool whole = beside.crowd;
         CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig, whole));

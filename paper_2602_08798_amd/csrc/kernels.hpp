@@ -1825,6 +1825,37 @@ __device__ __forceinline__ void sum_digits(const double *lds, const HoistTab &T,
     }
 }
 
+// mod-down with rounding and the final additions of relinearisation / rotation:
+//   u = floor((A + floor(P/2)) / P) = (A - x) / P mod Q with x the centred residue of A modulo P, in balanced
+//   digits (garner_balanced takes the transforms' results, below 2p);  out[b][c] = u (+ add0) (+ add1)
+// add0: relin -> in3[b][c];  rotate -> sigma_g(in2[b][0]) for c = 0, nothing for c = 1
+// add1: rotate with accumulate -> acc_add[b][c] (the rotated ciphertext itself, or another one)
+struct ModdownArgs {
+    const double *acc;        // [b][2][L][N] lazy, coefficient order
+    uint64_t *out;            // unit b at out + b*out_stride, [2][k][N]
+    size_t out_stride;
+    const uint64_t *add;      // base of the addend ciphertexts (unit 0) or null
+    size_t add_stride;        // uint64 per unit in add
+    uint32_t galois;          // != 0: add is permuted by X -> X^galois and only applies to c = 0
+    int accumulate;           // also add the un-permuted acc_add[b][c]
+    int batch;
+    const uint64_t *acc_add;  // base of the ciphertexts added un-permuted (accumulate)
+    size_t acc_stride;
+};
+// HOIST: the units are the rotations of a series, unit u = i * rot_batch + b being rotation i of
+// ciphertext b: its Galois element comes from the table, its addend is ciphertext b and its output
+// ciphertext b * out_per_b + i.
+// n_sum: rotations whose accumulators were summed (moddown_sum_kernel).
+template <int LOGN> constexpr int moddown_sum_split() { return (1 << LOGN) / 2048 >= 4 ? 4 : (1 << LOGN) / 2048; }
+struct ModdownHoist {
+    uint32_t ginv[MAXROT];
+    int rot_batch, out_per_b, n_sum;
+};
+// a + w or a - w as the top bit of s says
+__device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
+{
+    return a + bits_f64(f64_bits(w) ^ ((uint64_t)(s & 0x80000000u) << 32));
+}
 // ---------------------------------------------------------------------------
 // Summed rotations of one (unit, prime), or of two units, per workgroup: digits lifted and transformed one after the other; a
 // transformed digit lies in LDS, from where every rotation takes its permuted values, while the keys stream past;
@@ -1835,16 +1866,63 @@ __device__ __forceinline__ void sum_digits(const double *lds, const HoistTab &T,
 // mod-up, sums and inverse transforms 475 + 899 + 369 us in three launches, 1513 us here with one unit, 1391 with two (1314
 // since the two sums of a unit are transformed back together).
 // ---------------------------------------------------------------------------
+// the sums of units b ... b + U - 1 (those of the batch) modulo prime r: s (both components), and of a second unit s2 and s3
+template <int LOGN, int E, int U>
+__device__ __forceinline__ void sum_units(double *lds, const LdModup<false, 1> &ld, const HoistTab &T, int n_rot, int batch, int b, int r, int tid,
+                                          const double *__restrict__ tw, const ModD m, const DevConst *__restrict__ C, double (&s)[2 * E],
+                                          double (&s2)[U > 1 ? E : 1], double (&s3)[U > 1 ? E : 1])
+{
+    constexpr int TH = (1 << LOGN) / E, ROW = lds_doubles<LOGN>();
+    const int L = C->L, dnum = C->dnum;
+    uint64_t raw[E][1];
+    // (an odd batch's last workgroup takes its one unit twice and stores it once)
+    auto fetch = [&](int u, int j) {
+        const uint64_t *src = ld.src + (size_t)(b + u < batch ? b + u : b) * ld.unit_stride + ((size_t)j << LOGN);
+#pragma unroll
+        for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + it * TH, tid);
+    };
+    fetch(0, 0);
+#pragma unroll
+    for (int it = 0; it < E; it++) {
+        s[it] = s[E + it] = 0.0;
+        if (U > 1) s2[it % (U > 1 ? E : 1)] = s3[it % (U > 1 ? E : 1)] = 0.0;
+    }
+    for (int j = 0; j < dnum; j++) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            double x[E];
+            const int row = ((b + u) * dnum + j) * L + r;
+#pragma unroll
+            for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, tid + it * TH, m, C);
+            if (u == 0) lds_barrier();      // the previous digit's (or unit's) LDS reads
+            fwd_row<LOGN, E, false>(lds + u * ROW, x, x, tid, tw, m);
+            if (U > 1) fetch(u + 1 < U ? u + 1 : 0, u + 1 < U || j + 1 == dnum ? j : j + 1);
+#pragma unroll
+            for (int it = 0; it < E; it += 2)
+                pair_at(lds + u * ROW, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
+        }
+        lds_barrier();
+        int tk = tid;
+        asm volatile("" : "+v"(tk));
+        if constexpr (U == 1) sum_digit<LOGN, E, 4>(lds, T, n_rot, j, r, L, tk, m, s);
+        else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s, s + E, s2, s3);
+        if (U == 1) fetch(0, j + 1 < dnum ? j + 1 : j);     // (sooner there are no registers for it: 77.9 us there, 79.5 before the transform)
+    }
+    lds_barrier();
+}
+// What an inverse transform of a sum may expect
+template <int U> constexpr int sum_bound() { return U > 1 ? 52 : hundredths(DotSum::OUT); }
+
+// r0: first prime of the launch
 template <int LOGN, int E, int U>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF64 st,
                   const double *__restrict__ tw_all, const double *__restrict__ itw_all,
-                  const DevConst *__restrict__ C, int nwg)
+                  const DevConst *__restrict__ C, int nwg, int r0)
 {
     static_assert(U == 1 || U == 2, "units of a workgroup");
-    constexpr int TH = (1 << LOGN) / E, ROW = lds_doubles<LOGN>();
-    __shared__ __align__(16) double lds[2 * ROW];
-    const int tid = threadIdx.x, L = C->L, dnum = C->dnum, sets = (batch + U - 1) / U;
+    __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
+    const int tid = threadIdx.x, L = C->L, sets = (batch + U - 1) / U;
     // logical order: prime, then unit; XCD x takes the x-th eighth of it, so that an XCD works with the keys
     // of one or two primes
     const int per_xcd = (nwg + 7) >> 3;
@@ -1853,45 +1931,11 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
     for (int p = blockIdx.x; p < total; p += (int)gridDim.x) {
         const int wg = logical(p);
         if (wg >= nwg) continue;
-        const int r = wg / sets, b = (wg - r * sets) * U;
+        const int q = wg / sets, r = r0 + q, b = (wg - q * sets) * U;
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
-        uint64_t raw[E][1];
-        // (an odd batch's last workgroup takes its one unit twice and stores it once)
-        auto fetch = [&](int u, int j) {
-            const uint64_t *src = ld.src + (size_t)(b + u < batch ? b + u : b) * ld.unit_stride + ((size_t)j << LOGN);
-#pragma unroll
-            for (int it = 0; it < E; it++) raw[it][0] = at_lane(src + it * TH, tid);
-        };
-        fetch(0, 0);
         double s[2 * E], s2[U > 1 ? E : 1], s3[U > 1 ? E : 1];
-#pragma unroll
-        for (int it = 0; it < E; it++) {
-            s[it] = s[E + it] = 0.0;
-            if (U > 1) s2[it % (U > 1 ? E : 1)] = s3[it % (U > 1 ? E : 1)] = 0.0;
-        }
-        for (int j = 0; j < dnum; j++) {
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                double x[E];
-                const int row = ((b + u) * dnum + j) * L + r;
-#pragma unroll
-                for (int it = 0; it < E; it++) x[it] = ld.finish(raw[it], row, tid + it * TH, m, C);
-                if (u == 0) lds_barrier();      // the previous digit's (or unit's) LDS reads
-                fwd_row<LOGN, E, false>(lds + u * ROW, x, x, tid, tw, m);
-                if (U > 1) fetch(u + 1 < U ? u + 1 : 0, u + 1 < U || j + 1 == dnum ? j : j + 1);
-#pragma unroll
-                for (int it = 0; it < E; it += 2)
-                    pair_at(lds + u * ROW, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
-            }
-            lds_barrier();
-            int tk = tid;
-            asm volatile("" : "+v"(tk));
-            if constexpr (U == 1) sum_digit<LOGN, E, 4>(lds, T, n_rot, j, r, L, tk, m, s);
-            else sum_digits<LOGN, E>(lds, T, n_rot, j, r, L, tk, m, s, s + E, s2, s3);
-            if (U == 1) fetch(0, j + 1 < dnum ? j + 1 : j);     // (sooner there are no registers for it: 77.9 us there, 79.5 before the transform)
-        }
-        lds_barrier();
+        sum_units<LOGN, E, U>(lds, ld, T, n_rot, batch, b, r, tid, tw, m, C, s, s2, s3);
         // both components of a unit
         auto inverse = [&](const double *a, const double *c, int unit) {
             double y[2 * E];
@@ -1900,12 +1944,101 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
                 y[it] = a[it];
                 y[E + it] = c[it];
             }
-            inv_row<LOGN, E, false, (U > 1 ? 52 : hundredths(DotSum::OUT)), 2>(lds, y, st, (unit * 2) * L + r, tid, itw, m, r, C, L);
+            inv_row<LOGN, E, false, sum_bound<U>(), 2>(lds, y, st, (unit * 2) * L + r, tid, itw, m, r, C, L);
         };
         inverse(s, s + E, b);
         if (U > 1 && b + 1 < batch) {
             lds_barrier();
             inverse(s2, s3, b + 1);
+        }
+    }
+}
+
+// The same modulo the ciphertext primes, two units to a workgroup, once the accumulators modulo the special prime are there: the division by P
+// and the additions follow in registers, c0 permuted through LDS, as in ks_unit_kernel.  The accumulators of the other primes (six rows of
+// eight a ciphertext, written and read again) never reach memory and the mod-down launch, which memory bounds, is gone.  N = 8192, three digits, 7
+// rotations, 1536 ciphertexts: 1723 us with the mod-down, 1568 here and for the special prime (1673 with component 1's words asked for only when
+// component 0 is stored); what follows the transforms takes 24 to 31 us a workgroup, twelve rows' trips from memory.
+template <int LOGN, int E>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ks_sum_down_kernel(LdModup<false, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist H, const double *__restrict__ tw_all,
+                   const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    constexpr int TH = (1 << LOGN) / E, N = 1 << LOGN;
+    __shared__ __align__(16) double lds[2 * lds_doubles<LOGN>()];
+    const int tid = threadIdx.x, k = C->k, L = C->L, sets = (A.batch + 1) / 2;
+    const int per_xcd = (nwg + 7) >> 3, total = per_xcd * 8;       // as in ks_sum_row_kernel
+    for (int p = blockIdx.x; p < total; p += (int)gridDim.x) {
+        const int wg = (p & 7) * per_xcd + (p >> 3);
+        if (wg >= nwg) continue;
+        const int r = wg / sets, b0 = (wg - r * sets) * 2;
+        const ModD m = C->mod[r];
+        const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
+        double s[2 * E], s2[E], s3[E];
+        sum_units<LOGN, E, 2>(lds, ld, T, H.n_sum, A.batch, b0, r, tid, tw, m, C, s, s2, s3);
+        auto finish = [&](const double *s0, const double *s1, int b) {
+            double y[2 * E], xs[E];
+            uint64_t own[E];
+            const size_t row = (size_t)r << LOGN, comp = (size_t)k << LOGN;
+            const double *special = A.acc + ((size_t)(2 * b * L + k) << LOGN);
+            const uint64_t *in = A.add + (size_t)b * A.add_stride + row;
+            uint64_t *out = A.out + (size_t)b * A.out_stride + row;
+#pragma unroll
+            for (int it = 0; it < E; it++) {
+                y[it] = s0[it];
+                y[E + it] = s1[it];
+                xs[it] = 0.0, own[it] = 0;
+            }
+            auto ask = [&](int c) {
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+#pragma unroll
+                for (int it = 0; it < E; it++) {
+                    xs[it] = at_lane(special + ((size_t)(c * L) << LOGN) + it * TH, tk);
+                    own[it] = at_lane(in + c * comp + it * TH, tk);
+                }
+            };
+            inv_row<LOGN, E, false, sum_bound<2>(), 2>(lds, y, StRegs{y}, 0, tid, itw, m, r, C, 0, [&] { ask(0); });
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                int tk = tid;
+                asm volatile("" : "+v"(tk));
+                double v[E];
+#pragma unroll
+                for (int it = 0; it < E; it++) v[it] = mulmod(y[c * E + it] - red(xs[it], C->mod[k]), C->Pinv_q[r], m);
+                if (c == 0) {
+                    lds_barrier();
+#pragma unroll
+                    for (int it = 0; it < E; it++) lds[tk + it * TH] = u64_to_f64(own[it]);
+                    ask(1);     // (component 0's own words are read back from LDS)
+                    lds_barrier();
+                    for (int i = 0; i < H.n_sum; i++) {
+                        // terms are canonical up to their sign: four of them between two reductions
+                        const uint32_t ginv = H.ginv[i], e0 = (uint32_t)tk * ginv;
+#pragma unroll
+                        for (int it = 0; it < E; it++) {
+                            const uint32_t e = e0 + (uint32_t)(it * TH) * ginv;
+                            v[it] = signed_add(v[it], lds[e & (N - 1)], e << (31 - LOGN));
+                        }
+                        if ((i & 3) == 3) {
+#pragma unroll
+                            for (int it = 0; it < E; it++) v[it] = red(v[it], m);
+                        }
+                    }
+#pragma unroll
+                    for (int it = 0; it < E; it++) v[it] += lds[tk + it * TH];
+                } else {
+#pragma unroll
+                    for (int it = 0; it < E; it++) v[it] += u64_to_f64(own[it]);
+                }
+#pragma unroll
+                for (int it = 0; it < E; it++) put_lane(out + c * comp + it * TH, tk, f64_to_u64(canon(v[it], m)));
+            }
+        };
+        finish(s, s + E, b0);
+        if (b0 + 1 < A.batch) {
+            lds_barrier();
+            finish(s2, s3, b0 + 1);
         }
     }
 }
@@ -2757,37 +2890,6 @@ lift_kernel(MulSrc src, double *__restrict__ dst, const DevConst *__restrict__ C
     }
 }
 
-// mod-down with rounding and the final additions of relinearisation / rotation:
-//   u = floor((A + floor(P/2)) / P) = (A - x) / P mod Q with x the centred residue of A modulo P, in balanced
-//   digits (garner_balanced takes the transforms' results, below 2p);  out[b][c] = u (+ add0) (+ add1)
-// add0: relin -> in3[b][c];  rotate -> sigma_g(in2[b][0]) for c = 0, nothing for c = 1
-// add1: rotate with accumulate -> acc_add[b][c] (the rotated ciphertext itself, or another one)
-struct ModdownArgs {
-    const double *acc;        // [b][2][L][N] lazy, coefficient order
-    uint64_t *out;            // unit b at out + b*out_stride, [2][k][N]
-    size_t out_stride;
-    const uint64_t *add;      // base of the addend ciphertexts (unit 0) or null
-    size_t add_stride;        // uint64 per unit in add
-    uint32_t galois;          // != 0: add is permuted by X -> X^galois and only applies to c = 0
-    int accumulate;           // also add the un-permuted acc_add[b][c]
-    int batch;
-    const uint64_t *acc_add;  // base of the ciphertexts added un-permuted (accumulate)
-    size_t acc_stride;
-};
-// HOIST: the units are the rotations of a series, unit u = i * rot_batch + b being rotation i of
-// ciphertext b: its Galois element comes from the table, its addend is ciphertext b and its output
-// ciphertext b * out_per_b + i.
-// n_sum: rotations whose accumulators were summed (moddown_sum_kernel).
-template <int LOGN> constexpr int moddown_sum_split() { return (1 << LOGN) / 2048 >= 4 ? 4 : (1 << LOGN) / 2048; }
-struct ModdownHoist {
-    uint32_t ginv[MAXROT];
-    int rot_batch, out_per_b, n_sum;
-};
-// a + w or a - w as the top bit of s says
-__device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
-{
-    return a + bits_f64(f64_bits(w) ^ ((uint64_t)(s & 0x80000000u) << 32));
-}
 template <bool HOIST, int NSP>
 __global__ void __launch_bounds__(PW_THREADS)
 moddown_kernel(ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
