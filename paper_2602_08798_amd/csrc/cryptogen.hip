@@ -550,8 +550,9 @@ static unsigned ntt_grid(cg_ctx *c, size_t nwg, int threads)
 // 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726; N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
 // longer: theirs is the chain with more dependent key switches, which the step waits for.
 // wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
+// busy: their mod-ups have rows for three eighths of the compute units.
 struct Beside {
-    bool others = false, crowd = false, wide = false, longer = false;
+    bool others = false, crowd = false, wide = false, longer = false, busy = false;
 };
 
 // elements per thread for this context's transforms
@@ -753,6 +754,23 @@ static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t 
     case 5: return launch_ks_sum_d<5>(c, s, dig, T, n_rot, acc, batch);
     default: return launch_ks_sum_d<6>(c, s, dig, T, n_rot, acc, batch);
     }
+}
+
+// one ciphertext a thread, and the rows of the mod-down before
+static int launch_ks_sum_after(cg_ctx *c, hipStream_t s, double bytes, const uint64_t *dig, const HoistTab &T, uint32_t n_rot, double *acc, uint32_t batch,
+                               const ModdownArgs &A, const ModdownHoist &H)
+{
+    ProfScope ps(c, s, KID_KSSUM, bytes, (double)batch);
+    const unsigned sums = (unsigned)((size_t)batch * c->L * c->N / PW_THREADS), down = (unsigned)((size_t)batch * 2 * c->k * c->N / (2 * PW_THREADS));
+    const DevConst *dc = c->dc;
+#define CG_KSAFTER(D) return launch_kernel(ks_sum_after_kernel<D>, dim3(sums + down), dim3(PW_THREADS), s, dig, T, (int)n_rot, acc, (int)batch, (int)sums, A, H, dc)
+    switch (c->dnum) {
+    case 1: CG_KSAFTER(1);
+    case 2: CG_KSAFTER(2);
+    case 3: CG_KSAFTER(3);
+    default: return CG_EINVAL;
+    }
+#undef CG_KSAFTER
 }
 
 // The kernels that take a (unit, prime) through several transforms in one workgroup work in rounds of one row per compute
@@ -1356,6 +1374,21 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 #undef CG_MODUP
 }
 
+// the same behind a mod-down, in parts of rows
+static int launch_modup_down(cg_ctx *c, hipStream_t s, const LdModupDown &ld, uint64_t *dig, size_t nrows, int parts)
+{
+    ProfScope ps(c, s, KID_FWD_MODUP, (double)limb_bytes(c) * (2.0 * c->k + 1.0 + c->L * c->dnum) * ((double)nrows / (c->L * c->dnum)), (double)nrows);
+#define CG_MODUPDOWN(LG, LS)                                                                                                  \
+    return launch_kernel(ntt_fwd_part_kernel<LG, LS, LdModupDown, StU64>, dim3((unsigned)nrows << LS), dim3(1u << (LG - LS - 3)), s, ld, \
+                         StU64{dig, c->logn}, (const double *)c->tw, (const DevConst *)c->dc, (int)nrows)
+    switch (c->logn * 10 + parts) {
+    case 121: CG_MODUPDOWN(12, 1);
+    case 122: CG_MODUPDOWN(12, 2);
+    case 132: CG_MODUPDOWN(13, 2);
+    default: return CG_EINVAL;
+    }
+#undef CG_MODUPDOWN
+}
 // mod-up, inner product with the key and inverse transforms in one launch
 static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                          const double *key, double *acc, uint32_t batch)
@@ -1381,6 +1414,24 @@ static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t s
     }
 #undef CG_KSROW
 }
+// inner product with the key fused into the inverse transform's load
+static int launch_ks_inner(cg_ctx *c, hipStream_t s, const uint64_t *dig, const double *key, double *acc, uint32_t batch)
+{
+    const size_t irows = (size_t)batch * 2 * c->L;
+    const double dig_rows = (double)c->dnum * c->L;
+    const double ibytes = (double)limb_bytes(c) * ((dig_rows + 2.0 * c->L) * batch + 2.0 * dig_rows);
+    const StInvF64 ist{acc, c->logn};
+#define CG_KSI(D) return launch_inv(c, s, irows, LdInvKsInner<D>{dig, key, c->logn}, ist, KID_INV_KSINNER, ibytes)
+    switch (c->dnum) {
+    case 1: CG_KSI(1);
+    case 2: CG_KSI(2);
+    case 3: CG_KSI(3);
+    case 4: CG_KSI(4);
+    case 5: CG_KSI(5);
+    default: CG_KSI(6);
+    }
+#undef CG_KSI
+}
 // key switch of one ring element per unit (src + b*src_stride), then the final additions
 static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
                         const double *key, uint64_t *out2, size_t out_stride, const uint64_t *add, size_t add_stride,
@@ -1392,7 +1443,6 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
     uint64_t *dig = w.take<uint64_t>((size_t)c->dnum * c->L * batch);
     double *acc = w.take<double>((size_t)2 * c->L * batch);
     const double LB = (double)limb_bytes(c), B = batch;
-    const double dig_rows = (double)c->dnum * c->L;
     ModdownArgs A{acc, out2, out_stride, add, add_stride, galois_inv, accumulate, (int)batch, acc_add, acc_stride};
     const double add_rows = !add ? 0.0 : (galois_inv ? c->k + (accumulate ? 2.0 * c->k : 0.0) : 2.0 * c->k);
     if (add && ks_unit_wins(c, batch, 1, galois == 0)) {
@@ -1410,22 +1460,7 @@ static int do_keyswitch(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
         CG_TRY(launch_ks_row(c, s, src, src_stride, galois, key, acc, batch));
     } else {
         CG_TRY(launch_modup(c, s, src, src_stride, galois, batch, dig, beside.crowd));
-        // inner product with the key fused into the inverse transform's load
-        const size_t irows = (size_t)batch * 2 * c->L;
-        const double ibytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows);
-        const StInvF64 ist{acc, c->logn};
-        int rc;
-#define CG_KSI(D) launch_inv(c, s, irows, LdInvKsInner<D>{dig, key, c->logn}, ist, KID_INV_KSINNER, ibytes)
-        switch (c->dnum) {
-        case 1: rc = CG_KSI(1); break;
-        case 2: rc = CG_KSI(2); break;
-        case 3: rc = CG_KSI(3); break;
-        case 4: rc = CG_KSI(4); break;
-        case 5: rc = CG_KSI(5); break;
-        default: rc = CG_KSI(6); break;
-        }
-#undef CG_KSI
-        CG_TRY(rc);
+        CG_TRY(launch_ks_inner(c, s, dig, key, acc, batch));
     }
     return launch_moddown<false>(c, s, LB * (2.0 * c->L + add_rows + 2.0 * c->k) * B, batch, A, ModdownHoist{});
 }
@@ -1898,6 +1933,52 @@ static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint
     return CG_OK;
 }
 
+// A relinearisation and the rounds behind it where few units leave every launch bound by its own latency: the mod-up of a round takes the mod-down
+// before it in its loader, and that mod-down's rows come with the round's sums (ks_sum_after_kernel), three launches a round instead of four.  Every part of
+// every row repeats the mod-down of its digit, so up to half a row of the mod-up per compute unit at N = 4096, a quarter at N = 8192 (quarters of rows, as
+// row_parts), and there in a step's context only beside scores of up to 3/8, which the repeated work holds up otherwise.  us a step, four launches / three, heads x
+// ciphertexts (plain cache, with a transformed one).  N = 8192, three primes: 1 x 2 178 / 161, 179 / 168, 1 x 4 177 / 164, 181 / 172, 1 x 6 184 / 175, 194 / 184, 4 x 1 (d2 = 32)
+// 176 / 166, 183 / 177, 4 x 2 181 / 176, 190 / 187, 5 x 1 176 / 173, 185 / 183; beyond a quarter 9 x 1 208 / 213, 216 / 221, 10 x 1 (d2 = 32) 215 / 229, 228 / 241; beside more
+// scores 4 x 4 221 / 220, 224 / 228, 5 x 2 (d2 = 128) 199 / 212, 204 / 218, 5 x 4 254 / 259, 257 / 260.  N = 4096, two primes: 1 x 2 161 / 147, 3 x 1 178 / 158, 10 x 1 174 / 156,
+// 16 x 1 167 / 154, 163 / 153, 20 x 1 163 / 154, 167 / 166, 12 x 2 169 / 164, 168 / 163.
+static bool fold_joined_wins(const cg_ctx *c, uint32_t batch, const FoldRounds &R, const Beside &beside)
+{
+    if (c->logn > 13 || c->alpha != 1 || c->nsp != 1 || c->dnum > 3 || !R.n_rounds || beside.crowd || (c->logn == 13 && beside.busy)) return false;
+    return row_parts(c, (size_t)batch * c->dnum * c->L, false) >= (c->logn == 13 ? 2 : 1);
+}
+static int fold_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *x0, uint64_t *x1, uint64_t *out,
+                       const FoldRounds &R, const void *const *keys, uint32_t batch, void *ws, Beside beside)
+{
+    const size_t ct2 = (size_t)2 * c->k * c->N, ct3 = (size_t)3 * c->k * c->N, c1 = (size_t)c->k * c->N;
+    const size_t nrows = (size_t)batch * c->dnum * c->L, irows = (size_t)batch * 2 * c->L;
+    const double LB = (double)limb_bytes(c), B = batch, dig_rows = (double)c->dnum * c->L;
+    Bump w = bump(c, ws);
+    uint64_t *dig = w.take<uint64_t>(nrows);
+    double *acc = w.take<double>(irows), *sums = w.take<double>(irows);      // (ws_total has room for a product's rows here)
+    const int parts = row_parts(c, nrows, false);
+    CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig));
+    CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(rlk), acc, batch));
+    ModdownArgs A{acc, x0, ct2, in3, ct3, 1u, 1, (int)batch, in3, ct3};
+    ModdownHoist H{};
+    for (int r = 0; r < R.n_rounds; r++) {
+        const uint32_t n_rot = (uint32_t)R.count[r];
+        HoistTab T{};
+        for (uint32_t i = 0; i < n_rot; i++) {
+            T.g[i] = R.g[R.first[r] + i];
+            T.key[i] = static_cast<const double *>(keys[R.first[r] + i]);
+        }
+        CG_TRY(launch_modup_down(c, s, LdModupDown{acc, A.add + c1, A.add_stride, c->logn}, dig, nrows, parts));
+        CG_TRY(launch_ks_sum_after(c, s, LB * ((dig_rows + 4.0 * c->L + 4.0 * c->k) * B + 2.0 * dig_rows * n_rot), dig, T, n_rot, sums, batch, A, H));
+        CG_TRY(launch_inv(c, s, irows, LdInvF64{sums, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64, LB * 2.0 * irows,
+                          acc_parts(c, irows, beside.others)));
+        uint64_t *cur = A.out;
+        A = ModdownArgs{acc, r == R.n_rounds - 1 ? out : cur == x0 ? x1 : x0, ct2, cur, ct2, 1u, 1, (int)batch, cur, ct2};
+        for (uint32_t i = 0; i < n_rot; i++) H.ginv[i] = inv_mod_pow2(T.g[i], 2u * c->N);
+        H.n_sum = (int)n_rot;
+    }
+    return launch_moddown_sum(c, s, LB * (2.0 * c->L + 4.0 * c->k) * B, batch, A, H);
+}
+
 // generators of the two folding sums: the slots of a block (scores), the blocks and the two rows (context)
 static int fold_generators(const cg_ctx *c, uint32_t d2, uint32_t *gs)
 {
@@ -1950,6 +2031,7 @@ static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_
     uint64_t *d3 = w.take<uint64_t>((size_t)3 * c->k * batch);
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * batch), *xb = w.take<uint64_t>((size_t)2 * c->k * batch);
     CG_TRY(do_mul(c, s, q, kc, d3, batch, n_cts, w.p, 0, n_cts, cache_stride_cts, kext));
+    if (fold_w && fold_joined_wins(c, batch, R, beside)) return fold_joined(c, s, d3, rlk, xa, xb, out, R, gk_fold, batch, w.p, beside);
     CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
@@ -2002,6 +2084,7 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
         CG_LAUNCH_PW(KID_SUM_GROUPS, (double)limb_bytes(c) * rows * (batch + heads), (double)batch, sum_groups_kernel,
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
+    if (fold_w && fold_joined_wins(c, heads, R, beside)) return fold_joined(c, s, y, rlk, xa, xb, out, R, gk_block, heads, w.p, beside);
     CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p);
@@ -2113,8 +2196,9 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const bool few = 8 * srows <= (c->logn == 14 ? 3 : 4) * n, over = c->logn == 13 && 4 * (srows + own) >= 5 * n && srows <= n;
     const uint32_t own_switches = switches(c->N / d2, block_w), their = switches(d2, fold_w);
     const bool longer = own_switches > their || (c->logn == 12 && own_switches == their), context_first = longer && (few || over);
-    const Beside by_context{true}, by_scores{true, (size_t)heads * n_cts * c->dnum * c->L > n,
-                                             fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches};
+    const size_t modups = (size_t)heads * n_cts * c->dnum * c->L;
+    const Beside by_context{true}, by_scores{true, modups > n, fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches,
+                                             8 * modups > 3 * n};
     auto scores_on = [&](hipStream_t st) {
         return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, by_context);
     };

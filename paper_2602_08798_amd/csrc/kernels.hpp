@@ -1178,6 +1178,35 @@ struct LdModup {
     }
 };
 
+// The mod-up of a ciphertext that a mod-down is still to deliver (one special prime, one prime to a digit, no map): its second component modulo prime j is
+// add + (A_j - x) / P, as moddown_kernel and moddown_sum_kernel leave it (nothing permuted is added there), canonical as every digit.
+struct LdModupDown {
+    static constexpr int kRaw = 3;
+    static constexpr bool kPrefetch = false;
+    static constexpr bool kScatter = false;
+    const double *acc;       // [unit][2][L][N], coefficients
+    const uint64_t *add;     // second component of unit 0
+    size_t add_stride;       // in uint64
+    int logn;
+    __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % C->L; }
+    __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const { return wg; }
+    __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *C, uint64_t *raw) const
+    {
+        const int L = C->L, k = C->k, j = (wg / L) % k, b = wg / (L * k);
+        const double *a = acc + (((size_t)(2 * b + 1) * L) << logn) + idx;
+        raw[0] = f64_bits(a[(size_t)j << logn]);
+        raw[1] = f64_bits(a[(size_t)k << logn]);
+        raw[2] = add[(size_t)b * add_stride + ((size_t)j << logn) + idx];
+    }
+    __device__ __forceinline__ double finish(const uint64_t *raw, int wg, int, const ModD, const DevConst *C) const
+    {
+        const int k = C->k, j = (wg / C->L) % k;
+        const ModD mj = C->mod[j];
+        const double x = red(bits_f64(raw[1]), C->mod[k]);
+        return canon(mulmod(bits_f64(raw[0]) - x, C->Pinv_q[j], mj) + u64_to_f64(raw[2]), mj);
+    }
+};
+
 // plaintext polynomial mod t -> centred lift -> row modulo q_i: workgroup -> (b, i)
 struct LdPlain {
     static constexpr int kRaw = 1;
@@ -3428,17 +3457,17 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
 // 32 x 32 + 64 multiply-adds, which run at the FP64 rate here, and one modular reduction ends it.
 // N = 8192, 7 rotations, with the inverse transforms: 48 ciphertexts 77 -> 54 us, 12: 33 -> 20 us,
 // one: 32 -> 14 us.
+// block blk of nblk
 template <int DNUM, int U>
-__global__ void __launch_bounds__(PW_THREADS)
-ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch,
-              const DevConst *__restrict__ C)
+__device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *__restrict__ dig, const HoistTab &T, int n_rot, double *__restrict__ acc,
+                                             int batch, const DevConst *__restrict__ C)
 {
     const int logn = C->logn, L = C->L, chunks = (1 << logn) / PW_THREADS;
     // Logical order: prime, ciphertext group, chunk of the row (fastest); XCD x takes the x-th eighth of
     // it.  The gathers of a digit row then stay on one XCD, and an XCD works with the keys of one or
     // two primes.  (chunks is a multiple of 8.)
-    const int per_xcd = (int)gridDim.x >> 3;
-    const int lg = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    const int per_xcd = nblk >> 3;
+    const int lg = (blk & 7) * per_xcd + (blk >> 3);
     const int groups = (batch + U - 1) / U;
     const int idx = (lg % chunks) * PW_THREADS + (int)threadIdx.x;
     const int ug = lg / chunks % groups, r = lg / (chunks * groups);
@@ -3539,6 +3568,64 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
             acc[(((size_t)((ug * U + u) * 2 + c) * L + r) << logn) + idx] = v;
         }
     }
+}
+
+template <int DNUM, int U>
+__global__ void __launch_bounds__(PW_THREADS)
+ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch,
+              const DevConst *__restrict__ C)
+{
+    ks_sum_block<DNUM, U>((int)blockIdx.x, (int)gridDim.x, dig, T, n_rot, acc, batch, C);
+}
+
+// The same, and behind its n_sums blocks those of the mod-down that the digits' mod-up took ahead of it (LdModupDown): a workgroup takes 512
+// coefficients of one row (unit, component, prime) of
+//   out = in + u (+ sum_r sigma_r(c0), component 0),
+// the permuted coefficients gathered from L2, four rotations' together; next to the sums, which take longer, that is hidden.  A series of dependent
+// key switches of few units is bound by its launches, of which this takes one away for each.
+template <int DNUM>
+__global__ void __launch_bounds__(PW_THREADS)
+ks_sum_after_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch, int n_sums,
+                    ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
+{
+    if ((int)blockIdx.x < n_sums) {
+        ks_sum_block<DNUM, 1>((int)blockIdx.x, n_sums, dig, T, n_rot, acc, batch, C);
+        return;
+    }
+    const int logn = C->logn, k = C->k, chunks = (1 << logn) / (2 * PW_THREADS), blk = (int)blockIdx.x - n_sums;
+    const int row = blk / chunks, n = (blk % chunks * PW_THREADS + (int)threadIdx.x) * 2, i = row % k, bc = row / k, b = bc >> 1, c = bc & 1;
+    const uint32_t mask = (1u << logn) - 1u;
+    const ModD m = C->mod[i];
+    const uint64_t *in = A.add + (size_t)b * A.add_stride + ((size_t)(c * k + i) << logn);
+    const double *a = A.acc + (((size_t)bc * C->L) << logn) + n;
+    const double2 xp = *reinterpret_cast<const double2 *>(a + ((size_t)k << logn)), ap = *reinterpret_cast<const double2 *>(a + ((size_t)i << logn));
+    const ulonglong2 own = *reinterpret_cast<const ulonglong2 *>(in + n);
+    double v0 = mulmod(ap.x - red(xp.x, C->mod[k]), C->Pinv_q[i], m), v1 = mulmod(ap.y - red(xp.y, C->mod[k]), C->Pinv_q[i], m);
+    const int n_sum = c ? 0 : H.n_sum;
+    for (int r0 = 0; r0 < n_sum; r0 += 4) {
+        // terms are canonical up to their sign: four of them between two reductions
+        uint64_t w[4][2];
+        uint32_t e[4][2];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const uint32_t g = H.ginv[r0 + r < n_sum ? r0 + r : 0];
+            e[r][0] = (uint32_t)n * g;
+            e[r][1] = e[r][0] + g;
+#pragma unroll
+            for (int h = 0; h < 2; h++) w[r][h] = in[e[r][h] & mask];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+            if (r0 + r < n_sum) {
+                v0 = signed_add(v0, u64_to_f64(w[r][0]), e[r][0] << (31 - logn));
+                v1 = signed_add(v1, u64_to_f64(w[r][1]), e[r][1] << (31 - logn));
+            }
+        v0 = red(v0, m);
+        v1 = red(v1, m);
+    }
+    uint64_t *o = A.out + (size_t)b * A.out_stride + ((size_t)(c * k + i) << logn) + n;
+    *reinterpret_cast<ulonglong2 *>(o) =
+        make_ulonglong2(f64_to_u64(canon(v0 + u64_to_f64(own.x), m)), f64_to_u64(canon(v1 + u64_to_f64(own.y), m)));
 }
 
 // ciphertext u of `src` (src_stride words apart) to dst + u * dst_stride, two words per thread

@@ -1,0 +1,64 @@
+"""Attention calls of few units, whose rounds of summed rotations take the mod-down before them in the mod-up's loader and beside the sums, against the
+same product, relinearisation and summed rotations as calls of their own, bit for bit (those are compared with the oracle elsewhere).  Numbers of units on
+both sides of the rule's limits (256 compute units) and of where rows go from quarters to halves; rounds of one to four bits (1 to 15 rotations);
+uniform residues and the largest ones."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from workloads import PRESETS
+from workloads.params import ParamSet
+
+from .bruteforce import ntt_primes
+from .test_gpu_parity import say
+
+_P = ntt_primes(1 << 50, 2 << 13, 2)
+SETS = {**PRESETS, "k1": ParamSet("n8192_k1_joined", 13, q=tuple(_P[:1]), p=tuple(_P[1:]), alpha=1)}
+_state = {}
+
+
+def _residues(primes, n, largest, *lead):
+    import torch
+    g = _state.setdefault("generator", torch.Generator(device="cuda").manual_seed(78))
+    out = torch.empty(*lead, len(primes), n, dtype=torch.int64, device="cuda")
+    for i, p in enumerate(primes):
+        out[..., i, :] = int(p) - 1 if largest else torch.randint(0, int(p), (*lead, n), generator=g, device="cuda")
+    return out
+
+
+def _ctx(name, largest):
+    import paper_2602_08798_amd as P
+    if (name, largest) not in _state:
+        prm = SETS[name]
+        ctx = P.Context(prm)
+        _state[name, largest] = ctx, [ctx.ksk_prepare(_residues(list(prm.q) + list(prm.p), prm.n, largest, prm.dnum, 2)) for _ in range(3)]
+    return _state[name, largest]
+
+
+def _rounds(bits, w):
+    n = -(-bits // w)
+    lo, extra = divmod(bits, n)
+    return [(1 << (lo + (r < extra))) - 1 for r in range(n)]
+
+
+@pytest.mark.parametrize("name,units,d2,w,largest", [
+    ("C2", 1, 64, 3, False), ("C2", 1, 2, 3, False), ("C2", 2, 128, 1, False), ("C2", 3, 32, 2, True), ("C2", 5, 256, 4, False), ("C2", 6, 64, 3, False),
+    ("C1", 1, 64, 3, True), ("C1", 10, 64, 3, False), ("C1", 11, 32, 3, False), ("C1", 21, 16, 4, True), ("C1", 22, 64, 3, False),
+    ("k1", 3, 64, 3, False), ("k1", 32, 16, 2, False)])
+def test_joined_rounds(name, units, d2, w, largest):
+    import torch
+    say(f"joined rounds {name}: {units} units, d2 = {d2}, {w} bits, largest {largest}")
+    prm = SETS[name]
+    ctx, keys = _ctx(name, largest)
+    x, y = _residues(prm.q, prm.n, largest, units, 2), _residues(prm.q, prm.n, largest, units, 2)
+    slots, blocks = d2.bit_length() - 1, (prm.n // d2).bit_length() - 1
+    for which, bits in ((0, slots), (1, blocks)):
+        gs = ctx.round_galois(which, d2, w)
+        used = [keys[1 + i % 2] for i in range(len(gs))]
+        want, at = ctx.relin(ctx.mul(x, y, units), keys[0], units), 0
+        for n in _rounds(bits, w):
+            want = ctx.rotate_sum_hoisted(want, gs[at:at + n], used[at:at + n], units)
+            at += n
+        assert at == len(gs)
+        got = (ctx.decode_context_hoisted if which else ctx.decode_scores_hoisted)(x, y, units, 1, d2, w, keys[0], used)
+        assert torch.equal(got.view(-1), want.view(-1)), (name, units, which)
