@@ -551,8 +551,9 @@ static unsigned ntt_grid(cg_ctx *c, size_t nwg, int threads)
 // longer: theirs is the chain with more dependent key switches, which the step waits for.
 // wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
 // busy: their mod-ups have rows for three eighths of the compute units.
+// leads: theirs is the chain with at least two dependent key switches fewer, and their (unit, prime) rows take one round.
 struct Beside {
-    bool others = false, crowd = false, wide = false, longer = false, busy = false;
+    bool others = false, crowd = false, wide = false, longer = false, busy = false, leads = false;
 };
 
 // elements per thread for this context's transforms
@@ -1374,13 +1375,13 @@ static int launch_modup(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t sr
 #undef CG_MODUP
 }
 
-// the same behind a mod-down, in parts of rows
-static int launch_modup_down(cg_ctx *c, hipStream_t s, const LdModupDown &ld, uint64_t *dig, size_t nrows, int parts)
+// the same behind a mod-down: in parts of rows, and with a map whole rows (no occupancy to look up: a workgroup takes one row)
+static int launch_modup_down(cg_ctx *c, hipStream_t s, const LdModupDown<false> &ld, uint64_t *dig, size_t nrows, int parts)
 {
     ProfScope ps(c, s, KID_FWD_MODUP, (double)limb_bytes(c) * (2.0 * c->k + 1.0 + c->L * c->dnum) * ((double)nrows / (c->L * c->dnum)), (double)nrows);
 #define CG_MODUPDOWN(LG, LS)                                                                                                  \
-    return launch_kernel(ntt_fwd_part_kernel<LG, LS, LdModupDown, StU64>, dim3((unsigned)nrows << LS), dim3(1u << (LG - LS - 3)), s, ld, \
-                         StU64{dig, c->logn}, (const double *)c->tw, (const DevConst *)c->dc, (int)nrows)
+    return launch_kernel(ntt_fwd_part_kernel<LG, LS, LdModupDown<false>, StU64>, dim3((unsigned)nrows << LS), dim3(1u << (LG - LS - 3)), s, \
+                         ld, StU64{dig, c->logn}, (const double *)c->tw, (const DevConst *)c->dc, (int)nrows)
     switch (c->logn * 10 + parts) {
     case 121: CG_MODUPDOWN(12, 1);
     case 122: CG_MODUPDOWN(12, 2);
@@ -1388,6 +1389,38 @@ static int launch_modup_down(cg_ctx *c, hipStream_t s, const LdModupDown &ld, ui
     default: return CG_EINVAL;
     }
 #undef CG_MODUPDOWN
+}
+static int launch_modup_down(cg_ctx *c, hipStream_t s, const LdModupDown<true> &ld, uint64_t *dig, size_t nrows)
+{
+    ProfScope ps(c, s, KID_FWD_MODUP, (double)limb_bytes(c) * (2.0 * c->k + 1.0 + c->L * c->dnum) * ((double)nrows / (c->L * c->dnum)), (double)nrows);
+#define CG_MODUPDOWN(LG)                                                                                                      \
+    return launch_kernel(ntt_fwd_kernel<LG, 8, LdModupDown<true>, StU64>, dim3((unsigned)nrows), dim3((1u << LG) / 8), s, ld,  \
+                         StU64{dig, c->logn}, (const double *)c->tw, (const DevConst *)c->dc, (int)nrows)
+    if (c->logn == 12) CG_MODUPDOWN(12);
+    CG_MODUPDOWN(13);
+#undef CG_MODUPDOWN
+}
+// inner product and inverse transforms, and the rows of the mod-down before
+static int launch_ks_inner_after(cg_ctx *c, hipStream_t s, const uint64_t *dig, const double *key, double *acc, uint32_t batch, const ModdownArgs &A,
+                                 const ModdownHoist &H)
+{
+    const size_t irows = (size_t)batch * 2 * c->L, pairs = (size_t)batch * c->k * c->N;
+    const double dig_rows = (double)c->dnum * c->L;
+    ProfScope ps(c, s, KID_INV_KSINNER, (double)limb_bytes(c) * ((dig_rows + 4.0 * c->L + 4.0 * c->k) * batch + 2.0 * dig_rows), (double)irows);
+    const DevConst *dc = c->dc;
+#define CG_INNERAFTER(LG, D)                                                                                                  \
+    return launch_kernel(ks_inner_after_kernel<LG, 8, D>, dim3((unsigned)(irows + pairs / ((1u << LG) / 8))), dim3((1u << LG) / 8), s, \
+                         LdInvKsInner<D>{dig, key, c->logn}, StInvF64{acc, c->logn}, (const double *)c->itw, (int)irows, A, H, dc)
+    switch (c->logn * 10 + c->dnum) {
+    case 121: CG_INNERAFTER(12, 1);
+    case 122: CG_INNERAFTER(12, 2);
+    case 123: CG_INNERAFTER(12, 3);
+    case 131: CG_INNERAFTER(13, 1);
+    case 132: CG_INNERAFTER(13, 2);
+    case 133: CG_INNERAFTER(13, 3);
+    default: return CG_EINVAL;
+    }
+#undef CG_INNERAFTER
 }
 // mod-up, inner product with the key and inverse transforms in one launch
 static int launch_ks_row(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t src_stride, uint32_t galois,
@@ -1864,11 +1897,59 @@ static uint32_t pow3_mod(uint32_t e, uint32_t two_n)
     return (uint32_t)r;
 }
 
+// A relinearisation (in3; null: x0 holds what the first rotation takes) and a chain of single rotations, each added to what it rotates: a rotation's mod-up
+// takes the mod-down before it in its loader, and that mod-down's rows come with the rotation's inner products (ks_inner_after_kernel), two launches a rotation instead
+// of three.  Taken while the mod-up has no more rows than compute units, at N = 4096 (two workgroups to a unit) one and a half times as many.  Beside scores whose mod-ups
+// have a row for every unit only a context that leads: the step waits for its chain, and the scores' work fits in beside it.  us a step, three launches / two, heads x
+// ciphertexts, d2 = 64 unless said.  N = 8192, three primes: 1 x 1 267 / 239, 4 x 2 302 / 277, 9 x 1 317 / 298, 12 x 1 354 / 311, 16 x 1 394 / 371, 5 x 4 374 / 350, 8 x 2
+// (d2 = 128) 352 / 318, 7 x 3 393 / 362; above, with a limit at 3/2: 11 x 2 406 / 421, 10 x 3 480 / 498, 8 x 3 415 / 410.  N = 4096, two: 1 x 1 239 / 200, 10 x 2 243 / 198,
+// 16 x 1 240 / 192, 11 x 4 278 / 260, 12 x 5 297 / 286, 16 x 4 306 / 299, and at twice the units 16 x 5 317 / 336.  A context beside more scores: d2 = 32 (eight rotations
+// against five) 12 x 4 621 / 561, 10 x 3 489 / 437, 5 x 7 510 / 470, 16 x 4 733 / 724, N = 4096 11 x 4 290 / 245, 16 x 5 323 / 297; with more than a round of (unit,
+// prime) 14 x 8 1033 / 1054, N = 4096 16 x 8 403 / 408; seven rotations against six 16 x 2 517 / 532, 5 x 7 504 / 515, 8 x 5 594 / 572.  Projections of a token, a
+// chain of eight rotations of 1, 4, 9, 16 and 21 units: N = 8192 198 / 163, 202 / 177, 236 / 195, 248 / 203, 249 / 228, N = 4096, seven, 112 / 89 to 136 / 114, 36 units 147 / 123.
+static bool chain_joined_wins(const cg_ctx *c, uint32_t batch, int n, const Beside &beside)
+{
+    if (c->logn > 13 || c->alpha != 1 || c->nsp != 1 || c->dnum > 3 || !n || (beside.crowd && !beside.leads)) return false;
+    return 2 * (size_t)batch * c->dnum * c->L <= (c->logn == 12 ? 3 : 2) * (size_t)c->n_cu;
+}
+static int chain_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *x0, uint64_t *x1, uint64_t *out,
+                        const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws)
+{
+    const size_t ct2 = (size_t)2 * c->k * c->N, ct3 = (size_t)3 * c->k * c->N, c1 = (size_t)c->k * c->N;
+    const size_t nrows = (size_t)batch * c->dnum * c->L, irows = (size_t)batch * 2 * c->L;
+    Bump w = bump(c, ws);
+    uint64_t *dig = w.take<uint64_t>(nrows);
+    double *acc[2] = {w.take<double>(irows), w.take<double>(irows)};
+    ModdownArgs A{acc[0], x0, ct2, in3, ct3, 1u, 1, (int)batch, in3, ct3};
+    ModdownHoist H{};
+    if (in3) {
+        CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig));
+        CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(rlk), acc[0], batch));
+    } else {
+        CG_TRY(launch_modup(c, s, x0 + c1, ct2, gs[0], batch, dig));
+        CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(keys[0]), acc[0], batch));
+        A = ModdownArgs{acc[0], n == 1 ? out : x1, ct2, x0, ct2, 1u, 1, (int)batch, x0, ct2};
+        H.ginv[0] = inv_mod_pow2(gs[0], 2u * c->N);
+        H.n_sum = 1;
+    }
+    for (int i = in3 ? 0 : 1; i < n; i++) {
+        double *to = A.acc == acc[0] ? acc[1] : acc[0];
+        CG_TRY(launch_modup_down(c, s, LdModupDown<true>{A.acc, A.add + c1, A.add_stride, gs[i], c->logn}, dig, nrows));
+        CG_TRY(launch_ks_inner_after(c, s, dig, static_cast<const double *>(keys[i]), to, batch, A, H));
+        uint64_t *cur = A.out;
+        A = ModdownArgs{to, i == n - 1 ? out : cur == x0 ? x1 : x0, ct2, cur, ct2, 1u, 1, (int)batch, cur, ct2};
+        H.ginv[0] = inv_mod_pow2(gs[i], 2u * c->N);
+        H.n_sum = 1;
+    }
+    return launch_moddown_sum(c, s, (double)limb_bytes(c) * (2.0 * c->L + 4.0 * c->k) * batch, batch, A, H);
+}
+
 // x <- x + rotate(x, g) for each g of the list, ping-ponging between two buffers;
 // the last result lands in `out`.  x0 holds the start value.
 static int rotate_add_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint64_t *out,
-                            const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws)
+                            const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws, Beside beside = {})
 {
+    if (n > 1 && chain_joined_wins(c, batch, n, beside)) return chain_joined(c, s, nullptr, nullptr, x0, x1, out, gs, keys, n, batch, ws);
     uint64_t *cur = x0, *nxt = x1;
     for (int i = 0; i < n; i++) {
         uint64_t *dst = (i == n - 1) ? out : nxt;
@@ -1956,10 +2037,10 @@ static int fold_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void
     uint64_t *dig = w.take<uint64_t>(nrows);
     double *acc = w.take<double>(irows), *sums = w.take<double>(irows);      // (ws_total has room for a product's rows here)
     const int parts = row_parts(c, nrows, false);
-    CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig));
-    CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(rlk), acc, batch));
     ModdownArgs A{acc, x0, ct2, in3, ct3, 1u, 1, (int)batch, in3, ct3};
     ModdownHoist H{};
+    CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig));
+    CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(rlk), acc, batch));
     for (int r = 0; r < R.n_rounds; r++) {
         const uint32_t n_rot = (uint32_t)R.count[r];
         HoistTab T{};
@@ -1967,7 +2048,7 @@ static int fold_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void
             T.g[i] = R.g[R.first[r] + i];
             T.key[i] = static_cast<const double *>(keys[R.first[r] + i]);
         }
-        CG_TRY(launch_modup_down(c, s, LdModupDown{acc, A.add + c1, A.add_stride, c->logn}, dig, nrows, parts));
+        CG_TRY(launch_modup_down(c, s, LdModupDown<false>{acc, A.add + c1, A.add_stride, 0, c->logn}, dig, nrows, parts));
         CG_TRY(launch_ks_sum_after(c, s, LB * ((dig_rows + 4.0 * c->L + 4.0 * c->k) * B + 2.0 * dig_rows * n_rot), dig, T, n_rot, sums, batch, A, H));
         CG_TRY(launch_inv(c, s, irows, LdInvF64{sums, c->L, c->logn}, StInvF64{acc, c->logn}, KID_INV_F64, LB * 2.0 * irows,
                           acc_parts(c, irows, beside.others)));
@@ -2032,9 +2113,10 @@ static int scores_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_
     uint64_t *xa = w.take<uint64_t>((size_t)2 * c->k * batch), *xb = w.take<uint64_t>((size_t)2 * c->k * batch);
     CG_TRY(do_mul(c, s, q, kc, d3, batch, n_cts, w.p, 0, n_cts, cache_stride_cts, kext));
     if (fold_w && fold_joined_wins(c, batch, R, beside)) return fold_joined(c, s, d3, rlk, xa, xb, out, R, gk_fold, batch, w.p, beside);
+    if (!fold_w && chain_joined_wins(c, batch, nrot, beside)) return chain_joined(c, s, d3, rlk, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
     CG_TRY(do_relin(c, s, d3, rlk, xa, batch, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_fold, batch, w.p, beside);
-    return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p);
+    return rotate_add_chain(c, s, xa, xb, out, gs, gk_fold, nrot, batch, w.p, beside);
 }
 extern "C" int cg_decode_scores(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t *kc, uint32_t heads,
                                 uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
@@ -2085,9 +2167,10 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
     if (fold_w && fold_joined_wins(c, heads, R, beside)) return fold_joined(c, s, y, rlk, xa, xb, out, R, gk_block, heads, w.p, beside);
+    if (!fold_w && chain_joined_wins(c, heads, nrot, beside)) return chain_joined(c, s, y, rlk, xa, xb, out, gs, gk_block, nrot, heads, w.p);
     CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, beside);
-    return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p);
+    return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p, beside);
 }
 extern "C" int cg_decode_context(cg_ctx *c, void *stream, const uint64_t *a, const uint64_t *vc, uint32_t heads,
                                  uint32_t n_cts, uint32_t cache_stride_cts, uint32_t d2, const void *rlk,
@@ -2198,7 +2281,7 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const bool longer = own_switches > their || (c->logn == 12 && own_switches == their), context_first = longer && (few || over);
     const size_t modups = (size_t)heads * n_cts * c->dnum * c->L;
     const Beside by_context{true}, by_scores{true, modups > n, fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches,
-                                             8 * modups > 3 * n};
+                                             8 * modups > 3 * n, own_switches >= their + 2 && srows <= n};
     auto scores_on = [&](hipStream_t st) {
         return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, by_context);
     };

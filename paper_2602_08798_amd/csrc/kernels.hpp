@@ -763,20 +763,19 @@ __device__ __forceinline__ void inv_pass(double *lds, const ST &st, int wg, int 
     }
 }
 
+// rows p, p + step, ... of nwg
 template <int LOGN, int E, class LD, class ST>
-__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
-ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+__device__ __forceinline__ void inv_rows(double *lds, int p, int step, const LD &ld, const ST &st, const double *__restrict__ itw_all,
+                                         const DevConst *__restrict__ C, int nwg)
 {
-    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
     constexpr bool PF = LD::kPrefetch && prefetch_rows<LOGN, E>();
     constexpr int NP = Plan<LOGN, E>::NP, IN = ld_in<LD>::value;
     static_assert(NP - 1 >= Plan<LOGN, E>::NC, "the first inverse pass must be wave-local");
     // (N = 4096, 1500 rows: 24.9 -> 23.6 us, 4096: 57 -> 55.  N = 8192, 512 threads: inv_wide; 1024 threads: 1000 rows 35.7 -> 37.0, 4000 the
     // same; 4000 of 16384: 274 -> 286.)
-    const bool prio = (LOGN <= 12 || (LOGN == 13 && E == 16)) && row_alone<LD, ST>::value && 2 * nwg >= 3 * (int)gridDim.x;
+    const bool prio = (LOGN <= 12 || (LOGN == 13 && E == 16)) && row_alone<LD, ST>::value && 2 * nwg >= 3 * step;
     const int tid = threadIdx.x;
     const int S = ld.share(C);
-    int p = blockIdx.x;
     int wg = xcd_row(p, nwg, S);
     uint64_t raw[PF ? E : 1][LD::kRaw];
     if constexpr (PF) fetch_row<LOGN, E, true>(ld, wg, tid, C, raw);
@@ -804,7 +803,7 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
                 });
             }
         }
-        p += (int)gridDim.x;
+        p += step;
         const bool more = p < nwg;
         const int wg_next = more ? xcd_row(p, nwg, S) : 0;
         const int orow = ld.out_row(wg, C);
@@ -833,6 +832,13 @@ ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst 
         wg = wg_next;
         lds_barrier();   // pass 0's LDS reads precede the next row's LDS writes
     }
+}
+template <int LOGN, int E, class LD, class ST>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ntt_inv_kernel(LD ld, ST st, const double *__restrict__ itw_all, const DevConst *__restrict__ C, int nwg)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    inv_rows<LOGN, E>(lds, (int)blockIdx.x, (int)gridDim.x, ld, st, itw_all, C, nwg);
 }
 
 // Inverse loaders marked here run with 16 elements per thread at N = 8192 where there are more rows than this many halves of the compute units,
@@ -1178,17 +1184,21 @@ struct LdModup {
     }
 };
 
-// The mod-up of a ciphertext that a mod-down is still to deliver (one special prime, one prime to a digit, no map): its second component modulo prime j is
+// The mod-up of a ciphertext that a mod-down is still to deliver (one special prime, one prime to a digit; GALOIS: mapped first, as in LdModup): its second component modulo prime j is
 // add + (A_j - x) / P, as moddown_kernel and moddown_sum_kernel leave it (nothing permuted is added there), canonical as every digit.
+template <bool GALOIS>
 struct LdModupDown {
     static constexpr int kRaw = 3;
     static constexpr bool kPrefetch = false;
-    static constexpr bool kScatter = false;
+    static constexpr bool kScatter = GALOIS;
     const double *acc;       // [unit][2][L][N], coefficients
     const uint64_t *add;     // second component of unit 0
     size_t add_stride;       // in uint64
+    uint32_t galois;
     int logn;
     __device__ __forceinline__ int prime(int wg, const DevConst *C) const { return wg % C->L; }
+    __device__ __forceinline__ int share(const DevConst *C) const { return C->L; }
+    __device__ __forceinline__ int place(int idx, int n) const { return (int)((uint32_t)idx * galois & (n - 1)); }
     __device__ __forceinline__ int dst_limb(int wg, const DevConst *) const { return wg; }
     __device__ __forceinline__ void fetch(int wg, int idx, const DevConst *C, uint64_t *raw) const
     {
@@ -1198,12 +1208,13 @@ struct LdModupDown {
         raw[1] = f64_bits(a[(size_t)k << logn]);
         raw[2] = add[(size_t)b * add_stride + ((size_t)j << logn) + idx];
     }
-    __device__ __forceinline__ double finish(const uint64_t *raw, int wg, int, const ModD, const DevConst *C) const
+    __device__ __forceinline__ double finish(const uint64_t *raw, int wg, int idx, const ModD, const DevConst *C) const
     {
         const int k = C->k, j = (wg / C->L) % k;
         const ModD mj = C->mod[j];
         const double x = red(bits_f64(raw[1]), C->mod[k]);
-        return canon(mulmod(bits_f64(raw[0]) - x, C->Pinv_q[j], mj) + u64_to_f64(raw[2]), mj);
+        const double v = canon(mulmod(bits_f64(raw[0]) - x, C->Pinv_q[j], mj) + u64_to_f64(raw[2]), mj);
+        return GALOIS && ((uint32_t)idx * galois >> logn & 1) && v != 0.0 ? mj.p - v : v;
     }
 };
 
@@ -3578,22 +3589,14 @@ ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *_
     ks_sum_block<DNUM, U>((int)blockIdx.x, (int)gridDim.x, dig, T, n_rot, acc, batch, C);
 }
 
-// The same, and behind its n_sums blocks those of the mod-down that the digits' mod-up took ahead of it (LdModupDown): a workgroup takes 512
-// coefficients of one row (unit, component, prime) of
+// Block blk of a mod-down that a mod-up took ahead of it (LdModupDown): THREADS pairs of coefficients of one row (unit, component, prime) of
 //   out = in + u (+ sum_r sigma_r(c0), component 0),
-// the permuted coefficients gathered from L2, four rotations' together; next to the sums, which take longer, that is hidden.  A series of dependent
-// key switches of few units is bound by its launches, of which this takes one away for each.
-template <int DNUM>
-__global__ void __launch_bounds__(PW_THREADS)
-ks_sum_after_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch, int n_sums,
-                    ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
+// the permuted coefficients gathered from L2, four rotations' together; it runs beside longer blocks.
+template <int THREADS>
+__device__ __forceinline__ void down_block(int blk, const ModdownArgs &A, const ModdownHoist &H, const DevConst *__restrict__ C)
 {
-    if ((int)blockIdx.x < n_sums) {
-        ks_sum_block<DNUM, 1>((int)blockIdx.x, n_sums, dig, T, n_rot, acc, batch, C);
-        return;
-    }
-    const int logn = C->logn, k = C->k, chunks = (1 << logn) / (2 * PW_THREADS), blk = (int)blockIdx.x - n_sums;
-    const int row = blk / chunks, n = (blk % chunks * PW_THREADS + (int)threadIdx.x) * 2, i = row % k, bc = row / k, b = bc >> 1, c = bc & 1;
+    const int logn = C->logn, k = C->k, chunks = (1 << logn) / (2 * THREADS);
+    const int row = blk / chunks, n = (blk % chunks * THREADS + (int)threadIdx.x) * 2, i = row % k, bc = row / k, b = bc >> 1, c = bc & 1;
     const uint32_t mask = (1u << logn) - 1u;
     const ModD m = C->mod[i];
     const uint64_t *in = A.add + (size_t)b * A.add_stride + ((size_t)(c * k + i) << logn);
@@ -3626,6 +3629,27 @@ ks_sum_after_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, dou
     uint64_t *o = A.out + (size_t)b * A.out_stride + ((size_t)(c * k + i) << logn) + n;
     *reinterpret_cast<ulonglong2 *>(o) =
         make_ulonglong2(f64_to_u64(canon(v0 + u64_to_f64(own.x), m)), f64_to_u64(canon(v1 + u64_to_f64(own.y), m)));
+}
+
+// The same, and behind its n_sums blocks those of the mod-down before.  A series of dependent key switches of few units is bound by its launches, of
+// which this takes one away for each.
+template <int DNUM>
+__global__ void __launch_bounds__(PW_THREADS)
+ks_sum_after_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch, int n_sums,
+                    ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
+{
+    if ((int)blockIdx.x < n_sums) ks_sum_block<DNUM, 1>((int)blockIdx.x, n_sums, dig, T, n_rot, acc, batch, C);
+    else down_block<PW_THREADS>((int)blockIdx.x - n_sums, A, H, C);
+}
+// One rotation's, or a relinearisation's, inner product in the loader of its inverse transform, nwg rows
+template <int LOGN, int E, int DNUM>
+__global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
+ks_inner_after_kernel(LdInvKsInner<DNUM> ld, StInvF64 st, const double *__restrict__ itw_all, int nwg, ModdownArgs A, ModdownHoist H,
+                      const DevConst *__restrict__ C)
+{
+    __shared__ __align__(16) double lds[lds_doubles<LOGN>()];
+    if ((int)blockIdx.x < nwg) inv_rows<LOGN, E>(lds, (int)blockIdx.x, nwg, ld, st, itw_all, C, nwg);
+    else down_block<(1 << LOGN) / E>((int)blockIdx.x - nwg, A, H, C);
 }
 
 // ciphertext u of `src` (src_stride words apart) to dst + u * dst_stride, two words per thread

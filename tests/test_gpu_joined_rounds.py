@@ -1,7 +1,7 @@
 """Attention calls of few units, whose rounds of summed rotations take the mod-down before them in the mod-up's loader and beside the sums, against the
 same product, relinearisation and summed rotations as calls of their own, bit for bit (those are compared with the oracle elsewhere).  Numbers of units on
 both sides of the rule's limits (256 compute units) and of where rows go from quarters to halves; rounds of one to four bits (1 to 15 rotations);
-uniform residues and the largest ones."""
+uniform residues and the largest ones.  The same for chains of single rotations."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -62,3 +62,40 @@ def test_joined_rounds(name, units, d2, w, largest):
         assert at == len(gs)
         got = (ctx.decode_context_hoisted if which else ctx.decode_scores_hoisted)(x, y, units, 1, d2, w, keys[0], used)
         assert torch.equal(got.view(-1), want.view(-1)), (name, units, which)
+
+
+@pytest.mark.parametrize("name,units,d2,largest", [("C2", 1, 2, False), ("C2", 3, 64, True), ("C2", 21, 128, False), ("C2", 22, 64, False), ("C1", 1, 64, True),
+                                                   ("C1", 42, 32, False), ("C1", 43, 64, False), ("C1", 64, 16, False), ("C1", 65, 64, False), ("k1", 5, 64, False)])
+def test_joined_chain(name, units, d2, largest):
+    import torch
+    say(f"joined chain {name}: {units} units, d2 = {d2}, largest {largest}")
+    prm = SETS[name]
+    ctx, keys = _ctx(name, largest)
+    x, y = _residues(prm.q, prm.n, largest, units, 2), _residues(prm.q, prm.n, largest, units, 2)
+    slots, blocks = d2.bit_length() - 1, (prm.n // d2).bit_length() - 1
+    step = lambda i: pow(3, 1 << i, 2 * prm.n)
+    for which, gs in ((0, [step(i) for i in range(slots)]), (1, [step(slots + i) for i in range(blocks - 1)] + [2 * prm.n - 1])):
+        used = [keys[1 + i % 2] for i in range(len(gs))]
+        want = ctx.relin(ctx.mul(x, y, units), keys[0], units)
+        for g, key in zip(gs, used):
+            want = ctx.rotate(want, g, key, units, accumulate=True)
+        got = (ctx.decode_context if which else ctx.decode_scores)(x, y, units, 1, d2, keys[0], used)
+        assert torch.equal(got.view(-1), want.view(-1)), (name, units, which)
+
+
+# ... and where no relinearisation is ahead of the chain
+@pytest.mark.parametrize("name,units", [("C2", 1), ("C2", 20), ("C1", 1), ("C1", 30)])
+def test_joined_chain_of_a_projection(name, units):
+    import torch
+    say(f"joined chain of a projection {name}: {units} units")
+    prm, d2 = SETS[name], 64
+    ctx, keys = _ctx(name, False)
+    x, zero = _residues(prm.q, prm.n, False, 1, 2), []
+    diags = ctx.plain_prepare(torch.randint(0, prm.t, (units, prm.n), device="cuda"))
+    gs = ctx.round_galois(1, d2, 1)
+    used = [keys[i % 3] for i in range(len(gs))]
+    want = ctx.mul_plain(x.expand(units, -1, -1, -1).contiguous(), diags, units, plain_stride=1)
+    for g, key in zip(gs, used):
+        want = ctx.rotate(want, g, key, units, accumulate=True)
+    got = ctx.cpvm(x, diags, units, 1, d2, zero, used)
+    assert torch.equal(got.view(-1), want.view(-1)), (name, units)
