@@ -72,8 +72,9 @@ FP64_LANE_INSTR_PER_ITEM = {
     # operand transformed already, as the scores have it
     "mul_row": 2999 * 1024,
     "ks_row": 2692 * 1024,
-    "ks_sum_row": 2572 * 1024,
-    "ks_sum_row per rotation": 336 * 1024,
+    # (the sums reduced once for up to eight rotations are in the first figure)
+    "ks_sum_row": 2692 * 1024,
+    "ks_sum_row per rotation": 192 * 1024,
     # the accumulation is in integers: FP64 makes integers of the keys and reduces the sums
     "ks_sum": 60 * 4 * 4096,
     "ks_sum per rotation": 12 * 4 * 4096,
