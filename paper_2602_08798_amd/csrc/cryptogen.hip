@@ -723,8 +723,10 @@ static unsigned pw_blocks(const cg_ctx *c, size_t rows) { return (unsigned)((row
     } while (0)
 
 // Summed inner products of a series of rotations.  Ciphertexts per thread: as many as leave every
-// compute unit three workgroups (N = 8192, 7 rotations: 12 ciphertexts 14.5 / 13.6 / 14.3 us at one / two /
-// four per thread, 48: 56 / 44 / 40 us) and no more than a quarter of the last group's places empty
+// compute unit three workgroups and no more than a quarter of the last group's places empty.  us a series with mod-up and mod-down at
+// one / two / four / eight a thread, 7 rotations, N = 8192: 12 ciphertexts 39.1 / 36.2 / 37.9 / 40.5, 24: 58.3 / 52.2 / 49.7 / 53.4, 36: 76.1 / 67.4 / 67.4 / 70.5,
+// 40: 80.9 / 71.9 / 68.1 / 73.4; N = 4096, 24: 28.6 / 27.7 / 28.5 / 30.8, 42: 34.0 / 32.0 / 34.9 / 36.1; N = 16384, 4: 61.9 / 52.4 / 49.0 / 54.3, 12: 144 / 116 / 106 / 109.
+// 3 rotations, N = 8192: 20 37.4 / 35.2 / 36.3 / 38.3, 32: 50.3 / 47.7 / 47.1 / 47.8
 template <int DNUM>
 static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const HoistTab &T, uint32_t n_rot, double *acc,
                            uint32_t batch)
