@@ -722,6 +722,19 @@ static unsigned pw_blocks(const cg_ctx *c, size_t rows) { return (unsigned)((row
         CG_TRY(rc_pw_);                                                                                \
     } while (0)
 
+// Summed inner products whose words are asked for a rotation ahead: with one or two ciphertexts a thread, where there are registers for two rotations' and few
+// waves to cover a wait, and at N = 8192, from more than one workgroup per compute unit on, only while the keys of a prime leave an eighth of an XCD's L2 (4 MB)
+// to the digits: fewer waves fit on a unit then, and beyond L2 they no longer share what they read.  us a series with mod-up and mod-down, words
+// asked for as they are multiplied / ahead.  N = 8192, three digits (0.375 MB a rotation): 1 ciphertext, 7 rotations 22.4 / 21.4, 15 28.1 / 24.7; 2, 15 29.2 / 27.3; 6, 7 29.3 / 28.9,
+// 9 30.9 / 30.0; 12, 7 35.7 / 35.6; 16, 7 39.1 / 39.1; 14, 9 41.3 / 42.1; with more keys 6, 15 36.3 / 38.8; 8, 11 36.2 / 36.7; 10, 15 46.3 / 52.7; 12, 15 46.1 / 47.5; 18, 11 50.4 / 52.1;
+// two digits, 12, 15 (3.75 MB) 38.6 / 36.4, 31 54.5 / 60.4; four, 12, 7 43.6 / 44.7; six, one a thread, 4, 7 45.3 / 46.8, two, 12, 7 81.7 / 76.8, 15 139 / 124.  N = 4096, two digits, 4, 15
+// 23.2 / 20.6, 24, 31 53.1 / 47.6; N = 16384, three, 6, 15 95.5 / 92.8.  (With four and eight a thread no difference and up to +12 %.)
+static bool ks_sum_ahead_wins(const cg_ctx *c, uint32_t u, size_t blocks, uint32_t n_rot)
+{
+    if (u > 2 || n_rot == 1) return false;
+    const size_t keys = 2 * (size_t)c->dnum * n_rot * limb_bytes(c);      // of one prime
+    return c->logn != 13 || c->dnum == 1 || 2 * keys < (7u << 20) || blocks <= (size_t)c->n_cu || (c->dnum > 4 && u == 2);
+}
 // Summed inner products of a series of rotations.  Ciphertexts per thread: as many as leave every
 // compute unit three workgroups and no more than a quarter of the last group's places empty.  us a series with mod-up and mod-down at
 // one / two / four / eight a thread, 7 rotations, N = 8192: 12 ciphertexts 39.1 / 36.2 / 37.9 / 40.5, 24: 58.3 / 52.2 / 49.7 / 53.4, 36: 76.1 / 67.4 / 67.4 / 70.5,
@@ -737,12 +750,15 @@ static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const 
     while (u > 1 && (per * groups() < 3 * (size_t)c->n_cu || 4 * (size_t)groups() * u > 5 * (size_t)batch)) u /= 2;
     const dim3 block(PW_THREADS), grid((unsigned)(per * groups()));
     const DevConst *dc = c->dc;
+    const bool ahead = ks_sum_ahead_wins(c, u, per * groups(), n_rot);
+#define CG_KSSUM(U, AHEAD) return launch_kernel(ks_sum_kernel<DNUM, U, AHEAD>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc)
     switch (u) {
-    case 8: return launch_kernel(ks_sum_kernel<DNUM, 8>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
-    case 4: return launch_kernel(ks_sum_kernel<DNUM, 4>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
-    case 2: return launch_kernel(ks_sum_kernel<DNUM, 2>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
-    default: return launch_kernel(ks_sum_kernel<DNUM, 1>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc);
+    case 8: CG_KSSUM(8, false);
+    case 4: CG_KSSUM(4, false);
+    case 2: if (ahead) CG_KSSUM(2, true); CG_KSSUM(2, false);
+    default: if (ahead) CG_KSSUM(1, true); CG_KSSUM(1, false);
     }
+#undef CG_KSSUM
 }
 static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t *dig, const HoistTab &T, uint32_t n_rot,
                          double *acc, uint32_t batch)

@@ -3468,8 +3468,10 @@ ks_unit_kernel(LdModup<MODE == KS_ROTATE, 1> ld, HoistTab T, ModdownArgs A, Modd
 // 32 x 32 + 64 multiply-adds, which run at the FP64 rate here, and one modular reduction ends it.
 // N = 8192, 7 rotations, with the inverse transforms: 48 ciphertexts 77 -> 54 us, 12: 33 -> 20 us,
 // one: 32 -> 14 us.
+// AHEAD: a rotation's words are asked for while those of the one before are multiplied, its key's address and Galois element read one rotation sooner
+// still (the dispatch says where).
 // block blk of nblk
-template <int DNUM, int U>
+template <int DNUM, int U, bool AHEAD>
 __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *__restrict__ dig, const HoistTab &T, int n_rot, double *__restrict__ acc,
                                              int batch, const DevConst *__restrict__ C)
 {
@@ -3496,43 +3498,32 @@ __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *
     for (int u = 0; u < U; u++)
 #pragma unroll
         for (int c = 0; c < 2; c++) lo[u][c] = mid[u][c] = hi[u][c] = 0;
-    // A rotation's words are asked for while those of the one before are multiplied, its key's address and Galois element read one rotation sooner
-    // still: with one or two ciphertexts a thread, where there are registers for both and few waves to cover a wait.  Series of 7, N = 8192, three digits: one
-    // ciphertext 22.5 -> 20.9 us, 12 36.0 -> 35.3; six digits, 12 82 -> 77; with four and eight a thread no difference and up to +12 %.
-    struct Words {
-        uint64_t kv[DNUM][2], dv[U][DNUM];
-    };
-    uint32_t g = T.g[0];
-    const double *key = T.key[0];
-    auto ask = [&](Words &w, int next) {
+    auto load = [&](uint32_t g, const double *key, uint64_t (&kv)[DNUM][2], uint64_t (&dv)[U][DNUM]) {
         const uint32_t e = (e0 * g) & ((2u << logn) - 1u);
         const int sidx = (int)(__brev(e >> 1) >> (32 - logn));
         const double *kb = key + key_off;
 #pragma unroll
         for (int j = 0; j < DNUM; j++)
 #pragma unroll
-            for (int c = 0; c < 2; c++) w.kv[j][c] = f64_bits(kb[(size_t)(j * 2 + c) * row]);
+            for (int c = 0; c < 2; c++) kv[j][c] = f64_bits(kb[(size_t)(j * 2 + c) * row]);
 #pragma unroll
         for (int u = 0; u < U; u++)
 #pragma unroll
-            for (int j = 0; j < DNUM; j++) w.dv[u][j] = d[u][(size_t)j * row + sidx];
-        next = next < n_rot ? next : n_rot - 1;
-        g = T.g[next];
-        key = T.key[next];
+            for (int j = 0; j < DNUM; j++) dv[u][j] = d[u][(size_t)j * row + sidx];
     };
-    auto use = [&](const Words &w) {
+    auto use = [&](const uint64_t (&kv)[DNUM][2], const uint64_t (&dv)[U][DNUM]) {
 #pragma unroll
         for (int j = 0; j < DNUM; j++) {
             uint32_t kl[2], kh[2];
 #pragma unroll
             for (int c = 0; c < 2; c++) {
-                const uint64_t q = f64_to_u64(bits_f64(w.kv[j][c]) + m.p);     // positive, below 2^51
+                const uint64_t q = f64_to_u64(bits_f64(kv[j][c]) + m.p);     // positive, below 2^51
                 kl[c] = (uint32_t)q & 0x1FFFFFFu;
                 kh[c] = (uint32_t)(q >> 25);
             }
 #pragma unroll
             for (int u = 0; u < U; u++) {
-                const uint32_t dl = (uint32_t)w.dv[u][j] & 0x1FFFFFFu, dh = (uint32_t)(w.dv[u][j] >> 25);
+                const uint32_t dl = (uint32_t)dv[u][j] & 0x1FFFFFFu, dh = (uint32_t)(dv[u][j] >> 25);
 #pragma unroll
                 for (int c = 0; c < 2; c++) {
                     lo[u][c] += (uint64_t)dl * kl[c];
@@ -3542,26 +3533,36 @@ __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *
             }
         }
     };
-    Words w0;
-    if constexpr (U <= 2) {
-        Words w1;
+    if constexpr (AHEAD) {
+        uint32_t g = T.g[0];
+        const double *key = T.key[0];
+        uint64_t kv[2][DNUM][2], dv[2][U][DNUM];
+        auto ask = [&](int w, int next) {
+            load(g, key, kv[w], dv[w]);
+            next = next < n_rot ? next : n_rot - 1;
+            g = T.g[next];
+            key = T.key[next];
+        };
+        ask(0, 1);
         int i = 0;
-        ask(w0, 1);
-        for (; i + 1 < n_rot; i += 2) {
-            ask(w1, i + 2);
+        for (; i + 2 < n_rot; i += 2) {
+            ask(1, i + 2);
             __builtin_amdgcn_sched_barrier(0);
-            use(w0);
-            ask(w0, i + 3);     // (an even number's last one in vain)
+            use(kv[0], dv[0]);
+            ask(0, i + 3);
             __builtin_amdgcn_sched_barrier(0);
-            use(w1);
+            use(kv[1], dv[1]);
         }
-        if (i < n_rot) use(w0);
+        const bool two = i + 1 < n_rot;
+        if (two) ask(1, n_rot);
+        __builtin_amdgcn_sched_barrier(0);
+        use(kv[0], dv[0]);
+        if (two) use(kv[1], dv[1]);
     } else {
         for (int i = 0; i < n_rot; i++) {
-            g = T.g[i];
-            key = T.key[i];
-            ask(w0, i);
-            use(w0);
+            uint64_t kv[DNUM][2], dv[U][DNUM];
+            load(T.g[i], T.key[i], kv, dv);
+            use(kv, dv);
         }
     }
     const double t50 = C->two50[r], t81 = C->two81[r];
@@ -3581,12 +3582,12 @@ __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *
     }
 }
 
-template <int DNUM, int U>
+template <int DNUM, int U, bool AHEAD>
 __global__ void __launch_bounds__(PW_THREADS)
 ks_sum_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch,
               const DevConst *__restrict__ C)
 {
-    ks_sum_block<DNUM, U>((int)blockIdx.x, (int)gridDim.x, dig, T, n_rot, acc, batch, C);
+    ks_sum_block<DNUM, U, AHEAD>((int)blockIdx.x, (int)gridDim.x, dig, T, n_rot, acc, batch, C);
 }
 
 // Block blk of a mod-down that a mod-up took ahead of it (LdModupDown): THREADS pairs of coefficients of one row (unit, component, prime) of
@@ -3638,7 +3639,7 @@ __global__ void __launch_bounds__(PW_THREADS)
 ks_sum_after_kernel(const uint64_t *__restrict__ dig, HoistTab T, int n_rot, double *__restrict__ acc, int batch, int n_sums,
                     ModdownArgs A, ModdownHoist H, const DevConst *__restrict__ C)
 {
-    if ((int)blockIdx.x < n_sums) ks_sum_block<DNUM, 1>((int)blockIdx.x, n_sums, dig, T, n_rot, acc, batch, C);
+    if ((int)blockIdx.x < n_sums) ks_sum_block<DNUM, 1, true>((int)blockIdx.x, n_sums, dig, T, n_rot, acc, batch, C);
     else down_block<PW_THREADS>((int)blockIdx.x - n_sums, A, H, C);
 }
 // One rotation's, or a relinearisation's, inner product in the loader of its inverse transform, nwg rows

@@ -29,10 +29,12 @@ def _env(name):
 
 
 # 256 compute units, N = 8192: 48 units take 192 workgroups of one (unit, prime) each, 256 units one workgroup each (up to five rotations: keys of a
-# prime fit an L2); N = 4096: 100 units 300 workgroups, 470 units one each.  1 and 2 units: sums from digits in memory, one ciphertext to a thread, 12: two.
+# prime fit an L2); N = 4096: 100 units 300 workgroups, 470 units one each.  1, 2 and 6 units: sums from digits in memory, one ciphertext to a thread, 12: two,
+# both without words asked for ahead as well (one rotation, and more than nine).
 # 460, 901 and 511 (a last pair of one): two units to a workgroup with the division by P, whole rounds of them and not
 @pytest.mark.parametrize("name,batch,counts", [("C2", 48, (1, 2, 7, 8, 9, 16, 17)), ("C2", 256, (1, 2, 5)), ("C1", 100, (7, 8, 9)), ("C1", 470, (1, 8, 9)),
                                                ("C2", 1, (1, 2, 3, 6, 9)), ("C2", 12, (2, 5)), ("C5", 2, (2, 3)),
+                                               ("C2", 6, (4, 11, 15)), ("C2", 12, (1, 15)),
                                                ("C2", 460, (7, 9)), ("C2", 901, (1, 8)), ("k4", 511, (3, 7))])
 def test_numbers_of_rotations(name, batch, counts):
     env = _env(name)
