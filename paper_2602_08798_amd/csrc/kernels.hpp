@@ -3543,9 +3543,15 @@ __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *
             g = T.g[next];
             key = T.key[next];
         };
-        ask(0, 1);
         int i = 0;
-        for (; i + 2 < n_rot; i += 2) {
+        // an even number's first one goes by itself, so that nothing is asked for in vain
+        if (n_rot % 2 == 0) {
+            ask(0, 1);
+            use(kv[0], dv[0]);
+            i = 1;
+        }
+        ask(0, i + 1);
+        for (; i + 1 < n_rot; i += 2) {
             ask(1, i + 2);
             __builtin_amdgcn_sched_barrier(0);
             use(kv[0], dv[0]);
@@ -3553,11 +3559,7 @@ __device__ __forceinline__ void ks_sum_block(int blk, int nblk, const uint64_t *
             __builtin_amdgcn_sched_barrier(0);
             use(kv[1], dv[1]);
         }
-        const bool two = i + 1 < n_rot;
-        if (two) ask(1, n_rot);
-        __builtin_amdgcn_sched_barrier(0);
-        use(kv[0], dv[0]);
-        if (two) use(kv[1], dv[1]);
+        if (i < n_rot) use(kv[0], dv[0]);
     } else {
         for (int i = 0; i < n_rot; i++) {
             uint64_t kv[DNUM][2], dv[U][DNUM];
