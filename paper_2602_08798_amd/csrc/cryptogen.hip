@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -550,10 +551,12 @@ static unsigned ntt_grid(cg_ctx *c, size_t nwg, int threads)
 // 6 x 7 (d2 = 128) 612 / 630, 10 x 6 694 / 726; N = 4096, 12 x 7 212 / 219; N = 16384, 4 x 3 586 / 607.
 // longer: theirs is the chain with more dependent key switches, which the step waits for.
 // wide: their summed rotations take ks_wide_kernel, a workgroup of which leaves no room on its compute unit.
-// busy: their mod-ups have rows for three eighths of the compute units.
+// rows: of their mod-ups.  most: rotations of their largest round, where these count.
 // leads: theirs is the chain with at least two dependent key switches fewer, and their (unit, prime) rows take one round.
 struct Beside {
-    bool others = false, crowd = false, wide = false, longer = false, busy = false, leads = false;
+    bool others = false, crowd = false, wide = false, longer = false, leads = false;
+    size_t rows = 0;
+    uint32_t most = 0;
 };
 
 // elements per thread for this context's transforms
@@ -729,11 +732,14 @@ static unsigned pw_blocks(const cg_ctx *c, size_t rows) { return (unsigned)((row
 // 9 30.9 / 30.0; 12, 7 35.7 / 35.6; 16, 7 39.1 / 39.1; 14, 9 41.3 / 42.1; with more keys 6, 15 36.3 / 38.8; 8, 11 36.2 / 36.7; 10, 15 46.3 / 52.7; 12, 15 46.1 / 47.5; 18, 11 50.4 / 52.1;
 // two digits, 12, 15 (3.75 MB) 38.6 / 36.4, 31 54.5 / 60.4; four, 12, 7 43.6 / 44.7; six, one a thread, 4, 7 45.3 / 46.8, two, 12, 7 81.7 / 76.8, 15 139 / 124.  N = 4096, two digits, 4, 15
 // 23.2 / 20.6, 24, 31 53.1 / 47.6; N = 16384, three, 6, 15 95.5 / 92.8.  (With four and eight a thread no difference and up to +12 %.)
-static bool ks_sum_ahead_wins(const cg_ctx *c, uint32_t u, size_t blocks, uint32_t n_rot)
+static bool sum_keys_stay(const cg_ctx *c, size_t blocks, uint32_t n_rot, bool others)
 {
-    if (u > 2 || n_rot == 1) return false;
     const size_t keys = 2 * (size_t)c->dnum * n_rot * limb_bytes(c);      // of one prime
-    return c->logn != 13 || c->dnum == 1 || 2 * keys < (7u << 20) || blocks <= (size_t)c->n_cu || (c->dnum > 4 && u == 2);
+    return c->logn != 13 || c->dnum == 1 || 2 * keys < (7u << 20) || 2 * blocks <= (others ? 3 : 2) * (size_t)c->n_cu;
+}
+static bool ks_sum_ahead_wins(const cg_ctx *c, uint32_t u, size_t blocks, uint32_t n_rot, bool others)
+{
+    return u <= 2 && n_rot > 1 && (sum_keys_stay(c, blocks, n_rot, others) || (c->dnum > 4 && u == 2));
 }
 // Summed inner products of a series of rotations.  Ciphertexts per thread: as many as leave every
 // compute unit three workgroups and no more than a quarter of the last group's places empty.  us a series with mod-up and mod-down at
@@ -742,7 +748,7 @@ static bool ks_sum_ahead_wins(const cg_ctx *c, uint32_t u, size_t blocks, uint32
 // 3 rotations, N = 8192: 20 37.4 / 35.2 / 36.3 / 38.3, 32: 50.3 / 47.7 / 47.1 / 47.8
 template <int DNUM>
 static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const HoistTab &T, uint32_t n_rot, double *acc,
-                           uint32_t batch)
+                           uint32_t batch, bool others)
 {
     const size_t per = (size_t)c->L * c->N / PW_THREADS;
     uint32_t u = 8;
@@ -750,7 +756,7 @@ static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const 
     while (u > 1 && (per * groups() < 3 * (size_t)c->n_cu || 4 * (size_t)groups() * u > 5 * (size_t)batch)) u /= 2;
     const dim3 block(PW_THREADS), grid((unsigned)(per * groups()));
     const DevConst *dc = c->dc;
-    const bool ahead = ks_sum_ahead_wins(c, u, per * groups(), n_rot);
+    const bool ahead = ks_sum_ahead_wins(c, u, per * groups(), n_rot, others);
 #define CG_KSSUM(U, AHEAD) return launch_kernel(ks_sum_kernel<DNUM, U, AHEAD>, grid, block, s, dig, T, (int)n_rot, acc, (int)batch, dc)
     switch (u) {
     case 8: CG_KSSUM(8, false);
@@ -761,17 +767,17 @@ static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const 
 #undef CG_KSSUM
 }
 static int launch_ks_sum(cg_ctx *c, hipStream_t s, double bytes, const uint64_t *dig, const HoistTab &T, uint32_t n_rot,
-                         double *acc, uint32_t batch)
+                         double *acc, uint32_t batch, bool others)
 {
     if (c->dry) return CG_OK;
     ProfScope ps(c, s, KID_KSSUM, bytes, (double)batch);
     switch (c->dnum) {
-    case 1: return launch_ks_sum_d<1>(c, s, dig, T, n_rot, acc, batch);
-    case 2: return launch_ks_sum_d<2>(c, s, dig, T, n_rot, acc, batch);
-    case 3: return launch_ks_sum_d<3>(c, s, dig, T, n_rot, acc, batch);
-    case 4: return launch_ks_sum_d<4>(c, s, dig, T, n_rot, acc, batch);
-    case 5: return launch_ks_sum_d<5>(c, s, dig, T, n_rot, acc, batch);
-    default: return launch_ks_sum_d<6>(c, s, dig, T, n_rot, acc, batch);
+    case 1: return launch_ks_sum_d<1>(c, s, dig, T, n_rot, acc, batch, others);
+    case 2: return launch_ks_sum_d<2>(c, s, dig, T, n_rot, acc, batch, others);
+    case 3: return launch_ks_sum_d<3>(c, s, dig, T, n_rot, acc, batch, others);
+    case 4: return launch_ks_sum_d<4>(c, s, dig, T, n_rot, acc, batch, others);
+    case 5: return launch_ks_sum_d<5>(c, s, dig, T, n_rot, acc, batch, others);
+    default: return launch_ks_sum_d<6>(c, s, dig, T, n_rot, acc, batch, others);
     }
 }
 
@@ -1677,7 +1683,7 @@ static int do_rotate_sum(cg_ctx *c, hipStream_t s, const uint64_t *in2, size_t i
         const bool whole = beside.crowd;
         CG_TRY(launch_modup(c, s, c1, in_stride, 0, batch, dig, whole));
         const double sbytes = LB * ((dig_rows + 2.0 * c->L) * B + 2.0 * dig_rows * n_rot);
-        CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch));
+        CG_TRY(launch_ks_sum(c, s, sbytes, dig, T, n_rot, acc, batch, beside.others));
         const size_t irows = (size_t)batch * 2 * c->L;
         // few rows are transformed in parts, and so not in place: two digits' rows have room for the results
         const int parts = !whole && c->dnum >= 2 ? acc_parts(c, irows, beside.others) : 0;
@@ -1925,10 +1931,18 @@ static uint32_t pow3_mod(uint32_t e, uint32_t two_n)
 // against five) 12 x 4 621 / 561, 10 x 3 489 / 437, 5 x 7 510 / 470, 16 x 4 733 / 724, N = 4096 11 x 4 290 / 245, 16 x 5 323 / 297; with more than a round of (unit,
 // prime) 14 x 8 1033 / 1054, N = 4096 16 x 8 403 / 408; seven rotations against six 16 x 2 517 / 532, 5 x 7 504 / 515, 8 x 5 594 / 572.  Projections of a token, a
 // chain of eight rotations of 1, 4, 9, 16 and 21 units: N = 8192 198 / 163, 202 / 177, 236 / 195, 248 / 203, 249 / 228, N = 4096, seven, 112 / 89 to 136 / 114, 36 units 147 / 123.
+// The launch of inner products and mod-down holds on to the end of a chain of fewer digits, whose mod-up has few rows: up to three of its workgroups to a unit at N = 8192, 5 1/2 at
+// N = 4096, 3 3/4 with one rotation.  Scores or context alone, d2 = 64: one prime 48 units 236 / 212, 64 259 / 251, 100 335 / 356, 128 355 / 404; two 30 260 / 246, 34 271 / 261,
+// context of 42 337 / 346; N = 4096, one 96 197 / 186, projection of 128 175 / 178; two, one rotation, 42 74.9 / 71.9, 64 98.5 / 105.  In a step, with other numbers of digits than
+// three at N = 8192 and two at N = 4096, up to 9/4: one prime 48 x 1 355 / 353, 64 x 1 426 / 438; two 24 x 1 373 / 356, 28 x 1 398 / 411; N = 4096, one 48 x 1 216 / 200, 96 x 1
+// 284 / 302, three 20 x 1 250 / 227, 24 x 1 282 / 287.  Scores beside a context with a mod-up row for every unit, N = 4096, 48 x 1 296 / 306, 64 x 1 349 / 372.
 static bool chain_joined_wins(const cg_ctx *c, uint32_t batch, int n, const Beside &beside)
 {
     if (c->logn > 13 || c->alpha != 1 || c->nsp != 1 || c->dnum > 3 || !n || (beside.crowd && !beside.leads)) return false;
-    return 2 * (size_t)batch * c->dnum * c->L <= (c->logn == 12 ? 3 : 2) * (size_t)c->n_cu;
+    const size_t cu = (size_t)c->n_cu, rows = (size_t)batch * c->dnum * c->L, blocks = (size_t)batch * (2 * c->L + 8 * c->k);
+    if (beside.others && c->dnum != (c->logn == 12 ? 2 : 3)) return rows <= cu && 4 * blocks <= 9 * cu;
+    if (c->logn == 12) return 2 * rows <= (beside.rows > cu ? 2 : 3) * cu && 4 * blocks <= (n == 1 ? 15 : 22) * cu;
+    return rows <= cu && blocks <= 3 * cu;
 }
 static int chain_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *x0, uint64_t *x1, uint64_t *out,
                         const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws)
@@ -2035,15 +2049,27 @@ static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint
 // A relinearisation and the rounds behind it where few units leave every launch bound by its own latency: the mod-up of a round takes the mod-down
 // before it in its loader, and that mod-down's rows come with the round's sums (ks_sum_after_kernel), three launches a round instead of four.  Every part of
 // every row repeats the mod-down of its digit, so up to half a row of the mod-up per compute unit at N = 4096, a quarter at N = 8192 (quarters of rows, as
-// row_parts), and there in a step's context only beside scores of up to 3/8, which the repeated work holds up otherwise.  us a step, four launches / three, heads x
-// ciphertexts (plain cache, with a transformed one).  N = 8192, three primes: 1 x 2 178 / 161, 179 / 168, 1 x 4 177 / 164, 181 / 172, 1 x 6 184 / 175, 194 / 184, 4 x 1 (d2 = 32)
-// 176 / 166, 183 / 177, 4 x 2 181 / 176, 190 / 187, 5 x 1 176 / 173, 185 / 183; beyond a quarter 9 x 1 208 / 213, 216 / 221, 10 x 1 (d2 = 32) 215 / 229, 228 / 241; beside more
-// scores 4 x 4 221 / 220, 224 / 228, 5 x 2 (d2 = 128) 199 / 212, 204 / 218, 5 x 4 254 / 259, 257 / 260.  N = 4096, two primes: 1 x 2 161 / 147, 3 x 1 178 / 158, 10 x 1 174 / 156,
-// 16 x 1 167 / 154, 163 / 153, 20 x 1 163 / 154, 167 / 166, 12 x 2 169 / 164, 168 / 163.
+// row_parts).  us, four launches / three, steps as heads x ciphertexts (plain cache, with a transformed one).
+// - The sums take one ciphertext a thread, with the mod-down's blocks behind them: up to three workgroups to a unit at N = 8192 (five in a step, whose other branch
+//   waits as well), seven at N = 4096.  Alone, 3 bits a round: three primes, scores (d2 = 64) 2 units 94.9 / 91.0, 4 102 / 102, context (d2 = 2) 4 156 / 160, 5 166 / 171; one
+//   prime, context (d2 = 64) 8 110 / 108, 16 122 / 128, 32 153 / 166; N = 4096, one 37 91.3 / 89.0, 64 95.1 / 103.  Steps: three primes 1 x 2 178 / 161, 179 / 168, 1 x 4 177 / 164,
+//   181 / 172, 4 x 1 (d2 = 32) 176 / 166, 183 / 177, 5 x 1 176 / 173, 185 / 183; beyond 9 x 1 208 / 213, 216 / 221, 10 x 1 (d2 = 32) 215 / 229, 228 / 241; one 16 x 1 167 / 159, 24 x 1
+//   173 / 184, 32 x 1 192 / 223; two 8 x 1 171 / 163, 10 x 1 172 / 173, 180 / 195.
+// - Its keys stay in L2 (sum_keys_stay), also those of the other branch's rounds, whose sums it would hold up: context alone, d2 = 64, a round of 15 rotations, 2 units 102 / 99.9,
+//   4 110 / 113, 5 117 / 123; steps of 4 bits 3 x 2 (d2 = 32) 169 / 168, 4 x 1 158 / 165, 4 x 2 174 / 183, 5 x 1 166 / 183, (d2 = 64) 159 / 177.
+// - A step's context at N = 8192 only beside scores whose mod-ups have rows for 3/8 of the units: 4 x 2 181 / 176, 190 / 187, 4 x 4 221 / 220, 224 / 228, 5 x 4 254 / 259, 257 / 260; beside
+//   longer scores for a quarter: d2 = 128, 5 x 1 179 / 168, 4 x 2 182 / 189, 2 x 4 (2 bits) 193 / 199.
+// - N = 4096: both branches' mod-ups have rows for 7/8 of the units.  1 x 2 161 / 147, 10 x 1 174 / 156, 16 x 1 167 / 154, 163 / 153, 12 x 2 169 / 164, 151 / 154; beyond 20 x 1 140 / 148,
+//   151 / 165, 10 x 3 147 / 151, 155 / 161, 16 x 2 154 / 161, 157 / 163 (on a host that launches more slowly 161 / 150, 165 / 158, 162 / 162).
 static bool fold_joined_wins(const cg_ctx *c, uint32_t batch, const FoldRounds &R, const Beside &beside)
 {
-    if (c->logn > 13 || c->alpha != 1 || c->nsp != 1 || c->dnum > 3 || !R.n_rounds || beside.crowd || (c->logn == 13 && beside.busy)) return false;
-    return row_parts(c, (size_t)batch * c->dnum * c->L, false) >= (c->logn == 13 ? 2 : 1);
+    if (c->logn > 13 || c->alpha != 1 || c->nsp != 1 || c->dnum > 3 || !R.n_rounds || beside.crowd) return false;
+    const size_t cu = (size_t)c->n_cu, rows = (size_t)batch * c->dnum * c->L, per = (size_t)batch * (c->N / PW_THREADS), sums = per * c->L, down = per * c->k;
+    if (sums + down > (c->logn == 12 ? 7 : beside.others ? 5 : 3) * cu) return false;
+    if (c->logn == 12 ? beside.others && 8 * (beside.rows + rows) > 7 * cu : 8 * beside.rows > 3 * cu) return false;
+    if (c->logn == 13 && beside.longer && 4 * beside.rows > cu) return false;
+    if (!sum_keys_stay(c, sums, std::max(beside.most, (uint32_t)*std::max_element(R.count, R.count + R.n_rounds)), beside.others)) return false;
+    return row_parts(c, rows, false) >= (c->logn == 13 ? 2 : 1);
 }
 static int fold_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *x0, uint64_t *x1, uint64_t *out,
                        const FoldRounds &R, const void *const *keys, uint32_t batch, void *ws, Beside beside)
@@ -2298,8 +2324,11 @@ static int step_impl(cg_ctx *c, void *stream, const uint64_t *q, const uint64_t 
     const uint32_t own_switches = switches(c->N / d2, block_w), their = switches(d2, fold_w);
     const bool longer = own_switches > their || (c->logn == 12 && own_switches == their), context_first = longer && (few || over);
     const size_t modups = (size_t)heads * n_cts * c->dnum * c->L;
-    const Beside by_context{true}, by_scores{true, modups > n, fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches,
-                                             8 * modups > 3 * n, own_switches >= their + 2 && srows <= n};
+    // rotations of the largest round
+    auto most = [](uint32_t slots, uint32_t w, uint32_t rounds) { return w && rounds ? (1u << ((31 - __builtin_clz(slots) + rounds - 1) / rounds)) - 1 : 0u; };
+    const Beside by_context{true, false, false, false, false, own, most(c->N / d2, block_w, own_switches)};
+    const Beside by_scores{true, modups > n, fold_w && ks_wide_wins(c, heads * n_cts, false, by_context), their > own_switches, own_switches >= their + 2 && srows <= n,
+                           modups, most(d2, fold_w, their)};
     auto scores_on = [&](hipStream_t st) {
         return scores_impl(c, st, q, cache, kext, heads, n_cts, cache_stride_cts, d2, rlk, gk_fold, scores, ws_scores, fold_w, by_context);
     };

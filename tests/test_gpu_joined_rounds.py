@@ -12,8 +12,9 @@ from workloads.params import ParamSet
 from .bruteforce import ntt_primes
 from .test_gpu_parity import say
 
-_P = ntt_primes(1 << 50, 2 << 13, 2)
-SETS = {**PRESETS, "k1": ParamSet("n8192_k1_joined", 13, q=tuple(_P[:1]), p=tuple(_P[1:]), alpha=1)}
+_P, _P12 = ntt_primes(1 << 50, 2 << 13, 3), ntt_primes(1 << 50, 2 << 12, 4)
+_set = lambda log2n, k, p: ParamSet(f"n{1 << log2n}_k{k}_joined", log2n, q=tuple(p[:k]), p=tuple(p[k:k + 1]), alpha=1)
+SETS = {**PRESETS, "k1": _set(13, 1, _P), "k2": _set(13, 2, _P), "n4096_k1": _set(12, 1, _P12), "n4096_k3": _set(12, 3, _P12)}
 _state = {}
 
 
@@ -44,7 +45,9 @@ def _rounds(bits, w):
 @pytest.mark.parametrize("name,units,d2,w,largest", [
     ("C2", 1, 64, 3, False), ("C2", 1, 2, 3, False), ("C2", 2, 128, 1, False), ("C2", 3, 32, 2, True), ("C2", 5, 256, 4, False), ("C2", 6, 64, 3, False),
     ("C1", 1, 64, 3, True), ("C1", 10, 64, 3, False), ("C1", 11, 32, 3, False), ("C1", 21, 16, 4, True), ("C1", 22, 64, 3, False),
-    ("k1", 3, 64, 3, False), ("k1", 32, 16, 2, False)])
+    ("k1", 3, 64, 3, False), ("k1", 32, 16, 2, False),
+    ("C2", 2, 64, 4, True), ("k1", 8, 64, 3, True), ("k2", 1, 64, 3, True), ("k2", 4, 32, 4, False), ("n4096_k1", 1, 64, 3, False), ("n4096_k1", 37, 16, 3, True),
+    ("n4096_k3", 2, 64, 3, False), ("n4096_k3", 10, 32, 4, True)])
 def test_joined_rounds(name, units, d2, w, largest):
     import torch
     say(f"joined rounds {name}: {units} units, d2 = {d2}, {w} bits, largest {largest}")
@@ -65,7 +68,9 @@ def test_joined_rounds(name, units, d2, w, largest):
 
 
 @pytest.mark.parametrize("name,units,d2,largest", [("C2", 1, 2, False), ("C2", 3, 64, True), ("C2", 21, 128, False), ("C2", 22, 64, False), ("C1", 1, 64, True),
-                                                   ("C1", 42, 32, False), ("C1", 43, 64, False), ("C1", 64, 16, False), ("C1", 65, 64, False), ("k1", 5, 64, False)])
+                                                   ("C1", 42, 32, False), ("C1", 43, 64, False), ("C1", 64, 16, False), ("C1", 65, 64, False), ("k1", 5, 64, False),
+                                                   ("k2", 1, 64, False), ("k2", 34, 16, True), ("n4096_k1", 3, 64, True), ("n4096_k1", 117, 16, False), ("n4096_k3", 1, 64, False),
+                                                   ("n4096_k3", 32, 16, True)])
 def test_joined_chain(name, units, d2, largest):
     import torch
     say(f"joined chain {name}: {units} units, d2 = {d2}, largest {largest}")

@@ -78,3 +78,32 @@ def test_step_and_calls_made_alone(name, heads, n_cts, d2, copy):
     assert torch.equal(cache, own)
     assert torch.equal(got_scores.view(-1), scores.view(-1))
     assert torch.equal(got_context.view(-1), context.view(-1))
+
+
+# chains of single rotations: a context that takes the mod-downs in its mod-ups beside scores of a mod-up row for every unit, which it has two switches or
+# more to do than; both branches of few units; neither
+CHAINS = [("C2", 12, 4, 32), ("C2", 3, 4, 64), ("C2", 10, 3, 64), ("C1", 11, 4, 32), ("C1", 4, 4, 64)]
+
+
+@pytest.mark.parametrize("name,heads,n_cts,d2", CHAINS)
+def test_step_of_chains_and_calls_made_alone(name, heads, n_cts, d2):
+    import torch
+    say(f"step of chains against calls {name}: {heads} heads, {n_cts} ciphertexts, d2 = {d2}")
+    prm = PRESETS[name]
+    ctx, keys = _ctx(name)
+    n, stride = prm.n, n_cts + 1
+    ct = lambda *lead: _residues(prm.q, n, *lead, 2)
+    q, a, rows, cache = ct(heads), ct(heads * n_cts), ct(2 * heads), ct(2 * heads * stride)
+    masks = ctx.plain_prepare(torch.randint(0, prm.t, (n // d2, n), device="cuda"))
+    fold, block = ([keys[1 + i % 3] for i in range(m.bit_length() - 1)] for m in (d2, n // d2))
+    tau = n_cts * (n // d2) - 1
+
+    own = cache.clone()
+    ctx.kv_append(own, stride, 2 * heads, tau, rows, masks, d2)
+    scores = ctx.decode_scores(q, own[:heads * stride], heads, n_cts, d2, keys[0], fold, cache_stride_cts=stride)
+    context = ctx.decode_context(a, own[heads * stride:], heads, n_cts, d2, keys[0], block, cache_stride_cts=stride)
+    got_scores, got_context = ctx.decode_step(q, a, cache, heads, n_cts, stride, d2, tau, rows, masks, keys[0], fold, block)
+    torch.cuda.synchronize()
+    assert torch.equal(cache, own)
+    assert torch.equal(got_scores.view(-1), scores.view(-1))
+    assert torch.equal(got_context.view(-1), context.view(-1))
