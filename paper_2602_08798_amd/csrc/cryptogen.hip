@@ -1944,8 +1944,9 @@ static bool chain_joined_wins(const cg_ctx *c, uint32_t batch, int n, const Besi
     if (c->logn == 12) return 2 * rows <= (beside.rows > cu ? 2 : 3) * cu && 4 * blocks <= (n == 1 ? 15 : 22) * cu;
     return rows <= cu && blocks <= 3 * cu;
 }
+// beside: whole rows in the first mod-up beside a crowd, as elsewhere: 10 x 3 440 / 435 (parts / whole rows), 4 x 8 415 / 402, 5 x 7 466 / 463, 8 x 5 546 / 552, with d2 = 32
 static int chain_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const void *rlk, uint64_t *x0, uint64_t *x1, uint64_t *out,
-                        const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws)
+                        const uint32_t *gs, const void *const *keys, int n, uint32_t batch, void *ws, const Beside &beside = {})
 {
     const size_t ct2 = (size_t)2 * c->k * c->N, ct3 = (size_t)3 * c->k * c->N, c1 = (size_t)c->k * c->N;
     const size_t nrows = (size_t)batch * c->dnum * c->L, irows = (size_t)batch * 2 * c->L;
@@ -1955,7 +1956,7 @@ static int chain_joined(cg_ctx *c, hipStream_t s, const uint64_t *in3, const voi
     ModdownArgs A{acc[0], x0, ct2, in3, ct3, 1u, 1, (int)batch, in3, ct3};
     ModdownHoist H{};
     if (in3) {
-        CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig));
+        CG_TRY(launch_modup(c, s, in3 + 2 * c1, ct3, 0, batch, dig, beside.crowd));
         CG_TRY(launch_ks_inner(c, s, dig, static_cast<const double *>(rlk), acc[0], batch));
     } else {
         CG_TRY(launch_modup(c, s, x0 + c1, ct2, gs[0], batch, dig));
@@ -2211,7 +2212,7 @@ static int context_impl(cg_ctx *c, void *stream, const uint64_t *a, const uint64
                      pw_blocks(c, (size_t)heads * rows), d3, y, (int)heads, (int)n_cts, rows, c->dc);
     }
     if (fold_w && fold_joined_wins(c, heads, R, beside)) return fold_joined(c, s, y, rlk, xa, xb, out, R, gk_block, heads, w.p, beside);
-    if (!fold_w && chain_joined_wins(c, heads, nrot, beside)) return chain_joined(c, s, y, rlk, xa, xb, out, gs, gk_block, nrot, heads, w.p);
+    if (!fold_w && chain_joined_wins(c, heads, nrot, beside)) return chain_joined(c, s, y, rlk, xa, xb, out, gs, gk_block, nrot, heads, w.p, beside);
     CG_TRY(do_relin(c, s, y, rlk, xa, heads, w.p, beside));
     if (fold_w) return fold_chain(c, s, xa, xb, out, R, gk_block, heads, w.p, beside);
     return rotate_add_chain(c, s, xa, xb, out, gs, gk_block, nrot, heads, w.p, beside);

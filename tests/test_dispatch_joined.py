@@ -47,6 +47,8 @@ ROUNDS = {
     # ... N = 4096: both branches' mod-ups for 7/8 of the units
     **{("n4096_k2", "step", *s, 64, 3): n for s, n in (((18, 1), 4), ((19, 1), 0), ((12, 2), 2), ((13, 2), 0), ((9, 3), 2), ((10, 3), 0))},
 }
+# the first mod-up of a chain of up to half a row per unit in parts, but beside a mod-up row for every unit of the other branch
+PARTS = {("k3", "context", 10, 64): True, ("k3", "step", 10, 3, 32): False, ("k3", "step", 4, 8, 32): False, ("k3", "step", 7, 3, 64): True}
 INVERSE = {("k3", 384): 8, ("k3", 385): 16, ("k3", 16384): 16}      # rows -> elements per thread
 
 
@@ -60,11 +62,12 @@ def _launches(lib):
         tau = lambda c, d2: u32(c * (1 << log2n) // d2 - 1)
         calls = {"scores": lambda u, d2, w=0: f.cg_decode_scores_hoisted(ctx, None, d, d, None, *b(u, 1, 1, d2, w), d, keys, out, d) if w else
                            f.cg_decode_scores(ctx, None, d, d, *b(u, 1, 1, d2), d, keys, out, d),
-                 "context": lambda u, d2, w: f.cg_decode_context_hoisted(ctx, None, d, d, None, *b(u, 1, 1, d2, w, 1), d, keys, out, d),
+                 "context": lambda u, d2, w=0: f.cg_decode_context_hoisted(ctx, None, d, d, None, *b(u, 1, 1, d2, w, 1), d, keys, out, d) if w else
+                            f.cg_decode_context(ctx, None, d, d, *b(u, 1, 1, d2), d, keys, out, d),
                  "step": lambda h, c, d2, w=0: f.cg_decode_step_hoisted(ctx, None, d, d, d, None, *b(h, c, c + 1, d2), tau(c, d2), d, d, d, u32(w), keys, u32(w), 1,
                                                                         keys, out, out, d) if w else
                          f.cg_decode_step(ctx, None, d, d, d, *b(h, c, c + 1, d2), tau(c, d2), d, d, d, keys, keys, out, out, d)}
-        for s, op, *sizes in [*CHAINS, *ROUNDS]:
+        for s, op, *sizes in [*CHAINS, *ROUNDS, *PARTS]:
             if s == name:
                 got[" ".join(map(str, (s, op, *sizes)))] = lib.kernels(lambda: calls[op](*sizes))
         for s, rows in INVERSE:
@@ -93,6 +96,12 @@ def test_chains(launches, case):
 @pytest.mark.parametrize("case", ROUNDS, ids=lambda c: " ".join(map(str, c)))
 def test_rounds(launches, case):
     assert _count(launches, case, "ks_sum_after_kernel<") == ROUNDS[case]
+
+
+@pytest.mark.parametrize("case", PARTS, ids=lambda c: " ".join(map(str, c)))
+def test_first_mod_up(launches, case):
+    assert _count(launches, case, "ks_inner_after_kernel<")
+    assert bool(_count(launches, case, "ntt_fwd_part_kernel<13, 1, LdModup<false, 1>")) == PARTS[case]
 
 
 @pytest.mark.parametrize("case", INVERSE, ids=lambda c: " ".join(map(str, c)))
