@@ -1704,11 +1704,12 @@ ks_row_kernel(LdModup<GALOIS, 1> ld, const double *__restrict__ key, StInvF64 st
 
 // A sum of products reduced once: `a` adds up the products' multiples of 2^50 (from 1.5 * 2^102 on, where an FP64 number's last bit is worth
 // 2^50), `l` what each addition rounded away, which the next FMA returns exactly.  Four instructions a product where one that is
-// reduced and added takes seven; close() takes six.  Up to eight products of centred residues (below 2^98 each) between open and close: a stays
-// within 2^102 ... 2^103, l within 4 * 2^50 of what it was opened with.  close(): the quotient of a sum of 2^101 at most is off by 1/4 for
+// reduced and added takes seven; close() takes six.  Between open and close up to CENTRED products of centred residues (below 2^98
+// each), or up to CANONICAL of a canonical and a centred one (below 2^99): a stays within 2^102 ... 2^103, l within 4 * 2^50 of what it was opened with.  close(): the quotient of a sum of 2^101 at most is off by 1/4 for
 // rounding h + l, the reciprocal and the product each, so the result is below 1.25 * 2^50, and fma(-c, p, h) = result - l below
 // 2^53: exact.
 struct DotSum {
+    static constexpr int CENTRED = 8, CANONICAL = 4;
     static constexpr double ZERO = 0x1.8p102, OUT = 1.26;
     double a, l;
     __device__ __forceinline__ void open(double start) { a = ZERO, l = start; }
@@ -1792,7 +1793,7 @@ __device__ __forceinline__ void sum_pairs(const double *lds, RotWalk &way, size_
         }
         way.step();
         i++;
-        if ((i & 7) == 0 && i < way.n) {
+        if (i % DotSum::CENTRED == 0 && i < way.n) {
 #pragma unroll
             for (int x = 0; x < 4 * W; x++) d[x].open(d[x].close(m));
         }
@@ -3178,6 +3179,7 @@ rot_row_kernel(const uint64_t *__restrict__ dig, HoistTab T, ModdownArgs A, Modd
             int tk = tid;
             asm volatile("" : "+v"(tk));
             if constexpr (AHEAD) {
+                static_assert(DNUM <= DotSum::CANONICAL, "canonical digits times centred keys, one sum for all digits");
                 DotSum sum[E];
 #pragma unroll
                 for (int it = 0; it < E; it++) sum[it].open(0.0);
