@@ -1908,7 +1908,8 @@ __device__ __forceinline__ double signed_add(double a, double w, uint32_t s)
 // since the two sums of a unit are transformed back together).
 // ---------------------------------------------------------------------------
 // the sums of units b ... b + U - 1 (those of the batch) modulo prime r: s (both components), and of a second unit s2 and s3
-template <int LOGN, int E, int U>
+// AGAIN: LDS places worked out for each digit again instead of held, which the kernel that divides by P has no registers for
+template <int LOGN, int E, int U, bool AGAIN>
 __device__ __forceinline__ void sum_units(double *lds, const LdModup<false, 1> &ld, const HoistTab &T, int n_rot, int batch, int b, int r, int tid,
                                           const double *__restrict__ tw, const ModD m, const DevConst *__restrict__ C, double (&s)[2 * E],
                                           double (&s2)[U > 1 ? E : 1], double (&s3)[U > 1 ? E : 1])
@@ -1938,9 +1939,11 @@ __device__ __forceinline__ void sum_units(double *lds, const LdModup<false, 1> &
             if (u == 0) lds_barrier();      // the previous digit's (or unit's) LDS reads
             fwd_row<LOGN, E, false>(lds + u * ROW, x, x, tid, tw, m);
             if (U > 1) fetch(u + 1 < U ? u + 1 : 0, u + 1 < U || j + 1 == dnum ? j : j + 1);
+            int ts = tid;
+            if (AGAIN) asm volatile("" : "+v"(ts));
 #pragma unroll
             for (int it = 0; it < E; it += 2)
-                pair_at(lds + u * ROW, pad(chunk_elem<E>(tid, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
+                pair_at(lds + u * ROW, pad(chunk_elem<E>(ts, it))) = make_double2(red(x[it], m), red(x[it + 1], m));
         }
         lds_barrier();
         int tk = tid;
@@ -1976,7 +1979,7 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         double s[2 * E], s2[U > 1 ? E : 1], s3[U > 1 ? E : 1];
-        sum_units<LOGN, E, U>(lds, ld, T, n_rot, batch, b, r, tid, tw, m, C, s, s2, s3);
+        sum_units<LOGN, E, U, false>(lds, ld, T, n_rot, batch, b, r, tid, tw, m, C, s, s2, s3);
         // both components of a unit
         auto inverse = [&](const double *a, const double *c, int unit) {
             double y[2 * E];
@@ -1999,7 +2002,8 @@ ks_sum_row_kernel(LdModup<false, 1> ld, HoistTab T, int n_rot, int batch, StInvF
 // and the additions follow in registers, c0 permuted through LDS, as in ks_unit_kernel.  The accumulators of the other primes (six rows of
 // eight a ciphertext, written and read again) never reach memory and the mod-down launch, which memory bounds, is gone.  N = 8192, three digits, 7
 // rotations, 1536 ciphertexts: 1723 us with the mod-down, 1568 here and for the special prime (1673 with component 1's words asked for only when
-// component 0 is stored); what follows the transforms takes 24 to 31 us a workgroup, twelve rows' trips from memory.
+// component 0 is stored); what follows the transforms takes 24 to 31 us a workgroup, twelve rows' trips from memory.  A flag that was spilled (is there a
+// rotation at all) had component 1's words waited for before component 0's rotations: 1242 us a launch of 1536 ciphertexts, 1231 since nothing is.
 template <int LOGN, int E>
 __global__ void __launch_bounds__((1 << LOGN) / E, (min_waves<LOGN, E>()))
 ks_sum_down_kernel(LdModup<false, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist H, const double *__restrict__ tw_all,
@@ -2016,7 +2020,7 @@ ks_sum_down_kernel(LdModup<false, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist
         const ModD m = C->mod[r];
         const double *tw = tw_all + ((size_t)r << LOGN), *itw = itw_all + ((size_t)r << LOGN);
         double s[2 * E], s2[E], s3[E];
-        sum_units<LOGN, E, 2>(lds, ld, T, H.n_sum, A.batch, b0, r, tid, tw, m, C, s, s2, s3);
+        sum_units<LOGN, E, 2, true>(lds, ld, T, H.n_sum, A.batch, b0, r, tid, tw, m, C, s, s2, s3);
         auto finish = [&](const double *s0, const double *s1, int b) {
             double y[2 * E], xs[E];
             uint64_t own[E];
@@ -2053,7 +2057,8 @@ ks_sum_down_kernel(LdModup<false, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist
                     for (int it = 0; it < E; it++) lds[tk + it * TH] = u64_to_f64(own[it]);
                     ask(1);     // (component 0's own words are read back from LDS)
                     lds_barrier();
-                    for (int i = 0; i < H.n_sum; i++) {
+                    int i = 0;
+                    do {
                         // terms are canonical up to their sign: four of them between two reductions
                         const uint32_t ginv = H.ginv[i], e0 = (uint32_t)tk * ginv;
 #pragma unroll
@@ -2065,7 +2070,7 @@ ks_sum_down_kernel(LdModup<false, 1> ld, HoistTab T, ModdownArgs A, ModdownHoist
 #pragma unroll
                             for (int it = 0; it < E; it++) v[it] = red(v[it], m);
                         }
-                    }
+                    } while (++i < H.n_sum);
 #pragma unroll
                     for (int it = 0; it < E; it++) v[it] += lds[tk + it * TH];
                 } else {

@@ -8,7 +8,7 @@ import pytest
 
 from paper_2602_08798_amd import binding
 
-FITS = ("mul_row_kernel", "mul_sum_row_kernel", "ks_row_kernel", "ks_sum_row_kernel", "rot_row_kernel", "ks_wide_kernel")
+FITS = ("mul_row_kernel", "mul_sum_row_kernel", "ks_row_kernel", "ks_sum_row_kernel", "rot_row_kernel", "ks_wide_kernel", "ks_sum_down_kernel", "ks_unit_kernel")
 
 
 def _kernels():
