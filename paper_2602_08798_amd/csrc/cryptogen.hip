@@ -743,9 +743,10 @@ static bool ks_sum_ahead_wins(const cg_ctx *c, uint32_t u, size_t blocks, uint32
 }
 // Summed inner products of a series of rotations.  Ciphertexts per thread: as many as leave every
 // compute unit three workgroups and no more than a quarter of the last group's places empty.  us a series with mod-up and mod-down at
-// one / two / four / eight a thread, 7 rotations, N = 8192: 12 ciphertexts 39.1 / 36.2 / 37.9 / 40.5, 24: 58.3 / 52.2 / 49.7 / 53.4, 36: 76.1 / 67.4 / 67.4 / 70.5,
-// 40: 80.9 / 71.9 / 68.1 / 73.4; N = 4096, 24: 28.6 / 27.7 / 28.5 / 30.8, 42: 34.0 / 32.0 / 34.9 / 36.1; N = 16384, 4: 61.9 / 52.4 / 49.0 / 54.3, 12: 144 / 116 / 106 / 109.
-// 3 rotations, N = 8192: 20 37.4 / 35.2 / 36.3 / 38.3, 32: 50.3 / 47.7 / 47.1 / 47.8
+// one / two / four / eight a thread, 7 rotations, N = 8192: 12 ciphertexts 39.4 / 36.4 / 38.1 / 40.6, 24: 58.2 / 52.1 / 49.8 / 53.5, 36: 76.6 / 67.1 / 66.4 / 70.4,
+// 40: 80.7 / 70.3 / 67.7 / 73.5; N = 4096, 24: 28.5 / 28.0 / 28.7 / 30.9, 42: 34.3 / 32.2 / 34.8 / 36.1; N = 16384, 4: 62.1 / 52.3 / 49.1 / 54.2, 12: 145 / 116 / 106 / 108.
+// 3 rotations, N = 8192: 20 37.6 / 35.4 / 36.4 / 38.5, 24 45.2 / 42.8 / 42.6 / 45.3, 32: 50.1 / 46.6 / 46.5 / 47.6, 40: 60.4 / 56.2 / 55.8 / 59.8, but 28 47.3 / 44.7 / 45.0 / 46.0, 36 57.8 / 54.1 /
+// 55.0 / 57.6 and 41 61.8 / 57.6 / 58.3 / 59.4, where two would be better than the rule's four.
 template <int DNUM>
 static int launch_ks_sum_d(cg_ctx *c, hipStream_t s, const uint64_t *dig, const HoistTab &T, uint32_t n_rot, double *acc,
                            uint32_t batch, bool others)
@@ -812,10 +813,11 @@ static bool rounds_pay(const cg_ctx *c, size_t rows, IdleLimits lim)
 }
 
 // Two units to a workgroup of ks_sum_row_kernel at N = 8192, where a round of pairs takes the time of 1.84 rounds of one and there are
-// few enough of them.  us, one unit / two, three digits, 7 rotations: 64 ciphertexts (one round / one) 83 / 116, 107 (two / one)
-// 155 / 139, 128: 166 / 150, 192 (three / two) 246 / 268, 193 (four / two) 295 / 267, 320 (five / three) 404 / 415, 321 (six / three) 450 / 410, 768: 945 / 872;
-// 3 rotations, 128: 131 / 120, 192: 193 / 211, 384: 381 / 352; two digits, 7 rotations, 128: 111 / 100, 256 (three / two) 192 / 205; six, 111: 492 / 430.  At N = 4096,
-// where a compute unit holds two workgroups of one unit, pairs gain nothing: two digits, 7 rotations, 256: 88 / 95, 512: 150 / 150, 1536: 462 / 463.
+// few enough of them.  us, one unit / two, three digits, 7 rotations: 64 ciphertexts (one round / one) 82 / 117, 107 (two / one)
+// 152 / 139, 128: 163 / 151, 192 (three / two) 242 / 267, 193 (four / two) 286 / 266, 320 (five / three) 400 / 412, 321 (six / three) 438 / 410, 768: 932 / 880;
+// 3 rotations, 128: 129 / 120, 192: 191 / 211, 384: 378 / 354; two digits, 7 rotations, 128: 104 / 98, 256 (three / two) 187 / 204; six, 111: 489 / 431.  At N = 4096,
+// where a compute unit holds two workgroups of one unit, pairs gain nothing: two digits, 7 rotations, 256: 88 / 95, 512: 150 / 150, 1536: 462 / 463 (before sums were
+// added up unreduced with one unit, which 256 now takes in 83).
 static bool ks_sum_pairs(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn != 13) return false;
@@ -881,16 +883,16 @@ static bool ks_sum_down_wins(const cg_ctx *c, uint32_t batch, uint32_t n_rot)
     auto rounds = [&](size_t primes) { return (sets * primes + n - 1) / n; };
     return rounds(1) + rounds(c->k) <= rounds(c->L) || (c->dnum <= 3 && n_rot <= 8 && batch >= 4 * n);
 }
-// us with the mod-down and other keys on every call, three launches / one.  N = 8192, three digits, 7 rotations: 36 ciphertexts (112 units idle)
-// 67.2 / 69.1, 40 (96): 68.2 / 69.8, 41 (92): 73.7 / 72.2, 42 (88): 74.5 / 70.3, 64: 102 / 81; 3 rotations, 32 (128): 47.3 / 51.7, 36: 55.7 / 53.1, 42: 61.1 / 55.0;
-// 15 rotations, 42: 102 / 104, 48 (64): 114 / 108.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 42 (130 idle): 33.0 / 33.8, 43 (127): 36.8 / 34.0,
-// 86 (254): 49.6 / 51.3, 107 (191): 55.1 / 53.2.  Three digits, 7 rotations: 33 (124 idle) 40.7 / 42.5, 42 (88): 44.2 / 42.3, 72 (224):
-// 61.6 / 66.1, 84 (176): 66.2 / 67.0, 90 (152): 71.9 / 69.0; six digits: 20 (116) 61.5 / 68.5, 24 (88): 69.6 / 70.6, 26 (74): 79.9 / 70.5.
-// The limits of the second and third round at N = 8192 are older than these figures, which would have them at about 3/4 and 5/8 of the units: 7 rotations, 65
-// (252 idle) 120 / 118, 80 (192): 131 / 123, 96 (128): 152 / 133, 103 (100): 170 / 138, 129 (252) 214 / 219, 150 (168): 241 / 228, 166 (104): 259 / 234; 3 rotations, 80:
-// 106 / 94, 150: 191 / 178; two digits, 7 rotations, 110 (182): 103 / 96, 136 (104): 134 / 103, and in one round 48 (112): 58 / 54.
+// us with the mod-down and other keys on every call, launches of single transforms / one.  N = 8192, three digits, 7 rotations: 32 ciphertexts (128 units idle) 56.5 / 63.9,
+// 36 (112) 67.5 / 65.7, 40 (96): 68.7 / 66.4, 42 (88): 73.9 / 66.7, 64: 102 / 79; 3 rotations, 32: 47.7 / 50.3, 36: 55.9 / 51.8, 42: 60.7 / 53.3;
+// 15 rotations, 36 92 / 96, 42: 101 / 97, 48 (64): 114 / 101.  At N = 4096 a unit holds two workgroups.  Two digits, 7 rotations, 42 (130 idle): 32.2 / 33.4, 43 (127): 36.2 / 33.4,
+// 86 (254): 49.9 / 47.8, 107 (191): 54.9 / 50.1.  Three digits, 7 rotations: 33 (124 idle) 41.0 / 41.5, 42 (88): 44.2 / 41.6, 72 (224):
+// 62.1 / 62.3, 84 (176): 66.6 / 62.6, 90 (152): 71.9 / 65.0; six digits: 20 (116) 61.1 / 66.5, 24 (88): 68.4 / 68.5, 26 (74): 78.3 / 68.8.
+// The limits at N = 8192 are older than these figures, which would have them at 3/7 of the units in one round and 3/4 and more in the second and third: 7 rotations, 65
+// (252 idle) 119 / 118, 80 (192): 131 / 122, 96 (128): 153 / 131, 103 (100): 170 / 136, 129 (252) 215 / 212, 150 (168): 241 / 220, 166 (104): 259 / 227; 3 rotations, 80:
+// 105 / 94, 150: 193 / 173; two digits, 7 rotations, 110 (182): 103 / 95, 136 (104): 132 / 103, and in one round 43 (127) 57.6 / 53.0, 48 (112): 58.4 / 51.8.
 // Pairs of units (ks_sum_pairs), four digits and more: from a quarter more rows than compute units on.  N = 8192, 7 rotations: four
-// digits, 63 ciphertexts (315 rows) 200 / 155, 81 (405): 278 / 169; six, 37 (259): 204 / 209, 45 (315): 241 / 215, 54: 275 / 223.
+// digits, 63 ciphertexts (315 rows) 200 / 154, 81 (405): 278 / 168; six, 37 (259): 202 / 208, 45 (315): 239 / 215, 54: 275 / 222.
 static bool ks_sum_row_wins(const cg_ctx *c, uint32_t batch)
 {
     if (c->logn > 13 || c->alpha != 1) return false;
@@ -969,9 +971,9 @@ static int launch_ks_unit(cg_ctx *c, hipStream_t s, const uint64_t *src, size_t 
 // Whole units are coarse pieces: taken where the last round of workgroups leaves a tenth of the compute units idle at
 // most, from two workgroups per unit on at N = 4096, and where the keys of a prime stay in an XCD's L2, whose
 // workgroups are at different primes.  us by row / by unit with another key on every call.  N = 8192, three digits, rotations:
-// 231 units 181 / 182, 256: 188 / 187, 300: 234 / 344, 450: 372 / 353, 600: 474 / 515, 693: 529 / 525, 768: 580 / 537; 3 summed rotations, 231: 227 / 238, 256: 237 / 245,
-// 461: 446 / 450, 768: 700 / 698; two digits, rotations, 231: 114 / 106, 420: 191 / 204, 461: 218 / 208.  N = 4096, two digits, relinearisation: 420 units 86 / 79,
-// 461: 99 / 84, 768: 154 / 128; rotation, 256: 55 / 67, 461: 106 / 91; 7 summed rotations, 256: 87 / 89, 461: 163 / 138.
+// 231 units 181 / 182, 256: 188 / 187, 300: 234 / 344, 450: 372 / 353, 600: 474 / 515, 693: 529 / 525, 768: 580 / 537; 3 summed rotations, 231: 226 / 213, 256: 237 / 220,
+// 693 668 / 611, 768: 700 / 633, but with the mod-down in the kernel that sums (ks_sum_down_wins) 461: 369 / 406, 512 389 / 425, which the rule does not look at; two digits, rotations, 231: 114 / 106, 420: 191 / 204, 461: 218 / 208.  N = 4096, two digits, relinearisation: 420 units 86 / 79,
+// 461: 99 / 84, 768: 154 / 128; rotation, 256: 55 / 67, 461: 106 / 91; 7 summed rotations, 256: 83 / 93, 461: 159 / 144.
 // Relinearisations of three digits at N = 8192 go by unit in the second round, and from the third on with a sixteenth idle at most.  That line is older than the
 // kernel, which has since transformed both sums back together and gains wherever the rule for the others holds: 231 units 163 / 151,
 // 256: 171 / 160, 420 (which that leaves out) 313 / 292, 461: 353 / 298, 512: 372 / 311, 693: 501 / 439, 720: 532 / 446, 768: 553 / 459; two digits, 231: 104 / 93, 461: 215 / 184.
