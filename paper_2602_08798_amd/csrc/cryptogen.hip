@@ -2062,7 +2062,7 @@ static int fold_chain(cg_ctx *c, hipStream_t s, uint64_t *x0, uint64_t *x1, uint
 //   4 110 / 113, 5 117 / 123; steps of 4 bits 3 x 2 (d2 = 32) 169 / 168, 4 x 1 158 / 165, 4 x 2 174 / 183, 5 x 1 166 / 183, (d2 = 64) 159 / 177.
 // - A step's context at N = 8192 only beside scores whose mod-ups have rows for 3/8 of the units: 4 x 2 181 / 176, 190 / 187, 4 x 4 221 / 220, 224 / 228, 5 x 4 254 / 259, 257 / 260; beside
 //   longer scores for a quarter: d2 = 128, 5 x 1 179 / 168, 4 x 2 182 / 189, 2 x 4 (2 bits) 193 / 199.
-// - N = 4096: both branches' mod-ups have rows for 7/8 of the units.  1 x 2 161 / 147, 10 x 1 174 / 156, 16 x 1 167 / 154, 163 / 153, 12 x 2 169 / 164, 151 / 154; beyond 20 x 1 140 / 148,
+// - N = 4096: both branches' mod-ups have rows for 7/8 of the units.  1 x 2 161 / 147, 10 x 1 174 / 156, 16 x 1 167 / 154, 163 / 153, 12 x 2 169 / 164, 151 / 154, 18 x 1 161 / 149, 148 / 155; beyond 20 x 1 140 / 148,
 //   151 / 165, 10 x 3 147 / 151, 155 / 161, 16 x 2 154 / 161, 157 / 163 (on a host that launches more slowly 161 / 150, 165 / 158, 162 / 162).
 static bool fold_joined_wins(const cg_ctx *c, uint32_t batch, const FoldRounds &R, const Beside &beside)
 {
